@@ -332,6 +332,41 @@ int32_t varco_accumulate_returned(varco_ctx* ctx, int32_t layer, int32_t p, cons
                                   const int32_t* ret_src, const void* returned, void* dx_local,
                                   varco_stream stream);
 
+/* ------------------------------------------------------------------------------------------------
+ * All partitions of one device at once. When every partition of the graph is registered in one context, the calls below
+ * run Algorithm 1's passes over all of them with one launch per kernel instead of one per partition, kernel and layer;
+ * results are those of the per-partition calls in turn (sums over partitions and consumers in another order).
+ *
+ * varco_link_partitions joins the registered partitions (set-up call: allocates, synchronises; again after a partition
+ * was registered again). The partitions' local rows form one arena of n_total rows, partition 0's first; compressed and
+ * returned rows are numbered by z_row_offset and halo_row_offset, which must be consecutive over the partitions, and
+ * every partition must have its map of returned rows. VARCO_ERR_UNSUPPORTED when the partitions have 2^31 or more
+ * entries together (the per-partition calls have no such limit), VARCO_ERR_SHAPE when the maps do not fit.
+ *
+ * The errors that the consumers of a node hand back (k elements per entry of a halo column) are summed for all consumers
+ * at once and added to the owner's row; they are not summed per consumer first, so dz_halo is used only by layers that
+ * transform first. The exchange counters count the same volume as in the per-partition calls. */
+typedef struct {
+    void* x[VARCO_MAX_LAYERS + 1];       /* n_total x width[l]; x[0] given, the rest written by forward */
+    void* z[VARCO_MAX_LAYERS];           /* compressed boundary rows of x[l], all partitions: written by forward */
+    void* m[VARCO_MAX_LAYERS];           /* n_total x width[l]: aggregates saved by forward for backward */
+    const void* h1[VARCO_MAX_LAYERS];    /* weights, fp32 */
+    const void* h0[VARCO_MAX_LAYERS];    /* self-tap weights (SAGE), else ignored */
+    void* dh1[VARCO_MAX_LAYERS];         /* fp32, accumulated into */
+    void* dh0[VARCO_MAX_LAYERS];
+    void* dx[VARCO_MAX_LAYERS + 1];      /* n_total x width[l]; dx[L] given, dx[1..L-1] written by backward, dx[0] not used */
+    void* dz_halo[VARCO_MAX_LAYERS];     /* all partitions' returned rows, for layers that transform first (else may be NULL) */
+} varco_network_buffers;
+int32_t varco_link_partitions(varco_ctx* ctx);
+/* Compresses x[0]'s boundary rows and runs every layer forward; layers in order, each as varco_layer_fwd. */
+int32_t varco_network_forward(varco_ctx* ctx, const varco_network_buffers* b, varco_stream stream);
+/* Every layer backward, last first, each as varco_layer_bwd on all partitions and varco_accumulate_returned. */
+int32_t varco_network_backward(varco_ctx* ctx, const varco_network_buffers* b, varco_stream stream);
+/* varco_compress of the boundary rows, varco_aggregate_fwd, and varco_aggregate_bwd with the owner-side sums, on arenas. */
+int32_t varco_network_compress(varco_ctx* ctx, int32_t tap, const void* x, void* z, varco_stream stream);
+int32_t varco_network_aggregate_fwd(varco_ctx* ctx, int32_t tap, const void* y, const void* z_in, void* y_out, varco_stream stream);
+int32_t varco_network_aggregate_bwd(varco_ctx* ctx, int32_t tap, const void* g_out, void* g_in, varco_stream stream);
+
 int32_t varco_get_stats(const varco_ctx* ctx, varco_stats* out);
 int32_t varco_reset_stats(varco_ctx* ctx);
 

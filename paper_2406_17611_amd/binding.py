@@ -32,6 +32,8 @@ EXPORTS = [
     "varco_step_table_enable", "varco_set_step", "varco_advance_step",
     "varco_aggregate_fwd", "varco_aggregate_bwd", "varco_transform_fwd", "varco_transform_bwd_weight",
     "varco_transform_bwd_input", "varco_transform_bwd_weight_static",
+    "varco_link_partitions", "varco_network_forward", "varco_network_backward", "varco_network_compress",
+    "varco_network_aggregate_fwd", "varco_network_aggregate_bwd",
 ]
 KERNEL_CLASSES = ["compress", "decompress", "agg_fwd", "gemm_fwd", "gemm_wgrad", "gemm_dgrad", "agg_bwd_local",
                   "agg_bwd_halo", "reduce", "agg_bwd_halo_sum"]
@@ -63,6 +65,13 @@ class Stats(C.Structure):
 class Profile(C.Structure):
     _fields_ = [("launches", C.c_int64 * 10), ("ms", C.c_double * 10), ("bytes", C.c_double * 10),
                 ("flops", C.c_double * 10), ("stream_bytes", C.c_double * 10)]
+
+
+class NetworkBuffers(C.Structure):
+    """varco_network_buffers: device addresses of the arenas of a whole network."""
+    _fields_ = [("x", C.c_void_p * (MAX_LAYERS + 1)), ("z", C.c_void_p * MAX_LAYERS), ("m", C.c_void_p * MAX_LAYERS),
+                ("h1", C.c_void_p * MAX_LAYERS), ("h0", C.c_void_p * MAX_LAYERS), ("dh1", C.c_void_p * MAX_LAYERS),
+                ("dh0", C.c_void_p * MAX_LAYERS), ("dx", C.c_void_p * (MAX_LAYERS + 1)), ("dz_halo", C.c_void_p * MAX_LAYERS)]
 
 
 class VarcoError(RuntimeError):
@@ -118,6 +127,12 @@ def lib() -> C.CDLL:
         L.varco_transform_bwd_weight.argtypes = [vp, i32, i64, vp, vp, vp, vp, vp]
         L.varco_transform_bwd_input.argtypes = [vp, i32, i64, vp, vp, vp, vp, i32, vp]
         L.varco_transform_bwd_weight_static.argtypes = [vp, i32, i64, vp, vp, vp, vp, vp]
+        L.varco_link_partitions.argtypes = [vp]
+        L.varco_network_forward.argtypes = [vp, C.POINTER(NetworkBuffers), vp]
+        L.varco_network_backward.argtypes = [vp, C.POINTER(NetworkBuffers), vp]
+        L.varco_network_compress.argtypes = [vp, i32, vp, vp, vp]
+        L.varco_network_aggregate_fwd.argtypes = [vp, i32, vp, vp, vp, vp]
+        L.varco_network_aggregate_bwd.argtypes = [vp, i32, vp, vp, vp]
         L.varco_profile_enable.argtypes = [vp, i32]
         L.varco_profile_read.argtypes = [vp, C.POINTER(Profile), i32]
         for name in EXPORTS:
@@ -361,6 +376,29 @@ class Context:
     def transform_bwd_input(self, layer, dx_out, x_out, h, g_out, accumulate, stream=None):
         _check(lib().varco_transform_bwd_input(self._h, layer, dx_out.shape[0], _ptr(dx_out), _ptr(x_out), _ptr(h),
                                                _ptr(g_out), int(accumulate), _stream(stream)), self._h)
+
+    def link_partitions(self):
+        """Joins all registered partitions for the network_* calls; False when they are too large for that (2^31 entries)."""
+        code = lib().varco_link_partitions(self._h)
+        if code == ERR_UNSUPPORTED:
+            return False
+        _check(code, self._h)
+        return True
+
+    def network_forward(self, buffers, stream=None):
+        _check(lib().varco_network_forward(self._h, C.byref(buffers), _stream(stream)), self._h)
+
+    def network_backward(self, buffers, stream=None):
+        _check(lib().varco_network_backward(self._h, C.byref(buffers), _stream(stream)), self._h)
+
+    def network_compress(self, tap, x, z, stream=None):
+        _check(lib().varco_network_compress(self._h, tap, _ptr(x), _ptr(z), _stream(stream)), self._h)
+
+    def network_aggregate_fwd(self, tap, y, z_in, y_out, stream=None):
+        _check(lib().varco_network_aggregate_fwd(self._h, tap, _ptr(y), _ptr(z_in), _ptr(y_out), _stream(stream)), self._h)
+
+    def network_aggregate_bwd(self, tap, g_out, g_in, stream=None):
+        _check(lib().varco_network_aggregate_bwd(self._h, tap, _ptr(g_out), _ptr(g_in), _stream(stream)), self._h)
 
     def softmax_xent(self, logits, labels, n_classes, scale, dlogits, row_loss, row_correct, totals, stream=None):
         n_rows = logits.shape[0]

@@ -998,24 +998,18 @@ hipError_t spmm_short_t(const SpmmPlan& plan, const int32_t* colidx, const float
     return hipGetLastError();
 }
 
+// First pass: see halo_products_kernel.
 template <typename T>
-hipError_t halo_grad_t(const SpmmPlan& fwd_plan, const SpmmPlan& t_halo_plan, const VarcoEdge* edge, const float* vals,
-                       const int32_t* prow, int32_t prod_base, const void* dm, const MaskRule& rule, void* prod_v,
-                       void* out_v, int32_t row_base, float* partial, hipStream_t stream, const LaunchTag& tag,
-                       const LaunchTag& sum_tag) {
-    T* out = static_cast<T*>(out_v);
+hipError_t halo_products_t(const SpmmPlan& fwd_plan, const VarcoEdge* edge, const float* vals, const int32_t* prow, const void* dm,
+                           const MaskRule& rule, void* prod_v, hipStream_t stream, const LaunchTag& tag) {
     T* prod = static_cast<T*>(prod_v);
     const int32_t width = int32_t(rule.width);
     int ev = 1;
     for (int c : {4, 2})
-        if (rule.k % c == 0 && aligned_to(prod, c * sizeof(T)) && aligned_to(out, c * sizeof(T)) && aligned_to(partial, 4 * c)) {
+        if (rule.k % c == 0 && aligned_to(prod, c * sizeof(T))) {
             ev = c;
             break;
         }
-    const int ku = int(rule.k) / ev;
-    int lpe_log2 = 0;
-    while ((1 << lpe_log2) < ku && lpe_log2 < 6) ++lpe_log2;
-
     ProductArgs<T> a;
     a.items = fwd_plan.items;
     a.n_items = fwd_plan.n_items;
@@ -1025,14 +1019,34 @@ hipError_t halo_grad_t(const SpmmPlan& fwd_plan, const SpmmPlan& t_halo_plan, co
     a.dm = static_cast<const T*>(dm);
     a.rule = rule;
     a.prod = prod;
-    a.ev = ev, a.ku = ku, a.lpe_log2 = lpe_log2;
+    a.ev = ev, a.ku = int(rule.k) / ev, a.lpe_log2 = 0;
+    while ((1 << a.lpe_log2) < a.ku && a.lpe_log2 < 6) ++a.lpe_log2;
     const size_t lds_bytes = size_t(kWaves) * width * sizeof(float) + size_t(rule.n_units) * sizeof(uint16_t);
     tag.begin(stream);
     hipLaunchKernelGGL(halo_products_kernel<T>, dim3((fwd_plan.n_items + kWaves - 1) / kWaves), dim3(kBlock), lds_bytes,
                        stream, a);
     tag.end(stream);
-    hipError_t err = hipGetLastError();
+    return hipGetLastError();
+}
+
+template <typename T>
+hipError_t halo_grad_t(const SpmmPlan& fwd_plan, const SpmmPlan& t_halo_plan, const VarcoEdge* edge, const float* vals,
+                       const int32_t* prow, int32_t prod_base, const void* dm, const MaskRule& rule, void* prod_v,
+                       void* out_v, int32_t row_base, float* partial, hipStream_t stream, const LaunchTag& tag,
+                       const LaunchTag& sum_tag) {
+    hipError_t err = halo_products_t<T>(fwd_plan, edge, vals, prow, dm, rule, prod_v, stream, tag);
     if (err != hipSuccess) return err;
+    T* out = static_cast<T*>(out_v);
+    T* prod = static_cast<T*>(prod_v);
+    int ev = 1;
+    for (int c : {4, 2})
+        if (rule.k % c == 0 && aligned_to(prod, c * sizeof(T)) && aligned_to(out, c * sizeof(T)) && aligned_to(partial, 4 * c)) {
+            ev = c;
+            break;
+        }
+    const int ku = int(rule.k) / ev;
+    int lpe_log2 = 0;
+    while ((1 << lpe_log2) < ku && lpe_log2 < 6) ++lpe_log2;
     SegsumArgs<T> b;
     b.items = t_halo_plan.items;
     b.n_items = t_halo_plan.n_items;
@@ -1122,6 +1136,13 @@ hipError_t varco_launch_build_prow(const int32_t* rowptr, const int32_t* colidx,
     hipLaunchKernelGGL(build_prow_kernel, dim3(unsigned((n_local + kBlock - 1) / kBlock)), dim3(kBlock), 0, stream, rowptr,
                        colidx, n_local, t_rowptr, t_colidx, prow);
     return hipGetLastError();
+}
+
+hipError_t varco_launch_halo_products(int dtype, const SpmmPlan& fwd_plan, const VarcoEdge* edge, const float* vals, const int32_t* prow,
+                                      const void* dm, const MaskRule& rule, void* prod, hipStream_t stream, const LaunchTag& tag) {
+    if (fwd_plan.n_items == 0) return hipSuccess;
+    return dtype == VARCO_BF16 ? halo_products_t<bf16_t>(fwd_plan, edge, vals, prow, dm, rule, prod, stream, tag)
+                               : halo_products_t<float>(fwd_plan, edge, vals, prow, dm, rule, prod, stream, tag);
 }
 
 hipError_t varco_launch_halo_grad(int dtype, const SpmmPlan& fwd_plan, const SpmmPlan& t_halo_plan, const VarcoEdge* edge,

@@ -10,7 +10,9 @@
 #include <string>
 #include <vector>
 
-#include "varco_internal.h"
+#include "varco_context.h"
+
+using namespace varco;
 
 namespace {
 
@@ -20,51 +22,6 @@ namespace {
 // chain. Measured on the two large configurations: 256 / 256 -> 128 / 32 is 126.1 -> 114.9 ms (bf16) and
 // 65.3 -> 64.8 ms (fp32) per step; 64 / 32 loses again to the extra partial rows.
 constexpr int32_t kSpmmChunk = 128, kSpmmChunkDense = 32;
-
-struct LayerState {
-    uint32_t num = 1, den = 1;
-    int32_t k = 0;
-    int32_t n_units = 0;
-    std::vector<uint16_t> h_units, h_units_inv;   // host copies; uploaded on first device use
-    uint16_t* units = nullptr;       // device
-    uint16_t* units_inv = nullptr;   // device
-    bool ran_forward = false;        // in the current step
-    int32_t order = VARCO_ORDER_AGGREGATE_FIRST;
-};
-
-struct PartState {
-    bool registered = false;
-    varco_partition_desc d{};
-    SpmmPlan fwd, t_local, t_halo;
-    VarcoEdge* edges = nullptr;      // device [nnz]: per-entry {source row, node id}
-    int32_t* prow = nullptr;         // device [nnz]: per-entry row of the halo-gradient product buffer
-    int32_t* boundary_gid = nullptr; // device [n_boundary]
-    int64_t nnz_t_local = 0;         // transposed entries whose row is a local node
-    int64_t z_rows = 0;              // 1 + the largest row of the compressed buffer a halo entry refers to
-    int64_t n_returned = 0;          // rows of the registered owner-side map (d.ret_ptr / d.ret_src), 0 without one
-};
-
-// Device scratch of the layer calls. Calls issued on different streams may run concurrently, so every
-// stream that calls into a context gets a set of its own (up to kMaxStreams), sized from what the
-// registered partitions need.
-struct Workspace {
-    hipStream_t stream = nullptr;
-    bool used = false;
-    float* dm = nullptr;        size_t dm_elems = 0;        // dM: n_local x width (elements of the storage type)
-    float* spmm = nullptr;      size_t spmm_elems = 0;      // partial rows of split CSR rows
-    float* gemm = nullptr;      size_t gemm_elems = 0;      // split-K partial products
-    float* prod = nullptr;      size_t prod_elems = 0;      // halo-gradient products: (halo entries) x k elements
-    float* w = nullptr;         size_t w_elems = 0;         // converted copies of the weights, one slot per (layer, weight, orientation)
-    float* tf = nullptr;        size_t tf_elems = 0;        // transform-first layers: [Y_loc ; Y_halo], (n_local + n_halo) x width[l+1]
-    float* hrows = nullptr;     size_t hrows_elems = 0;     // and one record (two words) per halo row
-    struct WeightTag {          // what a slot holds: made from `h` during step epoch `epoch` in the form `terms`
-        const void* h = nullptr;
-        uint64_t epoch = 0;
-        int32_t terms = -1;
-    };
-    std::vector<WeightTag> w_tags;
-};
-constexpr int kMaxStreams = 8;
 
 std::mutex g_err_mutex;
 std::string g_global_error;
@@ -98,35 +55,6 @@ hipError_t scratch_of_current_device(float** out) {
 
 }  // namespace
 
-struct varco_ctx {
-    int32_t n_layers = 0, n_parts = 0, conv = 0, dtype = 0;
-    int32_t f32_terms = 3;           // fp32 storage: bf16 terms per operand on the matrix cores (0: fp32 instructions)
-    uint64_t weight_epoch = 1;       // converted weight copies are reused within an epoch (= a step)
-    std::vector<size_t> w_slot;      // offset (bf16 elements) of every slot in a workspace's weight buffer, and the total
-    uint64_t key = 0, step = 0;
-    std::vector<int32_t> widths, act;
-    std::vector<LayerState> layers;
-    std::vector<PartState> parts;
-    uint64_t* d_step = nullptr;      // device-resident step state (varco_step_table_enable), or null
-    uint32_t* d_table = nullptr;     // its key words: 2 per tap address
-    Workspace ws[kMaxStreams];
-    size_t need_dm = 0, need_spmm = 0, need_gemm = 0, need_w = 0;   // what the registered partitions ask for
-    int32_t* d_flags = nullptr;      // device word the index checks of a registration report into
-    varco_stats stats{};
-    VarcoProfiler prof;
-    double prof_ms[VARCO_K_COUNT] = {}, prof_bytes[VARCO_K_COUNT] = {}, prof_flops[VARCO_K_COUNT] = {};
-    double prof_stream_bytes[VARCO_K_COUNT] = {};
-    int64_t prof_launches[VARCO_K_COUNT] = {};
-    mutable std::string error;
-    double elem_bytes() const { return dtype == VARCO_BF16 ? 2.0 : 4.0; }
-    LaunchTag tag(int cls, double bytes, double flops, double stream_bytes = -1.0) {
-        LaunchTag t;
-        t.prof = prof.on ? &prof : nullptr;
-        t.cls = cls, t.bytes = bytes, t.flops = flops, t.stream_bytes = stream_bytes;
-        return t;
-    }
-};
-
 int32_t varco_fail(const varco_ctx* ctx, int32_t code, const char* msg) {
     if (ctx) {
         ctx->error = msg;
@@ -137,18 +65,12 @@ int32_t varco_fail(const varco_ctx* ctx, int32_t code, const char* msg) {
     return code;
 }
 
-namespace {
+namespace varco {
 
 int32_t hip_fail(const varco_ctx* ctx, hipError_t e, const char* what) {
     std::string m = std::string(what) + ": " + hipGetErrorString(e);
     return varco_fail(ctx, VARCO_ERR_HIP, m.c_str());
 }
-
-#define VARCO_HIP(ctx, call)                                   \
-    do {                                                       \
-        hipError_t e_ = (call);                                \
-        if (e_ != hipSuccess) return hip_fail(ctx, e_, #call); \
-    } while (0)
 
 uint64_t mix64(uint64_t x) {   // splitmix64 output function
     x ^= x >> 30;
@@ -161,7 +83,7 @@ uint64_t mix64(uint64_t x) {   // splitmix64 output function
 
 // hop > 0: the exchange before the hop-th application of the shift operator inside a K-tap layer draws
 // positions of its own (as if it were layer index layer + 16 * hop).
-MaskRule make_rule(const varco_ctx* ctx, int32_t layer, int32_t hop = 0) {
+MaskRule make_rule(const varco_ctx* ctx, int32_t layer, int32_t hop) {
     const LayerState& ls = ctx->layers[layer];
     const uint64_t inner = mix64(ctx->step + 0x9E3779B97F4A7C15ull * uint64_t(layer + VARCO_MAX_LAYERS * hop + 1));
     const uint64_t s = mix64(ctx->key ^ inner);
@@ -178,7 +100,6 @@ MaskRule make_rule(const varco_ctx* ctx, int32_t layer, int32_t hop = 0) {
     return r;
 }
 
-// A rule that keeps every element of `width`-wide rows (used for purely dense aggregations).
 MaskRule full_rule(int32_t width) {
     MaskRule r{};
     r.width = uint32_t(width);
@@ -209,6 +130,15 @@ void free_part(PartState& ps) {
     if (ps.prow) (void)hipFree(ps.prow);
     if (ps.boundary_gid) (void)hipFree(ps.boundary_gid);
     ps = PartState{};
+}
+
+void free_network(NetState& net) {
+    free_plan(net.fwd);
+    for (void* p : {static_cast<void*>(net.edges), static_cast<void*>(net.arow), static_cast<void*>(net.vals), static_cast<void*>(net.prow),
+                    static_cast<void*>(net.t_local), static_cast<void*>(net.t_cross), static_cast<void*>(net.nodes.nodes),
+                    static_cast<void*>(net.nodes.pieces), static_cast<void*>(net.brow), static_cast<void*>(net.bgid)})
+        if (p) (void)hipFree(p);
+    net = NetState{};
 }
 
 // Work list for rows [r0, r1) of a CSR given its host row pointers: long rows first (split into chunks
@@ -271,7 +201,6 @@ hipError_t grow(float*& buf, size_t& have, size_t want) {
 // compute unit, 256 compute units), so that no partly filled second round is left over.
 // (The bf16 kernel has 256-row tiles, the kernel on expanded fp32 operands 128-row tiles; both take 32
 // reduction steps per tile and have two resident workgroups per unit.)
-enum GemmKind { kGemmF32 = 0, kGemmBf16 = 1, kGemmExpanded = 2 };
 int32_t gemm_split_for(int32_t m, int32_t n, int64_t k, int kind) {
     const int64_t bm = kind == kGemmBf16 || (kind == kGemmF32 && n <= 64) ? 256 : 128, bn = n <= 64 ? 64 : 128;
     const int64_t tiles = ((m + bm - 1) / bm) * ((n + bn - 1) / bn);
@@ -363,6 +292,14 @@ int32_t size_workspace(varco_ctx* ctx, Workspace& ws) {
     VARCO_HIP(ctx, grow(ws.w, ws.w_elems, ctx->need_w));
     const size_t prod = prod_need(ctx);
     if (prod > ws.prod_elems) VARCO_HIP(ctx, grow(ws.prod, ws.prod_elems, prod + prod / 4));   // head-room: schedules raise k step by step
+    // the block's product buffer is an option (without it whole rows are gathered): a device that has no room for it goes on without
+    if (ctx->net.linked) {
+        const size_t want = network_prod_need(ctx);
+        if (want > ws.prod_elems && grow(ws.prod, ws.prod_elems, want) != hipSuccess) {
+            (void)hipGetLastError();
+            if (prod > ws.prod_elems) VARCO_HIP(ctx, grow(ws.prod, ws.prod_elems, prod + prod / 4));
+        }
+    }
     size_t tf_rows = 0, tf_records = 0;
     transform_first_need(ctx, &tf_rows, &tf_records);
     VARCO_HIP(ctx, grow(ws.tf, ws.tf_elems, tf_rows));
@@ -440,7 +377,7 @@ int32_t check_wide_rows(const varco_ctx* ctx, int32_t width, std::initializer_li
     return VARCO_OK;
 }
 
-}  // namespace
+}  // namespace varco
 
 extern "C" const char* varco_last_error(const varco_ctx* ctx) {
     if (ctx) return ctx->error.c_str();
@@ -529,6 +466,7 @@ extern "C" int32_t varco_destroy(varco_ctx* ctx) {
         if (ls.units_inv) (void)hipFree(ls.units_inv);
     }
     for (PartState& ps : ctx->parts) free_part(ps);
+    free_network(ctx->net);
     for (Workspace& w : ctx->ws)
         for (float* p : {w.dm, w.spmm, w.gemm, w.prod, w.w, w.tf, w.hrows})
             if (p) (void)hipFree(p);
@@ -567,6 +505,7 @@ extern "C" int32_t varco_register_partition(varco_ctx* ctx, int32_t q, const var
     if (int32_t rc = ensure_tables(ctx)) return rc;
     PartState& ps = ctx->parts[q];
     free_part(ps);
+    free_network(ctx->net);                 // a block that held the previous partition is no longer valid
     ps.d = *dev;
     const int32_t nl = dev->n_local, nh = dev->n_halo, nb = dev->n_boundary;
 
@@ -613,6 +552,7 @@ extern "C" int32_t varco_register_partition(varco_ctx* ctx, int32_t q, const var
         }
     }
     ps.nnz_t_local = t_rowptr[nl];
+    ps.t_local_ptr.assign(t_rowptr.begin(), t_rowptr.begin() + nl + 1);
     VARCO_HIP(ctx, build_plan(rowptr, 0, nl, ps.fwd, kSpmmChunk));
     // transposed local block: with fewer than three entries per row on average (fine partitions keep few
     // entries local) its short rows are taken four to a wavefront

@@ -106,6 +106,23 @@ struct VarcoEdge {
     int32_t src, gid;
 };
 
+// Backward aggregation seen from the nodes of all partitions at once: node row `row` of the arena receives
+//   sum of its local entries [l0, l1) (dense rows of dM) + its kept positions of the sum of its cross entries [c0, c1),
+// both ranges in node order. When a range is longer than a wavefront should take, it is cut into pieces whose partial
+// sums lie in slots [l0, l1) / [c0, c1) of the partial buffer instead (flags).
+struct NodeItem {
+    int32_t row;
+    uint32_t gid;
+    int32_t l0, l1, c0, c1;
+    int32_t flags, pad;
+};
+enum { VARCO_NODE_LOCAL_SPLIT = 1, VARCO_NODE_CROSS_SPLIT = 2 };
+struct NodePlan {
+    int32_t n_nodes = 0, n_pieces = 0;     // pieces: row = 0 for a local range, 1 for a cross range; dst = its slot
+    NodeItem* nodes = nullptr;             // device
+    SpmmItem* pieces = nullptr;            // device
+};
+
 // `dtype` (VARCO_F32 / VARCO_BF16) is the storage type of every activation, message and gradient buffer
 // passed as void*; sums are formed in fp32 and rounded to nearest even on store.
 hipError_t varco_launch_compress(int dtype, const MaskRule& rule, const int32_t* gids, const int32_t* rows, int64_t n_rows,
@@ -136,7 +153,8 @@ hipError_t varco_launch_step_table(uint64_t* d_step, uint32_t* table, uint64_t k
 // of each kind.
 enum {
     VARCO_BAD_COLUMN_RANGE = 1, VARCO_BAD_COLUMN_ORDER = 2, VARCO_BAD_TROW_RANGE = 4, VARCO_BAD_TROW_ORDER = 8,
-    VARCO_BAD_TRANSPOSE = 16, VARCO_BAD_ID = 32, VARCO_BAD_BOUNDARY = 64, VARCO_BAD_RETURN_MAP = 128
+    VARCO_BAD_TRANSPOSE = 16, VARCO_BAD_ID = 32, VARCO_BAD_BOUNDARY = 64, VARCO_BAD_RETURN_MAP = 128,
+    VARCO_BAD_LINK = 256
 };
 hipError_t varco_launch_validate_partition(const varco_partition_desc& d, int32_t* flags, hipStream_t stream);
 
@@ -164,6 +182,36 @@ hipError_t varco_launch_halo_grad(int dtype, const SpmmPlan& fwd_plan, const Spm
                                   const float* vals, const int32_t* prow, int32_t prod_base, const void* dm,
                                   const MaskRule& rule, void* prod, void* out, int32_t row_base, float* partial,
                                   hipStream_t stream, const LaunchTag& tag, const LaunchTag& sum_tag);
+
+// First pass of the product form: prod[prow[e], j] = vals[e] * dm[row of e, pi_v(j)], j < k, for the halo entries of `fwd_plan`.
+hipError_t varco_launch_halo_products(int dtype, const SpmmPlan& fwd_plan, const VarcoEdge* edge, const float* vals, const int32_t* prow,
+                                      const void* dm, const MaskRule& rule, void* prod, hipStream_t stream, const LaunchTag& tag);
+
+// How the cross entries of varco_launch_node_sum are taken: not at all (k = 0); summed from the product buffer (prod[c, j],
+// already weighted); gathered as whole rows of dm and kept only at the node's positions; gathered as whole rows (k = width).
+enum VarcoCross { kCrossNone = 0, kCrossProducts = 1, kCrossMasked = 2, kCrossFull = 3 };
+// out[row, :] (+)= sum of local entries + cross entries for every node of the plan (see NodeItem). partial: one
+// width-float row per piece.
+hipError_t varco_launch_node_sum(int dtype, const NodePlan& plan, const uint2* t_local, const uint2* t_cross, const void* dm,
+                                 const void* prod, const MaskRule& rule, VarcoCross cross, void* out, bool add_old, float* partial,
+                                 hipStream_t stream, const LaunchTag& tag);
+
+// Set-up kernels of the network block (kernels_network.hip); *flags collects VARCO_BAD_* bits.
+struct LinkPartition {           // one partition inside the block
+    varco_partition_desc d;
+    int64_t row_off, ent_off, local_off;
+};
+hipError_t varco_launch_link_edges(const LinkPartition& p, const int32_t* prow_part, const int32_t* owner_row, const int32_t* prod_start,
+                                   VarcoEdge* edges, int32_t* arow, float* vals, int32_t* prow, hipStream_t stream);
+hipError_t varco_launch_link_halo(const LinkPartition& p, int32_t* halo_len, int32_t* halo_gid, int32_t* halo_zrow, hipStream_t stream);
+hipError_t varco_launch_link_owner(const LinkPartition& p, int64_t halo_total, const int32_t* halo_len, const int32_t* halo_gid,
+                                   const int32_t* halo_zrow, int32_t* owner_row, int32_t* cross_len, int32_t* brow, int32_t* bgid,
+                                   int32_t* flags, hipStream_t stream);
+hipError_t varco_launch_link_starts(const LinkPartition& p, const int32_t* halo_len, const int32_t* cross_ptr, int32_t* prod_start,
+                                    hipStream_t stream);
+hipError_t varco_launch_link_transposed(const LinkPartition& p, const int32_t* prod_start, uint2* t_local, uint2* t_cross, hipStream_t stream);
+hipError_t varco_launch_link_items(const SpmmPlan& part, int32_t row_off, int32_t ent_off, int32_t slot_off, int32_t item_off,
+                                   int32_t split_off, const SpmmPlan& out, hipStream_t stream);
 
 // C (+)= op(A) op(B) in fp32 on the matrix cores, row-major everywhere.
 struct GemmOperand {

@@ -1,0 +1,424 @@
+// The calls that serve all partitions of one device at once: the layers of Algorithm 1 with every kernel launched once
+// for all partitions instead of once per partition. The arithmetic is that of varco_layer_fwd / varco_layer_bwd /
+// varco_accumulate_returned; the partitions' rows lie one after the other in one arena (partition 0 first), the dense
+// products run over the arena, and the exchange goes through the same compressed buffer.
+#include <algorithm>
+#include <cstring>
+#include <string>
+#include <vector>
+
+#include "varco_context.h"
+
+using namespace varco;
+
+namespace {
+
+// Longest range of local / cross entries that one wavefront of the node sums takes; longer ones (hub nodes) are cut.
+constexpr int32_t kNodeLocal = 64, kNodeCross = 128;
+// Largest product buffer (bytes); beyond it the masked form is used, which needs none.
+constexpr double kProdBytes = 48.0 * (1ull << 30);
+
+// Products of k values per cross entry are written and read back (2 k elements at about 4.8 TB/s), or whole rows are
+// gathered (width elements at about 7 TB/s).
+bool products_pay(const varco_ctx* ctx, int32_t layer) {
+    const int64_t k = ctx->layers[layer].k, width = ctx->widths[layer];
+    return k > 0 && 3 * k < width && double(ctx->net.nnz_cross) * double(k) * ctx->elem_bytes() <= kProdBytes;
+}
+size_t prod_floats(const varco_ctx* ctx, int32_t layer) {
+    return (size_t(ctx->net.nnz_cross) * size_t(ctx->layers[layer].k) * size_t(ctx->elem_bytes()) + 3) / 4;
+}
+
+template <typename P>
+hipError_t alloc(P*& p, size_t n) {
+    return n ? hipMalloc(reinterpret_cast<void**>(&p), n * sizeof(P)) : hipSuccess;
+}
+
+struct Temp {                     // device memory of the set-up, given back on every path
+    void* p = nullptr;
+    ~Temp() {
+        if (p) (void)hipFree(p);
+    }
+    hipError_t make(size_t bytes) { return bytes ? hipMalloc(&p, bytes) : hipSuccess; }
+    int32_t* i32() const { return static_cast<int32_t*>(p); }
+};
+
+int32_t link_impl(varco_ctx* ctx) {
+    NetState& net = ctx->net;
+    const int32_t P = ctx->n_parts;
+    std::vector<LinkPartition> lp(P);
+    net.row_off.assign(P + 1, 0), net.halo_off.assign(P + 1, 0);
+    int64_t ent = 0, local = 0, items = 0, splits = 0, slots = 0, returned = 0;
+    for (int32_t q = 0; q < P; ++q) {
+        const PartState& ps = ctx->parts[q];
+        if (!ps.registered) return varco_fail(ctx, VARCO_ERR_STATE, "varco_link_partitions: every partition must be registered first");
+        lp[q].d = ps.d;
+        lp[q].row_off = net.row_off[q], lp[q].ent_off = ent, lp[q].local_off = local;
+        if (ps.d.z_row_offset != net.boundary || ps.d.halo_row_offset != net.halo_off[q])
+            return varco_fail(ctx, VARCO_ERR_SHAPE, "varco_link_partitions: the partitions' boundary or halo rows do not follow one another");
+        if (ps.d.n_boundary > 0 && !ps.d.ret_ptr)
+            return varco_fail(ctx, VARCO_ERR_UNSUPPORTED, "varco_link_partitions: a partition has no map of returned rows");
+        net.row_off[q + 1] = net.row_off[q] + ps.d.n_local;
+        net.halo_off[q + 1] = net.halo_off[q] + ps.d.n_halo;
+        net.boundary += ps.d.n_boundary;
+        ent += ps.d.nnz, local += ps.nnz_t_local;
+        items += ps.fwd.n_items, splits += ps.fwd.n_splits, slots += ps.fwd.n_partials;
+        returned += ps.n_returned;
+    }
+    net.rows = net.row_off[P], net.halo_rows = net.halo_off[P];
+    net.nnz = ent, net.nnz_local = local, net.nnz_cross = ent - local;
+    const int64_t lim = (int64_t(1) << 31) - 1;
+    if (ent > lim || net.rows > lim || net.halo_rows > lim || items > lim || slots > lim)
+        return varco_fail(ctx, VARCO_ERR_UNSUPPORTED, "varco_link_partitions: 2^31 or more entries over all partitions");
+    if (returned != net.halo_rows)
+        return varco_fail(ctx, VARCO_ERR_SHAPE, "varco_link_partitions: the maps of returned rows do not cover the halo rows");
+
+    // halo rows, their owners, and the number of cross entries of every arena row
+    Temp halo_len, halo_gid, halo_zrow, owner_row, cross_len, cross_ptr_d, prod_start;
+    for (Temp* t : {&halo_len, &halo_gid, &halo_zrow, &owner_row, &prod_start}) VARCO_HIP(ctx, t->make(size_t(net.halo_rows) * 4));
+    VARCO_HIP(ctx, cross_len.make(size_t(net.rows) * 4));
+    VARCO_HIP(ctx, cross_ptr_d.make(size_t(net.rows + 1) * 4));
+    VARCO_HIP(ctx, alloc(net.brow, size_t(net.boundary)));
+    VARCO_HIP(ctx, alloc(net.bgid, size_t(net.boundary)));
+    if (net.halo_rows) VARCO_HIP(ctx, hipMemset(owner_row.p, 0xFF, size_t(net.halo_rows) * 4));
+    if (net.rows) VARCO_HIP(ctx, hipMemset(cross_len.p, 0, size_t(net.rows) * 4));
+    if (!ctx->d_flags) VARCO_HIP(ctx, hipMalloc(reinterpret_cast<void**>(&ctx->d_flags), sizeof(int32_t)));
+    int32_t flags = 0;
+    VARCO_HIP(ctx, hipMemcpy(ctx->d_flags, &flags, sizeof(flags), hipMemcpyHostToDevice));
+    for (int32_t q = 0; q < P; ++q) VARCO_HIP(ctx, varco_launch_link_halo(lp[q], halo_len.i32(), halo_gid.i32(), halo_zrow.i32(), nullptr));
+    for (int32_t q = 0; q < P; ++q)
+        VARCO_HIP(ctx, varco_launch_link_owner(lp[q], net.halo_rows, halo_len.i32(), halo_gid.i32(), halo_zrow.i32(), owner_row.i32(),
+                                               cross_len.i32(), net.brow, net.bgid, ctx->d_flags, nullptr));
+    VARCO_HIP(ctx, hipMemcpy(&flags, ctx->d_flags, sizeof(flags), hipMemcpyDeviceToHost));
+    if (flags) return varco_fail(ctx, VARCO_ERR_SHAPE, "varco_link_partitions: a map of returned rows does not fit the consumers' halo rows");
+    std::vector<int32_t> len(size_t(net.rows)), cross_ptr(size_t(net.rows) + 1, 0);
+    if (net.rows) VARCO_HIP(ctx, hipMemcpy(len.data(), cross_len.p, len.size() * 4, hipMemcpyDeviceToHost));
+    for (int64_t r = 0; r < net.rows; ++r) cross_ptr[r + 1] = cross_ptr[r] + len[r];
+    if (cross_ptr[net.rows] != net.nnz_cross)
+        return varco_fail(ctx, VARCO_ERR_SHAPE, "varco_link_partitions: the returned rows do not hold every entry of the halo columns");
+    VARCO_HIP(ctx, hipMemcpy(cross_ptr_d.p, cross_ptr.data(), cross_ptr.size() * 4, hipMemcpyHostToDevice));
+
+    // entry arrays of both directions
+    VARCO_HIP(ctx, alloc(net.edges, size_t(net.nnz)));
+    VARCO_HIP(ctx, alloc(net.arow, size_t(net.nnz)));
+    VARCO_HIP(ctx, alloc(net.vals, size_t(net.nnz)));
+    VARCO_HIP(ctx, alloc(net.prow, size_t(net.nnz)));
+    VARCO_HIP(ctx, alloc(net.t_local, size_t(net.nnz_local)));
+    VARCO_HIP(ctx, alloc(net.t_cross, size_t(net.nnz_cross)));
+    net.fwd.n_items = int32_t(items), net.fwd.n_splits = int32_t(splits), net.fwd.n_partials = int32_t(slots);
+    VARCO_HIP(ctx, alloc(net.fwd.items, size_t(items)));
+    VARCO_HIP(ctx, alloc(net.fwd.splits, size_t(splits)));
+    for (int32_t q = 0; q < P; ++q)
+        VARCO_HIP(ctx, varco_launch_link_starts(lp[q], halo_len.i32(), cross_ptr_d.i32(), prod_start.i32(), nullptr));
+    items = splits = slots = 0;
+    for (int32_t q = 0; q < P; ++q) {
+        const PartState& ps = ctx->parts[q];
+        VARCO_HIP(ctx, varco_launch_link_edges(lp[q], ps.prow, owner_row.i32(), prod_start.i32(), net.edges, net.arow, net.vals, net.prow, nullptr));
+        VARCO_HIP(ctx, varco_launch_link_transposed(lp[q], prod_start.i32(), net.t_local, net.t_cross, nullptr));
+        VARCO_HIP(ctx, varco_launch_link_items(ps.fwd, int32_t(lp[q].row_off), int32_t(lp[q].ent_off), int32_t(slots), int32_t(items),
+                                               int32_t(splits), net.fwd, nullptr));
+        items += ps.fwd.n_items, splits += ps.fwd.n_splits, slots += ps.fwd.n_partials;
+    }
+
+    // work list of the node sums
+    std::vector<NodeItem> nodes(static_cast<size_t>(net.rows));
+    std::vector<SpmmItem> pieces;
+    int32_t n_slots = 0;
+    auto cut = [&](int32_t kind, int32_t& e0, int32_t& e1, int32_t longest, int32_t flag, int32_t& f) {
+        if (e1 - e0 <= longest) return;
+        const int32_t first = n_slots;
+        for (int32_t e = e0; e < e1; e += longest) pieces.push_back({kind, e, std::min(e + longest, e1), n_slots++});
+        e0 = first, e1 = n_slots, f |= flag;
+    };
+    for (int32_t q = 0; q < P; ++q) {
+        const PartState& ps = ctx->parts[q];
+        std::vector<int32_t> gid(size_t(ps.d.n_local));
+        if (!gid.empty()) VARCO_HIP(ctx, hipMemcpy(gid.data(), ps.d.local_gid, gid.size() * 4, hipMemcpyDeviceToHost));
+        for (int32_t i = 0; i < ps.d.n_local; ++i) {
+            const int64_t r = lp[q].row_off + i;
+            NodeItem& it = nodes[size_t(r)];
+            it.row = int32_t(r), it.gid = uint32_t(gid[size_t(i)]);
+            it.l0 = int32_t(lp[q].local_off) + ps.t_local_ptr[size_t(i)], it.l1 = int32_t(lp[q].local_off) + ps.t_local_ptr[size_t(i) + 1];
+            it.c0 = cross_ptr[size_t(r)], it.c1 = cross_ptr[size_t(r) + 1];
+            it.flags = it.pad = 0;
+            cut(0, it.l0, it.l1, kNodeLocal, VARCO_NODE_LOCAL_SPLIT, it.flags);
+            cut(1, it.c0, it.c1, kNodeCross, VARCO_NODE_CROSS_SPLIT, it.flags);
+        }
+    }
+    net.nodes.n_nodes = int32_t(nodes.size()), net.nodes.n_pieces = int32_t(pieces.size());
+    VARCO_HIP(ctx, alloc(net.nodes.nodes, nodes.size()));
+    VARCO_HIP(ctx, alloc(net.nodes.pieces, pieces.size()));
+    if (!nodes.empty()) VARCO_HIP(ctx, hipMemcpy(net.nodes.nodes, nodes.data(), nodes.size() * sizeof(NodeItem), hipMemcpyHostToDevice));
+    if (!pieces.empty()) VARCO_HIP(ctx, hipMemcpy(net.nodes.pieces, pieces.data(), pieces.size() * sizeof(SpmmItem), hipMemcpyHostToDevice));
+    VARCO_HIP(ctx, hipDeviceSynchronize());
+
+    // workspace: dM over the arena, partial rows, partial products of the weight gradients
+    const int32_t wmax = *std::max_element(ctx->widths.begin(), ctx->widths.end());
+    int64_t gemm_elems = 0;
+    for (int32_t l = 0; l < ctx->n_layers; ++l)
+        for (int kind : {kGemmF32, kGemmBf16, kGemmExpanded}) {
+            const int64_t fi = ctx->widths[l], fo = ctx->widths[l + 1];
+            gemm_elems = std::max<int64_t>(gemm_elems, gemm_split_for(int32_t(fi), int32_t(fo), net.rows, kind) * fi * fo);
+        }
+    ctx->need_dm = std::max(ctx->need_dm, (size_t(net.rows) * size_t(wmax) * size_t(ctx->elem_bytes()) + 3) / 4);
+    ctx->need_spmm = std::max(ctx->need_spmm, size_t(std::max<int64_t>(net.fwd.n_partials, n_slots)) * size_t(wmax));
+    ctx->need_gemm = std::max(ctx->need_gemm, size_t(gemm_elems));
+    net.linked = true;
+    return size_all_workspaces(ctx);
+}
+
+int32_t check_linked(const varco_ctx* ctx, const char* fn) {
+    if (!ctx) return varco_fail(nullptr, VARCO_ERR_INVALID_ARG, "null context");
+    if (ctx->net.linked) return VARCO_OK;
+    std::string m = std::string(fn) + ": call varco_link_partitions first";
+    return varco_fail(ctx, VARCO_ERR_STATE, m.c_str());
+}
+
+int32_t null_pointer(const varco_ctx* ctx, const char* fn) {
+    std::string m = std::string(fn) + ": null pointer";
+    return varco_fail(ctx, VARCO_ERR_INVALID_ARG, m.c_str());
+}
+
+// M = S [local rows of x; compressed rows of z] for all partitions.
+int32_t aggregate_fwd(varco_ctx* ctx, Workspace& ws, int32_t layer, const MaskRule& rule, const void* x, const void* z, void* m, hipStream_t st) {
+    const NetState& net = ctx->net;
+    const double es = ctx->elem_bytes();
+    const int32_t fi = ctx->widths[layer];
+    const double bytes = double(net.nnz) * 8.0 + (double(net.rows) + 1.0) * 4.0 + (2.0 * double(net.rows) * fi + double(net.halo_rows) * rule.k) * es;
+    const double stream = double(net.nnz) * 8.0 + (double(net.rows) + 1.0) * 4.0 +
+                          (double(net.rows) * fi + double(net.nnz_local) * fi + double(net.nnz_cross) * rule.k) * es;
+    const LaunchTag tag = ctx->tag(VARCO_K_AGG_FWD, bytes, 0, stream);
+    if (rule.k == rule.width)   // lossless: a message equals the owner's row, which is nearer (the same rows serve the local entries)
+        VARCO_HIP(ctx, varco_launch_spmm(ctx->dtype, net.fwd, nullptr, net.arow, net.vals, x, nullptr, 0, full_rule(fi), m, 0, ws.spmm, st, tag));
+    else
+        VARCO_HIP(ctx, varco_launch_spmm(ctx->dtype, net.fwd, net.edges, nullptr, net.vals, x, z, net.boundary, rule, m, 0, ws.spmm, st, tag));
+    ctx->stats.fwd_elems[layer] += net.halo_rows * rule.k;
+    ctx->stats.full_fwd_elems[layer] += net.halo_rows * fi;
+    return VARCO_OK;
+}
+
+// dX (+)= S^T dM, cross entries at the kept positions of their node.
+int32_t aggregate_bwd(varco_ctx* ctx, Workspace& ws, int32_t layer, const MaskRule& rule, const void* dm, void* dx, bool add_old, hipStream_t st) {
+    const NetState& net = ctx->net;
+    const double es = ctx->elem_bytes();
+    const int32_t fi = ctx->widths[layer];
+    VarcoCross cross = net.nnz_cross == 0 || rule.k == 0 ? kCrossNone : rule.k == rule.width ? kCrossFull : kCrossMasked;
+    if (cross == kCrossMasked && products_pay(ctx, layer) && prod_floats(ctx, layer) <= ws.prod_elems) {
+        cross = kCrossProducts;
+        const double bytes = double(net.nnz_cross) * 8.0 + double(net.rows) * fi * es;
+        VARCO_HIP(ctx, varco_launch_halo_products(ctx->dtype, net.fwd, net.edges, net.vals, net.prow, dm, rule, ws.prod, st,
+                                                  ctx->tag(VARCO_K_AGG_BWD_HALO, bytes, 0)));
+    }
+    const double bytes = double(net.nnz_local) * 8.0 + (double(net.rows) + 1.0) * 4.0 + 2.0 * double(net.rows) * fi * es;
+    const double stream = double(net.nnz_local) * (8.0 + fi * es) + (double(net.rows) + 1.0) * 4.0 + double(net.rows) * fi * es;
+    VARCO_HIP(ctx, varco_launch_node_sum(ctx->dtype, net.nodes, net.t_local, net.t_cross, dm, ws.prod, rule, cross, dx, add_old, ws.spmm, st,
+                                         ctx->tag(VARCO_K_AGG_BWD_LOCAL, bytes, 0, stream)));
+    if (rule.k > 0) {
+        ctx->stats.bwd_elems[layer] += net.halo_rows * rule.k;
+        ctx->stats.full_bwd_elems[layer] += net.halo_rows * fi;
+    }
+    return VARCO_OK;
+}
+
+int32_t compress_all(varco_ctx* ctx, int32_t layer, const MaskRule& rule, const void* x, void* z, hipStream_t st) {
+    const NetState& net = ctx->net;
+    if (net.boundary == 0 || rule.k == 0) return VARCO_OK;
+    ctx->layers[layer].ran_forward = true;
+    VARCO_HIP(ctx, varco_launch_compress(ctx->dtype, rule, net.bgid, net.brow, net.boundary, x, ctx->widths[layer], z, st,
+                                         ctx->tag(VARCO_K_COMPRESS, double(net.boundary) * (rule.width + rule.k) * ctx->elem_bytes(), 0)));
+    return VARCO_OK;
+}
+
+const char* at(const void* base, int64_t row, int32_t width, double es) {
+    return base ? static_cast<const char*>(base) + row * width * int64_t(es) : nullptr;
+}
+char* at(void* base, int64_t row, int32_t width, double es) {
+    return base ? static_cast<char*>(base) + row * width * int64_t(es) : nullptr;
+}
+
+int32_t layer_fwd(varco_ctx* ctx, Workspace& ws, const varco_network_buffers& b, int32_t l, hipStream_t st) {
+    const NetState& net = ctx->net;
+    const int32_t fi = ctx->widths[l], fo = ctx->widths[l + 1];
+    const bool sage = ctx->conv == VARCO_CONV_SAGE, last = l == ctx->n_layers - 1;
+    const int dt = ctx->dtype;
+    const double es = ctx->elem_bytes();
+    if (ctx->layers[l].order == VARCO_ORDER_TRANSFORM_FIRST) {
+        for (int32_t q = 0; q < ctx->n_parts; ++q)
+            if (int32_t rc = varco_layer_fwd(ctx, l, q, at(b.x[l], net.row_off[q], fi, es), b.z[l], b.h1[l], sage ? b.h0[l] : nullptr,
+                                             at(b.x[l + 1], net.row_off[q], fo, es), last ? nullptr : b.z[l + 1], nullptr, st))
+                return rc;
+        return VARCO_OK;
+    }
+    const MaskRule rule = make_rule(ctx, l);
+    ctx->layers[l].ran_forward = true;
+    if (int32_t rc = aggregate_fwd(ctx, ws, l, rule, b.x[l], b.z[l], b.m[l], st)) return rc;
+    if (net.rows > 0) {
+        GemmArgs g;
+        g.m = int32_t(net.rows), g.n = fo, g.k = fi;
+        g.a.ptr = b.m[l], g.a.ld = fi, g.a.dtype = dt;
+        g.b.ptr = b.h1[l], g.b.ld = fo;
+        if (sage) {
+            g.k2 = fi;
+            g.a2.ptr = b.x[l], g.a2.ld = fi, g.a2.dtype = dt;
+            g.b2.ptr = b.h0[l], g.b2.ld = fo;
+        }
+        g.c = b.x[l + 1], g.ldc = fo, g.c_dtype = dt;
+        g.relu = ctx->act[l] == VARCO_ACT_RELU;
+        VARCO_HIP(ctx, prep_weight(ctx, ws, l, b.h1[l], fi, fo, true, 0, false, st, g));
+        if (sage) VARCO_HIP(ctx, prep_weight(ctx, ws, l, b.h0[l], fi, fo, true, 1, true, st, g));
+        VARCO_HIP(ctx, varco_launch_gemm(g, st, ctx->tag(VARCO_K_GEMM_FWD, 0, 2.0 * g.m * double(g.n) * (double(g.k) + g.k2))));
+    }
+    return last ? VARCO_OK : compress_all(ctx, l + 1, make_rule(ctx, l + 1), b.x[l + 1], b.z[l + 1], st);
+}
+
+int32_t layer_bwd(varco_ctx* ctx, Workspace& ws, const varco_network_buffers& b, int32_t l, hipStream_t st) {
+    const NetState& net = ctx->net;
+    const int32_t fi = ctx->widths[l], fo = ctx->widths[l + 1];
+    const bool sage = ctx->conv == VARCO_CONV_SAGE, need = l > 0;
+    const int dt = ctx->dtype;
+    const double es = ctx->elem_bytes();
+    if (ctx->layers[l].order == VARCO_ORDER_TRANSFORM_FIRST) {
+        for (int32_t q = 0; q < ctx->n_parts; ++q)
+            if (int32_t rc = varco_layer_bwd(ctx, l, q, at(b.dx[l + 1], net.row_off[q], fo, es), at(b.x[l + 1], net.row_off[q], fo, es),
+                                             at(b.x[l], net.row_off[q], fi, es), b.z[l], b.h1[l], sage ? b.h0[l] : nullptr, b.dh1[l],
+                                             sage ? b.dh0[l] : nullptr, need ? at(b.dx[l], net.row_off[q], fi, es) : nullptr,
+                                             need ? at(b.dz_halo[l], net.halo_off[q], ctx->layers[l].k, es) : nullptr, st))
+                return rc;
+        for (int32_t q = 0; need && q < ctx->n_parts; ++q)
+            if (int32_t rc = varco_accumulate_returned(ctx, l, q, nullptr, nullptr, b.dz_halo[l], at(b.dx[l], net.row_off[q], fi, es), st))
+                return rc;
+        return VARCO_OK;
+    }
+    if (net.rows == 0) return VARCO_OK;
+    const int32_t nl = int32_t(net.rows);
+    const void* gate = ctx->act[l] == VARCO_ACT_RELU ? b.x[l + 1] : nullptr;
+    {   // weight gradients: one reduction over the rows of all partitions (their sum is what Algorithm 1 asks for)
+        GemmArgs g;
+        g.m = fi, g.n = fo, g.k = nl;
+        g.a.ptr = b.m[l], g.a.ld = fi, g.a.transposed = true, g.a.dtype = dt;
+        g.b.ptr = b.dx[l + 1], g.b.gate = gate, g.b.ld = fo, g.b.dtype = dt;
+        g.c = b.dh1[l], g.ldc = fo;
+        g.accumulate = true;
+        g.partial = ws.gemm;
+        g.f32_terms = dt == VARCO_F32 ? ctx->f32_terms : 0;
+        for (int tap = 0; tap < (sage ? 2 : 1); ++tap) {
+            if (tap == 1) g.a.ptr = b.x[l], g.c = b.dh0[l];
+            g.split_k = gemm_split_for(fi, fo, nl, gemm_kind(g));
+            if (size_t(g.split_k) * fi * fo > ws.gemm_elems) return varco_fail(ctx, VARCO_ERR_STATE, "varco_network_backward: workspace too small");
+            VARCO_HIP(ctx, varco_launch_gemm(g, st, ctx->tag(VARCO_K_GEMM_WGRAD, 0, 2.0 * fi * fo * double(nl))));
+        }
+    }
+    if (!need) return VARCO_OK;
+    GemmArgs g;                    // dM = dZ H1^T
+    g.m = nl, g.n = fi, g.k = fo;
+    g.a.ptr = b.dx[l + 1], g.a.gate = gate, g.a.ld = fo, g.a.dtype = dt;
+    g.b.ptr = b.h1[l], g.b.ld = fo, g.b.transposed = true;
+    g.c = ws.dm, g.ldc = fi, g.c_dtype = dt;
+    VARCO_HIP(ctx, prep_weight(ctx, ws, l, b.h1[l], fi, fo, false, 0, false, st, g));
+    VARCO_HIP(ctx, varco_launch_gemm(g, st, ctx->tag(VARCO_K_GEMM_DGRAD, 0, 2.0 * fi * fo * double(nl))));
+    if (sage) {                    // self tap: dX = dZ H0^T, the aggregated part is added to it
+        g.b.ptr = b.h0[l];
+        g.c = b.dx[l];
+        VARCO_HIP(ctx, prep_weight(ctx, ws, l, b.h0[l], fi, fo, false, 1, false, st, g));
+        VARCO_HIP(ctx, varco_launch_gemm(g, st, ctx->tag(VARCO_K_GEMM_DGRAD, 0, 2.0 * fi * fo * double(nl))));
+    }
+    return aggregate_bwd(ctx, ws, l, make_rule(ctx, l), ws.dm, b.dx[l], sage, st);
+}
+
+int32_t check_buffers(const varco_ctx* ctx, const varco_network_buffers* b, bool backward, const char* fn) {
+    if (!b) return null_pointer(ctx, fn);
+    const NetState& net = ctx->net;
+    const int32_t L = ctx->n_layers;
+    const bool sage = ctx->conv == VARCO_CONV_SAGE;
+    for (int32_t l = 0; l < L; ++l) {
+        const bool first = ctx->layers[l].order == VARCO_ORDER_TRANSFORM_FIRST, sent = net.halo_rows > 0 && ctx->layers[l].k > 0;
+        if (!b->h1[l] || (sage && !b->h0[l]) || (net.rows > 0 && (!b->x[l] || (!first && !b->m[l]))) || (sent && !b->z[l])) return null_pointer(ctx, fn);
+        if (backward && (!b->dh1[l] || (sage && !b->dh0[l]) || (net.rows > 0 && !b->dx[l + 1]) || (first && l > 0 && sent && !b->dz_halo[l])))
+            return null_pointer(ctx, fn);
+        if (int32_t rc = check_wide_rows(ctx, ctx->widths[l], {b->x[l], b->z[l], b->m[l], backward ? b->dx[l + 1] : nullptr}, fn)) return rc;
+    }
+    return net.rows > 0 && !b->x[L] ? null_pointer(ctx, fn) : VARCO_OK;
+}
+
+// Shared prologue of the calls on one buffer pair (a tap of a K-tap layer).
+int32_t tap_prologue(varco_ctx* ctx, int32_t tap, varco_stream stream, const char* fn, int32_t* layer, int32_t* hop, Workspace** ws) {
+    if (int32_t rc = check_linked(ctx, fn)) return rc;
+    ctx->prof.interrupt();
+    *layer = tap;
+    if (int32_t rc = split_tap(ctx, layer, hop, fn)) return rc;
+    return workspace_for(ctx, static_cast<hipStream_t>(stream), ws, fn);
+}
+
+}  // namespace
+
+size_t varco::network_prod_need(const varco_ctx* ctx) {
+    size_t need = 0;
+    for (int32_t l = 1; l < ctx->n_layers; ++l)       // the first layer's input needs no gradient
+        if (products_pay(ctx, l)) need = std::max(need, prod_floats(ctx, l));
+    return need;
+}
+
+extern "C" int32_t varco_link_partitions(varco_ctx* ctx) {
+    if (!ctx) return varco_fail(nullptr, VARCO_ERR_INVALID_ARG, "varco_link_partitions: null context");
+    VARCO_HIP(ctx, hipDeviceSynchronize());
+    free_network(ctx->net);
+    const int32_t rc = link_impl(ctx);
+    if (rc != VARCO_OK) free_network(ctx->net);
+    return rc;
+}
+
+extern "C" int32_t varco_network_forward(varco_ctx* ctx, const varco_network_buffers* b, varco_stream stream) {
+    const char* fn = "varco_network_forward";
+    if (int32_t rc = check_linked(ctx, fn)) return rc;
+    ctx->prof.interrupt();
+    if (int32_t rc = check_buffers(ctx, b, false, fn)) return rc;
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    Workspace* ws = nullptr;
+    if (int32_t rc = workspace_for(ctx, st, &ws, fn)) return rc;
+    if (int32_t rc = compress_all(ctx, 0, make_rule(ctx, 0), b->x[0], b->z[0], st)) return rc;
+    for (int32_t l = 0; l < ctx->n_layers; ++l)
+        if (int32_t rc = layer_fwd(ctx, *ws, *b, l, st)) return rc;
+    return VARCO_OK;
+}
+
+extern "C" int32_t varco_network_backward(varco_ctx* ctx, const varco_network_buffers* b, varco_stream stream) {
+    const char* fn = "varco_network_backward";
+    if (int32_t rc = check_linked(ctx, fn)) return rc;
+    ctx->prof.interrupt();
+    if (int32_t rc = check_buffers(ctx, b, true, fn)) return rc;
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    Workspace* ws = nullptr;
+    if (int32_t rc = workspace_for(ctx, st, &ws, fn)) return rc;
+    for (int32_t l = ctx->n_layers - 1; l >= 0; --l)
+        if (int32_t rc = layer_bwd(ctx, *ws, *b, l, st)) return rc;
+    return VARCO_OK;
+}
+
+extern "C" int32_t varco_network_compress(varco_ctx* ctx, int32_t tap, const void* x, void* z, varco_stream stream) {
+    const char* fn = "varco_network_compress";
+    int32_t layer = 0, hop = 0;
+    Workspace* ws = nullptr;
+    if (int32_t rc = tap_prologue(ctx, tap, stream, fn, &layer, &hop, &ws)) return rc;
+    if (ctx->net.boundary > 0 && ctx->layers[layer].k > 0 && (!x || !z)) return null_pointer(ctx, fn);
+    return compress_all(ctx, layer, make_rule(ctx, layer, hop), x, z, static_cast<hipStream_t>(stream));
+}
+
+extern "C" int32_t varco_network_aggregate_fwd(varco_ctx* ctx, int32_t tap, const void* y, const void* z_in, void* y_out, varco_stream stream) {
+    const char* fn = "varco_network_aggregate_fwd";
+    int32_t layer = 0, hop = 0;
+    Workspace* ws = nullptr;
+    if (int32_t rc = tap_prologue(ctx, tap, stream, fn, &layer, &hop, &ws)) return rc;
+    if ((ctx->net.rows > 0 && (!y || !y_out)) || (ctx->net.halo_rows > 0 && ctx->layers[layer].k > 0 && !z_in)) return null_pointer(ctx, fn);
+    if (int32_t rc = check_wide_rows(ctx, ctx->widths[layer], {y, z_in, y_out}, fn)) return rc;
+    ctx->layers[layer].ran_forward = true;
+    return aggregate_fwd(ctx, *ws, layer, make_rule(ctx, layer, hop), y, z_in, y_out, static_cast<hipStream_t>(stream));
+}
+
+extern "C" int32_t varco_network_aggregate_bwd(varco_ctx* ctx, int32_t tap, const void* g_out, void* g_in, varco_stream stream) {
+    const char* fn = "varco_network_aggregate_bwd";
+    int32_t layer = 0, hop = 0;
+    Workspace* ws = nullptr;
+    if (int32_t rc = tap_prologue(ctx, tap, stream, fn, &layer, &hop, &ws)) return rc;
+    if (ctx->net.rows > 0 && (!g_out || !g_in)) return null_pointer(ctx, fn);
+    if (int32_t rc = check_wide_rows(ctx, ctx->widths[layer], {g_out, g_in}, fn)) return rc;
+    return aggregate_bwd(ctx, *ws, layer, make_rule(ctx, layer, hop), g_out, g_in, false, static_cast<hipStream_t>(stream));
+}

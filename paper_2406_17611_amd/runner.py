@@ -1,6 +1,7 @@
-"""Harness that holds all partitions of a graph in one GPU's memory and drives the C ABI "in turn":
-Algorithm 1's forward and backward for every layer and partition, with the inter-machine exchange
-replaced by on-device buffers (the compressed rows an owner writes are read in place by its consumers).
+"""Harness that holds all partitions of a graph in one GPU's memory and drives the C ABI: Algorithm 1's
+forward and backward for every layer and partition, with the inter-machine exchange replaced by on-device
+buffers (the compressed rows an owner writes are read in place by its consumers). The partitions share
+every kernel launch (varco_network_*); graphs too large for that are served partition after partition.
 
 Only sequencing and buffer bookkeeping live here; all arithmetic is in libvarco's kernels.
 """
@@ -16,9 +17,9 @@ class PartitionedNetwork:
     def __init__(self, host_parts, widths, conv: str, mask_key: int, device="cuda", need_backward=True, dtype="f32",
                  n_streams=1, transform_first=()):
         """dtype: storage of activations, messages and their gradients ("f32" or "bf16"); weights and weight
-        gradients are always fp32. n_streams > 1: the partitions of a layer are dealt to that many HIP
-        streams, so that the matrix-core-bound kernels of one partition overlap the memory-bound kernels of
-        another; streams are joined wherever a step needs all partitions (layer boundaries, owner-side sums).
+        gradients are always fp32. n_streams > 1: where partitions are served one after the other (graphs with
+        2^31 or more entries), those of a layer are dealt to that many HIP streams, joined wherever a step needs
+        all partitions; with all partitions in every launch there is nothing left to deal.
         transform_first: layers whose calls apply the weights before the aggregation (varco_set_layer_order)."""
         assert dtype in ("f32", "bf16")
         assert 1 <= n_streams <= 4
@@ -38,6 +39,9 @@ class PartitionedNetwork:
         self.transform_first = frozenset(transform_first)
         for l in self.transform_first:
             self.ctx.set_layer_order(l, vb.ORDER_TRANSFORM_FIRST)
+
+        self.linked = self.ctx.link_partitions()
+        self._buffers = vb.NetworkBuffers()
 
         self.n_local = [hp.n_local for hp in host_parts]
         self.n_halo = [hp.n_halo for hp in host_parts]
@@ -68,9 +72,9 @@ class PartitionedNetwork:
             self.dh0 = [torch.zeros_like(h) if conv == "sage" else None for h in self.h1]
             # one more set of weight-gradient accumulators per extra stream (overlapping calls must not
             # read-modify-write the same buffer); folded into dh1 / dh0 at the end of backward()
-            self._dh1_extra = [[torch.zeros_like(h) for h in self.h1] for _ in range(n_streams - 1)]
-            self._dh0_extra = [[torch.zeros_like(h) if conv == "sage" else None for h in self.h1]
-                               for _ in range(n_streams - 1)]
+            n_extra = 0 if self.linked else n_streams - 1
+            self._dh1_extra = [[torch.zeros_like(h) for h in self.h1] for _ in range(n_extra)]
+            self._dh0_extra = [[torch.zeros_like(h) if conv == "sage" else None for h in self.h1] for _ in range(n_extra)]
             self.dx = [None] + [torch.empty((self.n_total, self.widths[l]), **act) for l in range(1, self.L + 1)]
             self.dz_halo = [None] * self.L
         self._zcap = [0] * self.L
@@ -149,18 +153,38 @@ class PartitionedNetwork:
         return out
 
     # ------------------------------------------------------------------ one step
-    def _ensure_buffers(self):
+    def _ensure_buffers(self, returned=True):
+        """Message buffers of the current ratios. returned: those of the backward exchange, for every layer (what
+        per-partition calls hand back); otherwise only for the layers that transform first."""
         for l in range(self.L):
             k = self.ctx.keep(l)
             need = self.b_total * k
             if self.z[l] is None or self._zcap[l] < need:
                 self.z[l] = torch.empty(max(need, 1), dtype=self.act_dtype, device=self.device)
                 self._zcap[l] = need
-            if self.need_backward and l > 0:
+            if self.need_backward and l > 0 and (returned or l in self.transform_first):
                 need = int(self.halo_off[-1]) * k
                 if self.dz_halo[l] is None or self._dzcap[l] < need:
                     self.dz_halo[l] = torch.empty(max(need, 1), dtype=self.act_dtype, device=self.device)
                     self._dzcap[l] = need
+
+    def _network_buffers(self):
+        """The arenas' addresses, as they are now."""
+        b = self._buffers
+        for l in range(self.L):
+            b.x[l], b.z[l], b.m[l] = self.x[l].data_ptr(), self.z[l].data_ptr(), self.m[l].data_ptr()
+            b.h1[l] = self.h1[l].data_ptr()
+            if self.h0[l] is not None:
+                b.h0[l] = self.h0[l].data_ptr()
+            if self.need_backward:
+                b.dh1[l] = self.dh1[l].data_ptr()
+                if self.dh0[l] is not None:
+                    b.dh0[l] = self.dh0[l].data_ptr()
+                b.dx[l + 1] = self.dx[l + 1].data_ptr()
+                if self.dz_halo[l] is not None:
+                    b.dz_halo[l] = self.dz_halo[l].data_ptr()
+        b.x[self.L] = self.x[self.L].data_ptr()
+        return b
 
     def forward(self, step: int, ratio=None, stream=None):
         """Forward of all layers and partitions for training step `step`. `ratio` = (num, den) for every layer
@@ -176,7 +200,11 @@ class PartitionedNetwork:
                     ctx.set_ratio(l, num, den)
             else:
                 ctx.set_ratio(-1, ratio[0], ratio[1])
-        self._ensure_buffers()
+        self._ensure_buffers(not self.linked)
+        if self.linked:
+            self._prepare([stream])
+            ctx.network_forward(self._network_buffers(), stream)
+            return
         streams = self._stream_set(stream)
         self._prepare(streams)
         ns = len(streams)
@@ -199,6 +227,10 @@ class PartitionedNetwork:
 
     def backward(self, stream=None):
         ctx = self.ctx
+        if self.linked:
+            self._prepare([stream])
+            ctx.network_backward(self._network_buffers(), stream)
+            return
         streams = self._stream_set(stream)
         self._prepare(streams)
         ns = len(streams)
@@ -237,6 +269,10 @@ class PartitionedNetwork:
                             vb.sum_gradients(self.dh0[l], extra0[l], streams[0])
                             extra0[l].zero_()
 
+    def _blocks(self):
+        """Row ranges that the calls without a partition argument are issued on."""
+        return [slice(0, self.n_total)] if self.linked else [self.rows(q) for q in range(self.P)]
+
     # ------------------------------------------------------------------ training (Algorithm 1's iteration)
     def set_labels(self, labels_global: np.ndarray, train_mask: np.ndarray):
         """Class labels of all nodes and which of them are training nodes (the rest is held out)."""
@@ -258,8 +294,7 @@ class PartitionedNetwork:
         scale = 1.0 / max(1, self.n_train if train else self.n_test)
         c = self.widths[-1]
         self._totals.zero_()
-        for q in range(self.P):
-            r = self.rows(q)
+        for r in self._blocks():
             self.ctx.softmax_xent(self.x[self.L][r], labels[r], c, scale, self.dx[self.L][r] if with_gradient else None,
                                   self._row_loss[r], self._row_correct[r], self._totals, stream)
         return self._totals
@@ -344,12 +379,16 @@ class KTapNetwork(PartitionedNetwork):
         ctx.set_step(step, stream)
         if ratio is not None:
             ctx.set_ratio(-1, ratio[0], ratio[1])
-        self._ensure_buffers()
+        self._ensure_buffers(not self.linked)
         self._prepare([stream])
         for l in range(self.L):
             fi, k = self.widths[l], ctx.keep(l)
             for hop in range(1, self.K):
                 tap, src = vb.tap(l, hop), self.y[l][hop - 1]
+                if self.linked:
+                    ctx.network_compress(tap, src, self.z[l], stream)
+                    ctx.network_aggregate_fwd(tap, src, self.z[l], self.y[l][hop], stream)
+                    continue
                 for p, hp in enumerate(self.host_parts):
                     if hp.n_boundary:
                         ctx.compress(tap, self.boundary_gid[p], self.dev_parts[p]["boundary_rows"], hp.n_boundary,
@@ -357,8 +396,7 @@ class KTapNetwork(PartitionedNetwork):
                 for q in range(self.P):
                     r = self.rows(q)
                     ctx.aggregate_fwd(tap, q, src[r], self.z[l], self.y[l][hop][r], stream)
-            for q in range(self.P):
-                r = self.rows(q)
+            for r in self._blocks():
                 for hop in range(self.K):
                     ctx.transform_fwd(l, self.y[l][hop][r], self.h[l][hop], self.x[l + 1][r], hop > 0, hop == self.K - 1,
                                       stream)
@@ -367,20 +405,23 @@ class KTapNetwork(PartitionedNetwork):
         ctx = self.ctx
         for l in range(self.L - 1, -1, -1):
             fi, k = self.widths[l], ctx.keep(l)
-            for q in range(self.P):
-                r = self.rows(q)
+            for r in self._blocks():
                 for hop in range(self.K):
                     ctx.transform_bwd_weight(l, self.y[l][hop][r], self.dx[l + 1][r], self.x[l + 1][r], self.dh[l][hop], stream)
             if l == 0:
                 continue
             bufs = [b[:self.n_total * fi].view(self.n_total, fi) for b in self._g]
             cur = self.dx[l] if self.K == 1 else bufs[0]
-            for q in range(self.P):
-                r = self.rows(q)
+            for r in self._blocks():
                 ctx.transform_bwd_input(l, self.dx[l + 1][r], self.x[l + 1][r], self.h[l][self.K - 1], cur[r], False, stream)
             for hop in range(self.K - 1, 0, -1):
                 tap = vb.tap(l, hop)
                 nxt = self.dx[l] if hop == 1 else (bufs[1] if cur is bufs[0] else bufs[0])
+                if self.linked:
+                    ctx.network_aggregate_bwd(tap, cur, nxt, stream)
+                    ctx.transform_bwd_input(l, self.dx[l + 1], self.x[l + 1], self.h[l][hop - 1], nxt, True, stream)
+                    cur = nxt
+                    continue
                 for q in range(self.P):
                     r = self.rows(q)
                     dzh = self.dz_halo[l][int(self.halo_off[q]) * k:] if self.n_halo[q] else None

@@ -1,0 +1,58 @@
+"""The calls that serve all partitions at once (varco_link_partitions, varco_network_*) at the sizes where their node
+sums change form: hub nodes whose local and cross entries are cut into pieces, widths that need one to several loads per
+lane or element loads, messages summed from the product buffer, taken from whole rows, complete or absent."""
+import numpy as np
+import pytest
+import torch
+
+from gpu_common import KEY, both_partitions, hub_graph
+from paper_2406_17611_amd import binding as vb
+from paper_2406_17611_amd import synth
+from paper_2406_17611_amd.runner import PartitionedNetwork
+from test_gpu_network import BF16_TOL, _compare_network
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("conv,widths,dtype", [("gcn", (20, 64, 9), "f32"), ("sage", (33, 30, 7), "f32"), ("gcn", (16, 256, 12), "f32"),
+                                               ("sage", (24, 516, 5), "f32"), ("gcn", (20, 96, 9), "bf16"), ("sage", (17, 512, 6), "bf16")])
+def test_node_sums_with_hubs(conv, widths, dtype):
+    g = hub_graph(1500, 3, 1100, 6.0, conv, seed=81)
+    part = synth.random_partition(g.n, 3, seed=82)
+    # 1/8 and 1/5 (ragged k) of a row: products; 2/3: whole rows masked; all; nothing
+    ratios = [(8, 1), (5, 1), (3, 2), (1, 1), (1, 0)]
+    _compare_network(g, part, 3, conv, widths, ratios, steps=list(range(5)), tol=BF16_TOL if dtype == "bf16" else 1e-4, dtype=dtype)
+
+
+def test_uneven_and_empty_partitions():
+    g = synth.small_random_graph(300, 5.0, "gcn", seed=83)
+    part = np.zeros(g.n, dtype=np.int32)
+    part[20:] = 2                                        # partition 1 owns nothing
+    _compare_network(g, part, 3, "gcn", (12, 40, 5), [(4, 1), (1, 1)], steps=[0, 1])
+
+
+def test_linked_calls_need_a_link_and_a_changed_partition_drops_it():
+    g = synth.small_random_graph(200, 5.0, "gcn", seed=84)
+    host, _ = both_partitions(g, synth.random_partition(g.n, 2, seed=85), 2)
+    net = PartitionedNetwork(host, (8, 16, 4), "gcn", KEY)
+    assert net.linked
+    net.set_weights([synth.glorot(8, 16, 1), synth.glorot(16, 4, 2)])
+    net.set_inputs(synth.features(g.n, 8, 3))
+    net.forward(0, (2, 1))
+    torch.cuda.synchronize()
+    want = net.x[2].clone()
+    net.ctx.register_partition(1, host[1])
+    with pytest.raises(vb.VarcoError) as e:
+        net.forward(0, (2, 1))
+    assert e.value.code == vb.ERR_STATE
+    assert net.ctx.link_partitions()
+    net.forward(0, (2, 1))
+    torch.cuda.synchronize()
+    assert torch.equal(net.x[2], want)
+    # a map of returned rows that names another node's rows is refused
+    bad = host[0]
+    bad.ret_src = bad.ret_src[::-1].copy()
+    net.ctx.register_partition(0, bad)
+    with pytest.raises(vb.VarcoError) as e:
+        net.ctx.link_partitions()
+    assert e.value.code == vb.ERR_SHAPE
