@@ -544,20 +544,52 @@ struct ProductArgs {
     const T* dm;                // n_local x width
     MaskRule rule;
     T* prod;                    // (halo entries) x k, in the storage type
-    int32_t ev;                 // floats per lane and store: 4, 2 or 1
-    int32_t ku;                 // stores per entry = k / ev
+    int32_t ku;                 // stores per entry = k / (elements per store)
     int32_t lpe_log2;           // lanes per entry
 };
 
+// EV elements per lane and store (16 bytes where k and the alignment allow it: with 8 bf16 values per lane a 128-element
+// message takes 16 lanes, and what is done once per lane and entry - fetching its record from another lane, the store
+// address, the first position - is shared by twice as many elements as with 4; this pass issues vector instructions all
+// the time, so their number is its time). Positions are kept as byte offsets into the LDS row; they wrap with a mask for
+// power-of-two widths and with one unsigned minimum otherwise (q - width is huge when q < width).
+// SWZ: lanes of one entry step by EV positions, which meet in few LDS banks; position bits 6-8 folded into bits 0-2 of the
+// address (the same map as when the row was staged) spread them.
+constexpr uint32_t swizzled(uint32_t q_bytes) { return q_bytes ^ ((q_bytes >> 6) & 0x1Cu); }
+
+// The product rows are read back by another kernel, long after they have left the caches: streaming stores.
 template <typename T, int EV>
+__device__ __forceinline__ void store_products(T* dst, const float (&x)[EV]) {
+    typedef uint32_t words4 __attribute__((ext_vector_type(4)));
+    typedef uint32_t words2 __attribute__((ext_vector_type(2)));
+    constexpr int N = EV * int(sizeof(T)) / 4;
+    uint32_t u[N > 0 ? N : 1];
+    if constexpr (sizeof(T) == 4) {
+#pragma unroll
+        for (int i = 0; i < EV; ++i) u[i] = __float_as_uint(x[i]);
+    } else {
+#pragma unroll
+        for (int i = 0; i < N; ++i) u[i] = uint32_t(float_to_bf16(x[2 * i])) | (uint32_t(float_to_bf16(x[2 * i + 1])) << 16);
+    }
+    if constexpr (N == 4)
+        __builtin_nontemporal_store(words4{u[0], u[1], u[2], u[3]}, reinterpret_cast<words4*>(dst));
+    else if constexpr (N == 2)
+        __builtin_nontemporal_store(words2{u[0], u[1]}, reinterpret_cast<words2*>(dst));
+    else if constexpr (N == 1)
+        __builtin_nontemporal_store(u[0], reinterpret_cast<uint32_t*>(dst));
+    else
+        Elem<T>::store(dst, x[0]);
+}
+
+template <typename T, int EV, bool POW2, bool SWZ>
 __device__ __forceinline__ void product_phase(const ProductArgs<T>& p, int lane, int first, int ns, int32_t pr, float w,
                                               uint32_t mab, const float* lrow) {
-    using V = typename Vec<EV>::type;
     const int64_t k = p.rule.k;
-    const uint32_t width = p.rule.width;
+    const uint32_t width = p.rule.width, row_bytes = width * 4u;
     const int epi = 64 >> p.lpe_log2;
     const int sub = lane >> p.lpe_log2;
     const int jl = lane & ((1 << p.lpe_log2) - 1);
+    const char* const row = reinterpret_cast<const char*>(lrow);
     for (int j0 = 0; j0 < p.ku; j0 += 64) {
         const int ju = j0 + jl;
         const bool j_ok = ju < p.ku;
@@ -566,32 +598,33 @@ __device__ __forceinline__ void product_phase(const ProductArgs<T>& p, int lane,
             const int es = r0 + sub;
             const bool act = j_ok && es < ns;
             const int src_lane = act ? first + es : 0;
-            const int32_t row = __shfl(pr, src_lane);
+            const int32_t dst_row = __shfl(pr, src_lane);
             const float wi = __shfl(w, src_lane);
             const uint32_t ab = __shfl(mab, src_lane);
             if (act) {
-                const uint32_t a = ab & 0xFFFFu;
-                uint32_t q = varco_mod_width(a * uint32_t(j) + (ab >> 16), width, p.rule.width_magic);
+                const uint32_t a = ab & 0xFFFFu, a4 = a * 4u;
+                uint32_t q = __umul24(a, uint32_t(j)) + (ab >> 16);
+                q = (POW2 ? q & (width - 1u) : varco_mod_width(q, width, p.rule.width_magic)) * 4u;
                 float out[EV];
 #pragma unroll
                 for (int i = 0; i < EV; ++i) {
-                    out[i] = wi * lrow[q];
-                    q += a;
-                    if (q >= width) q -= width;
+                    out[i] = wi * *reinterpret_cast<const float*>(row + (SWZ ? swizzled(q) : q));
+                    q += a4;
+                    q = POW2 ? q & (row_bytes - 1u) : min(q, q - row_bytes);
                 }
-                T* dst = p.prod + int64_t(row) * k + j;
-                if constexpr (EV == 4)
-                    store_vec<T, 4>(dst, make_float4(out[0], out[1], out[2], out[3]));
-                else if constexpr (EV == 2)
-                    store_vec<T, 2>(dst, make_float2(out[0], out[1]));
-                else
-                    store_vec<T, 1>(dst, out[0]);
+                store_products<T, EV>(p.prod + int64_t(dst_row) * k + j, out);
             }
         }
     }
 }
 
-template <typename T>
+// A wavefront takes kProductItems consecutive items of the work list. Its time per item is a chain - records of the entries
+// and the row of dM, the hash, LDS, the stores - so the next item's records and row are requested before the current item's
+// products are formed: on a graph with 10 halo entries per row an item is 1.3 KB of stores, far too little to cover that
+// chain by resident wavefronts alone. ROWV: 4-element loads per lane that hold a row of dM in registers ahead of its turn
+// (width <= 256 ROWV, rows aligned to 4 elements); 0: the row is copied to LDS when its turn comes.
+constexpr int kProductItems = 4;
+template <typename T, int EV, bool POW2, bool SWZ, int ROWV>
 __global__ __launch_bounds__(kBlock) void halo_products_kernel(ProductArgs<T> p) {
     extern __shared__ float lds[];
     const int lane = threadIdx.x & 63;
@@ -599,54 +632,93 @@ __global__ __launch_bounds__(kBlock) void halo_products_kernel(ProductArgs<T> p)
     const int32_t width = int32_t(p.rule.width);
     float* lrow = lds + wave * width;
     uint16_t* lunits = reinterpret_cast<uint16_t*>(lds + kWaves * width);
-    const int32_t idx = blockIdx.x * kWaves + __builtin_amdgcn_readfirstlane(wave);   // uniform: the item sits in scalar registers
-    const bool has_item = idx < p.n_items;
-    SpmmItem it{};                      // empty range for a wavefront without an item
-    if (has_item) it = p.items[idx];
-
+    int32_t idx = (blockIdx.x * kWaves + __builtin_amdgcn_readfirstlane(wave)) * kProductItems;   // uniform: items sit in scalar registers
+    const int32_t end = min(idx + kProductItems, p.n_items);
+    auto item_at = [&](int32_t i) {
+        SpmmItem it{};                  // empty range past the end
+        if (i < end) it = p.items[i];
+        return it;
+    };
     // The records of a batch (entry, weight, product row) are loaded together and for every entry, halo or
-    // not, so that one memory round trip serves all three; the first batch's loads are in flight while the
-    // row of dM is staged in LDS, and all of that is requested before the workgroup stages the multiplier
-    // table and meets at the barrier.
+    // not, so that one memory round trip serves all three.
     VarcoEdge ed{0, -1};
     float w = 0.f;
     int32_t pr = 0;
-    auto load_batch = [&](int32_t base) {
+    auto load_batch = [&](const SpmmItem& it, int32_t base) {
         const int32_t e = base + lane;
         ed = VarcoEdge{0, -1}, w = 0.f, pr = 0;
         if (e < it.e1) ed = p.edge[e], w = p.vals[e], pr = p.prow[e];
     };
-    load_batch(it.e0);
-    if (it.e0 < it.e1) {
-        const T* src = p.dm + int64_t(it.row) * width;
-        for (int c = lane; c < width; c += 64) lrow[c] = Elem<T>::load(src + c);
-    }
+    using R = typename Stored<T, 4>::type;
+    R ahead[ROWV > 0 ? ROWV : 1];
+    auto load_row = [&](const SpmmItem& it) {
+        if constexpr (ROWV > 0) {
+            const T* src = p.dm + int64_t(it.row) * width;
+#pragma unroll
+            for (int m = 0; m < ROWV; ++m) {
+                const int c = 4 * (lane + 64 * m);
+                ahead[m] = R{};
+                if (it.e0 < it.e1 && c < width) ahead[m] = *reinterpret_cast<const R*>(src + c);
+            }
+        }
+    };
+    auto stash_row = [&](const SpmmItem& it) {
+        if constexpr (ROWV > 0) {
+#pragma unroll
+            for (int m = 0; m < ROWV; ++m) {
+                const int c = 4 * (lane + 64 * m);
+                if (c < width) {
+                    float4 x = make_float4(Stored<T, 4>::get(ahead[m], 0), Stored<T, 4>::get(ahead[m], 1), Stored<T, 4>::get(ahead[m], 2),
+                                           Stored<T, 4>::get(ahead[m], 3));
+                    if constexpr (SWZ) {    // position i of the group of four goes to i ^ (s & 3) of the group with index bit 2 flipped by s & 4
+                        const int s = (c >> 6) & 7;
+                        const float e[4] = {x.x, x.y, x.z, x.w};
+                        x = make_float4(e[s & 3], e[1 ^ (s & 3)], e[2 ^ (s & 3)], e[3 ^ (s & 3)]);
+                        *reinterpret_cast<float4*>(lrow + (c ^ (s & 4))) = x;
+                    } else {
+                        *reinterpret_cast<float4*>(lrow + c) = x;
+                    }
+                }
+            }
+        } else if (it.e0 < it.e1) {
+            const T* src = p.dm + int64_t(it.row) * width;
+            for (int c = lane; c < width; c += 64) lrow[SWZ ? swizzled(4u * c) / 4u : uint32_t(c)] = Elem<T>::load(src + c);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    };
+
+    SpmmItem it = item_at(idx);
+    load_batch(it, it.e0);
+    load_row(it);
     for (uint32_t i = threadIdx.x; i < p.rule.n_units; i += kBlock) lunits[i] = p.rule.units[i];
-    __syncthreads();                    // also orders the wavefront's own row behind its writes
-    if (it.e0 >= it.e1) return;         // no block-wide barrier below
-    for (int32_t base = it.e0; base < it.e1; base += 64) {
-        const bool is_halo = ed.gid >= 0;
-        const uint64_t hmask = __ballot(is_halo);
-        uint32_t mab = 0;
-        if (is_halo) {
-            const uint32_t h1 = varco_mix32(uint32_t(ed.gid) ^ varco_key0(p.rule));
-            const uint32_t h2 = varco_mix32(h1 ^ varco_key1(p.rule));
-            mab = uint32_t(lunits[__umulhi(h2, p.rule.n_units)]) | (__umulhi(h1, p.rule.width) << 16);
-        }
-        const int cnt = min(64, it.e1 - base);
-        const int ns = __popcll(hmask);
-        const int first = cnt - ns;     // columns ascend within a row: halo entries sit in the last lanes
-        const float wb = w;
-        const int32_t prb = pr;
-        if (base + 64 < it.e1) load_batch(base + 64);
-        if (ns > 0) {
-            if (p.ev == 4)
-                product_phase<T, 4>(p, lane, first, ns, prb, wb, mab, lrow);
-            else if (p.ev == 2)
-                product_phase<T, 2>(p, lane, first, ns, prb, wb, mab, lrow);
+    __syncthreads();                    // no block-wide barrier below
+    for (; idx < end; ++idx) {
+        stash_row(it);
+        const SpmmItem nx = item_at(idx + 1);
+        load_row(nx);
+        if (it.e0 >= it.e1) load_batch(nx, nx.e0);
+        for (int32_t base = it.e0; base < it.e1; base += 64) {
+            const bool is_halo = ed.gid >= 0;
+            const uint64_t hmask = __ballot(is_halo);
+            uint32_t mab = 0;
+            if (is_halo) {
+                const uint32_t h1 = varco_mix32(uint32_t(ed.gid) ^ varco_key0(p.rule));
+                const uint32_t h2 = varco_mix32(h1 ^ varco_key1(p.rule));
+                mab = uint32_t(lunits[__umulhi(h2, p.rule.n_units)]) | (__umulhi(h1, p.rule.width) << 16);
+            }
+            const int cnt = min(64, it.e1 - base);
+            const int ns = __popcll(hmask);
+            const int first = cnt - ns;     // columns ascend within a row: halo entries sit in the last lanes
+            const float wb = w;
+            const int32_t prb = pr;
+            if (base + 64 < it.e1)
+                load_batch(it, base + 64);
             else
-                product_phase<T, 1>(p, lane, first, ns, prb, wb, mab, lrow);
+                load_batch(nx, nx.e0);
+            if (ns > 0) product_phase<T, EV, POW2, SWZ>(p, lane, first, ns, prb, wb, mab, lrow);
         }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");     // the row has been read: the next one may overwrite it
+        it = nx;
     }
 }
 
@@ -1005,7 +1077,7 @@ hipError_t halo_products_t(const SpmmPlan& fwd_plan, const VarcoEdge* edge, cons
     T* prod = static_cast<T*>(prod_v);
     const int32_t width = int32_t(rule.width);
     int ev = 1;
-    for (int c : {4, 2})
+    for (int c : {int(16 / sizeof(T)), 4, 2})
         if (rule.k % c == 0 && aligned_to(prod, c * sizeof(T))) {
             ev = c;
             break;
@@ -1019,12 +1091,40 @@ hipError_t halo_products_t(const SpmmPlan& fwd_plan, const VarcoEdge* edge, cons
     a.dm = static_cast<const T*>(dm);
     a.rule = rule;
     a.prod = prod;
-    a.ev = ev, a.ku = int(rule.k) / ev, a.lpe_log2 = 0;
+    a.ku = int(rule.k) / ev, a.lpe_log2 = 0;
     while ((1 << a.lpe_log2) < a.ku && a.lpe_log2 < 6) ++a.lpe_log2;
     const size_t lds_bytes = size_t(kWaves) * width * sizeof(float) + size_t(rule.n_units) * sizeof(uint16_t);
+    const bool pow2 = (width & (width - 1)) == 0;
+    const dim3 grid((fwd_plan.n_items + kWaves * kProductItems - 1) / (kWaves * kProductItems));
+    const int rowv = width % 4 != 0 || !aligned_to(dm, 4 * sizeof(T)) || width > 512 ? 0 : width > 256 ? 2 : 1;
+    auto go = [&](auto evc, auto p2, auto swz) {
+        constexpr int EV = decltype(evc)::value;
+        constexpr bool P2 = decltype(p2)::value, SW = decltype(swz)::value;
+        if (rowv == 1)
+            hipLaunchKernelGGL((halo_products_kernel<T, EV, P2, SW, 1>), grid, dim3(kBlock), lds_bytes, stream, a);
+        else if (rowv == 2)
+            hipLaunchKernelGGL((halo_products_kernel<T, EV, P2, SW, 2>), grid, dim3(kBlock), lds_bytes, stream, a);
+        else
+            hipLaunchKernelGGL((halo_products_kernel<T, EV, P2, SW, 0>), grid, dim3(kBlock), lds_bytes, stream, a);
+    };
+    auto with_wrap = [&](auto evc) {
+        constexpr bool kSwz = (decltype(evc)::value >= 8);
+        if (pow2 && kSwz && width >= 512)
+            go(evc, std::true_type{}, std::integral_constant<bool, kSwz>{});
+        else if (pow2)
+            go(evc, std::true_type{}, std::false_type{});
+        else
+            go(evc, std::false_type{}, std::false_type{});
+    };
     tag.begin(stream);
-    hipLaunchKernelGGL(halo_products_kernel<T>, dim3((fwd_plan.n_items + kWaves - 1) / kWaves), dim3(kBlock), lds_bytes,
-                       stream, a);
+    if constexpr (sizeof(T) == 2)
+        if (ev == 8) with_wrap(std::integral_constant<int, 8>{});
+    if (ev == 4)
+        with_wrap(std::integral_constant<int, 4>{});
+    else if (ev == 2)
+        with_wrap(std::integral_constant<int, 2>{});
+    else if (ev == 1)
+        with_wrap(std::integral_constant<int, 1>{});
     tag.end(stream);
     return hipGetLastError();
 }
