@@ -3,6 +3,7 @@
 // HBM-bound, no index bytes are stored or read. A power-of-two group of lanes serves one row, so that
 // narrow messages (k of 4..32) still fill the 64-wide wavefront with several rows.
 #include <algorithm>
+#include <type_traits>
 
 #include "elem.h"
 #include "mask_device.h"
@@ -31,66 +32,150 @@ __global__ __launch_bounds__(kBlock) void compress_kernel(MaskRule rule, const i
         const int64_t src = rows ? int64_t(rows[row]) : row;
         const T* xr = x + src * ldx;
         T* zr = z + row * int64_t(rule.k);
-        if (rule.k == rule.width) {
-            for (uint32_t j = gl; j < rule.k; j += g) zr[j] = xr[j];
-        } else {
-            const MaskAffine m = varco_affine(rule, uint32_t(gids[row]));
-            for (uint32_t j = gl; j < rule.k; j += g) zr[j] = xr[varco_position(rule, m, j)];
-        }
-    }
-}
-
-// bf16 rows: picking the kept elements straight from memory is 64 scattered 2-byte loads per instruction, which the
-// vector memory unit takes about one per cycle. Here a wavefront copies the row into LDS with 16-byte loads (a
-// 512-wide row is one instruction), picks from there, two elements per lane, and writes 4 bytes per lane.
-// Needs width % 8 == 0, width <= kStagedWidth, k even, 16-byte aligned rows of x and 4-byte aligned rows of z.
-constexpr int kStagedWidth = 2048;
-__global__ __launch_bounds__(kBlock) void compress_staged_kernel(MaskRule rule, const int32_t* __restrict__ gids,
-                                                                 const int32_t* __restrict__ rows, int64_t n_rows,
-                                                                 const uint16_t* __restrict__ x, int64_t ldx,
-                                                                 uint16_t* __restrict__ z) {
-    __shared__ __attribute__((aligned(16))) uint16_t staged[kBlock / 64][kStagedWidth];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    uint16_t* row_lds = staged[wave];
-    const int64_t stride = int64_t(gridDim.x) * (kBlock / 64);
-    for (int64_t row = int64_t(blockIdx.x) * (kBlock / 64) + wave; row < n_rows; row += stride) {
-        const uint16_t* xr = x + (rows ? int64_t(rows[row]) : row) * ldx;
-        for (uint32_t c = lane * 8; c < rule.width; c += 512) *reinterpret_cast<uint4*>(row_lds + c) = *reinterpret_cast<const uint4*>(xr + c);
         const MaskAffine m = varco_affine(rule, uint32_t(gids[row]));
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");     // the wavefront's own LDS writes, then its reads
-        uint16_t* zr = z + row * int64_t(rule.k);
-        for (uint32_t j = 2 * lane; j < rule.k; j += 128) {
-            const uint32_t p0 = varco_position(rule, m, j);
-            uint32_t p1 = p0 + m.a;
-            if (p1 >= rule.width) p1 -= rule.width;
-            *reinterpret_cast<uint32_t*>(zr + j) = uint32_t(row_lds[p0]) | (uint32_t(row_lds[p1]) << 16);
-        }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");     // reads done before the next row overwrites the buffer
+        for (uint32_t j = gl; j < rule.k; j += g) zr[j] = xr[varco_position(rule, m, j)];
     }
 }
 
-// Full rows are written in one coalesced pass: column c holds z[j] when its inverse position j is kept.
-template <typename T>
-__global__ __launch_bounds__(kBlock) void decompress_kernel(MaskRule rule, const int32_t* __restrict__ gids,
-                                                            const int32_t* __restrict__ rows, int64_t n_rows,
-                                                            const T* __restrict__ z, T* __restrict__ x,
-                                                            int64_t ldx, int g_log2) {
-    const uint32_t g = 1u << g_log2;
-    const uint32_t gl = threadIdx.x & (g - 1);
-    const int64_t stride = (int64_t(gridDim.x) * kBlock) >> g_log2;
-    for (int64_t row = group_row(g_log2); row < n_rows; row += stride) {
-        const int64_t dst = rows ? int64_t(rows[row]) : row;
-        T* xr = x + dst * ldx;
-        const T* zr = z + row * int64_t(rule.k);
-        if (rule.k == rule.width) {
-            for (uint32_t c = gl; c < rule.width; c += g) xr[c] = zr[c];
-        } else {
-            const MaskAffine m = varco_affine(rule, uint32_t(gids[row]));
-            for (uint32_t c = gl; c < rule.width; c += g) {
-                const uint32_t j = varco_inverse_position(rule, m, c);
-                xr[c] = j < rule.k ? zr[j] : T{};
+// Encoder and decoder through LDS. Kept positions are spread over the whole row, so a row's cache lines all travel whether
+// 4 bytes of a line are wanted or 128, and element-wise accesses (64 scattered addresses per instruction) cost the vector
+// memory unit about a cycle each: instead a wavefront moves whole rows with 16-byte accesses, kRowsInFlight of them at a
+// time with the next ones already requested, and picks (encoder) or places (decoder) the kept elements in LDS. 450,000 rows
+// of 256, element-wise -> through LDS: decoder 265 -> 116 us (fp32, k = 32), 197 -> 64 (bf16, k = 64); encoder 197 -> 133
+// (fp32, k = 128), 136 -> 46 (bf16, k = 64); decoder with sum 224 -> 196 (fp32, k = 32: the rate of a copy), 194 -> 135
+// (bf16, k = 128). Where the element-wise kernels win (few kept elements, narrow or unaligned rows): codec_rows_pay.
+//   MODE 0: z[i, j] = x[row_i, pi(j)];  1: x[row_i, :] = 0 except x[row_i, pi(j)] = z[i, j];  2: x[row_i, pi(j)] += z[i, j]
+// S: the storage word (fp32 or bf16 bits); V: elements per access to x (16 bytes, or 1 for unaligned rows); PE: elements of z
+// per lane (2 for bf16 pairs); ONE: a row is at most one access per lane.
+constexpr int kRowsInFlight = 4;
+template <typename S>
+__device__ __forceinline__ S add_words(S x, S z) {
+    if constexpr (sizeof(S) == 4)
+        return __float_as_uint(__uint_as_float(x) + __uint_as_float(z));
+    else
+        return float_to_bf16(bf16_to_float(x) + bf16_to_float(z));
+}
+
+template <typename S, int MODE, int V, int PE, bool ONE>
+__global__ __launch_bounds__(kBlock) void codec_rows_kernel(MaskRule rule, const int32_t* __restrict__ gids, const int32_t* __restrict__ rows,
+                                                            int64_t n_rows, S* x, int64_t ldx, S* z, int lpe_log2) {
+    constexpr int U = kRowsInFlight;
+    typedef S Vec __attribute__((ext_vector_type(V)));
+    typedef S Pair __attribute__((ext_vector_type(PE)));
+    extern __shared__ __attribute__((aligned(16))) unsigned char codec_lds[];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int32_t width = int32_t(rule.width), k = int32_t(rule.k);
+    const int32_t pitch = (width + 7) & ~7;
+    S* const buf = reinterpret_cast<S*>(codec_lds) + wave * U * pitch;
+    const int lpe = 1 << lpe_log2, sub = lane >> lpe_log2, jl = lane & (lpe - 1), n_sub = 64 >> lpe_log2;
+    auto clear = [&]() {
+        for (int u = 0; u < U; ++u)
+            for (int c = lane * V; c < width; c += 64 * V) *reinterpret_cast<Vec*>(buf + u * pitch + c) = Vec(S(0));
+    };
+    if (MODE != 0) clear();
+    const int64_t stride = int64_t(gridDim.x) * (kBlock / 64) * U;
+    int64_t r0 = (int64_t(blockIdx.x) * (kBlock / 64) + wave) * U;
+    if (r0 >= n_rows) return;                        // wavefronts are independent: no barrier
+    // Software pipeline over groups of U rows: the rows' ids are fetched two groups ahead, their data one group ahead.
+    int32_t gid = 0, src = 0;                        // lane u: of row u of a group (past the end: the last row)
+    auto load_ids = [&](int64_t r) {
+        const int64_t i = min(r + (lane & (U - 1)), n_rows - 1);
+        gid = gids[i];
+        src = rows ? rows[i] : int32_t(i);
+    };
+    int64_t at[U];                                   // element offset of the group's rows in x
+    uint32_t ab = 0;
+    auto resolve = [&]() {
+        const MaskAffine m = varco_affine(rule, uint32_t(gid));
+        ab = m.a | (m.b << 16);
+#pragma unroll
+        for (int u = 0; u < U; ++u) at[u] = int64_t(__shfl(src, u)) * ldx;
+    };
+    Vec v[U];
+    const int own = min(lane * V, width - V);        // lanes past the row repeat its last access (never stored)
+    auto load_rows = [&]() {
+        if constexpr (ONE && MODE != 1) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) v[u] = *reinterpret_cast<const Vec*>(x + at[u] + own);
+        }
+    };
+    load_ids(r0);
+    resolve();
+    load_rows();
+    if (r0 + stride < n_rows) load_ids(r0 + stride);
+    for (; r0 < n_rows; r0 += stride) {
+        const int n_here = int(min(int64_t(U), n_rows - r0));
+        const uint32_t ab_now = ab;
+        int64_t at_now[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) at_now[u] = at[u];
+        Vec old[MODE == 2 ? U : 1];
+        if constexpr (MODE == 0) {
+            if constexpr (ONE) {
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    if (lane * V < width) *reinterpret_cast<Vec*>(buf + u * pitch + lane * V) = v[u];
+            } else {
+                for (int c = lane * V; c < width; c += 64 * V)
+#pragma unroll
+                    for (int u = 0; u < U; ++u) *reinterpret_cast<Vec*>(buf + u * pitch + c) = *reinterpret_cast<const Vec*>(x + at_now[u] + c);
+            }
+        } else if constexpr (MODE == 2 && ONE) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) old[u] = v[u];
+        }
+        if (r0 + stride < n_rows) {
+            resolve();
+            load_rows();
+            if (r0 + 2 * stride < n_rows) load_ids(r0 + 2 * stride);
+        }
+        __builtin_amdgcn_wave_barrier();
+        // the kept elements: a group of lanes serves one row, the groups different rows
+        for (int u0 = 0; u0 < n_here; u0 += n_sub) {
+            const int u = u0 + sub;
+            const uint32_t m = __shfl(ab_now, u & (U - 1)), a = m & 0xFFFFu;
+            if (u < n_here) {
+                S* const row = buf + u * pitch;
+                for (int j = jl * PE; j < k; j += lpe * PE) {
+                    uint32_t q = varco_mod_width(__umul24(a, uint32_t(j)) + (m >> 16), rule.width, rule.width_magic);
+                    Pair* const zp = reinterpret_cast<Pair*>(z + (r0 + u) * k + j);
+                    Pair e;
+                    if constexpr (MODE != 0) e = *zp;
+#pragma unroll
+                    for (int i = 0; i < PE; ++i) {
+                        if constexpr (MODE == 0)
+                            e[i] = row[q];
+                        else
+                            row[q] = e[i];
+                        q += a;
+                        q = min(q, q - rule.width);
+                    }
+                    if (MODE == 0) *zp = e;
+                }
             }
         }
+        __builtin_amdgcn_wave_barrier();
+        if (MODE == 0) continue;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (u >= n_here) break;
+            for (int c = lane * V; c < width; c += 64 * V) {
+                Vec o = *reinterpret_cast<const Vec*>(buf + u * pitch + c);
+                S* const dst = x + at_now[u] + c;
+                if constexpr (MODE == 2) {
+                    Vec before;
+                    if constexpr (ONE)
+                        before = old[u];
+                    else
+                        before = *reinterpret_cast<const Vec*>(dst);
+#pragma unroll
+                    for (int i = 0; i < V; ++i) o[i] = add_words<S>(before[i], o[i]);
+                }
+                *reinterpret_cast<Vec*>(dst) = o;
+            }
+        }
+        clear();
+        __builtin_amdgcn_wave_barrier();
     }
 }
 
@@ -108,10 +193,9 @@ __global__ __launch_bounds__(kBlock) void decompress_add_kernel(MaskRule rule, c
         const int64_t dst = rows ? int64_t(rows[row]) : row;
         T* xr = x + dst * ldx;
         const T* zr = z + row * int64_t(rule.k);
-        MaskAffine m{1, 0, 1};
-        if (rule.k != rule.width) m = varco_affine(rule, uint32_t(gids[row]));
+        const MaskAffine m = varco_affine(rule, uint32_t(gids[row]));
         for (uint32_t j = gl; j < rule.k; j += g) {
-            T* dstp = xr + (rule.k == rule.width ? j : varco_position(rule, m, j));
+            T* dstp = xr + varco_position(rule, m, j);
             Elem<T>::store(dstp, Elem<T>::load(dstp) + Elem<T>::load(zr + j));
         }
     }
@@ -229,16 +313,106 @@ __global__ __launch_bounds__(kBlock) void halo_rows_kernel(MaskRule rule, const 
     out[s] = make_uint2(ab, uint32_t(zrow[s]));
 }
 
+// Whether whole rows through LDS beat element-wise accesses (measured over widths 75 to 512 and ratios 2 to 64). The decoder
+// writes whole rows either way. The encoder's element-wise form costs per kept element, the other one per row: the line lies
+// at an eighth (fp32) or a sixteenth (bf16) of the row, at a quarter for rows that take one element per access. Adding
+// element-wise also spares the write-back of untouched sectors, so the line is higher for rows that leave half of a
+// wavefront's 16-byte accesses unused.
+template <typename T, int MODE>
+bool codec_rows_pay(const MaskRule& rule, const void* x, int64_t ldx) {
+    if (rule.k >= rule.width) return false;
+    if (MODE == 1) return true;
+    constexpr uint32_t V16 = 16 / sizeof(T);
+    const bool vec = rule.width % V16 == 0 && ldx % V16 == 0 && (reinterpret_cast<uintptr_t>(x) & 15u) == 0;
+    uint32_t part = MODE == 0 ? (vec ? (sizeof(T) == 4 ? 8 : 16) : 4) : 2;
+    if (MODE == 2 && vec) part = rule.width * sizeof(T) >= 512 ? (sizeof(T) == 4 ? 16 : 8) : (sizeof(T) == 4 ? 4 : 2);
+    return rule.k * part >= rule.width;
+}
+
+// Everything is kept: rows are copied (TO_Z: x -> z, else z -> x) or added to x, V elements per access.
+template <typename S, int V, bool TO_Z, bool ADD>
+__global__ __launch_bounds__(kBlock) void whole_rows_kernel(const int32_t* __restrict__ rows, int64_t n_rows, S* x, int64_t ldx, S* z, int32_t width,
+                                                            int g_log2) {
+    typedef S Vec __attribute__((ext_vector_type(V)));
+    const int g = 1 << g_log2, gl = threadIdx.x & (g - 1);
+    const int64_t stride = (int64_t(gridDim.x) * kBlock) >> g_log2;
+    for (int64_t row = group_row(g_log2); row < n_rows; row += stride) {
+        S* const xr = x + (rows ? int64_t(rows[row]) : row) * ldx;
+        S* const zr = z + row * width;
+        for (int c = gl * V; c < width; c += g * V) {
+            if constexpr (TO_Z) {
+                *reinterpret_cast<Vec*>(zr + c) = *reinterpret_cast<const Vec*>(xr + c);
+            } else {
+                Vec v = *reinterpret_cast<const Vec*>(zr + c);
+                if constexpr (ADD) {
+                    const Vec old = *reinterpret_cast<const Vec*>(xr + c);
+#pragma unroll
+                    for (int i = 0; i < V; ++i) v[i] = add_words<S>(old[i], v[i]);
+                }
+                *reinterpret_cast<Vec*>(xr + c) = v;
+            }
+        }
+    }
+}
+
+template <typename T, bool TO_Z, bool ADD>
+hipError_t launch_whole_rows(const MaskRule& rule, const int32_t* rows, int64_t n_rows, void* x, int64_t ldx, void* z, hipStream_t stream) {
+    using S = std::conditional_t<sizeof(T) == 2, uint16_t, uint32_t>;
+    constexpr int V16 = 16 / int(sizeof(S));
+    // (adding fp32 rows is bound by the copy rate and ran 5 % slower with wide accesses)
+    const bool vec = !(ADD && sizeof(S) == 4) && rule.width % V16 == 0 && ldx % V16 == 0 &&
+                     ((reinterpret_cast<uintptr_t>(x) | reinterpret_cast<uintptr_t>(z)) & 15u) == 0;
+    const int gl = group_log2(vec ? rule.width / V16 : rule.width);
+    auto go = [&](auto vc) {
+        hipLaunchKernelGGL((whole_rows_kernel<S, decltype(vc)::value, TO_Z, ADD>), dim3(grid_for(n_rows, gl)), dim3(kBlock), 0, stream, rows, n_rows,
+                           static_cast<S*>(x), ldx, static_cast<S*>(z), int32_t(rule.width), gl);
+    };
+    if (vec)
+        go(std::integral_constant<int, V16>{});
+    else
+        go(std::integral_constant<int, 1>{});
+    return hipGetLastError();
+}
+
+template <typename T, int MODE>
+hipError_t launch_codec_rows(const MaskRule& rule, const int32_t* gids, const int32_t* rows, int64_t n_rows, void* x, int64_t ldx, void* z,
+                             hipStream_t stream) {
+    using S = std::conditional_t<sizeof(T) == 2, uint16_t, uint32_t>;
+    constexpr int V16 = 16 / int(sizeof(S));
+    constexpr int W = kBlock / 64;
+    const bool vec = rule.width % V16 == 0 && ldx % V16 == 0 && (reinterpret_cast<uintptr_t>(x) & 15u) == 0;
+    const bool pair = sizeof(S) == 2 && rule.k % 2 == 0 && (reinterpret_cast<uintptr_t>(z) & 3u) == 0;
+    const bool one = int(rule.width) <= 64 * (vec ? V16 : 1);
+    const int lpe = group_log2(pair ? rule.k / 2 : rule.k);
+    const size_t lds = size_t(W) * kRowsInFlight * ((rule.width + 7) & ~7u) * sizeof(S);
+    const int64_t blocks = std::min<int64_t>((n_rows + W * kRowsInFlight - 1) / (W * kRowsInFlight), 256 * 32);
+    auto go = [&](auto vc, auto pc, auto oc) {
+        hipLaunchKernelGGL((codec_rows_kernel<S, MODE, decltype(vc)::value, decltype(pc)::value, decltype(oc)::value>), dim3(unsigned(blocks)),
+                           dim3(kBlock), lds, stream, rule, gids, rows, n_rows, static_cast<S*>(x), ldx, static_cast<S*>(z), lpe);
+    };
+    auto with_one = [&](auto vc, auto pc) {
+        if (one)
+            go(vc, pc, std::true_type{});
+        else
+            go(vc, pc, std::false_type{});
+    };
+    auto with_pair = [&](auto vc) {
+        if constexpr (sizeof(S) == 2)
+            if (pair) return with_one(vc, std::integral_constant<int, 2>{});
+        with_one(vc, std::integral_constant<int, 1>{});
+    };
+    if (vec)
+        with_pair(std::integral_constant<int, V16>{});
+    else
+        with_pair(std::integral_constant<int, 1>{});
+    return hipGetLastError();
+}
+
 template <typename T>
 hipError_t launch_compress_t(const MaskRule& rule, const int32_t* gids, const int32_t* rows, int64_t n_rows, const void* x,
                              int64_t ldx, void* z, hipStream_t stream) {
-    if (sizeof(T) == 2 && rule.k < rule.width && rule.k % 2 == 0 && rule.width % 8 == 0 && rule.width <= uint32_t(kStagedWidth) &&
-        ldx % 8 == 0 && (reinterpret_cast<uintptr_t>(x) & 15u) == 0 && (reinterpret_cast<uintptr_t>(z) & 3u) == 0) {
-        const int64_t blocks = std::min<int64_t>((n_rows + kBlock / 64 - 1) / (kBlock / 64), 256 * 8);
-        hipLaunchKernelGGL(compress_staged_kernel, dim3(unsigned(blocks)), dim3(kBlock), 0, stream, rule, gids, rows, n_rows,
-                           static_cast<const uint16_t*>(x), ldx, static_cast<uint16_t*>(z));
-        return hipGetLastError();
-    }
+    if (rule.k == rule.width) return launch_whole_rows<T, true, false>(rule, rows, n_rows, const_cast<void*>(x), ldx, z, stream);
+    if (codec_rows_pay<T, 0>(rule, x, ldx)) return launch_codec_rows<T, 0>(rule, gids, rows, n_rows, const_cast<void*>(x), ldx, z, stream);
     const int gl = group_log2(rule.k);
     hipLaunchKernelGGL(compress_kernel<T>, dim3(grid_for(n_rows, gl)), dim3(kBlock), 0, stream, rule, gids, rows, n_rows,
                        static_cast<const T*>(x), ldx, static_cast<T*>(z), gl);
@@ -248,15 +422,15 @@ hipError_t launch_compress_t(const MaskRule& rule, const int32_t* gids, const in
 template <typename T>
 hipError_t launch_decompress_t(const MaskRule& rule, const int32_t* gids, const int32_t* rows, int64_t n_rows,
                                const void* z, void* x, int64_t ldx, int accumulate, hipStream_t stream) {
-    if (accumulate) {
-        const int gl = group_log2(rule.k);
-        hipLaunchKernelGGL(decompress_add_kernel<T>, dim3(grid_for(n_rows, gl)), dim3(kBlock), 0, stream, rule, gids,
-                           rows, n_rows, static_cast<const T*>(z), static_cast<T*>(x), ldx, gl);
-    } else {
-        const int gl = group_log2(rule.width);
-        hipLaunchKernelGGL(decompress_kernel<T>, dim3(grid_for(n_rows, gl)), dim3(kBlock), 0, stream, rule, gids, rows,
-                           n_rows, static_cast<const T*>(z), static_cast<T*>(x), ldx, gl);
-    }
+    void* const zw = const_cast<void*>(z);
+    if (rule.k == rule.width)
+        return accumulate ? launch_whole_rows<T, false, true>(rule, rows, n_rows, x, ldx, zw, stream)
+                          : launch_whole_rows<T, false, false>(rule, rows, n_rows, x, ldx, zw, stream);
+    if (!accumulate) return launch_codec_rows<T, 1>(rule, gids, rows, n_rows, x, ldx, zw, stream);
+    if (codec_rows_pay<T, 2>(rule, x, ldx)) return launch_codec_rows<T, 2>(rule, gids, rows, n_rows, x, ldx, zw, stream);
+    const int gl = group_log2(rule.k);
+    hipLaunchKernelGGL(decompress_add_kernel<T>, dim3(grid_for(n_rows, gl)), dim3(kBlock), 0, stream, rule, gids, rows, n_rows,
+                       static_cast<const T*>(z), static_cast<T*>(x), ldx, gl);
     return hipGetLastError();
 }
 

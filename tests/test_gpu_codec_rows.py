@@ -1,0 +1,51 @@
+"""Encoder and decoders on aligned rows (16-byte accesses, rows through LDS) at the edges of their groups of rows and of the
+rules that choose between the forms; compared bit for bit with the oracle."""
+import numpy as np
+import pytest
+import torch
+
+from gpu_common import KEY, dev
+from oracle import layer as olayer
+from oracle import mask as omask
+from oracle.rounding import round_bf16
+from paper_2406_17611_amd import binding as vb
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n_rows", [1, 3, 4, 1025])
+@pytest.mark.parametrize("dtype,width,ratio", [("f32", 256, (8, 1)), ("f32", 256, (32, 1)), ("f32", 260, (2, 1)), ("f32", 12, (4, 1)),
+                                               ("f32", 2048, (4, 1)), ("f32", 256, (1, 1)), ("bf16", 512, (4, 1)), ("bf16", 512, (7, 1)),
+                                               ("bf16", 520, (64, 1)), ("bf16", 8, (2, 1)), ("bf16", 2048, (3, 1)), ("bf16", 256, (1, 1))])
+def test_aligned_rows(dtype, width, ratio, n_rows):
+    bf16 = dtype == "bf16"
+    rng = np.random.default_rng(width + n_rows)
+    stored = (lambda a: round_bf16(a).astype(np.float32)) if bf16 else (lambda a: np.asarray(a, dtype=np.float32))
+    tdt = torch.bfloat16 if bf16 else torch.float32
+    n_src = n_rows + 7
+    x = stored(rng.standard_normal((n_src, width)))
+    rows = np.sort(rng.permutation(n_src)[:n_rows]).astype(np.int32)
+    gids = rng.integers(0, 2_449_029, size=n_rows).astype(np.int32)
+    ctx = vb.Context([8, width, 8], [1, 0], vb.CONV_GCN, 1, KEY, vb.BF16 if bf16 else vb.F32)
+    ctx.prepare()
+    ctx.begin_step(6)
+    ctx.set_ratio(1, *ratio)
+    k = ctx.keep(1)
+    cols = omask.kept_columns(gids, width, k, KEY, 6, 1)
+    xd, rd, gd = dev(x, tdt), dev(rows), dev(gids)
+    z = torch.zeros((n_rows + 1, k), dtype=tdt, device="cuda")          # one row of slack: must stay untouched
+    ctx.compress(1, gd, rd, n_rows, xd, width, z)
+    want_z = olayer.compress(x, rows, cols).astype(np.float32)
+    assert np.array_equal(z[:n_rows].float().cpu().numpy(), want_z) and not z[n_rows].any()
+    out = torch.full((n_src, width), 7.0, dtype=tdt, device="cuda")
+    ctx.decompress(1, gd, rd, n_rows, z, out, width, 0)
+    want = np.full((n_src, width), 7.0, dtype=np.float32)
+    want[rows] = olayer.decompress(want_z.astype(np.float64), cols, width).astype(np.float32)
+    assert np.array_equal(out.float().cpu().numpy(), want)
+    acc = dev(x, tdt)
+    ctx.decompress(1, gd, rd, n_rows, z, acc, width, 1)
+    want_acc = x.copy()
+    for i in range(n_rows):
+        want_acc[rows[i], cols[i]] = stored(want_acc[rows[i], cols[i]] + want_z[i])
+    assert np.array_equal(acc.float().cpu().numpy(), want_acc)
+    ctx.close()
