@@ -272,35 +272,63 @@ __global__ __launch_bounds__(kThreads, 4) void gemm_kernel(GemmDev g) {
     }
 }
 
-// C (+)= sum over splits of partial[s]. 64 consecutive output elements per workgroup; the four wavefronts
-// sum interleaved quarters of the splits (several loads in flight each) and the quarters are added in a
-// fixed order, so the result does not depend on scheduling.
+// Sum over `splits` partial products of element i. 64 consecutive output elements per workgroup; the four wavefronts sum
+// interleaved quarters of the splits (eight loads in flight each) and the quarters are added in a fixed order, so the
+// result does not depend on scheduling. Valid in the first wavefront.
+__device__ __forceinline__ float sum_splits(const float* partial, int32_t splits, int64_t mn, int64_t i, bool in) {
+    __shared__ float part[4][64];
+    const int e = threadIdx.x & 63, quarter = threadIdx.x >> 6;
+    float x = 0.f;
+    if (in) {
+        int32_t s = quarter;
+        for (; s + 28 < splits; s += 32) {
+            float v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = partial[int64_t(s + 4 * u) * mn + i];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) x += v[u];
+        }
+        float v[7];                     // the rest, fetched together as well (slots past the end re-read slot 0 and are dropped)
+#pragma unroll
+        for (int u = 0; u < 7; ++u) v[u] = partial[int64_t(s + 4 * u < splits ? s + 4 * u : 0) * mn + i];
+#pragma unroll
+        for (int u = 0; u < 7; ++u)
+            if (s + 4 * u < splits) x += v[u];
+    }
+    part[quarter][e] = x;
+    __syncthreads();
+    return ((part[0][e] + part[1][e]) + part[2][e]) + part[3][e];
+}
+
+// C (+)= sum over splits of partial[s].
 template <typename TC>
 __global__ __launch_bounds__(kThreads) void gemm_reduce_kernel(const float* partial, int32_t splits, int64_t mn,
                                                                int32_t n, TC* c, int64_t ldc, int32_t accumulate,
                                                                int32_t relu) {
-    __shared__ float part[4][64];
-    const int e = threadIdx.x & 63, quarter = threadIdx.x >> 6;
-    const int64_t i = int64_t(blockIdx.x) * 64 + e;
-    float x = 0.f;
-    if (i < mn) {
-        int32_t s = quarter;
-        for (; s + 12 < splits; s += 16) {
-            const float x0 = partial[int64_t(s) * mn + i], x1 = partial[int64_t(s + 4) * mn + i];
-            const float x2 = partial[int64_t(s + 8) * mn + i], x3 = partial[int64_t(s + 12) * mn + i];
-            x += x0, x += x1, x += x2, x += x3;
-        }
-        for (; s < splits; s += 4) x += partial[int64_t(s) * mn + i];
-    }
-    part[quarter][e] = x;
-    __syncthreads();
-    if (quarter == 0 && i < mn) {
-        x = ((part[0][e] + part[1][e]) + part[2][e]) + part[3][e];
-        TC* dst = c + (i / n) * ldc + (i % n);
-        if (accumulate) x += Elem<TC>::load(dst);
-        if (relu) x = fmaxf(x, 0.f);
-        Elem<TC>::store(dst, x);
-    }
+    const int64_t i = int64_t(blockIdx.x) * 64 + (threadIdx.x & 63);
+    float x = sum_splits(partial, splits, mn, i, i < mn);
+    if (threadIdx.x >= 64 || i >= mn) return;
+    TC* dst = c + (i / n) * ldc + (i % n);
+    if (accumulate) x += Elem<TC>::load(dst);
+    if (relu) x = fmaxf(x, 0.f);
+    Elem<TC>::store(dst, x);
+}
+
+// The same for several fp32 results (the weight gradients of all layers of a pass).
+struct ReduceJobs {
+    ReduceJob job[kMaxReduceJobs];
+    int32_t n, accumulate;
+};
+__global__ __launch_bounds__(kThreads) void gemm_reduce_jobs_kernel(ReduceJobs jobs) {
+    int32_t at = 0;
+    while (at + 1 < jobs.n && int32_t(blockIdx.x) >= jobs.job[at + 1].first_block) ++at;
+    const ReduceJob& jb = jobs.job[at];
+    const int64_t mn = int64_t(jb.m) * jb.n, i = int64_t(int32_t(blockIdx.x) - jb.first_block) * 64 + (threadIdx.x & 63);
+    float x = sum_splits(jb.partial, jb.splits, mn, i, i < mn);
+    if (threadIdx.x >= 64 || i >= mn) return;
+    float* dst = jb.c + (i / jb.n) * jb.ldc + (i % jb.n);
+    if (jobs.accumulate) x += *dst;
+    *dst = x;
 }
 
 // Loads of 4 elements are legal for an operand when its base (and gate) are aligned to them, its leading
@@ -520,8 +548,46 @@ hipError_t varco_launch_gemm_reduce(const float* partial, int32_t slabs, int32_t
     return launch_reduce(ga, slabs, stream, tag);
 }
 
+hipError_t varco_launch_gemm_reduce_jobs(ReduceJob* jobs, int n, bool accumulate, hipStream_t stream, const LaunchTag& tag) {
+    if (n > kMaxReduceJobs) return hipErrorInvalidValue;
+    ReduceJobs args{};
+    int64_t blocks = 0;
+    double bytes = 0.0;
+    for (int i = 0; i < n; ++i) {
+        ReduceJob& j = jobs[i];
+        const int64_t mn = int64_t(j.m) * j.n;
+        if (j.splits <= 1 || mn == 0) continue;
+        j.first_block = int32_t(blocks);
+        blocks += (mn + 63) / 64;
+        bytes += double(mn) * 4.0 * (j.splits + (accumulate ? 2.0 : 1.0));
+        args.job[args.n++] = j;
+    }
+    args.accumulate = accumulate ? 1 : 0;
+    if (blocks == 0) return hipSuccess;
+    tag.begin_as(VARCO_K_REDUCE, stream, bytes);
+    hipLaunchKernelGGL(gemm_reduce_jobs_kernel, dim3(unsigned(blocks)), dim3(kThreads), 0, stream, args);
+    tag.end(stream);
+    return hipGetLastError();
+}
+
+bool varco_gemm_short_usable(const GemmArgs& ga) { return small_k_usable(ga); }
+
+bool varco_gemm_dual_usable(const GemmArgs& ga) {
+    if (!ga.c_dual || ga.m == 0 || ga.n == 0) return false;
+    if (ga.a.transposed && !ga.deferred) return false;               // partial products of both are summed by the caller
+    if (small_k_usable(ga)) return ga.b_dual && (ga.a.dtype == VARCO_BF16 || ga.f32_terms == 2 || ga.f32_terms == 3);
+    return varco_gemm_bf16_usable(ga) || varco_gemm_split_usable(ga);
+}
+
 hipError_t varco_launch_gemm(const GemmArgs& ga, hipStream_t stream, const LaunchTag& tag) {
+    if (ga.deferred) *ga.deferred = 1;
     if (ga.m == 0 || ga.n == 0) return hipSuccess;
+    // partial products of a split reduction are summed here, or by the caller
+    auto finish = [&](int32_t split) {
+        if (ga.deferred) *ga.deferred = split;
+        return split <= 1 || ga.deferred ? hipSuccess : launch_reduce(ga, split, stream, tag);
+    };
+    if (ga.c_dual && !varco_gemm_dual_usable(ga)) return hipErrorInvalidValue;
     if (small_k_usable(ga)) {
         tag.begin(stream);
         hipError_t e = hipSuccess;
@@ -537,14 +603,12 @@ hipError_t varco_launch_gemm(const GemmArgs& ga, hipStream_t stream, const Launc
     if (varco_gemm_bf16_usable(ga)) {
         int32_t split = 1;
         const hipError_t e = varco_launch_gemm_bf16(ga, stream, tag, &split);
-        if (e != hipSuccess || split <= 1) return e;
-        return launch_reduce(ga, split, stream, tag);
+        return e != hipSuccess ? e : finish(split);
     }
     if (varco_gemm_split_usable(ga)) {
         int32_t split = 1;
         const hipError_t e = varco_launch_gemm_split(ga, stream, tag, &split);
-        if (e != hipSuccess || split <= 1) return e;
-        return launch_reduce(ga, split, stream, tag);
+        return e != hipSuccess ? e : finish(split);
     }
     // A is M x K: k-contiguous as stored unless transposed. B is K x N: k-contiguous only when transposed.
     const bool a_kc = !ga.a.transposed, b_kc = ga.b.transposed;
@@ -626,6 +690,5 @@ hipError_t varco_launch_gemm(const GemmArgs& ga, hipStream_t stream, const Launc
     tag.end(stream);
     hipError_t err = hipGetLastError();
     if (err != hipSuccess) return err;
-    if (split > 1) err = launch_reduce(ga, split, stream, tag);
-    return err;
+    return finish(split);
 }

@@ -1,7 +1,7 @@
 // Dense feature transform of eq. (2) and its gradients for bf16-stored activations, on the bf16 matrix
 // cores with fp32 accumulation (v_mfma_f32_32x32x16_bf16): X_out = act(M H1 + X H0), dM = dZ H1^T,
 // dH += M^T dZ. Weights are kept in fp32 by the caller; the library hands this kernel a bf16 copy laid out
-// [output index][reduction index] (see varco_launch_prep_weight), and weight gradients leave in fp32.
+// [output index][reduction index] (see varco_launch_prep_weights), and weight gradients leave in fp32.
 //
 // One 256-thread workgroup (4 wavefronts) computes a 256 x 128 tile of C (256 x 64 for outputs at most 64
 // columns wide). A wavefront owns 128 x 64 (or 64 x 64) of it as 32 x 32 blocks: at bf16 rates a wavefront
@@ -47,6 +47,8 @@ struct GemmDev {
     float* partial;
     int32_t tiles_m, tiles_n;
     int32_t inner, outer;
+    const uint16_t* dual;            // second A (TN) or second weight copy (NT), or null
+    void* c_dual;
 };
 
 // Two bf16 values packed in a word: keep each where the packed gate value is > 0.
@@ -249,17 +251,24 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_bf16_kernel(GemmDev g) {
     const int32_t in = within % g.inner, out = (within / g.inner) * 8 + xcd;
     if (out >= g.outer) return;        // whole workgroup leaves together: no barrier is skipped
     int32_t tm, tn, z;
-    if (g.split_k > 1) {
-        z = out, tm = in / g.tiles_n, tn = in % g.tiles_n;
+    bool second = false;               // this workgroup's tile belongs to the dual product
+    if (g.split_k > 1 || TN) {
+        const int32_t tiles = g.tiles_m * g.tiles_n;
+        second = in >= tiles;
+        const int32_t tile = second ? in - tiles : in;
+        z = out, tm = tile / g.tiles_n, tn = tile % g.tiles_n;
     } else {
-        z = 0, tm = out, tn = in;
+        second = in >= g.tiles_n;
+        z = 0, tm = out, tn = second ? in - g.tiles_n : in;
     }
+    const uint16_t* const a_ptr = TN && second ? g.dual : g.a.ptr;
+    const uint16_t* const b_ptr = !TN && second ? g.dual : g.b.ptr;
     const int32_t m0 = tm * BM, n0 = tn * BN;
 
     const int32_t tiles1 = (g.k + BK - 1) / BK;
     const int32_t tiles2 = (g.k2 + BK - 1) / BK;
     int32_t t_begin = 0, t_end = tiles1 + tiles2;
-    if (g.split_k > 1) {
+    if (g.split_k > 1 || TN) {
         t_begin = z * g.tiles_per_split;
         t_end = min(t_end, t_begin + g.tiles_per_split);
     }
@@ -283,8 +292,8 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_bf16_kernel(GemmDev g) {
     auto fetch = [&](int32_t t) {
         const bool first = t < tiles1;
         OperandDev oa, ob;
-        oa.ptr = first ? g.a.ptr : g.a2.ptr, oa.gate = first ? g.a.gate : g.a2.gate, oa.ld = first ? g.a.ld : g.a2.ld;
-        ob.ptr = first ? g.b.ptr : g.b2.ptr, ob.gate = first ? g.b.gate : g.b2.gate, ob.ld = first ? g.b.ld : g.b2.ld;
+        oa.ptr = first ? a_ptr : g.a2.ptr, oa.gate = first ? g.a.gate : g.a2.gate, oa.ld = first ? g.a.ld : g.a2.ld;
+        ob.ptr = first ? b_ptr : g.b2.ptr, ob.gate = first ? g.b.gate : g.b2.gate, ob.ld = first ? g.b.ld : g.b2.ld;
         const int32_t k0 = (first ? t : t - tiles1) * BK, kmax = first ? g.k : g.k2;
         StageA::load(oa, m0, g.m, k0, kmax, ra);
         StageB::load(ob, n0, g.n, k0, kmax, rb);
@@ -327,7 +336,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_bf16_kernel(GemmDev g) {
     // addresses), not one round trip per element.
     const int32_t col_base = n0 + wn + lrow;
     if (g.split_k > 1) {
-        float* pout = g.partial + int64_t(z) * g.m * g.n;
+        float* pout = g.partial + (int64_t(second ? g.split_k : 0) + z) * g.m * g.n;
 #pragma unroll
         for (int i = 0; i < TMB; ++i)
 #pragma unroll
@@ -339,7 +348,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_bf16_kernel(GemmDev g) {
                 }
         return;
     }
-    TC* const base = static_cast<TC*>(g.c);
+    TC* const base = static_cast<TC*>(second ? g.c_dual : g.c);
     const bool add_old = g.accumulate, relu = g.relu;
     auto finish = [&](auto guard) {
         constexpr bool GUARD = decltype(guard)::value;
@@ -384,19 +393,6 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_bf16_kernel(GemmDev g) {
         finish(std::true_type{});
 }
 
-// out[r][c] (bf16, pitch `pitch` >= cols, zero beyond cols) = transpose ? h[c][r] : h[r][c], h fp32 with
-// leading dimension ld.
-__global__ __launch_bounds__(kThreads) void prep_weight_kernel(const float* __restrict__ h, int64_t ld, int32_t rows,
-                                                               int32_t cols, int32_t pitch, int32_t transpose,
-                                                               bf16_t* __restrict__ out) {
-    const int64_t idx = int64_t(blockIdx.x) * kThreads + threadIdx.x;
-    if (idx >= int64_t(rows) * pitch) return;
-    const int32_t r = int32_t(idx / pitch), c = int32_t(idx % pitch);
-    float x = 0.f;
-    if (c < cols) x = transpose ? h[int64_t(c) * ld + r] : h[int64_t(r) * ld + c];
-    Elem<bf16_t>::store(out + idx, x);
-}
-
 bool aligned_to(const void* p, uintptr_t bytes) { return (reinterpret_cast<uintptr_t>(p) & (bytes - 1)) == 0; }
 
 template <class F>
@@ -408,15 +404,6 @@ void with_flag(bool b, F&& f) {
 }
 
 }  // namespace
-
-hipError_t varco_launch_prep_weight(const float* h, int64_t ld, int32_t rows, int32_t cols, int32_t pitch, bool transpose,
-                                    void* out, hipStream_t stream) {
-    const int64_t total = int64_t(rows) * pitch;
-    if (total == 0) return hipSuccess;
-    hipLaunchKernelGGL(prep_weight_kernel, dim3(unsigned((total + kThreads - 1) / kThreads)), dim3(kThreads), 0, stream, h,
-                       ld, rows, cols, pitch, transpose ? 1 : 0, static_cast<bf16_t*>(out));
-    return hipGetLastError();
-}
 
 namespace {
 // TN: B can be read four columns at a time.
@@ -436,9 +423,10 @@ bool varco_gemm_bf16_usable(const GemmArgs& ga) {
         if (ga.k2 > 0 && (!ga.b2_prep || ga.b2_prep_ld % 8 != 0 || !aligned_to(ga.b2_prep, 16) || ga.k2 % 4 != 0 ||
                           !ok8(ga.a2) || ga.a2.gate || ga.a2.dtype != VARCO_BF16 || ga.a2.transposed))
             return false;
-        return true;
+        return !ga.c_dual || (ga.k2 == 0 && ga.split_k <= 1 && ga.b_dual_prep && aligned_to(ga.b_dual_prep, 16));
     }
     // TN: weight gradient
+    if (ga.c_dual && (!ga.a_dual || !aligned_to(ga.a_dual, 8))) return false;
     if (b_kc || ga.b.dtype != VARCO_BF16 || ga.c_dtype != VARCO_F32 || ga.k2 > 0 || ga.a.gate) return false;
     if (!ok8(ga.a) || ga.m % 4 != 0) return false;
     return b_vector_ok(ga) || (ga.n <= 64 && !ga.b.gate && aligned_to(ga.b.ptr, 2));   // else B element by element
@@ -481,11 +469,14 @@ hipError_t varco_launch_gemm_bf16(const GemmArgs& ga, hipStream_t stream, const 
     g.split_k = split;
     g.partial = ga.partial;
     if (split > 1 && !ga.partial) return hipErrorInvalidValue;
-    if (split > 1) {
-        g.inner = g.tiles_m * g.tiles_n;
+    g.dual = ga.c_dual ? u16(tn ? ga.a_dual : ga.b_dual_prep) : nullptr;
+    g.c_dual = ga.c_dual;
+    const int32_t products = ga.c_dual ? 2 : 1;     // the dual product's tiles come right behind the first one's, on the same XCD
+    if (split > 1 || tn) {
+        g.inner = g.tiles_m * g.tiles_n * products;
         g.outer = split;
     } else {
-        g.inner = g.tiles_n;
+        g.inner = g.tiles_n * products;
         g.outer = g.tiles_m;
     }
     const int64_t blocks = int64_t((g.outer + 7) / 8 * 8) * g.inner;

@@ -13,7 +13,7 @@
 // reduction steps is fetched into registers one step ahead, then expanded and written to LDS as TERMS planes of
 // bf16 rows (one output index per row, reduction index contiguous, 80-byte pitch).
 //   "NT" products (transform, input gradient): A has the reduction index contiguous and is expanded here;
-//        B is the library's own expanded copy of the weights (varco_launch_prep_weight_split), zero-padded
+//        B is the library's own expanded copy of the weights (varco_launch_prep_weights), zero-padded
 //        to whole tiles and copied as is.
 //   "TN" products (weight gradient, reduction over nodes): both operands have the node index as the slow
 //        one; a thread loads an 8 (nodes) x 4 (columns) block with eight 16-byte loads and expands the values of
@@ -52,6 +52,8 @@ struct SplitGemm {
     float* partial;
     int32_t tiles_m, tiles_n;
     int32_t inner, outer;            // tiles along the fast and the slow direction of the workgroup order
+    const void* dual;                // second A (TN) or second expanded B (NT), or null
+    float* c_dual;
 };
 
 
@@ -327,13 +329,20 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_split_kernel(SplitGemm g) {
     const int32_t tiles2 = (g.k2 + BK - 1) / BK;
     int32_t t_begin = 0, t_end = tiles1 + tiles2;
     int32_t tm, tn, z;
-    if (g.split_k > 1) {
+    bool second = false;             // this workgroup's tile belongs to the dual product
+    if (g.split_k > 1 || TN) {
         t_begin = out * g.tiles_per_split;
         t_end = min(t_end, t_begin + g.tiles_per_split);
-        z = out, tm = in / g.tiles_n, tn = in % g.tiles_n;
+        const int32_t tiles = g.tiles_m * g.tiles_n;
+        second = in >= tiles;
+        const int32_t tile = second ? in - tiles : in;
+        z = out, tm = tile / g.tiles_n, tn = tile % g.tiles_n;
     } else {
-        z = 0, tm = out, tn = in;
+        second = in >= g.tiles_n;
+        z = 0, tm = out, tn = second ? in - g.tiles_n : in;
     }
+    const void* const a_ptr = TN && second ? g.dual : g.a.ptr;
+    const void* const b_ptr = !TN && second ? g.dual : g.b.ptr;
     const int32_t steps = max(t_end - t_begin, 0);
     const int32_t m0 = tm * BM, n0 = tn * BN;
 
@@ -363,9 +372,9 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_split_kernel(SplitGemm g) {
     auto fetch = [&](int32_t t) {                 // NT
         const bool first = t < tiles1;
         const int32_t k0 = (first ? t : t - tiles1) * BK, k_left = (first ? g.k : g.k2) - k0;
-        const float* abase = static_cast<const float*>(first ? g.a.ptr : g.a2.ptr) + int64_t(m0) * g.a.ld + k0;
+        const float* abase = static_cast<const float*>(first ? a_ptr : g.a2.ptr) + int64_t(m0) * g.a.ld + k0;
         const float* gbase = GATE ? g.a.gate + int64_t(m0) * g.a.ld + k0 : nullptr;   // never with a second product
-        const uint16_t* bbase = static_cast<const uint16_t*>(first ? g.b.ptr : g.b2.ptr) +
+        const uint16_t* bbase = static_cast<const uint16_t*>(first ? b_ptr : g.b2.ptr) +
                                 (int64_t(tn) * (g.b.ld / BK) + k0 / BK) * (TERMS * BN * BK);      // g.b.ld: padded reduction length
         if constexpr (!TN) {
             load_rows<BM, A_CH, GATE>(tid, abase, gbase, plan_a, k_left, ra);
@@ -430,7 +439,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_split_kernel(SplitGemm g) {
             const uint32_t ld_bytes = uint32_t(op.ld) * 4u;
             auto fetch_cols = [&](int32_t t) {
                 const int32_t k0 = t * BK, k_left = g.k - k0;
-                const float* base = static_cast<const float*>(op.ptr) + int64_t(k0) * op.ld + (A ? m0 : n0);
+                const float* base = static_cast<const float*>(A ? a_ptr : op.ptr) + int64_t(k0) * op.ld + (A ? m0 : n0);
                 const float* gbase = G ? op.gate + int64_t(k0) * op.ld + n0 : nullptr;
                 if constexpr (RAGGED)
                     load_cols_ragged(base, b, n0, g.n, ld_bytes, k_left, cr);
@@ -460,7 +469,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_split_kernel(SplitGemm g) {
     // by loads that are all issued before the first one is used, not one round trip per element.
     const bool to_partial = g.split_k > 1;
     const int64_t pitch = to_partial ? int64_t(g.n) : g.ldc;
-    float* const base = to_partial ? g.partial + int64_t(z) * g.m * g.n : g.c;
+    float* const base = to_partial ? g.partial + (int64_t(second ? g.split_k : 0) + z) * g.m * g.n : second ? g.c_dual : g.c;
     const bool add_old = !to_partial && g.accumulate, relu = !to_partial && g.relu;
     if (m0 + BM <= g.m && n0 + BN <= g.n) {
         float* const tile = base + int64_t(m0 + wm) * pitch + (n0 + wn);               // scalar
@@ -563,7 +572,9 @@ template <typename T, int KS, bool GATE, int TERMS>
 __global__ __launch_bounds__(kThreads, 2) void gemm_short_k_kernel(const T* __restrict__ a, const T* __restrict__ gate,
                                                                    const float* __restrict__ b, int64_t ldb, T* __restrict__ c,
                                                                    int64_t ldc, int32_t m, int32_t n, int32_t k,
-                                                                   int32_t accumulate) {
+                                                                   int32_t accumulate, const float* __restrict__ b_dual,
+                                                                   T* __restrict__ c_dual) {
+    if (blockIdx.z == 1) b = b_dual, c = c_dual;                  // second product of the same A
     constexpr int VE = 16 / int(sizeof(T));                       // elements per 16-byte load
     __shared__ __attribute__((aligned(16))) float tile[kShortRows * 16 * KS + 64];
     __shared__ __attribute__((aligned(16))) float epi[4 * 32 * kEpiPitch];      // a 32 x 64 block per wavefront
@@ -707,23 +718,34 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_short_k_kernel(const T* __re
     }
 }
 
-// Expanded copy of (transpose ? h[c][r] : h[r][c]), r < rows, c < cols, zero beyond, in the tiled layout the product
-// kernel fetches: element (term p, row r, column c) sits at
-//   (((r / bn) * (pitch / BK) + c / BK) * TERMS + p) * bn * BK + (r % bn) * BK + c % BK,
-// bn = rows of a B tile (64 for at most 64 rows, else 128), rows padded to `rows_padded`, columns to `pitch`.
-template <int TERMS>
-__global__ __launch_bounds__(kThreads) void prep_weight_split_kernel(const float* __restrict__ h, int64_t ld, int32_t rows,
-                                                                     int32_t cols, int32_t rows_padded, int32_t pitch,
-                                                                     int32_t bn, int32_t transpose, uint16_t* __restrict__ out) {
-    const int64_t idx = int64_t(blockIdx.x) * kThreads + threadIdx.x;
-    if (idx >= int64_t(rows_padded) * pitch) return;
-    const int32_t r = int32_t(idx / pitch), c = int32_t(idx % pitch);
+// Weight copies (see PrepJob). Expanded copies: element (term p, row r, column c) sits at
+//   (((r / bn) * (pitch / BK) + c / BK) * terms + p) * bn * BK + (r % bn) * BK + c % BK,
+// bn = rows of a B tile (64 for at most 64 rows, else 128). All copies of a step are made by one launch: a copy is a few
+// thousand elements, far less than a launch costs.
+template <int CAP>               // the table travels with the launch: a single copy should not carry 3 KB of it
+struct PrepJobs {
+    PrepJob job[CAP];
+    int32_t n;
+};
+template <int CAP>
+__global__ __launch_bounds__(kThreads) void prep_weights_kernel(PrepJobs<CAP> jobs) {
+    int32_t at = 0;
+    while (at + 1 < jobs.n && int32_t(blockIdx.x) >= jobs.job[at + 1].first_block) ++at;
+    const PrepJob& jb = jobs.job[at];
+    const int64_t idx = int64_t(int32_t(blockIdx.x) - jb.first_block) * kThreads + threadIdx.x;
+    if (idx >= int64_t(jb.rows_padded) * jb.pitch) return;
+    const int32_t r = int32_t(idx / jb.pitch), c = int32_t(idx % jb.pitch);
     float x = 0.f;
-    if (r < rows && c < cols) x = transpose ? h[int64_t(c) * ld + r] : h[int64_t(r) * ld + c];
-    const int64_t block = (int64_t(r / bn) * (pitch / BK) + c / BK) * TERMS;
+    if (r < jb.rows && c < jb.cols) x = jb.transpose ? jb.h[int64_t(c) * jb.ld + r] : jb.h[int64_t(r) * jb.ld + c];
+    uint16_t* const out = static_cast<uint16_t*>(jb.out);
+    if (jb.terms == 1) {
+        out[idx] = float_to_bf16(x);
+        return;
+    }
+    const int32_t bn = jb.rows <= 64 ? 64 : 128;
+    const int64_t block = (int64_t(r / bn) * (jb.pitch / BK) + c / BK) * jb.terms;
     const int32_t inside = (r % bn) * BK + c % BK;
-#pragma unroll
-    for (int p = 0; p < TERMS; ++p) {
+    for (int p = 0; p < jb.terms; ++p) {
         const uint16_t t = float_to_bf16(x);
         out[(block + p) * bn * BK + inside] = t;
         x -= __uint_as_float(uint32_t(t) << 16);
@@ -742,20 +764,31 @@ void with_flag(bool b, F&& f) {
 
 }  // namespace
 
-hipError_t varco_launch_prep_weight_split(int terms, const float* h, int64_t ld, int32_t rows, int32_t cols,
-                                          int32_t rows_padded, int32_t pitch, bool transpose, void* out, hipStream_t stream) {
-    const int64_t total = int64_t(rows_padded) * pitch;
-    if (total == 0) return hipSuccess;
-    if (terms != 2 && terms != 3) return hipErrorInvalidValue;
-    if (rows_padded < rows || rows_padded % kPrepRows != 0 || pitch < cols || pitch % BK != 0) return hipErrorInvalidValue;
-    const dim3 grid(unsigned((total + kThreads - 1) / kThreads));
-    const int32_t bn = rows <= 64 ? 64 : 128;      // the product kernel's B tile for this many output columns
-    if (terms == 3)
-        hipLaunchKernelGGL(prep_weight_split_kernel<3>, grid, dim3(kThreads), 0, stream, h, ld, rows, cols, rows_padded,
-                           pitch, bn, transpose ? 1 : 0, static_cast<uint16_t*>(out));
+hipError_t varco_launch_prep_weights(PrepJob* jobs, int n, hipStream_t stream) {
+    if (n <= 0) return hipSuccess;
+    if (n > kMaxPrepJobs) return hipErrorInvalidValue;
+    int64_t blocks = 0;
+    for (int i = 0; i < n; ++i) {
+        PrepJob& j = jobs[i];
+        const bool plain = j.terms == 1 && j.rows_padded == j.rows && j.pitch >= j.cols;
+        const bool tiled = (j.terms == 2 || j.terms == 3) && j.rows_padded >= j.rows && j.rows_padded % kPrepRows == 0 && j.pitch >= j.cols && j.pitch % BK == 0;
+        if (!plain && !tiled) return hipErrorInvalidValue;
+        j.first_block = int32_t(blocks);
+        blocks += (int64_t(j.rows_padded) * j.pitch + kThreads - 1) / kThreads;
+    }
+    if (blocks == 0) return hipSuccess;
+    auto go = [&](auto cap) {
+        PrepJobs<decltype(cap)::value> args{};
+        for (int i = 0; i < n; ++i) args.job[i] = jobs[i];
+        args.n = n;
+        hipLaunchKernelGGL((prep_weights_kernel<decltype(cap)::value>), dim3(unsigned(blocks)), dim3(kThreads), 0, stream, args);
+    };
+    if (n == 1)
+        go(std::integral_constant<int, 1>{});
+    else if (n <= 8)
+        go(std::integral_constant<int, 8>{});
     else
-        hipLaunchKernelGGL(prep_weight_split_kernel<2>, grid, dim3(kThreads), 0, stream, h, ld, rows, cols, rows_padded,
-                           pitch, bn, transpose ? 1 : 0, static_cast<uint16_t*>(out));
+        go(std::integral_constant<int, kMaxPrepJobs>{});
     return hipGetLastError();
 }
 
@@ -768,7 +801,7 @@ struct TypeTag {
 
 // Short reductions (see gemm_short_k_kernel): terms = 1 for bf16 storage, 2 or 3 for fp32 storage.
 hipError_t varco_launch_gemm_short_k(const GemmArgs& ga, int terms, hipStream_t stream) {
-    const dim3 grid(unsigned((ga.m + kShortRows - 1) / kShortRows), unsigned((ga.n + 255) / 256));
+    const dim3 grid(unsigned((ga.m + kShortRows - 1) / kShortRows), unsigned((ga.n + 255) / 256), ga.c_dual ? 2 : 1);
     const int ks = (ga.k + 15) / 16;
     if (ks < 1 || ks > 4) return hipErrorInvalidValue;
     auto go = [&](auto type, auto ksc, auto gt, auto tc) {
@@ -776,7 +809,7 @@ hipError_t varco_launch_gemm_short_k(const GemmArgs& ga, int terms, hipStream_t 
         hipLaunchKernelGGL((gemm_short_k_kernel<T, decltype(ksc)::value, decltype(gt)::value, decltype(tc)::value>), grid,
                            dim3(kThreads), 0, stream, static_cast<const T*>(ga.a.ptr), static_cast<const T*>(ga.a.gate),
                            static_cast<const float*>(ga.b.ptr), ga.b.ld, static_cast<T*>(ga.c), ga.ldc, ga.m, ga.n, ga.k,
-                           ga.accumulate ? 1 : 0);
+                           ga.accumulate ? 1 : 0, static_cast<const float*>(ga.b_dual), static_cast<T*>(ga.c_dual));
     };
     auto with_ks = [&](auto type, auto gt, auto tc) {
         switch (ks) {
@@ -825,9 +858,10 @@ bool varco_gemm_split_usable(const GemmArgs& ga) {
                 ga.a2.transposed)
                 return false;
         }
-        return true;
+        return !ga.c_dual || (ga.k2 == 0 && ga.split_k <= 1 && ga.b_dual_prep && aligned_to(ga.b_dual_prep, 16));
     }
     // TN: weight gradient
+    if (ga.c_dual && (!ga.a_dual || !aligned_to(ga.a_dual, 16))) return false;
     if (ga.b.transposed || ga.b.dtype != VARCO_F32 || ga.k2 > 0 || ga.a.gate) return false;
     if (!ok16(ga.a) || ga.m % 4 != 0) return false;
     return b_vector_ok(ga) || (ga.n <= 64 && !ga.b.gate && aligned_to(ga.b.ptr, 4));   // else B element by element
@@ -867,11 +901,14 @@ hipError_t varco_launch_gemm_split(const GemmArgs& ga, hipStream_t stream, const
     g.split_k = split;
     g.partial = ga.partial;
     if (split > 1 && !ga.partial) return hipErrorInvalidValue;
-    if (split > 1) {
-        g.inner = g.tiles_m * g.tiles_n;
+    g.dual = ga.c_dual ? (tn ? ga.a_dual : ga.b_dual_prep) : nullptr;
+    g.c_dual = static_cast<float*>(ga.c_dual);
+    const int32_t products = ga.c_dual ? 2 : 1;     // the dual product's tiles come right behind the first one's, on the same XCD
+    if (split > 1 || tn) {
+        g.inner = g.tiles_m * g.tiles_n * products;
         g.outer = split;
     } else {
-        g.inner = g.tiles_n;
+        g.inner = g.tiles_n * products;
         g.outer = g.tiles_m;
     }
     const int64_t blocks = int64_t((g.outer + 7) / 8 * 8) * g.inner;

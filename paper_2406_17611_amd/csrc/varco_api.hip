@@ -233,11 +233,12 @@ int32_t ensure_tables(varco_ctx* ctx) {
 // output index, pitch padded; bf16 storage: one rounded copy; fp32 storage: the terms of the exact bf16
 // expansion, one plane each. Nothing to do when fp32 instructions are used. Every (layer, weight, orientation)
 // has a slot of its own in the stream's workspace, and a copy made earlier in the same step from the same
-// pointer is reused: the weights of a step do not change (they are updated between steps).
-hipError_t prep_weight(varco_ctx* ctx, Workspace& ws, int32_t layer, const void* h, int32_t fi, int32_t fo, bool transpose,
-                       int which, bool as_b2, hipStream_t st, GemmArgs& g) {
+// pointer is reused: the weights of a step do not change (they are updated between steps). Returns whether `job`, which
+// makes the copy, has to run before the product.
+bool prep_slot(varco_ctx* ctx, Workspace& ws, int32_t layer, const void* h, int32_t fi, int32_t fo, bool transpose, int which, bool as_b2,
+               GemmArgs& g, PrepJob* job) {
     const bool bf16 = ctx->dtype == VARCO_BF16;
-    if (!bf16 && ctx->f32_terms == 0) return hipSuccess;
+    if (!bf16 && ctx->f32_terms == 0) return false;
     const int32_t terms = bf16 ? 1 : ctx->f32_terms;
     const int32_t rows = transpose ? fo : fi, cols = transpose ? fi : fo;
     const int32_t p = bf16 ? pad8(cols) : pad_to(cols, 32);
@@ -251,11 +252,17 @@ hipError_t prep_weight(varco_ctx* ctx, Workspace& ws, int32_t layer, const void*
         g.f32_terms = terms;
     }
     Workspace::WeightTag& tag = ws.w_tags[slot];
-    if (tag.h == h && tag.epoch == ctx->weight_epoch && tag.terms == terms) return hipSuccess;
+    if (tag.h == h && tag.epoch == ctx->weight_epoch && tag.terms == terms) return false;
     tag.h = h, tag.epoch = ctx->weight_epoch, tag.terms = terms;
+    *job = PrepJob{static_cast<const float*>(h), dst, fo, rows, cols, rows_padded, p, transpose ? 1 : 0, terms, 0};
+    return true;
+}
+hipError_t prep_weight(varco_ctx* ctx, Workspace& ws, int32_t layer, const void* h, int32_t fi, int32_t fo, bool transpose,
+                       int which, bool as_b2, hipStream_t st, GemmArgs& g) {
+    PrepJob job;
+    if (!prep_slot(ctx, ws, layer, h, fi, fo, transpose, which, as_b2, g, &job)) return hipSuccess;
     ctx->prof.interrupt();   // an untimed launch: the next bracketed launch records a start event of its own
-    if (bf16) return varco_launch_prep_weight(static_cast<const float*>(h), fo, rows, cols, p, transpose, dst, st);
-    return varco_launch_prep_weight_split(terms, static_cast<const float*>(h), fo, rows, cols, rows_padded, p, transpose, dst, st);
+    return varco_launch_prep_weights(&job, 1, st);
 }
 
 // Elements (floats) of the halo-gradient product buffer the current ratios ask for: the largest (halo entries of a
@@ -290,6 +297,7 @@ int32_t size_workspace(varco_ctx* ctx, Workspace& ws) {
     VARCO_HIP(ctx, grow(ws.spmm, ws.spmm_elems, ctx->need_spmm));
     VARCO_HIP(ctx, grow(ws.gemm, ws.gemm_elems, ctx->need_gemm));
     VARCO_HIP(ctx, grow(ws.w, ws.w_elems, ctx->need_w));
+    VARCO_HIP(ctx, grow(ws.loss, ws.loss_elems, size_t(2) * kLossBlocks));
     const size_t prod = prod_need(ctx);
     if (prod > ws.prod_elems) VARCO_HIP(ctx, grow(ws.prod, ws.prod_elems, prod + prod / 4));   // head-room: schedules raise k step by step
     // the block's product buffer is an option (without it whole rows are gathered): a device that has no room for it goes on without
@@ -468,7 +476,7 @@ extern "C" int32_t varco_destroy(varco_ctx* ctx) {
     for (PartState& ps : ctx->parts) free_part(ps);
     free_network(ctx->net);
     for (Workspace& w : ctx->ws)
-        for (float* p : {w.dm, w.spmm, w.gemm, w.prod, w.w, w.tf, w.hrows})
+        for (float* p : {w.dm, w.spmm, w.gemm, w.prod, w.w, w.tf, w.hrows, w.loss})
             if (p) (void)hipFree(p);
     if (ctx->d_flags) (void)hipFree(ctx->d_flags);
     if (ctx->d_step) (void)hipFree(ctx->d_step);
@@ -1360,8 +1368,11 @@ extern "C" int32_t varco_softmax_xent(varco_ctx* ctx, const void* logits, int64_
     if (n_rows == 0) return VARCO_OK;
     if (!logits || !labels || !row_loss || !row_correct)
         return varco_fail(ctx, VARCO_ERR_INVALID_ARG, "varco_softmax_xent: null pointer");
+    float* block_sums = nullptr;             // a stream without a workspace set takes the form that needs none
+    for (const Workspace& w : ctx->ws)
+        if (w.used && w.stream == static_cast<hipStream_t>(stream)) block_sums = w.loss;
     VARCO_HIP(ctx, varco_launch_softmax_xent(ctx->dtype, logits, ld, labels, n_rows, n_classes, scale, dlogits, ldd, row_loss,
-                                             row_correct, totals, static_cast<hipStream_t>(stream)));
+                                             row_correct, totals, block_sums, static_cast<hipStream_t>(stream)));
     return VARCO_OK;
 }
 

@@ -65,6 +65,7 @@ struct Workspace {
     float* w = nullptr;         size_t w_elems = 0;         // converted copies of the weights, one slot per (layer, weight, orientation)
     float* tf = nullptr;        size_t tf_elems = 0;        // transform-first layers: [Y_loc ; Y_halo], (n_local + n_halo) x width[l+1]
     float* hrows = nullptr;     size_t hrows_elems = 0;     // and one record (two words) per halo row
+    float* loss = nullptr;      size_t loss_elems = 0;      // the loss's sums per workgroup
     struct WeightTag {          // what a slot holds: made from `h` during step epoch `epoch` in the form `terms`
         const void* h = nullptr;
         uint64_t epoch = 0;
@@ -128,6 +129,8 @@ hipError_t grow(float*& buf, size_t& have, size_t want);
 enum GemmKind { kGemmF32 = 0, kGemmBf16 = 1, kGemmExpanded = 2 };
 int32_t gemm_split_for(int32_t m, int32_t n, int64_t k, int kind);
 int gemm_kind(const GemmArgs& g);
+bool prep_slot(varco_ctx* ctx, Workspace& ws, int32_t layer, const void* h, int32_t fi, int32_t fo, bool transpose, int which, bool as_b2,
+               GemmArgs& g, PrepJob* job);
 hipError_t prep_weight(varco_ctx* ctx, Workspace& ws, int32_t layer, const void* h, int32_t fi, int32_t fo, bool transpose,
                        int which, bool as_b2, hipStream_t st, GemmArgs& g);
 int32_t size_all_workspaces(varco_ctx* ctx);

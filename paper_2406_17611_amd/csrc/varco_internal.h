@@ -243,11 +243,30 @@ struct GemmArgs {
     bool relu = false;            // C = max(., 0)
     int32_t split_k = 1;          // > 1: partial products into `partial` then reduced in a second kernel
     float* partial = nullptr;     // split_k * m * n floats
+    // A second product of the same shape that shares an operand, formed by the same launch (varco_gemm_dual_usable): with A
+    // transposed another A against the same B (the two taps' weight gradients), else another B against the same A (the two
+    // taps' input gradients); its result goes to c_dual, its partial products behind the first product's.
+    const void* a_dual = nullptr;
+    const void* b_dual = nullptr;         // the weights as given, and their copy (same layout as b_prep)
+    const void* b_dual_prep = nullptr;
+    void* c_dual = nullptr;
+    int32_t* deferred = nullptr;  // when set: the number of partial products written to `partial` (1: C holds the result); the
+                                  // caller sums them (varco_launch_gemm_reduce_jobs)
 };
 hipError_t varco_launch_gemm(const GemmArgs& g, hipStream_t stream, const LaunchTag& tag);
 // c (+)= sum over s < slabs of partial[s][m x n], in a fixed order (the second pass of every split reduction).
 hipError_t varco_launch_gemm_reduce(const float* partial, int32_t slabs, int32_t m, int32_t n, float* c, int64_t ldc,
                                     bool accumulate, hipStream_t stream, const LaunchTag& tag);
+
+// The same for several products in one launch; splits <= 1 are skipped. At most kMaxReduceJobs jobs.
+struct ReduceJob {
+    const float* partial;
+    float* c;
+    int64_t ldc;
+    int32_t splits, m, n, first_block;
+};
+constexpr int kMaxReduceJobs = 2 * VARCO_MAX_LAYERS;
+hipError_t varco_launch_gemm_reduce_jobs(ReduceJob* jobs, int n, bool accumulate, hipStream_t stream, const LaunchTag& tag);
 
 // The halo rows of a partition as an exchange delivered them (kernels_halo_transform.hip; bf16 storage): row s holds
 // the k elements z[rec[s].y * k + j] at positions (a j + b) mod width, (a << 16) | b = rec[s].x, of a width-wide row
@@ -274,27 +293,37 @@ hipError_t varco_launch_halo_transform_wgrad(const HaloTransform& h, const void*
 // slabs it wrote to g.partial (1: the result is already in C).
 bool varco_gemm_bf16_usable(const GemmArgs& g);
 hipError_t varco_launch_gemm_bf16(const GemmArgs& g, hipStream_t stream, const LaunchTag& tag, int32_t* split_used);
-// out[r][c] (bf16, row pitch `pitch` >= cols, zero beyond cols) = transpose ? h[c][r] : h[r][c] for r < rows.
-hipError_t varco_launch_prep_weight(const float* h, int64_t ld, int32_t rows, int32_t cols, int32_t pitch, bool transpose,
-                                    void* out, hipStream_t stream);
-
 // fp32 operands as sums of bf16 terms on the bf16 matrix cores (kernels_gemm_split.hip); same contract as
 // the bf16 path above.
 bool varco_gemm_split_usable(const GemmArgs& g);
 hipError_t varco_launch_gemm_split(const GemmArgs& g, hipStream_t stream, const LaunchTag& tag, int32_t* split_used);
-// Expanded copy of (transpose ? h[c][r] : h[r][c]) (bf16 terms; rows padded to rows_padded, a multiple of 128, columns
-// to pitch, a multiple of 32; zero beyond rows x cols), stored by row tile and stage of 32 columns as the product
-// kernel fetches it (layout: kernels_gemm_split.hip). Same size as a plain [term][row][pitch] copy.
-hipError_t varco_launch_prep_weight_split(int terms, const float* h, int64_t ld, int32_t rows, int32_t cols,
-                                          int32_t rows_padded, int32_t pitch, bool transpose, void* out, hipStream_t stream);
+// Copies of weight matrices in the form the bf16 matrix-core kernels take, several per launch: (transpose ? h[c][r] : h[r][c])
+// for r < rows, c < cols, zero beyond.
+//   terms = 1: one rounded bf16 copy [row][pitch], rows_padded = rows;
+//   terms = 2, 3: the terms of the exact expansion, rows padded to rows_padded (a multiple of 128) and columns to pitch (a
+//   multiple of 32), stored by row tile and stage of 32 columns as the product kernel fetches it (kernels_gemm_split.hip).
+struct PrepJob {
+    const float* h;
+    void* out;
+    int32_t ld, rows, cols, rows_padded, pitch, transpose, terms, first_block;
+};
+constexpr int kMaxPrepJobs = 4 * VARCO_MAX_LAYERS;
+hipError_t varco_launch_prep_weights(PrepJob* jobs, int n, hipStream_t stream);
+
+// Whether varco_launch_gemm forms g and its dual product in one launch.
+bool varco_gemm_dual_usable(const GemmArgs& g);
+// Whether varco_launch_gemm takes the short-reduction kernels, which read the weights as they are.
+bool varco_gemm_short_usable(const GemmArgs& g);
 
 // C (+)= A B^T with at most 64 reduction steps on the bf16 matrix units (terms: 1 for bf16 storage, 2 or 3 bf16 terms
 // per fp32 operand); same operand contract as the fp32-instruction kernel of kernels_gemm.hip that it replaces.
 hipError_t varco_launch_gemm_short_k(const GemmArgs& g, int terms, hipStream_t stream);
 
 // Loss and update of a training iteration (kernels_train.hip). row_loss / row_correct: n_rows each; totals
-// (2 floats) may be null.
+// (2 floats) may be null. block_sums: 2 * kLossBlocks floats of scratch of the stream, or null (then the rows are summed by
+// one workgroup from row_loss / row_correct).
+constexpr int kLossBlocks = 2048;
 hipError_t varco_launch_softmax_xent(int dtype, const void* logits, int64_t ld, const int32_t* labels, int64_t n_rows,
                                      int32_t n_classes, float scale, void* dlogits, int64_t ldd, float* row_loss,
-                                     int32_t* row_correct, float* totals, hipStream_t stream);
+                                     int32_t* row_correct, float* totals, float* block_sums, hipStream_t stream);
 hipError_t varco_launch_sgd(float* w, const float* dw, int64_t n, float lr, hipStream_t stream);

@@ -28,6 +28,16 @@ size_t prod_floats(const varco_ctx* ctx, int32_t layer) {
     return (size_t(ctx->net.nnz_cross) * size_t(ctx->layers[layer].k) * size_t(ctx->elem_bytes()) + 3) / 4;
 }
 
+// Split of a weight gradient's reduction over the arena's rows: one round of two workgroups per compute unit, at least two
+// stages of 32 rows each. (The per-partition calls stop at eight stages: with few rows - 2,000 rows and a 32 x 8 weight
+// matrix - a handful of workgroups then walks a chain of round trips while the device idles, 16 us against 6.)
+int32_t wgrad_splits(int32_t m, int32_t n, int64_t rows, int kind, int products) {
+    const int64_t bm = kind == kGemmBf16 || (kind == kGemmF32 && n <= 64) ? 256 : 128, bn = n <= 64 ? 64 : 128;
+    const int64_t tiles = products * ((m + bm - 1) / bm) * ((n + bn - 1) / bn), step = kind == kGemmF32 ? 16 : 32;
+    const int64_t split = std::max<int64_t>(1, ((kind == kGemmF32 ? 3 : 2) * 256) / tiles);
+    return int32_t(std::min<int64_t>(split, std::max<int64_t>(1, (rows + step - 1) / step / 2)));
+}
+
 template <typename P>
 hipError_t alloc(P*& p, size_t n) {
     return n ? hipMalloc(reinterpret_cast<void**>(&p), n * sizeof(P)) : hipSuccess;
@@ -154,11 +164,14 @@ int32_t link_impl(varco_ctx* ctx) {
     // workspace: dM over the arena, partial rows, partial products of the weight gradients
     const int32_t wmax = *std::max_element(ctx->widths.begin(), ctx->widths.end());
     int64_t gemm_elems = 0;
-    for (int32_t l = 0; l < ctx->n_layers; ++l)
+    for (int32_t l = 0; l < ctx->n_layers; ++l) {
+        int64_t layer_elems = 0;
         for (int kind : {kGemmF32, kGemmBf16, kGemmExpanded}) {
             const int64_t fi = ctx->widths[l], fo = ctx->widths[l + 1];
-            gemm_elems = std::max<int64_t>(gemm_elems, gemm_split_for(int32_t(fi), int32_t(fo), net.rows, kind) * fi * fo);
+            layer_elems = std::max<int64_t>(layer_elems, wgrad_splits(int32_t(fi), int32_t(fo), net.rows, kind, 1) * fi * fo);
         }
+        gemm_elems += layer_elems * (ctx->conv == VARCO_CONV_SAGE ? 2 : 1);   // the partial products of all layers wait for one sum
+    }
     ctx->need_dm = std::max(ctx->need_dm, (size_t(net.rows) * size_t(wmax) * size_t(ctx->elem_bytes()) + 3) / 4);
     ctx->need_spmm = std::max(ctx->need_spmm, size_t(std::max<int64_t>(net.fwd.n_partials, n_slots)) * size_t(wmax));
     ctx->need_gemm = std::max(ctx->need_gemm, size_t(gemm_elems));
@@ -270,7 +283,14 @@ int32_t layer_fwd(varco_ctx* ctx, Workspace& ws, const varco_network_buffers& b,
     return last ? VARCO_OK : compress_all(ctx, l + 1, make_rule(ctx, l + 1), b.x[l + 1], b.z[l + 1], st);
 }
 
-int32_t layer_bwd(varco_ctx* ctx, Workspace& ws, const varco_network_buffers& b, int32_t l, hipStream_t st) {
+// Partial products of the weight gradients of a backward pass, summed by one launch at its end.
+struct WeightSums {
+    ReduceJob job[kMaxReduceJobs];
+    int n = 0;
+    size_t used = 0;              // floats of the workspace's partial buffer
+};
+
+int32_t layer_bwd(varco_ctx* ctx, Workspace& ws, const varco_network_buffers& b, int32_t l, WeightSums& sums, hipStream_t st) {
     const NetState& net = ctx->net;
     const int32_t fi = ctx->widths[l], fo = ctx->widths[l + 1];
     const bool sage = ctx->conv == VARCO_CONV_SAGE, need = l > 0;
@@ -298,13 +318,27 @@ int32_t layer_bwd(varco_ctx* ctx, Workspace& ws, const varco_network_buffers& b,
         g.b.ptr = b.dx[l + 1], g.b.gate = gate, g.b.ld = fo, g.b.dtype = dt;
         g.c = b.dh1[l], g.ldc = fo;
         g.accumulate = true;
-        g.partial = ws.gemm;
         g.f32_terms = dt == VARCO_F32 ? ctx->f32_terms : 0;
-        for (int tap = 0; tap < (sage ? 2 : 1); ++tap) {
+        // both taps' gradients by one launch where the kernels can: they share dZ (and its mask)
+        int32_t split = 1;
+        g.deferred = &split;
+        if (sage) {
+            g.a_dual = b.x[l], g.c_dual = b.dh0[l];
+            if (!varco_gemm_dual_usable(g)) g.a_dual = nullptr, g.c_dual = nullptr;
+        }
+        const int products = g.c_dual ? 2 : 1;
+        for (int tap = 0; tap < (sage ? 2 : 1); tap += products) {
             if (tap == 1) g.a.ptr = b.x[l], g.c = b.dh0[l];
-            g.split_k = gemm_split_for(fi, fo, nl, gemm_kind(g));
-            if (size_t(g.split_k) * fi * fo > ws.gemm_elems) return varco_fail(ctx, VARCO_ERR_STATE, "varco_network_backward: workspace too small");
-            VARCO_HIP(ctx, varco_launch_gemm(g, st, ctx->tag(VARCO_K_GEMM_WGRAD, 0, 2.0 * fi * fo * double(nl))));
+            g.split_k = wgrad_splits(fi, fo, nl, gemm_kind(g), products);
+            const size_t one = size_t(fi) * fo;
+            if (sums.used + size_t(g.split_k) * one * products > ws.gemm_elems)
+                return varco_fail(ctx, VARCO_ERR_STATE, "varco_network_backward: workspace too small");
+            g.partial = ws.gemm + sums.used;
+            VARCO_HIP(ctx, varco_launch_gemm(g, st, ctx->tag(VARCO_K_GEMM_WGRAD, 0, 2.0 * products * fi * fo * double(nl))));
+            for (int i = 0; split > 1 && i < products; ++i) {
+                sums.job[sums.n++] = ReduceJob{g.partial + size_t(i) * split * one, static_cast<float*>(i ? g.c_dual : g.c), g.ldc, split, fi, fo, 0};
+                sums.used += size_t(split) * one;
+            }
         }
     }
     if (!need) return VARCO_OK;
@@ -313,15 +347,50 @@ int32_t layer_bwd(varco_ctx* ctx, Workspace& ws, const varco_network_buffers& b,
     g.a.ptr = b.dx[l + 1], g.a.gate = gate, g.a.ld = fo, g.a.dtype = dt;
     g.b.ptr = b.h1[l], g.b.ld = fo, g.b.transposed = true;
     g.c = ws.dm, g.ldc = fi, g.c_dtype = dt;
-    VARCO_HIP(ctx, prep_weight(ctx, ws, l, b.h1[l], fi, fo, false, 0, false, st, g));
-    VARCO_HIP(ctx, varco_launch_gemm(g, st, ctx->tag(VARCO_K_GEMM_DGRAD, 0, 2.0 * fi * fo * double(nl))));
+    g.f32_terms = dt == VARCO_F32 ? ctx->f32_terms : 0;
+    const bool short_k = varco_gemm_short_usable(g);      // reads the weights as they are
+    const double flops = 2.0 * fi * fo * double(nl);
+    if (!short_k) VARCO_HIP(ctx, prep_weight(ctx, ws, l, b.h1[l], fi, fo, false, 0, false, st, g));
     if (sage) {                    // self tap: dX = dZ H0^T, the aggregated part is added to it
-        g.b.ptr = b.h0[l];
-        g.c = b.dx[l];
-        VARCO_HIP(ctx, prep_weight(ctx, ws, l, b.h0[l], fi, fo, false, 1, false, st, g));
-        VARCO_HIP(ctx, varco_launch_gemm(g, st, ctx->tag(VARCO_K_GEMM_DGRAD, 0, 2.0 * fi * fo * double(nl))));
+        GemmArgs g0 = g;
+        g0.b.ptr = b.h0[l], g0.c = b.dx[l];
+        if (!short_k) VARCO_HIP(ctx, prep_weight(ctx, ws, l, b.h0[l], fi, fo, false, 1, false, st, g0));
+        g.b_dual = b.h0[l], g.b_dual_prep = g0.b_prep, g.c_dual = b.dx[l];
+        if (!varco_gemm_dual_usable(g)) {
+            g.b_dual = g.b_dual_prep = nullptr, g.c_dual = nullptr;
+            VARCO_HIP(ctx, varco_launch_gemm(g0, st, ctx->tag(VARCO_K_GEMM_DGRAD, 0, flops)));
+        }
     }
+    VARCO_HIP(ctx, varco_launch_gemm(g, st, ctx->tag(VARCO_K_GEMM_DGRAD, 0, g.c_dual ? 2.0 * flops : flops)));
     return aggregate_bwd(ctx, ws, l, make_rule(ctx, l), ws.dm, b.dx[l], sage, st);
+}
+
+int32_t finish_sums(varco_ctx* ctx, WeightSums& sums, hipStream_t st) {
+    VARCO_HIP(ctx, varco_launch_gemm_reduce_jobs(sums.job, sums.n, true, st, ctx->tag(VARCO_K_REDUCE, 0, 0)));
+    sums.n = 0, sums.used = 0;
+    return VARCO_OK;
+}
+
+// All weight copies a pass needs, in one launch: those of the forward products, and when the buffers hold weight gradients
+// (a backward pass follows) those of the input gradients as well.
+int32_t prep_all(varco_ctx* ctx, Workspace& ws, const varco_network_buffers& b, hipStream_t st) {
+    PrepJob jobs[kMaxPrepJobs];
+    int n = 0;
+    GemmArgs unused;
+    for (int32_t l = 0; l < ctx->n_layers; ++l) {
+        const int32_t fi = ctx->widths[l], fo = ctx->widths[l + 1];
+        const bool first = ctx->layers[l].order == VARCO_ORDER_TRANSFORM_FIRST;
+        for (int which = 0; which < (ctx->conv == VARCO_CONV_SAGE ? 2 : 1); ++which) {
+            const void* h = which ? b.h0[l] : b.h1[l];
+            n += prep_slot(ctx, ws, l, h, fi, fo, true, which, false, unused, jobs + n) ? 1 : 0;
+            // at most 64 outputs: the short-reduction kernels take the weights as they are
+            if (b.dh1[l] && l > 0 && (fo > 64 || (first && which == 0)))
+                n += prep_slot(ctx, ws, l, h, fi, fo, false, which, false, unused, jobs + n) ? 1 : 0;
+        }
+    }
+    ctx->prof.interrupt();
+    VARCO_HIP(ctx, varco_launch_prep_weights(jobs, n, st));
+    return VARCO_OK;
 }
 
 int32_t check_buffers(const varco_ctx* ctx, const varco_network_buffers* b, bool backward, const char* fn) {
@@ -374,6 +443,7 @@ extern "C" int32_t varco_network_forward(varco_ctx* ctx, const varco_network_buf
     hipStream_t st = static_cast<hipStream_t>(stream);
     Workspace* ws = nullptr;
     if (int32_t rc = workspace_for(ctx, st, &ws, fn)) return rc;
+    if (int32_t rc = prep_all(ctx, *ws, *b, st)) return rc;
     if (int32_t rc = compress_all(ctx, 0, make_rule(ctx, 0), b->x[0], b->z[0], st)) return rc;
     for (int32_t l = 0; l < ctx->n_layers; ++l)
         if (int32_t rc = layer_fwd(ctx, *ws, *b, l, st)) return rc;
@@ -388,9 +458,14 @@ extern "C" int32_t varco_network_backward(varco_ctx* ctx, const varco_network_bu
     hipStream_t st = static_cast<hipStream_t>(stream);
     Workspace* ws = nullptr;
     if (int32_t rc = workspace_for(ctx, st, &ws, fn)) return rc;
-    for (int32_t l = ctx->n_layers - 1; l >= 0; --l)
-        if (int32_t rc = layer_bwd(ctx, *ws, *b, l, st)) return rc;
-    return VARCO_OK;
+    WeightSums sums;
+    for (int32_t l = ctx->n_layers - 1; l >= 0; --l) {
+        if (ctx->layers[l].order == VARCO_ORDER_TRANSFORM_FIRST) {   // uses the partial buffer from its start
+            if (int32_t rc = finish_sums(ctx, sums, st)) return rc;
+        }
+        if (int32_t rc = layer_bwd(ctx, *ws, *b, l, sums, st)) return rc;
+    }
+    return finish_sums(ctx, sums, st);
 }
 
 extern "C" int32_t varco_network_compress(varco_ctx* ctx, int32_t tap, const void* x, void* z, varco_stream stream) {

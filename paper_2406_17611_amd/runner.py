@@ -63,13 +63,11 @@ class PartitionedNetwork:
         act = dict(dtype=self.act_dtype, device=self.device)
         self.x = [torch.empty((self.n_total, w), **act) for w in self.widths]
         self.m = [torch.empty((self.n_total, self.widths[l]), **act) for l in range(self.L)]
-        self.h1 = [torch.empty((self.widths[l], self.widths[l + 1]), **f32) for l in range(self.L)]
-        self.h0 = [torch.empty_like(h) if conv == "sage" else None for h in self.h1]
+        self.h1, self.h0, self._h_flat = self._weight_set()
         self.z = [None] * self.L           # allocated per step (k changes with the ratio)
         self.need_backward = need_backward
         if need_backward:
-            self.dh1 = [torch.zeros_like(h) for h in self.h1]
-            self.dh0 = [torch.zeros_like(h) if conv == "sage" else None for h in self.h1]
+            self.dh1, self.dh0, self._dh_flat = self._weight_set()
             # one more set of weight-gradient accumulators per extra stream (overlapping calls must not
             # read-modify-write the same buffer); folded into dh1 / dh0 at the end of backward()
             n_extra = 0 if self.linked else n_streams - 1
@@ -82,6 +80,28 @@ class PartitionedNetwork:
         self._streams = None
         self._prepared = set()
         self._prepare([None])
+
+    def _weight_set(self):
+        """Zeroed fp32 matrices of all layers as views of one buffer, in one order for weights and gradients: what is done
+        to all of them (clearing, the gradient step) is one call."""
+        taps = 2 if self.conv == "sage" else 1
+        pad = lambda n: (n + 63) // 64 * 64      # noqa: E731  (every matrix starts on a 256-byte boundary)
+        sizes = [self.widths[l] * self.widths[l + 1] for l in range(self.L) for _ in range(taps)]
+        flat = torch.zeros(sum(pad(n) for n in sizes), dtype=torch.float32, device=self.device)
+        views, at = [], 0
+        for i, n in enumerate(sizes):
+            l = i // taps
+            views.append(flat[at:at + n].view(self.widths[l], self.widths[l + 1]))
+            at += pad(n)
+        h0 = views[1::2] if taps == 2 else [None] * self.L
+        return views[::taps], h0, (flat, tuple(views))
+
+    @staticmethod
+    def _whole(flat, first, second):
+        """The one buffer behind the matrices, or None once a matrix was replaced by another tensor."""
+        buf, views = flat
+        mine = [m for pair in zip(first, second) for m in pair if m is not None]
+        return buf if len(mine) == len(views) and all(a is b for a, b in zip(mine, views)) else None
 
     # ------------------------------------------------------------------ streams
     def _prepare(self, streams):
@@ -294,12 +314,19 @@ class PartitionedNetwork:
         scale = 1.0 / max(1, self.n_train if train else self.n_test)
         c = self.widths[-1]
         self._totals.zero_()
+        if self.linked:
+            self.ctx.softmax_xent(self.x[self.L], labels, c, scale, self.dx[self.L] if with_gradient else None, self._row_loss,
+                                  self._row_correct, self._totals, stream)
+            return self._totals
         for r in self._blocks():
             self.ctx.softmax_xent(self.x[self.L][r], labels[r], c, scale, self.dx[self.L][r] if with_gradient else None,
                                   self._row_loss[r], self._row_correct[r], self._totals, stream)
         return self._totals
 
     def sgd(self, lr: float, stream=None):
+        w, dw = self._whole(self._h_flat, self.h1, self.h0), self._whole(self._dh_flat, self.dh1, self.dh0)
+        if w is not None and dw is not None:
+            return vb.sgd_step(w, dw, lr, stream)
         for l in range(self.L):
             vb.sgd_step(self.h1[l], self.dh1[l], lr, stream)
             if self.h0[l] is not None:
@@ -334,6 +361,10 @@ class PartitionedNetwork:
         return graph
 
     def zero_grads(self):
+        dw = self._whole(self._dh_flat, self.dh1, self.dh0)
+        if dw is not None:
+            dw.zero_()
+            return
         for l in range(self.L):
             self.dh1[l].zero_()
             if self.dh0[l] is not None:
