@@ -344,8 +344,8 @@ int32_t varco_accumulate_returned(varco_ctx* ctx, int32_t layer, int32_t p, cons
  * entries together (the per-partition calls have no such limit), VARCO_ERR_SHAPE when the maps do not fit.
  *
  * The errors that the consumers of a node hand back (k elements per entry of a halo column) are summed for all consumers
- * at once and added to the owner's row; they are not summed per consumer first, so dz_halo is used only by layers that
- * transform first. The exchange counters count the same volume as in the per-partition calls. */
+ * at once and added to the owner's row; they are not summed per consumer first, so no buffer of returned rows is needed.
+ * The exchange counters count the same volume as in the per-partition calls. */
 typedef struct {
     void* x[VARCO_MAX_LAYERS + 1];       /* n_total x width[l]; x[0] given, the rest written by forward */
     void* z[VARCO_MAX_LAYERS];           /* compressed boundary rows of x[l], all partitions: written by forward */
@@ -355,7 +355,6 @@ typedef struct {
     void* dh1[VARCO_MAX_LAYERS];         /* fp32, accumulated into */
     void* dh0[VARCO_MAX_LAYERS];
     void* dx[VARCO_MAX_LAYERS + 1];      /* n_total x width[l]; dx[L] given, dx[1..L-1] written by backward, dx[0] not used */
-    void* dz_halo[VARCO_MAX_LAYERS];     /* all partitions' returned rows, for layers that transform first (else may be NULL) */
 } varco_network_buffers;
 int32_t varco_link_partitions(varco_ctx* ctx);
 /* Compresses x[0]'s boundary rows and runs every layer forward; layers in order, each as varco_layer_fwd. */

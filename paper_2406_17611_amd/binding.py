@@ -71,7 +71,7 @@ class NetworkBuffers(C.Structure):
     """varco_network_buffers: device addresses of the arenas of a whole network."""
     _fields_ = [("x", C.c_void_p * (MAX_LAYERS + 1)), ("z", C.c_void_p * MAX_LAYERS), ("m", C.c_void_p * MAX_LAYERS),
                 ("h1", C.c_void_p * MAX_LAYERS), ("h0", C.c_void_p * MAX_LAYERS), ("dh1", C.c_void_p * MAX_LAYERS),
-                ("dh0", C.c_void_p * MAX_LAYERS), ("dx", C.c_void_p * (MAX_LAYERS + 1)), ("dz_halo", C.c_void_p * MAX_LAYERS)]
+                ("dh0", C.c_void_p * MAX_LAYERS), ("dx", C.c_void_p * (MAX_LAYERS + 1))]
 
 
 class VarcoError(RuntimeError):

@@ -310,7 +310,7 @@ __global__ __launch_bounds__(kBlock) void halo_rows_kernel(MaskRule rule, const 
         const MaskAffine m = varco_affine(rule, uint32_t(gids[s]));
         ab = (m.a << 16) | m.b;
     }
-    out[s] = make_uint2(ab, uint32_t(zrow[s]));
+    out[s] = make_uint2(ab, uint32_t(zrow ? zrow[s] : s));
 }
 
 // Whether whole rows through LDS beat element-wise accesses (measured over widths 75 to 512 and ratios 2 to 64). The decoder

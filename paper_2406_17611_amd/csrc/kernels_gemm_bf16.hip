@@ -406,9 +406,9 @@ void with_flag(bool b, F&& f) {
 }  // namespace
 
 namespace {
-// TN: B can be read four columns at a time.
+// TN: B can be read four columns at a time (columns between n and the pitch may be read; their products are not stored).
 bool b_vector_ok(const GemmArgs& ga) {
-    return aligned_to(ga.b.ptr, 8) && aligned_to(ga.b.gate, 8) && ga.b.ld % 4 == 0 && ga.n % 4 == 0;
+    return aligned_to(ga.b.ptr, 8) && aligned_to(ga.b.gate, 8) && ga.b.ld % 4 == 0 && (ga.n % 4 == 0 || ga.b.ld >= (ga.n + 3) / 4 * 4);
 }
 }  // namespace
 

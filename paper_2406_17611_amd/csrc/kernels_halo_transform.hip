@@ -38,6 +38,7 @@ struct HaloRows {
     int32_t n;              // halo rows
     uint32_t width, k, magic;
     int32_t fo;             // columns of the transformed rows
+    int32_t ldy;            // elements between rows of y / dy
 };
 
 __device__ __forceinline__ uint32_t position(const HaloRows& p, uint32_t ab, uint32_t j) {
@@ -224,7 +225,7 @@ __global__ __launch_bounds__(kThreads, 2) void halo_transform_fwd_kernel(HaloRow
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
             const int32_t r = rb * 32 + 8 * (v >> 2) + 4 * lk + (v & 3);
-            if (r < rows && col < p.fo) y[int64_t(row0 + r) * p.fo + col] = float_to_bf16(acc[v]);
+            if (r < rows && col < p.fo) y[int64_t(row0 + r) * p.ldy + col] = float_to_bf16(acc[v]);
         }
         __syncthreads();                           // every fragment has been read
         walk_rows<VEC, kClear, false>(p, row0, rows, tile, nullptr, VEC == 8 ? &cur : nullptr);
@@ -336,7 +337,7 @@ __global__ __launch_bounds__(kThreads, 2) void halo_transform_wgrad_kernel(HaloR
     Ahead next, cur;
     auto fetch_tile = [&](int32_t t) {
         const int32_t row0 = t * kTileT, rows = min(kTileT, p.n - row0);
-        fetch_dy<kDy>(dy + int64_t(row0) * p.fo, rows * p.fo, dnext);      // rows beyond the tile: zeros
+        fetch_dy<kDy>(dy + int64_t(row0) * p.ldy, rows * p.ldy, dnext);    // rows beyond the tile: zeros
         if (VEC == 8) fetch_ahead<true>(p, row0, rows, next);
     };
     if (int32_t(blockIdx.x) < n_tiles) fetch_tile(blockIdx.x);
@@ -347,9 +348,9 @@ __global__ __launch_bounds__(kThreads, 2) void halo_transform_wgrad_kernel(HaloR
 #pragma unroll
         for (int i = 0; i < kDy; ++i) {
             const int32_t e = threadIdx.x + i * kThreads;
-            if (e < kTileT * p.fo) {
-                const int32_t r = e / p.fo;
-                dtile[(e - r * p.fo) * kPitchT + r] = dnext[i];
+            if (e < kTileT * p.ldy) {
+                const int32_t r = e / p.ldy;
+                dtile[(e - r * p.ldy) * kPitchT + r] = dnext[i];      // (columns beyond fo are never read back)
             }
         }
         __syncthreads();
@@ -386,7 +387,7 @@ bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) ==
 
 bool shape_ok(const HaloTransform& h) {
     return h.width >= 16 && h.width <= uint32_t(kMaxWidth) && h.width % 16 == 0 && h.k <= h.width && h.fo >= 1 && h.fo <= 64 &&
-           h.rec && (h.z || h.k == 0);
+           (h.ldy == 0 || (h.ldy >= h.fo && h.ldy <= 64)) && h.rec && (h.z || h.k == 0);
 }
 
 HaloRows device_args(const HaloTransform& h) {
@@ -396,6 +397,7 @@ HaloRows device_args(const HaloTransform& h) {
     p.n = h.n;
     p.width = h.width, p.k = h.k, p.magic = h.width_magic;
     p.fo = h.fo;
+    p.ldy = h.ldy ? h.ldy : h.fo;
     return p;
 }
 
@@ -410,7 +412,7 @@ hipError_t varco_launch_halo_transform_fwd(const HaloTransform& h, const void* w
     if (h.n <= 0) return hipSuccess;
     if (!shape_ok(h) || !wt || !y || wpitch < int32_t(h.width) || wpitch % 8 != 0 || !aligned16(wt)) return hipErrorInvalidValue;
     const HaloRows p = device_args(h);
-    const dim3 grid(grid_for(h.n, kTile, 512)), block(kThreads);
+    const dim3 grid(grid_for(h.n, kTile, kHaloTransformGroups)), block(kThreads);
     if (h.k % 8 == 0 && aligned16(h.z))
         hipLaunchKernelGGL(halo_transform_fwd_kernel<8>, grid, block, 0, stream, p, static_cast<const uint16_t*>(wt), wpitch,
                            static_cast<uint16_t*>(y));
@@ -425,7 +427,7 @@ hipError_t varco_launch_halo_transform_bwd(const HaloTransform& h, const void* d
     if (h.n <= 0 || h.k == 0) return hipSuccess;
     if (!shape_ok(h) || !dy || !wr || !dz || cpitch < h.fo || cpitch % 8 != 0 || !aligned16(wr)) return hipErrorInvalidValue;
     const HaloRows p = device_args(h);
-    const dim3 grid(grid_for(h.n, kTile, 512)), block(kThreads);
+    const dim3 grid(grid_for(h.n, kTile, kHaloTransformGroups)), block(kThreads);
     if (h.k % 8 == 0 && aligned16(dz))
         hipLaunchKernelGGL(halo_transform_bwd_kernel<8>, grid, block, 0, stream, p, static_cast<const uint16_t*>(dy),
                            static_cast<const uint16_t*>(wr), cpitch, static_cast<uint16_t*>(dz));
@@ -443,7 +445,7 @@ hipError_t varco_launch_halo_transform_wgrad(const HaloTransform& h, const void*
     const int64_t fit = partial_elems / (int64_t(h.width) * h.fo);
     if (fit < 1) return hipErrorInvalidValue;
     const HaloRows p = device_args(h);
-    const dim3 grid(grid_for(h.n, kTileT, std::min<int64_t>(512, fit))), block(kThreads);
+    const dim3 grid(grid_for(h.n, kTileT, std::min<int64_t>(kHaloTransformGroups, fit))), block(kThreads);
     *slabs = int32_t(grid.x);
     if (h.k % 8 == 0 && aligned16(h.z))
         hipLaunchKernelGGL(halo_transform_wgrad_kernel<8>, grid, block, 0, stream, p, static_cast<const uint16_t*>(dy), partial);

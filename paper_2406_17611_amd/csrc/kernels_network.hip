@@ -425,7 +425,8 @@ __global__ __launch_bounds__(kBlock) void link_halo_kernel(LinkPartition p, int3
 // consumers' halo rows must all be of this boundary node, and of its row of the compressed buffer.
 __global__ __launch_bounds__(kBlock) void link_owner_kernel(LinkPartition p, int64_t halo_total, const int32_t* halo_len,
                                                             const int32_t* halo_gid, const int32_t* halo_zrow, int32_t* owner_row,
-                                                            int32_t* cross_len, int32_t* brow, int32_t* bgid, int32_t* flags) {
+                                                            int32_t* cross_len, int32_t* brow, int32_t* bgid, int32_t* zrow_of,
+                                                            int32_t* flags) {
     const int32_t b = blockIdx.x * kBlock + threadIdx.x;
     if (b >= p.d.n_boundary) return;
     const int32_t i = p.d.boundary_rows[b], gid = p.d.local_gid[i], row = int32_t(p.row_off) + i, zrow = p.d.z_row_offset + b;
@@ -440,7 +441,7 @@ __global__ __launch_bounds__(kBlock) void link_owner_kernel(LinkPartition p, int
         if (halo_gid[h] != gid || halo_zrow[h] != zrow || atomicExch(owner_row + h, row) != -1) bad = true;
         total += halo_len[h];
     }
-    brow[zrow] = row, bgid[zrow] = gid;
+    brow[zrow] = row, bgid[zrow] = gid, zrow_of[row] = zrow;
     cross_len[row] = total;
     if (bad) atomicOr(flags, VARCO_BAD_LINK);
 }
@@ -526,10 +527,10 @@ hipError_t varco_launch_link_halo(const LinkPartition& p, int32_t* halo_len, int
 }
 hipError_t varco_launch_link_owner(const LinkPartition& p, int64_t halo_total, const int32_t* halo_len, const int32_t* halo_gid,
                                    const int32_t* halo_zrow, int32_t* owner_row, int32_t* cross_len, int32_t* brow, int32_t* bgid,
-                                   int32_t* flags, hipStream_t stream) {
+                                   int32_t* zrow_of, int32_t* flags, hipStream_t stream) {
     if (p.d.n_boundary == 0) return hipSuccess;
     hipLaunchKernelGGL(link_owner_kernel, blocks_for(p.d.n_boundary), dim3(kBlock), 0, stream, p, halo_total, halo_len, halo_gid,
-                       halo_zrow, owner_row, cross_len, brow, bgid, flags);
+                       halo_zrow, owner_row, cross_len, brow, bgid, zrow_of, flags);
     return hipGetLastError();
 }
 hipError_t varco_launch_link_starts(const LinkPartition& p, const int32_t* halo_len, const int32_t* cross_ptr, int32_t* prod_start,

@@ -136,7 +136,7 @@ void free_network(NetState& net) {
     free_plan(net.fwd);
     for (void* p : {static_cast<void*>(net.edges), static_cast<void*>(net.arow), static_cast<void*>(net.vals), static_cast<void*>(net.prow),
                     static_cast<void*>(net.t_local), static_cast<void*>(net.t_cross), static_cast<void*>(net.nodes.nodes),
-                    static_cast<void*>(net.nodes.pieces), static_cast<void*>(net.brow), static_cast<void*>(net.bgid)})
+                    static_cast<void*>(net.nodes.pieces), static_cast<void*>(net.brow), static_cast<void*>(net.bgid), static_cast<void*>(net.zrow_of)})
         if (p) (void)hipFree(p);
     net = NetState{};
 }
@@ -279,15 +279,25 @@ size_t prod_need(const varco_ctx* ctx) {
 
 // Floats of the two buffers of the layers that transform first: transformed rows of the local and halo nodes of the
 // largest registered partition at the widest such layer's output, and a two-word record per halo row.
-void transform_first_need(const varco_ctx* ctx, size_t* rows_out, size_t* records_out) {
+// shares_out: floats of the shares of a weight gradient over the received rows (linked partitions).
+void transform_first_need(const varco_ctx* ctx, size_t* rows_out, size_t* records_out, size_t* shares_out) {
     int32_t fo = 0;
+    *shares_out = 0;
     for (int32_t l = 0; l < ctx->n_layers; ++l)
-        if (ctx->layers[l].order == VARCO_ORDER_TRANSFORM_FIRST) fo = std::max(fo, ctx->widths[l + 1]);
+        if (ctx->layers[l].order == VARCO_ORDER_TRANSFORM_FIRST) {
+            fo = std::max(fo, ctx->widths[l + 1]);
+            if (ctx->net.linked) *shares_out = std::max(*shares_out, size_t(kHaloTransformGroups) * size_t(ctx->widths[l]) * size_t(ctx->widths[l + 1]));
+        }
     int64_t rows = 0, halo = 0;
     for (const PartState& ps : ctx->parts)
         if (ps.registered) rows = std::max(rows, int64_t(ps.d.n_local) + ps.d.n_halo), halo = std::max<int64_t>(halo, ps.d.n_halo);
     *rows_out = fo ? (size_t(rows) * size_t(fo) * size_t(ctx->elem_bytes()) + 3) / 4 : 0;
     *records_out = fo ? size_t(halo) * 2 : 0;
+    if (fo && ctx->net.linked) {     // all partitions at once: [Y ; Y_z], or dZ, G_loc and G_z, in rows of kClassPitch elements
+        const size_t block = size_t(2 * ctx->net.rows + ctx->net.boundary) * kClassPitch * size_t(ctx->elem_bytes()) / 4;
+        *rows_out = std::max(*rows_out, block);
+        *records_out = std::max(*records_out, size_t(ctx->net.boundary) * 2);
+    }
 }
 
 // Brings one workspace set up to what the registered partitions and the current ratios need (host side of
@@ -295,7 +305,9 @@ void transform_first_need(const varco_ctx* ctx, size_t* rows_out, size_t* record
 int32_t size_workspace(varco_ctx* ctx, Workspace& ws) {
     VARCO_HIP(ctx, grow(ws.dm, ws.dm_elems, ctx->need_dm));
     VARCO_HIP(ctx, grow(ws.spmm, ws.spmm_elems, ctx->need_spmm));
-    VARCO_HIP(ctx, grow(ws.gemm, ws.gemm_elems, ctx->need_gemm));
+    size_t tf_rows = 0, tf_records = 0, tf_shares = 0;
+    transform_first_need(ctx, &tf_rows, &tf_records, &tf_shares);
+    VARCO_HIP(ctx, grow(ws.gemm, ws.gemm_elems, ctx->need_gemm + tf_shares));
     VARCO_HIP(ctx, grow(ws.w, ws.w_elems, ctx->need_w));
     VARCO_HIP(ctx, grow(ws.loss, ws.loss_elems, size_t(2) * kLossBlocks));
     const size_t prod = prod_need(ctx);
@@ -308,8 +320,6 @@ int32_t size_workspace(varco_ctx* ctx, Workspace& ws) {
             if (prod > ws.prod_elems) VARCO_HIP(ctx, grow(ws.prod, ws.prod_elems, prod + prod / 4));
         }
     }
-    size_t tf_rows = 0, tf_records = 0;
-    transform_first_need(ctx, &tf_rows, &tf_records);
     VARCO_HIP(ctx, grow(ws.tf, ws.tf_elems, tf_rows));
     VARCO_HIP(ctx, grow(ws.hrows, ws.hrows_elems, tf_records));
     if (ws.w_tags.empty()) ws.w_tags.resize(size_t(ctx->n_layers) * 4);

@@ -50,6 +50,7 @@ struct NetState {
     NodePlan nodes;
     int32_t* brow = nullptr;          // [boundary] arena rows of the boundary nodes, in compressed-buffer order
     int32_t* bgid = nullptr;          // [boundary] their node ids
+    int32_t* zrow_of = nullptr;       // [rows] compressed-buffer row of an arena row, -1 for a row that is no boundary node
 };
 
 // Device scratch of the layer calls. Calls issued on different streams may run concurrently, so every

@@ -140,7 +140,7 @@ hipError_t varco_launch_calibration_copy(void* dst, const void* src, int64_t byt
 hipError_t varco_launch_sum_gradients(float* dst, const float* src, int64_t n, hipStream_t stream);
 
 // out[s] = {(a << 16) | b of node gids[s] under `rule` (1 << 16, the identity, when every element is kept), zrow[s]}:
-// element j of halo row s sits at position (a j + b) mod width; the per-row records of HaloTransform.
+// element j of halo row s sits at position (a j + b) mod width; the per-row records of HaloTransform. zrow null: row s.
 hipError_t varco_launch_halo_rows(const MaskRule& rule, const int32_t* gids, const int32_t* zrow, int32_t n, uint2* out,
                                   hipStream_t stream);
 
@@ -206,7 +206,7 @@ hipError_t varco_launch_link_edges(const LinkPartition& p, const int32_t* prow_p
 hipError_t varco_launch_link_halo(const LinkPartition& p, int32_t* halo_len, int32_t* halo_gid, int32_t* halo_zrow, hipStream_t stream);
 hipError_t varco_launch_link_owner(const LinkPartition& p, int64_t halo_total, const int32_t* halo_len, const int32_t* halo_gid,
                                    const int32_t* halo_zrow, int32_t* owner_row, int32_t* cross_len, int32_t* brow, int32_t* bgid,
-                                   int32_t* flags, hipStream_t stream);
+                                   int32_t* zrow_of, int32_t* flags, hipStream_t stream);
 hipError_t varco_launch_link_starts(const LinkPartition& p, const int32_t* halo_len, const int32_t* cross_ptr, int32_t* prod_start,
                                     hipStream_t stream);
 hipError_t varco_launch_link_transposed(const LinkPartition& p, const int32_t* prod_start, uint2* t_local, uint2* t_cross, hipStream_t stream);
@@ -277,7 +277,22 @@ struct HaloTransform {
     int32_t n = 0;
     uint32_t width = 0, k = 0, width_magic = 0;
     int32_t fo = 0;
+    int32_t ldy = 0;              // elements between rows of y / dy (0: fo)
 };
+
+constexpr int kHaloTransformGroups = 512;      // most workgroups (shares of a weight gradient) of a launch: two per compute unit
+
+// The same layer for all partitions at once (kernels_class_first.hip): rows of Y, G and dZ take kClassPitch elements.
+constexpr int kClassPitch = 64;
+hipError_t varco_launch_narrow_forward(const SpmmPlan& plan, const VarcoEdge* edge, const float* vals, const void* y, int32_t rows, void* out,
+                                       int32_t fo, float* partial, hipStream_t stream, const LaunchTag& tag);
+// g_z may be null (nothing exchanged). dz: rows x fo; dz_padded, g_loc: rows x kClassPitch; partial: kClassPitch floats per piece.
+hipError_t varco_launch_narrow_backward(const NodePlan& plan, const uint2* t_local, const uint2* t_cross, const void* dz, int64_t rows,
+                                        const int32_t* zrow_of, void* dz_padded, void* g_loc, void* g_z, int32_t fo, float* partial,
+                                        hipStream_t stream, const LaunchTag& tag);
+hipError_t varco_launch_class_dgrad(const void* g_loc, const void* g_z, const int32_t* zrow_of, const int32_t* bgid, int64_t rows,
+                                    const MaskRule& rule, int32_t fo, const void* wr, int32_t cpitch, void* dx, hipStream_t stream,
+                                    const LaunchTag& tag);
 // y[s, :] = X~[s, :] H (n x fo, bf16), H as its bf16 copy wt[column][position] (pitch wpitch).
 hipError_t varco_launch_halo_transform_fwd(const HaloTransform& h, const void* wt, int32_t wpitch, void* y, hipStream_t stream);
 // dz[s, j] = (dy[s, :] H^T)[position of j] (n x k, bf16), H as its bf16 copy wr[position][column] (pitch cpitch).

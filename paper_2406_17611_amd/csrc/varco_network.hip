@@ -89,6 +89,8 @@ int32_t link_impl(varco_ctx* ctx) {
     VARCO_HIP(ctx, cross_ptr_d.make(size_t(net.rows + 1) * 4));
     VARCO_HIP(ctx, alloc(net.brow, size_t(net.boundary)));
     VARCO_HIP(ctx, alloc(net.bgid, size_t(net.boundary)));
+    VARCO_HIP(ctx, alloc(net.zrow_of, size_t(net.rows)));
+    if (net.rows) VARCO_HIP(ctx, hipMemset(net.zrow_of, 0xFF, size_t(net.rows) * 4));
     if (net.halo_rows) VARCO_HIP(ctx, hipMemset(owner_row.p, 0xFF, size_t(net.halo_rows) * 4));
     if (net.rows) VARCO_HIP(ctx, hipMemset(cross_len.p, 0, size_t(net.rows) * 4));
     if (!ctx->d_flags) VARCO_HIP(ctx, hipMalloc(reinterpret_cast<void**>(&ctx->d_flags), sizeof(int32_t)));
@@ -97,7 +99,7 @@ int32_t link_impl(varco_ctx* ctx) {
     for (int32_t q = 0; q < P; ++q) VARCO_HIP(ctx, varco_launch_link_halo(lp[q], halo_len.i32(), halo_gid.i32(), halo_zrow.i32(), nullptr));
     for (int32_t q = 0; q < P; ++q)
         VARCO_HIP(ctx, varco_launch_link_owner(lp[q], net.halo_rows, halo_len.i32(), halo_gid.i32(), halo_zrow.i32(), owner_row.i32(),
-                                               cross_len.i32(), net.brow, net.bgid, ctx->d_flags, nullptr));
+                                               cross_len.i32(), net.brow, net.bgid, net.zrow_of, ctx->d_flags, nullptr));
     VARCO_HIP(ctx, hipMemcpy(&flags, ctx->d_flags, sizeof(flags), hipMemcpyDeviceToHost));
     if (flags) return varco_fail(ctx, VARCO_ERR_SHAPE, "varco_link_partitions: a map of returned rows does not fit the consumers' halo rows");
     std::vector<int32_t> len(size_t(net.rows)), cross_ptr(size_t(net.rows) + 1, 0);
@@ -173,7 +175,7 @@ int32_t link_impl(varco_ctx* ctx) {
         gemm_elems += layer_elems * (ctx->conv == VARCO_CONV_SAGE ? 2 : 1);   // the partial products of all layers wait for one sum
     }
     ctx->need_dm = std::max(ctx->need_dm, (size_t(net.rows) * size_t(wmax) * size_t(ctx->elem_bytes()) + 3) / 4);
-    ctx->need_spmm = std::max(ctx->need_spmm, size_t(std::max<int64_t>(net.fwd.n_partials, n_slots)) * size_t(wmax));
+    ctx->need_spmm = std::max(ctx->need_spmm, size_t(std::max<int64_t>(net.fwd.n_partials, n_slots)) * size_t(std::max(wmax, kClassPitch)));
     ctx->need_gemm = std::max(ctx->need_gemm, size_t(gemm_elems));
     net.linked = true;
     return size_all_workspaces(ctx);
@@ -241,11 +243,156 @@ int32_t compress_all(varco_ctx* ctx, int32_t layer, const MaskRule& rule, const 
     return VARCO_OK;
 }
 
-const char* at(const void* base, int64_t row, int32_t width, double es) {
-    return base ? static_cast<const char*>(base) + row * width * int64_t(es) : nullptr;
+// Partial products of the weight gradients of a backward pass, summed by one launch at its end.
+struct WeightSums {
+    ReduceJob job[kMaxReduceJobs];
+    int n = 0;
+    size_t used = 0;              // floats of the workspace's partial buffer
+};
+
+// A layer that transforms before it aggregates (kernels_class_first.hip).
+int32_t class_fits(varco_ctx* ctx, const Workspace& ws, const char* fn) {
+    const NetState& net = ctx->net;
+    const size_t need = size_t(2 * net.rows + net.boundary) * kClassPitch * size_t(ctx->elem_bytes()) / 4;
+    if (need <= ws.tf_elems && size_t(net.boundary) * 2 <= ws.hrows_elems) return VARCO_OK;
+    std::string m = std::string(fn) + ": the stream's workspace is too small; call varco_prepare";
+    return varco_fail(ctx, VARCO_ERR_STATE, m.c_str());
 }
-char* at(void* base, int64_t row, int32_t width, double es) {
-    return base ? static_cast<char*>(base) + row * width * int64_t(es) : nullptr;
+
+HaloTransform boundary_transform(const varco_ctx* ctx, const Workspace& ws, const MaskRule& rule, const void* z, int32_t fo) {
+    HaloTransform h;
+    h.z = z;
+    h.rec = reinterpret_cast<const uint2*>(ws.hrows);
+    h.n = int32_t(ctx->net.boundary);
+    h.width = rule.width, h.k = rule.k, h.width_magic = rule.width_magic;
+    h.fo = fo, h.ldy = kClassPitch;
+    return h;
+}
+
+int32_t class_fwd(varco_ctx* ctx, Workspace& ws, const varco_network_buffers& b, int32_t l, hipStream_t st) {
+    const NetState& net = ctx->net;
+    const int32_t fi = ctx->widths[l], fo = ctx->widths[l + 1];
+    const int dt = ctx->dtype;
+    const double es = ctx->elem_bytes();
+    const MaskRule rule = make_rule(ctx, l);
+    ctx->layers[l].ran_forward = true;
+    ctx->stats.fwd_elems[l] += net.halo_rows * rule.k;
+    ctx->stats.full_fwd_elems[l] += net.halo_rows * fi;
+    if (net.rows == 0) return VARCO_OK;
+    if (int32_t rc = class_fits(ctx, ws, "varco_network_forward")) return rc;
+    uint16_t* const y = reinterpret_cast<uint16_t*>(ws.tf);
+    uint16_t* const yz = y + net.rows * kClassPitch;
+    GemmArgs g;
+    g.m = int32_t(net.rows), g.n = fo, g.k = fi;
+    g.a.ptr = b.x[l], g.a.ld = fi, g.a.dtype = dt;
+    g.b.ptr = b.h1[l], g.b.ld = fo;
+    g.c = y, g.ldc = kClassPitch, g.c_dtype = dt;
+    VARCO_HIP(ctx, prep_weight(ctx, ws, l, b.h1[l], fi, fo, true, 0, false, st, g));
+    VARCO_HIP(ctx, varco_launch_gemm(g, st, ctx->tag(VARCO_K_GEMM_FWD, 0, 2.0 * double(net.rows) * fo * fi)));
+    if (net.boundary > 0) {          // k = 0: rows of zeros
+        ctx->prof.interrupt();
+        VARCO_HIP(ctx, varco_launch_halo_rows(rule, net.bgid, nullptr, int32_t(net.boundary), reinterpret_cast<uint2*>(ws.hrows), st));
+        const LaunchTag tag = ctx->tag(VARCO_K_GEMM_FWD, double(net.boundary) * (rule.k + fo) * es, 2.0 * double(net.boundary) * fo * rule.k);
+        tag.begin(st);
+        const hipError_t e = varco_launch_halo_transform_fwd(boundary_transform(ctx, ws, rule, b.z[l], fo), g.b_prep, int32_t(g.b_prep_ld), yz, st);
+        tag.end(st);
+        VARCO_HIP(ctx, e);
+    }
+    const double entries = double(net.nnz) * 8.0 + (double(net.rows) + 1.0) * 4.0;
+    VARCO_HIP(ctx, varco_launch_narrow_forward(net.fwd, net.edges, net.vals, y, int32_t(net.rows), b.x[l + 1], fo, ws.spmm, st,
+                                               ctx->tag(VARCO_K_AGG_FWD, entries + (2.0 * double(net.rows) + double(net.boundary)) * fo * es, 0,
+                                                        entries + (double(net.rows) + double(net.nnz)) * fo * es)));
+    if (ctx->conv == VARCO_CONV_SAGE) {   // self tap
+        GemmArgs g0;
+        g0.m = int32_t(net.rows), g0.n = fo, g0.k = fi;
+        g0.a = g.a;
+        g0.b.ptr = b.h0[l], g0.b.ld = fo;
+        g0.c = b.x[l + 1], g0.ldc = fo, g0.c_dtype = dt;
+        g0.accumulate = true;
+        VARCO_HIP(ctx, prep_weight(ctx, ws, l, b.h0[l], fi, fo, true, 1, false, st, g0));
+        VARCO_HIP(ctx, varco_launch_gemm(g0, st, ctx->tag(VARCO_K_GEMM_FWD, 0, 2.0 * double(net.rows) * fo * fi)));
+    }
+    return VARCO_OK;
+}
+
+// One split product into the weight sums; `g` with everything but the split set.
+int32_t add_weight_product(varco_ctx* ctx, Workspace& ws, GemmArgs& g, WeightSums& sums, hipStream_t st) {
+    const int products = g.c_dual ? 2 : 1;
+    const size_t one = size_t(g.m) * g.n;
+    int32_t split = 1;
+    g.deferred = &split;
+    g.split_k = wgrad_splits(g.m, g.n, g.k, gemm_kind(g), products);
+    if (sums.used + size_t(g.split_k) * one * products > ws.gemm_elems || sums.n + products > kMaxReduceJobs)
+        return varco_fail(ctx, VARCO_ERR_STATE, "varco_network_backward: workspace too small");
+    g.partial = ws.gemm + sums.used;
+    VARCO_HIP(ctx, varco_launch_gemm(g, st, ctx->tag(VARCO_K_GEMM_WGRAD, 0, 2.0 * products * double(one) * double(g.k))));
+    for (int i = 0; split > 1 && i < products; ++i) {
+        sums.job[sums.n++] = ReduceJob{g.partial + size_t(i) * split * one, static_cast<float*>(i ? g.c_dual : g.c), g.ldc, split, g.m, g.n, 0};
+        sums.used += size_t(split) * one;
+    }
+    return VARCO_OK;
+}
+
+int32_t class_bwd(varco_ctx* ctx, Workspace& ws, const varco_network_buffers& b, int32_t l, WeightSums& sums, hipStream_t st) {
+    const NetState& net = ctx->net;
+    const int32_t fi = ctx->widths[l], fo = ctx->widths[l + 1];
+    const int dt = ctx->dtype;
+    const double es = ctx->elem_bytes();
+    const bool sage = ctx->conv == VARCO_CONV_SAGE, need = l > 0;
+    const MaskRule rule = make_rule(ctx, l);
+    const bool far = net.nnz_cross > 0 && rule.k > 0;
+    if (int32_t rc = class_fits(ctx, ws, "varco_network_backward")) return rc;
+    uint16_t* const dz = reinterpret_cast<uint16_t*>(ws.tf);
+    uint16_t* const g_loc = dz + net.rows * kClassPitch;
+    uint16_t* const g_z = g_loc + net.rows * kClassPitch;
+    const double entries = double(net.nnz) * 8.0 + (double(net.rows) + 1.0) * 4.0;
+    VARCO_HIP(ctx, varco_launch_narrow_backward(net.nodes, net.t_local, net.t_cross, b.dx[l + 1], net.rows, net.zrow_of, dz, g_loc, far ? g_z : nullptr,
+                                                fo, ws.spmm, st,
+                                                ctx->tag(VARCO_K_AGG_BWD_LOCAL, entries + (2.0 * double(net.rows) + double(net.boundary)) * fo * es, 0,
+                                                         entries + (double(net.rows) + double(net.nnz)) * fo * es)));
+    GemmArgs g;
+    g.m = fi, g.n = fo, g.k = int32_t(net.rows);
+    g.a.ptr = b.x[l], g.a.ld = fi, g.a.transposed = true, g.a.dtype = dt;
+    g.b.ptr = g_loc, g.b.ld = kClassPitch, g.b.dtype = dt;
+    g.c = b.dh1[l], g.ldc = fo;
+    g.accumulate = true;
+    if (int32_t rc = add_weight_product(ctx, ws, g, sums, st)) return rc;
+    if (sage) {
+        g.b.ptr = dz, g.c = b.dh0[l];
+        if (int32_t rc = add_weight_product(ctx, ws, g, sums, st)) return rc;
+    }
+    if (far) {   // + X~_z^T G_z: per-workgroup shares
+        VARCO_HIP(ctx, varco_launch_halo_rows(rule, net.bgid, nullptr, int32_t(net.boundary), reinterpret_cast<uint2*>(ws.hrows), st));
+        const LaunchTag tag = ctx->tag(VARCO_K_GEMM_WGRAD, double(net.boundary) * (rule.k + fo) * es, 2.0 * double(rule.k) * fo * double(net.boundary));
+        int32_t slabs = 0;
+        float* const partial = ws.gemm + sums.used;
+        tag.begin(st);
+        const hipError_t e = varco_launch_halo_transform_wgrad(boundary_transform(ctx, ws, rule, b.z[l], fo), g_z, partial,
+                                                               int64_t(ws.gemm_elems - sums.used), &slabs, st);
+        tag.end(st);
+        VARCO_HIP(ctx, e);
+        // (added by a launch of its own: the sums of a pass go to distinct results)
+        VARCO_HIP(ctx, varco_launch_gemm_reduce(partial, slabs, fi, fo, static_cast<float*>(b.dh1[l]), fo, true, st, tag));
+    }
+    if (!need) return VARCO_OK;
+    GemmArgs gw;                       // carries the slot of the weights' bf16 copy [position][column]
+    VARCO_HIP(ctx, prep_weight(ctx, ws, l, b.h1[l], fi, fo, false, 0, false, st, gw));
+    VARCO_HIP(ctx, varco_launch_class_dgrad(g_loc, far ? g_z : nullptr, net.zrow_of, net.bgid, net.rows, rule, fo, gw.b_prep, int32_t(gw.b_prep_ld),
+                                            b.dx[l], st, ctx->tag(VARCO_K_GEMM_DGRAD, 0, 2.0 * fi * fo * double(net.rows))));
+    if (sage) {                        // + dZ H0^T
+        GemmArgs g0;
+        g0.m = int32_t(net.rows), g0.n = fi, g0.k = fo;
+        g0.a.ptr = b.dx[l + 1], g0.a.ld = fo, g0.a.dtype = dt;
+        g0.b.ptr = b.h0[l], g0.b.ld = fo, g0.b.transposed = true;
+        g0.c = b.dx[l], g0.ldc = fi, g0.c_dtype = dt;
+        g0.accumulate = true;
+        VARCO_HIP(ctx, varco_launch_gemm(g0, st, ctx->tag(VARCO_K_GEMM_DGRAD, 0, 2.0 * fi * fo * double(net.rows))));
+    }
+    if (rule.k > 0) {
+        ctx->stats.bwd_elems[l] += net.halo_rows * rule.k;
+        ctx->stats.full_bwd_elems[l] += net.halo_rows * fi;
+    }
+    return VARCO_OK;
 }
 
 int32_t layer_fwd(varco_ctx* ctx, Workspace& ws, const varco_network_buffers& b, int32_t l, hipStream_t st) {
@@ -255,11 +402,8 @@ int32_t layer_fwd(varco_ctx* ctx, Workspace& ws, const varco_network_buffers& b,
     const int dt = ctx->dtype;
     const double es = ctx->elem_bytes();
     if (ctx->layers[l].order == VARCO_ORDER_TRANSFORM_FIRST) {
-        for (int32_t q = 0; q < ctx->n_parts; ++q)
-            if (int32_t rc = varco_layer_fwd(ctx, l, q, at(b.x[l], net.row_off[q], fi, es), b.z[l], b.h1[l], sage ? b.h0[l] : nullptr,
-                                             at(b.x[l + 1], net.row_off[q], fo, es), last ? nullptr : b.z[l + 1], nullptr, st))
-                return rc;
-        return VARCO_OK;
+        if (int32_t rc = class_fwd(ctx, ws, b, l, st)) return rc;
+        return last ? VARCO_OK : compress_all(ctx, l + 1, make_rule(ctx, l + 1), b.x[l + 1], b.z[l + 1], st);
     }
     const MaskRule rule = make_rule(ctx, l);
     ctx->layers[l].ran_forward = true;
@@ -283,33 +427,15 @@ int32_t layer_fwd(varco_ctx* ctx, Workspace& ws, const varco_network_buffers& b,
     return last ? VARCO_OK : compress_all(ctx, l + 1, make_rule(ctx, l + 1), b.x[l + 1], b.z[l + 1], st);
 }
 
-// Partial products of the weight gradients of a backward pass, summed by one launch at its end.
-struct WeightSums {
-    ReduceJob job[kMaxReduceJobs];
-    int n = 0;
-    size_t used = 0;              // floats of the workspace's partial buffer
-};
-
 int32_t layer_bwd(varco_ctx* ctx, Workspace& ws, const varco_network_buffers& b, int32_t l, WeightSums& sums, hipStream_t st) {
     const NetState& net = ctx->net;
     const int32_t fi = ctx->widths[l], fo = ctx->widths[l + 1];
     const bool sage = ctx->conv == VARCO_CONV_SAGE, need = l > 0;
     const int dt = ctx->dtype;
     const double es = ctx->elem_bytes();
-    if (ctx->layers[l].order == VARCO_ORDER_TRANSFORM_FIRST) {
-        for (int32_t q = 0; q < ctx->n_parts; ++q)
-            if (int32_t rc = varco_layer_bwd(ctx, l, q, at(b.dx[l + 1], net.row_off[q], fo, es), at(b.x[l + 1], net.row_off[q], fo, es),
-                                             at(b.x[l], net.row_off[q], fi, es), b.z[l], b.h1[l], sage ? b.h0[l] : nullptr, b.dh1[l],
-                                             sage ? b.dh0[l] : nullptr, need ? at(b.dx[l], net.row_off[q], fi, es) : nullptr,
-                                             need ? at(b.dz_halo[l], net.halo_off[q], ctx->layers[l].k, es) : nullptr, st))
-                return rc;
-        for (int32_t q = 0; need && q < ctx->n_parts; ++q)
-            if (int32_t rc = varco_accumulate_returned(ctx, l, q, nullptr, nullptr, b.dz_halo[l], at(b.dx[l], net.row_off[q], fi, es), st))
-                return rc;
-        return VARCO_OK;
-    }
     if (net.rows == 0) return VARCO_OK;
     const int32_t nl = int32_t(net.rows);
+    if (ctx->layers[l].order == VARCO_ORDER_TRANSFORM_FIRST) return class_bwd(ctx, ws, b, l, sums, st);
     const void* gate = ctx->act[l] == VARCO_ACT_RELU ? b.x[l + 1] : nullptr;
     {   // weight gradients: one reduction over the rows of all partitions (their sum is what Algorithm 1 asks for)
         GemmArgs g;
@@ -320,25 +446,16 @@ int32_t layer_bwd(varco_ctx* ctx, Workspace& ws, const varco_network_buffers& b,
         g.accumulate = true;
         g.f32_terms = dt == VARCO_F32 ? ctx->f32_terms : 0;
         // both taps' gradients by one launch where the kernels can: they share dZ (and its mask)
-        int32_t split = 1;
-        g.deferred = &split;
         if (sage) {
+            int32_t unused = 0;
+            g.deferred = &unused;
             g.a_dual = b.x[l], g.c_dual = b.dh0[l];
             if (!varco_gemm_dual_usable(g)) g.a_dual = nullptr, g.c_dual = nullptr;
         }
         const int products = g.c_dual ? 2 : 1;
         for (int tap = 0; tap < (sage ? 2 : 1); tap += products) {
             if (tap == 1) g.a.ptr = b.x[l], g.c = b.dh0[l];
-            g.split_k = wgrad_splits(fi, fo, nl, gemm_kind(g), products);
-            const size_t one = size_t(fi) * fo;
-            if (sums.used + size_t(g.split_k) * one * products > ws.gemm_elems)
-                return varco_fail(ctx, VARCO_ERR_STATE, "varco_network_backward: workspace too small");
-            g.partial = ws.gemm + sums.used;
-            VARCO_HIP(ctx, varco_launch_gemm(g, st, ctx->tag(VARCO_K_GEMM_WGRAD, 0, 2.0 * products * fi * fo * double(nl))));
-            for (int i = 0; split > 1 && i < products; ++i) {
-                sums.job[sums.n++] = ReduceJob{g.partial + size_t(i) * split * one, static_cast<float*>(i ? g.c_dual : g.c), g.ldc, split, fi, fo, 0};
-                sums.used += size_t(split) * one;
-            }
+            if (int32_t rc = add_weight_product(ctx, ws, g, sums, st)) return rc;
         }
     }
     if (!need) return VARCO_OK;
@@ -401,7 +518,7 @@ int32_t check_buffers(const varco_ctx* ctx, const varco_network_buffers* b, bool
     for (int32_t l = 0; l < L; ++l) {
         const bool first = ctx->layers[l].order == VARCO_ORDER_TRANSFORM_FIRST, sent = net.halo_rows > 0 && ctx->layers[l].k > 0;
         if (!b->h1[l] || (sage && !b->h0[l]) || (net.rows > 0 && (!b->x[l] || (!first && !b->m[l]))) || (sent && !b->z[l])) return null_pointer(ctx, fn);
-        if (backward && (!b->dh1[l] || (sage && !b->dh0[l]) || (net.rows > 0 && !b->dx[l + 1]) || (first && l > 0 && sent && !b->dz_halo[l])))
+        if (backward && (!b->dh1[l] || (sage && !b->dh0[l]) || (net.rows > 0 && !b->dx[l + 1]) ))
             return null_pointer(ctx, fn);
         if (int32_t rc = check_wide_rows(ctx, ctx->widths[l], {b->x[l], b->z[l], b->m[l], backward ? b->dx[l + 1] : nullptr}, fn)) return rc;
     }
@@ -459,12 +576,8 @@ extern "C" int32_t varco_network_backward(varco_ctx* ctx, const varco_network_bu
     Workspace* ws = nullptr;
     if (int32_t rc = workspace_for(ctx, st, &ws, fn)) return rc;
     WeightSums sums;
-    for (int32_t l = ctx->n_layers - 1; l >= 0; --l) {
-        if (ctx->layers[l].order == VARCO_ORDER_TRANSFORM_FIRST) {   // uses the partial buffer from its start
-            if (int32_t rc = finish_sums(ctx, sums, st)) return rc;
-        }
+    for (int32_t l = ctx->n_layers - 1; l >= 0; --l)
         if (int32_t rc = layer_bwd(ctx, *ws, *b, l, sums, st)) return rc;
-    }
     return finish_sums(ctx, sums, st);
 }
 

@@ -174,15 +174,15 @@ class PartitionedNetwork:
 
     # ------------------------------------------------------------------ one step
     def _ensure_buffers(self, returned=True):
-        """Message buffers of the current ratios. returned: those of the backward exchange, for every layer (what
-        per-partition calls hand back); otherwise only for the layers that transform first."""
+        """Message buffers of the current ratios. returned: those of the backward exchange too, which the
+        per-partition calls hand back."""
         for l in range(self.L):
             k = self.ctx.keep(l)
             need = self.b_total * k
             if self.z[l] is None or self._zcap[l] < need:
                 self.z[l] = torch.empty(max(need, 1), dtype=self.act_dtype, device=self.device)
                 self._zcap[l] = need
-            if self.need_backward and l > 0 and (returned or l in self.transform_first):
+            if self.need_backward and l > 0 and returned:
                 need = int(self.halo_off[-1]) * k
                 if self.dz_halo[l] is None or self._dzcap[l] < need:
                     self.dz_halo[l] = torch.empty(max(need, 1), dtype=self.act_dtype, device=self.device)
@@ -201,8 +201,6 @@ class PartitionedNetwork:
                 if self.dh0[l] is not None:
                     b.dh0[l] = self.dh0[l].data_ptr()
                 b.dx[l + 1] = self.dx[l + 1].data_ptr()
-                if self.dz_halo[l] is not None:
-                    b.dz_halo[l] = self.dz_halo[l].data_ptr()
         b.x[self.L] = self.x[self.L].data_ptr()
         return b
 

@@ -24,6 +24,15 @@ def test_node_sums_with_hubs(conv, widths, dtype):
     _compare_network(g, part, 3, conv, widths, ratios, steps=list(range(5)), tol=BF16_TOL if dtype == "bf16" else 1e-4, dtype=dtype)
 
 
+@pytest.mark.parametrize("conv,widths", [("gcn", (16, 48, 5)), ("sage", (24, 512, 64)), ("gcn", (40, 208, 47)), ("sage", (32, 7))])
+def test_class_layer_transforms_first_with_hubs(conv, widths):
+    # rows of 1 to 64 outputs; k ragged, complete and 0; tiles of 32 and 64 rows with a remainder
+    g = hub_graph(1500, 3, 1100, 6.0, conv, seed=86)
+    part = synth.random_partition(g.n, 3, seed=87)
+    ratios = [(8, 1), (5, 1), (3, 2), (1, 1), (1, 0)]
+    _compare_network(g, part, 3, conv, widths, ratios, steps=list(range(5)), tol=BF16_TOL, dtype="bf16", transform_first=(len(widths) - 2,))
+
+
 def test_uneven_and_empty_partitions():
     g = synth.small_random_graph(300, 5.0, "gcn", seed=83)
     part = np.zeros(g.n, dtype=np.int32)
