@@ -1,0 +1,186 @@
+// Sums of gathered dense rows by one wavefront, shared by the forward aggregation and the node sums of the backward pass.
+#pragma once
+
+#include <type_traits>
+
+#include "elem.h"
+
+// N consecutive stored elements, packed as they lie in memory until they are used: load(), get() converts, put() rounds and
+// stores.
+template <typename T, int N>
+struct Packed;
+template <int N>
+struct Packed<float, N> {
+    typedef float type __attribute__((ext_vector_type(N)));
+    static __device__ __forceinline__ type load(const float* p) { return *reinterpret_cast<const type*>(p); }
+    static __device__ __forceinline__ void get(const type& v, float (&x)[N]) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) x[i] = v[i];
+    }
+    static __device__ __forceinline__ void put(float* p, const float (&x)[N]) {
+        type v;
+#pragma unroll
+        for (int i = 0; i < N; ++i) v[i] = x[i];
+        *reinterpret_cast<type*>(p) = v;
+    }
+};
+template <>
+struct Packed<float, 1> {
+    using type = float;
+    static __device__ __forceinline__ type load(const float* p) { return *p; }
+    static __device__ __forceinline__ void get(const type& v, float (&x)[1]) { x[0] = v; }
+    static __device__ __forceinline__ void put(float* p, const float (&x)[1]) { *p = x[0]; }
+};
+template <int N>
+struct Packed<bf16_t, N> {
+    typedef uint32_t type __attribute__((ext_vector_type(N / 2)));
+    static __device__ __forceinline__ type load(const bf16_t* p) { return *reinterpret_cast<const type*>(p); }
+    static __device__ __forceinline__ void get(const type& v, float (&x)[N]) {
+#pragma unroll
+        for (int i = 0; i < N / 2; ++i) x[2 * i] = __uint_as_float(v[i] << 16), x[2 * i + 1] = __uint_as_float(v[i] & 0xFFFF0000u);
+    }
+    static __device__ __forceinline__ void put(bf16_t* p, const float (&x)[N]) {
+        type v;
+#pragma unroll
+        for (int i = 0; i < N / 2; ++i) v[i] = uint32_t(float_to_bf16(x[2 * i])) | (uint32_t(float_to_bf16(x[2 * i + 1])) << 16);
+        *reinterpret_cast<type*>(p) = v;
+    }
+};
+template <>
+struct Packed<bf16_t, 2> {
+    using type = uint32_t;
+    static __device__ __forceinline__ type load(const bf16_t* p) { return *reinterpret_cast<const uint32_t*>(p); }
+    static __device__ __forceinline__ void get(const type& v, float (&x)[2]) { x[0] = __uint_as_float(v << 16), x[1] = __uint_as_float(v & 0xFFFF0000u); }
+    static __device__ __forceinline__ void put(bf16_t* p, const float (&x)[2]) {
+        *reinterpret_cast<uint32_t*>(p) = uint32_t(float_to_bf16(x[0])) | (uint32_t(float_to_bf16(x[1])) << 16);
+    }
+};
+template <>
+struct Packed<bf16_t, 1> {
+    using type = uint16_t;
+    static __device__ __forceinline__ type load(const bf16_t* p) { return p->bits; }
+    static __device__ __forceinline__ void get(const type& v, float (&x)[1]) { x[0] = bf16_to_float(v); }
+    static __device__ __forceinline__ void put(bf16_t* p, const float (&x)[1]) { p->bits = float_to_bf16(x[0]); }
+};
+
+// Load from an address in global memory that was handled as a number (a generic address would go through the LDS check).
+template <typename T, int N>
+__device__ __forceinline__ typename Packed<T, N>::type load_packed(uint64_t address, uint32_t byte_offset) {
+    using V = typename Packed<T, N>::type;
+    return *(const __attribute__((address_space(1))) V*)((const __attribute__((address_space(1))) char*)address + byte_offset);
+}
+
+__device__ __forceinline__ uint32_t lane_value(uint32_t v, int byte_lane) { return uint32_t(__builtin_amdgcn_ds_bpermute(byte_lane, int(v))); }
+
+// acc += sum over i < n of w_i * row_i: lane i holds entry i's weight and the address of its row. NV > 0: a row of `width`
+// elements takes all 64 lanes, NV loads of VEC elements each; NV = 0: it takes one load of 1 << lpr_log2 lanes, and the groups
+// of lanes take different entries (sum_groups adds them). U rows of a group are requested before the first is used.
+// These kernels issue vector instructions most of the time on graphs of ordinary degree (a wavefront has a dozen entries), so
+// what is the same for the whole wavefront stays in scalar registers: with all lanes on one row its address and weight come by
+// v_readlane and the load takes a scalar base; the last batch leaves out by scalar branches what
+// is not there.
+constexpr int loads_per_row(int nv) { return nv > 0 ? nv : 1; }
+template <typename T, int VEC, int NV, int U>
+__device__ __forceinline__ void gather_rows(uint64_t addr, float w, int n, int32_t width, int lane, int lpr_log2, float (&acc)[loads_per_row(NV)][VEC]) {
+    using P = Packed<T, VEC>;
+    uint32_t lo = uint32_t(addr), hi = uint32_t(addr >> 32), wb = __float_as_uint(w);
+    // v_readlane reads lanes that are switched off, too: their values must be formed here, where every lane is on, and not (as
+    // the compiler is free to do) where the loads of the lanes below `width` are issued.
+    asm volatile("" : "+v"(lo), "+v"(hi), "+v"(wb));
+    if constexpr (NV > 0) {
+        uint32_t off[NV];                        // lanes beyond the row re-read its start (their sums are never stored)
+#pragma unroll
+        for (int m = 0; m < NV; ++m) off[m] = VEC * (lane + 64 * m) < width ? uint32_t(VEC * sizeof(T)) * uint32_t(lane + 64 * m) : 0u;
+        auto batch = [&](int i0, auto partial) {
+            constexpr bool PART = decltype(partial)::value;
+            typename P::type v[U][NV];
+            float wi[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (!PART || u == 0 || i0 + u < n) {
+                    const uint64_t row = (uint64_t(uint32_t(__builtin_amdgcn_readlane(int(hi), i0 + u))) << 32) |
+                                         uint32_t(__builtin_amdgcn_readlane(int(lo), i0 + u));
+                    wi[u] = __uint_as_float(uint32_t(__builtin_amdgcn_readlane(int(wb), i0 + u)));
+#pragma unroll
+                    for (int m = 0; m < NV; ++m) v[u][m] = load_packed<T, VEC>(row, off[m]);
+                }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (!PART || u == 0 || i0 + u < n)
+#pragma unroll
+                    for (int m = 0; m < NV; ++m) {
+                        float x[VEC];
+                        P::get(v[u][m], x);
+#pragma unroll
+                        for (int i = 0; i < VEC; ++i) acc[m][i] += wi[u] * x[i];
+                    }
+        };
+        int i0 = 0;
+        for (; i0 + U <= n; i0 += U) batch(i0, std::false_type{});
+        if (i0 < n) batch(i0, std::true_type{});
+    } else {
+        const int lpr = 1 << lpr_log2, ng = 64 >> lpr_log2, c = VEC * (lane & (lpr - 1)), g = lane >> lpr_log2;
+        const uint32_t off = c < width ? uint32_t(c) * uint32_t(sizeof(T)) : 0u;
+        auto batch = [&](int i0, auto count, auto partial) {
+            constexpr int N = decltype(count)::value;
+            constexpr bool PART = decltype(partial)::value;
+            typename P::type v[N];
+            uint32_t wi[N];
+#pragma unroll
+            for (int u = 0; u < N; ++u) {
+                const int i = i0 + u * ng + g;
+                const uint64_t row = (uint64_t(lane_value(hi, 4 * i)) << 32) | lane_value(lo, 4 * i);
+                wi[u] = lane_value(wb, 4 * i);
+                if (!PART || i < n) v[u] = load_packed<T, VEC>(row, off);
+            }
+#pragma unroll
+            for (int u = 0; u < N; ++u)
+                if (!PART || i0 + u * ng + g < n) {
+                    float x[VEC];
+                    P::get(v[u], x);
+#pragma unroll
+                    for (int i = 0; i < VEC; ++i) acc[0][i] += __uint_as_float(wi[u]) * x[i];
+                }
+        };
+        int i0 = 0;
+        for (; i0 + ng * U <= n; i0 += ng * U) batch(i0, std::integral_constant<int, U>{}, std::false_type{});
+        if (i0 + ng < n)
+            batch(i0, std::integral_constant<int, U>{}, std::true_type{});
+        else if (i0 < n)
+            batch(i0, std::integral_constant<int, 1>{}, std::true_type{});
+    }
+}
+
+// Every lane of a position gets the sum over the groups.
+template <int VEC, int NV>
+__device__ __forceinline__ void sum_groups(int lpr_log2, float (&acc)[loads_per_row(NV)][VEC]) {
+    if constexpr (NV == 0)
+        for (int off = 1 << lpr_log2; off < 64; off <<= 1)
+#pragma unroll
+            for (int i = 0; i < VEC; ++i) acc[0][i] += __shfl_xor(acc[0][i], off);
+}
+
+// Rows of fp32 in LDS or memory, VEC at a time.
+template <int VEC>
+__device__ __forceinline__ void add_floats(const float* p, float (&x)[VEC]) {
+    constexpr int W = VEC < 4 ? VEC : 4;
+#pragma unroll
+    for (int i = 0; i < VEC; i += W) {
+        const typename FloatVec<W>::type v = *reinterpret_cast<const typename FloatVec<W>::type*>(p + i);
+        const float* e = reinterpret_cast<const float*>(&v);
+#pragma unroll
+        for (int q = 0; q < W; ++q) x[i + q] += e[q];
+    }
+}
+template <int VEC>
+__device__ __forceinline__ void put_floats(float* p, const float (&x)[VEC]) {
+    constexpr int W = VEC < 4 ? VEC : 4;
+#pragma unroll
+    for (int i = 0; i < VEC; i += W) {
+        typename FloatVec<W>::type v;
+        float* e = reinterpret_cast<float*>(&v);
+#pragma unroll
+        for (int q = 0; q < W; ++q) e[q] = x[i + q];
+        *reinterpret_cast<typename FloatVec<W>::type*>(p + i) = v;
+    }
+}

@@ -11,8 +11,9 @@
 // eight lanes with 16-byte loads, eight rows per instruction (rows of 47 elements, unaligned, took a 2-byte load per lane and
 // one row per instruction).
 #include <algorithm>
+#include <type_traits>
 
-#include "elem.h"
+#include "gather_device.h"
 #include "mask_device.h"
 
 namespace {
@@ -30,46 +31,60 @@ __device__ __forceinline__ void add_row(float (&acc)[8], float w, const uint4& v
     for (int i = 0; i < 4; ++i) acc[2 * i] += w * __uint_as_float(u[i] << 16), acc[2 * i + 1] += w * __uint_as_float(u[i] & 0xFFFF0000u);
 }
 
-// Sum of the rows of a range of entries; lane t of a group of eight holds columns 8 t .. 8 t + 7, the groups take different
-// entries, and at the end every group holds the total. record(e): {row of src, weight bits} of entry e.
+// Sum of the rows of a range of entries, column `lane` of it in every lane. Lane t of a group of eight takes columns 8 t ..
+// 8 t + 7, the groups take different entries; at the end the groups exchange halves of what they hold until one column is left
+// per lane (7 exchanges and additions instead of 24 in a butterfly of whole rows). record(e): {row of src, weight bits}.
+__device__ __forceinline__ float add_halves32(float a, float b) {      // lanes below 32: a of both halves; above: b of both
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float add_halves16(float a, float b) {      // the same for the two 16-lane rows of each half
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
 template <class F>
-__device__ __forceinline__ void narrow_sum(const uint16_t* src, int32_t e0, int32_t e1, int lane, F&& record, float (&acc)[8]) {
-    constexpr int U = 4;
+__device__ __forceinline__ float narrow_sum(const uint16_t* src, int32_t e0, int32_t e1, int lane, F&& record) {
     const int t = lane & 7, g = lane >> 3;
+    float acc[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) acc[i] = 0.f;
     for (int32_t base = e0; base < e1; base += 64) {
         uint2 mine = make_uint2(0u, 0u);
         if (base + lane < e1) mine = record(base + lane);
         const int cnt = min(64, e1 - base);
-        for (int i0 = 0; i0 < cnt; i0 += 8 * U) {
-            uint4 v[U];
-            float w[U];
+        auto batch = [&](int i0, auto count) {
+            constexpr int N = decltype(count)::value;
+            uint4 v[N];
+            uint32_t w[N];
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
+            for (int u = 0; u < N; ++u) {
                 const int i = i0 + 8 * u + g;
-                const uint32_t r = __shfl(mine.x, i & 63);
-                w[u] = __uint_as_float(__shfl(mine.y, i & 63));
-                v[u] = make_uint4(0u, 0u, 0u, 0u);
-                if (i < cnt) v[u] = *reinterpret_cast<const uint4*>(src + int64_t(r) * P + 8 * t);
-                if (i >= cnt) w[u] = 0.f;
+                const uint32_t r = lane_value(mine.x, 4 * i);
+                w[u] = lane_value(mine.y, 4 * i);
+                v[u] = *reinterpret_cast<const uint4*>(src + int64_t(i < cnt ? r : 0u) * P + 8 * t);
             }
 #pragma unroll
-            for (int u = 0; u < U; ++u) add_row(acc, w[u], v[u]);
-        }
+            for (int u = 0; u < N; ++u)
+                if (i0 + 8 * u + g < cnt) add_row(acc, __uint_as_float(w[u]), v[u]);
+        };
+        int i0 = 0;
+        for (; i0 + 16 < cnt; i0 += 32) batch(i0, std::integral_constant<int, 4>{});
+        if (i0 + 8 < cnt)
+            batch(i0, std::integral_constant<int, 2>{});
+        else if (i0 < cnt)
+            batch(i0, std::integral_constant<int, 1>{});
     }
-    for (int off = 8; off < 64; off <<= 1)
+    // columns 8 t + 4 (lane / 32) + 2 (lane / 16 % 2) + (lane / 8 % 2) of the sums
+    float h[4], q[2];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) acc[i] += __shfl_xor(acc[i], off);
-}
-
-// Lane (g, t) stores element 8 t + g of a row: 64 consecutive elements per instruction.
-__device__ __forceinline__ float my_element(const float (&acc)[8], int g) {
-    float x = acc[0];
+    for (int i = 0; i < 4; ++i) h[i] = add_halves32(acc[i], acc[i + 4]);
 #pragma unroll
-    for (int i = 1; i < 8; ++i) x = g == i ? acc[i] : x;
-    return x;
+    for (int i = 0; i < 2; ++i) q[i] = add_halves16(h[i], h[i + 2]);
+    const bool odd = lane & 8;
+    const float keep = odd ? q[1] : q[0], give = odd ? q[0] : q[1];
+    return keep + __shfl_xor(give, 8);
 }
+__device__ __forceinline__ int my_column(int lane) { return 8 * (lane & 7) + 4 * (lane >> 5) + 2 * ((lane >> 4) & 1) + ((lane >> 3) & 1); }
 
 // X_out rows from the forward work list; pieces of split rows go to `partial` (P floats each).
 __global__ __launch_bounds__(kBlock) void narrow_forward_kernel(const SpmmItem* items, int32_t n_items, const VarcoEdge* edge, const float* vals,
@@ -78,13 +93,11 @@ __global__ __launch_bounds__(kBlock) void narrow_forward_kernel(const SpmmItem* 
     const int32_t idx = blockIdx.x * kWaves + __builtin_amdgcn_readfirstlane(int32_t(threadIdx.x >> 6));
     if (idx >= n_items) return;
     const SpmmItem it = items[idx];
-    float acc[8];
-    narrow_sum(y, it.e0, it.e1, lane, [&](int32_t e) {
+    const float x = narrow_sum(y, it.e0, it.e1, lane, [&](int32_t e) {
         const VarcoEdge ed = edge[e];
         return make_uint2(uint32_t(ed.gid < 0 ? ed.src : rows + ed.src), __float_as_uint(vals[e]));
-    }, acc);
-    const int g = lane >> 3, c = 8 * (lane & 7) + g;
-    const float x = my_element(acc, g);
+    });
+    const int c = my_column(lane);
     if (it.dst >= 0)
         partial[int64_t(it.dst) * P + c] = x;
     else if (c < fo)
@@ -101,36 +114,36 @@ __global__ __launch_bounds__(kBlock) void narrow_fixup_kernel(const SpmmSplit* s
     if (c < fo) Elem<bf16_t>::store(out + int64_t(sp.row) * fo + c, x);
 }
 
-// G_loc[row] and G_z[zrow of row] (zeros beyond fo); PIECES: partial sums of long ranges.
-template <bool PIECES>
-__global__ __launch_bounds__(kBlock) void narrow_backward_kernel(const NodeItem* nodes, const SpmmItem* pieces, int32_t n, const uint2* t_local,
-                                                                 const uint2* t_cross, const uint16_t* dz, const int32_t* zrow_of, bf16_t* g_loc,
-                                                                 bf16_t* g_z, int32_t fo, float* partial) {
-    const int lane = threadIdx.x & 63, g = lane >> 3, c = 8 * (lane & 7) + g;
-    const int32_t idx = blockIdx.x * kWaves + __builtin_amdgcn_readfirstlane(int32_t(threadIdx.x >> 6));
-    if (idx >= n) return;
-    float acc[8];
-    if constexpr (PIECES) {
-        const SpmmItem it = pieces[idx];
-        const uint2* pairs = it.row == 0 ? t_local : t_cross;
-        narrow_sum(dz, it.e0, it.e1, lane, [&](int32_t e) { return pairs[e]; }, acc);
-        partial[int64_t(it.dst) * P + c] = my_element(acc, g);
-    } else {
-        const NodeItem it = nodes[idx];
-        auto range = [&](const uint2* pairs, int32_t e0, int32_t e1, bool split) {
-            float x = 0.f;
-            if (split) {
-                for (int32_t s = e0; s < e1; ++s) x += partial[int64_t(s) * P + c];
-            } else {
-                narrow_sum(dz, e0, e1, lane, [&](int32_t e) { return pairs[e]; }, acc);
-                x = my_element(acc, g);
-            }
-            return c < fo ? x : 0.f;
-        };
-        Elem<bf16_t>::store(g_loc + int64_t(it.row) * P + c, range(t_local, it.l0, it.l1, it.flags & VARCO_NODE_LOCAL_SPLIT));
-        const int32_t zr = zrow_of[it.row];
-        if (g_z && zr >= 0) Elem<bf16_t>::store(g_z + int64_t(zr) * P + c, range(t_cross, it.c0, it.c1, it.flags & VARCO_NODE_CROSS_SPLIT));
+// G_loc[row] and G_z[zrow of row] (zeros beyond fo). SPLIT = false: partial sums of the pieces of long ranges (the launch's
+// first wavefronts) and the nodes without pieces; SPLIT = true: the others, from the partial sums.
+template <bool SPLIT>
+__global__ __launch_bounds__(kBlock) void narrow_backward_kernel(const NodeItem* nodes, int32_t n, const SpmmItem* pieces, int32_t n_pieces,
+                                                                 const uint2* t_local, const uint2* t_cross, const uint16_t* dz,
+                                                                 const int32_t* zrow_of, bf16_t* g_loc, bf16_t* g_z, int32_t fo, float* partial) {
+    const int lane = threadIdx.x & 63, c = my_column(lane);
+    int32_t idx = blockIdx.x * kWaves + __builtin_amdgcn_readfirstlane(int32_t(threadIdx.x >> 6));
+    if constexpr (!SPLIT) {
+        if (idx < n_pieces) {
+            const SpmmItem it = pieces[idx];
+            const uint2* pairs = it.row == 0 ? t_local : t_cross;
+            partial[int64_t(it.dst) * P + c] = narrow_sum(dz, it.e0, it.e1, lane, [&](int32_t e) { return pairs[e]; });
+            return;
+        }
+        idx -= n_pieces;
     }
+    if (idx >= n) return;
+    const NodeItem it = nodes[idx];
+    auto range = [&](const uint2* pairs, int32_t e0, int32_t e1, bool split) {
+        float x = 0.f;
+        if (SPLIT && split)
+            for (int32_t s = e0; s < e1; ++s) x += partial[int64_t(s) * P + c];
+        else
+            x = narrow_sum(dz, e0, e1, lane, [&](int32_t e) { return pairs[e]; });
+        return c < fo ? x : 0.f;
+    };
+    const int32_t zr = zrow_of[it.row];
+    Elem<bf16_t>::store(g_loc + int64_t(it.row) * P + c, range(t_local, it.l0, it.l1, it.flags & VARCO_NODE_LOCAL_SPLIT));
+    if (g_z && zr >= 0) Elem<bf16_t>::store(g_z + int64_t(zr) * P + c, range(t_cross, it.c0, it.c1, it.flags & VARCO_NODE_CROSS_SPLIT));
 }
 
 // Rows of fo elements -> rows of P elements, zeros beyond fo.
@@ -262,11 +275,12 @@ hipError_t varco_launch_narrow_backward(const NodePlan& plan, const uint2* t_loc
     hipLaunchKernelGGL(pad_rows_kernel, dim3(unsigned(std::min<int64_t>((rows + kWaves - 1) / kWaves, 256 * 32))), dim3(kBlock), 0, stream,
                        static_cast<const uint16_t*>(dz), rows, fo, static_cast<uint16_t*>(dz_padded));
     const uint16_t* src = static_cast<const uint16_t*>(dz_padded);
-    if (plan.n_pieces > 0)
-        hipLaunchKernelGGL(narrow_backward_kernel<true>, waves_for(plan.n_pieces), dim3(kBlock), 0, stream, plan.nodes, plan.pieces, plan.n_pieces,
-                           t_local, t_cross, src, zrow_of, static_cast<bf16_t*>(g_loc), static_cast<bf16_t*>(g_z), fo, partial);
-    hipLaunchKernelGGL(narrow_backward_kernel<false>, waves_for(plan.n_nodes), dim3(kBlock), 0, stream, plan.nodes, plan.pieces, plan.n_nodes, t_local,
-                       t_cross, src, zrow_of, static_cast<bf16_t*>(g_loc), static_cast<bf16_t*>(g_z), fo, partial);
+    hipLaunchKernelGGL(narrow_backward_kernel<false>, waves_for(int64_t(plan.n_pieces) + plan.n_whole), dim3(kBlock), 0, stream, plan.nodes, plan.n_whole,
+                       plan.pieces, plan.n_pieces, t_local, t_cross, src, zrow_of, static_cast<bf16_t*>(g_loc), static_cast<bf16_t*>(g_z), fo, partial);
+    if (plan.n_nodes > plan.n_whole)
+        hipLaunchKernelGGL(narrow_backward_kernel<true>, waves_for(plan.n_nodes - plan.n_whole), dim3(kBlock), 0, stream, plan.nodes + plan.n_whole,
+                           plan.n_nodes - plan.n_whole, plan.pieces, 0, t_local, t_cross, src, zrow_of, static_cast<bf16_t*>(g_loc),
+                           static_cast<bf16_t*>(g_z), fo, partial);
     tag.end(stream);
     return hipGetLastError();
 }

@@ -18,7 +18,7 @@
 #include <algorithm>
 #include <type_traits>
 
-#include "elem.h"
+#include "gather_device.h"
 #include "mask_device.h"
 
 namespace {
@@ -27,46 +27,11 @@ constexpr int kBlock = 256;
 constexpr int kWaves = kBlock / 64;
 constexpr int kXcdRun = 32;      // consecutive workgroups that one XCD takes, as in the aggregation kernels
 
-__device__ __forceinline__ void fma_vec(float4& a, float w, const float4& v) { a.x += w * v.x, a.y += w * v.y, a.z += w * v.z, a.w += w * v.w; }
-__device__ __forceinline__ void fma_vec(float& a, float w, const float& v) { a += w * v; }
-__device__ __forceinline__ void add_vec(float4& a, const float4& b) { a.x += b.x, a.y += b.y, a.z += b.z, a.w += b.w; }
-__device__ __forceinline__ void add_vec(float& a, const float& b) { a += b; }
-__device__ __forceinline__ float4 shfl_xor_vec(const float4& v, int m) {
-    return make_float4(__shfl_xor(v.x, m), __shfl_xor(v.y, m), __shfl_xor(v.z, m), __shfl_xor(v.w, m));
-}
-__device__ __forceinline__ float shfl_xor_vec(const float& v, int m) { return __shfl_xor(v, m); }
-__device__ __forceinline__ void zero_vec(float4& v) { v = make_float4(0.f, 0.f, 0.f, 0.f); }
-__device__ __forceinline__ void zero_vec(float& v) { v = 0.f; }
-
-// N consecutive stored elements of a product row, packed as they come from memory.
-template <typename T, int N>
-struct Packed;
-template <>
-struct Packed<float, 4> { using type = float4; static __device__ __forceinline__ void get(const float4& v, float (&x)[4]) { x[0] = v.x, x[1] = v.y, x[2] = v.z, x[3] = v.w; } };
-template <>
-struct Packed<float, 2> { using type = float2; static __device__ __forceinline__ void get(const float2& v, float (&x)[2]) { x[0] = v.x, x[1] = v.y; } };
-template <>
-struct Packed<float, 1> { using type = float; static __device__ __forceinline__ void get(const float& v, float (&x)[1]) { x[0] = v; } };
-__device__ __forceinline__ void unpack2(uint32_t u, float& lo, float& hi) { lo = __uint_as_float(u << 16), hi = __uint_as_float(u & 0xFFFF0000u); }
-template <>
-struct Packed<bf16_t, 8> {
-    using type = uint4;
-    static __device__ __forceinline__ void get(const uint4& v, float (&x)[8]) {
-        unpack2(v.x, x[0], x[1]), unpack2(v.y, x[2], x[3]), unpack2(v.z, x[4], x[5]), unpack2(v.w, x[6], x[7]);
-    }
-};
-template <>
-struct Packed<bf16_t, 4> { using type = uint2; static __device__ __forceinline__ void get(const uint2& v, float (&x)[4]) { unpack2(v.x, x[0], x[1]), unpack2(v.y, x[2], x[3]); } };
-template <>
-struct Packed<bf16_t, 2> { using type = uint32_t; static __device__ __forceinline__ void get(const uint32_t& v, float (&x)[2]) { unpack2(v, x[0], x[1]); } };
-template <>
-struct Packed<bf16_t, 1> { using type = uint16_t; static __device__ __forceinline__ void get(const uint16_t& v, float (&x)[1]) { x[0] = bf16_to_float(v); } };
-
 template <typename T>
 struct NodeArgs {
-    const NodeItem* nodes;
+    const NodeItem* nodes;      // of this launch
     int32_t n_nodes;
-    const SpmmItem* pieces;
+    const SpmmItem* pieces;     // taken by the launch's first wavefronts
     int32_t n_pieces;
     const uint2* t_local;
     const uint2* t_cross;
@@ -80,171 +45,183 @@ struct NodeArgs {
     int32_t ku, lpe_log2;     // loads per product row, lanes per product row = 1 << lpe_log2
 };
 
-// Groups of lanes gather the rows of entries [e0, e1), `U` row loads in flight per group.
+// acc += the rows of dM of entries [e0, e1).
 template <typename T, int VEC, int NV>
-__device__ __forceinline__ void gather_rows(const NodeArgs<T>& p, const uint2* pairs, int32_t e0, int32_t e1, int lane, int t, int g,
-                                            int ng, int lpr, typename FloatVec<VEC>::type (&acc)[NV]) {
-    using V = typename FloatVec<VEC>::type;
+__device__ __forceinline__ void gather_entries(const NodeArgs<T>& p, const uint2* pairs, int32_t e0, int32_t e1, int lane,
+                                               float (&acc)[loads_per_row(NV)][VEC]) {
     constexpr int U = NV >= 4 ? 1 : (NV == 2 ? 2 : 4);
     const int32_t width = int32_t(p.rule.width);
     for (int32_t base = e0; base < e1; base += 64) {
         uint2 mine = make_uint2(0u, 0u);
         if (base + lane < e1) mine = pairs[base + lane];
-        const int cnt = min(64, e1 - base);
-        for (int i0 = 0; i0 < cnt; i0 += ng * U) {
-            V v[U][NV];
-            float w[U];
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int i = i0 + u * ng + g;
-                const bool ok = i < cnt;
-                const int src_lane = ok ? i : 0;
-                const int32_t r = __shfl(int32_t(mine.x), src_lane);
-                const float wi = __uint_as_float(__shfl(mine.y, src_lane));
-                w[u] = ok ? wi : 0.f;
-                const T* src = p.dm + int64_t(r) * width;
-#pragma unroll
-                for (int m = 0; m < NV; ++m) {
-                    const int c = VEC * (t + lpr * m);
-                    zero_vec(v[u][m]);
-                    if (ok && c < width) v[u][m] = load_vec<T, VEC>(src + c);
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < U; ++u)
-#pragma unroll
-                for (int m = 0; m < NV; ++m) fma_vec(acc[m], w[u], v[u][m]);
-        }
+        const uint64_t addr = reinterpret_cast<uint64_t>(p.dm + int64_t(int32_t(mine.x)) * width);
+        gather_rows<T, VEC, NV, U>(addr, __uint_as_float(mine.y), min(64, e1 - base), width, lane, p.lpr_log2, acc);
     }
 }
 
 // The same over rows of fp32 partial sums (pieces of a long range), slot order.
 template <int VEC, int NV>
-__device__ __forceinline__ void add_partials(const float* partial, int32_t width, int32_t s0, int32_t s1, int t, int g, int ng, int lpr,
-                                             typename FloatVec<VEC>::type (&acc)[NV]) {
-    for (int32_t s = s0 + g; s < s1; s += ng)
+__device__ __forceinline__ void add_partials(const float* partial, int32_t width, int32_t s0, int32_t s1, int lane, int lpr_log2,
+                                             float (&acc)[loads_per_row(NV)][VEC]) {
+    if constexpr (NV > 0) {
+        for (int32_t s = s0; s < s1; ++s)
 #pragma unroll
-        for (int m = 0; m < NV; ++m) {
-            const int c = VEC * (t + lpr * m);
-            if (c < width) add_vec(acc[m], load_vec<float, VEC>(partial + int64_t(s) * width + c));
-        }
+            for (int m = 0; m < NV; ++m)
+                if (VEC * (lane + 64 * m) < width) add_floats<VEC>(partial + int64_t(s) * width + VEC * (lane + 64 * m), acc[m]);
+    } else {
+        const int c = VEC * (lane & ((1 << lpr_log2) - 1));
+        for (int32_t s = s0 + (lane >> lpr_log2); s < s1; s += 64 >> lpr_log2)
+            if (c < width) add_floats<VEC>(partial + int64_t(s) * width + c, acc[0]);
+    }
 }
 
-template <int VEC, int NV>
-__device__ __forceinline__ void reduce_groups(int lpr, typename FloatVec<VEC>::type (&acc)[NV]) {
-    for (int off = lpr; off < 64; off <<= 1)
+template <int VEC, int NR>
+__device__ __forceinline__ void clear(float (&acc)[NR][VEC]) {
 #pragma unroll
-        for (int m = 0; m < NV; ++m) add_vec(acc[m], shfl_xor_vec(acc[m], off));
+    for (int m = 0; m < NR; ++m)
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) acc[m][i] = 0.f;
 }
 
 // Sum of the rows [c0, c1) of `src` (pitch `pitch` elements of type S), elements j0 .. j0 + EV - 1 of every row; lane
-// groups take different rows, six rows of a group in flight; the groups' sums are added at the end, so that every lane
-// of position jl holds the total.
+// groups take different rows, six rows of a group in flight (fewer at the end of the range); the groups' sums are added at the
+// end, so that every lane of position jl holds the total.
 template <typename S, int EV>
 __device__ __forceinline__ void sum_rows(const S* src, int64_t pitch, int32_t c0, int32_t c1, int j0, bool on, int sub, int n_sub,
                                          int lpe_log2, float (&acc)[EV]) {
     using P = Packed<S, EV>;
-    constexpr int U = 6;
 #pragma unroll
     for (int i = 0; i < EV; ++i) acc[i] = 0.f;
-    const S* base = src + j0;
-    for (int32_t r = c0; r < c1; r += n_sub * U) {
-        typename P::type v[U];
+    const uint32_t mine = (uint32_t(sub) * uint32_t(pitch) + uint32_t(j0)) * uint32_t(sizeof(S));
+    auto batch = [&](int32_t r, auto count) {
+        constexpr int N = decltype(count)::value;
+        typename P::type v[N];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int32_t row = r + u * n_sub + sub;
+        for (int u = 0; u < N; ++u) {
+            const int32_t first = r + u * n_sub;      // uniform: the rows' base is a scalar
             v[u] = typename P::type{};
-            if (on && row < c1) v[u] = *reinterpret_cast<const typename P::type*>(base + int64_t(row) * pitch);
+            if (on && first + sub < c1) v[u] = load_packed<S, EV>(reinterpret_cast<uint64_t>(src + int64_t(first) * pitch), mine);
         }
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
+        for (int u = 0; u < N; ++u) {
             float x[EV];
             P::get(v[u], x);
 #pragma unroll
             for (int i = 0; i < EV; ++i) acc[i] += x[i];
         }
-    }
+    };
+    int32_t r = c0;
+    for (; r + 2 * n_sub < c1; r += 6 * n_sub) batch(r, std::integral_constant<int, 6>{});
+    if (r + n_sub < c1)
+        batch(r, std::integral_constant<int, 2>{});
+    else if (r < c1)
+        batch(r, std::integral_constant<int, 1>{});
     for (int off = 1 << lpe_log2; off < 64; off <<= 1)
 #pragma unroll
         for (int i = 0; i < EV; ++i) acc[i] += __shfl_xor(acc[i], off);
 }
 
-__device__ __forceinline__ int32_t item_of_wave() {
-    const int32_t xcd = int32_t(blockIdx.x & 7u), seq = int32_t(blockIdx.x >> 3);
-    const int32_t block = ((seq / kXcdRun) * 8 + xcd) * kXcdRun + seq % kXcdRun;
-    return block * kWaves + __builtin_amdgcn_readfirstlane(int32_t(threadIdx.x >> 6));
+// Partial sum of a piece of a long range (hub nodes): a dense row of width floats, or k floats of summed products.
+template <typename T, int VEC, int NV, int CROSS, int EV>
+__device__ __forceinline__ void node_piece(const NodeArgs<T>& p, const SpmmItem& it, int lane) {
+    const int32_t width = int32_t(p.rule.width);
+    float* dst = p.partial + int64_t(it.dst) * width;
+    if (it.row == 1 && CROSS == kCrossNone) return;
+    if (it.row == 1 && CROSS == kCrossProducts) {
+        const int sub = lane >> p.lpe_log2, n_sub = 64 >> p.lpe_log2, jl = lane & ((1 << p.lpe_log2) - 1);
+        for (int u0 = 0; u0 < p.ku; u0 += 64) {
+            const int ju = u0 + jl;
+            const bool on = ju < p.ku;
+            float s[EV];
+            sum_rows<T, EV>(p.prod, p.rule.k, it.e0, it.e1, ju * EV, on, sub, n_sub, p.lpe_log2, s);
+            if (on && sub == 0)
+#pragma unroll
+                for (int i = 0; i < EV; ++i) dst[ju * EV + i] = s[i];
+        }
+        return;
+    }
+    float acc[loads_per_row(NV)][VEC];
+    clear(acc);
+    gather_entries<T, VEC, NV>(p, it.row == 0 ? p.t_local : p.t_cross, it.e0, it.e1, lane, acc);
+    sum_groups<VEC, NV>(p.lpr_log2, acc);
+    if (NV == 0 && lane >= (1 << p.lpr_log2)) return;
+#pragma unroll
+    for (int m = 0; m < loads_per_row(NV); ++m) {
+        const int c = VEC * (lane + 64 * m);
+        if (c < width) put_floats<VEC>(dst + c, acc[m]);
+    }
 }
 
-template <typename T, int VEC, int NV, int CROSS, int EV>
+// One wavefront per item. SPLIT = false: the pieces of the long ranges, then the nodes without one (the pieces are the longest
+// items and go first; a launch of their own left most of the device idle: 4,096 pieces took 58 us beside 258 us for 169,343
+// nodes of 512 bf16 elements). SPLIT = true: the nodes whose ranges were cut, from the partial sums.
+template <typename T, int VEC, int NV, int CROSS, int EV, bool SPLIT>
 __global__ __launch_bounds__(kBlock) void node_sum_kernel(NodeArgs<T> p) {
-    using V = typename FloatVec<VEC>::type;
-    extern __shared__ float lds[];
+    constexpr int NR = loads_per_row(NV);
+    extern __shared__ __attribute__((aligned(16))) float lds[];
     const int lane = threadIdx.x & 63;
-    const int32_t idx = item_of_wave();
-    if (idx >= p.n_nodes) return;            // no barrier below: wavefronts are independent
+    const int32_t xcd = int32_t(blockIdx.x & 7u), seq = int32_t(blockIdx.x >> 3);
+    const int32_t block = ((seq / kXcdRun) * 8 + xcd) * kXcdRun + seq % kXcdRun;
+    int32_t idx = block * kWaves + __builtin_amdgcn_readfirstlane(int32_t(threadIdx.x >> 6));
+    if constexpr (!SPLIT) {                  // no barrier below: wavefronts are independent
+        if (idx < p.n_pieces) {
+            node_piece<T, VEC, NV, CROSS, EV>(p, p.pieces[idx], lane);
+            return;
+        }
+        idx -= p.n_pieces;
+    }
+    if (idx >= p.n_nodes) return;
     const NodeItem it = p.nodes[idx];
     const int32_t width = int32_t(p.rule.width);
-    const int lpr = 1 << p.lpr_log2, t = lane & (lpr - 1), g = lane >> p.lpr_log2, ng = 64 >> p.lpr_log2;
+    const bool local_split = SPLIT && (it.flags & VARCO_NODE_LOCAL_SPLIT), cross_split = SPLIT && (it.flags & VARCO_NODE_CROSS_SPLIT);
 
-    V acc[NV];
-#pragma unroll
-    for (int m = 0; m < NV; ++m) zero_vec(acc[m]);
-    if (it.flags & VARCO_NODE_LOCAL_SPLIT)
-        add_partials<VEC, NV>(p.partial, width, it.l0, it.l1, t, g, ng, lpr, acc);
+    float acc[NR][VEC];
+    clear(acc);
+    if (local_split)
+        add_partials<VEC, NV>(p.partial, width, it.l0, it.l1, lane, p.lpr_log2, acc);
     else
-        gather_rows<T, VEC, NV>(p, p.t_local, it.l0, it.l1, lane, t, g, ng, lpr, acc);
+        gather_entries<T, VEC, NV>(p, p.t_local, it.l0, it.l1, lane, acc);
 
     const bool cross = CROSS != kCrossNone && it.c1 > it.c0;
-    float* lrow = lds + (threadIdx.x >> 6) * width;
+    float* lrow = lds + (threadIdx.x >> 6) * ((width + 3) & ~3);
     if constexpr (CROSS == kCrossFull) {
-        if (it.flags & VARCO_NODE_CROSS_SPLIT)
-            add_partials<VEC, NV>(p.partial, width, it.c0, it.c1, t, g, ng, lpr, acc);
+        if (cross_split)
+            add_partials<VEC, NV>(p.partial, width, it.c0, it.c1, lane, p.lpr_log2, acc);
         else
-            gather_rows<T, VEC, NV>(p, p.t_cross, it.c0, it.c1, lane, t, g, ng, lpr, acc);
+            gather_entries<T, VEC, NV>(p, p.t_cross, it.c0, it.c1, lane, acc);
     }
-    reduce_groups<VEC, NV>(lpr, acc);
+    sum_groups<VEC, NV>(p.lpr_log2, acc);
+    const int first = NV == 0 ? VEC * (lane & ((1 << p.lpr_log2) - 1)) : VEC * lane;     // first column of this lane
     if constexpr (CROSS == kCrossMasked) {
         if (cross) {
-            V far[NV];
-#pragma unroll
-            for (int m = 0; m < NV; ++m) zero_vec(far[m]);
-            if (it.flags & VARCO_NODE_CROSS_SPLIT)
-                add_partials<VEC, NV>(p.partial, width, it.c0, it.c1, t, g, ng, lpr, far);
+            float far[NR][VEC];
+            clear(far);
+            if (cross_split)
+                add_partials<VEC, NV>(p.partial, width, it.c0, it.c1, lane, p.lpr_log2, far);
             else
-                gather_rows<T, VEC, NV>(p, p.t_cross, it.c0, it.c1, lane, t, g, ng, lpr, far);
-            reduce_groups<VEC, NV>(lpr, far);
+                gather_entries<T, VEC, NV>(p, p.t_cross, it.c0, it.c1, lane, far);
+            sum_groups<VEC, NV>(p.lpr_log2, far);
             const MaskAffine ma = varco_affine(p.rule, it.gid);
 #pragma unroll
-            for (int m = 0; m < NV; ++m) {
-                const int c = VEC * (t + lpr * m);
-                if (c < width) {
-                    float x[VEC];
-                    if constexpr (VEC == 4)
-                        x[0] = far[m].x, x[1] = far[m].y, x[2] = far[m].z, x[3] = far[m].w;
-                    else
-                        x[0] = far[m];
+            for (int m = 0; m < NR; ++m) {
+                const int c = first + VEC * 64 * m;
 #pragma unroll
-                    for (int i = 0; i < VEC; ++i)
-                        if (varco_inverse_position(p.rule, ma, uint32_t(c + i)) >= p.rule.k) x[i] = 0.f;
-                    if constexpr (VEC == 4)
-                        add_vec(acc[m], make_float4(x[0], x[1], x[2], x[3]));
-                    else
-                        acc[m] += x[0];
-                }
+                for (int i = 0; i < VEC; ++i)
+                    if (c < width && varco_inverse_position(p.rule, ma, uint32_t(c + i)) < p.rule.k) acc[m][i] += far[m][i];
             }
         }
     }
     if constexpr (CROSS == kCrossProducts) {
         if (cross) {
-            for (int c = lane; c < width; c += 64) lrow[c] = 0.f;
+            for (int c = 4 * lane; c < width; c += 256) *reinterpret_cast<float4*>(lrow + c) = make_float4(0.f, 0.f, 0.f, 0.f);
             const MaskAffine ma = varco_affine(p.rule, it.gid);
             const int sub = lane >> p.lpe_log2, n_sub = 64 >> p.lpe_log2, jl = lane & ((1 << p.lpe_log2) - 1);
-            const bool split = (it.flags & VARCO_NODE_CROSS_SPLIT) != 0;
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             for (int u0 = 0; u0 < p.ku; u0 += 64) {
                 const int ju = u0 + jl;
                 const bool on = ju < p.ku;
                 float s[EV];
-                if (split) {          // fp32 partial rows, EV elements at a time as well (rows are width floats apart)
+                if (cross_split) {          // fp32 partial rows, EV elements at a time as well (rows are width floats apart)
 #pragma unroll
                     for (int i = 0; i < EV; ++i) s[i] = 0.f;
                     for (int32_t r = it.c0 + sub; r < it.c1; r += n_sub)
@@ -263,62 +240,28 @@ __global__ __launch_bounds__(kBlock) void node_sum_kernel(NodeArgs<T> p) {
                     for (int i = 0; i < EV; ++i) {
                         lrow[q] = s[i];
                         q += ma.a;
-                        if (q >= p.rule.width) q -= p.rule.width;
+                        q = min(q, q - p.rule.width);
                     }
                 }
             }
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         }
     }
-    if (g != 0) return;
+    if (NV == 0 && lane >= (1 << p.lpr_log2)) return;
     T* dst = p.out + int64_t(it.row) * width;
 #pragma unroll
-    for (int m = 0; m < NV; ++m) {
-        const int c = VEC * (t + lpr * m);
+    for (int m = 0; m < NR; ++m) {
+        const int c = first + VEC * 64 * m;
         if (c < width) {
-            V v = acc[m];
-            if (CROSS == kCrossProducts && cross) add_vec(v, *reinterpret_cast<const V*>(lrow + c));
-            if (p.add_old) add_vec(v, load_vec<T, VEC>(dst + c));
-            store_vec<T, VEC>(dst + c, v);
+            if (CROSS == kCrossProducts && cross) add_floats<VEC>(lrow + c, acc[m]);
+            if (p.add_old) {
+                float old[VEC];
+                Packed<T, VEC>::get(Packed<T, VEC>::load(dst + c), old);
+#pragma unroll
+                for (int i = 0; i < VEC; ++i) acc[m][i] += old[i];
+            }
+            Packed<T, VEC>::put(dst + c, acc[m]);
         }
-    }
-}
-
-// Partial sums of the pieces of long ranges (hub nodes): a dense row of width floats, or k floats of summed products.
-template <typename T, int VEC, int NV, int CROSS, int EV>
-__global__ __launch_bounds__(kBlock) void node_piece_kernel(NodeArgs<T> p) {
-    using V = typename FloatVec<VEC>::type;
-    const int lane = threadIdx.x & 63;
-    const int32_t idx = item_of_wave();
-    if (idx >= p.n_pieces) return;
-    const SpmmItem it = p.pieces[idx];
-    const int32_t width = int32_t(p.rule.width);
-    float* dst = p.partial + int64_t(it.dst) * width;
-    if (it.row == 1 && CROSS == kCrossNone) return;
-    if (it.row == 1 && CROSS == kCrossProducts) {
-        const int sub = lane >> p.lpe_log2, n_sub = 64 >> p.lpe_log2, jl = lane & ((1 << p.lpe_log2) - 1);
-        for (int u0 = 0; u0 < p.ku; u0 += 64) {
-            const int ju = u0 + jl;
-            const bool on = ju < p.ku;
-            float s[EV];
-            sum_rows<T, EV>(p.prod, p.rule.k, it.e0, it.e1, ju * EV, on, sub, n_sub, p.lpe_log2, s);
-            if (on && sub == 0)
-#pragma unroll
-                for (int i = 0; i < EV; ++i) dst[ju * EV + i] = s[i];
-        }
-        return;
-    }
-    const int lpr = 1 << p.lpr_log2, t = lane & (lpr - 1), g = lane >> p.lpr_log2, ng = 64 >> p.lpr_log2;
-    V acc[NV];
-#pragma unroll
-    for (int m = 0; m < NV; ++m) zero_vec(acc[m]);
-    gather_rows<T, VEC, NV>(p, it.row == 0 ? p.t_local : p.t_cross, it.e0, it.e1, lane, t, g, ng, lpr, acc);
-    reduce_groups<VEC, NV>(lpr, acc);
-    if (g != 0) return;
-#pragma unroll
-    for (int m = 0; m < NV; ++m) {
-        const int c = VEC * (t + lpr * m);
-        if (c < width) *reinterpret_cast<V*>(dst + c) = acc[m];
     }
 }
 
@@ -331,7 +274,6 @@ hipError_t node_sum_t(const NodePlan& plan, const uint2* t_local, const uint2* t
                       const MaskRule& rule, VarcoCross cross, void* out, bool add_old, float* partial, hipStream_t stream,
                       const LaunchTag& tag) {
     NodeArgs<T> a;
-    a.nodes = plan.nodes, a.n_nodes = plan.n_nodes;
     a.pieces = plan.pieces, a.n_pieces = plan.n_pieces;
     a.t_local = t_local, a.t_cross = t_cross;
     a.dm = static_cast<const T*>(dm), a.prod = static_cast<const T*>(prod);
@@ -340,12 +282,15 @@ hipError_t node_sum_t(const NodePlan& plan, const uint2* t_local, const uint2* t
     a.add_old = add_old ? 1 : 0;
     a.partial = partial;
     const int32_t width = int32_t(rule.width);
-    const bool vec4 = width % 4 == 0 && aligned_to(dm, 4 * sizeof(T)) && aligned_to(out, 4 * sizeof(T)) && aligned_to(partial, 16);
-    const int per_row = vec4 ? width / 4 : width;
+    auto vec_ok = [&](int v) {
+        return width % v == 0 && aligned_to(dm, v * sizeof(T)) && aligned_to(out, v * sizeof(T)) && aligned_to(partial, 16);
+    };
+    const int vec = sizeof(T) == 2 && vec_ok(8) ? 8 : vec_ok(4) ? 4 : 1;
+    const int per_row = width / vec;
     a.lpr_log2 = 0;
     while ((1 << a.lpr_log2) < per_row && a.lpr_log2 < 6) ++a.lpr_log2;
-    int nv = 1;
-    while (nv * (1 << a.lpr_log2) < per_row) nv <<= 1;
+    int nv = a.lpr_log2 < 6 ? 0 : 1;
+    while (nv && nv * 64 < per_row) nv <<= 1;
     if (nv > 8) return hipErrorInvalidValue;
     int ev = 1;
     if (cross == kCrossProducts)
@@ -362,17 +307,19 @@ hipError_t node_sum_t(const NodePlan& plan, const uint2* t_local, const uint2* t
         const int32_t per_round = 8 * kXcdRun;
         return dim3(unsigned(((n + kWaves - 1) / kWaves + per_round - 1) / per_round * per_round));
     };
-    const size_t lds_bytes = cross == kCrossProducts ? size_t(kWaves) * width * sizeof(float) : 0;
+    const size_t lds_bytes = cross == kCrossProducts ? size_t(kWaves) * ((width + 3) / 4 * 4) * sizeof(float) : 0;
     auto launch = [&](auto vec, auto nvc, auto cr, auto evc) {
         constexpr int VEC = decltype(vec)::value, NV = decltype(nvc)::value, CR = decltype(cr)::value, EV = decltype(evc)::value;
-        if (plan.n_pieces > 0) {
+        a.nodes = plan.nodes, a.n_nodes = plan.n_whole;
+        tag.begin(stream);
+        hipLaunchKernelGGL((node_sum_kernel<T, VEC, NV, CR, EV, false>), grid_for(plan.n_pieces + plan.n_whole), dim3(kBlock), lds_bytes, stream, a);
+        tag.end(stream);
+        if (plan.n_nodes > plan.n_whole) {
+            a.nodes = plan.nodes + plan.n_whole, a.n_nodes = plan.n_nodes - plan.n_whole;
             tag.begin_as(VARCO_K_REDUCE, stream, 0.0);
-            hipLaunchKernelGGL((node_piece_kernel<T, VEC, NV, CR, EV>), grid_for(plan.n_pieces), dim3(kBlock), 0, stream, a);
+            hipLaunchKernelGGL((node_sum_kernel<T, VEC, NV, CR, EV, true>), grid_for(a.n_nodes), dim3(kBlock), lds_bytes, stream, a);
             tag.end(stream);
         }
-        tag.begin(stream);
-        hipLaunchKernelGGL((node_sum_kernel<T, VEC, NV, CR, EV>), grid_for(plan.n_nodes), dim3(kBlock), lds_bytes, stream, a);
-        tag.end(stream);
     };
     auto with_cross = [&](auto vec, auto nvc) {
         switch (cross) {
@@ -394,14 +341,22 @@ hipError_t node_sum_t(const NodePlan& plan, const uint2* t_local, const uint2* t
         }
     };
     auto with_nv = [&](auto vec) {
+        constexpr int VEC = decltype(vec)::value;
         switch (nv) {
+            case 0: with_cross(vec, Int<0>{}); break;
             case 1: with_cross(vec, Int<1>{}); break;
             case 2: with_cross(vec, Int<2>{}); break;
             case 4: with_cross(vec, Int<4>{}); break;
-            default: with_cross(vec, Int<8>{}); break;
+            default:
+                if constexpr (VEC < 8) with_cross(vec, Int<8>{});
         }
     };
-    if (vec4)
+    if constexpr (sizeof(T) == 2)
+        if (vec == 8) {
+            with_nv(Int<8>{});
+            return hipGetLastError();
+        }
+    if (vec == 4)
         with_nv(Int<4>{});
     else
         with_nv(Int<1>{});

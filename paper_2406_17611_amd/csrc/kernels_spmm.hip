@@ -22,6 +22,7 @@
 #include <type_traits>
 
 #include "elem.h"
+#include "gather_device.h"
 #include "mask_device.h"
 
 namespace {
@@ -37,6 +38,7 @@ constexpr int agg_block(int mode) { return mode == 0 /* dense rows only */ ? kBl
 // compressed rows see sparse_phase): their register budget is the 64 of eight wavefronts per SIMD, or the 72 of
 // seven; resident wavefronts, each a chain of dependent round trips, are what their rate is made of.
 constexpr int kXcdRun = 32;       // consecutive workgroups of the work list that one XCD takes (see spmm_kernel)
+constexpr int kHaloWaves = 7;
 constexpr int kUnroll = 3;
 constexpr int kUnrollDense = 4;   // dense-only kernels have registers to spare
 
@@ -86,11 +88,9 @@ struct SpmmArgs {
     int32_t row_base;
     float* partial;           // partial sums of split rows stay in fp32
     int32_t lpr_log2;         // lanes per dense row = 1 << lpr_log2
-    int32_t ev;               // stored elements of a compressed row per lane and load: 4, 2 or 1
     int32_t ku;               // loads per compressed row = k / ev
     int32_t lpe_log2;         // lanes that share one compressed row = 1 << lpe_log2 (>= min(ku, 64))
     int32_t epi;              // compressed rows handled per instruction = private LDS rows per wavefront
-    int32_t swizzle;          // private rows hold position q at q ^ ((q >> 5) & 3) (see sparse_phase)
 };
 
 // N consecutive stored elements as they come from memory (bf16 stays packed until it is used).
@@ -120,24 +120,38 @@ struct Stored<bf16_t, 1> {
     static __device__ __forceinline__ float get(const uint16_t& v, int) { return bf16_to_float(v); }
 };
 
-// Scatter-accumulate the compressed rows of the wavefront's current batch: lanes [nd, nd + ns) hold one
-// halo entry each (row in z, weight, packed (a, b)). A group of `lpe` lanes takes one entry (lane = group
-// of EV stored elements), `epi` entries are handled per instruction, and each of those lane groups adds
-// into a private LDS row of its own: the positions of one entry are distinct, so plain read-add-write is
-// race-free and no LDS atomics (which run at a small fraction of the plain LDS rate) are needed.
-// Z32: every element of the compressed buffer lies below 2^32 bytes, so a row's address is the (uniform) base
-// plus a 32-bit offset: one address register per gather in flight instead of two, which is what decides how
-// many wavefronts fit a SIMD here. `srow` then holds the row's element offset (row * k), not the row.
-// SWZ: the lanes of one entry step through its stored elements EV at a time, so at one instruction their positions
-// differ by multiples of EV * a: with 16 or more lanes per entry, lanes 8 (EV = 4) apart meet in one LDS bank at
-// different addresses, a 4-way conflict on every access of a 512-wide row. Their positions differ by odd multiples
-// of 32, so folding bits 5-6 of the position into bits 0-1 of the address (which the lanes of an instruction share)
-// separates them; the row is read back through the same map.
-// POW2: the width is a power of two, so positions wrap with a mask instead of a division by multiplication and
-// conditional subtractions (the kernel is bound by its vector instructions once the conflicts are gone).
-template <typename T, int EV, bool Z32, bool SWZ, bool POW2 = false>
-__device__ __forceinline__ void sparse_phase(const SpmmArgs<T>& p, int lane, int nd, int ns, int32_t srow, float w,
-                                             uint32_t mab, float* lpriv) {
+// The four elements in the order rot, rot + 1, .. (mod 4); rot differs between lanes.
+__device__ __forceinline__ uint2 rotated(const uint2& v, uint32_t rot) {
+    const uint32_t sel = 0x03020100u + rot * 0x02020202u;           // bytes 2 rot .. 2 rot + 3, each mod 8
+    return make_uint2(__builtin_amdgcn_perm(v.y, v.x, sel & 0x07070707u), __builtin_amdgcn_perm(v.y, v.x, (sel + 0x04040404u) & 0x07070707u));
+}
+__device__ __forceinline__ float4 rotated(const float4& v, uint32_t rot) {
+    const bool one = rot & 1u, two = rot & 2u;
+    const float4 s = make_float4(one ? v.y : v.x, one ? v.z : v.y, one ? v.w : v.z, one ? v.x : v.w);
+    return make_float4(two ? s.z : s.x, two ? s.w : s.y, two ? s.x : s.z, two ? s.y : s.w);
+}
+
+// Scatter-accumulate the compressed rows of the wavefront's current batch: lanes [nd, nd + ns) hold one halo entry each (its
+// row of z, weight, packed (a, b)). A group of `lpe` lanes takes one entry (lane = group of EV stored elements), `epi` entries
+// are handled per instruction, and each of those lane groups adds into a private LDS row of its own: the positions of one
+// entry are distinct, so plain read-add-write is race-free and no LDS atomics (which run at a small fraction of the plain LDS
+// rate) are needed.
+// The kernel issues vector instructions three quarters of the time, so their number is its time:
+// Z32: every element of the compressed buffer lies below 2^32 bytes: `zoff` is the row's byte offset, an address is the
+// (uniform) base plus 32 bits, one register per gather in flight; otherwise `zoff` is the row.
+// POW2: positions are byte offsets (a and b come multiplied by 4) that wrap with the mask that also sets the row's base;
+// otherwise they wrap with one unsigned minimum (q - width is huge when q < width).
+// EV = 4: the lanes of one entry step through its stored elements four at a time, so at one instruction their positions would
+// differ by multiples of 4 a: with 16 or more lanes per entry, lanes 8 apart would meet in one LDS bank at different
+// addresses. Lane j therefore takes its four elements in the order r, r + 1, .. (mod 4), r = j / 8: lanes 8 apart then are at
+// positions that differ by an odd number modulo 32. One byte permutation of the loaded words, against three instructions per
+// element for folding position bits into the address, and the rows are read back as they are.
+// (bf16, 512 wide, k = 128, a dozen entries per row: the forward aggregation took 314 us with the folded addresses, the
+// multiplier table staged per wavefront and per-lane dense addresses; %SPMM% now.)
+template <typename T, int EV, bool Z32, bool POW2>
+__device__ __forceinline__ void sparse_phase(const SpmmArgs<T>& p, int lane, int nd, int ns, uint32_t zoff, float w, uint32_t mab,
+                                             char* lrows) {
+    constexpr bool ROT = EV == 4;
     using S = typename Stored<T, EV>::type;
     // Gathers in flight per lane: six of at most 8 bytes (four bf16 or two fp32 elements), three of 16 bytes:
     // about the same registers either way. A wavefront waits for the slowest of its gathers, so fewer, larger
@@ -145,93 +159,108 @@ __device__ __forceinline__ void sparse_phase(const SpmmArgs<T>& p, int lane, int
     // aggregation 30.6 -> 24.8 ms per step; the fp32 kernel keeps 8: 13.8 -> 13.5 ms). Eight gathers, or four
     // of 16 bytes, cost more wavefronts than they gain (27.6 ms and 14.5 ms).
     constexpr int G = EV * sizeof(T) <= 8 ? 2 * kUnroll : kUnroll;
-    const int32_t k = int32_t(p.rule.k);
     const uint32_t width = p.rule.width;
     const int sub = lane >> p.lpe_log2;
     const int jl = lane & ((1 << p.lpe_log2) - 1);
     const bool lane_ok = sub < p.epi && jl < p.ku;
-    float* row = lpriv + sub * int32_t(width);
+    using lds_float = __attribute__((address_space(3))) float;
+    const uint32_t base = uint32_t(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) char*)lrows)) + uint32_t(sub) * width * 4u;
+    const uint32_t mask = (width - 1u) * 4u;
+    const uint32_t rot = ROT ? uint32_t(jl >> 3) & 3u : 0u;
     for (int j0 = 0; j0 < p.ku; j0 += 64) {          // more than one pass only when an entry needs > 64 lanes
         const int ju = j0 + jl;
         const bool j_ok = lane_ok && ju < p.ku;
-        const int j = ju * EV;
-        for (int r0 = 0; r0 < ns; r0 += p.epi * G) {
-            // Issue all gathers first; only the loaded values stay in registers across the wait. Everything
-            // else about an entry (weight, multiplier, offset, positions) is fetched from its lane and
-            // computed after the wait, so that more gathers fit the registers of a wavefront.
-            S v[G];
+        const uint32_t j = uint32_t(ju) * EV, j_bytes = j * uint32_t(sizeof(T));
+        // `count` entries per lane group from entry r0 on. All gathers are issued first, with the entries' weights and rules
+        // fetched from their lanes behind them; the positions are computed after the wait, so that more gathers fit the
+        // registers of a wavefront. Straight-line code: a branch per entry would wait for every fetch by itself.
+        auto batch = [&](int r0, auto count) {
+            constexpr int N = decltype(count)::value;
+            S v[N];
+            float wi[N];
+            uint32_t ab[N];
 #pragma unroll
-            for (int u = 0; u < G; ++u) {
+            for (int u = 0; u < N; ++u) {
                 const int es = r0 + u * p.epi + sub;
-                const bool act = j_ok && es < ns;
-                const int32_t r = __shfl(srow, act ? nd + es : 0);
+                const uint32_t r = lane_value(zoff, 4 * (nd + es));
                 // lanes without an entry re-read the start of the buffer (never used, but no branch around the load)
                 if constexpr (Z32)
-                    v[u] = *reinterpret_cast<const S*>(p.z + (act ? uint32_t(r) + uint32_t(j) : 0u));
+                    v[u] = *reinterpret_cast<const S*>(reinterpret_cast<const char*>(p.z) + (j_ok && es < ns ? r + j_bytes : 0u));
                 else
-                    v[u] = *reinterpret_cast<const S*>(p.z + (act ? int64_t(r) * k + j : int64_t(0)));
+                    v[u] = *reinterpret_cast<const S*>(p.z + (j_ok && es < ns ? int64_t(r) * p.rule.k + j : int64_t(0)));
+            }
+#pragma unroll
+            for (int u = 0; u < N; ++u) {
+                const int at = 4 * (nd + r0 + u * p.epi + sub);
+                wi[u] = __uint_as_float(lane_value(__float_as_uint(w), at));
+                ab[u] = lane_value(mab, at);
             }
             __builtin_amdgcn_sched_barrier(0);       // keep the work below behind the loads
 #pragma unroll
-            for (int u = 0; u < G; ++u) {
-                const int es = r0 + u * p.epi + sub;
-                const bool act = j_ok && es < ns;
-                const int src_lane = act ? nd + es : 0;
-                const float wi = __shfl(w, src_lane);
-                const uint32_t ab = __shfl(mab, src_lane);
-                const uint32_t a = ab & 0xFFFFu;
-                if (act) {
-                    uint32_t q[EV];
+            for (int u = 0; u < N; ++u)
+                if (j_ok && r0 + u * p.epi + sub < ns) {
+                    const uint32_t a = ab[u] & 0xFFFFu;
+                    uint32_t q = __umul24(a, j + rot) + (ab[u] >> 16);
+                    uint32_t at[EV];
                     float cur[EV];
                     if constexpr (POW2) {
-                        q[0] = (__umul24(a, uint32_t(j)) + (ab >> 16)) & (width - 1u);
+                        at[0] = (q & mask) | base;
+                        const uint32_t back = a * uint32_t(1 - EV);          // from element 3 to element 0
 #pragma unroll
-                        for (int i = 1; i < EV; ++i) q[i] = (q[i - 1] + a) & (width - 1u);
+                        for (int i = 1; i < EV; ++i) at[i] = ((at[i - 1] + (ROT && rot == uint32_t(EV - i) ? back : a)) & mask) | base;
                     } else {
-                        q[0] = varco_mod_width(__umul24(a, uint32_t(j)) + (ab >> 16), width, p.rule.width_magic);
+                        q = varco_mod_width(q, width, p.rule.width_magic);
+                        at[0] = q * 4u + base;
+                        uint32_t back = 0u;
+                        if constexpr (ROT) {
+                            back = 2u * a, back = min(back, back - width);
+                            back += a, back = min(back, back - width);
+                            back = width - back;                             // -3 a mod width (width itself for 0)
+                        }
 #pragma unroll
                         for (int i = 1; i < EV; ++i) {
-                            q[i] = q[i - 1] + a;
-                            if (q[i] >= width) q[i] -= width;
+                            q += ROT && rot == uint32_t(EV - i) ? back : a;
+                            q = min(q, q - width);
+                            at[i] = q * 4u + base;
                         }
                     }
-                    if constexpr (SWZ) {
+                    S x = v[u];
+                    if constexpr (ROT) x = rotated(x, rot);
 #pragma unroll
-                        for (int i = 0; i < EV; ++i) q[i] ^= (q[i] >> 5) & 3u;
-                    }
+                    for (int i = 0; i < EV; ++i) cur[i] = *(const lds_float*)(uintptr_t(at[i]));   // distinct positions of one entry
 #pragma unroll
-                    for (int i = 0; i < EV; ++i) cur[i] = row[q[i]];          // distinct positions of one entry
-#pragma unroll
-                    for (int i = 0; i < EV; ++i) row[q[i]] = cur[i] + wi * Stored<T, EV>::get(v[u], i);
+                    for (int i = 0; i < EV; ++i) *(lds_float*)(uintptr_t(at[i])) = cur[i] + wi[u] * Stored<T, EV>::get(x, i);
                 }
-            }
-        }
+        };
+        constexpr int kHalf = G / 2;
+        int r0 = 0;
+        for (; r0 + p.epi * kHalf < ns; r0 += p.epi * G) batch(r0, std::integral_constant<int, G>{});
+        if (r0 + p.epi < ns)
+            batch(r0, std::integral_constant<int, (kHalf > 1 ? kHalf : 2)>{});
+        else if (r0 < ns)
+            batch(r0, std::integral_constant<int, 1>{});
     }
 }
 
 // T: storage type of the dense rows, the compressed rows and the output (sums are kept in fp32);
-// VEC: elements per lane per load of a dense row (4 needs width % 4 == 0 and bases aligned to 4 elements);
-// NV: such loads per lane per row, so that width <= VEC * NV * lanes-per-row;
-// MODE: kDenseOnly: all rows are dense; kHalo / kHaloZ32: entries may refer to compressed halo rows (forward
-// aggregation), the latter with 32-bit offsets into the compressed buffer (see sparse_phase).
-constexpr int kDenseOnly = 0, kHalo = 1, kHaloZ32 = 2;
-template <typename T, int VEC, int NV, int MODE>
-__global__ __launch_bounds__(agg_block(MODE)) void spmm_kernel(SpmmArgs<T> p) {
-    using V = typename Vec<VEC>::type;
-    constexpr bool HALO = MODE != kDenseOnly, Z32 = MODE == kHaloZ32;
+// VEC: elements per lane per load of a dense row (16 bytes, or fewer when the width or the bases do not allow it);
+// NV: such loads per lane per row (0: fewer than 64 lanes cover a row, see gather_rows);
+// MODE: kDenseOnly: all rows are dense; forward aggregation: kFull: halo rows are complete; kSparse / kSparseZ32: compressed,
+// EV elements per lane and load, power-of-two width or not, the latter mode with 32-bit offsets (see sparse_phase). One
+// kernel per form: the constants of forms that do not run would take registers, i.e. resident wavefronts, from the one
+// that does.
+constexpr int kDenseOnly = 0, kFull = 1, kSparse = 2, kSparseZ32 = 3;
+template <typename T, int VEC, int NV, int MODE, int EV = 1, bool POW2 = false>
+__global__ __launch_bounds__(agg_block(MODE), MODE >= kSparse && VEC * NV <= 8 ? kHaloWaves : 1) void spmm_kernel(SpmmArgs<T> p) {
+    constexpr bool HALO = MODE != kDenseOnly, SPARSE = MODE >= kSparse, Z32 = MODE == kSparseZ32;
     constexpr int kAggBlock = agg_block(MODE), kAggWaves = kAggBlock / 64;
-    constexpr int U = NV >= 4 ? 1 : (NV == 2 ? 2 : (HALO ? kUnroll : kUnrollDense));
-    extern __shared__ float lds[];
+    constexpr int U = NV >= 4 ? 1 : (NV == 2 ? 2 : (HALO ? kUnroll : kUnrollDense)), NR = loads_per_row(NV);
+    extern __shared__ __attribute__((aligned(16))) float lds[];     // HALO: the workgroup's (one wavefront's) private rows of compressed-row sums
+    static_assert(!HALO || kAggWaves == 1, "the private rows start at the workgroup's LDS");
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     const int32_t width = int32_t(p.rule.width);
-    const bool full = p.rule.k == p.rule.width;
-    const bool sparse = HALO && !full;
-    float* lpriv = lds + wave * p.epi * width;   // this wavefront's private rows of compressed-row sums
-    uint16_t* lunits = reinterpret_cast<uint16_t*>(lds + kAggWaves * p.epi * width);
 
-    // The wavefront's item and the records of its first batch are requested before the table is staged and the
-    // workgroup meets at the barrier: three round trips in a row become little more than one.
     // Workgroups are dealt to the 8 XCDs round-robin; an XCD takes the work list in runs of kXcdRun consecutive
     // workgroups (the grid is a multiple of 8 runs), so that rows next to each other - which on a graph with any
     // locality share source rows - are aggregated through the same L2 at about the same time, while every XCD still
@@ -239,9 +268,8 @@ __global__ __launch_bounds__(agg_block(MODE)) void spmm_kernel(SpmmArgs<T> p) {
     const int32_t xcd = int32_t(blockIdx.x & 7u), seq = int32_t(blockIdx.x >> 3);
     const int32_t block = ((seq / kXcdRun) * 8 + xcd) * kXcdRun + seq % kXcdRun;
     const int32_t idx = block * kAggWaves + __builtin_amdgcn_readfirstlane(wave);   // uniform: the item sits in scalar registers
-    const bool has_item = idx < p.n_items;
-    SpmmItem it{};                      // empty range for a wavefront without an item
-    if (has_item) it = p.items[idx];
+    if (idx >= p.n_items) return;       // no barriers: wavefronts are independent
+    const SpmmItem it = p.items[idx];
     VarcoEdge ed{0, -1};                // the current batch's records: one entry per lane
     int32_t col = 0;
     float w = 0.f;
@@ -256,117 +284,56 @@ __global__ __launch_bounds__(agg_block(MODE)) void spmm_kernel(SpmmArgs<T> p) {
         }
     };
     load_records(it.e0);
-    if (sparse) {   // the multiplier table is looked up once per halo entry: keep it in LDS
-        for (uint32_t i = threadIdx.x; i < p.rule.n_units; i += kAggBlock) lunits[i] = p.rule.units[i];
-        for (int c = lane; c < p.epi * width; c += 64) lpriv[c] = 0.f;
-        __syncthreads();
-    }
-    if (!has_item) return;              // no block-wide barrier below: wavefronts are independent
+    if constexpr (SPARSE)
+        for (int c = 4 * lane; c < p.epi * width; c += 256) *reinterpret_cast<float4*>(lds + c) = make_float4(0.f, 0.f, 0.f, 0.f);
 
-    const int lpr = 1 << p.lpr_log2;
-    const int t = lane & (lpr - 1);     // position inside the group
-    const int g = lane >> p.lpr_log2;   // group index: which edge of a step this lane works on
-    const int ng = 64 >> p.lpr_log2;
-
-    V acc[NV];
+    float acc[NR][VEC];
 #pragma unroll
-    for (int m = 0; m < NV; ++m) zero_vec(acc[m]);
+    for (int m = 0; m < NR; ++m)
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) acc[m][i] = 0.f;
     bool any_sparse = false;
+    const uint32_t key0 = SPARSE ? varco_key0(p.rule) : 0u, key1 = SPARSE ? varco_key1(p.rule) : 0u;
 
     for (int32_t base = it.e0; base < it.e1; base += 64) {
         if (base != it.e0) load_records(base);
-        int32_t srow = 0;
-        bool is_halo = false;
-        uint32_t mab = 0;
-        if (HALO) {
-            srow = ed.src;
-            is_halo = ed.gid >= 0;
-            if (Z32 && sparse && is_halo) srow = int32_t(uint32_t(ed.src) * p.rule.k);   // one multiply per entry, not per gather
-            if (sparse && is_halo) {
-                const uint32_t h1 = varco_mix32(uint32_t(ed.gid) ^ varco_key0(p.rule));
-                const uint32_t h2 = varco_mix32(h1 ^ varco_key1(p.rule));
-                mab = uint32_t(lunits[__umulhi(h2, p.rule.n_units)]) | (__umulhi(h1, p.rule.width) << 16);
-            }
-        } else {
-            srow = col;
+        const bool is_halo = HALO && ed.gid >= 0;
+        uint32_t zoff = 0, shift = 0, unit = 0;
+        if (SPARSE && is_halo) {         // the multiplier table (at most 2 KB) comes from the cache, used behind the first rows
+            zoff = Z32 ? uint32_t(ed.src) * (p.rule.k * uint32_t(sizeof(T))) : uint32_t(ed.src);
+            const uint32_t h1 = varco_mix32(uint32_t(ed.gid) ^ key0);
+            unit = p.rule.units[__umulhi(varco_mix32(h1 ^ key1), p.rule.n_units)];
+            shift = __umulhi(h1, p.rule.width) << 16;
         }
-        const uint64_t hmask = HALO ? __ballot(is_halo) : 0ull;
+        const T* const from = MODE == kFull && is_halo ? p.z : p.dense;
+        const uint64_t addr = reinterpret_cast<uint64_t>(from + int64_t(HALO ? ed.src : col) * width);
+        const uint64_t hmask = SPARSE ? __ballot(is_halo) : 0ull;
         const int cnt = min(64, it.e1 - base);
-        const int ns = sparse ? __popcll(hmask) : 0;
+        const int ns = SPARSE ? __popcll(hmask) : 0;
         const int nd = cnt - ns;        // columns ascend within a row, so dense entries sit in lanes [0, nd)
-
-        // dense rows: group g takes entries g, g + ng, ...; U row loads are issued before they are used
-        for (int i0 = 0; i0 < nd; i0 += ng * U) {
-            V v[U][NV];
-            float wi[U];
-            bool ok[U];
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int i = i0 + u * ng + g;
-                ok[u] = i < nd;
-                const int src_lane = ok[u] ? i : 0;
-                const int32_t r = __shfl(srow, src_lane);
-                wi[u] = __shfl(w, src_lane);
-                const bool h = HALO && ((hmask >> src_lane) & 1);
-                const T* src = (h ? p.z : p.dense) + int64_t(r) * width;
-#pragma unroll
-                for (int m = 0; m < NV; ++m) {
-                    const int col = VEC * (t + lpr * m);
-                    zero_vec(v[u][m]);
-                    if (ok[u] && col < width) v[u][m] = load_vec<T, VEC>(src + col);
-                }
+        gather_rows<T, VEC, NV, U>(addr, w, nd, width, lane, p.lpr_log2, acc);
+        if constexpr (SPARSE) {
+            if (ns > 0) {
+                if (!any_sparse) __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");     // the rows are cleared
+                any_sparse = true;
+                sparse_phase<T, EV, Z32, POW2>(p, lane, nd, ns, zoff, w, (unit | shift) << (POW2 ? 2 : 0), reinterpret_cast<char*>(lds));
             }
-#pragma unroll
-            for (int u = 0; u < U; ++u)
-#pragma unroll
-                for (int m = 0; m < NV; ++m) fma_vec(acc[m], ok[u] ? wi[u] : 0.f, v[u][m]);
-        }
-
-        if (ns > 0) {
-            any_sparse = true;
-            if (p.ev == 4 && p.swizzle && (width & (width - 1)) == 0)
-                sparse_phase<T, 4, Z32, true, true>(p, lane, nd, ns, srow, w, mab, lpriv);
-            else if (p.ev == 4 && p.swizzle)
-                sparse_phase<T, 4, Z32, true>(p, lane, nd, ns, srow, w, mab, lpriv);
-            else if (p.ev == 4)
-                sparse_phase<T, 4, Z32, false>(p, lane, nd, ns, srow, w, mab, lpriv);
-            else if (p.ev == 2)
-                sparse_phase<T, 2, Z32, false>(p, lane, nd, ns, srow, w, mab, lpriv);
-            else
-                sparse_phase<T, 1, Z32, false>(p, lane, nd, ns, srow, w, mab, lpriv);
         }
     }
 
-    // sum the groups' partial rows
-    for (int off = lpr; off < 64; off <<= 1) {
-#pragma unroll
-        for (int m = 0; m < NV; ++m) add_vec(acc[m], shfl_xor_vec(acc[m], off));
-    }
+    sum_groups<VEC, NV>(p.lpr_log2, acc);
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    if (g == 0) {
+    if (NV == 0 && lane >= (1 << p.lpr_log2)) return;
 #pragma unroll
-        for (int m = 0; m < NV; ++m) {
-            const int col = VEC * (t + lpr * m);
-            if (col < width) {
-                V v = acc[m];
-                if (any_sparse) {
-                    for (int sub = 0; sub < p.epi; ++sub) {
-                        V x = *reinterpret_cast<const V*>(lpriv + sub * width + col);
-                        if constexpr (VEC == 4) {
-                            if (p.swizzle) {        // element i of the group of 4 sits at i ^ s
-                                const int sw = (col >> 5) & 3;
-                                const float e[4] = {x.x, x.y, x.z, x.w};
-                                x = make_float4(e[sw], e[1 ^ sw], e[2 ^ sw], e[3 ^ sw]);
-                            }
-                        }
-                        add_vec(v, x);
-                    }
-                }
-                if (it.dst < 0)
-                    store_vec<T, VEC>(p.out + int64_t(it.row - p.row_base) * width + col, v);
-                else
-                    *reinterpret_cast<V*>(p.partial + int64_t(it.dst) * width + col) = v;
-            }
+    for (int m = 0; m < NR; ++m) {
+        const int c = VEC * (lane + 64 * m);
+        if (c < width) {
+            if (SPARSE && any_sparse)
+                for (int sub = 0; sub < p.epi; ++sub) add_floats<VEC>(lds + sub * width + c, acc[m]);
+            if (it.dst < 0)
+                Packed<T, VEC>::put(p.out + int64_t(it.row - p.row_base) * width + c, acc[m]);
+            else
+                put_floats<VEC>(p.partial + int64_t(it.dst) * width + c, acc[m]);
         }
     }
 }
@@ -926,16 +893,38 @@ __global__ __launch_bounds__(kBlock) void validate_ids_kernel(const int32_t* a, 
     if (bad) atomicOr(flags, bit);
 }
 
-template <typename T, int VEC, int MODE>
-hipError_t launch_spmm_vec(int nv, const SpmmArgs<T>& a, dim3 grid, size_t lds_bytes, hipStream_t stream) {
+template <typename T, int VEC, int MODE, int EV, bool POW2>
+hipError_t launch_spmm_nv(int nv, const SpmmArgs<T>& a, dim3 grid, size_t lds_bytes, hipStream_t stream) {
+    auto go = [&](auto n) {
+        constexpr int NV = decltype(n)::value;
+        hipLaunchKernelGGL((spmm_kernel<T, VEC, NV, MODE, EV, POW2>), grid, dim3(agg_block(MODE)), lds_bytes, stream, a);
+        return hipGetLastError();
+    };
     switch (nv) {
-        case 1: hipLaunchKernelGGL((spmm_kernel<T, VEC, 1, MODE>), grid, dim3(agg_block(MODE)), lds_bytes, stream, a); break;
-        case 2: hipLaunchKernelGGL((spmm_kernel<T, VEC, 2, MODE>), grid, dim3(agg_block(MODE)), lds_bytes, stream, a); break;
-        case 4: hipLaunchKernelGGL((spmm_kernel<T, VEC, 4, MODE>), grid, dim3(agg_block(MODE)), lds_bytes, stream, a); break;
-        case 8: hipLaunchKernelGGL((spmm_kernel<T, VEC, 8, MODE>), grid, dim3(agg_block(MODE)), lds_bytes, stream, a); break;
-        default: return hipErrorInvalidValue;
+        case 0: return go(std::integral_constant<int, 0>{});
+        case 1: return go(std::integral_constant<int, 1>{});
+        case 2: return go(std::integral_constant<int, 2>{});
+        case 4: return go(std::integral_constant<int, 4>{});
+        case 8:
+            if constexpr (VEC < 8) return go(std::integral_constant<int, 8>{});
     }
-    return hipGetLastError();
+    return hipErrorInvalidValue;
+}
+template <typename T, int VEC, int MODE>
+hipError_t launch_spmm_vec(int nv, int ev, const SpmmArgs<T>& a, dim3 grid, size_t lds_bytes, hipStream_t stream) {
+    if constexpr (MODE < kSparse) {
+        return launch_spmm_nv<T, VEC, MODE, 1, false>(nv, a, grid, lds_bytes, stream);
+    } else {
+        const bool pow2 = (a.rule.width & (a.rule.width - 1)) == 0;
+        auto with_ev = [&](auto e) {
+            constexpr int EV = decltype(e)::value;
+            if constexpr (VEC > 1)
+                if (pow2) return launch_spmm_nv<T, VEC, MODE, EV, true>(nv, a, grid, lds_bytes, stream);
+            return launch_spmm_nv<T, VEC, MODE, EV, false>(nv, a, grid, lds_bytes, stream);
+        };
+        return ev == 4 ? with_ev(std::integral_constant<int, 4>{}) : ev == 2 ? with_ev(std::integral_constant<int, 2>{})
+                                                                             : with_ev(std::integral_constant<int, 1>{});
+    }
 }
 
 bool aligned_to(const void* p, size_t bytes) { return (reinterpret_cast<uintptr_t>(p) & (bytes - 1)) == 0; }
@@ -950,14 +939,17 @@ hipError_t spmm_t(const SpmmPlan& plan, const VarcoEdge* edge, const int32_t* co
     const int32_t width = int32_t(rule.width);
     const bool full = rule.k == rule.width;
     const bool halo = edge != nullptr;
-    const bool vec4 = width % 4 == 0 && aligned_to(dense, 4 * sizeof(T)) && aligned_to(out, 4 * sizeof(T)) &&
-                      aligned_to(partial, 16) && (!(halo && full) || aligned_to(z, 4 * sizeof(T)));
-    const int vec = vec4 ? 4 : 1;
+    auto vec_ok = [&](int v) {
+        return width % v == 0 && aligned_to(dense, v * sizeof(T)) && aligned_to(out, v * sizeof(T)) && aligned_to(partial, 16) &&
+               (!(halo && full) || aligned_to(z, v * sizeof(T)));
+    };
+    const bool vec4 = vec_ok(4);
+    const int vec = sizeof(T) == 2 && vec_ok(8) ? 8 : vec4 ? 4 : 1;
     const int per_row = (width + vec - 1) / vec;   // loads of VEC elements that cover a row
     int lpr_log2 = 0;
     while ((1 << lpr_log2) < per_row && lpr_log2 < 6) ++lpr_log2;
-    int nv = 1;
-    while (nv * (1 << lpr_log2) < per_row) nv <<= 1;
+    int nv = lpr_log2 < 6 ? 0 : 1;
+    while (nv && nv * 64 < per_row) nv <<= 1;
     if (nv > 8) return hipErrorInvalidValue;
 
     SpmmArgs<T> a;
@@ -977,41 +969,44 @@ hipError_t spmm_t(const SpmmPlan& plan, const VarcoEdge* edge, const int32_t* co
     // rows per instruction, each with a private LDS row. Prefer wide loads, but keep the private rows of
     // a wavefront within 4 KB so that LDS does not limit the number of resident wavefronts.
     const int epi_cap = std::max(1, 1024 / width);
-    a.ev = 1;
-    for (int ev : {4, 2}) {
-        if (rule.k % ev != 0 || !aligned_to(z, ev * sizeof(T))) continue;
+    int ev = 1;
+    for (int c : {4, 2}) {
+        if (rule.k % c != 0 || !aligned_to(z, c * sizeof(T))) continue;
         int lg = 0;
-        while ((1 << lg) < int(rule.k) / ev && lg < 6) ++lg;
+        while ((1 << lg) < int(rule.k) / c && lg < 6) ++lg;
         if ((64 >> lg) <= epi_cap) {
-            a.ev = ev;
+            ev = c;
             break;
         }
     }
-    a.ku = int32_t(rule.k) / a.ev;
+    a.ku = int32_t(rule.k) / ev;
     a.lpe_log2 = 0;
     while ((1 << a.lpe_log2) < a.ku && a.lpe_log2 < 6) ++a.lpe_log2;
     a.epi = std::max(1, std::min(64 >> a.lpe_log2, epi_cap));
-    // 16 or more lanes per compressed row, 4 elements each, rows of whole 128-position blocks read back 4 at a time
-    a.swizzle = halo && !full && a.ev == 4 && a.lpe_log2 >= 4 && vec4 && width % 128 == 0 ? 1 : 0;
-    const int agg_waves = agg_block(halo ? kHalo : kDenseOnly) / 64;
+    const int agg_waves = agg_block(halo ? kFull : kDenseOnly) / 64;
     const int32_t per_round = 8 * kXcdRun;                                         // see the kernel's XCD mapping
     const dim3 grid(((plan.n_items + agg_waves - 1) / agg_waves + per_round - 1) / per_round * per_round);
     size_t lds_bytes = 0;
     if (halo && !full)
-        lds_bytes = size_t(agg_waves) * a.epi * width * sizeof(float) + size_t(rule.n_units) * sizeof(uint16_t);
+        lds_bytes = (size_t(a.epi) * width * sizeof(float) + 15) / 16 * 16;
     tag.begin(stream);
-    hipError_t err;
+    hipError_t err = hipErrorInvalidValue;
     // compressed buffer below 4 GiB: 32-bit row offsets (z_rows = 0: size unknown)
     const bool z32 = halo && !full && z_rows > 0 && z_rows * int64_t(rule.k) * int64_t(sizeof(T)) < (int64_t(1) << 32);
-    if (halo && z32)
-        err = vec4 ? launch_spmm_vec<T, 4, kHaloZ32>(nv, a, grid, lds_bytes, stream)
-                   : launch_spmm_vec<T, 1, kHaloZ32>(nv, a, grid, lds_bytes, stream);
+    auto with_vec = [&](auto mode) {
+        constexpr int MODE = decltype(mode)::value;
+        if constexpr (sizeof(T) == 2)
+            if (vec == 8) return launch_spmm_vec<T, 8, MODE>(nv, ev, a, grid, lds_bytes, stream);
+        return vec4 ? launch_spmm_vec<T, 4, MODE>(nv, ev, a, grid, lds_bytes, stream) : launch_spmm_vec<T, 1, MODE>(nv, ev, a, grid, lds_bytes, stream);
+    };
+    if (halo && full)
+        err = with_vec(std::integral_constant<int, kFull>{});
+    else if (halo && z32)
+        err = with_vec(std::integral_constant<int, kSparseZ32>{});
     else if (halo)
-        err = vec4 ? launch_spmm_vec<T, 4, kHalo>(nv, a, grid, lds_bytes, stream)
-                   : launch_spmm_vec<T, 1, kHalo>(nv, a, grid, lds_bytes, stream);
+        err = with_vec(std::integral_constant<int, kSparse>{});
     else
-        err = vec4 ? launch_spmm_vec<T, 4, kDenseOnly>(nv, a, grid, lds_bytes, stream)
-                   : launch_spmm_vec<T, 1, kDenseOnly>(nv, a, grid, lds_bytes, stream);
+        err = with_vec(std::integral_constant<int, kDenseOnly>{});
     tag.end(stream);
     if (err != hipSuccess) return err;
     if (plan.n_splits > 0) {

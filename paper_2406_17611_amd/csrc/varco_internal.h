@@ -119,6 +119,7 @@ struct NodeItem {
 enum { VARCO_NODE_LOCAL_SPLIT = 1, VARCO_NODE_CROSS_SPLIT = 2 };
 struct NodePlan {
     int32_t n_nodes = 0, n_pieces = 0;     // pieces: row = 0 for a local range, 1 for a cross range; dst = its slot
+    int32_t n_whole = 0;                   // the nodes without pieces come first
     NodeItem* nodes = nullptr;             // device
     SpmmItem* pieces = nullptr;            // device
 };

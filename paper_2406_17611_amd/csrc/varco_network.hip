@@ -156,6 +156,7 @@ int32_t link_impl(varco_ctx* ctx) {
             cut(1, it.c0, it.c1, kNodeCross, VARCO_NODE_CROSS_SPLIT, it.flags);
         }
     }
+    net.nodes.n_whole = int32_t(std::stable_partition(nodes.begin(), nodes.end(), [](const NodeItem& it) { return it.flags == 0; }) - nodes.begin());
     net.nodes.n_nodes = int32_t(nodes.size()), net.nodes.n_pieces = int32_t(pieces.size());
     VARCO_HIP(ctx, alloc(net.nodes.nodes, nodes.size()));
     VARCO_HIP(ctx, alloc(net.nodes.pieces, pieces.size()));
