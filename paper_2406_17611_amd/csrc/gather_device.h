@@ -42,7 +42,7 @@ struct Packed<bf16_t, N> {
     static __device__ __forceinline__ void put(bf16_t* p, const float (&x)[N]) {
         type v;
 #pragma unroll
-        for (int i = 0; i < N / 2; ++i) v[i] = uint32_t(float_to_bf16(x[2 * i])) | (uint32_t(float_to_bf16(x[2 * i + 1])) << 16);
+        for (int i = 0; i < N / 2; ++i) v[i] = bf16_pair(x[2 * i], x[2 * i + 1]);
         *reinterpret_cast<type*>(p) = v;
     }
 };
@@ -52,7 +52,7 @@ struct Packed<bf16_t, 2> {
     static __device__ __forceinline__ type load(const bf16_t* p) { return *reinterpret_cast<const uint32_t*>(p); }
     static __device__ __forceinline__ void get(const type& v, float (&x)[2]) { x[0] = __uint_as_float(v << 16), x[1] = __uint_as_float(v & 0xFFFF0000u); }
     static __device__ __forceinline__ void put(bf16_t* p, const float (&x)[2]) {
-        *reinterpret_cast<uint32_t*>(p) = uint32_t(float_to_bf16(x[0])) | (uint32_t(float_to_bf16(x[1])) << 16);
+        *reinterpret_cast<uint32_t*>(p) = bf16_pair(x[0], x[1]);
     }
 };
 template <>

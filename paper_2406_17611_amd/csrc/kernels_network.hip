@@ -42,6 +42,7 @@ struct NodeArgs {
     int32_t add_old;
     float* partial;           // one width-float row per piece
     int32_t lpr_log2;         // lanes per dense row = 1 << lpr_log2
+    int32_t pitch;            // elements between product rows
     int32_t ku, lpe_log2;     // loads per product row, lanes per product row = 1 << lpe_log2
 };
 
@@ -133,7 +134,7 @@ __device__ __forceinline__ void node_piece(const NodeArgs<T>& p, const SpmmItem&
             const int ju = u0 + jl;
             const bool on = ju < p.ku;
             float s[EV];
-            sum_rows<T, EV>(p.prod, p.rule.k, it.e0, it.e1, ju * EV, on, sub, n_sub, p.lpe_log2, s);
+            sum_rows<T, EV>(p.prod, p.pitch, it.e0, it.e1, ju * EV, on, sub, n_sub, p.lpe_log2, s);
             if (on && sub == 0)
 #pragma unroll
                 for (int i = 0; i < EV; ++i) dst[ju * EV + i] = s[i];
@@ -232,13 +233,13 @@ __global__ __launch_bounds__(kBlock) void node_sum_kernel(NodeArgs<T> p) {
 #pragma unroll
                         for (int i = 0; i < EV; ++i) s[i] += __shfl_xor(s[i], off);
                 } else {
-                    sum_rows<T, EV>(p.prod, p.rule.k, it.c0, it.c1, ju * EV, on, sub, n_sub, p.lpe_log2, s);
+                    sum_rows<T, EV>(p.prod, p.pitch, it.c0, it.c1, ju * EV, on, sub, n_sub, p.lpe_log2, s);
                 }
                 if (on && sub == 0) {
                     uint32_t q = varco_position(p.rule, ma, uint32_t(ju * EV));
 #pragma unroll
                     for (int i = 0; i < EV; ++i) {
-                        lrow[q] = s[i];
+                        if (i == 0 || uint32_t(ju * EV + i) < p.rule.k) lrow[q] = s[i];
                         q += ma.a;
                         q = min(q, q - p.rule.width);
                     }
@@ -292,14 +293,15 @@ hipError_t node_sum_t(const NodePlan& plan, const uint2* t_local, const uint2* t
     int nv = a.lpr_log2 < 6 ? 0 : 1;
     while (nv && nv * 64 < per_row) nv <<= 1;
     if (nv > 8) return hipErrorInvalidValue;
+    a.pitch = varco_product_pitch(rule, int(sizeof(T)));
     int ev = 1;
     if (cross == kCrossProducts)
         for (int c : {int(16 / sizeof(T)), int(8 / sizeof(T)), 2})
-            if (rule.k % uint32_t(c) == 0 && aligned_to(prod, c * sizeof(T))) {
+            if (a.pitch % c == 0 && aligned_to(prod, c * sizeof(T))) {
                 ev = c;
                 break;
             }
-    a.ku = int32_t(rule.k) / ev;
+    a.ku = (int32_t(rule.k) + ev - 1) / ev;
     a.lpe_log2 = 0;
     while ((1 << a.lpe_log2) < a.ku && a.lpe_log2 < 6) ++a.lpe_log2;
 

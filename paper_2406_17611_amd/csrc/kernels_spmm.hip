@@ -321,15 +321,22 @@ __global__ __launch_bounds__(agg_block(MODE), MODE >= kSparse && VEC * NV <= 8 ?
         }
     }
 
+    if (SPARSE && any_sparse) {          // the private rows: each group of lanes adds some of them
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+        for (int m = 0; m < NR; ++m) {
+            const int c = NV == 0 ? VEC * (lane & ((1 << p.lpr_log2) - 1)) : VEC * (lane + 64 * m);
+            if (c < width)
+                for (int sub = NV == 0 ? lane >> p.lpr_log2 : 0; sub < p.epi; sub += NV == 0 ? 64 >> p.lpr_log2 : 1)
+                    add_floats<VEC>(lds + sub * width + c, acc[m]);
+        }
+    }
     sum_groups<VEC, NV>(p.lpr_log2, acc);
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     if (NV == 0 && lane >= (1 << p.lpr_log2)) return;
 #pragma unroll
     for (int m = 0; m < NR; ++m) {
         const int c = VEC * (lane + 64 * m);
         if (c < width) {
-            if (SPARSE && any_sparse)
-                for (int sub = 0; sub < p.epi; ++sub) add_floats<VEC>(lds + sub * width + c, acc[m]);
             if (it.dst < 0)
                 Packed<T, VEC>::put(p.out + int64_t(it.row - p.row_base) * width + c, acc[m]);
             else
@@ -510,7 +517,8 @@ struct ProductArgs {
     const int32_t* prow;        // per entry: row of the product buffer (halo entries only)
     const T* dm;                // n_local x width
     MaskRule rule;
-    T* prod;                    // (halo entries) x k, in the storage type
+    T* prod;                    // (halo entries) x pitch, in the storage type
+    int32_t pitch;              // elements per row: k, or k rounded up to whole 16-byte stores (see varco_product_pitch)
     int32_t ku;                 // stores per entry = k / (elements per store)
     int32_t lpe_log2;           // lanes per entry
 };
@@ -526,9 +534,10 @@ constexpr uint32_t swizzled(uint32_t q_bytes) { return q_bytes ^ ((q_bytes >> 6)
 
 // The product rows are read back by another kernel, long after they have left the caches: streaming stores.
 template <typename T, int EV>
-__device__ __forceinline__ void store_products(T* dst, const float (&x)[EV]) {
+__device__ __forceinline__ void store_products(T* row, const float (&x)[EV]) {
     typedef uint32_t words4 __attribute__((ext_vector_type(4)));
     typedef uint32_t words2 __attribute__((ext_vector_type(2)));
+    auto* const dst = (__attribute__((address_space(1))) T*)row;
     constexpr int N = EV * int(sizeof(T)) / 4;
     uint32_t u[N > 0 ? N : 1];
     if constexpr (sizeof(T) == 4) {
@@ -536,50 +545,48 @@ __device__ __forceinline__ void store_products(T* dst, const float (&x)[EV]) {
         for (int i = 0; i < EV; ++i) u[i] = __float_as_uint(x[i]);
     } else {
 #pragma unroll
-        for (int i = 0; i < N; ++i) u[i] = uint32_t(float_to_bf16(x[2 * i])) | (uint32_t(float_to_bf16(x[2 * i + 1])) << 16);
+        for (int i = 0; i < N; ++i) u[i] = bf16_pair(x[2 * i], x[2 * i + 1]);
     }
     if constexpr (N == 4)
-        __builtin_nontemporal_store(words4{u[0], u[1], u[2], u[3]}, reinterpret_cast<words4*>(dst));
+        __builtin_nontemporal_store(words4{u[0], u[1], u[2], u[3]}, (__attribute__((address_space(1))) words4*)dst);
     else if constexpr (N == 2)
-        __builtin_nontemporal_store(words2{u[0], u[1]}, reinterpret_cast<words2*>(dst));
+        __builtin_nontemporal_store(words2{u[0], u[1]}, (__attribute__((address_space(1))) words2*)dst);
     else if constexpr (N == 1)
-        __builtin_nontemporal_store(u[0], reinterpret_cast<uint32_t*>(dst));
+        __builtin_nontemporal_store(u[0], (__attribute__((address_space(1))) uint32_t*)dst);
     else
-        Elem<T>::store(dst, x[0]);
+        Elem<T>::store(row, x[0]);
 }
 
+// `row`: LDS byte address of the wavefront's row of dM; dst: every entry's row of the product buffer (its lane's).
 template <typename T, int EV, bool POW2, bool SWZ>
-__device__ __forceinline__ void product_phase(const ProductArgs<T>& p, int lane, int first, int ns, int32_t pr, float w,
-                                              uint32_t mab, const float* lrow) {
-    const int64_t k = p.rule.k;
+__device__ __forceinline__ void product_phase(const ProductArgs<T>& p, int lane, int first, int ns, uint64_t dst, float w,
+                                              uint32_t mab, uint32_t row) {
+    using lds_float = __attribute__((address_space(3))) float;
     const uint32_t width = p.rule.width, row_bytes = width * 4u;
     const int epi = 64 >> p.lpe_log2;
     const int sub = lane >> p.lpe_log2;
     const int jl = lane & ((1 << p.lpe_log2) - 1);
-    const char* const row = reinterpret_cast<const char*>(lrow);
     for (int j0 = 0; j0 < p.ku; j0 += 64) {
         const int ju = j0 + jl;
         const bool j_ok = ju < p.ku;
         const int j = ju * EV;
         for (int r0 = 0; r0 < ns; r0 += epi) {
-            const int es = r0 + sub;
-            const bool act = j_ok && es < ns;
-            const int src_lane = act ? first + es : 0;
-            const int32_t dst_row = __shfl(pr, src_lane);
-            const float wi = __shfl(w, src_lane);
-            const uint32_t ab = __shfl(mab, src_lane);
-            if (act) {
+            const int at = 4 * (first + r0 + sub);
+            const uint64_t to = (uint64_t(lane_value(uint32_t(dst >> 32), at)) << 32) | lane_value(uint32_t(dst), at);
+            const float wi = __uint_as_float(lane_value(__float_as_uint(w), at));
+            const uint32_t ab = lane_value(mab, at);
+            if (j_ok && r0 + sub < ns) {
                 const uint32_t a = ab & 0xFFFFu, a4 = a * 4u;
                 uint32_t q = __umul24(a, uint32_t(j)) + (ab >> 16);
                 q = (POW2 ? q & (width - 1u) : varco_mod_width(q, width, p.rule.width_magic)) * 4u;
                 float out[EV];
 #pragma unroll
                 for (int i = 0; i < EV; ++i) {
-                    out[i] = wi * *reinterpret_cast<const float*>(row + (SWZ ? swizzled(q) : q));
+                    out[i] = wi * *(const lds_float*)(uintptr_t((SWZ ? swizzled(q) : q) + row));
                     q += a4;
                     q = POW2 ? q & (row_bytes - 1u) : min(q, q - row_bytes);
                 }
-                store_products<T, EV>(p.prod + int64_t(dst_row) * k + j, out);
+                store_products<T, EV>(reinterpret_cast<T*>(to) + j, out);
             }
         }
     }
@@ -598,6 +605,7 @@ __global__ __launch_bounds__(kBlock) void halo_products_kernel(ProductArgs<T> p)
     const int wave = threadIdx.x >> 6;
     const int32_t width = int32_t(p.rule.width);
     float* lrow = lds + wave * width;
+    const uint32_t lrow_at = uint32_t(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) float*)lrow));
     uint16_t* lunits = reinterpret_cast<uint16_t*>(lds + kWaves * width);
     int32_t idx = (blockIdx.x * kWaves + __builtin_amdgcn_readfirstlane(wave)) * kProductItems;   // uniform: items sit in scalar registers
     const int32_t end = min(idx + kProductItems, p.n_items);
@@ -677,12 +685,12 @@ __global__ __launch_bounds__(kBlock) void halo_products_kernel(ProductArgs<T> p)
             const int ns = __popcll(hmask);
             const int first = cnt - ns;     // columns ascend within a row: halo entries sit in the last lanes
             const float wb = w;
-            const int32_t prb = pr;
+            const uint64_t dst = reinterpret_cast<uint64_t>(p.prod + int64_t(pr) * p.pitch);
             if (base + 64 < it.e1)
                 load_batch(it, base + 64);
             else
                 load_batch(nx, nx.e0);
-            if (ns > 0) product_phase<T, EV, POW2, SWZ>(p, lane, first, ns, prb, wb, mab, lrow);
+            if (ns > 0) product_phase<T, EV, POW2, SWZ>(p, lane, first, ns, dst, wb, mab, lrow_at);
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");     // the row has been read: the next one may overwrite it
         it = nx;
@@ -1068,12 +1076,12 @@ hipError_t spmm_short_t(const SpmmPlan& plan, const int32_t* colidx, const float
 // First pass: see halo_products_kernel.
 template <typename T>
 hipError_t halo_products_t(const SpmmPlan& fwd_plan, const VarcoEdge* edge, const float* vals, const int32_t* prow, const void* dm,
-                           const MaskRule& rule, void* prod_v, hipStream_t stream, const LaunchTag& tag) {
+                           const MaskRule& rule, void* prod_v, int32_t pitch, hipStream_t stream, const LaunchTag& tag) {
     T* prod = static_cast<T*>(prod_v);
     const int32_t width = int32_t(rule.width);
     int ev = 1;
     for (int c : {int(16 / sizeof(T)), 4, 2})
-        if (rule.k % c == 0 && aligned_to(prod, c * sizeof(T))) {
+        if (pitch % c == 0 && aligned_to(prod, c * sizeof(T))) {
             ev = c;
             break;
         }
@@ -1086,7 +1094,8 @@ hipError_t halo_products_t(const SpmmPlan& fwd_plan, const VarcoEdge* edge, cons
     a.dm = static_cast<const T*>(dm);
     a.rule = rule;
     a.prod = prod;
-    a.ku = int(rule.k) / ev, a.lpe_log2 = 0;
+    a.pitch = pitch;
+    a.ku = pitch / ev, a.lpe_log2 = 0;      // elements beyond k are products as well, and are not read
     while ((1 << a.lpe_log2) < a.ku && a.lpe_log2 < 6) ++a.lpe_log2;
     const size_t lds_bytes = size_t(kWaves) * width * sizeof(float) + size_t(rule.n_units) * sizeof(uint16_t);
     const bool pow2 = (width & (width - 1)) == 0;
@@ -1129,7 +1138,7 @@ hipError_t halo_grad_t(const SpmmPlan& fwd_plan, const SpmmPlan& t_halo_plan, co
                        const int32_t* prow, int32_t prod_base, const void* dm, const MaskRule& rule, void* prod_v,
                        void* out_v, int32_t row_base, float* partial, hipStream_t stream, const LaunchTag& tag,
                        const LaunchTag& sum_tag) {
-    hipError_t err = halo_products_t<T>(fwd_plan, edge, vals, prow, dm, rule, prod_v, stream, tag);
+    hipError_t err = halo_products_t<T>(fwd_plan, edge, vals, prow, dm, rule, prod_v, int32_t(rule.k), stream, tag);
     if (err != hipSuccess) return err;
     T* out = static_cast<T*>(out_v);
     T* prod = static_cast<T*>(prod_v);
@@ -1234,10 +1243,10 @@ hipError_t varco_launch_build_prow(const int32_t* rowptr, const int32_t* colidx,
 }
 
 hipError_t varco_launch_halo_products(int dtype, const SpmmPlan& fwd_plan, const VarcoEdge* edge, const float* vals, const int32_t* prow,
-                                      const void* dm, const MaskRule& rule, void* prod, hipStream_t stream, const LaunchTag& tag) {
+                                      const void* dm, const MaskRule& rule, void* prod, int32_t pitch, hipStream_t stream, const LaunchTag& tag) {
     if (fwd_plan.n_items == 0) return hipSuccess;
-    return dtype == VARCO_BF16 ? halo_products_t<bf16_t>(fwd_plan, edge, vals, prow, dm, rule, prod, stream, tag)
-                               : halo_products_t<float>(fwd_plan, edge, vals, prow, dm, rule, prod, stream, tag);
+    return dtype == VARCO_BF16 ? halo_products_t<bf16_t>(fwd_plan, edge, vals, prow, dm, rule, prod, pitch, stream, tag)
+                               : halo_products_t<float>(fwd_plan, edge, vals, prow, dm, rule, prod, pitch, stream, tag);
 }
 
 hipError_t varco_launch_halo_grad(int dtype, const SpmmPlan& fwd_plan, const SpmmPlan& t_halo_plan, const VarcoEdge* edge,

@@ -20,12 +20,17 @@ constexpr double kProdBytes = 48.0 * (1ull << 30);
 
 // Products of k values per cross entry are written and read back (2 k elements at about 4.8 TB/s), or whole rows are
 // gathered (width elements at about 7 TB/s).
+int32_t product_pitch(const varco_ctx* ctx, int32_t layer) {
+    MaskRule r{};
+    r.k = uint32_t(ctx->layers[layer].k), r.width = uint32_t(ctx->widths[layer]);
+    return varco_product_pitch(r, ctx->elem_bytes());
+}
 bool products_pay(const varco_ctx* ctx, int32_t layer) {
     const int64_t k = ctx->layers[layer].k, width = ctx->widths[layer];
-    return k > 0 && 3 * k < width && double(ctx->net.nnz_cross) * double(k) * ctx->elem_bytes() <= kProdBytes;
+    return k > 0 && 3 * k < width && double(ctx->net.nnz_cross) * product_pitch(ctx, layer) * ctx->elem_bytes() <= kProdBytes;
 }
 size_t prod_floats(const varco_ctx* ctx, int32_t layer) {
-    return (size_t(ctx->net.nnz_cross) * size_t(ctx->layers[layer].k) * size_t(ctx->elem_bytes()) + 3) / 4;
+    return (size_t(ctx->net.nnz_cross) * size_t(product_pitch(ctx, layer)) * size_t(ctx->elem_bytes()) + 3) / 4;
 }
 
 // Split of a weight gradient's reduction over the arena's rows: one round of two workgroups per compute unit, at least two
@@ -221,7 +226,8 @@ int32_t aggregate_bwd(varco_ctx* ctx, Workspace& ws, int32_t layer, const MaskRu
     if (cross == kCrossMasked && products_pay(ctx, layer) && prod_floats(ctx, layer) <= ws.prod_elems) {
         cross = kCrossProducts;
         const double bytes = double(net.nnz_cross) * 8.0 + double(net.rows) * fi * es;
-        VARCO_HIP(ctx, varco_launch_halo_products(ctx->dtype, net.fwd, net.edges, net.vals, net.prow, dm, rule, ws.prod, st,
+        VARCO_HIP(ctx, varco_launch_halo_products(ctx->dtype, net.fwd, net.edges, net.vals, net.prow, dm, rule, ws.prod,
+                                                  product_pitch(ctx, layer), st,
                                                   ctx->tag(VARCO_K_AGG_BWD_HALO, bytes, 0)));
     }
     const double bytes = double(net.nnz_local) * 8.0 + (double(net.rows) + 1.0) * 4.0 + 2.0 * double(net.rows) * fi * es;
