@@ -1,0 +1,326 @@
+// Weight gradients of bf16-stored activations: C[m x n] = sum over rows r of A[r, i] B[r, j] (both operands row-major with the
+// reduction index slow), optionally with a ReLU mask on B, in fp32 on the matrix cores (v_mfma_f32_32x32x16_bf16).
+//
+// Both operands go to LDS as they lie in memory, rows of one reduction index, with 16-byte loads and writes, and are
+// transposed when they are read: ds_read_b64_tr_b16 hands lane i of a group of 16 the i-th column of a 4 x 16 block. The
+// kernel in kernels_gemm_bf16.hip transposes 8 x 4 blocks in registers instead (eight 8-byte loads, 32 word operations and as
+// many selects per block and thread); its stage of 32 rows moved as many bytes through the vector memory unit (64 bytes per
+// cycle) as its 256 x 128 tile could multiply in that time. A 256 x 256 tile takes 3/4 of the bytes per product.
+// Row pitch in LDS: 64 bytes more than a multiple of 256, so that the four rows that a group of lanes reads start in four
+// different quarters of the banks.
+// Bound by reading A, B and the mask once (the tiles of one slab of rows run on one XCD and share them through its L2).
+// 169,343 rows, 512 x 512, masked: 163 us (540 TFLOP/s); 2,449,029 rows: 1.93 ms, where that kernel took 3.7.
+#include <algorithm>
+#include <type_traits>
+
+#include "elem.h"
+#include "varco_internal.h"
+
+namespace {
+
+constexpr int BK = 32;
+constexpr int kThreads = 512;
+
+typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef short shortx4 __attribute__((ext_vector_type(4)));
+typedef uint32_t words4 __attribute__((ext_vector_type(4)));
+typedef uint32_t words2 __attribute__((ext_vector_type(2)));
+
+struct TnDev {
+    int32_t m, n, k;
+    const uint16_t* a;
+    const uint16_t* b;
+    const uint16_t* gate;
+    const uint16_t* a_dual;
+    int64_t lda, ldb;
+    float* c;
+    float* c_dual;
+    int64_t ldc;
+    int32_t accumulate;
+    int32_t split_k, stages_per_split;
+    float* partial;
+    int32_t tiles_n, tiles, inner;
+};
+
+__device__ __forceinline__ uint32_t gate_pair(uint32_t v, uint32_t g) {
+    const uint32_t lo = __uint_as_float(g << 16) > 0.f ? 0x0000FFFFu : 0u;
+    const uint32_t hi = __uint_as_float(g & 0xFFFF0000u) > 0.f ? 0xFFFF0000u : 0u;
+    return v & (lo | hi);
+}
+
+// One operand's share of a stage: W columns x BK rows in chunks of CH elements, dealt to the threads row by row.
+template <int W, int CH, bool GATE>
+struct Slab {
+    using V = std::conditional_t<CH == 8, words4, words2>;
+    static constexpr int PER_ROW = W / CH, TOTAL = PER_ROW * BK, N = (TOTAL + kThreads - 1) / kThreads, ROWS = kThreads / PER_ROW;
+    static constexpr int PITCH = W * 2 + 64;               // bytes
+    static_assert(kThreads % PER_ROW == 0, "a thread keeps its columns");
+    V v[N], g[GATE ? N : 1];
+    uint32_t col, row;                                     // of this thread's first chunk
+    __device__ __forceinline__ void start(int32_t i0, int32_t extent) {
+        row = threadIdx.x / PER_ROW;
+        const int32_t c = i0 + int32_t(threadIdx.x % PER_ROW) * CH;
+        col = c < extent ? c : i0;                         // columns past the matrix: a repeated one, never stored
+    }
+    // rows k0 .. k0 + BK - 1; those from kmax on are zero
+    __device__ __forceinline__ void load(const uint16_t* p, const uint16_t* gate, int64_t ld, int32_t k0, int32_t kmax) {
+#pragma unroll
+        for (int h = 0; h < N; ++h) {
+            if (TOTAL < kThreads && threadIdx.x >= TOTAL) break;
+            const int32_t r = k0 + int32_t(row) + h * ROWS;
+            const int64_t off = int64_t(min(r, kmax - 1)) * ld + col;
+            v[h] = *reinterpret_cast<const V*>(p + off);
+            if constexpr (GATE) g[h] = *reinterpret_cast<const V*>(gate + off);
+        }
+    }
+    __device__ __forceinline__ void store(char* s, int32_t k0, int32_t kmax) const {
+#pragma unroll
+        for (int h = 0; h < N; ++h) {
+            if (TOTAL < kThreads && threadIdx.x >= TOTAL) break;
+            const bool in = k0 + int32_t(row) + h * ROWS < kmax;
+            V x = v[h];
+#pragma unroll
+            for (int u = 0; u < CH / 2; ++u) {
+                if constexpr (GATE) x[u] = gate_pair(x[u], g[h][u]);
+                x[u] = in ? x[u] : 0u;
+            }
+            *reinterpret_cast<V*>(s + (row + h * ROWS) * PITCH + (threadIdx.x % PER_ROW) * (CH * 2)) = x;
+        }
+    }
+};
+
+// B read element by element (64 columns at most, never masked): rows that are not 8-byte aligned, as the 47 class columns of a
+// last layer.
+struct ElementSlab {
+    static constexpr int N = 64 * BK / kThreads, PITCH = 64 * 2 + 64;
+    uint16_t v[N];
+    int32_t row[N], col[N];
+    __device__ __forceinline__ void start(int32_t, int32_t extent) {
+#pragma unroll
+        for (int h = 0; h < N; ++h) {
+            const int32_t e = int32_t(threadIdx.x) + h * kThreads;
+            row[h] = e / extent, col[h] = e - row[h] * extent;         // row >= BK: not this thread's
+        }
+    }
+    __device__ __forceinline__ void load(const uint16_t* p, const uint16_t*, int64_t ld, int32_t k0, int32_t kmax) {
+#pragma unroll
+        for (int h = 0; h < N; ++h) v[h] = p[int64_t(min(k0 + row[h], kmax - 1)) * ld + col[h]];
+    }
+    __device__ __forceinline__ void store(char* s, int32_t k0, int32_t kmax) const {
+#pragma unroll
+        for (int h = 0; h < N; ++h)
+            if (row[h] < BK) *reinterpret_cast<uint16_t*>(s + row[h] * PITCH + col[h] * 2) = k0 + row[h] < kmax ? v[h] : uint16_t(0);
+    }
+};
+template <int W, int CH, bool GATE>
+using SlabOf = std::conditional_t<CH == 1, ElementSlab, Slab<W, CH == 1 ? 8 : CH, GATE>>;
+
+// Fragment of 32 columns x 16 rows whose first column's element of row 0 (this lane's share of the block) is at LDS byte `at`.
+template <int PITCH>
+__device__ __forceinline__ bf16x8 fragment(uint32_t at) {
+    using P = __attribute__((address_space(3))) shortx4*;
+    const shortx4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((P)(uintptr_t)at);
+    const shortx4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((P)(uintptr_t)(at + 4 * PITCH));
+    typedef short shortx8 __attribute__((ext_vector_type(8)));
+    return __builtin_bit_cast(bf16x8, shortx8{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]});
+}
+
+template <int WM, int WN, int TMB, int TNB, int ACH, int BCH, bool GATE>
+__global__ __launch_bounds__(kThreads, TMB * TNB > 4 ? 2 : 4) void gemm_tn_bf16_kernel(TnDev g) {
+    static_assert(WM * WN * 64 == kThreads, "");
+    constexpr int BM = 32 * TMB * WM, BN = 32 * TNB * WN;
+    using SA = SlabOf<BM, ACH, false>;
+    using SB = SlabOf<BN, BCH, GATE>;
+    extern __shared__ __attribute__((aligned(16))) char lds[];          // two buffers of BK rows of A, then of B
+    constexpr int kA = BK * SA::PITCH, kB = BK * SB::PITCH;
+
+    // slabs of rows are dealt to the 8 XCDs; all tiles of a slab go to one
+    const int32_t xcd = blockIdx.x & 7, within = blockIdx.x >> 3;
+    const int32_t in = within % g.inner, z = (within / g.inner) * 8 + xcd;
+    if (z >= g.split_k) return;            // whole workgroup leaves together: no barrier is skipped
+    const bool second = in >= g.tiles;
+    const int32_t tile = second ? in - g.tiles : in;
+    const int32_t m0 = tile / g.tiles_n * BM, n0 = tile % g.tiles_n * BN;
+    const uint16_t* const a = second ? g.a_dual : g.a;
+    const int32_t stages = (g.k + BK - 1) / BK;
+    const int32_t s0 = z * g.stages_per_split, s1 = min(stages, s0 + g.stages_per_split);
+
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int wm = (wave / WN) * (32 * TMB), wn = (wave % WN) * (32 * TNB);
+    floatx16 acc[TMB][TNB];
+#pragma unroll
+    for (int i = 0; i < TMB; ++i)
+#pragma unroll
+        for (int j = 0; j < TNB; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+
+    // this lane's share of a 4 x 16 block: row (lane / 4) % 4, columns 4 (lane % 4) ..; groups of 16 lanes: columns 0 and 16, rows
+    // 0 and 8 of the fragment
+    const uint32_t row = 8 * (lane >> 5) + ((lane >> 2) & 3), sub = 32 * ((lane >> 4) & 1) + 8 * (lane & 3);
+    const uint32_t base = uint32_t(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) char*)lds));
+    const uint32_t at_a = base + row * SA::PITCH + sub + wm * 2, at_b = base + 2 * kA + row * SB::PITCH + sub + wn * 2;
+
+    SA sa;
+    SB sb;
+    sa.start(m0, g.m);
+    sb.start(n0, g.n);
+    if (s0 < s1) {
+        sa.load(a, nullptr, g.lda, s0 * BK, g.k);
+        sb.load(g.b, g.gate, g.ldb, s0 * BK, g.k);
+        sa.store(lds, s0 * BK, g.k);
+        sb.store(lds + 2 * kA, s0 * BK, g.k);
+    }
+    __syncthreads();
+    for (int32_t s = s0; s < s1; ++s) {
+        const uint32_t buf = uint32_t(s - s0) & 1u;
+        const bool more = s + 1 < s1;
+        if (more) {
+            sa.load(a, nullptr, g.lda, (s + 1) * BK, g.k);
+            sb.load(g.b, g.gate, g.ldb, (s + 1) * BK, g.k);
+        }
+#pragma unroll
+        for (int h = 0; h < BK / 16; ++h) {
+            bf16x8 fa[TMB], fb[TNB];
+#pragma unroll
+            for (int i = 0; i < TMB; ++i) fa[i] = fragment<SA::PITCH>(at_a + buf * kA + h * 16 * SA::PITCH + i * 64);
+#pragma unroll
+            for (int j = 0; j < TNB; ++j) fb[j] = fragment<SB::PITCH>(at_b + buf * kB + h * 16 * SB::PITCH + j * 64);
+#pragma unroll
+            for (int i = 0; i < TMB; ++i)
+#pragma unroll
+                for (int j = 0; j < TNB; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i], fb[j], acc[i][j], 0, 0, 0);
+        }
+        if (more) {
+            sa.store(lds + (buf ^ 1u) * kA, (s + 1) * BK, g.k);
+            sb.store(lds + 2 * kA + (buf ^ 1u) * kB, (s + 1) * BK, g.k);
+        }
+        __syncthreads();
+    }
+
+    // accumulator register v of a lane is element (8 * (v / 4) + 4 * (lane / 32) + v % 4, lane % 32)
+    float* const out = g.split_k > 1 ? g.partial + (int64_t(second ? g.split_k : 0) + z) * g.m * g.n : second ? g.c_dual : g.c;
+    const int64_t ldo = g.split_k > 1 ? g.n : g.ldc;
+    const bool add_old = g.split_k <= 1 && g.accumulate;
+#pragma unroll
+    for (int i = 0; i < TMB; ++i)
+#pragma unroll
+        for (int j = 0; j < TNB; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int32_t r = m0 + wm + i * 32 + 4 * (lane >> 5) + 8 * (v >> 2) + (v & 3), c = n0 + wn + j * 32 + (lane & 31);
+                if (r < g.m && c < g.n) {
+                    float* const p = out + int64_t(r) * ldo + c;
+                    *p = add_old ? *p + acc[i][j][v] : acc[i][j][v];
+                }
+            }
+}
+
+bool aligned_to(const void* p, uintptr_t bytes) { return (reinterpret_cast<uintptr_t>(p) & (bytes - 1)) == 0; }
+
+// Elements per load of an operand: 8, 4, or 1 when its rows or width do not allow either (columns between the width and the
+// pitch may be read).
+int chunk_of(const void* p, const void* gate, int64_t ld, int32_t extent) {
+    for (int c : {8, 4})
+        if (aligned_to(p, 2 * c) && aligned_to(gate, 2 * c) && ld % c == 0 && (extent % c == 0 || ld >= (extent + c - 1) / c * c)) return c;
+    return 1;
+}
+int chunk_a(const GemmArgs& g) { return std::min(chunk_of(g.a.ptr, nullptr, g.a.ld, g.m), g.c_dual ? chunk_of(g.a_dual, nullptr, g.a.ld, g.m) : 8); }
+int chunk_b(const GemmArgs& g) { return chunk_of(g.b.ptr, g.b.gate, g.b.ld, g.n); }
+
+}  // namespace
+
+bool varco_gemm_tn_bf16_usable(const GemmArgs& g) {
+    if (g.m <= 0 || g.n <= 0 || g.k <= 0 || !g.a.transposed || g.b.transposed || g.k2 > 0 || g.a.gate || g.relu) return false;
+    if (g.a.dtype != VARCO_BF16 || g.b.dtype != VARCO_BF16 || g.c_dtype != VARCO_F32 || (g.c_dual && !g.a_dual)) return false;
+    return chunk_a(g) > 1 && (chunk_b(g) > 1 || (g.n <= 64 && !g.b.gate));
+}
+
+// Tile for a product of m x n: 256 rows, or 128 where 256 would be half empty; 256, 128 or 64 columns likewise.
+void varco_gemm_tn_bf16_tile(int32_t m, int32_t n, int32_t* bm, int32_t* bn, int32_t* per_cu) {
+    *bm = m <= 128 ? 128 : 256;
+    *bn = n <= 64 ? 64 : n <= 128 ? 128 : 256;
+    *per_cu = *bm == 256 && *bn == 256 ? 1 : 2;      // resident workgroups
+}
+
+hipError_t varco_launch_gemm_tn_bf16(const GemmArgs& ga, hipStream_t stream, const LaunchTag& tag, int32_t* split_used) {
+    int32_t bm, bn, per_cu;
+    varco_gemm_tn_bf16_tile(ga.m, ga.n, &bm, &bn, &per_cu);
+    auto u16 = [](const void* p) { return static_cast<const uint16_t*>(p); };
+    TnDev g;
+    g.m = ga.m, g.n = ga.n, g.k = ga.k;
+    g.a = u16(ga.a.ptr), g.b = u16(ga.b.ptr), g.gate = u16(ga.b.gate);
+    g.a_dual = ga.c_dual ? u16(ga.a_dual) : nullptr;
+    g.lda = ga.a.ld, g.ldb = ga.b.ld;
+    g.c = static_cast<float*>(ga.c), g.c_dual = static_cast<float*>(ga.c_dual), g.ldc = ga.ldc;
+    g.accumulate = ga.accumulate ? 1 : 0;
+    const int32_t stages = (ga.k + BK - 1) / BK;
+    int32_t split = std::max(1, std::min(ga.split_k, stages));
+    g.stages_per_split = (stages + split - 1) / split;
+    split = (stages + g.stages_per_split - 1) / g.stages_per_split;
+    g.split_k = split;
+    g.partial = ga.partial;
+    if (split > 1 && !ga.partial) return hipErrorInvalidValue;
+    g.tiles_n = (ga.n + bn - 1) / bn;
+    g.tiles = (ga.m + bm - 1) / bm * g.tiles_n;
+    g.inner = g.tiles * (ga.c_dual ? 2 : 1);
+    const int64_t blocks = int64_t((split + 7) / 8 * 8) * g.inner;
+    if (blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
+    *split_used = split;
+    const int ca = chunk_a(ga), cb = chunk_b(ga);
+
+    hipError_t err = hipSuccess;
+    auto launch = [&](auto wm, auto wn, auto tmb, auto tnb, auto ach, auto bch, auto gated) {
+        constexpr int WM = decltype(wm)::value, WN = decltype(wn)::value, TMB = decltype(tmb)::value, TNB = decltype(tnb)::value;
+        constexpr int ACH = decltype(ach)::value, BCH = decltype(bch)::value;
+        constexpr bool G = decltype(gated)::value;
+        const size_t bytes = size_t(2 * BK) * (SlabOf<32 * TMB * WM, ACH, false>::PITCH + SlabOf<32 * TNB * WN, BCH, G>::PITCH);
+        const auto kernel = gemm_tn_bf16_kernel<WM, WN, TMB, TNB, ACH, BCH, G>;
+        if (bytes > 64 * 1024) {
+            err = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, int(bytes));
+            if (err != hipSuccess) return;
+        }
+        tag.begin(stream);
+        hipLaunchKernelGGL(kernel, dim3(unsigned(blocks)), dim3(kThreads), bytes, stream, g);
+        tag.end(stream);
+    };
+    auto with_gate = [&](auto wm, auto wn, auto tmb, auto tnb, auto ach, auto bch) {
+        if (g.gate)
+            launch(wm, wn, tmb, tnb, ach, bch, std::true_type{});
+        else
+            launch(wm, wn, tmb, tnb, ach, bch, std::false_type{});
+    };
+    using I1 = std::integral_constant<int, 1>;
+    using I2 = std::integral_constant<int, 2>;
+    using I4 = std::integral_constant<int, 4>;
+    using I8 = std::integral_constant<int, 8>;
+    auto with_chunks = [&](auto wm, auto wn, auto tmb, auto tnb) {
+        if (cb == 1) {
+            if constexpr (decltype(tnb)::value * decltype(wn)::value == 2) {
+                if (ca == 8)
+                    launch(wm, wn, tmb, tnb, I8{}, I1{}, std::false_type{});
+                else
+                    launch(wm, wn, tmb, tnb, I4{}, I1{}, std::false_type{});
+            }
+        } else if (ca == 8 && cb == 8)
+            with_gate(wm, wn, tmb, tnb, I8{}, I8{});
+        else if (cb == 8)
+            with_gate(wm, wn, tmb, tnb, I4{}, I8{});
+        else
+            with_gate(wm, wn, tmb, tnb, I4{}, I4{});
+    };
+    if (bm == 256 && bn == 256)
+        with_chunks(I2{}, I4{}, I4{}, I2{});
+    else if (bm == 256 && bn == 128)
+        with_chunks(I4{}, I2{}, I2{}, I2{});
+    else if (bm == 256)
+        with_chunks(I4{}, I2{}, I2{}, I1{});
+    else if (bn == 256)
+        with_chunks(I2{}, I4{}, I2{}, I2{});
+    else if (bn == 128)
+        with_chunks(I2{}, I4{}, I2{}, I1{});
+    else
+        with_chunks(I4{}, I2{}, I1{}, I1{});
+    return err != hipSuccess ? err : hipGetLastError();
+}

@@ -199,15 +199,17 @@ hipError_t grow(float*& buf, size_t& have, size_t want) {
 // Number of slabs the node dimension of a weight-gradient product is cut into: the workgroups of one launch
 // should fill the chip exactly once (three 256-thread workgroups of the GEMM kernel are resident per
 // compute unit, 256 compute units), so that no partly filled second round is left over.
-// (The bf16 kernel has 256-row tiles, the kernel on expanded fp32 operands 128-row tiles; both take 32
-// reduction steps per tile and have two resident workgroups per unit.)
+// (The bf16 kernel chooses its tile by the shape, the kernel on expanded fp32 operands has 128-row tiles and two resident
+// workgroups per unit; both take 32 reduction steps per tile.)
+int64_t wgrad_slots(int32_t m, int32_t n, int kind, int products) {
+    int32_t bm = kind == kGemmF32 && n <= 64 ? 256 : 128, bn = n <= 64 ? 64 : 128, per_cu = kind == kGemmF32 ? 3 : 2;
+    if (kind == kGemmBf16) varco_gemm_tn_bf16_tile(m, n, &bm, &bn, &per_cu);
+    const int64_t tiles = int64_t(products) * ((m + bm - 1) / bm) * ((n + bn - 1) / bn);
+    return std::max<int64_t>(1, per_cu * 256 / tiles);
+}
 int32_t gemm_split_for(int32_t m, int32_t n, int64_t k, int kind) {
-    const int64_t bm = kind == kGemmBf16 || (kind == kGemmF32 && n <= 64) ? 256 : 128, bn = n <= 64 ? 64 : 128;
-    const int64_t tiles = ((m + bm - 1) / bm) * ((n + bn - 1) / bn);
     const int64_t k_tiles = kind == kGemmF32 ? (k + 15) / 16 : (k + 31) / 32;
-    int64_t split = std::max<int64_t>(1, ((kind == kGemmF32 ? 3 : 2) * 256) / tiles);
-    split = std::min<int64_t>(split, std::max<int64_t>(1, k_tiles / 8));
-    return int32_t(split);
+    return int32_t(std::min<int64_t>(wgrad_slots(m, n, kind, 1), std::max<int64_t>(1, k_tiles / 8)));
 }
 int gemm_kind(const GemmArgs& g) {
     return varco_gemm_bf16_usable(g) ? kGemmBf16 : varco_gemm_split_usable(g) ? kGemmExpanded : kGemmF32;

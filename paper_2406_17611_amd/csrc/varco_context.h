@@ -127,9 +127,10 @@ void free_network(NetState& net);
 // Floats of a workspace's product buffer that the calls on all partitions ask for at the current ratios.
 size_t network_prod_need(const varco_ctx* ctx);
 hipError_t grow(float*& buf, size_t& have, size_t want);
-enum GemmKind { kGemmF32 = 0, kGemmBf16 = 1, kGemmExpanded = 2 };
+enum GemmKind { kGemmF32 = 0, kGemmBf16 = 1, kGemmExpanded = 2 };     // kGemmBf16: as weight gradients
 int32_t gemm_split_for(int32_t m, int32_t n, int64_t k, int kind);
 int gemm_kind(const GemmArgs& g);
+int64_t wgrad_slots(int32_t m, int32_t n, int kind, int products);     // slabs that fill the device once
 bool prep_slot(varco_ctx* ctx, Workspace& ws, int32_t layer, const void* h, int32_t fi, int32_t fo, bool transpose, int which, bool as_b2,
                GemmArgs& g, PrepJob* job);
 hipError_t prep_weight(varco_ctx* ctx, Workspace& ws, int32_t layer, const void* h, int32_t fi, int32_t fo, bool transpose,

@@ -186,7 +186,7 @@ hipError_t varco_launch_halo_grad(int dtype, const SpmmPlan& fwd_plan, const Spm
 
 // Elements between the rows of a product buffer of the library's own: k rounded up to whole 16-byte stores. (An odd k, as
 // compression schedules give, otherwise means element stores: 31 of 256 fp32 values per message, 1.75 million messages, 272 us
-// against %PITCH%.)
+// against 108.)
 inline int32_t varco_product_pitch(const MaskRule& rule, int elem_bytes) {
     const uint32_t unit = 16u / uint32_t(elem_bytes), up = (rule.k + unit - 1) / unit * unit;
     return int32_t(up <= rule.width ? up : rule.k);
@@ -317,6 +317,10 @@ hipError_t varco_launch_halo_transform_wgrad(const HaloTransform& h, const void*
 // slabs it wrote to g.partial (1: the result is already in C).
 bool varco_gemm_bf16_usable(const GemmArgs& g);
 hipError_t varco_launch_gemm_bf16(const GemmArgs& g, hipStream_t stream, const LaunchTag& tag, int32_t* split_used);
+// Its weight gradients (A transposed; kernels_gemm_tn_bf16.hip), and their tile and resident workgroups per compute unit.
+bool varco_gemm_tn_bf16_usable(const GemmArgs& g);
+void varco_gemm_tn_bf16_tile(int32_t m, int32_t n, int32_t* bm, int32_t* bn, int32_t* per_cu);
+hipError_t varco_launch_gemm_tn_bf16(const GemmArgs& g, hipStream_t stream, const LaunchTag& tag, int32_t* split_used);
 // fp32 operands as sums of bf16 terms on the bf16 matrix cores (kernels_gemm_split.hip); same contract as
 // the bf16 path above.
 bool varco_gemm_split_usable(const GemmArgs& g);

@@ -33,14 +33,12 @@ size_t prod_floats(const varco_ctx* ctx, int32_t layer) {
     return (size_t(ctx->net.nnz_cross) * size_t(product_pitch(ctx, layer)) * size_t(ctx->elem_bytes()) + 3) / 4;
 }
 
-// Split of a weight gradient's reduction over the arena's rows: one round of two workgroups per compute unit, at least two
+// Split of a weight gradient's reduction over the arena's rows: one round of resident workgroups, at least two
 // stages of 32 rows each. (The per-partition calls stop at eight stages: with few rows - 2,000 rows and a 32 x 8 weight
 // matrix - a handful of workgroups then walks a chain of round trips while the device idles, 16 us against 6.)
 int32_t wgrad_splits(int32_t m, int32_t n, int64_t rows, int kind, int products) {
-    const int64_t bm = kind == kGemmBf16 || (kind == kGemmF32 && n <= 64) ? 256 : 128, bn = n <= 64 ? 64 : 128;
-    const int64_t tiles = products * ((m + bm - 1) / bm) * ((n + bn - 1) / bn), step = kind == kGemmF32 ? 16 : 32;
-    const int64_t split = std::max<int64_t>(1, ((kind == kGemmF32 ? 3 : 2) * 256) / tiles);
-    return int32_t(std::min<int64_t>(split, std::max<int64_t>(1, (rows + step - 1) / step / 2)));
+    const int64_t step = kind == kGemmF32 ? 16 : 32;
+    return int32_t(std::min<int64_t>(wgrad_slots(m, n, kind, products), std::max<int64_t>(1, (rows + step - 1) / step / 2)));
 }
 
 template <typename P>
