@@ -3,14 +3,13 @@
 // caller; the library hands this kernel a bf16 copy laid out [output index][reduction index] (see
 // varco_launch_prep_weights). Weight gradients are in kernels_gemm_tn_bf16.hip.
 //
-// One 256-thread workgroup (4 wavefronts) computes a 256 x 128 tile of C (256 x 64 for outputs at most 64
-// columns wide). A wavefront owns 128 x 64 (or 64 x 64) of it as 32 x 32 blocks: at bf16 rates a wavefront
-// tile smaller than that is limited by LDS reads of its fragments, not by the matrix cores. Operand tiles of
-// 32 reduction steps are staged through LDS as rows of one output index with the reduction index contiguous
-// (80-byte row pitch: 16-byte fragment reads without bank conflicts), double-buffered against the global
-// loads of the next tile. Both operands have the reduction index contiguous in memory, so the global -> LDS copy moves
-// 8 (or 4) elements at a time unchanged. The ReLU mask of the backward pass is applied when a tile is written to LDS, the
-// activation in the epilogue.
+// A workgroup of 8 wavefronts computes a 256 x 256 tile of C in stages of 64 reduction steps (rows of whole 128-byte lines
+// from memory), or one of 4 wavefronts a 256 x 128 or 256 x 64 tile in stages of 32. A wavefront owns 128 x 64 (or 64 x 64) of
+// it as 32 x 32 blocks: at bf16 rates a wavefront tile smaller than that is limited by LDS reads of its fragments, not by
+// the matrix cores. Operands are staged through LDS as rows of one output index with the reduction index contiguous (16
+// bytes of padding per row: fragment reads without bank conflicts), double-buffered against the global loads of the next
+// stage, copied 8 (or 4) elements at a time unchanged. The ReLU mask of the backward pass is applied when a stage is written
+// to LDS, the activation in the epilogue.
 #include <type_traits>
 
 #include "elem.h"
@@ -18,9 +17,6 @@
 
 namespace {
 
-constexpr int BK = 32;
-constexpr int kThreads = 256;
-constexpr int kPitch = BK + 8;   // bf16 elements per LDS row (80 bytes)
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -54,10 +50,10 @@ __device__ __forceinline__ uint32_t gate_pair(uint32_t v, uint32_t g) {
 // One operand's share of a stage: ROWS rows x BK reduction steps in chunks of CH elements. A thread keeps its place in the
 // stage, so its byte offsets into the operand are formed once and the stage's base stays in scalar registers. Rows past the
 // matrix repeat its last one (their results are never stored); reduction steps past the end are zero.
-template <int ROWS, int CH, bool GATE>
+template <int ROWS, int CH, bool GATE, int BK, int kThreads>
 struct RowSlab {
     using W = std::conditional_t<CH == 8, uint4, uint2>;
-    static constexpr int PER_ROW = BK / CH;
+    static constexpr int PER_ROW = BK / CH, kPitch = BK + 8;
     static constexpr int N = ROWS * PER_ROW / kThreads;
     W v[N], g[GATE ? N : 1];
     uint32_t at[N];
@@ -99,9 +95,7 @@ struct RowSlab {
     }
 };
 
-__device__ __forceinline__ bf16x8 fragment(const uint16_t* s, int row, int koff) {
-    return __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(s + row * kPitch + koff));
-}
+__device__ __forceinline__ bf16x8 fragment(const uint16_t* s) { return __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(s)); }
 
 // WM x WN wavefronts, each TMB x TNB blocks of 32 x 32. A_CH: elements per global load of A (B is the library's own padded
 // weight copy, always 8). GATE masks A.
@@ -109,11 +103,12 @@ __device__ __forceinline__ bf16x8 fragment(const uint16_t* s, int row, int koff)
 // in a lane: they are rounded in pairs, put through the wavefront's own part of LDS and stored 16 bytes per lane, whole lines
 // at a time. Stored from the registers, 2 bytes per lane, the 128 store instructions of a thread kept the vector memory unit
 // busy for as long as all matrix instructions of a K = 512 tile take.
-// 2,449,029 rows, 512 x 512: 2.10 ms before, %NT% now; with a mask 2.86, %NTG% now.
-template <int WM, int WN, int TMB, int TNB, int A_CH, bool GATE>
-__global__ __launch_bounds__(kThreads, 2) void gemm_bf16_kernel(GemmDev g) {
-    constexpr int BM = 32 * TMB * WM, BN = 32 * TNB * WN;
-    __shared__ __attribute__((aligned(16))) uint16_t lds[2 * (BM + BN) * kPitch];
+// 169,343 rows, 512 x 512, masked: 208 us with the 256 x 128 tile, whose four column tiles read A and the mask four times
+// through L2 in half lines (18 TB/s), 184 with 256 x 256.
+template <int WM, int WN, int TMB, int TNB, int BK, int A_CH, bool GATE>
+__global__ __launch_bounds__(WM * WN * 64, 2) void gemm_bf16_kernel(GemmDev g) {
+    constexpr int BM = 32 * TMB * WM, BN = 32 * TNB * WN, kThreads = WM * WN * 64, kPitch = BK + 8;
+    extern __shared__ __attribute__((aligned(16))) uint16_t lds[];       // two stages of A, then of B
     auto sa = [&](int buf) { return lds + buf * (BM * kPitch); };
     auto sb = [&](int buf) { return lds + 2 * BM * kPitch + buf * (BN * kPitch); };
 
@@ -140,8 +135,8 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_bf16_kernel(GemmDev g) {
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
 
-    RowSlab<BM, A_CH, GATE> ra;
-    RowSlab<BN, 8, false> rb;
+    RowSlab<BM, A_CH, GATE, BK, kThreads> ra;
+    RowSlab<BN, 8, false, BK, kThreads> rb;
     const uint16_t *pa = nullptr, *pg = nullptr, *pb = nullptr;     // the next stage's bases, and what is left of its product's steps
     int32_t left = 0;
     auto enter = [&](const OperandDev& a, const uint16_t* b, int64_t ldb, int32_t steps) {
@@ -177,9 +172,9 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_bf16_kernel(GemmDev g) {
             const int koff = s * 16 + lk * 8;
             bf16x8 fa[TMB], fb[TNB];
 #pragma unroll
-            for (int i = 0; i < TMB; ++i) fa[i] = fragment(sa(buf), wm + i * 32 + lrow, koff);
+            for (int i = 0; i < TMB; ++i) fa[i] = fragment(sa(buf) + (wm + i * 32 + lrow) * kPitch + koff);
 #pragma unroll
-            for (int j = 0; j < TNB; ++j) fb[j] = fragment(sb(buf), wn + j * 32 + lrow, koff);
+            for (int j = 0; j < TNB; ++j) fb[j] = fragment(sb(buf) + (wn + j * 32 + lrow) * kPitch + koff);
 #pragma unroll
             for (int i = 0; i < TMB; ++i)
 #pragma unroll
@@ -266,8 +261,9 @@ bool varco_gemm_bf16_usable(const GemmArgs& ga) {
 
 hipError_t varco_launch_gemm_bf16(const GemmArgs& ga, hipStream_t stream, const LaunchTag& tag, int32_t* split_used) {
     if (ga.a.transposed) return varco_launch_gemm_tn_bf16(ga, stream, tag, split_used);
-    const bool narrow = ga.n <= 64;
-    const int bm = 256, bn = narrow ? 64 : 128;
+    // 256 x 256 where its tiles fill the device and pad no more columns than 256 x 128
+    const int64_t wide = int64_t((ga.m + 255) / 256) * ((ga.n + 255) / 256);
+    const int bm = 256, bn = ga.n <= 64 ? 64 : wide >= 256 && (ga.n + 255) / 256 * 2 == (ga.n + 127) / 128 ? 256 : 128;
     auto chunk8 = [](const GemmOperand& o, int32_t k) {
         return !o.ptr || (aligned_to(o.ptr, 16) && aligned_to(o.gate, 16) && o.ld % 8 == 0 && k % 8 == 0);
     };
@@ -296,17 +292,33 @@ hipError_t varco_launch_gemm_bf16(const GemmArgs& ga, hipStream_t stream, const 
     const dim3 grid{unsigned(blocks)};
     *split_used = 1;
 
-    tag.begin(stream);
-    with_flag(narrow, [&](auto nr) {
+    hipError_t err = hipSuccess;
+    auto launch = [&](auto wm, auto wn, auto tmb, auto tnb, auto bk) {
+        constexpr int WM = decltype(wm)::value, WN = decltype(wn)::value, TMB = decltype(tmb)::value, TNB = decltype(tnb)::value;
+        constexpr int BK = decltype(bk)::value;
+        constexpr size_t bytes = size_t(2) * 32 * (TMB * WM + TNB * WN) * (BK + 8) * 2;
         with_flag(gate, [&](auto gt) {
-            constexpr bool NR = decltype(nr)::value, GT = decltype(gt)::value;
-            constexpr int WM = NR ? 4 : 2, WN = NR ? 1 : 2, TMB = NR ? 2 : 4, TNB = 2;
-            if (a8)
-                hipLaunchKernelGGL((gemm_bf16_kernel<WM, WN, TMB, TNB, 8, GT>), grid, dim3(kThreads), 0, stream, g);
-            else
-                hipLaunchKernelGGL((gemm_bf16_kernel<WM, WN, TMB, TNB, 4, GT>), grid, dim3(kThreads), 0, stream, g);
+            with_flag(a8, [&](auto c8) {
+                const auto kernel = gemm_bf16_kernel<WM, WN, TMB, TNB, BK, decltype(c8)::value ? 8 : 4, decltype(gt)::value>;
+                if (bytes > 64 * 1024)
+                    err = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, int(bytes));
+                if (err != hipSuccess) return;
+                tag.begin(stream);
+                hipLaunchKernelGGL(kernel, grid, dim3(WM * WN * 64), bytes, stream, g);
+                tag.end(stream);
+            });
         });
-    });
-    tag.end(stream);
-    return hipGetLastError();
+    };
+    using I1 = std::integral_constant<int, 1>;
+    using I2 = std::integral_constant<int, 2>;
+    using I4 = std::integral_constant<int, 4>;
+    using I32 = std::integral_constant<int, 32>;
+    using I64 = std::integral_constant<int, 64>;
+    if (bn == 256)
+        launch(I2{}, I4{}, I4{}, I2{}, I64{});
+    else if (bn == 128)
+        launch(I2{}, I2{}, I4{}, I2{}, I32{});
+    else
+        launch(I4{}, I1{}, I2{}, I2{}, I32{});
+    return err != hipSuccess ? err : hipGetLastError();
 }

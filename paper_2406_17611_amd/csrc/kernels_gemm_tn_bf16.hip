@@ -9,7 +9,7 @@
 // Row pitch in LDS: 64 bytes more than a multiple of 256, so that the four rows that a group of lanes reads start in four
 // different quarters of the banks.
 // Bound by reading A, B and the mask once (the tiles of one slab of rows run on one XCD and share them through its L2).
-// 169,343 rows, 512 x 512, masked: 163 us (540 TFLOP/s); 2,449,029 rows: 1.93 ms, where that kernel took 3.7.
+// 169,343 rows, 512 x 512, masked: 163 us with stages of 32 rows, 142 with 64 (620 TFLOP/s); that kernel took 270.
 #include <algorithm>
 #include <type_traits>
 
@@ -18,7 +18,6 @@
 
 namespace {
 
-constexpr int BK = 32;
 constexpr int kThreads = 512;
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
@@ -26,6 +25,10 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef short shortx4 __attribute__((ext_vector_type(4)));
 typedef uint32_t words4 __attribute__((ext_vector_type(4)));
 typedef uint32_t words2 __attribute__((ext_vector_type(2)));
+
+// Rows per stage: 32, and 64 for the 256 x 256 tile, whose single workgroup per compute unit has nothing else in flight while
+// it waits for a stage.
+constexpr int stage_rows(int bm, int bn) { return bm == 256 && bn == 256 ? 64 : 32; }
 
 struct TnDev {
     int32_t m, n, k;
@@ -50,7 +53,7 @@ __device__ __forceinline__ uint32_t gate_pair(uint32_t v, uint32_t g) {
 }
 
 // One operand's share of a stage: W columns x BK rows in chunks of CH elements, dealt to the threads row by row.
-template <int W, int CH, bool GATE>
+template <int W, int CH, bool GATE, int BK>
 struct Slab {
     using V = std::conditional_t<CH == 8, words4, words2>;
     static constexpr int PER_ROW = W / CH, TOTAL = PER_ROW * BK, N = (TOTAL + kThreads - 1) / kThreads, ROWS = kThreads / PER_ROW;
@@ -92,6 +95,7 @@ struct Slab {
 
 // B read element by element (64 columns at most, never masked): rows that are not 8-byte aligned, as the 47 class columns of a
 // last layer.
+template <int BK>
 struct ElementSlab {
     static constexpr int N = 64 * BK / kThreads, PITCH = 64 * 2 + 64;
     uint16_t v[N];
@@ -113,8 +117,8 @@ struct ElementSlab {
             if (row[h] < BK) *reinterpret_cast<uint16_t*>(s + row[h] * PITCH + col[h] * 2) = k0 + row[h] < kmax ? v[h] : uint16_t(0);
     }
 };
-template <int W, int CH, bool GATE>
-using SlabOf = std::conditional_t<CH == 1, ElementSlab, Slab<W, CH == 1 ? 8 : CH, GATE>>;
+template <int W, int CH, bool GATE, int BK>
+using SlabOf = std::conditional_t<CH == 1, ElementSlab<BK>, Slab<W, CH == 1 ? 8 : CH, GATE, BK>>;
 
 // Fragment of 32 columns x 16 rows whose first column's element of row 0 (this lane's share of the block) is at LDS byte `at`.
 template <int PITCH>
@@ -129,9 +133,9 @@ __device__ __forceinline__ bf16x8 fragment(uint32_t at) {
 template <int WM, int WN, int TMB, int TNB, int ACH, int BCH, bool GATE>
 __global__ __launch_bounds__(kThreads, TMB * TNB > 4 ? 2 : 4) void gemm_tn_bf16_kernel(TnDev g) {
     static_assert(WM * WN * 64 == kThreads, "");
-    constexpr int BM = 32 * TMB * WM, BN = 32 * TNB * WN;
-    using SA = SlabOf<BM, ACH, false>;
-    using SB = SlabOf<BN, BCH, GATE>;
+    constexpr int BM = 32 * TMB * WM, BN = 32 * TNB * WN, BK = stage_rows(BM, BN);
+    using SA = SlabOf<BM, ACH, false, BK>;
+    using SB = SlabOf<BN, BCH, GATE, BK>;
     extern __shared__ __attribute__((aligned(16))) char lds[];          // two buffers of BK rows of A, then of B
     constexpr int kA = BK * SA::PITCH, kB = BK * SB::PITCH;
 
@@ -255,7 +259,7 @@ hipError_t varco_launch_gemm_tn_bf16(const GemmArgs& ga, hipStream_t stream, con
     g.lda = ga.a.ld, g.ldb = ga.b.ld;
     g.c = static_cast<float*>(ga.c), g.c_dual = static_cast<float*>(ga.c_dual), g.ldc = ga.ldc;
     g.accumulate = ga.accumulate ? 1 : 0;
-    const int32_t stages = (ga.k + BK - 1) / BK;
+    const int32_t rows = stage_rows(bm, bn), stages = (ga.k + rows - 1) / rows;
     int32_t split = std::max(1, std::min(ga.split_k, stages));
     g.stages_per_split = (stages + split - 1) / split;
     split = (stages + g.stages_per_split - 1) / g.stages_per_split;
@@ -275,7 +279,8 @@ hipError_t varco_launch_gemm_tn_bf16(const GemmArgs& ga, hipStream_t stream, con
         constexpr int WM = decltype(wm)::value, WN = decltype(wn)::value, TMB = decltype(tmb)::value, TNB = decltype(tnb)::value;
         constexpr int ACH = decltype(ach)::value, BCH = decltype(bch)::value;
         constexpr bool G = decltype(gated)::value;
-        const size_t bytes = size_t(2 * BK) * (SlabOf<32 * TMB * WM, ACH, false>::PITCH + SlabOf<32 * TNB * WN, BCH, G>::PITCH);
+        constexpr int BK = stage_rows(32 * TMB * WM, 32 * TNB * WN);
+        const size_t bytes = size_t(2 * BK) * (SlabOf<32 * TMB * WM, ACH, false, BK>::PITCH + SlabOf<32 * TNB * WN, BCH, G, BK>::PITCH);
         const auto kernel = gemm_tn_bf16_kernel<WM, WN, TMB, TNB, ACH, BCH, G>;
         if (bytes > 64 * 1024) {
             err = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, int(bytes));
