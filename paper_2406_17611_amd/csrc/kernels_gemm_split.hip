@@ -20,6 +20,7 @@
 //        two consecutive nodes of a column together, which yields the transposed (node index contiguous) words
 //        directly; it writes four 16-byte LDS rows per plane. Half the threads serve A, half B.
 // The ReLU mask of the backward pass is applied before the expansion, the activation in the epilogue.
+#include <algorithm>
 #include <type_traits>
 
 #include "elem.h"
@@ -530,29 +531,19 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_split_kernel(SplitGemm g) {
 // ---------------------------------------------------------------------------------------------------------
 // Short reductions on the bf16 matrix units: C (+)= A B^T with at most 64 reduction steps and densely stored
 // rows of A (the input gradient of the last layer: the reduction runs over the classes). Rows of, say, 47
-// elements are not 16-byte aligned, so a workgroup copies its 128 rows of A, one contiguous range of memory,
-// into LDS with 16-byte loads (masked and widened to fp32 on the way; the row pitch stays k). Each wavefront
-// owns 64 columns of C: their weights, expanded into TERMS bf16 terms, sit in registers as matrix operands for
-// the whole kernel; for each block of 32 rows the wavefront reads its 8 values per 16 reduction steps from LDS,
-// expands them in registers and issues the products. With fp32 matrix instructions (the previous form of this
-// kernel, still used when the context asks for them) the same product took 2.7 times the matrix-unit time and
-// was bound by it; this form is bound by writing C. TERMS = 1: bf16 storage (the values are bf16 already; the
-// weights are rounded to bf16 as for the other products of that storage type).
-constexpr int kShortRows = 128;
+// elements are not 16-byte aligned, so a workgroup takes tiles of 64 rows of A, each one contiguous range of memory,
+// with 16-byte loads, masks the values, expands them into TERMS bf16 terms once and writes them to LDS as rows of matrix
+// operands (16 bytes of padding per row). Each wavefront owns 64 columns of C: their weights, expanded alike, sit in registers
+// for the whole kernel, so workgroups are persistent over the tiles, and the next tile's range is requested before the
+// current one is multiplied. The blocks are formed transposed (weights as the first matrix operand): a lane then holds four
+// consecutive columns of a row, and a block of 32 rows leaves through LDS in whole lines.
+// Bound by writing C. (One tile of 128 rows per workgroup, its values expanded by each wavefront from fp32 rows in LDS, which
+// lay in few banks when the number of classes was a multiple of 8: 169,343 x 256 from 40 classes 77 us, 57 now; 2,449,029
+// x 2 x 256 from 47: 1.96 ms, 1.40 now.)
+// With fp32 matrix instructions (still used when the context asks for them) the product is bound by those. TERMS = 1: bf16
+// storage (the values are bf16 already; the weights are rounded to bf16 as for the other products of that storage type).
+constexpr int kShortRows = 64;
 constexpr int kEpiPitch = 68;      // floats per row of the epilogue's LDS block (64 + 4: rows start on different banks)
-
-template <typename T>
-__device__ __forceinline__ void load_chunk16(const T* p, float (&x)[16 / sizeof(T)]) {
-    if constexpr (sizeof(T) == 4) {
-        const float4 v = *reinterpret_cast<const float4*>(p);
-        x[0] = v.x, x[1] = v.y, x[2] = v.z, x[3] = v.w;
-    } else {
-        const uint4 v = *reinterpret_cast<const uint4*>(p);
-        const uint32_t u[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-        for (int i = 0; i < 4; ++i) x[2 * i] = __uint_as_float(u[i] << 16), x[2 * i + 1] = __uint_as_float(u[i] & 0xFFFF0000u);
-    }
-}
 
 // Eight consecutive values as TERMS bf16 fragments.
 template <int TERMS>
@@ -563,10 +554,6 @@ __device__ __forceinline__ void expand8(const float (&x)[8], bf16x8 (&f)[3]) {
 #pragma unroll
     for (int p = 0; p < TERMS; ++p) f[p] = __builtin_bit_cast(bf16x8, make_uint4(w[0][p], w[1][p], w[2][p], w[3][p]));
 }
-template <>
-__device__ __forceinline__ void expand8<1>(const float (&x)[8], bf16x8 (&f)[3]) {
-    f[0] = __builtin_bit_cast(bf16x8, make_uint4(pack_bf16(x[0], x[1]), pack_bf16(x[2], x[3]), pack_bf16(x[4], x[5]), pack_bf16(x[6], x[7])));
-}
 
 template <typename T, int KS, bool GATE, int TERMS>
 __global__ __launch_bounds__(kThreads, 2) void gemm_short_k_kernel(const T* __restrict__ a, const T* __restrict__ gate,
@@ -576,12 +563,15 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_short_k_kernel(const T* __re
                                                                    T* __restrict__ c_dual) {
     if (blockIdx.z == 1) b = b_dual, c = c_dual;                  // second product of the same A
     constexpr int VE = 16 / int(sizeof(T));                       // elements per 16-byte load
-    __shared__ __attribute__((aligned(16))) float tile[kShortRows * 16 * KS + 64];
+    constexpr int kRow = 16 * KS + 8, kPlane = kShortRows * kRow; // elements per row and per term of the tile
+    constexpr int N = (kShortRows * 16 * KS / VE + 1 + kThreads - 1) / kThreads;
+    __shared__ __attribute__((aligned(16))) uint16_t tile[TERMS * kPlane];
     __shared__ __attribute__((aligned(16))) float epi[4 * 32 * kEpiPitch];      // a 32 x 64 block per wavefront
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int lcol = lane & 31, lk = lane >> 5;
-    const int32_t r0 = blockIdx.x * kShortRows, rows = min(kShortRows, m - r0);
-    const int32_t c0 = blockIdx.y * 256 + wave * 64;
+    // 64 columns to a wavefront; when there are fewer than four such groups, the blocks of 32 rows are dealt as well
+    const int groups = n - int32_t(blockIdx.y) * 256 > 128 ? 4 : n - int32_t(blockIdx.y) * 256 > 64 ? 2 : 1;
+    const int32_t c0 = blockIdx.y * 256 + wave % groups * 64;
     // rows of C can be written 4 elements at a time: whole vectors inside the matrix, aligned
     const bool vec_out = n % 4 == 0 && ldc % 4 == 0 && (reinterpret_cast<uintptr_t>(c) & (4 * sizeof(T) - 1)) == 0;
 
@@ -601,120 +591,150 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_short_k_kernel(const T* __re
             expand8<TERMS>(x, w[cb][s2]);
         }
     }
+    for (int i = threadIdx.x; i < TERMS * kPlane / 8; i += kThreads) reinterpret_cast<uint4*>(tile)[i] = make_uint4(0u, 0u, 0u, 0u);
 
-    // the rows of this tile as one contiguous range, read in 16-byte chunks on 16-byte boundaries (the range
-    // may start `skew` elements into a chunk; A and its mask have the same skew, checked by the launcher)
-    const int32_t n_el = rows * k;
-    const T* src = a + int64_t(r0) * k;
-    const T* gsrc = GATE ? gate + int64_t(r0) * k : nullptr;
-    const int32_t skew = int32_t((reinterpret_cast<uintptr_t>(src) & 15u) / sizeof(T));
-    for (int32_t e0 = threadIdx.x * VE - skew; e0 < n_el; e0 += kThreads * VE) {
-        float x[VE], y[VE];
-        if (e0 >= 0 && e0 + VE <= n_el) {
-            load_chunk16<T>(src + e0, x);
-            if (GATE) load_chunk16<T>(gsrc + e0, y);
-        } else {
+    // A tile is read in 16-byte chunks on 16-byte boundaries (its range may start `skew` elements into a chunk; a tile is a
+    // multiple of 16 bytes long, so every tile has the same skew, and so has the mask, checked by the launcher). A thread's
+    // chunks are at the same places of every tile.
+    const int32_t skew = int32_t((reinterpret_cast<uintptr_t>(a) & 15u) / sizeof(T));
+    int32_t row[N], kk0[N];
 #pragma unroll
-            for (int i = 0; i < VE; ++i) {
-                const bool in = e0 + i >= 0 && e0 + i < n_el;
-                x[i] = in ? Elem<T>::load(src + e0 + i) : 0.f;
-                if (GATE) y[i] = in ? Elem<T>::load(gsrc + e0 + i) : 0.f;
-            }
-        }
-#pragma unroll
-        for (int i = 0; i < VE; ++i) {
-            if (GATE) x[i] = y[i] > 0.f ? x[i] : 0.f;
-            if (e0 + i >= 0 && e0 + i < n_el) tile[e0 + i] = x[i];
-        }
+    for (int h = 0; h < N; ++h) {
+        const int32_t e = max((int32_t(threadIdx.x) + h * kThreads) * VE - skew, 0);
+        row[h] = e / k, kk0[h] = e - row[h] * k;
     }
-    __syncthreads();
-    if (c0 >= n) return;               // no barrier follows
-
-    for (int rb = 0; rb * 32 < rows; ++rb) {
-        const int32_t lrow = min(rb * 32 + lcol, rows - 1);          // rows past the end repeat the last one; never stored
-        floatx16 acc[2];
+    uint4 raw[N], graw[GATE ? N : 1];
+    const int32_t n_tiles = (m + kShortRows - 1) / kShortRows;
+    auto chunk = [&](const T* src, int32_t e0, int32_t n_el) {
+        if (e0 >= 0 && e0 + VE <= n_el) return *reinterpret_cast<const uint4*>(src + e0);
+        uint32_t u[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
-        for (int cb = 0; cb < 2; ++cb)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[cb][v] = 0.f;
-#pragma unroll
-        for (int s2 = 0; s2 < KS; ++s2) {
-            float x[8];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const int kk = 16 * s2 + 8 * lk + e;
-                const float v = tile[lrow * k + kk];                 // in bounds: the tile has 64 spare floats
-                x[e] = kk < k ? v : 0.f;
+        for (int i = 0; i < VE; ++i)
+            if (e0 + i >= 0 && e0 + i < n_el) {
+                if constexpr (sizeof(T) == 4)
+                    u[i] = reinterpret_cast<const uint32_t*>(src)[e0 + i];
+                else
+                    u[i >> 1] |= uint32_t(reinterpret_cast<const uint16_t*>(src)[e0 + i]) << (16 * (i & 1));
             }
-            bf16x8 fa[3];
-            expand8<TERMS>(x, fa);
+        return make_uint4(u[0], u[1], u[2], u[3]);
+    };
+    auto load = [&](int32_t t) {
+        const int32_t r0 = t * kShortRows, n_el = min(kShortRows, m - r0) * k;
 #pragma unroll
-            for (int cb = 0; cb < 2; ++cb) {
-                auto mul = [&](int pa, int pb) {
-                    acc[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[pa], w[cb][s2][pb], acc[cb], 0, 0, 0);
-                };
-                mul(0, 0);
-                if constexpr (TERMS >= 2) {
-                    mul(0, 1);
-                    mul(1, 0);
-                }
-                if constexpr (TERMS == 3) {
-                    mul(1, 1);
-                    mul(0, 2);
-                    mul(2, 0);
-                }
+        for (int h = 0; h < N; ++h) {
+            const int32_t e0 = (int32_t(threadIdx.x) + h * kThreads) * VE - skew;
+            if (e0 < n_el) {
+                raw[h] = chunk(a + int64_t(r0) * k, e0, n_el);
+                if constexpr (GATE) graw[h] = chunk(gate + int64_t(r0) * k, e0, n_el);
             }
         }
-        // accumulator register v of a lane is element (8 * (v / 4) + 4 * (lane / 32) + v % 4, lane % 32): a lane holds
-        // one column. Stored that way a wavefront needs 32 store instructions of 256 bytes each per block of rows,
-        // and the kernel is bound by issuing them; so the block goes through LDS once and leaves as 4-element
-        // vectors along the rows (8 stores of 1 KB; the old values of C, when added to, come in the same way).
-        if (vec_out) {
+    };
+    auto value = [](const uint4& v, int i) {
+        const uint32_t u[4] = {v.x, v.y, v.z, v.w};
+        if constexpr (sizeof(T) == 4) return __uint_as_float(u[i]);
+        return __uint_as_float((i & 1) ? (u[i >> 1] & 0xFFFF0000u) : (u[i >> 1] << 16));
+    };
+
+    int32_t t = blockIdx.x;
+    if (t < n_tiles) load(t);
+    __syncthreads();
+    for (; t < n_tiles; t += gridDim.x) {
+        const int32_t r0 = t * kShortRows, rows = min(kShortRows, m - r0), n_el = rows * k;
+#pragma unroll
+        for (int h = 0; h < N; ++h) {
+            const int32_t e0 = (int32_t(threadIdx.x) + h * kThreads) * VE - skew;
+            uint16_t* at = tile + row[h] * kRow + kk0[h];
+            int32_t kk = kk0[h];
+#pragma unroll
+            for (int i = 0; i < VE; i += 2) {
+                float x0 = value(raw[h], i), x1 = value(raw[h], i + 1);
+                if constexpr (GATE) x0 = value(graw[h], i) > 0.f ? x0 : 0.f, x1 = value(graw[h], i + 1) > 0.f ? x1 : 0.f;
+                uint32_t o[TERMS];
+                expand_pair<TERMS>(x0, x1, o);
+#pragma unroll
+                for (int q = 0; q < 2; ++q)
+                    if (e0 + i + q >= 0 && e0 + i + q < n_el) {
+#pragma unroll
+                        for (int p = 0; p < TERMS; ++p) at[p * kPlane] = uint16_t(o[p] >> (16 * q));
+                        ++at, ++kk;
+                        if (kk == k) kk = 0, at += kRow - k;
+                    }
+            }
+        }
+        __syncthreads();
+        if (t + int32_t(gridDim.x) < n_tiles) load(t + gridDim.x);
+        for (int rb = wave / groups; rb * 32 < rows && c0 < n; rb += 4 / groups) {
+            floatx16 acc[2];
+#pragma unroll
+            for (int cb = 0; cb < 2; ++cb)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[cb][v] = 0.f;
+#pragma unroll
+            for (int s2 = 0; s2 < KS; ++s2) {
+                bf16x8 fa[3];
+#pragma unroll
+                for (int p = 0; p < TERMS; ++p)
+                    fa[p] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(tile + p * kPlane + (rb * 32 + lcol) * kRow + 16 * s2 + 8 * lk));
+#pragma unroll
+                for (int cb = 0; cb < 2; ++cb) {
+                    auto mul = [&](int pa, int pb) {
+                        acc[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[cb][s2][pb], fa[pa], acc[cb], 0, 0, 0);
+                    };
+                    mul(0, 0);
+                    if constexpr (TERMS >= 2) {
+                        mul(0, 1);
+                        mul(1, 0);
+                    }
+                    if constexpr (TERMS == 3) {
+                        mul(1, 1);
+                        mul(0, 2);
+                        mul(2, 0);
+                    }
+                }
+            }
+            // accumulator register v of a lane is element (row lane % 32, column 8 * (v / 4) + 4 * (lane / 32) + v % 4)
             float* ep = epi + wave * (32 * kEpiPitch);
 #pragma unroll
             for (int cb = 0; cb < 2; ++cb)
 #pragma unroll
-                for (int v = 0; v < 16; ++v) ep[(8 * (v >> 2) + 4 * lk + (v & 3)) * kEpiPitch + cb * 32 + lcol] = acc[cb][v];
-            // same wavefront writes and reads: no barrier, the LDS operations of a wavefront complete in order
-            const int er = lane >> 4, ec = (lane & 15) * 4;
-            float4 old[8];
+                for (int q = 0; q < 4; ++q)
+                    *reinterpret_cast<float4*>(ep + lcol * kEpiPitch + cb * 32 + 8 * q + 4 * lk) =
+                        make_float4(acc[cb][4 * q], acc[cb][4 * q + 1], acc[cb][4 * q + 2], acc[cb][4 * q + 3]);
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            if (vec_out) {
+                const int er = lane >> 4, ec = (lane & 15) * 4;
+                float4 old[8];
 #pragma unroll
-            for (int i = 0; i < 8; ++i) old[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (accumulate) {
+                for (int i = 0; i < 8; ++i) old[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+                if (accumulate) {
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) {
+                        const int32_t r = min(rb * 32 + er + 4 * i, rows - 1);
+                        if (c0 + ec < n) old[i] = Elem<T>::load4(c + int64_t(r0 + r) * ldc + c0 + ec);
+                    }
+                }
 #pragma unroll
                 for (int i = 0; i < 8; ++i) {
-                    const int32_t row = min(rb * 32 + er + 4 * i, rows - 1);
-                    if (c0 + ec < n) old[i] = Elem<T>::load4(c + int64_t(r0 + row) * ldc + c0 + ec);
+                    const int32_t r = rb * 32 + er + 4 * i;
+                    float4 x = *reinterpret_cast<const float4*>(ep + (er + 4 * i) * kEpiPitch + ec);
+                    x.x += old[i].x, x.y += old[i].y, x.z += old[i].z, x.w += old[i].w;
+                    if (r < rows && c0 + ec < n) Elem<T>::store4(c + int64_t(r0 + r) * ldc + c0 + ec, x);
+                }
+            } else if (c0 + lane < n) {
+                T* out = c + int64_t(r0 + rb * 32) * ldc + c0 + lane;
+                const int32_t here = min(32, rows - rb * 32);
+                for (int i0 = 0; i0 < here; i0 += 8) {
+                    float old[8];
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) old[i] = accumulate ? Elem<T>::load(out + int64_t(min(i0 + i, here - 1)) * ldc) : 0.f;
+#pragma unroll
+                    for (int i = 0; i < 8; ++i)
+                        if (i0 + i < here) Elem<T>::store(out + int64_t(i0 + i) * ldc, ep[(i0 + i) * kEpiPitch + lane] + old[i]);
                 }
             }
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const int32_t row = rb * 32 + er + 4 * i;
-                float4 x = *reinterpret_cast<const float4*>(ep + (er + 4 * i) * kEpiPitch + ec);
-                x.x += old[i].x, x.y += old[i].y, x.z += old[i].z, x.w += old[i].w;
-                if (row < rows && c0 + ec < n) Elem<T>::store4(c + int64_t(r0 + row) * ldc + c0 + ec, x);
-            }
-            continue;
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         }
-#pragma unroll
-        for (int cb = 0; cb < 2; ++cb) {
-            const int32_t col = c0 + cb * 32 + lcol;
-            const int32_t row0 = rb * 32 + 4 * lk;
-            float old[16];
-#pragma unroll
-            for (int v = 0; v < 16; ++v) old[v] = 0.f;
-            if (accumulate) {   // all loads issued before the first use, from clamped (always valid) addresses
-                const T* cbase = c + min(col, n - 1);
-#pragma unroll
-                for (int v = 0; v < 16; ++v)
-                    old[v] = Elem<T>::load(cbase + int64_t(r0 + min(row0 + 8 * (v >> 2) + (v & 3), rows - 1)) * ldc);
-            }
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int32_t row = row0 + 8 * (v >> 2) + (v & 3);
-                if (row < rows && col < n) Elem<T>::store(c + int64_t(r0 + row) * ldc + col, acc[cb][v] + old[v]);
-            }
-        }
+        __syncthreads();               // the tile has been read: the next one may overwrite it
     }
 }
 
@@ -801,7 +821,8 @@ struct TypeTag {
 
 // Short reductions (see gemm_short_k_kernel): terms = 1 for bf16 storage, 2 or 3 for fp32 storage.
 hipError_t varco_launch_gemm_short_k(const GemmArgs& ga, int terms, hipStream_t stream) {
-    const dim3 grid(unsigned((ga.m + kShortRows - 1) / kShortRows), unsigned((ga.n + 255) / 256), ga.c_dual ? 2 : 1);
+    const int64_t tiles = (ga.m + kShortRows - 1) / kShortRows, others = int64_t((ga.n + 255) / 256) * (ga.c_dual ? 2 : 1);
+    const dim3 grid(unsigned(std::min<int64_t>(tiles, std::max<int64_t>(1, 512 / others))), unsigned((ga.n + 255) / 256), ga.c_dual ? 2 : 1);
     const int ks = (ga.k + 15) / 16;
     if (ks < 1 || ks > 4) return hipErrorInvalidValue;
     auto go = [&](auto type, auto ksc, auto gt, auto tc) {
