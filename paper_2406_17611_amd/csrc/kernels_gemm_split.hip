@@ -95,11 +95,25 @@ template <typename T>
 __device__ __forceinline__ T load_at(const void* base, uint32_t byte_offset) {
     return *reinterpret_cast<const T*>(static_cast<const char*>(base) + byte_offset);
 }
+// Four floats from any address of a float (the device loads 16 bytes from there just as well).
+__device__ __forceinline__ float4 load4_at(const void* base, uint32_t byte_offset) {
+    typedef float any4 __attribute__((ext_vector_type(4), aligned(4)));
+    const any4 v = *reinterpret_cast<const any4*>(static_cast<const char*>(base) + byte_offset);
+    return make_float4(v[0], v[1], v[2], v[3]);
+}
+// A group of four that crosses the end of its row is loaded from four elements before the end and moved up by `by` (1 to 3)
+// elements; what follows the end is zero.
+__device__ __forceinline__ float4 moved_up(float4 x, int by) {
+    if (by == 1) return make_float4(x.y, x.z, x.w, 0.f);
+    if (by == 2) return make_float4(x.z, x.w, 0.f, 0.f);
+    return make_float4(x.w, 0.f, 0.f, 0.f);
+}
 
 // ---- fp32 operand with the reduction index contiguous: chunks of CH floats ----
 // Addresses are a per-tile base (uniform) plus a 32-bit offset per chunk that does not change along the
 // reduction. Rows beyond the matrix are clamped to its last row (their results are never stored); chunks
-// beyond the reduction length re-read the tile's first chunk of the same row, and meet zeros in B.
+// beyond the reduction length re-read the tile's first chunk of the same row, and meet zeros in B. Rows need no alignment
+// and (chunks of 4) any length from 4 on: see moved_up.
 template <int ROWS, int CH, bool GATE>
 struct RowRegs {
     static constexpr int PER_ROW = BK / CH;
@@ -112,13 +126,13 @@ template <int ROWS, int CH>
 struct RowPlan {
     static constexpr int PER_ROW = BK / CH;
     static constexpr int N = ROWS * PER_ROW / kThreads;
-    uint32_t off[N];     // bytes from the tile base
+    uint32_t off[N];     // bytes from 4 floats before the tile base: a group moved up may start before it
     __device__ __forceinline__ void init(int tid, int32_t i0, int32_t extent, int64_t ld) {
 #pragma unroll
         for (int h = 0; h < N; ++h) {
             const int c = tid + h * kThreads;
             const int32_t r = min(tile_row(c / PER_ROW), extent - 1 - i0);
-            off[h] = uint32_t(r * ld + (c % PER_ROW) * CH) * 4u;
+            off[h] = uint32_t(r * ld + (c % PER_ROW) * CH + 4) * 4u;
         }
     }
 };
@@ -130,18 +144,20 @@ __device__ __forceinline__ void load_rows(int tid, const float* base, const floa
 #pragma unroll
     for (int h = 0; h < R::N; ++h) {
         const int kc = ((tid + h * kThreads) % R::PER_ROW) * CH;
-        const uint32_t off = kc < k_left ? plan.off[h] : plan.off[h] - uint32_t(kc) * 4u;   // k_left is a multiple of CH
+        uint32_t off = kc < k_left ? plan.off[h] : plan.off[h] - uint32_t(kc) * 4u;
+        if (CH == 4 && kc < k_left && kc + 4 > k_left) off -= uint32_t(kc + 4 - k_left) * 4u;
 #pragma unroll
         for (int u = 0; u < CH / 4; ++u) {
-            r.v[h][u] = load_at<float4>(base, off + 16u * u);
-            if (GATE) r.g[h][u] = load_at<float4>(gate, off + 16u * u);
+            r.v[h][u] = load4_at(base, off + 16u * u);
+            if (GATE) r.g[h][u] = load4_at(gate, off + 16u * u);
         }
     }
 }
 
 template <int TERMS, int ROWS, int CH, bool GATE>
-__device__ __forceinline__ void store_rows(int tid, const RowRegs<ROWS, CH, GATE>& r, uint16_t* s) {
+__device__ __forceinline__ void store_rows(int tid, const RowRegs<ROWS, CH, GATE>& r, int32_t k_left, uint16_t* s) {
     using R = RowRegs<ROWS, CH, GATE>;
+    const bool cut = CH == 4 && k_left < BK && (k_left & 3);        // this stage holds the rows' ends, inside a group of four
 #pragma unroll
     for (int h = 0; h < R::N; ++h) {
         const int c = tid + h * kThreads;
@@ -150,6 +166,7 @@ __device__ __forceinline__ void store_rows(int tid, const RowRegs<ROWS, CH, GATE
         for (int u = 0; u < CH / 4; ++u) {
             float4 x = r.v[h][u];
             if (GATE) x = gate4(x, r.g[h][u]);
+            if (cut && (c % R::PER_ROW) * CH == (k_left & ~3)) x = moved_up(x, 4 - (k_left & 3));
             expand_pair<TERMS>(x.x, x.y, w[2 * u]);
             expand_pair<TERMS>(x.z, x.w, w[2 * u + 1]);
         }
@@ -211,7 +228,8 @@ __device__ __forceinline__ void store_prep(int tid, const PrepRegs<TERMS, ROWS>&
 // Block b of an operand's tile covers reduction steps 8 * (b % 4) .. + 7 and output indices 4 * (b / 4) .. + 3:
 // eight consecutive lanes then write two LDS rows that are four rows apart, all four 16-byte chunks of each,
 // which touches every LDS bank once. Output indices beyond the matrix are clamped (their results are never
-// stored). In the last, partial tile of the reduction the node index is clamped and A is zeroed beyond it.
+// stored), a group of four that crosses its end is moved up (rows of the 47 class columns of a last layer, of 75 input features;
+// they need no alignment). In the last, partial tile of the reduction the node index is clamped and A is zeroed beyond it.
 template <bool GATE>
 struct ColRegs {
     float4 v[8];
@@ -219,7 +237,7 @@ struct ColRegs {
 };
 
 __device__ __forceinline__ uint32_t col_offset(int b, int32_t i0, int32_t extent) {
-    return uint32_t(min(i0 + (b >> 2) * 4, extent - 4) - i0) * 4u;      // bytes; extent is a multiple of 4
+    return uint32_t(min(i0 + (b >> 2) * 4, extent - 4) - i0 + 4) * 4u;  // bytes from 4 floats before the tile's first column
 }
 
 template <bool GATE, bool TAIL, bool ZERO>
@@ -230,31 +248,15 @@ __device__ __forceinline__ void load_cols(const float* base, const float* gate, 
     for (int kk = 0; kk < 8; ++kk) {
         const int node = TAIL ? min(kb + kk, k_left - 1) : kb + kk;
         const uint32_t off = uint32_t(node) * ld_bytes + col_off;
-        r.v[kk] = load_at<float4>(base, off);
-        if (GATE) r.g[kk] = load_at<float4>(gate, off);
+        r.v[kk] = load4_at(base, off);
+        if (GATE) r.g[kk] = load4_at(gate, off);
         if (TAIL && ZERO && kb + kk >= k_left) r.v[kk] = make_float4(0.f, 0.f, 0.f, 0.f);
     }
 }
 
-// The same block of an operand whose rows are not 16-byte aligned or whose width is not a multiple of 4 (the 47
-// class columns of the last layer): element loads; columns beyond the matrix repeat its last one (their products
-// are never stored), nodes beyond the reduction repeat the last one (the other operand is zero there).
-__device__ __forceinline__ void load_cols_ragged(const float* base, int b, int32_t i0, int32_t extent, uint32_t ld_bytes,
-                                                 int32_t k_left, ColRegs<false>& r) {
-    const int kb = (b & 3) * 8;
-    uint32_t off[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) off[e] = uint32_t(min(i0 + (b >> 2) * 4 + e, extent - 1) - i0) * 4u;
-#pragma unroll
-    for (int kk = 0; kk < 8; ++kk) {
-        const uint32_t row = uint32_t(min(kb + kk, k_left - 1)) * ld_bytes;
-        r.v[kk] = make_float4(load_at<float>(base, row + off[0]), load_at<float>(base, row + off[1]),
-                              load_at<float>(base, row + off[2]), load_at<float>(base, row + off[3]));
-    }
-}
-
 template <int TERMS, int ROWS, bool GATE>
-__device__ __forceinline__ void store_cols(const ColRegs<GATE>& r, int b, uint16_t* s) {
+__device__ __forceinline__ void store_cols(const ColRegs<GATE>& r, int b, int32_t i0, int32_t extent, uint16_t* s) {
+    const bool crosses = (extent & 3) && i0 + (b >> 2) * 4 == (extent & ~3);
     // An LDS row holds one output index with its 8 reduction steps contiguous, two steps per 32-bit word: the two
     // values expanded together are steps 2 q and 2 q + 1 of one output index, which is the transposition itself.
     float x[8][4];
@@ -262,6 +264,7 @@ __device__ __forceinline__ void store_cols(const ColRegs<GATE>& r, int b, uint16
     for (int kk = 0; kk < 8; ++kk) {
         float4 v = r.v[kk];
         if constexpr (GATE) v = gate4(v, r.g[kk]);
+        if (extent & 3) v = crosses ? moved_up(v, 4 - (extent & 3)) : v;
         x[kk][0] = v.x, x[kk][1] = v.y, x[kk][2] = v.z, x[kk][3] = v.w;
     }
     uint16_t* base = s + (b >> 2) * 4 * kPitch + (b & 3) * 8;
@@ -299,8 +302,7 @@ __device__ __forceinline__ void workgroup_barrier() {
 
 // TN: both operands stored with the output index contiguous (weight gradient), else A with the reduction
 // index contiguous and B an expanded weight copy. WM x WN wavefronts per tile, each TMB x TNB blocks of
-// 32 x 32. A_CH: floats per chunk of A (NT); in a TN product A_CH = 1 says that B is read element by element
-// (unaligned rows, never masked). GATE masks A (NT) or B (TN).
+// 32 x 32. A_CH: floats per chunk of A (NT). GATE masks A (NT) or B (TN).
 //
 // A workgroup is four wavefronts with one tile and one LDS stage (60 KB), so that two workgroups are resident
 // on a compute unit and each SIMD holds one wavefront of either. On this device the vector ALU and the matrix
@@ -315,7 +317,6 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_split_kernel(SplitGemm g) {
     static_assert(TERMS == 2 || TERMS == 3, "two or three bf16 terms per operand");
     constexpr int BM = 32 * TMB * WM, BN = 32 * TNB * WN;
     static_assert(BM + BN <= kThreads, "one 8 x 4 block per thread in the TN layout");
-    static_assert(!(TN && A_CH == 1 && GATE), "an operand read element by element is never masked");
     __shared__ __attribute__((aligned(16))) uint16_t smem[TERMS * (BM + BN) * kPitch];
     const int tid = threadIdx.x;
     uint16_t* const sa = smem;
@@ -370,11 +371,13 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_split_kernel(SplitGemm g) {
         plan_b.init(tid);
     }
 
+    int32_t held = 0;                             // reduction steps from the fetched stage's start to the end
     auto fetch = [&](int32_t t) {                 // NT
         const bool first = t < tiles1;
         const int32_t k0 = (first ? t : t - tiles1) * BK, k_left = (first ? g.k : g.k2) - k0;
-        const float* abase = static_cast<const float*>(first ? a_ptr : g.a2.ptr) + int64_t(m0) * g.a.ld + k0;
-        const float* gbase = GATE ? g.a.gate + int64_t(m0) * g.a.ld + k0 : nullptr;   // never with a second product
+        held = k_left;
+        const float* abase = static_cast<const float*>(first ? a_ptr : g.a2.ptr) + int64_t(m0) * g.a.ld + k0 - 4;
+        const float* gbase = GATE ? g.a.gate + int64_t(m0) * g.a.ld + k0 - 4 : nullptr;   // never with a second product
         const uint16_t* bbase = static_cast<const uint16_t*>(first ? b_ptr : g.b2.ptr) +
                                 (int64_t(tn) * (g.b.ld / BK) + k0 / BK) * (TERMS * BN * BK);      // g.b.ld: padded reduction length
         if constexpr (!TN) {
@@ -384,7 +387,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_split_kernel(SplitGemm g) {
     };
     auto stash = [&]() {                          // NT
         if constexpr (!TN) {
-            store_rows<TERMS, BM, A_CH, GATE>(tid, ra, sa);
+            store_rows<TERMS, BM, A_CH, GATE>(tid, ra, held, sa);
             store_prep<TERMS, BN>(tid, rb, sb);
         }
     };
@@ -434,22 +437,19 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_split_kernel(SplitGemm g) {
             constexpr bool G = GATE && !A;
             ColRegs<G> cr;
             const int b = A ? tid : tid - BM;
-            constexpr bool RAGGED = !A && A_CH == 1;
-            const uint32_t col_off = RAGGED ? 0u : (A ? col_offset(b, m0, g.m) : col_offset(b, n0, g.n));
+            const uint32_t col_off = A ? col_offset(b, m0, g.m) : col_offset(b, n0, g.n);
             const SplitOperand& op = A ? g.a : g.b;
             const uint32_t ld_bytes = uint32_t(op.ld) * 4u;
             auto fetch_cols = [&](int32_t t) {
                 const int32_t k0 = t * BK, k_left = g.k - k0;
-                const float* base = static_cast<const float*>(A ? a_ptr : op.ptr) + int64_t(k0) * op.ld + (A ? m0 : n0);
-                const float* gbase = G ? op.gate + int64_t(k0) * op.ld + n0 : nullptr;
-                if constexpr (RAGGED)
-                    load_cols_ragged(base, b, n0, g.n, ld_bytes, k_left, cr);
-                else if (k_left >= BK)
+                const float* base = static_cast<const float*>(A ? a_ptr : op.ptr) + int64_t(k0) * op.ld + (A ? m0 : n0) - 4;
+                const float* gbase = G ? op.gate + int64_t(k0) * op.ld + n0 - 4 : nullptr;
+                if (k_left >= BK)
                     load_cols<G, false, A>(base, gbase, b, col_off, ld_bytes, k_left, cr);
                 else
                     load_cols<G, true, A>(base, gbase, b, col_off, ld_bytes, k_left, cr);
             };
-            pipeline(fetch_cols, [&]() { store_cols<TERMS, A ? BM : BN, G>(cr, b, A ? sa : sb); });
+            pipeline(fetch_cols, [&]() { store_cols<TERMS, A ? BM : BN, G>(cr, b, A ? m0 : n0, A ? g.m : g.n, A ? sa : sb); });
         };
         if (role == 0)
             run(std::true_type{});
@@ -855,37 +855,29 @@ hipError_t varco_launch_gemm_short_k(const GemmArgs& ga, int terms, hipStream_t 
     return hipGetLastError();
 }
 
-namespace {
-// TN: B can be read four columns at a time.
-bool b_vector_ok(const GemmArgs& ga) {
-    return aligned_to(ga.b.ptr, 16) && aligned_to(ga.b.gate, 16) && ga.b.ld % 4 == 0 && ga.n % 4 == 0;
-}
-}  // namespace
-
 bool varco_gemm_split_usable(const GemmArgs& ga) {
     if (ga.f32_terms != 2 && ga.f32_terms != 3) return false;
     if (ga.m <= 0 || ga.n <= 0) return false;
     if (ga.a.dtype != VARCO_F32 || ga.c_dtype != VARCO_F32) return false;
-    auto ok16 = [](const GemmOperand& o) { return aligned_to(o.ptr, 16) && aligned_to(o.gate, 16) && o.ld % 4 == 0; };
+    auto ok4 = [](const GemmOperand& o) { return aligned_to(o.ptr, 4) && aligned_to(o.gate, 4); };
     if (!ga.a.transposed) {   // NT: needs the library's expanded weight copy [term][rows][pitch], padded to whole tiles
         auto prep_ok = [&](const void* p, int64_t ld, int64_t plane, int32_t k) {
             return p && aligned_to(p, 16) && ld % BK == 0 && ld >= k && plane == (int64_t(ga.n) + kPrepRows - 1) / kPrepRows * kPrepRows * ld;
         };
         if (!prep_ok(ga.b_prep, ga.b_prep_ld, ga.b_prep_plane, ga.k)) return false;
-        if (ga.b.gate || ga.k % 4 != 0 || !ok16(ga.a)) return false;
+        if (ga.b.gate || ga.k < 4 || !ok4(ga.a)) return false;
         if (ga.k2 > 0) {   // a chained product shares the first one's leading dimensions and is never masked
             if (!prep_ok(ga.b2_prep, ga.b2_prep_ld, ga.b2_prep_plane, ga.k2) || ga.b2_prep_ld != ga.b_prep_ld) return false;
-            if (ga.k2 % 4 != 0 || !ok16(ga.a2) || ga.a2.ld != ga.a.ld || ga.a.gate || ga.a2.gate || ga.a2.dtype != VARCO_F32 ||
+            if (ga.k2 < 4 || !ok4(ga.a2) || ga.a2.ld != ga.a.ld || ga.a.gate || ga.a2.gate || ga.a2.dtype != VARCO_F32 ||
                 ga.a2.transposed)
                 return false;
         }
         return !ga.c_dual || (ga.k2 == 0 && ga.split_k <= 1 && ga.b_dual_prep && aligned_to(ga.b_dual_prep, 16));
     }
     // TN: weight gradient
-    if (ga.c_dual && (!ga.a_dual || !aligned_to(ga.a_dual, 16))) return false;
+    if (ga.c_dual && (!ga.a_dual || !aligned_to(ga.a_dual, 4))) return false;
     if (ga.b.transposed || ga.b.dtype != VARCO_F32 || ga.k2 > 0 || ga.a.gate) return false;
-    if (!ok16(ga.a) || ga.m % 4 != 0) return false;
-    return b_vector_ok(ga) || (ga.n <= 64 && !ga.b.gate && aligned_to(ga.b.ptr, 4));   // else B element by element
+    return ok4(ga.a) && ok4(ga.b) && ga.m >= 4 && ga.n >= 4;
 }
 
 hipError_t varco_launch_gemm_split(const GemmArgs& ga, hipStream_t stream, const LaunchTag& tag, int32_t* split_used) {
@@ -944,10 +936,7 @@ hipError_t varco_launch_gemm_split(const GemmArgs& ga, hipStream_t stream, const
                 constexpr int T = decltype(t3)::value ? 3 : 2;
                 constexpr bool NR = decltype(nr)::value, GT = decltype(gt)::value;
                 constexpr int WM = NR ? 4 : 2, WN = NR ? 1 : 2, TMB = NR ? 1 : 2, TNB = 2;
-                if (tn && !b_vector_ok(ga)) {
-                    if constexpr (NR && !GT)
-                        hipLaunchKernelGGL((gemm_split_kernel<T, true, WM, WN, TMB, TNB, 1, false>), grid, dim3(kThreads), 0, stream, g);
-                } else if (tn) {
+                if (tn) {
                     hipLaunchKernelGGL((gemm_split_kernel<T, true, WM, WN, TMB, TNB, 4, GT>), grid, dim3(kThreads), 0, stream, g);
                 } else if (a8) {
                     hipLaunchKernelGGL((gemm_split_kernel<T, false, WM, WN, TMB, TNB, 8, GT>), grid, dim3(kThreads), 0, stream, g);
