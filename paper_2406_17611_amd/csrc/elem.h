@@ -59,6 +59,21 @@ struct Elem<bf16_t> {
     }
 };
 
+// Eight bf16 elements from any address of an element (the device loads 16 bytes from there just as well).
+__device__ __forceinline__ uint4 load8_any(const char* p) {
+    typedef uint32_t any4 __attribute__((ext_vector_type(4), aligned(2)));
+    const any4 v = *reinterpret_cast<const any4*>(p);
+    return make_uint4(v[0], v[1], v[2], v[3]);
+}
+// Eight bf16 elements that were loaded `by` (1 to 7, the same in all lanes) elements early, moved up; zeros follow.
+__device__ __forceinline__ uint4 moved_up8(uint4 x, int by) {
+    if (by & 4) x = make_uint4(x.z, x.w, 0u, 0u);
+    if (by & 2) x = make_uint4(x.y, x.z, x.w, 0u);
+    if (by & 1)
+        x = make_uint4((x.x >> 16) | (x.y << 16), (x.y >> 16) | (x.z << 16), (x.z >> 16) | (x.w << 16), x.w >> 16);
+    return x;
+}
+
 // Loads / stores of N = 1, 2 or 4 consecutive elements as a float vector type.
 template <int N>
 struct FloatVec;

@@ -8,7 +8,7 @@
 // it as 32 x 32 blocks: at bf16 rates a wavefront tile smaller than that is limited by LDS reads of its fragments, not by
 // the matrix cores. Operands are staged through LDS as rows of one output index with the reduction index contiguous (16
 // bytes of padding per row: fragment reads without bank conflicts), double-buffered against the global loads of the next
-// stage, copied 8 (or 4) elements at a time unchanged. The ReLU mask of the backward pass is applied when a stage is written
+// stage, copied 8 elements at a time unchanged. The ReLU mask of the backward pass is applied when a stage is written
 // to LDS, the activation in the epilogue.
 #include <type_traits>
 
@@ -47,65 +47,64 @@ __device__ __forceinline__ uint32_t gate_pair(uint32_t v, uint32_t g) {
     return v & (lo | hi);
 }
 
-// One operand's share of a stage: ROWS rows x BK reduction steps in chunks of CH elements. A thread keeps its place in the
+// One operand's share of a stage: ROWS rows x BK reduction steps in chunks of 8 elements. A thread keeps its place in the
 // stage, so its byte offsets into the operand are formed once and the stage's base stays in scalar registers. Rows past the
-// matrix repeat its last one (their results are never stored); reduction steps past the end are zero.
-template <int ROWS, int CH, bool GATE, int BK, int kThreads>
+// matrix repeat its last one (their results are never stored); reduction steps past the end are zero. ANY: rows of any
+// alignment and any length from 8 on (a chunk that crosses the end is loaded from before it and moved up), else padded ones.
+template <int ROWS, bool GATE, bool ANY, int BK, int kThreads>
 struct RowSlab {
-    using W = std::conditional_t<CH == 8, uint4, uint2>;
-    static constexpr int PER_ROW = BK / CH, kPitch = BK + 8;
+    static constexpr int PER_ROW = BK / 8, kPitch = BK + 8;
     static constexpr int N = ROWS * PER_ROW / kThreads;
-    W v[N], g[GATE ? N : 1];
-    uint32_t at[N];
+    uint4 v[N], g[GATE ? N : 1];
+    uint32_t at[N];                                        // from 8 elements before the base: a chunk moved up may start before it
     __device__ __forceinline__ void place(int32_t rows_left, int64_t ld) {
 #pragma unroll
         for (int h = 0; h < N; ++h) {
             const int c = int(threadIdx.x) + h * kThreads;
-            at[h] = (uint32_t(min(c / PER_ROW, rows_left - 1)) * uint32_t(ld) + uint32_t(c % PER_ROW) * CH) * 2u;
+            at[h] = (uint32_t(min(c / PER_ROW, rows_left - 1)) * uint32_t(ld) + uint32_t(c % PER_ROW) * 8u + 8u) * 2u;
         }
     }
     // base (and gate): the tile's first row at the stage's first reduction step; left: reduction steps from there to the end
     __device__ __forceinline__ void load(const uint16_t* base, const uint16_t* gate, int32_t left) {
-        const bool in = int32_t(threadIdx.x % PER_ROW) * CH < left;
+        const int32_t k = int32_t(threadIdx.x % PER_ROW) * 8, over = ANY ? max(k + 8 - left, 0) : 0;
+        const char* const from = reinterpret_cast<const char*>(base - 8);
+        const char* const mask = reinterpret_cast<const char*>(gate - 8);
 #pragma unroll
         for (int h = 0; h < N; ++h) {
-            const uint32_t off = in ? at[h] : 0u;          // (the end is a multiple of CH: a chunk is wholly in or out)
-            v[h] = *reinterpret_cast<const W*>(reinterpret_cast<const char*>(base) + off);
-            if constexpr (GATE) g[h] = *reinterpret_cast<const W*>(reinterpret_cast<const char*>(gate) + off);
+            const uint32_t off = k < left ? at[h] - 2u * uint32_t(over) : 16u;
+            v[h] = ANY ? load8_any(from + off) : *reinterpret_cast<const uint4*>(from + off);
+            if constexpr (GATE) g[h] = load8_any(mask + off);
         }
     }
     __device__ __forceinline__ void store(uint16_t* s, int32_t left) const {
-        const bool in = int32_t(threadIdx.x % PER_ROW) * CH < left;
+        const int32_t k = int32_t(threadIdx.x % PER_ROW) * 8;
 #pragma unroll
         for (int h = 0; h < N; ++h) {
             const int c = int(threadIdx.x) + h * kThreads;
-            W x = v[h];
-            uint32_t* u = reinterpret_cast<uint32_t*>(&x);
-            if constexpr (GATE) {
-                const uint32_t* w = reinterpret_cast<const uint32_t*>(&g[h]);
-#pragma unroll
-                for (int i = 0; i < CH / 2; ++i) u[i] = gate_pair(u[i], w[i]);
-            }
+            uint4 x = v[h];
+            if constexpr (GATE) x = make_uint4(gate_pair(x.x, g[h].x), gate_pair(x.y, g[h].y), gate_pair(x.z, g[h].z), gate_pair(x.w, g[h].w));
             if (left < BK) {
-#pragma unroll
-                for (int i = 0; i < CH / 2; ++i) u[i] = in ? u[i] : 0u;
+                if (ANY && (left & 7)) {
+                    const uint4 y = moved_up8(x, 8 - (left & 7));
+                    if (k < left && k + 8 > left) x = y;
+                }
+                if (k >= left) x = make_uint4(0u, 0u, 0u, 0u);
             }
-            *reinterpret_cast<W*>(s + (c / PER_ROW) * kPitch + (c % PER_ROW) * CH) = x;
+            *reinterpret_cast<uint4*>(s + (c / PER_ROW) * kPitch + (c % PER_ROW) * 8) = x;
         }
     }
 };
 
 __device__ __forceinline__ bf16x8 fragment(const uint16_t* s) { return __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(s)); }
 
-// WM x WN wavefronts, each TMB x TNB blocks of 32 x 32. A_CH: elements per global load of A (B is the library's own padded
-// weight copy, always 8). GATE masks A.
+// WM x WN wavefronts, each TMB x TNB blocks of 32 x 32. B is the library's own padded weight copy. GATE masks A.
 // The blocks are formed transposed (the weights as the first matrix operand), which leaves four consecutive columns of a row
 // in a lane: they are rounded in pairs, put through the wavefront's own part of LDS and stored 16 bytes per lane, whole lines
 // at a time. Stored from the registers, 2 bytes per lane, the 128 store instructions of a thread kept the vector memory unit
 // busy for as long as all matrix instructions of a K = 512 tile take.
 // 169,343 rows, 512 x 512, masked: 208 us with the 256 x 128 tile, whose four column tiles read A and the mask four times
 // through L2 in half lines (18 TB/s), 184 with 256 x 256.
-template <int WM, int WN, int TMB, int TNB, int BK, int A_CH, bool GATE>
+template <int WM, int WN, int TMB, int TNB, int BK, bool GATE>
 __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_bf16_kernel(GemmDev g) {
     constexpr int BM = 32 * TMB * WM, BN = 32 * TNB * WN, kThreads = WM * WN * 64, kPitch = BK + 8;
     extern __shared__ __attribute__((aligned(16))) uint16_t lds[];       // two stages of A, then of B
@@ -135,8 +134,8 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_bf16_kernel(GemmDev g) {
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
 
-    RowSlab<BM, A_CH, GATE, BK, kThreads> ra;
-    RowSlab<BN, 8, false, BK, kThreads> rb;
+    RowSlab<BM, GATE, true, BK, kThreads> ra;
+    RowSlab<BN, false, false, BK, kThreads> rb;
     const uint16_t *pa = nullptr, *pg = nullptr, *pb = nullptr;     // the next stage's bases, and what is left of its product's steps
     int32_t left = 0;
     auto enter = [&](const OperandDev& a, const uint16_t* b, int64_t ldb, int32_t steps) {
@@ -249,12 +248,12 @@ bool varco_gemm_bf16_usable(const GemmArgs& ga) {
     if (ga.m <= 0 || ga.n <= 0) return false;
     if (ga.a.transposed) return varco_gemm_tn_bf16_usable(ga);
     if (ga.a.dtype != VARCO_BF16) return false;
-    auto ok8 = [](const GemmOperand& o) { return aligned_to(o.ptr, 8) && aligned_to(o.gate, 8) && o.ld % 4 == 0; };
+    auto ok2 = [](const GemmOperand& o) { return aligned_to(o.ptr, 2) && aligned_to(o.gate, 2); };
     // needs the library's bf16 weight copy [n][pitch], pitch a multiple of 8
     if (ga.c_dtype != VARCO_BF16 || !ga.b_prep || ga.b_prep_ld % 8 != 0 || !aligned_to(ga.b_prep, 16)) return false;
-    if (ga.b.gate || ga.k % 4 != 0 || !ok8(ga.a) || ga.split_k > 1) return false;
-    if (ga.k2 > 0 && (!ga.b2_prep || ga.b2_prep_ld % 8 != 0 || !aligned_to(ga.b2_prep, 16) || ga.k2 % 4 != 0 ||
-                      !ok8(ga.a2) || ga.a2.gate || ga.a2.dtype != VARCO_BF16 || ga.a2.transposed))
+    if (ga.b.gate || ga.k < 8 || !ok2(ga.a) || ga.split_k > 1) return false;
+    if (ga.k2 > 0 && (!ga.b2_prep || ga.b2_prep_ld % 8 != 0 || !aligned_to(ga.b2_prep, 16) || ga.k2 < 8 ||
+                      !ok2(ga.a2) || ga.a2.gate || ga.a2.dtype != VARCO_BF16 || ga.a2.transposed))
         return false;
     return !ga.c_dual || (ga.k2 == 0 && ga.b_dual_prep && aligned_to(ga.b_dual_prep, 16));
 }
@@ -264,10 +263,6 @@ hipError_t varco_launch_gemm_bf16(const GemmArgs& ga, hipStream_t stream, const 
     // 256 x 256 where its tiles fill the device and pad no more columns than 256 x 128
     const int64_t wide = int64_t((ga.m + 255) / 256) * ((ga.n + 255) / 256);
     const int bm = 256, bn = ga.n <= 64 ? 64 : wide >= 256 && (ga.n + 255) / 256 * 2 == (ga.n + 127) / 128 ? 256 : 128;
-    auto chunk8 = [](const GemmOperand& o, int32_t k) {
-        return !o.ptr || (aligned_to(o.ptr, 16) && aligned_to(o.gate, 16) && o.ld % 8 == 0 && k % 8 == 0);
-    };
-    const bool a8 = chunk8(ga.a, ga.k) && (ga.k2 == 0 || chunk8(ga.a2, ga.k2));
     const bool gate = ga.a.gate != nullptr;
 
     GemmDev g;
@@ -298,15 +293,13 @@ hipError_t varco_launch_gemm_bf16(const GemmArgs& ga, hipStream_t stream, const 
         constexpr int BK = decltype(bk)::value;
         constexpr size_t bytes = size_t(2) * 32 * (TMB * WM + TNB * WN) * (BK + 8) * 2;
         with_flag(gate, [&](auto gt) {
-            with_flag(a8, [&](auto c8) {
-                const auto kernel = gemm_bf16_kernel<WM, WN, TMB, TNB, BK, decltype(c8)::value ? 8 : 4, decltype(gt)::value>;
-                if (bytes > 64 * 1024)
-                    err = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, int(bytes));
-                if (err != hipSuccess) return;
-                tag.begin(stream);
-                hipLaunchKernelGGL(kernel, grid, dim3(WM * WN * 64), bytes, stream, g);
-                tag.end(stream);
-            });
+            const auto kernel = gemm_bf16_kernel<WM, WN, TMB, TNB, BK, decltype(gt)::value>;
+            if (bytes > 64 * 1024)
+                err = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, int(bytes));
+            if (err != hipSuccess) return;
+            tag.begin(stream);
+            hipLaunchKernelGGL(kernel, grid, dim3(WM * WN * 64), bytes, stream, g);
+            tag.end(stream);
         });
     };
     using I1 = std::integral_constant<int, 1>;

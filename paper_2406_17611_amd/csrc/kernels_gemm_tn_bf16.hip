@@ -23,8 +23,6 @@ constexpr int kThreads = 512;
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef short shortx4 __attribute__((ext_vector_type(4)));
-typedef uint32_t words4 __attribute__((ext_vector_type(4)));
-typedef uint32_t words2 __attribute__((ext_vector_type(2)));
 
 // Rows per stage: 32, and 64 for the 256 x 256 tile, whose single workgroup per compute unit has nothing else in flight while
 // it waits for a stage.
@@ -52,49 +50,53 @@ __device__ __forceinline__ uint32_t gate_pair(uint32_t v, uint32_t g) {
     return v & (lo | hi);
 }
 
-// One operand's share of a stage: W columns x BK rows in chunks of CH elements, dealt to the threads row by row.
-template <int W, int CH, bool GATE, int BK>
+// One operand's share of a stage: W columns x BK rows in chunks of 8 elements, dealt to the threads row by row. Rows may have
+// any alignment and any length from 8 on: a chunk that crosses the last column is loaded from before it and moved up (ANY:
+// the lengths are no multiples of 8; 5 % of the 256 x 256 kernel's time).
+template <int W, bool ANY, bool GATE, int BK>
 struct Slab {
-    using V = std::conditional_t<CH == 8, words4, words2>;
-    static constexpr int PER_ROW = W / CH, TOTAL = PER_ROW * BK, N = (TOTAL + kThreads - 1) / kThreads, ROWS = kThreads / PER_ROW;
+    static constexpr int PER_ROW = W / 8, TOTAL = PER_ROW * BK, N = (TOTAL + kThreads - 1) / kThreads, ROWS = kThreads / PER_ROW;
     static constexpr int PITCH = W * 2 + 64;               // bytes
     static_assert(kThreads % PER_ROW == 0, "a thread keeps its columns");
-    V v[N], g[GATE ? N : 1];
-    uint32_t col, row;                                     // of this thread's first chunk
+    uint4 v[N], g[GATE ? N : 1];
+    uint32_t row;                                          // of this thread's first chunk
+    int32_t col;
+    bool crosses;
+    int by;                                                // columns that the crossing chunk of a row is loaded early (same in all lanes)
     __device__ __forceinline__ void start(int32_t i0, int32_t extent) {
         row = threadIdx.x / PER_ROW;
-        const int32_t c = i0 + int32_t(threadIdx.x % PER_ROW) * CH;
-        col = c < extent ? c : i0;                         // columns past the matrix: a repeated one, never stored
+        const int32_t c = i0 + int32_t(threadIdx.x % PER_ROW) * 8;
+        crosses = c < extent && c + 8 > extent;
+        by = extent & 7 ? 8 - (extent & 7) : 0;
+        col = min(c, extent - 8);                          // (columns past the matrix: repeated ones, never stored)
     }
     // rows k0 .. k0 + BK - 1; those from kmax on are zero
     __device__ __forceinline__ void load(const uint16_t* p, const uint16_t* gate, int64_t ld, int32_t k0, int32_t kmax) {
 #pragma unroll
         for (int h = 0; h < N; ++h) {
             if (TOTAL < kThreads && threadIdx.x >= TOTAL) break;
-            const int32_t r = k0 + int32_t(row) + h * ROWS;
-            const int64_t off = int64_t(min(r, kmax - 1)) * ld + col;
-            v[h] = *reinterpret_cast<const V*>(p + off);
-            if constexpr (GATE) g[h] = *reinterpret_cast<const V*>(gate + off);
+            const int64_t off = int64_t(min(k0 + int32_t(row) + h * ROWS, kmax - 1)) * ld + col;
+            v[h] = load8_any(reinterpret_cast<const char*>(p + off));
+            if constexpr (GATE) g[h] = load8_any(reinterpret_cast<const char*>(gate + off));
         }
     }
     __device__ __forceinline__ void store(char* s, int32_t k0, int32_t kmax) const {
 #pragma unroll
         for (int h = 0; h < N; ++h) {
             if (TOTAL < kThreads && threadIdx.x >= TOTAL) break;
-            const bool in = k0 + int32_t(row) + h * ROWS < kmax;
-            V x = v[h];
-#pragma unroll
-            for (int u = 0; u < CH / 2; ++u) {
-                if constexpr (GATE) x[u] = gate_pair(x[u], g[h][u]);
-                x[u] = in ? x[u] : 0u;
+            uint4 x = v[h];
+            if constexpr (GATE) x = make_uint4(gate_pair(x.x, g[h].x), gate_pair(x.y, g[h].y), gate_pair(x.z, g[h].z), gate_pair(x.w, g[h].w));
+            if (ANY && by) {
+                const uint4 y = moved_up8(x, by);
+                if (crosses) x = y;
             }
-            *reinterpret_cast<V*>(s + (row + h * ROWS) * PITCH + (threadIdx.x % PER_ROW) * (CH * 2)) = x;
+            if (k0 + int32_t(row) + h * ROWS >= kmax) x = make_uint4(0u, 0u, 0u, 0u);
+            *reinterpret_cast<uint4*>(s + (row + h * ROWS) * PITCH + (threadIdx.x % PER_ROW) * 16) = x;
         }
     }
 };
 
-// B read element by element (64 columns at most, never masked): rows that are not 8-byte aligned, as the 47 class columns of a
-// last layer.
+// B read element by element (64 columns at most, never masked): fewer than 8 columns.
 template <int BK>
 struct ElementSlab {
     static constexpr int N = 64 * BK / kThreads, PITCH = 64 * 2 + 64;
@@ -117,8 +119,8 @@ struct ElementSlab {
             if (row[h] < BK) *reinterpret_cast<uint16_t*>(s + row[h] * PITCH + col[h] * 2) = k0 + row[h] < kmax ? v[h] : uint16_t(0);
     }
 };
-template <int W, int CH, bool GATE, int BK>
-using SlabOf = std::conditional_t<CH == 1, ElementSlab<BK>, Slab<W, CH == 1 ? 8 : CH, GATE, BK>>;
+template <int W, bool FEW, bool ANY, bool GATE, int BK>
+using SlabOf = std::conditional_t<FEW, ElementSlab<BK>, Slab<W, ANY, GATE, BK>>;
 
 // Fragment of 32 columns x 16 rows whose first column's element of row 0 (this lane's share of the block) is at LDS byte `at`.
 template <int PITCH>
@@ -130,12 +132,12 @@ __device__ __forceinline__ bf16x8 fragment(uint32_t at) {
     return __builtin_bit_cast(bf16x8, shortx8{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]});
 }
 
-template <int WM, int WN, int TMB, int TNB, int ACH, int BCH, bool GATE>
+template <int WM, int WN, int TMB, int TNB, bool FEW, bool ANY, bool GATE>
 __global__ __launch_bounds__(kThreads, TMB * TNB > 4 ? 2 : 4) void gemm_tn_bf16_kernel(TnDev g) {
     static_assert(WM * WN * 64 == kThreads, "");
     constexpr int BM = 32 * TMB * WM, BN = 32 * TNB * WN, BK = stage_rows(BM, BN);
-    using SA = SlabOf<BM, ACH, false, BK>;
-    using SB = SlabOf<BN, BCH, GATE, BK>;
+    using SA = SlabOf<BM, false, ANY, false, BK>;
+    using SB = SlabOf<BN, FEW, ANY, GATE, BK>;
     extern __shared__ __attribute__((aligned(16))) char lds[];          // two buffers of BK rows of A, then of B
     constexpr int kA = BK * SA::PITCH, kB = BK * SB::PITCH;
 
@@ -223,22 +225,13 @@ __global__ __launch_bounds__(kThreads, TMB * TNB > 4 ? 2 : 4) void gemm_tn_bf16_
 
 bool aligned_to(const void* p, uintptr_t bytes) { return (reinterpret_cast<uintptr_t>(p) & (bytes - 1)) == 0; }
 
-// Elements per load of an operand: 8, 4, or 1 when its rows or width do not allow either (columns between the width and the
-// pitch may be read).
-int chunk_of(const void* p, const void* gate, int64_t ld, int32_t extent) {
-    for (int c : {8, 4})
-        if (aligned_to(p, 2 * c) && aligned_to(gate, 2 * c) && ld % c == 0 && (extent % c == 0 || ld >= (extent + c - 1) / c * c)) return c;
-    return 1;
-}
-int chunk_a(const GemmArgs& g) { return std::min(chunk_of(g.a.ptr, nullptr, g.a.ld, g.m), g.c_dual ? chunk_of(g.a_dual, nullptr, g.a.ld, g.m) : 8); }
-int chunk_b(const GemmArgs& g) { return chunk_of(g.b.ptr, g.b.gate, g.b.ld, g.n); }
-
 }  // namespace
 
 bool varco_gemm_tn_bf16_usable(const GemmArgs& g) {
     if (g.m <= 0 || g.n <= 0 || g.k <= 0 || !g.a.transposed || g.b.transposed || g.k2 > 0 || g.a.gate || g.relu) return false;
     if (g.a.dtype != VARCO_BF16 || g.b.dtype != VARCO_BF16 || g.c_dtype != VARCO_F32 || (g.c_dual && !g.a_dual)) return false;
-    return chunk_a(g) > 1 && (chunk_b(g) > 1 || (g.n <= 64 && !g.b.gate));
+    if (!aligned_to(g.a.ptr, 2) || !aligned_to(g.a_dual, 2) || !aligned_to(g.b.ptr, 2) || !aligned_to(g.b.gate, 2)) return false;
+    return g.m >= 8 && (g.n >= 8 || !g.b.gate);
 }
 
 // Tile for a product of m x n: 256 rows, or 128 where 256 would be half empty; 256, 128 or 64 columns likewise.
@@ -272,16 +265,14 @@ hipError_t varco_launch_gemm_tn_bf16(const GemmArgs& ga, hipStream_t stream, con
     const int64_t blocks = int64_t((split + 7) / 8 * 8) * g.inner;
     if (blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
     *split_used = split;
-    const int ca = chunk_a(ga), cb = chunk_b(ga);
 
     hipError_t err = hipSuccess;
-    auto launch = [&](auto wm, auto wn, auto tmb, auto tnb, auto ach, auto bch, auto gated) {
+    auto launch = [&](auto wm, auto wn, auto tmb, auto tnb, auto few, auto any, auto gated) {
         constexpr int WM = decltype(wm)::value, WN = decltype(wn)::value, TMB = decltype(tmb)::value, TNB = decltype(tnb)::value;
-        constexpr int ACH = decltype(ach)::value, BCH = decltype(bch)::value;
-        constexpr bool G = decltype(gated)::value;
+        constexpr bool F = decltype(few)::value, A = decltype(any)::value, G = decltype(gated)::value;
         constexpr int BK = stage_rows(32 * TMB * WM, 32 * TNB * WN);
-        const size_t bytes = size_t(2 * BK) * (SlabOf<32 * TMB * WM, ACH, false, BK>::PITCH + SlabOf<32 * TNB * WN, BCH, G, BK>::PITCH);
-        const auto kernel = gemm_tn_bf16_kernel<WM, WN, TMB, TNB, ACH, BCH, G>;
+        const size_t bytes = size_t(2 * BK) * (SlabOf<32 * TMB * WM, false, A, false, BK>::PITCH + SlabOf<32 * TNB * WN, F, A, G, BK>::PITCH);
+        const auto kernel = gemm_tn_bf16_kernel<WM, WN, TMB, TNB, F, A, G>;
         if (bytes > 64 * 1024) {
             err = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, int(bytes));
             if (err != hipSuccess) return;
@@ -290,42 +281,32 @@ hipError_t varco_launch_gemm_tn_bf16(const GemmArgs& ga, hipStream_t stream, con
         hipLaunchKernelGGL(kernel, dim3(unsigned(blocks)), dim3(kThreads), bytes, stream, g);
         tag.end(stream);
     };
-    auto with_gate = [&](auto wm, auto wn, auto tmb, auto tnb, auto ach, auto bch) {
-        if (g.gate)
-            launch(wm, wn, tmb, tnb, ach, bch, std::true_type{});
-        else
-            launch(wm, wn, tmb, tnb, ach, bch, std::false_type{});
+    auto with_gate = [&](auto wm, auto wn, auto tmb, auto tnb) {
+        using Yes = std::true_type;
+        using No = std::false_type;
+        const bool any = ga.m % 8 || ga.n % 8;
+        if (ga.n < 8) {
+            if constexpr (decltype(tnb)::value * decltype(wn)::value == 2) launch(wm, wn, tmb, tnb, Yes{}, Yes{}, No{});
+        } else if (g.gate) {
+            any ? launch(wm, wn, tmb, tnb, No{}, Yes{}, Yes{}) : launch(wm, wn, tmb, tnb, No{}, No{}, Yes{});
+        } else {
+            any ? launch(wm, wn, tmb, tnb, No{}, Yes{}, No{}) : launch(wm, wn, tmb, tnb, No{}, No{}, No{});
+        }
     };
     using I1 = std::integral_constant<int, 1>;
     using I2 = std::integral_constant<int, 2>;
     using I4 = std::integral_constant<int, 4>;
-    using I8 = std::integral_constant<int, 8>;
-    auto with_chunks = [&](auto wm, auto wn, auto tmb, auto tnb) {
-        if (cb == 1) {
-            if constexpr (decltype(tnb)::value * decltype(wn)::value == 2) {
-                if (ca == 8)
-                    launch(wm, wn, tmb, tnb, I8{}, I1{}, std::false_type{});
-                else
-                    launch(wm, wn, tmb, tnb, I4{}, I1{}, std::false_type{});
-            }
-        } else if (ca == 8 && cb == 8)
-            with_gate(wm, wn, tmb, tnb, I8{}, I8{});
-        else if (cb == 8)
-            with_gate(wm, wn, tmb, tnb, I4{}, I8{});
-        else
-            with_gate(wm, wn, tmb, tnb, I4{}, I4{});
-    };
     if (bm == 256 && bn == 256)
-        with_chunks(I2{}, I4{}, I4{}, I2{});
+        with_gate(I2{}, I4{}, I4{}, I2{});
     else if (bm == 256 && bn == 128)
-        with_chunks(I4{}, I2{}, I2{}, I2{});
+        with_gate(I4{}, I2{}, I2{}, I2{});
     else if (bm == 256)
-        with_chunks(I4{}, I2{}, I2{}, I1{});
+        with_gate(I4{}, I2{}, I2{}, I1{});
     else if (bn == 256)
-        with_chunks(I2{}, I4{}, I2{}, I2{});
+        with_gate(I2{}, I4{}, I2{}, I2{});
     else if (bn == 128)
-        with_chunks(I2{}, I4{}, I2{}, I1{});
+        with_gate(I2{}, I4{}, I2{}, I1{});
     else
-        with_chunks(I4{}, I2{}, I1{}, I1{});
+        with_gate(I4{}, I2{}, I1{}, I1{});
     return err != hipSuccess ? err : hipGetLastError();
 }
