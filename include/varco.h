@@ -361,10 +361,22 @@ int32_t varco_link_partitions(varco_ctx* ctx);
 int32_t varco_network_forward(varco_ctx* ctx, const varco_network_buffers* b, varco_stream stream);
 /* Every layer backward, last first, each as varco_layer_bwd on all partitions and varco_accumulate_returned. */
 int32_t varco_network_backward(varco_ctx* ctx, const varco_network_buffers* b, varco_stream stream);
-/* varco_compress of the boundary rows, varco_aggregate_fwd, and varco_aggregate_bwd with the owner-side sums, on arenas. */
+/* varco_compress of the boundary rows, varco_aggregate_fwd, and varco_aggregate_bwd with the owner-side sums (accumulate
+ * != 0: added to what g_in holds), on arenas. */
 int32_t varco_network_compress(varco_ctx* ctx, int32_t tap, const void* x, void* z, varco_stream stream);
 int32_t varco_network_aggregate_fwd(varco_ctx* ctx, int32_t tap, const void* y, const void* z_in, void* y_out, varco_stream stream);
-int32_t varco_network_aggregate_bwd(varco_ctx* ctx, int32_t tap, const void* g_out, void* g_in, varco_stream stream);
+int32_t varco_network_aggregate_bwd(varco_ctx* ctx, int32_t tap, const void* g_out, void* g_in, int32_t accumulate, varco_stream stream);
+/* The dense products of n_taps taps of a layer over the arena (cf. varco_transform_*): y, h, dh, g_out are host arrays of
+ * n_taps device pointers.
+ *   varco_network_taps_fwd          c = act(sum over taps of y[t] h[t])
+ *   varco_network_taps_bwd_weight   dh[t] += y[t]^T dz
+ *   varco_network_taps_bwd_input    g_out[t] = dz h[t]^T, one or two taps */
+int32_t varco_network_taps_fwd(varco_ctx* ctx, int32_t layer, int32_t n_taps, const void* const* y, const void* const* h, void* c,
+                               varco_stream stream);
+int32_t varco_network_taps_bwd_weight(varco_ctx* ctx, int32_t layer, int32_t n_taps, const void* const* y, const void* dx_out,
+                                      const void* x_out, void* const* dh, varco_stream stream);
+int32_t varco_network_taps_bwd_input(varco_ctx* ctx, int32_t layer, int32_t n_taps, const void* dx_out, const void* x_out,
+                                     const void* const* h, void* const* g_out, varco_stream stream);
 
 int32_t varco_get_stats(const varco_ctx* ctx, varco_stats* out);
 int32_t varco_reset_stats(varco_ctx* ctx);

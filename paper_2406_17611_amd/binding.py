@@ -34,6 +34,7 @@ EXPORTS = [
     "varco_transform_bwd_input", "varco_transform_bwd_weight_static",
     "varco_link_partitions", "varco_network_forward", "varco_network_backward", "varco_network_compress",
     "varco_network_aggregate_fwd", "varco_network_aggregate_bwd",
+    "varco_network_taps_fwd", "varco_network_taps_bwd_weight", "varco_network_taps_bwd_input",
 ]
 KERNEL_CLASSES = ["compress", "decompress", "agg_fwd", "gemm_fwd", "gemm_wgrad", "gemm_dgrad", "agg_bwd_local",
                   "agg_bwd_halo", "reduce", "agg_bwd_halo_sum"]
@@ -132,7 +133,10 @@ def lib() -> C.CDLL:
         L.varco_network_backward.argtypes = [vp, C.POINTER(NetworkBuffers), vp]
         L.varco_network_compress.argtypes = [vp, i32, vp, vp, vp]
         L.varco_network_aggregate_fwd.argtypes = [vp, i32, vp, vp, vp, vp]
-        L.varco_network_aggregate_bwd.argtypes = [vp, i32, vp, vp, vp]
+        L.varco_network_aggregate_bwd.argtypes = [vp, i32, vp, vp, i32, vp]
+        L.varco_network_taps_fwd.argtypes = [vp, i32, i32, vp, vp, vp, vp]
+        L.varco_network_taps_bwd_weight.argtypes = [vp, i32, i32, vp, vp, vp, vp, vp]
+        L.varco_network_taps_bwd_input.argtypes = [vp, i32, i32, vp, vp, vp, vp, vp]
         L.varco_profile_enable.argtypes = [vp, i32]
         L.varco_profile_read.argtypes = [vp, C.POINTER(Profile), i32]
         for name in EXPORTS:
@@ -400,8 +404,23 @@ class Context:
     def network_aggregate_fwd(self, tap, y, z_in, y_out, stream=None):
         _check(lib().varco_network_aggregate_fwd(self._h, tap, _ptr(y), _ptr(z_in), _ptr(y_out), _stream(stream)), self._h)
 
-    def network_aggregate_bwd(self, tap, g_out, g_in, stream=None):
-        _check(lib().varco_network_aggregate_bwd(self._h, tap, _ptr(g_out), _ptr(g_in), _stream(stream)), self._h)
+    def network_aggregate_bwd(self, tap, g_out, g_in, accumulate=False, stream=None):
+        _check(lib().varco_network_aggregate_bwd(self._h, tap, _ptr(g_out), _ptr(g_in), int(accumulate), _stream(stream)), self._h)
+
+    @staticmethod
+    def _ptrs(tensors):
+        return (C.c_void_p * len(tensors))(*[t.data_ptr() for t in tensors])
+
+    def network_taps_fwd(self, layer, y, h, c, stream=None):
+        _check(lib().varco_network_taps_fwd(self._h, layer, len(y), self._ptrs(y), self._ptrs(h), _ptr(c), _stream(stream)), self._h)
+
+    def network_taps_bwd_weight(self, layer, y, dx_out, x_out, dh, stream=None):
+        _check(lib().varco_network_taps_bwd_weight(self._h, layer, len(y), self._ptrs(y), _ptr(dx_out), _ptr(x_out), self._ptrs(dh),
+                                                   _stream(stream)), self._h)
+
+    def network_taps_bwd_input(self, layer, dx_out, x_out, h, g, stream=None):
+        _check(lib().varco_network_taps_bwd_input(self._h, layer, len(h), _ptr(dx_out), _ptr(x_out), self._ptrs(h), self._ptrs(g),
+                                                  _stream(stream)), self._h)
 
     def softmax_xent(self, logits, labels, n_classes, scale, dlogits, row_loss, row_correct, totals, stream=None):
         n_rows = logits.shape[0]

@@ -245,7 +245,7 @@ bool prep_slot(varco_ctx* ctx, Workspace& ws, int32_t layer, const void* h, int3
     const int32_t rows = transpose ? fo : fi, cols = transpose ? fi : fo;
     const int32_t p = bf16 ? pad8(cols) : pad_to(cols, 32);
     const int32_t rows_padded = bf16 ? rows : pad_to(rows, 128);   // whole tiles: the kernel reads the copy without bounds checks
-    const size_t slot = (size_t(layer) * 2 + which) * 2 + (transpose ? 0 : 1);
+    const size_t slot = (size_t(layer) * kWeightSlots + which) * 2 + (transpose ? 0 : 1);
     uint16_t* dst = reinterpret_cast<uint16_t*>(ws.w) + ctx->w_slot[slot];
     (as_b2 ? g.b2_prep : g.b_prep) = dst;
     (as_b2 ? g.b2_prep_ld : g.b_prep_ld) = p;
@@ -324,7 +324,7 @@ int32_t size_workspace(varco_ctx* ctx, Workspace& ws) {
     }
     VARCO_HIP(ctx, grow(ws.tf, ws.tf_elems, tf_rows));
     VARCO_HIP(ctx, grow(ws.hrows, ws.hrows_elems, tf_records));
-    if (ws.w_tags.empty()) ws.w_tags.resize(size_t(ctx->n_layers) * 4);
+    if (ws.w_tags.empty()) ws.w_tags.resize(size_t(ctx->n_layers) * kWeightSlots * 2);
     return VARCO_OK;
 }
 int32_t size_all_workspaces(varco_ctx* ctx) {
@@ -445,7 +445,7 @@ extern "C" int32_t varco_create(const varco_config* cfg, varco_ctx** out) {
             const int32_t fi = ctx->widths[l], fo = ctx->widths[l + 1];
             const size_t fwd = bf16 ? size_t(fo) * pad8(fi) : size_t(3) * pad_to(fo, 128) * pad_to(fi, 32);
             const size_t bwd = bf16 ? size_t(fi) * pad8(fo) : size_t(3) * pad_to(fi, 128) * pad_to(fo, 32);
-            for (int which = 0; which < 2; ++which)
+            for (int which = 0; which < kWeightSlots; ++which)
                 for (size_t sz : {fwd, bwd}) {
                     ctx->w_slot.push_back(total);
                     total += (sz + 7) / 8 * 8;       // slots stay 16-byte aligned

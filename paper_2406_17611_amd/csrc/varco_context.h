@@ -131,6 +131,7 @@ enum GemmKind { kGemmF32 = 0, kGemmBf16 = 1, kGemmExpanded = 2 };     // kGemmBf
 int32_t gemm_split_for(int32_t m, int32_t n, int64_t k, int kind);
 int gemm_kind(const GemmArgs& g);
 int64_t wgrad_slots(int32_t m, int32_t n, int kind, int products);     // slabs that fill the device once
+constexpr int kWeightSlots = 4;       // converted copies held per layer and orientation: of the two taps of a layer, or of the first taps of a K-tap layer
 bool prep_slot(varco_ctx* ctx, Workspace& ws, int32_t layer, const void* h, int32_t fi, int32_t fo, bool transpose, int which, bool as_b2,
                GemmArgs& g, PrepJob* job);
 hipError_t prep_weight(varco_ctx* ctx, Workspace& ws, int32_t layer, const void* h, int32_t fi, int32_t fo, bool transpose,

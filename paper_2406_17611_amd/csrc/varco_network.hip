@@ -606,12 +606,145 @@ extern "C" int32_t varco_network_aggregate_fwd(varco_ctx* ctx, int32_t tap, cons
     return aggregate_fwd(ctx, *ws, layer, make_rule(ctx, layer, hop), y, z_in, y_out, static_cast<hipStream_t>(stream));
 }
 
-extern "C" int32_t varco_network_aggregate_bwd(varco_ctx* ctx, int32_t tap, const void* g_out, void* g_in, varco_stream stream) {
+extern "C" int32_t varco_network_aggregate_bwd(varco_ctx* ctx, int32_t tap, const void* g_out, void* g_in, int32_t accumulate, varco_stream stream) {
     const char* fn = "varco_network_aggregate_bwd";
     int32_t layer = 0, hop = 0;
     Workspace* ws = nullptr;
     if (int32_t rc = tap_prologue(ctx, tap, stream, fn, &layer, &hop, &ws)) return rc;
     if (ctx->net.rows > 0 && (!g_out || !g_in)) return null_pointer(ctx, fn);
     if (int32_t rc = check_wide_rows(ctx, ctx->widths[layer], {g_out, g_in}, fn)) return rc;
-    return aggregate_bwd(ctx, *ws, layer, make_rule(ctx, layer, hop), g_out, g_in, false, static_cast<hipStream_t>(stream));
+    return aggregate_bwd(ctx, *ws, layer, make_rule(ctx, layer, hop), g_out, g_in, accumulate != 0, static_cast<hipStream_t>(stream));
+}
+
+// The dense products of all taps of a layer over the arena. Two taps share a launch where the kernels can: chained reductions
+// forward, products that share dZ backward; the copies of all weights are made by one launch (as many as there are slots).
+namespace {
+int32_t taps_prologue(varco_ctx* ctx, int32_t layer, int32_t n_taps, varco_stream stream, const char* fn, Workspace** ws) {
+    if (int32_t rc = check_linked(ctx, fn)) return rc;
+    ctx->prof.interrupt();
+    if (layer < 0 || layer >= ctx->n_layers || n_taps < 1) {
+        std::string m = std::string(fn) + ": no such layer, or no tap";
+        return varco_fail(ctx, VARCO_ERR_INVALID_ARG, m.c_str());
+    }
+    return workspace_for(ctx, static_cast<hipStream_t>(stream), ws, fn);
+}
+bool any_null(int32_t n, const void* const* p) {
+    if (!p) return true;
+    for (int32_t i = 0; i < n; ++i)
+        if (!p[i]) return true;
+    return false;
+}
+}  // namespace
+
+extern "C" int32_t varco_network_taps_fwd(varco_ctx* ctx, int32_t layer, int32_t n_taps, const void* const* y, const void* const* h, void* c,
+                                          varco_stream stream) {
+    const char* fn = "varco_network_taps_fwd";
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    Workspace* ws = nullptr;
+    if (int32_t rc = taps_prologue(ctx, layer, n_taps, stream, fn, &ws)) return rc;
+    if (ctx->net.rows == 0) return VARCO_OK;
+    if (any_null(n_taps, y) || any_null(n_taps, h) || !c) return null_pointer(ctx, fn);
+    const int32_t fi = ctx->widths[layer], fo = ctx->widths[layer + 1], rows = int32_t(ctx->net.rows);
+    const int dt = ctx->dtype;
+    for (int32_t t0 = 0; t0 < n_taps; t0 += kWeightSlots) {
+        const int32_t n = std::min(kWeightSlots, n_taps - t0);
+        GemmArgs g[kWeightSlots];
+        PrepJob jobs[kWeightSlots];
+        int n_jobs = 0;
+        for (int32_t i = 0; i < n; i += 2) {
+            GemmArgs& p = g[i];
+            p.m = rows, p.n = fo, p.k = fi;
+            p.a.ptr = y[t0 + i], p.a.ld = fi, p.a.dtype = dt;
+            p.b.ptr = h[t0 + i], p.b.ld = fo;
+            n_jobs += prep_slot(ctx, *ws, layer, h[t0 + i], fi, fo, true, i, false, p, jobs + n_jobs) ? 1 : 0;
+            if (i + 1 < n) {
+                p.k2 = fi, p.a2 = p.a, p.a2.ptr = y[t0 + i + 1];
+                p.b2.ptr = h[t0 + i + 1], p.b2.ld = fo;
+                n_jobs += prep_slot(ctx, *ws, layer, h[t0 + i + 1], fi, fo, true, i + 1, true, p, jobs + n_jobs) ? 1 : 0;
+            }
+            p.c = c, p.ldc = fo, p.c_dtype = dt;
+            p.accumulate = t0 + i > 0;
+            p.relu = t0 + i + 2 >= n_taps && ctx->act[layer] == VARCO_ACT_RELU;
+        }
+        ctx->prof.interrupt();
+        VARCO_HIP(ctx, varco_launch_prep_weights(jobs, n_jobs, st));
+        for (int32_t i = 0; i < n; i += 2)
+            VARCO_HIP(ctx, varco_launch_gemm(g[i], st, ctx->tag(VARCO_K_GEMM_FWD, 0, 2.0 * double(rows) * fo * (g[i].k + g[i].k2))));
+    }
+    return VARCO_OK;
+}
+
+extern "C" int32_t varco_network_taps_bwd_weight(varco_ctx* ctx, int32_t layer, int32_t n_taps, const void* const* y, const void* dx_out,
+                                                 const void* x_out, void* const* dh, varco_stream stream) {
+    const char* fn = "varco_network_taps_bwd_weight";
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    Workspace* ws = nullptr;
+    if (int32_t rc = taps_prologue(ctx, layer, n_taps, stream, fn, &ws)) return rc;
+    if (ctx->net.rows == 0) return VARCO_OK;
+    const bool relu = ctx->act[layer] == VARCO_ACT_RELU;
+    if (any_null(n_taps, y) || any_null(n_taps, dh) || !dx_out || (relu && !x_out)) return null_pointer(ctx, fn);
+    const int32_t fi = ctx->widths[layer], fo = ctx->widths[layer + 1];
+    const int dt = ctx->dtype;
+    WeightSums sums;
+    for (int32_t i = 0; i < n_taps;) {
+        GemmArgs g;
+        g.m = fi, g.n = fo, g.k = int32_t(ctx->net.rows);
+        g.a.ptr = y[i], g.a.ld = fi, g.a.transposed = true, g.a.dtype = dt;
+        g.b.ptr = dx_out, g.b.gate = relu ? x_out : nullptr, g.b.ld = fo, g.b.dtype = dt;
+        g.c = dh[i], g.ldc = fo;
+        g.accumulate = true;
+        g.f32_terms = dt == VARCO_F32 ? ctx->f32_terms : 0;
+        if (i + 1 < n_taps) {
+            int32_t unused = 0;
+            g.deferred = &unused;
+            g.a_dual = y[i + 1], g.c_dual = dh[i + 1];
+            if (!varco_gemm_dual_usable(g)) g.a_dual = nullptr, g.c_dual = nullptr;
+        }
+        const int32_t products = g.c_dual ? 2 : 1;
+        const size_t want = size_t(wgrad_splits(fi, fo, g.k, gemm_kind(g), products)) * products * fi * fo;
+        if (sums.n > 0 && (sums.used + want > ws->gemm_elems || sums.n + products > kMaxReduceJobs))
+            if (int32_t rc = finish_sums(ctx, sums, st)) return rc;
+        if (int32_t rc = add_weight_product(ctx, *ws, g, sums, st)) return rc;
+        i += products;
+    }
+    return finish_sums(ctx, sums, st);
+}
+
+extern "C" int32_t varco_network_taps_bwd_input(varco_ctx* ctx, int32_t layer, int32_t n_taps, const void* dx_out, const void* x_out,
+                                                const void* const* h, void* const* g_out, varco_stream stream) {
+    const char* fn = "varco_network_taps_bwd_input";
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    Workspace* ws = nullptr;
+    if (int32_t rc = taps_prologue(ctx, layer, n_taps, stream, fn, &ws)) return rc;
+    if (ctx->net.rows == 0) return VARCO_OK;
+    const bool relu = ctx->act[layer] == VARCO_ACT_RELU;
+    if (n_taps > 2) return varco_fail(ctx, VARCO_ERR_INVALID_ARG, "varco_network_taps_bwd_input: one or two taps");
+    if (any_null(n_taps, h) || any_null(n_taps, g_out) || !dx_out || (relu && !x_out)) return null_pointer(ctx, fn);
+    const int32_t fi = ctx->widths[layer], fo = ctx->widths[layer + 1];
+    const int dt = ctx->dtype;
+    GemmArgs g[2];
+    PrepJob jobs[2];
+    int n_jobs = 0;
+    for (int32_t i = 0; i < n_taps; ++i) {
+        g[i].m = int32_t(ctx->net.rows), g[i].n = fi, g[i].k = fo;
+        g[i].a.ptr = dx_out, g[i].a.gate = relu ? x_out : nullptr, g[i].a.ld = fo, g[i].a.dtype = dt;
+        g[i].b.ptr = h[i], g[i].b.ld = fo, g[i].b.transposed = true;
+        g[i].c = g_out[i], g[i].ldc = fi, g[i].c_dtype = dt;
+        g[i].f32_terms = dt == VARCO_F32 ? ctx->f32_terms : 0;
+        if (!varco_gemm_short_usable(g[i]))      // (short reductions take the weights as they are)
+            n_jobs += prep_slot(ctx, *ws, layer, h[i], fi, fo, false, i, false, g[i], jobs + n_jobs) ? 1 : 0;
+    }
+    ctx->prof.interrupt();
+    VARCO_HIP(ctx, varco_launch_prep_weights(jobs, n_jobs, st));
+    int32_t launches = n_taps;
+    if (n_taps == 2) {
+        g[0].b_dual = g[1].b.ptr, g[0].b_dual_prep = g[1].b_prep, g[0].c_dual = g[1].c;
+        if (varco_gemm_dual_usable(g[0]))
+            launches = 1;
+        else
+            g[0].c_dual = nullptr;
+    }
+    for (int32_t i = 0; i < launches; ++i)
+        VARCO_HIP(ctx, varco_launch_gemm(g[i], st, ctx->tag(VARCO_K_GEMM_DGRAD, 0, (g[i].c_dual ? 4.0 : 2.0) * fi * fo * double(g[i].m))));
+    return VARCO_OK;
 }

@@ -386,7 +386,10 @@ class KTapNetwork(PartitionedNetwork):
         f32 = dict(dtype=torch.float32, device=self.device)
         act = dict(dtype=self.act_dtype, device=self.device)
         self.h = [[torch.empty((self.widths[l], self.widths[l + 1]), **f32) for _ in range(n_taps)] for l in range(self.L)]
-        self.dh = [[torch.zeros_like(w) for w in hs] for hs in self.h]
+        sizes = [self.widths[l] * self.widths[l + 1] for l in range(self.L) for _ in range(n_taps)]
+        self._taps_grad = torch.zeros(sum(sizes), **f32)       # one buffer: cleared by one launch
+        flat = iter(self._taps_grad.split(sizes))
+        self.dh = [[next(flat).view(self.widths[l], self.widths[l + 1]) for _ in range(n_taps)] for l in range(self.L)]
         # y[l][hop] = S^hop X_l rows (hop 0 is x[l] itself)
         self.y = [[self.x[l]] + [torch.empty((self.n_total, self.widths[l]), **act) for _ in range(1, n_taps)]
                   for l in range(self.L)]
@@ -399,9 +402,7 @@ class KTapNetwork(PartitionedNetwork):
                 self.h[l][hop].copy_(torch.from_numpy(weights[l][hop]).to(self.device))
 
     def zero_grads(self):
-        for hs in self.dh:
-            for w in hs:
-                w.zero_()
+        self._taps_grad.zero_()
 
     def forward(self, step: int, ratio=None, stream=None):
         ctx = self.ctx
@@ -425,6 +426,9 @@ class KTapNetwork(PartitionedNetwork):
                 for q in range(self.P):
                     r = self.rows(q)
                     ctx.aggregate_fwd(tap, q, src[r], self.z[l], self.y[l][hop][r], stream)
+            if self.linked:
+                ctx.network_taps_fwd(l, self.y[l], self.h[l], self.x[l + 1], stream)
+                continue
             for r in self._blocks():
                 for hop in range(self.K):
                     ctx.transform_fwd(l, self.y[l][hop][r], self.h[l][hop], self.x[l + 1][r], hop > 0, hop == self.K - 1,
@@ -434,23 +438,23 @@ class KTapNetwork(PartitionedNetwork):
         ctx = self.ctx
         for l in range(self.L - 1, -1, -1):
             fi, k = self.widths[l], ctx.keep(l)
+            bufs = [b[:self.n_total * fi].view(self.n_total, fi) for b in self._g]
+            if self.linked:
+                ctx.network_taps_bwd_weight(l, self.y[l], self.dx[l + 1], self.x[l + 1], self.dh[l], stream)
+                if l > 0:
+                    self._input_gradient(l, bufs, stream)
+                continue
             for r in self._blocks():
                 for hop in range(self.K):
                     ctx.transform_bwd_weight(l, self.y[l][hop][r], self.dx[l + 1][r], self.x[l + 1][r], self.dh[l][hop], stream)
             if l == 0:
                 continue
-            bufs = [b[:self.n_total * fi].view(self.n_total, fi) for b in self._g]
             cur = self.dx[l] if self.K == 1 else bufs[0]
             for r in self._blocks():
                 ctx.transform_bwd_input(l, self.dx[l + 1][r], self.x[l + 1][r], self.h[l][self.K - 1], cur[r], False, stream)
             for hop in range(self.K - 1, 0, -1):
                 tap = vb.tap(l, hop)
                 nxt = self.dx[l] if hop == 1 else (bufs[1] if cur is bufs[0] else bufs[0])
-                if self.linked:
-                    ctx.network_aggregate_bwd(tap, cur, nxt, stream)
-                    ctx.transform_bwd_input(l, self.dx[l + 1], self.x[l + 1], self.h[l][hop - 1], nxt, True, stream)
-                    cur = nxt
-                    continue
                 for q in range(self.P):
                     r = self.rows(q)
                     dzh = self.dz_halo[l][int(self.halo_off[q]) * k:] if self.n_halo[q] else None
@@ -461,3 +465,16 @@ class KTapNetwork(PartitionedNetwork):
                         ctx.accumulate_returned(tap, p, self.ret_ptr[p], self.ret_src[p], self.dz_halo[l],
                                                 nxt[self.rows(p)], stream)
                 cur = nxt
+
+    def _input_gradient(self, l, bufs, stream):
+        """dx[l]: every tap's dZ H^T, the hops walked in reverse on top of them. Two taps' products share a call where the
+        second one's place is free (the last hop's sum, still being handed on, takes one of the two buffers)."""
+        ctx, into = self.ctx, lambda t: self.dx[l] if t == 0 else bufs[(self.K - 1 - t) % 2]   # noqa: E731
+        ready = self.K                                       # taps >= ready have their product in place
+        for t in range(self.K - 1, -1, -1):
+            if t < ready:
+                taps = [t, t - 1] if t > 0 and (t == self.K - 1 or t == 1) else [t]
+                ctx.network_taps_bwd_input(l, self.dx[l + 1], self.x[l + 1], [self.h[l][i] for i in taps], [into(i) for i in taps], stream)
+                ready = taps[-1]
+            if t < self.K - 1:
+                ctx.network_aggregate_bwd(vb.tap(l, t + 1), into(t + 1), into(t), True, stream)
