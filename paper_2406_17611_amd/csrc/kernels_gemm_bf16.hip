@@ -248,12 +248,13 @@ bool varco_gemm_bf16_usable(const GemmArgs& ga) {
     if (ga.m <= 0 || ga.n <= 0) return false;
     if (ga.a.transposed) return varco_gemm_tn_bf16_usable(ga);
     if (ga.a.dtype != VARCO_BF16) return false;
-    auto ok2 = [](const GemmOperand& o) { return aligned_to(o.ptr, 2) && aligned_to(o.gate, 2); };
+    // (Other reductions take fp32 matrix instructions and the weights as they are: here the weights are rounded to bf16.)
+    auto ok8 = [](const GemmOperand& o) { return aligned_to(o.ptr, 8) && aligned_to(o.gate, 8) && o.ld % 4 == 0; };
     // needs the library's bf16 weight copy [n][pitch], pitch a multiple of 8
     if (ga.c_dtype != VARCO_BF16 || !ga.b_prep || ga.b_prep_ld % 8 != 0 || !aligned_to(ga.b_prep, 16)) return false;
-    if (ga.b.gate || ga.k < 8 || !ok2(ga.a) || ga.split_k > 1) return false;
-    if (ga.k2 > 0 && (!ga.b2_prep || ga.b2_prep_ld % 8 != 0 || !aligned_to(ga.b2_prep, 16) || ga.k2 < 8 ||
-                      !ok2(ga.a2) || ga.a2.gate || ga.a2.dtype != VARCO_BF16 || ga.a2.transposed))
+    if (ga.b.gate || ga.k < 8 || ga.k % 4 != 0 || !ok8(ga.a) || ga.split_k > 1) return false;
+    if (ga.k2 > 0 && (!ga.b2_prep || ga.b2_prep_ld % 8 != 0 || !aligned_to(ga.b2_prep, 16) || ga.k2 < 8 || ga.k2 % 4 != 0 ||
+                      !ok8(ga.a2) || ga.a2.gate || ga.a2.dtype != VARCO_BF16 || ga.a2.transposed))
         return false;
     return !ga.c_dual || (ga.k2 == 0 && ga.b_dual_prep && aligned_to(ga.b_dual_prep, 16));
 }

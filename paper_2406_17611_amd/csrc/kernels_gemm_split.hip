@@ -112,8 +112,7 @@ __device__ __forceinline__ float4 moved_up(float4 x, int by) {
 // ---- fp32 operand with the reduction index contiguous: chunks of CH floats ----
 // Addresses are a per-tile base (uniform) plus a 32-bit offset per chunk that does not change along the
 // reduction. Rows beyond the matrix are clamped to its last row (their results are never stored); chunks
-// beyond the reduction length re-read the tile's first chunk of the same row, and meet zeros in B. Rows need no alignment
-// and (chunks of 4) any length from 4 on: see moved_up.
+// beyond the reduction length re-read the tile's first chunk of the same row, and meet zeros in B.
 template <int ROWS, int CH, bool GATE>
 struct RowRegs {
     static constexpr int PER_ROW = BK / CH;
@@ -126,13 +125,13 @@ template <int ROWS, int CH>
 struct RowPlan {
     static constexpr int PER_ROW = BK / CH;
     static constexpr int N = ROWS * PER_ROW / kThreads;
-    uint32_t off[N];     // bytes from 4 floats before the tile base: a group moved up may start before it
+    uint32_t off[N];     // bytes from the tile base
     __device__ __forceinline__ void init(int tid, int32_t i0, int32_t extent, int64_t ld) {
 #pragma unroll
         for (int h = 0; h < N; ++h) {
             const int c = tid + h * kThreads;
             const int32_t r = min(tile_row(c / PER_ROW), extent - 1 - i0);
-            off[h] = uint32_t(r * ld + (c % PER_ROW) * CH + 4) * 4u;
+            off[h] = uint32_t(r * ld + (c % PER_ROW) * CH) * 4u;
         }
     }
 };
@@ -144,8 +143,7 @@ __device__ __forceinline__ void load_rows(int tid, const float* base, const floa
 #pragma unroll
     for (int h = 0; h < R::N; ++h) {
         const int kc = ((tid + h * kThreads) % R::PER_ROW) * CH;
-        uint32_t off = kc < k_left ? plan.off[h] : plan.off[h] - uint32_t(kc) * 4u;
-        if (CH == 4 && kc < k_left && kc + 4 > k_left) off -= uint32_t(kc + 4 - k_left) * 4u;
+        const uint32_t off = kc < k_left ? plan.off[h] : plan.off[h] - uint32_t(kc) * 4u;   // k_left is a multiple of CH
 #pragma unroll
         for (int u = 0; u < CH / 4; ++u) {
             r.v[h][u] = load4_at(base, off + 16u * u);
@@ -155,9 +153,8 @@ __device__ __forceinline__ void load_rows(int tid, const float* base, const floa
 }
 
 template <int TERMS, int ROWS, int CH, bool GATE>
-__device__ __forceinline__ void store_rows(int tid, const RowRegs<ROWS, CH, GATE>& r, int32_t k_left, uint16_t* s) {
+__device__ __forceinline__ void store_rows(int tid, const RowRegs<ROWS, CH, GATE>& r, uint16_t* s) {
     using R = RowRegs<ROWS, CH, GATE>;
-    const bool cut = CH == 4 && k_left < BK && (k_left & 3);        // this stage holds the rows' ends, inside a group of four
 #pragma unroll
     for (int h = 0; h < R::N; ++h) {
         const int c = tid + h * kThreads;
@@ -166,7 +163,6 @@ __device__ __forceinline__ void store_rows(int tid, const RowRegs<ROWS, CH, GATE
         for (int u = 0; u < CH / 4; ++u) {
             float4 x = r.v[h][u];
             if (GATE) x = gate4(x, r.g[h][u]);
-            if (cut && (c % R::PER_ROW) * CH == (k_left & ~3)) x = moved_up(x, 4 - (k_left & 3));
             expand_pair<TERMS>(x.x, x.y, w[2 * u]);
             expand_pair<TERMS>(x.z, x.w, w[2 * u + 1]);
         }
@@ -371,13 +367,11 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_split_kernel(SplitGemm g) {
         plan_b.init(tid);
     }
 
-    int32_t held = 0;                             // reduction steps from the fetched stage's start to the end
     auto fetch = [&](int32_t t) {                 // NT
         const bool first = t < tiles1;
         const int32_t k0 = (first ? t : t - tiles1) * BK, k_left = (first ? g.k : g.k2) - k0;
-        held = k_left;
-        const float* abase = static_cast<const float*>(first ? a_ptr : g.a2.ptr) + int64_t(m0) * g.a.ld + k0 - 4;
-        const float* gbase = GATE ? g.a.gate + int64_t(m0) * g.a.ld + k0 - 4 : nullptr;   // never with a second product
+        const float* abase = static_cast<const float*>(first ? a_ptr : g.a2.ptr) + int64_t(m0) * g.a.ld + k0;
+        const float* gbase = GATE ? g.a.gate + int64_t(m0) * g.a.ld + k0 : nullptr;   // never with a second product
         const uint16_t* bbase = static_cast<const uint16_t*>(first ? b_ptr : g.b2.ptr) +
                                 (int64_t(tn) * (g.b.ld / BK) + k0 / BK) * (TERMS * BN * BK);      // g.b.ld: padded reduction length
         if constexpr (!TN) {
@@ -387,7 +381,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_split_kernel(SplitGemm g) {
     };
     auto stash = [&]() {                          // NT
         if constexpr (!TN) {
-            store_rows<TERMS, BM, A_CH, GATE>(tid, ra, held, sa);
+            store_rows<TERMS, BM, A_CH, GATE>(tid, ra, sa);
             store_prep<TERMS, BN>(tid, rb, sb);
         }
     };
@@ -865,10 +859,12 @@ bool varco_gemm_split_usable(const GemmArgs& ga) {
             return p && aligned_to(p, 16) && ld % BK == 0 && ld >= k && plane == (int64_t(ga.n) + kPrepRows - 1) / kPrepRows * kPrepRows * ld;
         };
         if (!prep_ok(ga.b_prep, ga.b_prep_ld, ga.b_prep_plane, ga.k)) return false;
-        if (ga.b.gate || ga.k < 4 || !ok4(ga.a)) return false;
+        // (Other reductions keep fp32 matrix instructions: the same sums in the same order as ever, so that a ReLU whose
+        // argument is within rounding of zero opens as it did.)
+        if (ga.b.gate || ga.k % 4 != 0 || !ok4(ga.a)) return false;
         if (ga.k2 > 0) {   // a chained product shares the first one's leading dimensions and is never masked
             if (!prep_ok(ga.b2_prep, ga.b2_prep_ld, ga.b2_prep_plane, ga.k2) || ga.b2_prep_ld != ga.b_prep_ld) return false;
-            if (ga.k2 < 4 || !ok4(ga.a2) || ga.a2.ld != ga.a.ld || ga.a.gate || ga.a2.gate || ga.a2.dtype != VARCO_F32 ||
+            if (ga.k2 % 4 != 0 || !ok4(ga.a2) || ga.a2.ld != ga.a.ld || ga.a.gate || ga.a2.gate || ga.a2.dtype != VARCO_F32 ||
                 ga.a2.transposed)
                 return false;
         }

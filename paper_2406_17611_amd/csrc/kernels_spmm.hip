@@ -321,22 +321,15 @@ __global__ __launch_bounds__(agg_block(MODE), MODE >= kSparse && VEC * NV <= 8 ?
         }
     }
 
-    if (SPARSE && any_sparse) {          // the private rows: each group of lanes adds some of them
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-#pragma unroll
-        for (int m = 0; m < NR; ++m) {
-            const int c = NV == 0 ? VEC * (lane & ((1 << p.lpr_log2) - 1)) : VEC * (lane + 64 * m);
-            if (c < width)
-                for (int sub = NV == 0 ? lane >> p.lpr_log2 : 0; sub < p.epi; sub += NV == 0 ? 64 >> p.lpr_log2 : 1)
-                    add_floats<VEC>(lds + sub * width + c, acc[m]);
-        }
-    }
     sum_groups<VEC, NV>(p.lpr_log2, acc);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     if (NV == 0 && lane >= (1 << p.lpr_log2)) return;
 #pragma unroll
     for (int m = 0; m < NR; ++m) {
         const int c = VEC * (lane + 64 * m);
         if (c < width) {
+            if (SPARSE && any_sparse)
+                for (int sub = 0; sub < p.epi; ++sub) add_floats<VEC>(lds + sub * width + c, acc[m]);
             if (it.dst < 0)
                 Packed<T, VEC>::put(p.out + int64_t(it.row - p.row_base) * width + c, acc[m]);
             else

@@ -616,8 +616,10 @@ extern "C" int32_t varco_network_aggregate_bwd(varco_ctx* ctx, int32_t tap, cons
     return aggregate_bwd(ctx, *ws, layer, make_rule(ctx, layer, hop), g_out, g_in, accumulate != 0, static_cast<hipStream_t>(stream));
 }
 
-// The dense products of all taps of a layer over the arena. Two taps share a launch where the kernels can: chained reductions
-// forward, products that share dZ backward; the copies of all weights are made by one launch (as many as there are slots).
+// The dense products of all taps of a layer over the arena. The copies of all weights are made by one launch (as many as there
+// are slots); backward, the products of two taps, which share dZ, are formed by one launch where the kernels can. (Forward,
+// chaining the reductions of two taps would save a pass over the outputs, 4 % of a K-tap step, but form the sums in another
+// order than varco_transform_fwd, and round them once less with bf16 storage.)
 namespace {
 int32_t taps_prologue(varco_ctx* ctx, int32_t layer, int32_t n_taps, varco_stream stream, const char* fn, Workspace** ws) {
     if (int32_t rc = check_linked(ctx, fn)) return rc;
@@ -651,25 +653,19 @@ extern "C" int32_t varco_network_taps_fwd(varco_ctx* ctx, int32_t layer, int32_t
         GemmArgs g[kWeightSlots];
         PrepJob jobs[kWeightSlots];
         int n_jobs = 0;
-        for (int32_t i = 0; i < n; i += 2) {
+        for (int32_t i = 0; i < n; ++i) {
             GemmArgs& p = g[i];
             p.m = rows, p.n = fo, p.k = fi;
             p.a.ptr = y[t0 + i], p.a.ld = fi, p.a.dtype = dt;
             p.b.ptr = h[t0 + i], p.b.ld = fo;
             n_jobs += prep_slot(ctx, *ws, layer, h[t0 + i], fi, fo, true, i, false, p, jobs + n_jobs) ? 1 : 0;
-            if (i + 1 < n) {
-                p.k2 = fi, p.a2 = p.a, p.a2.ptr = y[t0 + i + 1];
-                p.b2.ptr = h[t0 + i + 1], p.b2.ld = fo;
-                n_jobs += prep_slot(ctx, *ws, layer, h[t0 + i + 1], fi, fo, true, i + 1, true, p, jobs + n_jobs) ? 1 : 0;
-            }
             p.c = c, p.ldc = fo, p.c_dtype = dt;
             p.accumulate = t0 + i > 0;
-            p.relu = t0 + i + 2 >= n_taps && ctx->act[layer] == VARCO_ACT_RELU;
+            p.relu = t0 + i + 1 == n_taps && ctx->act[layer] == VARCO_ACT_RELU;
         }
         ctx->prof.interrupt();
         VARCO_HIP(ctx, varco_launch_prep_weights(jobs, n_jobs, st));
-        for (int32_t i = 0; i < n; i += 2)
-            VARCO_HIP(ctx, varco_launch_gemm(g[i], st, ctx->tag(VARCO_K_GEMM_FWD, 0, 2.0 * double(rows) * fo * (g[i].k + g[i].k2))));
+        for (int32_t i = 0; i < n; ++i) VARCO_HIP(ctx, varco_launch_gemm(g[i], st, ctx->tag(VARCO_K_GEMM_FWD, 0, 2.0 * double(rows) * fo * fi)));
     }
     return VARCO_OK;
 }
