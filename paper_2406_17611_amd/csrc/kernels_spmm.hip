@@ -902,7 +902,9 @@ hipError_t launch_spmm_nv(int nv, const SpmmArgs<T>& a, dim3 grid, size_t lds_by
         return hipGetLastError();
     };
     switch (nv) {
-        case 0: return go(std::integral_constant<int, 0>{});
+        case 0:
+            if constexpr (VEC < 8) return go(std::integral_constant<int, 0>{});
+            break;
         case 1: return go(std::integral_constant<int, 1>{});
         case 2: return go(std::integral_constant<int, 2>{});
         case 4: return go(std::integral_constant<int, 4>{});
@@ -945,7 +947,9 @@ hipError_t spmm_t(const SpmmPlan& plan, const VarcoEdge* edge, const int32_t* co
                (!(halo && full) || aligned_to(z, v * sizeof(T)));
     };
     const bool vec4 = vec_ok(4);
-    const int vec = sizeof(T) == 2 && vec_ok(8) ? 8 : vec4 ? 4 : 1;
+    // bf16: 16-byte loads where a row then still takes all lanes. (Narrower rows would have twice as many lane groups, and the
+    // forward sums another order.)
+    const int vec = sizeof(T) == 2 && width > 256 && vec_ok(8) ? 8 : vec4 ? 4 : 1;
     const int per_row = (width + vec - 1) / vec;   // loads of VEC elements that cover a row
     int lpr_log2 = 0;
     while ((1 << lpr_log2) < per_row && lpr_log2 < 6) ++lpr_log2;
