@@ -9,7 +9,7 @@ from test_gpu_network import BF16_TOL, _compare_network
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("n,fi,fo", [(1000, 75, 200), (129, 131, 129), (517, 201, 77), (33, 33, 67), (40, 5, 6), (300, 98, 130), (4, 4, 257)])
+@pytest.mark.parametrize("n,fi,fo", [(1000, 75, 200), (129, 131, 129), (517, 201, 77), (33, 33, 67), (40, 5, 6), (300, 98, 130), (4, 4, 257), (131, 3, 2), (70, 2, 131)])
 def test_products_of_odd_widths(n, fi, fo):
     check_products(n, fi, fo, 3)
 
