@@ -326,32 +326,36 @@ __global__ __launch_bounds__(kThreads, 4) void gemm_kernel(GemmDev g) {
     }
 }
 
+__device__ __forceinline__ double sum8(const float (&v)[8]) {
+    return ((double(v[0]) + v[1]) + (double(v[2]) + v[3])) + ((double(v[4]) + v[5]) + (double(v[6]) + v[7]));
+}
+
 // Sum over `splits` partial products of element i. 64 consecutive output elements per workgroup; the four wavefronts sum
 // interleaved quarters of the splits (eight loads in flight each) and the quarters are added in a fixed order, so the
-// result does not depend on scheduling. Valid in the first wavefront.
+// result does not depend on scheduling. Summed in fp64: the pass is bound by reading the partial products, and there may be
+// thousands. Valid in the first wavefront.
 __device__ __forceinline__ float sum_splits(const float* partial, int32_t splits, int64_t mn, int64_t i, bool in) {
-    __shared__ float part[4][64];
+    __shared__ double part[4][64];
     const int e = threadIdx.x & 63, quarter = threadIdx.x >> 6;
-    float x = 0.f;
+    double x = 0.0;
     if (in) {
         int32_t s = quarter;
         for (; s + 28 < splits; s += 32) {
             float v[8];
 #pragma unroll
             for (int u = 0; u < 8; ++u) v[u] = partial[int64_t(s + 4 * u) * mn + i];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) x += v[u];
+            x += sum8(v);
         }
-        float v[7];                     // the rest, fetched together as well (slots past the end re-read slot 0 and are dropped)
+        float v[8];                     // the rest, fetched together as well (slots past the end re-read slot 0 and are dropped)
 #pragma unroll
         for (int u = 0; u < 7; ++u) v[u] = partial[int64_t(s + 4 * u < splits ? s + 4 * u : 0) * mn + i];
 #pragma unroll
-        for (int u = 0; u < 7; ++u)
-            if (s + 4 * u < splits) x += v[u];
+        for (int u = 0; u < 8; ++u) v[u] = u < 7 && s + 4 * u < splits ? v[u] : 0.f;
+        x += sum8(v);
     }
     part[quarter][e] = x;
     __syncthreads();
-    return ((part[0][e] + part[1][e]) + part[2][e]) + part[3][e];
+    return float(((part[0][e] + part[1][e]) + part[2][e]) + part[3][e]);
 }
 
 // C (+)= sum over splits of partial[s].

@@ -19,6 +19,12 @@
 //        one; a thread loads an 8 (nodes) x 4 (columns) block with eight 16-byte loads and expands the values of
 //        two consecutive nodes of a column together, which yields the transposed (node index contiguous) words
 //        directly; it writes four 16-byte LDS rows per plane. Half the threads serve A, half B.
+//        When the matrix unit adds products far below the accumulator (five of the six here), what falls off the end
+//        is dropped towards minus infinity: measured, 98 % of the error of a long sum is its mean, always negative.
+//        So every second slab of rows multiplies -B and its sum changes sign in the epilogue, which lets the halves
+//        cancel. Relative error against fp64 of independent products, 256 x 256, 128 slabs: 2,449,029 rows 8.8e-6
+//        without, 2.0e-6 with; 169,343 rows 8.6e-7 and 5.4e-7. (A loop of its own for -B, the minus an operand modifier
+//        of the conversion, takes the same time.)
 // The ReLU mask of the backward pass is applied before the expansion, the activation in the epilogue.
 #include <algorithm>
 #include <type_traits>
@@ -250,8 +256,11 @@ __device__ __forceinline__ void load_cols(const float* base, const float* gate, 
     }
 }
 
-template <int TERMS, int ROWS, bool GATE>
-__device__ __forceinline__ void store_cols(const ColRegs<GATE>& r, int b, int32_t i0, int32_t extent, uint16_t* s) {
+__device__ __forceinline__ float with_sign(float x, uint32_t sign) { return __uint_as_float(__float_as_uint(x) ^ sign); }
+
+// SIGNED: the values change sign when `sign` holds a sign bit.
+template <int TERMS, int ROWS, bool GATE, bool SIGNED>
+__device__ __forceinline__ void store_cols(const ColRegs<GATE>& r, int b, int32_t i0, int32_t extent, uint32_t sign, uint16_t* s) {
     const bool crosses = (extent & 3) && i0 + (b >> 2) * 4 == (extent & ~3);
     // An LDS row holds one output index with its 8 reduction steps contiguous, two steps per 32-bit word: the two
     // values expanded together are steps 2 q and 2 q + 1 of one output index, which is the transposition itself.
@@ -261,6 +270,7 @@ __device__ __forceinline__ void store_cols(const ColRegs<GATE>& r, int b, int32_
         float4 v = r.v[kk];
         if constexpr (GATE) v = gate4(v, r.g[kk]);
         if (extent & 3) v = crosses ? moved_up(v, 4 - (extent & 3)) : v;
+        if constexpr (SIGNED) v = make_float4(with_sign(v.x, sign), with_sign(v.y, sign), with_sign(v.z, sign), with_sign(v.w, sign));
         x[kk][0] = v.x, x[kk][1] = v.y, x[kk][2] = v.z, x[kk][3] = v.w;
     }
     uint16_t* base = s + (b >> 2) * 4 * kPitch + (b & 3) * 8;
@@ -341,6 +351,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_split_kernel(SplitGemm g) {
     }
     const void* const a_ptr = TN && second ? g.dual : g.a.ptr;
     const void* const b_ptr = !TN && second ? g.dual : g.b.ptr;
+    const uint32_t sign = TN && (z & 1) ? 0x80000000u : 0u;       // set: this slab forms -C (see the head of this file)
     const int32_t steps = max(t_end - t_begin, 0);
     const int32_t m0 = tm * BM, n0 = tn * BN;
 
@@ -447,7 +458,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_split_kernel(SplitGemm g) {
                 else
                     load_cols<G, true, A>(base, gbase, b, col_off, ld_bytes, k_left, cr);
             };
-            pipeline(fetch_cols, [&]() { store_cols<TERMS, A ? BM : BN, G>(cr, b, A ? m0 : n0, A ? g.m : g.n, A ? sa : sb); });
+            pipeline(fetch_cols, [&]() { store_cols<TERMS, A ? BM : BN, G, !A>(cr, b, A ? m0 : n0, A ? g.m : g.n, sign, A ? sa : sb); });
         };
         if (role == 0)
             run(std::true_type{});
@@ -459,6 +470,12 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_split_kernel(SplitGemm g) {
         pipeline(fetch, stash);
     }
     if (steps == 0) return;
+    if (sign) {
+#pragma unroll
+        for (int i = 0; i < TMB; ++i)
+#pragma unroll
+            for (int j = 0; j < TNB; ++j) acc[i][j] = -acc[i][j];
+    }
 
     // epilogue: accumulator register v of a lane is element (8 * (v / 4) + 4 * (lane / 32) + v % 4, lane % 32).
     // A tile that lies wholly inside C (all but the last row and column of tiles) is stored through one scalar

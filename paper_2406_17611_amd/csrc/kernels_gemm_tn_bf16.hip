@@ -1,15 +1,16 @@
 // Weight gradients of bf16-stored activations: C[m x n] = sum over rows r of A[r, i] B[r, j] (both operands row-major with the
-// reduction index slow), optionally with a ReLU mask on B, in fp32 on the matrix cores (v_mfma_f32_32x32x16_bf16).
+// reduction index slow), optionally with a ReLU mask on B, in fp32 on the matrix cores (v_mfma_f32_16x16x32_bf16).
 //
 // Both operands go to LDS as they lie in memory, rows of one reduction index, with 16-byte loads and writes, and are
-// transposed when they are read: ds_read_b64_tr_b16 hands lane i of a group of 16 the i-th column of a 4 x 16 block. The
-// kernel in kernels_gemm_bf16.hip transposes 8 x 4 blocks in registers instead (eight 8-byte loads, 32 word operations and as
-// many selects per block and thread); its stage of 32 rows moved as many bytes through the vector memory unit (64 bytes per
-// cycle) as its 256 x 128 tile could multiply in that time. A 256 x 256 tile takes 3/4 of the bytes per product.
+// transposed when they are read: ds_read_b64_tr_b16 hands lane i of a group of 16 the i-th column of a 4 x 16 block. (Transposing
+// 8 x 4 blocks in registers instead takes eight 8-byte loads, 32 word operations and as many selects per block and thread, and
+// a stage of 32 rows then moves as many bytes through the vector memory unit, 64 bytes per cycle, as a 256 x 128 tile can
+// multiply in that time; a 256 x 256 tile takes 3/4 of the bytes per product.)
 // Row pitch in LDS: 64 bytes more than a multiple of 256, so that the four rows that a group of lanes reads start in four
 // different quarters of the banks.
 // Bound by reading A, B and the mask once (the tiles of one slab of rows run on one XCD and share them through its L2).
-// 169,343 rows, 512 x 512, masked: 163 us with stages of 32 rows, 142 with 64 (620 TFLOP/s); that kernel took 270.
+// 169,343 rows, 512 x 512, masked: transposed in registers 270 us, 163 with stages of 32 rows, 142 with 64; 2,449,029 rows in 64
+// slabs: 1.93 ms with 32 x 32 x 16 blocks, 1.81 with 16 x 16 x 32 (710 TFLOP/s).
 #include <algorithm>
 #include <type_traits>
 
@@ -20,7 +21,7 @@ namespace {
 
 constexpr int kThreads = 512;
 
-typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef short shortx4 __attribute__((ext_vector_type(4)));
 
@@ -122,7 +123,7 @@ struct ElementSlab {
 template <int W, bool FEW, bool ANY, bool GATE, int BK>
 using SlabOf = std::conditional_t<FEW, ElementSlab<BK>, Slab<W, ANY, GATE, BK>>;
 
-// Fragment of 32 columns x 16 rows whose first column's element of row 0 (this lane's share of the block) is at LDS byte `at`.
+// Fragment of 16 columns x 32 rows whose first column's element of row 0 (this lane's share of the block) is at LDS byte `at`.
 template <int PITCH>
 __device__ __forceinline__ bf16x8 fragment(uint32_t at) {
     using P = __attribute__((address_space(3))) shortx4*;
@@ -154,17 +155,16 @@ __global__ __launch_bounds__(kThreads, TMB * TNB > 4 ? 2 : 4) void gemm_tn_bf16_
 
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int wm = (wave / WN) * (32 * TMB), wn = (wave % WN) * (32 * TNB);
-    floatx16 acc[TMB][TNB];
+    constexpr int NA = 2 * TMB, NB = 2 * TNB;                           // blocks of 16 x 16 per wavefront
+    floatx4 acc[NA][NB];
 #pragma unroll
-    for (int i = 0; i < TMB; ++i)
+    for (int i = 0; i < NA; ++i)
 #pragma unroll
-        for (int j = 0; j < TNB; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+        for (int j = 0; j < NB; ++j) acc[i][j] = floatx4(0.f);
 
-    // this lane's share of a 4 x 16 block: row (lane / 4) % 4, columns 4 (lane % 4) ..; groups of 16 lanes: columns 0 and 16, rows
-    // 0 and 8 of the fragment
-    const uint32_t row = 8 * (lane >> 5) + ((lane >> 2) & 3), sub = 32 * ((lane >> 4) & 1) + 8 * (lane & 3);
+    // this lane's share of a 4 x 16 block: row (lane / 4) % 4, columns 4 (lane % 4) ..; group g of 16 lanes: rows 8 g of the
+    // fragment
+    const uint32_t row = 8 * (lane >> 4) + ((lane >> 2) & 3), sub = 8 * (lane & 3);
     const uint32_t base = uint32_t(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) char*)lds));
     const uint32_t at_a = base + row * SA::PITCH + sub + wm * 2, at_b = base + 2 * kA + row * SB::PITCH + sub + wn * 2;
 
@@ -187,16 +187,16 @@ __global__ __launch_bounds__(kThreads, TMB * TNB > 4 ? 2 : 4) void gemm_tn_bf16_
             sb.load(g.b, g.gate, g.ldb, (s + 1) * BK, g.k);
         }
 #pragma unroll
-        for (int h = 0; h < BK / 16; ++h) {
-            bf16x8 fa[TMB], fb[TNB];
+        for (int h = 0; h < BK / 32; ++h) {
+            bf16x8 fb[NB];
 #pragma unroll
-            for (int i = 0; i < TMB; ++i) fa[i] = fragment<SA::PITCH>(at_a + buf * kA + h * 16 * SA::PITCH + i * 64);
+            for (int j = 0; j < NB; ++j) fb[j] = fragment<SB::PITCH>(at_b + buf * kB + h * 32 * SB::PITCH + j * 32);
 #pragma unroll
-            for (int j = 0; j < TNB; ++j) fb[j] = fragment<SB::PITCH>(at_b + buf * kB + h * 16 * SB::PITCH + j * 64);
+            for (int i = 0; i < NA; ++i) {
+                const bf16x8 fa = fragment<SA::PITCH>(at_a + buf * kA + h * 32 * SA::PITCH + i * 32);
 #pragma unroll
-            for (int i = 0; i < TMB; ++i)
-#pragma unroll
-                for (int j = 0; j < TNB; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i], fb[j], acc[i][j], 0, 0, 0);
+                for (int j = 0; j < NB; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa, fb[j], acc[i][j], 0, 0, 0);
+            }
         }
         if (more) {
             sa.store(lds + (buf ^ 1u) * kA, (s + 1) * BK, g.k);
@@ -205,17 +205,17 @@ __global__ __launch_bounds__(kThreads, TMB * TNB > 4 ? 2 : 4) void gemm_tn_bf16_
         __syncthreads();
     }
 
-    // accumulator register v of a lane is element (8 * (v / 4) + 4 * (lane / 32) + v % 4, lane % 32)
+    // accumulator register v of a lane is element (4 * (lane / 16) + v, lane % 16)
     float* const out = g.split_k > 1 ? g.partial + (int64_t(second ? g.split_k : 0) + z) * g.m * g.n : second ? g.c_dual : g.c;
     const int64_t ldo = g.split_k > 1 ? g.n : g.ldc;
     const bool add_old = g.split_k <= 1 && g.accumulate;
 #pragma unroll
-    for (int i = 0; i < TMB; ++i)
+    for (int i = 0; i < NA; ++i)
 #pragma unroll
-        for (int j = 0; j < TNB; ++j)
+        for (int j = 0; j < NB; ++j)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int32_t r = m0 + wm + i * 32 + 4 * (lane >> 5) + 8 * (v >> 2) + (v & 3), c = n0 + wn + j * 32 + (lane & 31);
+            for (int v = 0; v < 4; ++v) {
+                const int32_t r = m0 + wm + i * 16 + 4 * (lane >> 4) + v, c = n0 + wn + j * 16 + (lane & 15);
                 if (r < g.m && c < g.n) {
                     float* const p = out + int64_t(r) * ldo + c;
                     *p = add_old ? *p + acc[i][j][v] : acc[i][j][v];

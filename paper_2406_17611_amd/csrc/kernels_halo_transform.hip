@@ -445,7 +445,7 @@ hipError_t varco_launch_halo_transform_wgrad(const HaloTransform& h, const void*
     const int64_t fit = partial_elems / (int64_t(h.width) * h.fo);
     if (fit < 1) return hipErrorInvalidValue;
     const HaloRows p = device_args(h);
-    const dim3 grid(grid_for(h.n, kTileT, std::min<int64_t>(kHaloTransformGroups, fit))), block(kThreads);
+    const dim3 grid(grid_for(h.n, kTileT, std::min(varco_halo_transform_shares(h.n), fit))), block(kThreads);
     *slabs = int32_t(grid.x);
     if (h.k % 8 == 0 && aligned16(h.z))
         hipLaunchKernelGGL(halo_transform_wgrad_kernel<8>, grid, block, 0, stream, p, static_cast<const uint16_t*>(dy), partial);

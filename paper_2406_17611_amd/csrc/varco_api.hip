@@ -288,7 +288,7 @@ void transform_first_need(const varco_ctx* ctx, size_t* rows_out, size_t* record
     for (int32_t l = 0; l < ctx->n_layers; ++l)
         if (ctx->layers[l].order == VARCO_ORDER_TRANSFORM_FIRST) {
             fo = std::max(fo, ctx->widths[l + 1]);
-            if (ctx->net.linked) *shares_out = std::max(*shares_out, size_t(kHaloTransformGroups) * size_t(ctx->widths[l]) * size_t(ctx->widths[l + 1]));
+            if (ctx->net.linked) *shares_out = std::max(*shares_out, size_t(varco_halo_transform_shares(ctx->net.boundary)) * size_t(ctx->widths[l]) * size_t(ctx->widths[l + 1]));
         }
     int64_t rows = 0, halo = 0;
     for (const PartState& ps : ctx->parts)

@@ -39,6 +39,7 @@ struct PartState {
 struct NetState {
     bool linked = false;
     int64_t rows = 0, nnz = 0, nnz_local = 0, nnz_cross = 0, halo_rows = 0, boundary = 0;
+    int64_t largest = 0;              // rows of the largest partition
     std::vector<int64_t> row_off, halo_off;   // first arena row / halo row of every partition, and the total
     SpmmPlan fwd;                     // the partitions' forward work lists, one after the other
     VarcoEdge* edges = nullptr;       // [nnz] {arena row, -1} or {compressed-buffer row, node id}

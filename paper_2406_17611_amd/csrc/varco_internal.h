@@ -289,7 +289,13 @@ struct HaloTransform {
     int32_t ldy = 0;              // elements between rows of y / dy (0: fo)
 };
 
-constexpr int kHaloTransformGroups = 512;      // most workgroups (shares of a weight gradient) of a launch: two per compute unit
+constexpr int kHaloTransformGroups = 512;      // workgroups that are resident at a time: two per compute unit
+// Most shares of a weight gradient over n rows: whole rounds of workgroups, none summing more than 1,024 rows (the error of an
+// fp32 sum grows with the square root of its length).
+inline int64_t varco_halo_transform_shares(int64_t n) {
+    constexpr int64_t round = int64_t(kHaloTransformGroups) * 1024;
+    return kHaloTransformGroups * (n > round ? (n + round - 1) / round : 1);
+}
 
 // The same layer for all partitions at once (kernels_class_first.hip): rows of Y, G and dZ take kClassPitch elements.
 constexpr int kClassPitch = 64;

@@ -17,6 +17,8 @@ namespace {
 constexpr int32_t kNodeLocal = 64, kNodeCross = 128;
 // Largest product buffer (bytes); beyond it the masked form is used, which needs none.
 constexpr double kProdBytes = 48.0 * (1ull << 30);
+// Most floats of partial products that one launch writes out for the sake of shorter sums (4 GiB).
+constexpr int64_t kPartialElems = int64_t(1) << 30;
 
 // Products of k values per cross entry are written and read back (2 k elements at about 4.8 TB/s), or whole rows are
 // gathered (width elements at about 7 TB/s).
@@ -33,12 +35,27 @@ size_t prod_floats(const varco_ctx* ctx, int32_t layer) {
     return (size_t(ctx->net.nnz_cross) * size_t(product_pitch(ctx, layer)) * size_t(ctx->elem_bytes()) + 3) / 4;
 }
 
-// Split of a weight gradient's reduction over the arena's rows: one round of resident workgroups, at least two
+// Split of a weight gradient's reduction over the arena's rows: whole rounds of resident workgroups, at least two
 // stages of 32 rows each. (The per-partition calls stop at eight stages: with few rows - 2,000 rows and a 32 x 8 weight
 // matrix - a handful of workgroups then walks a chain of round trips while the device idles, 16 us against 6.)
-int32_t wgrad_splits(int32_t m, int32_t n, int64_t rows, int kind, int products) {
+// The fp32 sum of a slab loses accuracy with the square root of its length, so there are as many rounds as keep the result
+// no less accurate than the partitions' gradients formed one after the other (by fp32 sums over the slabs of each). Those have
+// slabs of `alone` rows; the longest ones here are as long with fp32 instructions; longer with expanded operands, by a factor
+// that grows with the rows as the drift grew that slabs of alternating sign are free of (kernels_gemm_split.hip); 900 rows and
+// 28 per partition with bf16, where the sums over slabs and partitions, exact now, were most of the error. Relative error against fp64 of independent products, partition after
+// partition / one round / now (and the time of the last two):
+//   fp32  256 x 256   2,449,029 rows, 8 parts   3.4e-6 / 8.8e-6 / 2.0e-6  (one round)
+//                     169,343 rows, 4 parts     4.7e-7 / 8.6e-7 / 3.8e-7  (170, 180 us)
+//   bf16  512 x 512   2,449,029 rows, 32 parts  2.1e-7 / 1.2e-6 / 2.0e-7  (1.81, 2.30 ms)
+//                     169,343 rows, 4 parts     1.5e-7 / 2.6e-7 / 1.3e-7  (158, 210 us: writing and reading the partial products)
+int32_t wgrad_splits(const varco_ctx* ctx, int32_t m, int32_t n, int64_t rows, int kind, int products) {
     const int64_t step = kind == kGemmF32 ? 16 : 32;
-    return int32_t(std::min<int64_t>(wgrad_slots(m, n, kind, products), std::max<int64_t>(1, (rows + step - 1) / step / 2)));
+    const int64_t slots = wgrad_slots(m, n, kind, products);
+    const int64_t alone = ctx->net.largest / gemm_split_for(m, n, ctx->net.largest, kind);
+    const int64_t longest = kind == kGemmExpanded ? alone * (137'500 + rows) / 110'000 : kind == kGemmBf16 ? 900 + 28 * std::min(ctx->n_parts, 32) : alone;
+    const int64_t round = slots * std::max<int64_t>(1, longest);
+    const int64_t rounds = std::max<int64_t>(1, std::min((rows + round - 1) / round, kPartialElems / (slots * products * m * n)));
+    return int32_t(std::min<int64_t>(rounds * slots, std::max<int64_t>(1, (rows + step - 1) / step / 2)));
 }
 
 template <typename P>
@@ -71,6 +88,7 @@ int32_t link_impl(varco_ctx* ctx) {
         if (ps.d.n_boundary > 0 && !ps.d.ret_ptr)
             return varco_fail(ctx, VARCO_ERR_UNSUPPORTED, "varco_link_partitions: a partition has no map of returned rows");
         net.row_off[q + 1] = net.row_off[q] + ps.d.n_local;
+        net.largest = std::max<int64_t>(net.largest, ps.d.n_local);
         net.halo_off[q + 1] = net.halo_off[q] + ps.d.n_halo;
         net.boundary += ps.d.n_boundary;
         ent += ps.d.nnz, local += ps.nnz_t_local;
@@ -170,13 +188,13 @@ int32_t link_impl(varco_ctx* ctx) {
     // workspace: dM over the arena, partial rows, partial products of the weight gradients
     const int32_t wmax = *std::max_element(ctx->widths.begin(), ctx->widths.end());
     int64_t gemm_elems = 0;
-    for (int32_t l = 0; l < ctx->n_layers; ++l) {
-        int64_t layer_elems = 0;
-        for (int kind : {kGemmF32, kGemmBf16, kGemmExpanded}) {
-            const int64_t fi = ctx->widths[l], fo = ctx->widths[l + 1];
-            layer_elems = std::max<int64_t>(layer_elems, wgrad_splits(int32_t(fi), int32_t(fo), net.rows, kind, 1) * fi * fo);
-        }
-        gemm_elems += layer_elems * (ctx->conv == VARCO_CONV_SAGE ? 2 : 1);   // the partial products of all layers wait for one sum
+    for (int32_t l = 0; l < ctx->n_layers; ++l) {     // the partial products of all layers wait for one sum
+        const int32_t fi = ctx->widths[l], fo = ctx->widths[l + 1];
+        int64_t splits = 0;                           // of one tap, or of two taps that share a launch (any context's K-tap layers)
+        for (int kind : {kGemmF32, kGemmBf16, kGemmExpanded})
+            splits = std::max<int64_t>({splits, (ctx->conv == VARCO_CONV_SAGE ? 2 : 1) * int64_t(wgrad_splits(ctx, fi, fo, net.rows, kind, 1)),
+                                        2 * int64_t(wgrad_splits(ctx, fi, fo, net.rows, kind, 2))});
+        gemm_elems += splits * fi * fo;
     }
     ctx->need_dm = std::max(ctx->need_dm, (size_t(net.rows) * size_t(wmax) * size_t(ctx->elem_bytes()) + 3) / 4);
     ctx->need_spmm = std::max(ctx->need_spmm, size_t(std::max<int64_t>(net.fwd.n_partials, n_slots)) * size_t(std::max(wmax, kClassPitch)));
@@ -326,7 +344,7 @@ int32_t add_weight_product(varco_ctx* ctx, Workspace& ws, GemmArgs& g, WeightSum
     const size_t one = size_t(g.m) * g.n;
     int32_t split = 1;
     g.deferred = &split;
-    g.split_k = wgrad_splits(g.m, g.n, g.k, gemm_kind(g), products);
+    g.split_k = wgrad_splits(ctx, g.m, g.n, g.k, gemm_kind(g), products);
     if (sums.used + size_t(g.split_k) * one * products > ws.gemm_elems || sums.n + products > kMaxReduceJobs)
         return varco_fail(ctx, VARCO_ERR_STATE, "varco_network_backward: workspace too small");
     g.partial = ws.gemm + sums.used;
@@ -697,7 +715,7 @@ extern "C" int32_t varco_network_taps_bwd_weight(varco_ctx* ctx, int32_t layer, 
             if (!varco_gemm_dual_usable(g)) g.a_dual = nullptr, g.c_dual = nullptr;
         }
         const int32_t products = g.c_dual ? 2 : 1;
-        const size_t want = size_t(wgrad_splits(fi, fo, g.k, gemm_kind(g), products)) * products * fi * fo;
+        const size_t want = size_t(wgrad_splits(ctx, fi, fo, g.k, gemm_kind(g), products)) * products * fi * fo;
         if (sums.n > 0 && (sums.used + want > ws->gemm_elems || sums.n + products > kMaxReduceJobs))
             if (int32_t rc = finish_sums(ctx, sums, st)) return rc;
         if (int32_t rc = add_weight_product(ctx, *ws, g, sums, st)) return rc;
