@@ -308,9 +308,9 @@ int32_t varco_transform_bwd_input(varco_ctx* ctx, int32_t layer, int64_t n_rows,
  * whose workspace holds that split; but the partial products go to a static device array of the library (32 MiB
  * per GPU, held until the process ends) instead of a workspace set, so the call needs no varco_prepare and
  * allocates nothing. VARCO_ERR_SHAPE, with the sizes in the text, when width[layer] x width[layer+1] x (the
- * split chosen for n_rows) x 4 bytes exceeds the array: fp32 storage always fits (256 x 256 weights over 32,768
- * or more rows use all of it); bf16 storage, whose tiles are twice as tall, fits up to half its full split
- * (512 x 512 weights: up to 8,447 rows). All calls on one GPU share
+ * split chosen for n_rows) x 4 bytes exceeds the array: fp32 storage with bf16 terms always fits (256 x 256 weights over
+ * 32,768 or more rows use all of it), as do up to 128 rows of bf16 weights; larger bf16 weights fit up to half their full split
+ * (512 x 512 weights: up to 8,416 rows). All calls on one GPU share
  * the array: calls that may overlap on the device (different streams, different contexts, different host threads)
  * race and must be ordered by the caller. Nothing in the array has to start at zero. The first call on a device
  * (or varco_prepare) looks the array's address up once; that first call is not capturable. Not bracketed by the

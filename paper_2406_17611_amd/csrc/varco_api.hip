@@ -1218,6 +1218,26 @@ int32_t transform_prologue(varco_ctx* ctx, int32_t layer, int64_t n_rows, const 
 
 }  // namespace
 
+namespace {
+
+// Split of varco_transform_bwd_weight and its static form, the same for both wherever the static array holds the partial
+// products. bf16 products choose their tile by the shape, and a tile of few rows fills the device with up to twice the slabs
+// of a 256 x 128 tile (100 x 512 weights: 256 slabs, 50 MiB, against 128): the array takes every product whose split into such
+// tiles fits, cut into as many slabs as the array has room for. *need: floats of partial products.
+int32_t transform_split(int32_t m, int32_t n, int64_t rows, int kind, size_t* need) {
+    const size_t one = size_t(m) * size_t(n);
+    int32_t split = gemm_split_for(m, n, rows, kind);
+    if (kind == kGemmBf16) {
+        const int64_t tiles = int64_t((m + 255) / 256) * ((n + (n <= 64 ? 63 : 127)) / (n <= 64 ? 64 : 128));
+        const int64_t plain = std::min<int64_t>(std::max<int64_t>(1, 512 / tiles), std::max<int64_t>(1, (rows + 31) / 32 / 8));
+        if (size_t(plain) * one <= kScratchFloats) split = int32_t(std::min<int64_t>(split, int64_t(kScratchFloats / one)));
+    }
+    *need = split > 1 ? size_t(split) * one : 0;
+    return split;
+}
+
+}  // namespace
+
 extern "C" int32_t varco_transform_fwd(varco_ctx* ctx, int32_t layer, int64_t n_rows, const void* y, const void* h, void* c,
                                        int32_t accumulate, int32_t apply_act, varco_stream stream) {
     hipStream_t st = static_cast<hipStream_t>(stream);
@@ -1259,7 +1279,8 @@ extern "C" int32_t varco_transform_bwd_weight(varco_ctx* ctx, int32_t layer, int
     g.accumulate = true;
     g.partial = ws->gemm;
     g.f32_terms = dt == VARCO_F32 ? ctx->f32_terms : 0;
-    g.split_k = gemm_split_for(fi, fo, n_rows, gemm_kind(g));
+    size_t need = 0;
+    g.split_k = transform_split(fi, fo, n_rows, gemm_kind(g), &need);
     if (size_t(g.split_k) * fi * fo > ws->gemm_elems) {   // rows beyond what the registered partitions sized
         const int64_t fit = int64_t(ws->gemm_elems / (size_t(fi) * fo));
         if (fit < 1) return varco_fail(ctx, VARCO_ERR_STATE, "varco_transform_bwd_weight: workspace too small (register a partition first)");
@@ -1285,8 +1306,8 @@ extern "C" int32_t varco_transform_bwd_weight_static(varco_ctx* ctx, int32_t lay
     g.c = dh, g.ldc = fo;
     g.accumulate = true;
     g.f32_terms = dt == VARCO_F32 ? ctx->f32_terms : 0;
-    g.split_k = gemm_split_for(fi, fo, n_rows, gemm_kind(g));
-    const size_t need = g.split_k > 1 ? size_t(g.split_k) * fi * fo : 0;
+    size_t need = 0;
+    g.split_k = transform_split(fi, fo, n_rows, gemm_kind(g), &need);
     if (need > kScratchFloats) {
         char msg[256];
         std::snprintf(msg, sizeof msg,

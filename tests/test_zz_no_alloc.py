@@ -63,3 +63,23 @@ def test_static_scratch_variant_refuses_what_does_not_fit():
     torch.cuda.synchronize()
     assert float(dh.abs().max()) == 0.0
     ctx.close()
+
+
+@pytest.mark.parametrize("fi,fo,n", [(100, 512, 65536), (128, 512, 33024), (100, 256, 83968), (128, 256, 65792), (100, 512, 41983)])
+def test_static_scratch_variant_takes_flat_bf16_weights_of_any_row_count(fi, fo, n):
+    """Weights of at most 128 rows: the split that fills the device would exceed the array, the one that fits it is taken, by
+    both entry points."""
+    ref_ctx = _prepared_reference_context(fi, fo, vb.ACT_IDENTITY, vb.BF16, n)
+    ctx = vb.Context([fi, fo], [vb.ACT_IDENTITY], vb.CONV_GCN, 1, KEY, vb.BF16)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(n)
+    y = torch.randn(n, fi, generator=gen, device="cuda").to(torch.bfloat16)
+    d = (torch.randn(n, fo, generator=gen, device="cuda") / n).to(torch.bfloat16)
+    want, got = torch.zeros(fi, fo, device="cuda"), torch.zeros(fi, fo, device="cuda")
+    ref_ctx.transform_bwd_weight(0, y, d, None, want)
+    ctx.transform_bwd_weight_static(0, y, d, None, got)
+    torch.cuda.synchronize()
+    assert torch.equal(got, want)
+    assert_close(got.cpu().numpy(), (y.double().t() @ d.double()).cpu().numpy(), f"dH, {n} rows", 1e-5)
+    ctx.close()
+    ref_ctx.close()
