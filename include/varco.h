@@ -206,7 +206,10 @@ int32_t varco_set_matmul_terms(varco_ctx* ctx, int32_t terms);
  * the layer's positions are already in use in the current step (by compress, decompress or a forward
  * call; its backward must see the same positions). Host call: when the new k needs a larger halo-gradient
  * workspace than the prepared streams hold, it is reallocated here (synchronising the device), with a quarter
- * of head-room so that a schedule that raises k step by step reallocates rarely. */
+ * of head-room so that a schedule that raises k step by step reallocates rarely. Sequences captured earlier stay
+ * valid at the ratio they were captured with: buffers of the library that a captured call uses are kept until
+ * varco_destroy (a stream whose calls were captured is given the largest such workspace that any ratio needs at its
+ * next reallocation, so it has two at most). Registering or linking partitions again does invalidate them. */
 int32_t varco_set_ratio(varco_ctx* ctx, int32_t layer, uint32_t num, uint32_t den);
 /* k_l currently in force (negative status on error is not used: returns status, k through *k). */
 int32_t varco_get_keep(const varco_ctx* ctx, int32_t layer, int32_t* k);

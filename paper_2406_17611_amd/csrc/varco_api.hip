@@ -184,16 +184,32 @@ hipError_t build_plan(const std::vector<int32_t>& rowptr, int32_t r0, int32_t r1
     return e;
 }
 
-hipError_t grow(float*& buf, size_t& have, size_t want) {
+hipError_t grow(Workspace& ws, float*& buf, size_t& have, size_t want) {
     if (want <= have) return hipSuccess;
     hipError_t e = hipDeviceSynchronize();   // nothing may still be using the old buffer
     if (e != hipSuccess) return e;
-    if (buf) (void)hipFree(buf);
+    if (ws.captured && buf) {                // a graph goes on using it
+        ws.kept.push_back(buf);
+    } else if (buf) {
+        (void)hipFree(buf);
+    }
     buf = nullptr;
     have = 0;
     e = hipMalloc(reinterpret_cast<void**>(&buf), want * sizeof(float));
     if (e == hipSuccess) have = want;
     return e;
+}
+
+// The product buffer: `want` floats now, `most` at any ratio. A schedule raises k step by step, and every new buffer costs a
+// synchronisation: a quarter of head-room (16 -> 3 at width 256: 8 allocations, one per row of 16 bytes without). Buffers that a
+// graph uses are kept, so a workspace with one goes to its final size at once.
+hipError_t grow_products(Workspace& ws, size_t want, size_t most) {
+    if (want <= ws.prod_elems) return hipSuccess;
+    const size_t room = ws.captured ? most : std::min(most, want + want / 4);
+    const hipError_t e = grow(ws, ws.prod, ws.prod_elems, std::max(want, room));
+    if (e != hipErrorOutOfMemory || room <= want) return e;
+    (void)hipGetLastError();
+    return grow(ws, ws.prod, ws.prod_elems, want);
 }
 
 // Number of slabs the node dimension of a weight-gradient product is cut into: the workgroups of one launch
@@ -268,15 +284,19 @@ hipError_t prep_weight(varco_ctx* ctx, Workspace& ws, int32_t layer, const void*
 }
 
 // Elements (floats) of the halo-gradient product buffer the current ratios ask for: the largest (halo entries of a
-// registered partition) x (k of a layer that hands back part of a row) elements of the storage type.
-size_t prod_need(const varco_ctx* ctx) {
+// registered partition) x (k of a layer that hands back part of a row) elements of the storage type; *most: at any ratio.
+size_t prod_need(const varco_ctx* ctx, size_t* most) {
     int64_t entries = 0;
     for (const PartState& ps : ctx->parts)
         if (ps.registered) entries = std::max(entries, ps.d.nnz - ps.nnz_t_local);
-    int32_t k = 0;
-    for (int32_t l = 0; l < ctx->n_layers; ++l)
+    int32_t k = 0, k_most = 0;
+    for (int32_t l = 0; l < ctx->n_layers; ++l) {
         if (ctx->layers[l].k < ctx->widths[l]) k = std::max(k, ctx->layers[l].k);
-    return (size_t(entries) * size_t(k) * size_t(ctx->elem_bytes()) + 3) / 4;
+        k_most = std::max(k_most, ctx->widths[l] - 1);
+    }
+    auto floats = [&](int32_t kept) { return (size_t(entries) * size_t(kept) * size_t(ctx->elem_bytes()) + 3) / 4; };
+    *most = floats(k_most);
+    return floats(k);
 }
 
 // Floats of the two buffers of the layers that transform first: transformed rows of the local and halo nodes of the
@@ -305,25 +325,23 @@ void transform_first_need(const varco_ctx* ctx, size_t* rows_out, size_t* record
 // Brings one workspace set up to what the registered partitions and the current ratios need (host side of
 // varco_prepare, varco_set_ratio and varco_register_partition: may synchronise the device).
 int32_t size_workspace(varco_ctx* ctx, Workspace& ws) {
-    VARCO_HIP(ctx, grow(ws.dm, ws.dm_elems, ctx->need_dm));
-    VARCO_HIP(ctx, grow(ws.spmm, ws.spmm_elems, ctx->need_spmm));
+    VARCO_HIP(ctx, grow(ws, ws.dm, ws.dm_elems, ctx->need_dm));
+    VARCO_HIP(ctx, grow(ws, ws.spmm, ws.spmm_elems, ctx->need_spmm));
     size_t tf_rows = 0, tf_records = 0, tf_shares = 0;
     transform_first_need(ctx, &tf_rows, &tf_records, &tf_shares);
-    VARCO_HIP(ctx, grow(ws.gemm, ws.gemm_elems, ctx->need_gemm + tf_shares));
-    VARCO_HIP(ctx, grow(ws.w, ws.w_elems, ctx->need_w));
-    VARCO_HIP(ctx, grow(ws.loss, ws.loss_elems, size_t(2) * kLossBlocks));
-    const size_t prod = prod_need(ctx);
-    if (prod > ws.prod_elems) VARCO_HIP(ctx, grow(ws.prod, ws.prod_elems, prod + prod / 4));   // head-room: schedules raise k step by step
+    VARCO_HIP(ctx, grow(ws, ws.gemm, ws.gemm_elems, ctx->need_gemm + tf_shares));
+    VARCO_HIP(ctx, grow(ws, ws.w, ws.w_elems, ctx->need_w));
+    VARCO_HIP(ctx, grow(ws, ws.loss, ws.loss_elems, size_t(2) * kLossBlocks));
+    size_t most = 0, network_most = 0;
+    const size_t prod = prod_need(ctx, &most);
     // the block's product buffer is an option (without it whole rows are gathered): a device that has no room for it goes on without
-    if (ctx->net.linked) {
-        const size_t want = network_prod_need(ctx);
-        if (want > ws.prod_elems && grow(ws.prod, ws.prod_elems, want) != hipSuccess) {
-            (void)hipGetLastError();
-            if (prod > ws.prod_elems) VARCO_HIP(ctx, grow(ws.prod, ws.prod_elems, prod + prod / 4));
-        }
+    const size_t network = ctx->net.linked ? network_prod_need(ctx, &network_most) : 0;
+    if (network <= prod || grow_products(ws, network, std::max(most, network_most)) != hipSuccess) {
+        (void)hipGetLastError();
+        VARCO_HIP(ctx, grow_products(ws, prod, std::max(most, network_most)));
     }
-    VARCO_HIP(ctx, grow(ws.tf, ws.tf_elems, tf_rows));
-    VARCO_HIP(ctx, grow(ws.hrows, ws.hrows_elems, tf_records));
+    VARCO_HIP(ctx, grow(ws, ws.tf, ws.tf_elems, tf_rows));
+    VARCO_HIP(ctx, grow(ws, ws.hrows, ws.hrows_elems, tf_records));
     if (ws.w_tags.empty()) ws.w_tags.resize(size_t(ctx->n_layers) * kWeightSlots * 2);
     return VARCO_OK;
 }
@@ -338,6 +356,13 @@ int32_t size_all_workspaces(varco_ctx* ctx) {
 int32_t workspace_for(varco_ctx* ctx, hipStream_t st, Workspace** out, const char* fn) {
     for (Workspace& w : ctx->ws)
         if (w.used && w.stream == st) {
+            if (!w.captured && st) {         // (the default stream cannot be captured)
+                hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+                if (hipStreamIsCapturing(st, &status) != hipSuccess)
+                    (void)hipGetLastError();
+                else
+                    w.captured = status == hipStreamCaptureStatusActive;
+            }
             *out = &w;
             return VARCO_OK;
         }
@@ -487,9 +512,11 @@ extern "C" int32_t varco_destroy(varco_ctx* ctx) {
     }
     for (PartState& ps : ctx->parts) free_part(ps);
     free_network(ctx->net);
-    for (Workspace& w : ctx->ws)
+    for (Workspace& w : ctx->ws) {
         for (float* p : {w.dm, w.spmm, w.gemm, w.prod, w.w, w.tf, w.hrows, w.loss})
             if (p) (void)hipFree(p);
+        for (float* p : w.kept) (void)hipFree(p);
+    }
     if (ctx->d_flags) (void)hipFree(ctx->d_flags);
     if (ctx->d_step) (void)hipFree(ctx->d_step);
     if (ctx->d_table) (void)hipFree(ctx->d_table);

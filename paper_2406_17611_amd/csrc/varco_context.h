@@ -60,6 +60,8 @@ struct NetState {
 struct Workspace {
     hipStream_t stream = nullptr;
     bool used = false;
+    bool captured = false;              // a call on it was recorded into a graph, which goes on using its buffers: they are
+    std::vector<float*> kept;           // kept here, not freed, when larger ones take their place
     float* dm = nullptr;        size_t dm_elems = 0;        // dM: n_local x width (elements of the storage type)
     float* spmm = nullptr;      size_t spmm_elems = 0;      // partial rows of split CSR rows
     float* gemm = nullptr;      size_t gemm_elems = 0;      // split-K partial products
@@ -125,9 +127,8 @@ MaskRule make_rule(const varco_ctx* ctx, int32_t layer, int32_t hop = 0);
 MaskRule full_rule(int32_t width);
 void free_plan(SpmmPlan& p);
 void free_network(NetState& net);
-// Floats of a workspace's product buffer that the calls on all partitions ask for at the current ratios.
-size_t network_prod_need(const varco_ctx* ctx);
-hipError_t grow(float*& buf, size_t& have, size_t want);
+// Floats of a workspace's product buffer that the calls on all partitions ask for at the current ratios, and at most at any.
+size_t network_prod_need(const varco_ctx* ctx, size_t* most);
 enum GemmKind { kGemmF32 = 0, kGemmBf16 = 1, kGemmExpanded = 2 };     // kGemmBf16: as weight gradients
 int32_t gemm_split_for(int32_t m, int32_t n, int64_t k, int kind);
 int gemm_kind(const GemmArgs& g);

@@ -22,17 +22,17 @@ constexpr int64_t kPartialElems = int64_t(1) << 30;
 
 // Products of k values per cross entry are written and read back (2 k elements at about 4.8 TB/s), or whole rows are
 // gathered (width elements at about 7 TB/s).
-int32_t product_pitch(const varco_ctx* ctx, int32_t layer) {
+int32_t product_pitch(const varco_ctx* ctx, int32_t layer, int64_t k) {
     MaskRule r{};
-    r.k = uint32_t(ctx->layers[layer].k), r.width = uint32_t(ctx->widths[layer]);
+    r.k = uint32_t(k), r.width = uint32_t(ctx->widths[layer]);
     return varco_product_pitch(r, ctx->elem_bytes());
 }
-bool products_pay(const varco_ctx* ctx, int32_t layer) {
-    const int64_t k = ctx->layers[layer].k, width = ctx->widths[layer];
-    return k > 0 && 3 * k < width && double(ctx->net.nnz_cross) * product_pitch(ctx, layer) * ctx->elem_bytes() <= kProdBytes;
+bool products_pay(const varco_ctx* ctx, int32_t layer, int64_t k) {
+    return k > 0 && 3 * k < ctx->widths[layer] &&
+           double(ctx->net.nnz_cross) * product_pitch(ctx, layer, k) * ctx->elem_bytes() <= kProdBytes;
 }
-size_t prod_floats(const varco_ctx* ctx, int32_t layer) {
-    return (size_t(ctx->net.nnz_cross) * size_t(product_pitch(ctx, layer)) * size_t(ctx->elem_bytes()) + 3) / 4;
+size_t prod_floats(const varco_ctx* ctx, int32_t layer, int64_t k) {
+    return (size_t(ctx->net.nnz_cross) * size_t(product_pitch(ctx, layer, k)) * size_t(ctx->elem_bytes()) + 3) / 4;
 }
 
 // Split of a weight gradient's reduction over the arena's rows: whole rounds of resident workgroups, at least two
@@ -239,11 +239,11 @@ int32_t aggregate_bwd(varco_ctx* ctx, Workspace& ws, int32_t layer, const MaskRu
     const double es = ctx->elem_bytes();
     const int32_t fi = ctx->widths[layer];
     VarcoCross cross = net.nnz_cross == 0 || rule.k == 0 ? kCrossNone : rule.k == rule.width ? kCrossFull : kCrossMasked;
-    if (cross == kCrossMasked && products_pay(ctx, layer) && prod_floats(ctx, layer) <= ws.prod_elems) {
+    if (cross == kCrossMasked && products_pay(ctx, layer, rule.k) && prod_floats(ctx, layer, rule.k) <= ws.prod_elems) {
         cross = kCrossProducts;
         const double bytes = double(net.nnz_cross) * 8.0 + double(net.rows) * fi * es;
         VARCO_HIP(ctx, varco_launch_halo_products(ctx->dtype, net.fwd, net.edges, net.vals, net.prow, dm, rule, ws.prod,
-                                                  product_pitch(ctx, layer), st,
+                                                  product_pitch(ctx, layer, rule.k), st,
                                                   ctx->tag(VARCO_K_AGG_BWD_HALO, bytes, 0)));
     }
     const double bytes = double(net.nnz_local) * 8.0 + (double(net.rows) + 1.0) * 4.0 + 2.0 * double(net.rows) * fi * es;
@@ -559,10 +559,15 @@ int32_t tap_prologue(varco_ctx* ctx, int32_t tap, varco_stream stream, const cha
 
 }  // namespace
 
-size_t varco::network_prod_need(const varco_ctx* ctx) {
+size_t varco::network_prod_need(const varco_ctx* ctx, size_t* most) {
     size_t need = 0;
-    for (int32_t l = 1; l < ctx->n_layers; ++l)       // the first layer's input needs no gradient
-        if (products_pay(ctx, l)) need = std::max(need, prod_floats(ctx, l));
+    *most = 0;
+    for (int32_t l = 1; l < ctx->n_layers; ++l) {     // the first layer's input needs no gradient
+        if (products_pay(ctx, l, ctx->layers[l].k)) need = std::max(need, prod_floats(ctx, l, ctx->layers[l].k));
+        int64_t k = (ctx->widths[l] - 1) / 3;
+        while (k > 0 && !products_pay(ctx, l, k)) --k;
+        if (k > 0) *most = std::max(*most, prod_floats(ctx, l, k));
+    }
     return need;
 }
 

@@ -78,6 +78,7 @@ class PartitionedNetwork:
         self._zcap = [0] * self.L
         self._dzcap = [0] * self.L
         self._streams = None
+        self._capture_stream = None        # one for all captures: each stream has a workspace set of its own
         self._prepared = set()
         self._prepare([None])
 
@@ -346,7 +347,7 @@ class PartitionedNetwork:
         and the key words of the kept positions live on the device from here on (varco_step_table_enable); the
         ratio, i.e. every k, is frozen into the graph. Set the step the first replay should follow with
         ctx.set_step(step). Host-side exchange counters do not see replays."""
-        side = torch.cuda.Stream(device=self.device)
+        side = self._capture_stream = self._capture_stream or torch.cuda.Stream(device=self.device)
         side.wait_stream(torch.cuda.current_stream(self.device))
         with torch.cuda.stream(side):
             self.ctx.step_table_enable()
@@ -356,6 +357,7 @@ class PartitionedNetwork:
         graph = torch.cuda.CUDAGraph()
         with torch.cuda.graph(graph, stream=side):
             self.step(None, ratio)
+        graph.held = (list(self.z), list(self.dz_halo))        # a later ratio may replace them: the replays go on with these
         return graph
 
     def zero_grads(self):
