@@ -344,7 +344,17 @@ int32_t varco_accumulate_returned(varco_ctx* ctx, int32_t layer, int32_t p, cons
  * was registered again). The partitions' local rows form one arena of n_total rows, partition 0's first; compressed and
  * returned rows are numbered by z_row_offset and halo_row_offset, which must be consecutive over the partitions, and
  * every partition must have its map of returned rows. VARCO_ERR_UNSUPPORTED when the partitions have 2^31 or more
- * entries together (the per-partition calls have no such limit), VARCO_ERR_SHAPE when the maps do not fit.
+ * entries together, or the device has no room for the memory named next (the per-partition calls, which need none of it,
+ * go on as if the call had not been made), VARCO_ERR_SHAPE when the maps do not fit.
+ *
+ * Device memory of the joined form, allocated by the library itself (a caller whose allocator takes all memory sets the
+ * ratio first): 28 bytes per entry and up to 60 per node, in this call; per prepared stream, in varco_prepare, n_total
+ * rows of the widest layer and the partial products of the weight gradients (about 1 GB for 512 x 512 bf16 weights over
+ * 2.4 million nodes; 4 GiB per pair of weight matrices at most); and while 3 k < width[l] for an l > 0, in
+ * varco_set_ratio, up to 1.25 k elements per entry of a halo column, 48 GiB at most. The last is optional: beyond that size,
+ * or where it cannot be had, whole rows are gathered instead. With fp32 storage that changes the order of sums only; with
+ * bf16 storage the products are rounded to bf16 and gathered rows are not, so the input gradients then differ by such
+ * roundings (2^-9 each). A step captured into a graph prepares its own stream, hence takes a second set.
  *
  * The errors that the consumers of a node hand back (k elements per entry of a halo column) are summed for all consumers
  * at once and added to the owner's row; they are not summed per consumer first, so no buffer of returned rows is needed.

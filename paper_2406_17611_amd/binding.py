@@ -385,7 +385,8 @@ class Context:
                                                _ptr(g_out), int(accumulate), _stream(stream)), self._h)
 
     def link_partitions(self):
-        """Joins all registered partitions for the network_* calls; False when they are too large for that (2^31 entries)."""
+        """Joins all registered partitions for the network_* calls; False when they are too large for that (2^31 entries, or
+        no room on the device): the per-partition calls serve them then."""
         code = lib().varco_link_partitions(self._h)
         if code == ERR_UNSUPPORTED:
             return False

@@ -68,6 +68,7 @@ int32_t varco_fail(const varco_ctx* ctx, int32_t code, const char* msg) {
 namespace varco {
 
 int32_t hip_fail(const varco_ctx* ctx, hipError_t e, const char* what) {
+    if (ctx) ctx->last_hip = e;
     std::string m = std::string(what) + ": " + hipGetErrorString(e);
     return varco_fail(ctx, VARCO_ERR_HIP, m.c_str());
 }

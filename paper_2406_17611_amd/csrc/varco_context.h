@@ -102,6 +102,7 @@ struct varco_ctx {
     double prof_stream_bytes[VARCO_K_COUNT] = {};
     int64_t prof_launches[VARCO_K_COUNT] = {};
     mutable std::string error;
+    mutable hipError_t last_hip = hipSuccess;      // of the last failed runtime call
     double elem_bytes() const { return dtype == VARCO_BF16 ? 2.0 : 4.0; }
     LaunchTag tag(int cls, double bytes, double flops, double stream_bytes = -1.0) {
         LaunchTag t;

@@ -63,6 +63,18 @@ hipError_t alloc(P*& p, size_t n) {
     return n ? hipMalloc(reinterpret_cast<void**>(&p), n * sizeof(P)) : hipSuccess;
 }
 
+// An allocation of varco_link_partitions.
+#define VARCO_ROOM(ctx, call)                                                            \
+    do {                                                                                 \
+        const hipError_t e_ = (call);                                                    \
+        if (e_ == hipErrorOutOfMemory) return no_room(ctx);                              \
+        if (e_ != hipSuccess) return varco::hip_fail(ctx, e_, #call);                    \
+    } while (0)
+int32_t no_room(const varco_ctx* ctx) {
+    (void)hipGetLastError();
+    return varco_fail(ctx, VARCO_ERR_UNSUPPORTED, "varco_link_partitions: the device has no room for the joined partitions (the per-partition calls need none)");
+}
+
 struct Temp {                     // device memory of the set-up, given back on every path
     void* p = nullptr;
     ~Temp() {
@@ -103,14 +115,26 @@ int32_t link_impl(varco_ctx* ctx) {
     if (returned != net.halo_rows)
         return varco_fail(ctx, VARCO_ERR_SHAPE, "varco_link_partitions: the maps of returned rows do not cover the halo rows");
 
-    // halo rows, their owners, and the number of cross entries of every arena row
+    // everything whose size is known, before the first kernel: a device without room for it is left as it was
+    VARCO_ROOM(ctx, alloc(net.edges, size_t(net.nnz)));
+    VARCO_ROOM(ctx, alloc(net.arow, size_t(net.nnz)));
+    VARCO_ROOM(ctx, alloc(net.vals, size_t(net.nnz)));
+    VARCO_ROOM(ctx, alloc(net.prow, size_t(net.nnz)));
+    VARCO_ROOM(ctx, alloc(net.t_local, size_t(net.nnz_local)));
+    VARCO_ROOM(ctx, alloc(net.t_cross, size_t(net.nnz_cross)));
+    net.fwd.n_items = int32_t(items), net.fwd.n_splits = int32_t(splits), net.fwd.n_partials = int32_t(slots);
+    VARCO_ROOM(ctx, alloc(net.fwd.items, size_t(items)));
+    VARCO_ROOM(ctx, alloc(net.fwd.splits, size_t(splits)));
+    VARCO_ROOM(ctx, alloc(net.nodes.nodes, size_t(net.rows)));
     Temp halo_len, halo_gid, halo_zrow, owner_row, cross_len, cross_ptr_d, prod_start;
-    for (Temp* t : {&halo_len, &halo_gid, &halo_zrow, &owner_row, &prod_start}) VARCO_HIP(ctx, t->make(size_t(net.halo_rows) * 4));
-    VARCO_HIP(ctx, cross_len.make(size_t(net.rows) * 4));
-    VARCO_HIP(ctx, cross_ptr_d.make(size_t(net.rows + 1) * 4));
-    VARCO_HIP(ctx, alloc(net.brow, size_t(net.boundary)));
-    VARCO_HIP(ctx, alloc(net.bgid, size_t(net.boundary)));
-    VARCO_HIP(ctx, alloc(net.zrow_of, size_t(net.rows)));
+    for (Temp* t : {&halo_len, &halo_gid, &halo_zrow, &owner_row, &prod_start}) VARCO_ROOM(ctx, t->make(size_t(net.halo_rows) * 4));
+    VARCO_ROOM(ctx, cross_len.make(size_t(net.rows) * 4));
+    VARCO_ROOM(ctx, cross_ptr_d.make(size_t(net.rows + 1) * 4));
+    VARCO_ROOM(ctx, alloc(net.brow, size_t(net.boundary)));
+    VARCO_ROOM(ctx, alloc(net.bgid, size_t(net.boundary)));
+    VARCO_ROOM(ctx, alloc(net.zrow_of, size_t(net.rows)));
+
+    // halo rows, their owners, and the number of cross entries of every arena row
     if (net.rows) VARCO_HIP(ctx, hipMemset(net.zrow_of, 0xFF, size_t(net.rows) * 4));
     if (net.halo_rows) VARCO_HIP(ctx, hipMemset(owner_row.p, 0xFF, size_t(net.halo_rows) * 4));
     if (net.rows) VARCO_HIP(ctx, hipMemset(cross_len.p, 0, size_t(net.rows) * 4));
@@ -131,15 +155,6 @@ int32_t link_impl(varco_ctx* ctx) {
     VARCO_HIP(ctx, hipMemcpy(cross_ptr_d.p, cross_ptr.data(), cross_ptr.size() * 4, hipMemcpyHostToDevice));
 
     // entry arrays of both directions
-    VARCO_HIP(ctx, alloc(net.edges, size_t(net.nnz)));
-    VARCO_HIP(ctx, alloc(net.arow, size_t(net.nnz)));
-    VARCO_HIP(ctx, alloc(net.vals, size_t(net.nnz)));
-    VARCO_HIP(ctx, alloc(net.prow, size_t(net.nnz)));
-    VARCO_HIP(ctx, alloc(net.t_local, size_t(net.nnz_local)));
-    VARCO_HIP(ctx, alloc(net.t_cross, size_t(net.nnz_cross)));
-    net.fwd.n_items = int32_t(items), net.fwd.n_splits = int32_t(splits), net.fwd.n_partials = int32_t(slots);
-    VARCO_HIP(ctx, alloc(net.fwd.items, size_t(items)));
-    VARCO_HIP(ctx, alloc(net.fwd.splits, size_t(splits)));
     for (int32_t q = 0; q < P; ++q)
         VARCO_HIP(ctx, varco_launch_link_starts(lp[q], halo_len.i32(), cross_ptr_d.i32(), prod_start.i32(), nullptr));
     items = splits = slots = 0;
@@ -179,8 +194,7 @@ int32_t link_impl(varco_ctx* ctx) {
     }
     net.nodes.n_whole = int32_t(std::stable_partition(nodes.begin(), nodes.end(), [](const NodeItem& it) { return it.flags == 0; }) - nodes.begin());
     net.nodes.n_nodes = int32_t(nodes.size()), net.nodes.n_pieces = int32_t(pieces.size());
-    VARCO_HIP(ctx, alloc(net.nodes.nodes, nodes.size()));
-    VARCO_HIP(ctx, alloc(net.nodes.pieces, pieces.size()));
+    VARCO_ROOM(ctx, alloc(net.nodes.pieces, pieces.size()));
     if (!nodes.empty()) VARCO_HIP(ctx, hipMemcpy(net.nodes.nodes, nodes.data(), nodes.size() * sizeof(NodeItem), hipMemcpyHostToDevice));
     if (!pieces.empty()) VARCO_HIP(ctx, hipMemcpy(net.nodes.pieces, pieces.data(), pieces.size() * sizeof(SpmmItem), hipMemcpyHostToDevice));
     VARCO_HIP(ctx, hipDeviceSynchronize());
@@ -200,7 +214,8 @@ int32_t link_impl(varco_ctx* ctx) {
     ctx->need_spmm = std::max(ctx->need_spmm, size_t(std::max<int64_t>(net.fwd.n_partials, n_slots)) * size_t(std::max(wmax, kClassPitch)));
     ctx->need_gemm = std::max(ctx->need_gemm, size_t(gemm_elems));
     net.linked = true;
-    return size_all_workspaces(ctx);
+    const int32_t rc = size_all_workspaces(ctx);
+    return rc != VARCO_OK && ctx->last_hip == hipErrorOutOfMemory ? no_room(ctx) : rc;
 }
 
 int32_t check_linked(const varco_ctx* ctx, const char* fn) {
@@ -575,9 +590,16 @@ extern "C" int32_t varco_link_partitions(varco_ctx* ctx) {
     if (!ctx) return varco_fail(nullptr, VARCO_ERR_INVALID_ARG, "varco_link_partitions: null context");
     VARCO_HIP(ctx, hipDeviceSynchronize());
     free_network(ctx->net);
+    const size_t need_dm = ctx->need_dm, need_spmm = ctx->need_spmm, need_gemm = ctx->need_gemm;
+    ctx->last_hip = hipSuccess;
     const int32_t rc = link_impl(ctx);
-    if (rc != VARCO_OK) free_network(ctx->net);
-    return rc;
+    if (rc == VARCO_OK) return VARCO_OK;
+    // as before the call: workspaces of the per-partition calls, which go on
+    free_network(ctx->net);
+    ctx->need_dm = need_dm, ctx->need_spmm = need_spmm, ctx->need_gemm = need_gemm;
+    const std::string why = ctx->error;
+    if (int32_t lost = size_all_workspaces(ctx)) return lost;
+    return varco_fail(ctx, rc, why.c_str());
 }
 
 extern "C" int32_t varco_network_forward(varco_ctx* ctx, const varco_network_buffers* b, varco_stream stream) {
