@@ -222,7 +222,8 @@ int32_t varco_compress(varco_ctx* ctx, int32_t layer, const int32_t* gids, const
 
 /* Definition 1 / Appendix A, decoder. accumulate = 0: x[rows[i], :] = 0 except x[rows[i], pi_v(j)] =
  * z[i, j]. accumulate = 1: x[rows[i], pi_v(j)] += z[i, j] (the owner-side sum of returned errors); rows
- * must be distinct within one call. */
+ * must be distinct within one call. The other elements of these rows keep their bits, but the call may write the
+ * rows back whole: nothing else may write to them while it runs. */
 int32_t varco_decompress(varco_ctx* ctx, int32_t layer, const int32_t* gids, const int32_t* rows,
                          int64_t n_rows, const void* z, void* x, int64_t ldx, int32_t accumulate,
                          varco_stream stream);

@@ -44,7 +44,8 @@ __global__ __launch_bounds__(kBlock) void compress_kernel(MaskRule rule, const i
 // of 256, element-wise -> through LDS: decoder 265 -> 116 us (fp32, k = 32), 197 -> 64 (bf16, k = 64); encoder 197 -> 133
 // (fp32, k = 128), 136 -> 46 (bf16, k = 64); decoder with sum 224 -> 196 (fp32, k = 32: the rate of a copy), 194 -> 135
 // (bf16, k = 128). Where the element-wise kernels win (few kept elements, narrow or unaligned rows): codec_rows_pay.
-//   MODE 0: z[i, j] = x[row_i, pi(j)];  1: x[row_i, :] = 0 except x[row_i, pi(j)] = z[i, j];  2: x[row_i, pi(j)] += z[i, j]
+//   MODE 0: z[i, j] = x[row_i, pi(j)];  1: x[row_i, :] = 0 except x[row_i, pi(j)] = z[i, j];  2: x[row_i, pi(j)] += z[i, j],
+//   in LDS on the old row, which is written back whole: what is not added to keeps its bits
 // S: the storage word (fp32 or bf16 bits); V: elements per access to x (16 bytes, or 1 for unaligned rows); PE: elements of z
 // per lane (2 for bf16 pairs); ONE: a row is at most one access per lane.
 constexpr int kRowsInFlight = 4;
@@ -72,7 +73,7 @@ __global__ __launch_bounds__(kBlock) void codec_rows_kernel(MaskRule rule, const
         for (int u = 0; u < U; ++u)
             for (int c = lane * V; c < width; c += 64 * V) *reinterpret_cast<Vec*>(buf + u * pitch + c) = Vec(S(0));
     };
-    if (MODE != 0) clear();
+    if (MODE == 1) clear();
     const int64_t stride = int64_t(gridDim.x) * (kBlock / 64) * U;
     int64_t r0 = (int64_t(blockIdx.x) * (kBlock / 64) + wave) * U;
     if (r0 >= n_rows) return;                        // wavefronts are independent: no barrier
@@ -109,8 +110,7 @@ __global__ __launch_bounds__(kBlock) void codec_rows_kernel(MaskRule rule, const
         int64_t at_now[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) at_now[u] = at[u];
-        Vec old[MODE == 2 ? U : 1];
-        if constexpr (MODE == 0) {
+        if constexpr (MODE != 1) {
             if constexpr (ONE) {
 #pragma unroll
                 for (int u = 0; u < U; ++u)
@@ -120,9 +120,6 @@ __global__ __launch_bounds__(kBlock) void codec_rows_kernel(MaskRule rule, const
 #pragma unroll
                     for (int u = 0; u < U; ++u) *reinterpret_cast<Vec*>(buf + u * pitch + c) = *reinterpret_cast<const Vec*>(x + at_now[u] + c);
             }
-        } else if constexpr (MODE == 2 && ONE) {
-#pragma unroll
-            for (int u = 0; u < U; ++u) old[u] = v[u];
         }
         if (r0 + stride < n_rows) {
             resolve();
@@ -146,7 +143,7 @@ __global__ __launch_bounds__(kBlock) void codec_rows_kernel(MaskRule rule, const
                         if constexpr (MODE == 0)
                             e[i] = row[q];
                         else
-                            row[q] = e[i];
+                            row[q] = MODE == 1 ? e[i] : add_words<S>(row[q], e[i]);
                         q += a;
                         q = min(q, q - rule.width);
                     }
@@ -159,22 +156,9 @@ __global__ __launch_bounds__(kBlock) void codec_rows_kernel(MaskRule rule, const
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             if (u >= n_here) break;
-            for (int c = lane * V; c < width; c += 64 * V) {
-                Vec o = *reinterpret_cast<const Vec*>(buf + u * pitch + c);
-                S* const dst = x + at_now[u] + c;
-                if constexpr (MODE == 2) {
-                    Vec before;
-                    if constexpr (ONE)
-                        before = old[u];
-                    else
-                        before = *reinterpret_cast<const Vec*>(dst);
-#pragma unroll
-                    for (int i = 0; i < V; ++i) o[i] = add_words<S>(before[i], o[i]);
-                }
-                *reinterpret_cast<Vec*>(dst) = o;
-            }
+            for (int c = lane * V; c < width; c += 64 * V) *reinterpret_cast<Vec*>(x + at_now[u] + c) = *reinterpret_cast<const Vec*>(buf + u * pitch + c);
         }
-        clear();
+        if (MODE == 1) clear();
         __builtin_amdgcn_wave_barrier();
     }
 }

@@ -49,3 +49,33 @@ def test_aligned_rows(dtype, width, ratio, n_rows):
         want_acc[rows[i], cols[i]] = stored(want_acc[rows[i], cols[i]] + want_z[i])
     assert np.array_equal(acc.float().cpu().numpy(), want_acc)
     ctx.close()
+
+
+@pytest.mark.parametrize("dtype,width,ratio", [("f32", 256, (8, 1)), ("f32", 2048, (4, 1)), ("f32", 75, (2, 1)), ("bf16", 512, (4, 1)),
+                                               ("bf16", 2048, (3, 1)), ("bf16", 256, (1, 1))])
+def test_adding_decoder_leaves_other_elements_alone(dtype, width, ratio):
+    bf16 = dtype == "bf16"
+    tdt, idt = (torch.bfloat16, torch.int16) if bf16 else (torch.float32, torch.int32)
+    n = 37
+    # negative zeros, both infinities and NaNs with a payload, quiet and signalling
+    odd = np.array([0x8000, 0x7F80, 0xFF80, 0x7FC1, 0xFF81], dtype=np.uint16) if bf16 else \
+        np.array([0x80000000, 0x7F800000, 0xFF800000, 0x7FC00123, 0xFF800321], dtype=np.uint32)
+    bits = odd[np.random.default_rng(width).integers(0, len(odd), size=(n, width))]
+    signed = bits.view(np.int16 if bf16 else np.int32)
+    gids = (np.arange(n) * 3 + 1).astype(np.int32)
+    ctx = vb.Context([8, width, 8], [1, 0], vb.CONV_GCN, 1, KEY, vb.BF16 if bf16 else vb.F32)
+    ctx.prepare()
+    ctx.begin_step(6)
+    ctx.set_ratio(1, *ratio)
+    k = ctx.keep(1)
+    cols = omask.kept_columns(gids, width, k, KEY, 6, 1)
+    kept = np.zeros((n, width), dtype=bool)
+    np.put_along_axis(kept, np.asarray(cols, dtype=np.int64).reshape(n, k), True, axis=1)
+    x = dev(signed)
+    z = torch.full((n, k), -0.0, dtype=tdt, device="cuda")
+    ctx.decompress(1, dev(gids), None, n, z, x.view(tdt), width, 1)
+    got = x.view(idt).cpu().numpy()
+    assert np.array_equal(got[~kept], signed[~kept])
+    zero = kept & (bits == odd[0])
+    assert zero.any() and np.array_equal(got[zero], signed[zero])          # -0 + -0
+    ctx.close()
