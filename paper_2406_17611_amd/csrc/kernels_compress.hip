@@ -82,15 +82,15 @@ __global__ __launch_bounds__(kBlock) void codec_rows_kernel(MaskRule rule, const
     auto load_ids = [&](int64_t r) {
         const int64_t i = min(r + (lane & (U - 1)), n_rows - 1);
         gid = gids[i];
-        src = rows ? rows[i] : int32_t(i);
+        if (rows) src = rows[i];
     };
     int64_t at[U];                                   // element offset of the group's rows in x
     uint32_t ab = 0;
-    auto resolve = [&]() {
+    auto resolve = [&](int64_t r) {
         const MaskAffine m = varco_affine(rule, uint32_t(gid));
         ab = m.a | (m.b << 16);
 #pragma unroll
-        for (int u = 0; u < U; ++u) at[u] = int64_t(__shfl(src, u)) * ldx;
+        for (int u = 0; u < U; ++u) at[u] = (rows ? int64_t(__shfl(src, u)) : min(r + u, n_rows - 1)) * ldx;
     };
     Vec v[U];
     const int own = min(lane * V, width - V);        // lanes past the row repeat its last access (never stored)
@@ -101,7 +101,7 @@ __global__ __launch_bounds__(kBlock) void codec_rows_kernel(MaskRule rule, const
         }
     };
     load_ids(r0);
-    resolve();
+    resolve(r0);
     load_rows();
     if (r0 + stride < n_rows) load_ids(r0 + stride);
     for (; r0 < n_rows; r0 += stride) {
@@ -122,7 +122,7 @@ __global__ __launch_bounds__(kBlock) void codec_rows_kernel(MaskRule rule, const
             }
         }
         if (r0 + stride < n_rows) {
-            resolve();
+            resolve(r0 + stride);
             load_rows();
             if (r0 + 2 * stride < n_rows) load_ids(r0 + 2 * stride);
         }

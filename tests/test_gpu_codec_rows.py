@@ -79,3 +79,26 @@ def test_adding_decoder_leaves_other_elements_alone(dtype, width, ratio):
     zero = kept & (bits == odd[0])
     assert zero.any() and np.array_equal(got[zero], signed[zero])          # -0 + -0
     ctx.close()
+
+
+def test_more_rows_than_32_bits_count():
+    n = (1 << 31) + 5                                     # without a row list, rows are numbered by the kernels themselves
+    ctx = vb.Context([8, 2, 8], [1, 0], vb.CONV_GCN, 1, KEY, vb.BF16)
+    ctx.prepare()
+    ctx.begin_step(2)
+    ctx.set_ratio(1, 2, 1)
+    gids = torch.zeros(n, dtype=torch.int32, device="cuda")
+    col = int(np.asarray(omask.kept_columns(np.zeros(1, dtype=np.int32), 2, 1, KEY, 2, 1)).ravel()[0])
+    x = torch.zeros(n, 2, dtype=torch.bfloat16, device="cuda")
+    some = torch.tensor([0, 1, 7, (1 << 31) - 1, 1 << 31, n - 1], device="cuda")
+    val = torch.arange(1, 7, device="cuda").to(torch.bfloat16)
+    x[some, col] = val
+    z = torch.full((n,), 9.0, dtype=torch.bfloat16, device="cuda")
+    ctx.compress(1, gids, None, n, x, 2, z)
+    assert torch.equal(z[some], val) and int((z != 0).sum()) == 6
+    ctx.decompress(1, gids, None, n, z, x, 2, 1)
+    assert torch.equal(x[some, col], 2 * val) and int((x != 0).sum()) == 6
+    x.fill_(5.0)
+    ctx.decompress(1, gids, None, n, z, x, 2, 0)
+    assert torch.equal(x[some, col], val) and int((x != 0).sum()) == 6
+    ctx.close()
