@@ -443,7 +443,7 @@ int32_t varco_sum_gradients(void* dst, const void* src, int64_t n, varco_stream 
  * (int32, 1 when the largest logit, lowest index on ties, is the label); when totals != NULL also
  * totals[0] += scale * sum(row_loss), totals[1] += sum(row_correct), summed in a fixed order (fp32[2]).
  * logits (leading dimension ld) and dlogits (ldd) have the context's storage type; dlogits may be NULL
- * (evaluation only). All pointers device. */
+ * (evaluation only) or, with ldd = ld, the logits buffer itself. All pointers device. */
 int32_t varco_softmax_xent(varco_ctx* ctx, const void* logits, int64_t ld, const int32_t* labels, int64_t n_rows,
                            int32_t n_classes, float scale, void* dlogits, int64_t ldd, float* row_loss,
                            int32_t* row_correct, float* totals, varco_stream stream);

@@ -24,10 +24,12 @@ using Int = std::integral_constant<int, N>;
 // re-read, for more than 512 classes), so that the rows of 47 logits of a class layer fill a wavefront four at a time: with a
 // wavefront per row the kernel was bound by its shuffles, not by memory. 410,003 rows of 47: 119 -> 29 us, and the sum of the rows 121 -> 5 us.
 // A workgroup's sums of its rows go to block_sums (null: not wanted), its rows in a fixed order.
+// dlogits may be the logits themselves (same rows): every element is read by the lane that replaces it, and the label's logit
+// before that, so neither pointer promises to be the only one.
 template <typename T, int G, int E>
-__global__ __launch_bounds__(kBlock) void softmax_xent_kernel(const T* __restrict__ logits, int64_t ld,
+__global__ __launch_bounds__(kBlock) void softmax_xent_kernel(const T* logits, int64_t ld,
                                                               const int32_t* __restrict__ labels, int64_t n_rows,
-                                                              int32_t n_classes, float scale, T* __restrict__ dlogits,
+                                                              int32_t n_classes, float scale, T* dlogits,
                                                               int64_t ldd, float* __restrict__ row_loss,
                                                               int32_t* __restrict__ row_correct, float2* __restrict__ block_sums) {
     constexpr int kRows = kBlock / G;            // rows of a workgroup at a time
@@ -71,7 +73,8 @@ __global__ __launch_bounds__(kBlock) void softmax_xent_kernel(const T* __restric
         for (int off = G / 2; off > 0; off >>= 1) se += __shfl_xor(se, off);
         const bool on = y >= 0 && y < n_classes;
         float loss = 0.f;
-        if (on) loss = gmax + logf(se) - Elem<T>::load(z + y);      // before dlogits is written: it may be the same buffer
+        if (on) loss = gmax + logf(se) - Elem<T>::load(z + y);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");      // before any lane of the row writes dlogits
         if (dlogits) {
             T* d = dlogits + row * ldd;
             const float inv = scale / se;
