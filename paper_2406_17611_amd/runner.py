@@ -392,6 +392,7 @@ class KTapNetwork(PartitionedNetwork):
         self._taps_grad = torch.zeros(sum(sizes), **f32)       # one buffer: cleared by one launch
         flat = iter(self._taps_grad.split(sizes))
         self.dh = [[next(flat).view(self.widths[l], self.widths[l + 1]) for _ in range(n_taps)] for l in range(self.L)]
+        self._taps_views = tuple(m for taps in self.dh for m in taps)
         # y[l][hop] = S^hop X_l rows (hop 0 is x[l] itself)
         self.y = [[self.x[l]] + [torch.empty((self.n_total, self.widths[l]), **act) for _ in range(1, n_taps)]
                   for l in range(self.L)]
@@ -404,7 +405,12 @@ class KTapNetwork(PartitionedNetwork):
                 self.h[l][hop].copy_(torch.from_numpy(weights[l][hop]).to(self.device))
 
     def zero_grads(self):
-        self._taps_grad.zero_()
+        mine = [m for taps in self.dh for m in taps]
+        if len(mine) == len(self._taps_views) and all(a is b for a, b in zip(mine, self._taps_views)):
+            self._taps_grad.zero_()
+            return
+        for m in mine:                                         # a matrix was replaced by another tensor
+            m.zero_()
 
     def forward(self, step: int, ratio=None, stream=None):
         ctx = self.ctx

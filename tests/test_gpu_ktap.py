@@ -70,3 +70,13 @@ def test_ktap_network(n_taps, ratio, dtype):
     assert_close(net.to_global(net.dx[1]), _gather(orc, ref["dx"][1], g.n), "dX_1", tol)
     st = net.ctx.stats()
     assert st["fwd_elems"] == ref["fwd_elems"] and st["bwd_elems"] == ref["bwd_elems"]
+
+
+def test_zero_grads_clears_a_replaced_gradient():
+    g = synth.small_random_graph(200, 5.0, "sage", seed=75)
+    host, _ = both_partitions(g, synth.random_partition(g.n, 2, seed=76), 2)
+    net = KTapNetwork(host, (8, 16, 4), 3, KEY)
+    net.dh[1][2] = torch.ones(16, 4, device="cuda")
+    net.dh[0][0].fill_(1.0)
+    net.zero_grads()
+    assert not any(bool(m.any()) for taps in net.dh for m in taps)
