@@ -1,10 +1,9 @@
 #!/usr/bin/env python3
 """Benchmark of the VARCO layer hot path on one MI355X.
 
-A "step" is one pass of the whole hot path over the workload: for every layer and every partition in turn,
-compress boundary rows, aggregate (local rows + compressed halo rows), transform, activate, then the
-backward of the same (weight gradients, dM, transposed aggregation, compressed error hand-back, owner-side
-accumulation). Inputs are seeded synthetic graphs shaped like the paper's datasets and are resident in HBM
+A "step" is one pass of the whole hot path over the workload: for every layer and all partitions, compress
+boundary rows, aggregate (local rows + compressed halo rows), transform, activate, then the backward of the
+same (weight gradients, dM, transposed aggregation with the errors handed back at the kept positions). Inputs are seeded synthetic graphs shaped like the paper's datasets and are resident in HBM
 before the timed region starts.
 
     python bench.py [--gpus 1] [--steps K] [--warmup W]
@@ -114,9 +113,9 @@ def main():
     ap.add_argument("--workload", default="large_sage")
     ap.add_argument("--ratio", default=None, help="num/den, default: the configuration's ratio")
     ap.add_argument("--streams", type=int, default=None,
-                    help="HIP streams the partitions of a layer are dealt to in the timed steps (kernels of different "
-                         "partitions overlap; the per-kernel pass that follows always uses one stream). Default: 2, "
-                         "or 1 for a workload of two partitions (a step of a few hundred microseconds, where the joins cost more than the overlap gains)")
+                    help="HIP streams the partitions of a layer are dealt to where they are served one after the other (the "
+                         "per-kernel pass that follows always uses one stream). Default: 2, or 1 for a workload of two "
+                         "partitions. Linked partitions, the rule, share every launch and a single stream")
     ap.add_argument("--matmul-terms", type=int, default=None, choices=[0, 2, 3],
                     help="fp32 storage only: form of the dense products (library default 3; 0 = fp32 matrix instructions; "
                          "2 = lower precision, not a valid headline setting)")
@@ -130,7 +129,7 @@ def main():
     args = ap.parse_args()
     if args.gpus != 1:
         sys.exit("bench.py: this build runs on one GPU only (the partitions of the paper's setting are held in "
-                 "one MI355X's memory and processed in turn); --gpus must be 1")
+                 "one MI355X's memory and processed there); --gpus must be 1")
 
     from paper_2406_17611_amd import synth
     ratio = DEFAULT_RATIO.get(args.workload, (8, 1))
@@ -164,6 +163,7 @@ def main():
     L = len(w.widths) - 1
     net = PartitionedNetwork(host, w.widths, w.conv, synth.MASK_KEY, dtype=w.dtype, n_streams=args.streams,
                              transform_first=(L - 1,) if args.transform_first else ())
+    streams = 1 if net.linked else args.streams       # what the steps are issued on
     if args.matmul_terms is not None:
         net.ctx.set_matmul_terms(args.matmul_terms)
     net.set_inputs(synth.features(g.n, w.widths[0], synth.SEED_FEAT))
@@ -279,9 +279,9 @@ def main():
         "data": "synthetic",
         "config": {"workload": w.name, "nodes": g.n, "directed_entries": g.nnz, "partitions": w.n_parts,
                    "conv": w.conv, "widths": list(w.widths), "ratio": f"{ratio[0]}/{ratio[1]}",
-                   "keep": [net.ctx.keep(l) for l in range(L)], "layers": L, "streams": args.streams,
+                   "keep": [net.ctx.keep(l) for l in range(L)], "layers": L, "streams": streams,
                    "hip_graph": bool(args.graph), "transform_first_layers": [L - 1] if args.transform_first else [],
-                   "timed": f"{args.streams} stream{'s' if args.streams > 1 else ''}, " +
+                   "timed": f"{streams} stream{'s' if streams > 1 else ''}, " +
                             ("HIP graph replay" if args.graph else "eager launches") + ", no per-launch events; "
                             "per-kernel figures from a separate pass on one stream with HIP events around every launch",
                    "matmul_terms": (3 if args.matmul_terms is None else args.matmul_terms) if w.dtype == "f32" else None,

@@ -1159,7 +1159,7 @@ hipError_t halo_grad_t(const SpmmPlan& fwd_plan, const SpmmPlan& t_halo_plan, co
     b.partial = partial;
     b.ev = ev, b.ku = ku, b.lpe_log2 = lpe_log2;
     if (std::is_same_v<T, bf16_t> && rule.k % 8 == 0 && aligned_to(prod, 16) && aligned_to(out, 16) && aligned_to(partial, 16)) {
-        b.ev = 8, b.ku = int(rule.k) / 8;      // the sums read 16 bytes per lane (the products above are written 4 elements at a time)
+        b.ev = 8, b.ku = int(rule.k) / 8;      // the sums read 16 bytes per lane (as the products above are written)
         b.lpe_log2 = 0;
         while ((1 << b.lpe_log2) < b.ku && b.lpe_log2 < 6) ++b.lpe_log2;
     }

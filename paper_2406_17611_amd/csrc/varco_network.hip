@@ -42,8 +42,8 @@ size_t prod_floats(const varco_ctx* ctx, int32_t layer, int64_t k) {
 // no less accurate than the partitions' gradients formed one after the other (by fp32 sums over the slabs of each). Those have
 // slabs of `alone` rows; the longest ones here are as long with fp32 instructions; longer with expanded operands, by a factor
 // that grows with the rows as the drift grew that slabs of alternating sign are free of (kernels_gemm_split.hip); 900 rows and
-// 28 per partition with bf16, where the sums over slabs and partitions, exact now, were most of the error. Relative error against fp64 of independent products, partition after
-// partition / one round / now (and the time of the last two):
+// 28 per partition with bf16, where the sums over slabs and partitions, exact now, were most of the error. Relative error
+// against fp64 of independent products, partition after partition / one round / now (and the time of the last two):
 //   fp32  256 x 256   2,449,029 rows, 8 parts   3.4e-6 / 8.8e-6 / 2.0e-6  (one round)
 //                     169,343 rows, 4 parts     4.7e-7 / 8.6e-7 / 3.8e-7  (170, 180 us)
 //   bf16  512 x 512   2,449,029 rows, 32 parts  2.1e-7 / 1.2e-6 / 2.0e-7  (1.81, 2.30 ms)

@@ -1,7 +1,8 @@
 """Harness that holds all partitions of a graph in one GPU's memory and drives the C ABI: Algorithm 1's
 forward and backward for every layer and partition, with the inter-machine exchange replaced by on-device
 buffers (the compressed rows an owner writes are read in place by its consumers). The partitions share
-every kernel launch (varco_network_*); graphs too large for that are served partition after partition.
+every kernel launch (varco_network_*); graphs too large for that (2^31 entries, or no room for the joined arrays)
+are served partition after partition.
 
 Only sequencing and buffer bookkeeping live here; all arithmetic is in libvarco's kernels.
 """
@@ -17,8 +18,8 @@ class PartitionedNetwork:
     def __init__(self, host_parts, widths, conv: str, mask_key: int, device="cuda", need_backward=True, dtype="f32",
                  n_streams=1, transform_first=()):
         """dtype: storage of activations, messages and their gradients ("f32" or "bf16"); weights and weight
-        gradients are always fp32. n_streams > 1: where partitions are served one after the other (graphs with
-        2^31 or more entries), those of a layer are dealt to that many HIP streams, joined wherever a step needs
+        gradients are always fp32. n_streams > 1: where partitions are served one after the other (`linked` is
+        False), those of a layer are dealt to that many HIP streams, joined wherever a step needs
         all partitions; with all partitions in every launch there is nothing left to deal.
         transform_first: layers whose calls apply the weights before the aggregation (varco_set_layer_order)."""
         assert dtype in ("f32", "bf16")
@@ -59,7 +60,6 @@ class PartitionedNetwork:
         self.ret_src = [dp["ret_src"] for dp in self.dev_parts]
         assert all(hp.halo_row_offset == off for hp, off in zip(host_parts, self.halo_off))
 
-        f32 = dict(dtype=torch.float32, device=self.device)
         act = dict(dtype=self.act_dtype, device=self.device)
         self.x = [torch.empty((self.n_total, w), **act) for w in self.widths]
         self.m = [torch.empty((self.n_total, self.widths[l]), **act) for l in range(self.L)]
@@ -289,8 +289,8 @@ class PartitionedNetwork:
                             extra0[l].zero_()
 
     def _blocks(self):
-        """Row ranges that the calls without a partition argument are issued on."""
-        return [slice(0, self.n_total)] if self.linked else [self.rows(q) for q in range(self.P)]
+        """Row ranges of the partitions."""
+        return [self.rows(q) for q in range(self.P)]
 
     # ------------------------------------------------------------------ training (Algorithm 1's iteration)
     def set_labels(self, labels_global: np.ndarray, train_mask: np.ndarray):
@@ -306,7 +306,7 @@ class PartitionedNetwork:
         self._totals = torch.zeros(2, dtype=torch.float32, device=self.device)
 
     def loss(self, train: bool = True, with_gradient: bool = True, stream=None):
-        """Cross-entropy of the last layer's output on the training (or held-out) nodes, partition by partition;
+        """Cross-entropy of the last layer's output on the training (or held-out) nodes of all partitions;
         with_gradient writes the upstream gradient of the backward pass. Returns the device tensor
         [risk, number of correct rows] (read it after synchronising)."""
         labels = self.labels_train if train else self.labels_test
