@@ -190,8 +190,8 @@ int32_t varco_advance_step(varco_ctx* ctx, varco_stream stream);
  * is written exactly as a sum of three bf16 numbers and the six largest cross products are formed on the bf16
  * matrix units with fp32 accumulation; the dropped products are below 2^-24 of each full product, so the result
  * has the accuracy of fp32 arithmetic at well under half the cost. terms = 0: fp32 matrix instructions
- * throughout (also used, whatever the setting, for shapes the expanded form cannot take: rows not 16-byte
- * aligned). terms = 2: two terms, three products, relative error about 2^-16 per product (a faster,
+ * throughout (also used, whatever the setting, for shapes the expanded form does not take: forward and input-gradient
+ * products whose reduction length is no multiple of 4, weight gradients with fewer than 4 rows or columns). terms = 2: two terms, three products, relative error about 2^-16 per product (a faster,
  * lower-precision setting nothing in this library selects by itself). With terms 2 or 3 an operand that is
  * infinite, NaN or within 2^-9 of the fp32 overflow threshold turns the outputs it meets into NaN (fp32
  * instructions would keep an infinity times a finite number infinite); use terms = 0 where such values must
@@ -410,8 +410,9 @@ enum {
     VARCO_K_GEMM_FWD = 3,       /* act(M H1 + X H0) */
     VARCO_K_GEMM_WGRAD = 4,     /* dH += M^T dZ, X^T dZ (split reduction, partial products) */
     VARCO_K_GEMM_DGRAD = 5,     /* dM = dZ H1^T, dX += dZ H0^T */
-    VARCO_K_AGG_BWD_LOCAL = 6,  /* dX_loc = S_loc^T dM */
-    VARCO_K_AGG_BWD_HALO = 7,   /* dZ_halo = kept positions of S_halo^T dM (first pass: products in row order) */
+    VARCO_K_AGG_BWD_LOCAL = 6,  /* dX_loc = S_loc^T dM; linked partitions: all of dX, by node */
+    VARCO_K_AGG_BWD_HALO = 7,   /* dZ_halo = kept positions of S_halo^T dM (first pass: products in row order); linked
+                                 * partitions: the products alone */
     VARCO_K_REDUCE = 8,         /* fixed-order sums of split rows / split reductions */
     VARCO_K_AGG_BWD_HALO_SUM = 9, /* second pass of dZ_halo: sums of each halo row's products */
     VARCO_K_COUNT = 10

@@ -236,13 +236,13 @@ struct GemmArgs {
     GemmOperand a2, b2;           // optional second product summed into the same C (k2 reduction length)
     int32_t k2 = 0;
     // optional bf16 copies of B / B2 laid out [n][pitch] (reduction index contiguous, zero-padded to the pitch),
-    // made by varco_launch_prep_weight: with them, bf16 activations go through the bf16 matrix-core kernel
+    // made by varco_launch_prep_weights: with them, bf16 activations go through the bf16 matrix-core kernel
     const void* b_prep = nullptr;
     const void* b2_prep = nullptr;
     int64_t b_prep_ld = 0, b2_prep_ld = 0;
     // fp32 operands on the bf16 matrix cores: 0 = no (fp32 matrix instructions); 2 or 3 = each operand is
     // expanded into that many bf16 terms, and b_prep / b2_prep are expanded copies made by
-    // varco_launch_prep_weight_split, [term][n][pitch] with `plane` elements between terms
+    // varco_launch_prep_weights (by tile and stage, `plane` elements per term in all)
     int32_t f32_terms = 0;
     int64_t b_prep_plane = 0, b2_prep_plane = 0;
     void* c = nullptr;

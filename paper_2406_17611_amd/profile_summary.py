@@ -3,7 +3,7 @@ the entry of profiles/hbm_traffic.json that bench.py reports as `roofline.traffi
 
 The three runs (on the GPU machine, from /tmp with TMPDIR=/tmp; <out> is any directory; one counter per run):
 
-  rocprofv3 --kernel-trace --stats --output-format csv -d <out> -o trace -- python3 bench.py --workload W --steps 3 --warmup 1 --streams 1 --no-cpu-baseline > <out>/trace_bench.json
+  rocprofv3 --kernel-trace --stats --output-format csv -d <out> -o trace -- python3 bench.py --workload W --steps 3 --warmup 1 --no-cpu-baseline > <out>/trace_bench.json
   rocprofv3 --pmc FETCH_SIZE --output-format csv -d <out> -o fetch -- python3 bench.py --workload W --steps 1 --warmup 1 --no-cpu-baseline
   rocprofv3 --pmc WRITE_SIZE --output-format csv -d <out> -o write -- python3 bench.py --workload W --steps 1 --warmup 1 --no-cpu-baseline
 
@@ -46,11 +46,8 @@ def _short(name: str) -> str:
 
 def _kernel_class(n: str):
     """bench.py's kernel class of a kernel name (None for kernels outside the memory-bound classes)."""
-    if n.startswith("spmm_kernel"):
-        return "agg_bwd_local" if n.rstrip(">").endswith(" 0") else "agg_fwd"
-    for prefix, c in (("spmm_short_rows_kernel", "agg_bwd_local"), ("halo_products_kernel", "agg_bwd_halo"),
-                      ("halo_segsum_kernel", "agg_bwd_halo_sum"), ("compress_kernel", "compress"),
-                      ("accumulate_returned_kernel", "decompress")):
+    for prefix, c in (("spmm_kernel", "agg_fwd"), ("node_sum_kernel", "agg_bwd_local"), ("halo_products_kernel", "agg_bwd_halo"),
+                      ("codec_rows_kernel", "compress"), ("whole_rows_kernel", "compress"), ("compress_kernel", "compress")):
         if n.startswith(prefix):
             return c
     return None
@@ -86,9 +83,8 @@ def summarise(workload: str, out_dir: str) -> dict:
         rows = list(csv.DictReader(f))
     with open(os.path.join(prof_dir, f"{workload}_kernel_stats.txt"), "w") as f:
         f.write(f"rocprofv3 kernel statistics, bench.py on {desc}, MI355X;\n1 warm-up + 3 timed + 1 untimed + 3 event-bracketed "
-                f"steps (8 steps of launches), all on one stream, so that no two launches overlap and the averages\nbelow are those of "
-                f"kernels that have the device to themselves (the headline configuration deals the partitions to two streams).\n"
-                f"command: {cmd.format(what='--kernel-trace --stats', name='trace', steps=3, extra=' --streams 1')}\n"
+                f"steps (8 steps of launches).\n"
+                f"command: {cmd.format(what='--kernel-trace --stats', name='trace', steps=3, extra='')}\n"
                 f"summary written by: python -m paper_2406_17611_amd.profile_summary {workload} <out>\n\n")
         f.write(f"{'kernel':78s} {'calls':>6s} {'total ms':>10s} {'avg us':>10s} {'%':>6s}\n")
         for r in rows:
@@ -137,11 +133,10 @@ def summarise(workload: str, out_dir: str) -> dict:
             if c:
                 per_class[c][0] += sum(fetch[n]) * 1024 / sf
                 per_class[c][1] += sum(write[n]) * 1024 / sw if n in write else 0.0
-                if not n.startswith("spmm_short_rows_kernel"):      # second kernel of the same call
+                if not (n.startswith("node_sum_kernel") and n.endswith("true>")):      # second kernel of the same call
                     per_class[c][2] += len(fetch[n])
-        f.write("\n(spmm_kernel<..., 1 or 2>: forward aggregation, entries may refer to compressed rows (2: 32-bit offsets "
-                "into that buffer), all layers; spmm_kernel<..., 0>: dense rows only (transposed local block). Launches "
-                "of one class are averaged together.)\n")
+        f.write("\n(spmm_kernel: forward aggregation, all layers; node_sum_kernel: backward aggregation by node, in a second "
+                "launch (<..., true>) the hub nodes whose pieces the first one summed. Launches of one class are averaged together.)\n")
 
     path = os.path.join(prof_dir, "hbm_traffic.json")
     try:
