@@ -205,7 +205,7 @@ int32_t varco_set_matmul_terms(varco_ctx* ctx, int32_t terms);
  * subgraph). With k = 0 the compressed buffers of that layer are not touched and may be NULL. STATE error if
  * the layer's positions are already in use in the current step (by compress, decompress or a forward
  * call; its backward must see the same positions). Host call: when the new k needs a larger halo-gradient
- * workspace than the prepared streams hold, it is reallocated here (synchronising the device), with a quarter
+ * workspace than the prepared streams hold, it is reallocated here (synchronising the device), growing with a quarter
  * of head-room so that a schedule that raises k step by step reallocates rarely. Sequences captured earlier stay
  * valid at the ratio they were captured with: buffers of the library that a captured call uses are kept until
  * varco_destroy (a stream whose calls were captured is given the largest such workspace that any ratio needs at its
@@ -350,8 +350,8 @@ int32_t varco_accumulate_returned(varco_ctx* ctx, int32_t layer, int32_t p, cons
  *
  * Device memory of the joined form, allocated by the library itself (a caller whose allocator takes all memory sets the
  * ratio first): 28 bytes per entry and up to 60 per node, in this call; per prepared stream, in varco_prepare, n_total
- * rows of the widest layer and the partial products of the weight gradients (about 1 GB for 512 x 512 bf16 weights over
- * 2.4 million nodes; 4 GiB per pair of weight matrices at most); and while 3 k < width[l] for an l > 0, in
+ * rows of the widest layer and the partial products of the weight gradients (1.3 GB for 512 x 512 bf16 weights over
+ * 2.4 million nodes; 4 GiB per weight matrix or pair at most); and while 3 k < width[l] for an l > 0, in
  * varco_set_ratio, up to 1.25 k elements per entry of a halo column, 48 GiB at most. The last is optional: beyond that size,
  * or where it cannot be had, whole rows are gathered instead. With fp32 storage that changes the order of sums only; with
  * bf16 storage the products are rounded to bf16 and gathered rows are not, so the input gradients then differ by such

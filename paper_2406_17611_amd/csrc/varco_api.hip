@@ -202,11 +202,12 @@ hipError_t grow(Workspace& ws, float*& buf, size_t& have, size_t want) {
 }
 
 // The product buffer: `want` floats now, `most` at any ratio. A schedule raises k step by step, and every new buffer costs a
-// synchronisation: a quarter of head-room (16 -> 3 at width 256: 8 allocations, one per row of 16 bytes without). Buffers that a
-// graph uses are kept, so a workspace with one goes to its final size at once.
+// synchronisation: growing leaves a quarter of head-room (16 -> 3 at width 256: 8 allocations, one per row of 16 bytes without);
+// the first one, all that a constant ratio needs, leaves none. Buffers that a graph uses are kept, so a workspace with one goes
+// to its final size at once.
 hipError_t grow_products(Workspace& ws, size_t want, size_t most) {
     if (want <= ws.prod_elems) return hipSuccess;
-    const size_t room = ws.captured ? most : std::min(most, want + want / 4);
+    const size_t room = ws.captured ? most : ws.prod ? std::min(most, want + want / 4) : want;
     const hipError_t e = grow(ws, ws.prod, ws.prod_elems, std::max(want, room));
     if (e != hipErrorOutOfMemory || room <= want) return e;
     (void)hipGetLastError();
@@ -227,6 +228,11 @@ int64_t wgrad_slots(int32_t m, int32_t n, int kind, int products) {
 int32_t gemm_split_for(int32_t m, int32_t n, int64_t k, int kind) {
     const int64_t k_tiles = kind == kGemmF32 ? (k + 15) / 16 : (k + 31) / 32;
     return int32_t(std::min<int64_t>(wgrad_slots(m, n, kind, 1), std::max<int64_t>(1, k_tiles / 8)));
+}
+int32_t plain_bf16_split(int32_t m, int32_t n, int64_t k) {
+    const int32_t bn = n <= 64 ? 64 : 128;
+    const int64_t tiles = int64_t((m + 255) / 256) * ((n + bn - 1) / bn);
+    return int32_t(std::min<int64_t>(std::max<int64_t>(1, 512 / tiles), std::max<int64_t>(1, (k + 31) / 32 / 8)));
 }
 int gemm_kind(const GemmArgs& g) {
     return varco_gemm_bf16_usable(g) ? kGemmBf16 : varco_gemm_split_usable(g) ? kGemmExpanded : kGemmF32;
@@ -1255,11 +1261,8 @@ namespace {
 int32_t transform_split(int32_t m, int32_t n, int64_t rows, int kind, size_t* need) {
     const size_t one = size_t(m) * size_t(n);
     int32_t split = gemm_split_for(m, n, rows, kind);
-    if (kind == kGemmBf16) {
-        const int64_t tiles = int64_t((m + 255) / 256) * ((n + (n <= 64 ? 63 : 127)) / (n <= 64 ? 64 : 128));
-        const int64_t plain = std::min<int64_t>(std::max<int64_t>(1, 512 / tiles), std::max<int64_t>(1, (rows + 31) / 32 / 8));
-        if (size_t(plain) * one <= kScratchFloats) split = int32_t(std::min<int64_t>(split, int64_t(kScratchFloats / one)));
-    }
+    if (kind == kGemmBf16 && size_t(plain_bf16_split(m, n, rows)) * one <= kScratchFloats)
+        split = int32_t(std::min<int64_t>(split, int64_t(kScratchFloats / one)));
     *need = split > 1 ? size_t(split) * one : 0;
     return split;
 }

@@ -132,6 +132,7 @@ void free_network(NetState& net);
 size_t network_prod_need(const varco_ctx* ctx, size_t* most);
 enum GemmKind { kGemmF32 = 0, kGemmBf16 = 1, kGemmExpanded = 2 };     // kGemmBf16: as weight gradients
 int32_t gemm_split_for(int32_t m, int32_t n, int64_t k, int kind);
+int32_t plain_bf16_split(int32_t m, int32_t n, int64_t k);      // the same for bf16 in tiles of 256 x 128, two workgroups per compute unit
 int gemm_kind(const GemmArgs& g);
 int64_t wgrad_slots(int32_t m, int32_t n, int kind, int products);     // slabs that fill the device once
 constexpr int kWeightSlots = 4;       // converted copies held per layer and orientation: of the two taps of a layer, or of the first taps of a K-tap layer

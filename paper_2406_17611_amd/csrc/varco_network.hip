@@ -41,18 +41,19 @@ size_t prod_floats(const varco_ctx* ctx, int32_t layer, int64_t k) {
 // The fp32 sum of a slab loses accuracy with the square root of its length, so there are as many rounds as keep the result
 // no less accurate than the partitions' gradients formed one after the other (by fp32 sums over the slabs of each). Those have
 // slabs of `alone` rows; the longest ones here are as long with fp32 instructions; longer with expanded operands, by a factor
-// that grows with the rows as the drift grew that slabs of alternating sign are free of (kernels_gemm_split.hip); 900 rows and
-// 28 per partition with bf16, where the sums over slabs and partitions, exact now, were most of the error. Relative error
-// against fp64 of independent products, partition after partition / one round / now (and the time of the last two):
+// that grows with the rows as the drift grew that slabs of alternating sign are free of (kernels_gemm_split.hip); longer with
+// bf16 by 4 rows per slab and 16 per partition, which is what adding one cost (these sums are exact now). Fitted to 110 shapes
+// of 12,000 to 2,449,029 rows, 2 to 32 partitions and 64 x 64 to 512 x 512 weights; relative error against fp64 of independent
+// products, partition after partition / one round / now (and the time of the last two):
 //   fp32  256 x 256   2,449,029 rows, 8 parts   3.4e-6 / 8.8e-6 / 2.0e-6  (one round)
 //                     169,343 rows, 4 parts     4.7e-7 / 8.6e-7 / 3.8e-7  (170, 180 us)
-//   bf16  512 x 512   2,449,029 rows, 32 parts  2.1e-7 / 1.2e-6 / 2.0e-7  (1.81, 2.30 ms)
+//   bf16  512 x 512   2,449,029 rows, 32 parts  2.1e-7 / 1.2e-6 / 2.0e-7  (1.81, 2.26 ms)
 //                     169,343 rows, 4 parts     1.5e-7 / 2.6e-7 / 1.3e-7  (158, 210 us: writing and reading the partial products)
 int32_t wgrad_splits(const varco_ctx* ctx, int32_t m, int32_t n, int64_t rows, int kind, int products) {
     const int64_t step = kind == kGemmF32 ? 16 : 32;
-    const int64_t slots = wgrad_slots(m, n, kind, products);
-    const int64_t alone = ctx->net.largest / gemm_split_for(m, n, ctx->net.largest, kind);
-    const int64_t longest = kind == kGemmExpanded ? alone * (137'500 + rows) / 110'000 : kind == kGemmBf16 ? 900 + 28 * std::min(ctx->n_parts, 32) : alone;
+    const int64_t slots = wgrad_slots(m, n, kind, products), most = ctx->net.largest;
+    const int64_t split = kind == kGemmBf16 ? plain_bf16_split(m, n, most) : gemm_split_for(m, n, most, kind), alone = most / split;
+    const int64_t longest = kind == kGemmExpanded ? alone * (137'500 + rows) / 110'000 : kind == kGemmBf16 ? alone + 4 * split + 16 * ctx->n_parts : alone;
     const int64_t round = slots * std::max<int64_t>(1, longest);
     const int64_t rounds = std::max<int64_t>(1, std::min((rows + round - 1) / round, kPartialElems / (slots * products * m * n)));
     return int32_t(std::min<int64_t>(rounds * slots, std::max<int64_t>(1, (rows + step - 1) / step / 2)));
@@ -204,10 +205,13 @@ int32_t link_impl(varco_ctx* ctx) {
     int64_t gemm_elems = 0;
     for (int32_t l = 0; l < ctx->n_layers; ++l) {     // the partial products of all layers wait for one sum
         const int32_t fi = ctx->widths[l], fo = ctx->widths[l + 1];
-        int64_t splits = 0;                           // of one tap, or of two taps that share a launch (any context's K-tap layers)
-        for (int kind : {kGemmF32, kGemmBf16, kGemmExpanded})
-            splits = std::max<int64_t>({splits, (ctx->conv == VARCO_CONV_SAGE ? 2 : 1) * int64_t(wgrad_splits(ctx, fi, fo, net.rows, kind, 1)),
-                                        2 * int64_t(wgrad_splits(ctx, fi, fo, net.rows, kind, 2))});
+        const int usual = ctx->dtype == VARCO_BF16 ? kGemmBf16 : kGemmExpanded;
+        const bool other = ctx->dtype == VARCO_F32 || fi < 8 || fo < 8;        // fp32 instructions, on request or for narrow bf16 weights
+        const int taps = ctx->conv == VARCO_CONV_SAGE ? 2 : 1;
+        int64_t splits = 0;
+        for (int products = 1; products <= taps; ++products)                   // taps one by one, or sharing a launch
+            for (int kind : {usual, other ? int(kGemmF32) : usual})
+                splits = std::max(splits, int64_t(taps) * wgrad_splits(ctx, fi, fo, net.rows, kind, products));
         gemm_elems += splits * fi * fo;
     }
     ctx->need_dm = std::max(ctx->need_dm, (size_t(net.rows) * size_t(wmax) * size_t(ctx->elem_bytes()) + 3) / 4);
@@ -750,7 +754,9 @@ extern "C" int32_t varco_network_taps_bwd_weight(varco_ctx* ctx, int32_t layer, 
             int32_t unused = 0;
             g.deferred = &unused;
             g.a_dual = y[i + 1], g.c_dual = dh[i + 1];
-            if (!varco_gemm_dual_usable(g)) g.a_dual = nullptr, g.c_dual = nullptr;
+            // (a context of one tap per layer has room for one tap's partial products, which two taps may exceed)
+            if (!varco_gemm_dual_usable(g) || size_t(wgrad_splits(ctx, fi, fo, g.k, gemm_kind(g), 2)) * 2 * fi * fo > ws->gemm_elems)
+                g.a_dual = nullptr, g.c_dual = nullptr;
         }
         const int32_t products = g.c_dual ? 2 : 1;
         const size_t want = size_t(wgrad_splits(ctx, fi, fo, g.k, gemm_kind(g), products)) * products * fi * fo;

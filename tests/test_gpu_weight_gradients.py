@@ -30,7 +30,7 @@ def _linked_context(n, n_parts, fi, fo, dtype, terms):
 # rows a slab may hold for these sizes and roundings per row: the matrix units round once per 8 rows and product (six products
 # with three terms), with fp32 instructions once per 2 rows
 @pytest.mark.parametrize("dtype,terms,fi,fo,slab_rows,roundings", [(vb.F32, 3, 256, 256, 330 * (137_500 + 169_343) / 110_000, 6 / 8), (vb.F32, 0, 256, 256, 220, 1 / 2),
-                                                                   (vb.BF16, 1, 512, 512, 900 + 28 * 4, 1 / 8)])
+                                                                   (vb.BF16, 1, 512, 512, 661 + 4 * 64 + 16 * 4, 1 / 8)])
 def test_long_reductions_keep_the_accuracy_of_short_ones(dtype, terms, fi, fo, slab_rows, roundings):
     n, n_parts = 169_343, 4
     ctx, held = _linked_context(n, n_parts, fi, fo, dtype, terms)
