@@ -1,7 +1,7 @@
 """Turns the CSV output of three rocprofv3 runs of bench.py into the short text summaries under profiles/ and
 the entry of profiles/hbm_traffic.json that bench.py reports as `roofline.traffic`.
 
-The three runs (on the GPU machine, from /tmp with TMPDIR=/tmp; <out> is any directory; one counter per run):
+The three runs (where the GPU is, from /tmp with TMPDIR=/tmp; <out> is any directory; one counter per run):
 
   rocprofv3 --kernel-trace --stats --output-format csv -d <out> -o trace -- python3 bench.py --workload W --steps 3 --warmup 1 --no-cpu-baseline > <out>/trace_bench.json
   rocprofv3 --pmc FETCH_SIZE --output-format csv -d <out> -o fetch -- python3 bench.py --workload W --steps 1 --warmup 1 --no-cpu-baseline
