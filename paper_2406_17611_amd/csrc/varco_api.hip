@@ -322,9 +322,8 @@ void transform_first_need(const varco_ctx* ctx, size_t* rows_out, size_t* record
         if (ps.registered) rows = std::max(rows, int64_t(ps.d.n_local) + ps.d.n_halo), halo = std::max<int64_t>(halo, ps.d.n_halo);
     *rows_out = fo ? (size_t(rows) * size_t(fo) * size_t(ctx->elem_bytes()) + 3) / 4 : 0;
     *records_out = fo ? size_t(halo) * 2 : 0;
-    if (fo && ctx->net.linked) {     // all partitions at once: [Y ; Y_z], or dZ, G_loc and G_z, in rows of kClassPitch elements
-        const size_t block = size_t(2 * ctx->net.rows + ctx->net.boundary) * kClassPitch * size_t(ctx->elem_bytes()) / 4;
-        *rows_out = std::max(*rows_out, block);
+    if (fo && ctx->net.linked) {     // all partitions at once
+        *rows_out = std::max(*rows_out, class_block_floats(ctx));
         *records_out = std::max(*records_out, size_t(ctx->net.boundary) * 2);
     }
 }
@@ -347,11 +346,26 @@ int32_t size_workspace(varco_ctx* ctx, Workspace& ws) {
         (void)hipGetLastError();
         VARCO_HIP(ctx, grow_products(ws, prod, std::max(most, network_most)));
     }
-    VARCO_HIP(ctx, grow(ws, ws.tf, ws.tf_elems, tf_rows));
+    bool narrow = false;
+    for (int32_t l = 0; l < ctx->n_layers; ++l) narrow = narrow || (ctx->net.linked && narrow_sums_possible(ctx, l));
+    // (an option like the products: without these rows errors are summed at the width of the inputs)
+    if (!narrow || class_block_floats(ctx) <= tf_rows || grow(ws, ws.tf, ws.tf_elems, class_block_floats(ctx)) != hipSuccess) {
+        (void)hipGetLastError();
+        VARCO_HIP(ctx, grow(ws, ws.tf, ws.tf_elems, tf_rows));
+    }
     VARCO_HIP(ctx, grow(ws, ws.hrows, ws.hrows_elems, tf_records));
     if (ws.w_tags.empty()) ws.w_tags.resize(size_t(ctx->n_layers) * kWeightSlots * 2);
     return VARCO_OK;
 }
+bool narrow_sums_possible(const varco_ctx* ctx, int32_t l) {
+    const int32_t fi = ctx->widths[l], fo = ctx->widths[l + 1];
+    return l > 0 && ctx->dtype == VARCO_BF16 && ctx->layers[l].order == VARCO_ORDER_AGGREGATE_FIRST && ctx->act[l] == VARCO_ACT_IDENTITY &&
+           fo <= kClassPitch && fo < fi && fi % 16 == 0 && fi <= 512;
+}
+size_t class_block_floats(const varco_ctx* ctx) {
+    return size_t(2 * ctx->net.rows + ctx->net.boundary) * kClassPitch * size_t(ctx->elem_bytes()) / 4;
+}
+
 int32_t size_all_workspaces(varco_ctx* ctx) {
     for (Workspace& w : ctx->ws)
         if (w.used)

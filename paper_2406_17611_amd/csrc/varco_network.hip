@@ -59,6 +59,22 @@ int32_t wgrad_splits(const varco_ctx* ctx, int32_t m, int32_t n, int64_t rows, i
     return int32_t(std::min<int64_t>(rounds * slots, std::max<int64_t>(1, (rows + step - 1) / step / 2)));
 }
 
+// Whether the input gradient of a class layer that aggregated first is formed from errors summed at the width of the outputs
+// (class_sums, class_input). Bytes per entry: a row of kClassPitch elements, against a whole row of dM for a local entry and,
+// for a cross one, a row of products written and read back (which costs no less than 128 bytes do, however short) or a whole row
+// of dM; dM itself is then neither written nor read. A whole step, widths at the layer's inputs and products, us:
+//   bf16, 2,449,029 nodes, 97 % of 126,167,309 entries cross, 512 inputs: ratio 4 54,160 -> 44,070, 32 38,620 -> 33,160,
+//     64 38,000 -> 32,540
+//   bf16, 169,343 nodes, 75 % of 2,501,829 entries cross: 512 inputs, ratio 1 2,577 -> 2,343, 4 2,190 -> 1,931, 64 1,871 -> 1,737;
+//     64 inputs, ratio 32 1,029 -> 939; 128 inputs, ratio 8, SAGE 1,314 -> 1,255, ratio 16, GCN 1,098 -> 1,039
+bool narrow_sums_pay(const varco_ctx* ctx, int32_t l) {
+    if (!narrow_sums_possible(ctx, l)) return false;
+    const NetState& net = ctx->net;
+    const double row = ctx->widths[l] * ctx->elem_bytes(), k = ctx->layers[l].k, cross = k > 0 ? double(net.nnz_cross) : 0.0;
+    const double wide = double(net.nnz_local) * row + cross * std::min(std::max(2.0 * k * ctx->elem_bytes(), 128.0), row) + 2.0 * double(net.rows) * row;
+    return (double(net.nnz_local) + cross) * kClassPitch * ctx->elem_bytes() <= wide;
+}
+
 template <typename P>
 hipError_t alloc(P*& p, size_t n) {
     return n ? hipMalloc(reinterpret_cast<void**>(&p), n * sizeof(P)) : hipSuccess;
@@ -295,8 +311,7 @@ struct WeightSums {
 // A layer that transforms before it aggregates (kernels_class_first.hip).
 int32_t class_fits(varco_ctx* ctx, const Workspace& ws, const char* fn) {
     const NetState& net = ctx->net;
-    const size_t need = size_t(2 * net.rows + net.boundary) * kClassPitch * size_t(ctx->elem_bytes()) / 4;
-    if (need <= ws.tf_elems && size_t(net.boundary) * 2 <= ws.hrows_elems) return VARCO_OK;
+    if (class_block_floats(ctx) <= ws.tf_elems && size_t(net.boundary) * 2 <= ws.hrows_elems) return VARCO_OK;
     std::string m = std::string(fn) + ": the stream's workspace is too small; call varco_prepare";
     return varco_fail(ctx, VARCO_ERR_STATE, m.c_str());
 }
@@ -375,53 +390,41 @@ int32_t add_weight_product(varco_ctx* ctx, Workspace& ws, GemmArgs& g, WeightSum
     return VARCO_OK;
 }
 
-int32_t class_bwd(varco_ctx* ctx, Workspace& ws, const varco_network_buffers& b, int32_t l, WeightSums& sums, hipStream_t st) {
+// Backward pass of a narrowing class layer in two steps that do not depend on the order of its forward pass: the errors of all
+// its consumers are summed at the width of the outputs, G = S^T dZ, and then taken back through the weights,
+//   dX[v] = G_loc[v] H1^T + kept positions of (G_z[v] H1^T) (+ dZ[v] H0^T),
+// instead of through the weights first and summed at the width of the inputs (dM = dZ H1^T; dX = S^T dM).
+struct ClassRows {
+    uint16_t *dz, *g_loc, *g_z;      // rows of kClassPitch elements in the workspace; g_z null: no errors come back
+};
+ClassRows class_rows(const varco_ctx* ctx, const Workspace& ws, const MaskRule& rule) {
     const NetState& net = ctx->net;
-    const int32_t fi = ctx->widths[l], fo = ctx->widths[l + 1];
-    const int dt = ctx->dtype;
+    ClassRows r;
+    r.dz = reinterpret_cast<uint16_t*>(ws.tf);
+    r.g_loc = r.dz + net.rows * kClassPitch;
+    r.g_z = net.nnz_cross > 0 && rule.k > 0 ? r.g_loc + net.rows * kClassPitch : nullptr;
+    return r;
+}
+int32_t class_sums(varco_ctx* ctx, Workspace& ws, const varco_network_buffers& b, int32_t l, const ClassRows& r, hipStream_t st) {
+    const NetState& net = ctx->net;
+    const int32_t fo = ctx->widths[l + 1];
     const double es = ctx->elem_bytes();
-    const bool sage = ctx->conv == VARCO_CONV_SAGE, need = l > 0;
-    const MaskRule rule = make_rule(ctx, l);
-    const bool far = net.nnz_cross > 0 && rule.k > 0;
-    if (int32_t rc = class_fits(ctx, ws, "varco_network_backward")) return rc;
-    uint16_t* const dz = reinterpret_cast<uint16_t*>(ws.tf);
-    uint16_t* const g_loc = dz + net.rows * kClassPitch;
-    uint16_t* const g_z = g_loc + net.rows * kClassPitch;
     const double entries = double(net.nnz) * 8.0 + (double(net.rows) + 1.0) * 4.0;
-    VARCO_HIP(ctx, varco_launch_narrow_backward(net.nodes, net.t_local, net.t_cross, b.dx[l + 1], net.rows, net.zrow_of, dz, g_loc, far ? g_z : nullptr,
+    VARCO_HIP(ctx, varco_launch_narrow_backward(net.nodes, net.t_local, net.t_cross, b.dx[l + 1], net.rows, net.zrow_of, r.dz, r.g_loc, r.g_z,
                                                 fo, ws.spmm, st,
                                                 ctx->tag(VARCO_K_AGG_BWD_LOCAL, entries + (2.0 * double(net.rows) + double(net.boundary)) * fo * es, 0,
                                                          entries + (double(net.rows) + double(net.nnz)) * fo * es)));
-    GemmArgs g;
-    g.m = fi, g.n = fo, g.k = int32_t(net.rows);
-    g.a.ptr = b.x[l], g.a.ld = fi, g.a.transposed = true, g.a.dtype = dt;
-    g.b.ptr = g_loc, g.b.ld = kClassPitch, g.b.dtype = dt;
-    g.c = b.dh1[l], g.ldc = fo;
-    g.accumulate = true;
-    if (int32_t rc = add_weight_product(ctx, ws, g, sums, st)) return rc;
-    if (sage) {
-        g.b.ptr = dz, g.c = b.dh0[l];
-        if (int32_t rc = add_weight_product(ctx, ws, g, sums, st)) return rc;
-    }
-    if (far) {   // + X~_z^T G_z: per-workgroup shares
-        VARCO_HIP(ctx, varco_launch_halo_rows(rule, net.bgid, nullptr, int32_t(net.boundary), reinterpret_cast<uint2*>(ws.hrows), st));
-        const LaunchTag tag = ctx->tag(VARCO_K_GEMM_WGRAD, double(net.boundary) * (rule.k + fo) * es, 2.0 * double(rule.k) * fo * double(net.boundary));
-        int32_t slabs = 0;
-        float* const partial = ws.gemm + sums.used;
-        tag.begin(st);
-        const hipError_t e = varco_launch_halo_transform_wgrad(boundary_transform(ctx, ws, rule, b.z[l], fo), g_z, partial,
-                                                               int64_t(ws.gemm_elems - sums.used), &slabs, st);
-        tag.end(st);
-        VARCO_HIP(ctx, e);
-        // (added by a launch of its own: the sums of a pass go to distinct results)
-        VARCO_HIP(ctx, varco_launch_gemm_reduce(partial, slabs, fi, fo, static_cast<float*>(b.dh1[l]), fo, true, st, tag));
-    }
-    if (!need) return VARCO_OK;
+    return VARCO_OK;
+}
+int32_t class_input(varco_ctx* ctx, Workspace& ws, const varco_network_buffers& b, int32_t l, const MaskRule& rule, const ClassRows& r, hipStream_t st) {
+    const NetState& net = ctx->net;
+    const int32_t fi = ctx->widths[l], fo = ctx->widths[l + 1];
+    const int dt = ctx->dtype;
     GemmArgs gw;                       // carries the slot of the weights' bf16 copy [position][column]
     VARCO_HIP(ctx, prep_weight(ctx, ws, l, b.h1[l], fi, fo, false, 0, false, st, gw));
-    VARCO_HIP(ctx, varco_launch_class_dgrad(g_loc, far ? g_z : nullptr, net.zrow_of, net.bgid, net.rows, rule, fo, gw.b_prep, int32_t(gw.b_prep_ld),
+    VARCO_HIP(ctx, varco_launch_class_dgrad(r.g_loc, r.g_z, net.zrow_of, net.bgid, net.rows, rule, fo, gw.b_prep, int32_t(gw.b_prep_ld),
                                             b.dx[l], st, ctx->tag(VARCO_K_GEMM_DGRAD, 0, 2.0 * fi * fo * double(net.rows))));
-    if (sage) {                        // + dZ H0^T
+    if (ctx->conv == VARCO_CONV_SAGE) {                        // + dZ H0^T
         GemmArgs g0;
         g0.m = int32_t(net.rows), g0.n = fi, g0.k = fo;
         g0.a.ptr = b.dx[l + 1], g0.a.ld = fo, g0.a.dtype = dt;
@@ -435,6 +438,42 @@ int32_t class_bwd(varco_ctx* ctx, Workspace& ws, const varco_network_buffers& b,
         ctx->stats.full_bwd_elems[l] += net.halo_rows * fi;
     }
     return VARCO_OK;
+}
+
+int32_t class_bwd(varco_ctx* ctx, Workspace& ws, const varco_network_buffers& b, int32_t l, WeightSums& sums, hipStream_t st) {
+    const NetState& net = ctx->net;
+    const int32_t fi = ctx->widths[l], fo = ctx->widths[l + 1];
+    const int dt = ctx->dtype;
+    const double es = ctx->elem_bytes();
+    const MaskRule rule = make_rule(ctx, l);
+    if (int32_t rc = class_fits(ctx, ws, "varco_network_backward")) return rc;
+    const ClassRows r = class_rows(ctx, ws, rule);
+    if (int32_t rc = class_sums(ctx, ws, b, l, r, st)) return rc;
+    GemmArgs g;
+    g.m = fi, g.n = fo, g.k = int32_t(net.rows);
+    g.a.ptr = b.x[l], g.a.ld = fi, g.a.transposed = true, g.a.dtype = dt;
+    g.b.ptr = r.g_loc, g.b.ld = kClassPitch, g.b.dtype = dt;
+    g.c = b.dh1[l], g.ldc = fo;
+    g.accumulate = true;
+    if (int32_t rc = add_weight_product(ctx, ws, g, sums, st)) return rc;
+    if (ctx->conv == VARCO_CONV_SAGE) {
+        g.b.ptr = r.dz, g.c = b.dh0[l];
+        if (int32_t rc = add_weight_product(ctx, ws, g, sums, st)) return rc;
+    }
+    if (r.g_z) {   // + X~_z^T G_z: per-workgroup shares
+        VARCO_HIP(ctx, varco_launch_halo_rows(rule, net.bgid, nullptr, int32_t(net.boundary), reinterpret_cast<uint2*>(ws.hrows), st));
+        const LaunchTag tag = ctx->tag(VARCO_K_GEMM_WGRAD, double(net.boundary) * (rule.k + fo) * es, 2.0 * double(rule.k) * fo * double(net.boundary));
+        int32_t slabs = 0;
+        float* const partial = ws.gemm + sums.used;
+        tag.begin(st);
+        const hipError_t e = varco_launch_halo_transform_wgrad(boundary_transform(ctx, ws, rule, b.z[l], fo), r.g_z, partial,
+                                                               int64_t(ws.gemm_elems - sums.used), &slabs, st);
+        tag.end(st);
+        VARCO_HIP(ctx, e);
+        // (added by a launch of its own: the sums of a pass go to distinct results)
+        VARCO_HIP(ctx, varco_launch_gemm_reduce(partial, slabs, fi, fo, static_cast<float*>(b.dh1[l]), fo, true, st, tag));
+    }
+    return l > 0 ? class_input(ctx, ws, b, l, rule, r, st) : VARCO_OK;
 }
 
 int32_t layer_fwd(varco_ctx* ctx, Workspace& ws, const varco_network_buffers& b, int32_t l, hipStream_t st) {
@@ -501,6 +540,12 @@ int32_t layer_bwd(varco_ctx* ctx, Workspace& ws, const varco_network_buffers& b,
         }
     }
     if (!need) return VARCO_OK;
+    if (narrow_sums_pay(ctx, l) && class_block_floats(ctx) <= ws.tf_elems && (reinterpret_cast<uintptr_t>(b.dx[l]) & 15u) == 0) {
+        const MaskRule rule = make_rule(ctx, l);
+        const ClassRows r = class_rows(ctx, ws, rule);
+        if (int32_t rc = class_sums(ctx, ws, b, l, r, st)) return rc;
+        return class_input(ctx, ws, b, l, rule, r, st);
+    }
     GemmArgs g;                    // dM = dZ H1^T
     g.m = nl, g.n = fi, g.k = fo;
     g.a.ptr = b.dx[l + 1], g.a.gate = gate, g.a.ld = fo, g.a.dtype = dt;
@@ -554,7 +599,7 @@ int32_t prep_all(varco_ctx* ctx, Workspace& ws, const varco_network_buffers& b, 
             const void* h = which ? b.h0[l] : b.h1[l];
             n += prep_slot(ctx, ws, l, h, fi, fo, true, which, false, unused, jobs + n) ? 1 : 0;
             // at most 64 outputs: the short-reduction kernels take the weights as they are
-            if (b.dh1[l] && l > 0 && (fo > 64 || (first && which == 0)))
+            if (b.dh1[l] && l > 0 && (fo > 64 || (which == 0 && (first || narrow_sums_pay(ctx, l)))))
                 n += prep_slot(ctx, ws, l, h, fi, fo, false, which, false, unused, jobs + n) ? 1 : 0;
         }
     }
@@ -593,7 +638,7 @@ size_t varco::network_prod_need(const varco_ctx* ctx, size_t* most) {
     size_t need = 0;
     *most = 0;
     for (int32_t l = 1; l < ctx->n_layers; ++l) {     // the first layer's input needs no gradient
-        if (products_pay(ctx, l, ctx->layers[l].k)) need = std::max(need, prod_floats(ctx, l, ctx->layers[l].k));
+        if (products_pay(ctx, l, ctx->layers[l].k) && !narrow_sums_pay(ctx, l)) need = std::max(need, prod_floats(ctx, l, ctx->layers[l].k));
         int64_t k = (ctx->widths[l] - 1) / 3;
         while (k > 0 && !products_pay(ctx, l, k)) --k;
         if (k > 0) *most = std::max(*most, prod_floats(ctx, l, k));

@@ -33,6 +33,17 @@ def test_class_layer_transforms_first_with_hubs(conv, widths):
     _compare_network(g, part, 3, conv, widths, ratios, steps=list(range(5)), tol=BF16_TOL, dtype="bf16", transform_first=(len(widths) - 2,))
 
 
+@pytest.mark.parametrize("conv,widths,dtype", [("gcn", (20, 112, 1), "bf16"), ("sage", (16, 64, 33), "bf16"), ("sage", (24, 512, 64), "bf16"),
+                                               ("gcn", (40, 208, 47), "bf16"), ("gcn", (20, 24, 96, 80), "bf16"), ("sage", (17, 512, 72), "bf16")])
+def test_class_layer_errors_with_hubs(conv, widths, dtype):
+    # an aggregated-first class layer sums its errors at the width of its outputs (1 to 64 of them), wider outputs at the width of
+    # the inputs; k short, ragged, complete and 0
+    g = hub_graph(1500, 3, 1100, 6.0, conv, seed=91)
+    part = synth.random_partition(g.n, 3, seed=92)
+    ratios = [(16, 1), (5, 1), (3, 2), (1, 1), (1, 0)]
+    _compare_network(g, part, 3, conv, widths, ratios, steps=list(range(5)), tol=BF16_TOL if dtype == "bf16" else 1e-4, dtype=dtype)
+
+
 def test_uneven_and_empty_partitions():
     g = synth.small_random_graph(300, 5.0, "gcn", seed=83)
     part = np.zeros(g.n, dtype=np.int32)
