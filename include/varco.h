@@ -186,14 +186,18 @@ int32_t varco_set_step(varco_ctx* ctx, uint64_t step, varco_stream stream);
 int32_t varco_advance_step(varco_ctx* ctx, varco_stream stream);
 
 /* How the dense products of eq. (2) (X H, and the two gradient products) are formed for fp32 storage
- * (the paper fixes no arithmetic; VARCO_BF16 contexts ignore this). terms = 3 (the default): each fp32 operand
+ * (the paper fixes no arithmetic; VARCO_BF16 contexts ignore this). terms = 3 (the default): in the transform each fp32 operand
  * is written exactly as a sum of three bf16 numbers and the six largest cross products are formed on the bf16
  * matrix units with fp32 accumulation; the dropped products are below 2^-24 of each full product, so the result
- * has the accuracy of fp32 arithmetic at well under half the cost. terms = 0: fp32 matrix instructions
- * throughout (also used, whatever the setting, for shapes the expanded form does not take: forward and input-gradient
- * products whose reduction length is no multiple of 4, weight gradients with fewer than 4 rows or columns). terms = 2: two terms, three products, relative error about 2^-16 per product (a faster,
+ * has the accuracy of fp32 arithmetic at well under half the cost. In the gradients (the input gradient of more than 64
+ * outputs) each operand is scaled by a power of two and written as two fp16 numbers, 22 to 23 of its bits, three products, with sums
+ * that are rounded less often: less error than the former at under two thirds of its cost. Values more than 2^22 below the largest of their row (weight gradients: of
+ * 64 columns of a slab of rows) are within 2^-44 of that one. terms = 0: fp32 matrix instructions
+ * throughout (also used, whatever the setting, for shapes the expanded forms do not take: transforms whose reduction length is
+ * no multiple of 4, gradients with fewer than 4 rows or columns). terms = 2: transforms and input gradients of at most 64 outputs
+ * from two bf16 terms, three products, relative error about 2^-16 per product (a
  * lower-precision setting nothing in this library selects by itself). With terms 2 or 3 an operand that is
- * infinite, NaN or within 2^-9 of the fp32 overflow threshold turns the outputs it meets into NaN (fp32
+ * infinite, NaN or (bf16 terms) within 2^-9 of the fp32 overflow threshold turns the outputs it meets into NaN (fp32
  * instructions would keep an infinity times a finite number infinite); use terms = 0 where such values must
  * pass. INVALID_ARG for other values. Takes effect from the next call on. */
 int32_t varco_set_matmul_terms(varco_ctx* ctx, int32_t terms);
@@ -312,7 +316,7 @@ int32_t varco_transform_bwd_input(varco_ctx* ctx, int32_t layer, int64_t n_rows,
  * whose workspace holds that split; but the partial products go to a static device array of the library (32 MiB
  * per GPU, held until the process ends) instead of a workspace set, so the call needs no varco_prepare and
  * allocates nothing. VARCO_ERR_SHAPE, with the sizes in the text, when width[layer] x width[layer+1] x (the
- * split chosen for n_rows) x 4 bytes exceeds the array: fp32 storage with bf16 terms always fits (256 x 256 weights over
+ * split chosen for n_rows) x 4 bytes exceeds the array: fp32 storage with split operands always fits (256 x 256 weights over
  * 32,768 or more rows use all of it), as do up to 128 rows of bf16 weights; larger bf16 weights fit up to half their full split
  * (512 x 512 weights: up to 8,416 rows). All calls on one GPU share
  * the array: calls that may overlap on the device (different streams, different contexts, different host threads)

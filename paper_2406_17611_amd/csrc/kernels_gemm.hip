@@ -634,7 +634,7 @@ bool varco_gemm_dual_usable(const GemmArgs& ga) {
     if (!ga.c_dual || ga.m == 0 || ga.n == 0) return false;
     if (ga.a.transposed && !ga.deferred) return false;               // partial products of both are summed by the caller
     if (small_k_usable(ga)) return ga.b_dual && (ga.a.dtype == VARCO_BF16 || ga.f32_terms == 2 || ga.f32_terms == 3);
-    return varco_gemm_bf16_usable(ga) || varco_gemm_split_usable(ga);
+    return varco_gemm_bf16_usable(ga) || varco_gemm_half_usable(ga);
 }
 
 hipError_t varco_launch_gemm(const GemmArgs& ga, hipStream_t stream, const LaunchTag& tag) {
@@ -663,11 +663,12 @@ hipError_t varco_launch_gemm(const GemmArgs& ga, hipStream_t stream, const Launc
         const hipError_t e = varco_launch_gemm_bf16(ga, stream, tag, &split);
         return e != hipSuccess ? e : finish(split);
     }
-    if (varco_gemm_split_usable(ga)) {
+    if (varco_gemm_half_usable(ga)) {
         int32_t split = 1;
-        const hipError_t e = varco_launch_gemm_split(ga, stream, tag, &split);
+        const hipError_t e = varco_launch_gemm_half(ga, stream, tag, &split);
         return e != hipSuccess ? e : finish(split);
     }
+    if (varco_gemm_split_usable(ga)) return varco_launch_gemm_split(ga, stream, tag);
     // A is M x K: k-contiguous as stored unless transposed. B is K x N: k-contiguous only when transposed.
     const bool a_kc = !ga.a.transposed, b_kc = ga.b.transposed;
     const bool a_gate = ga.a.gate != nullptr, b_gate = ga.b.gate != nullptr;

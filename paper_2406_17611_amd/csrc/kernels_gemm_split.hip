@@ -1,4 +1,4 @@
-// Dense feature transform of eq. (2) and its gradients for fp32-stored activations, computed on the bf16
+// Dense feature transform of eq. (2) for fp32-stored activations, computed on the bf16
 // matrix cores from exact bf16 expansions of the fp32 operands:
 //     x = x0 + x1 + x2,   x0 = bf16(x), x1 = bf16(x - x0), x2 = bf16(x - x0 - x1)
 // (each difference is exact in fp32, and three 8-bit significands cover the 24 bits of x), so
@@ -7,29 +7,21 @@
 // result with the accuracy of an fp32 product-sum; six bf16 instructions cost 6/16 of the fp32 matrix
 // instructions that cover the same reduction steps. TERMS = 2 keeps x0 + x1 and three products (relative
 // error about 2^-16 per product); the library does not use it by default.
+// (The gradients take two fp16 terms and three products, kernels_gemm_half.hip, which is faster and no less accurate. The forward
+// pass keeps this form and the order of its sums, so that a ReLU whose argument, or an argmax whose two logits, are within rounding
+// of each other decide as they always did; that forgoes 0.9 of 3.47 ms for K = 2 x 256, N = 256 over 2,449,029 rows.)
 //
 // A workgroup of four wavefronts computes a 128 x 128 tile of C (128 x 64 for outputs at most 64 columns wide), a
 // wavefront 64 x 64 (32 x 64); two workgroups are resident per compute unit (see the kernel). A stage of 32
 // reduction steps is fetched into registers one step ahead, then expanded and written to LDS as TERMS planes of
-// bf16 rows (one output index per row, reduction index contiguous, 80-byte pitch).
-//   "NT" products (transform, input gradient): A has the reduction index contiguous and is expanded here;
-//        B is the library's own expanded copy of the weights (varco_launch_prep_weights), zero-padded
-//        to whole tiles and copied as is.
-//   "TN" products (weight gradient, reduction over nodes): both operands have the node index as the slow
-//        one; a thread loads an 8 (nodes) x 4 (columns) block with eight 16-byte loads and expands the values of
-//        two consecutive nodes of a column together, which yields the transposed (node index contiguous) words
-//        directly; it writes four 16-byte LDS rows per plane. Half the threads serve A, half B.
-//        When the matrix unit adds products far below the accumulator (five of the six here), what falls off the end
-//        is dropped towards minus infinity: measured, 98 % of the error of a long sum is its mean, always negative.
-//        So every second slab of rows multiplies -B and its sum changes sign in the epilogue, which lets the halves
-//        cancel. Relative error against fp64 of independent products, 256 x 256, 128 slabs: 2,449,029 rows 8.8e-6
-//        without, 2.0e-6 with; 169,343 rows 8.6e-7 and 5.4e-7. (A loop of its own for -B, the minus an operand modifier
-//        of the conversion, takes the same time.)
-// The ReLU mask of the backward pass is applied before the expansion, the activation in the epilogue.
+// bf16 rows (one output index per row, reduction index contiguous, 80-byte pitch). A has the reduction index contiguous and is
+// expanded here; B is the library's own expanded copy of the weights (varco_launch_prep_weights), zero-padded
+// to whole tiles and copied as is. The activation is applied in the epilogue.
 #include <algorithm>
 #include <type_traits>
 
 #include "elem.h"
+#include "half_terms.h"
 #include "varco_internal.h"
 
 namespace {
@@ -44,9 +36,7 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 struct SplitOperand {
     const void* ptr;      // fp32 matrix, or the expanded bf16 copy of a weight matrix
-    const float* gate;
     int64_t ld;
-    int64_t plane;        // elements between the planes of an expanded copy
 };
 
 struct SplitGemm {
@@ -55,14 +45,8 @@ struct SplitGemm {
     float* c;
     int64_t ldc;
     int32_t accumulate, relu;
-    int32_t split_k, tiles_per_split;
-    float* partial;
     int32_t tiles_m, tiles_n;
-    int32_t inner, outer;            // tiles along the fast and the slow direction of the workgroup order
-    const void* dual;                // second A (TN) or second expanded B (NT), or null
-    float* c_dual;
 };
-
 
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float floatx2 __attribute__((ext_vector_type(2)));
@@ -86,12 +70,6 @@ __device__ __forceinline__ void expand_pair(float x0, float x1, uint32_t (&w)[TE
     }
 }
 
-__device__ __forceinline__ float4 gate4(float4 x, float4 y) {
-    x.x = y.x > 0.f ? x.x : 0.f, x.y = y.y > 0.f ? x.y : 0.f;
-    x.z = y.z > 0.f ? x.z : 0.f, x.w = y.w > 0.f ? x.w : 0.f;
-    return x;
-}
-
 // Consecutive groups of lanes write consecutive tile rows; with an 80-byte pitch rows r and r + 1 overlap in
 // four LDS banks while rows r and r + 4 tile all of them, so the q-th row group of a wavefront goes to row
 // (q with its low three bits rotated): 0 4 1 5 2 6 3 7.
@@ -107,24 +85,15 @@ __device__ __forceinline__ float4 load4_at(const void* base, uint32_t byte_offse
     const any4 v = *reinterpret_cast<const any4*>(static_cast<const char*>(base) + byte_offset);
     return make_float4(v[0], v[1], v[2], v[3]);
 }
-// A group of four that crosses the end of its row is loaded from four elements before the end and moved up by `by` (1 to 3)
-// elements; what follows the end is zero.
-__device__ __forceinline__ float4 moved_up(float4 x, int by) {
-    if (by == 1) return make_float4(x.y, x.z, x.w, 0.f);
-    if (by == 2) return make_float4(x.z, x.w, 0.f, 0.f);
-    return make_float4(x.w, 0.f, 0.f, 0.f);
-}
-
 // ---- fp32 operand with the reduction index contiguous: chunks of CH floats ----
 // Addresses are a per-tile base (uniform) plus a 32-bit offset per chunk that does not change along the
 // reduction. Rows beyond the matrix are clamped to its last row (their results are never stored); chunks
 // beyond the reduction length re-read the tile's first chunk of the same row, and meet zeros in B.
-template <int ROWS, int CH, bool GATE>
+template <int ROWS, int CH>
 struct RowRegs {
     static constexpr int PER_ROW = BK / CH;
     static constexpr int N = ROWS * PER_ROW / kThreads;
     float4 v[N][CH / 4];
-    float4 g[GATE ? N : 1][CH / 4];
 };
 
 template <int ROWS, int CH>
@@ -142,33 +111,28 @@ struct RowPlan {
     }
 };
 
-template <int ROWS, int CH, bool GATE>
-__device__ __forceinline__ void load_rows(int tid, const float* base, const float* gate, const RowPlan<ROWS, CH>& plan,
-                                          int32_t k_left, RowRegs<ROWS, CH, GATE>& r) {
-    using R = RowRegs<ROWS, CH, GATE>;
+template <int ROWS, int CH>
+__device__ __forceinline__ void load_rows(int tid, const float* base, const RowPlan<ROWS, CH>& plan, int32_t k_left, RowRegs<ROWS, CH>& r) {
+    using R = RowRegs<ROWS, CH>;
 #pragma unroll
     for (int h = 0; h < R::N; ++h) {
         const int kc = ((tid + h * kThreads) % R::PER_ROW) * CH;
         const uint32_t off = kc < k_left ? plan.off[h] : plan.off[h] - uint32_t(kc) * 4u;   // k_left is a multiple of CH
 #pragma unroll
-        for (int u = 0; u < CH / 4; ++u) {
-            r.v[h][u] = load4_at(base, off + 16u * u);
-            if (GATE) r.g[h][u] = load4_at(gate, off + 16u * u);
-        }
+        for (int u = 0; u < CH / 4; ++u) r.v[h][u] = load4_at(base, off + 16u * u);
     }
 }
 
-template <int TERMS, int ROWS, int CH, bool GATE>
-__device__ __forceinline__ void store_rows(int tid, const RowRegs<ROWS, CH, GATE>& r, uint16_t* s) {
-    using R = RowRegs<ROWS, CH, GATE>;
+template <int TERMS, int ROWS, int CH>
+__device__ __forceinline__ void store_rows(int tid, const RowRegs<ROWS, CH>& r, uint16_t* s) {
+    using R = RowRegs<ROWS, CH>;
 #pragma unroll
     for (int h = 0; h < R::N; ++h) {
         const int c = tid + h * kThreads;
         uint32_t w[CH / 2][TERMS];
 #pragma unroll
         for (int u = 0; u < CH / 4; ++u) {
-            float4 x = r.v[h][u];
-            if (GATE) x = gate4(x, r.g[h][u]);
+            const float4 x = r.v[h][u];
             expand_pair<TERMS>(x.x, x.y, w[2 * u]);
             expand_pair<TERMS>(x.z, x.w, w[2 * u + 1]);
         }
@@ -226,65 +190,6 @@ __device__ __forceinline__ void store_prep(int tid, const PrepRegs<TERMS, ROWS>&
     }
 }
 
-// ---- fp32 operand with the output index contiguous: one 8 (reduction) x 4 (output) block per thread ----
-// Block b of an operand's tile covers reduction steps 8 * (b % 4) .. + 7 and output indices 4 * (b / 4) .. + 3:
-// eight consecutive lanes then write two LDS rows that are four rows apart, all four 16-byte chunks of each,
-// which touches every LDS bank once. Output indices beyond the matrix are clamped (their results are never
-// stored), a group of four that crosses its end is moved up (rows of the 47 class columns of a last layer, of 75 input features;
-// they need no alignment). In the last, partial tile of the reduction the node index is clamped and A is zeroed beyond it.
-template <bool GATE>
-struct ColRegs {
-    float4 v[8];
-    float4 g[GATE ? 8 : 1];
-};
-
-__device__ __forceinline__ uint32_t col_offset(int b, int32_t i0, int32_t extent) {
-    return uint32_t(min(i0 + (b >> 2) * 4, extent - 4) - i0 + 4) * 4u;  // bytes from 4 floats before the tile's first column
-}
-
-template <bool GATE, bool TAIL, bool ZERO>
-__device__ __forceinline__ void load_cols(const float* base, const float* gate, int b, uint32_t col_off, uint32_t ld_bytes,
-                                          int32_t k_left, ColRegs<GATE>& r) {
-    const int kb = (b & 3) * 8;
-#pragma unroll
-    for (int kk = 0; kk < 8; ++kk) {
-        const int node = TAIL ? min(kb + kk, k_left - 1) : kb + kk;
-        const uint32_t off = uint32_t(node) * ld_bytes + col_off;
-        r.v[kk] = load4_at(base, off);
-        if (GATE) r.g[kk] = load4_at(gate, off);
-        if (TAIL && ZERO && kb + kk >= k_left) r.v[kk] = make_float4(0.f, 0.f, 0.f, 0.f);
-    }
-}
-
-__device__ __forceinline__ float with_sign(float x, uint32_t sign) { return __uint_as_float(__float_as_uint(x) ^ sign); }
-
-// SIGNED: the values change sign when `sign` holds a sign bit.
-template <int TERMS, int ROWS, bool GATE, bool SIGNED>
-__device__ __forceinline__ void store_cols(const ColRegs<GATE>& r, int b, int32_t i0, int32_t extent, uint32_t sign, uint16_t* s) {
-    const bool crosses = (extent & 3) && i0 + (b >> 2) * 4 == (extent & ~3);
-    // An LDS row holds one output index with its 8 reduction steps contiguous, two steps per 32-bit word: the two
-    // values expanded together are steps 2 q and 2 q + 1 of one output index, which is the transposition itself.
-    float x[8][4];
-#pragma unroll
-    for (int kk = 0; kk < 8; ++kk) {
-        float4 v = r.v[kk];
-        if constexpr (GATE) v = gate4(v, r.g[kk]);
-        if (extent & 3) v = crosses ? moved_up(v, 4 - (extent & 3)) : v;
-        if constexpr (SIGNED) v = make_float4(with_sign(v.x, sign), with_sign(v.y, sign), with_sign(v.z, sign), with_sign(v.w, sign));
-        x[kk][0] = v.x, x[kk][1] = v.y, x[kk][2] = v.z, x[kk][3] = v.w;
-    }
-    uint16_t* base = s + (b >> 2) * 4 * kPitch + (b & 3) * 8;
-#pragma unroll
-    for (int ii = 0; ii < 4; ++ii) {                          // output index i + ii: its 8 reduction steps
-        uint32_t o[4][TERMS];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) expand_pair<TERMS>(x[2 * q][ii], x[2 * q + 1][ii], o[q]);
-#pragma unroll
-        for (int p = 0; p < TERMS; ++p)
-            *reinterpret_cast<uint4*>(base + p * ROWS * kPitch + ii * kPitch) = make_uint4(o[0][p], o[1][p], o[2][p], o[3][p]);
-    }
-}
-
 __device__ __forceinline__ bf16x8 fragment(const uint16_t* s, int row, int koff) {
     return __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(s + row * kPitch + koff));
 }
@@ -298,17 +203,7 @@ __device__ __forceinline__ void multiply(const bf16x8 (&fa)[3][TMB], const bf16x
             acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[PA][i], fb[PB][j], acc[i][j], 0, 0, 0);
 }
 
-// All wavefronts of the workgroup meet here (same fences as __syncthreads); the two halves of a workgroup call
-// it from different places, always the same number of times.
-__device__ __forceinline__ void workgroup_barrier() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-}
-
-// TN: both operands stored with the output index contiguous (weight gradient), else A with the reduction
-// index contiguous and B an expanded weight copy. WM x WN wavefronts per tile, each TMB x TNB blocks of
-// 32 x 32. A_CH: floats per chunk of A (NT). GATE masks A (NT) or B (TN).
+// WM x WN wavefronts per tile, each TMB x TNB blocks of 32 x 32. A_CH: floats per chunk of A.
 //
 // A workgroup is four wavefronts with one tile and one LDS stage (60 KB), so that two workgroups are resident
 // on a compute unit and each SIMD holds one wavefront of either. On this device the vector ALU and the matrix
@@ -318,11 +213,10 @@ __device__ __forceinline__ void workgroup_barrier() {
 // Two independent workgroups give the first: while one waits at a barrier, for its global loads, or stores its
 // tile, the other multiplies. (Two groups in lock step inside one 512-thread workgroup, the previous form, left
 // a tile's first fetch and epilogue uncovered and tied both groups to the slower one.)
-template <int TERMS, bool TN, int WM, int WN, int TMB, int TNB, int A_CH, bool GATE>
+template <int TERMS, int WM, int WN, int TMB, int TNB, int A_CH>
 __global__ __launch_bounds__(kThreads, 2) void gemm_split_kernel(SplitGemm g) {
     static_assert(TERMS == 2 || TERMS == 3, "two or three bf16 terms per operand");
     constexpr int BM = 32 * TMB * WM, BN = 32 * TNB * WN;
-    static_assert(BM + BN <= kThreads, "one 8 x 4 block per thread in the TN layout");
     __shared__ __attribute__((aligned(16))) uint16_t smem[TERMS * (BM + BN) * kPitch];
     const int tid = threadIdx.x;
     uint16_t* const sa = smem;
@@ -331,28 +225,9 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_split_kernel(SplitGemm g) {
     // workgroup -> tile: tiles that share streamed data go to one XCD (workgroups are dealt to the 8 XCDs
     // round-robin), so that the streamed operand is fetched into a single L2
     const int32_t xcd = blockIdx.x & 7, within = blockIdx.x >> 3;
-    const int32_t in = within % g.inner, out = (within / g.inner) * 8 + xcd;
-    if (out >= g.outer) return;                // whole workgroup leaves together: no barrier is skipped
-    const int32_t tiles1 = (g.k + BK - 1) / BK;
-    const int32_t tiles2 = (g.k2 + BK - 1) / BK;
-    int32_t t_begin = 0, t_end = tiles1 + tiles2;
-    int32_t tm, tn, z;
-    bool second = false;             // this workgroup's tile belongs to the dual product
-    if (g.split_k > 1 || TN) {
-        t_begin = out * g.tiles_per_split;
-        t_end = min(t_end, t_begin + g.tiles_per_split);
-        const int32_t tiles = g.tiles_m * g.tiles_n;
-        second = in >= tiles;
-        const int32_t tile = second ? in - tiles : in;
-        z = out, tm = tile / g.tiles_n, tn = tile % g.tiles_n;
-    } else {
-        second = in >= g.tiles_n;
-        z = 0, tm = out, tn = second ? in - g.tiles_n : in;
-    }
-    const void* const a_ptr = TN && second ? g.dual : g.a.ptr;
-    const void* const b_ptr = !TN && second ? g.dual : g.b.ptr;
-    const uint32_t sign = TN && (z & 1) ? 0x80000000u : 0u;       // set: this slab forms -C (see the head of this file)
-    const int32_t steps = max(t_end - t_begin, 0);
+    const int32_t tn = within % g.tiles_n, tm = (within / g.tiles_n) * 8 + xcd;
+    if (tm >= g.tiles_m) return;               // whole workgroup leaves together: no barrier is skipped
+    const int32_t tiles1 = (g.k + BK - 1) / BK, tiles2 = (g.k2 + BK - 1) / BK, steps = tiles1 + tiles2;
     const int32_t m0 = tm * BM, n0 = tn * BN;
 
     const int lane = tid & 63;
@@ -368,38 +243,31 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_split_kernel(SplitGemm g) {
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
 
-    // staging registers and per-thread offsets of the two layouts (only one set is used per instantiation)
-    RowRegs<BM, A_CH, GATE && !TN> ra;
+    // staging registers and per-thread offsets
+    RowRegs<BM, A_CH> ra;
     PrepRegs<TERMS, BN> rb;
     RowPlan<BM, A_CH> plan_a;
     PrepPlan<TERMS, BN> plan_b;
-    if constexpr (!TN) {
-        plan_a.init(tid, m0, g.m, g.a.ld);        // a chained second product has the same leading dimensions
-        plan_b.init(tid);
-    }
+    plan_a.init(tid, m0, g.m, g.a.ld);            // a chained second product has the same leading dimensions
+    plan_b.init(tid);
 
-    auto fetch = [&](int32_t t) {                 // NT
+    auto fetch = [&](int32_t t) {
         const bool first = t < tiles1;
         const int32_t k0 = (first ? t : t - tiles1) * BK, k_left = (first ? g.k : g.k2) - k0;
-        const float* abase = static_cast<const float*>(first ? a_ptr : g.a2.ptr) + int64_t(m0) * g.a.ld + k0;
-        const float* gbase = GATE ? g.a.gate + int64_t(m0) * g.a.ld + k0 : nullptr;   // never with a second product
-        const uint16_t* bbase = static_cast<const uint16_t*>(first ? b_ptr : g.b2.ptr) +
+        const float* abase = static_cast<const float*>(first ? g.a.ptr : g.a2.ptr) + int64_t(m0) * g.a.ld + k0;
+        const uint16_t* bbase = static_cast<const uint16_t*>(first ? g.b.ptr : g.b2.ptr) +
                                 (int64_t(tn) * (g.b.ld / BK) + k0 / BK) * (TERMS * BN * BK);      // g.b.ld: padded reduction length
-        if constexpr (!TN) {
-            load_rows<BM, A_CH, GATE>(tid, abase, gbase, plan_a, k_left, ra);
-            load_prep<TERMS, BN>(bbase, plan_b, rb);
-        }
+        load_rows<BM, A_CH>(tid, abase, plan_a, k_left, ra);
+        load_prep<TERMS, BN>(bbase, plan_b, rb);
     };
-    auto stash = [&]() {                          // NT
-        if constexpr (!TN) {
-            store_rows<TERMS, BM, A_CH, GATE>(tid, ra, sa);
-            store_prep<TERMS, BN>(tid, rb, sb);
-        }
+    auto stash = [&]() {
+        store_rows<TERMS, BM, A_CH>(tid, ra, sa);
+        store_prep<TERMS, BN>(tid, rb, sb);
     };
-    // Half steps that hold padding only are left out (NT): at most 16 values left means that only the first half multiplies.
+    // Half steps that hold padding only are left out: at most 16 values left means that only the first half multiplies.
     // (K = 2 x 100, N = 256 over 2,449,029 rows: 2.04 ms for all of 2 x 128, 1.92 now.)
     auto compute = [&](int32_t t) {
-        const int32_t left = TN ? BK : t < tiles1 ? g.k - t * BK : g.k2 - (t - tiles1) * BK;
+        const int32_t left = t < tiles1 ? g.k - t * BK : g.k2 - (t - tiles1) * BK;
 #pragma unroll
         for (int s = 0; s < BK / 16; ++s) {
             if (s * 16 >= left) break;
@@ -426,55 +294,13 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_split_kernel(SplitGemm g) {
     // One LDS stage: a step's operands are fetched into registers while the previous step is multiplied, then
     // expanded and written once its fragments have been read. (A second register set, fetching two steps ahead,
     // was measured and changes nothing.)
-    auto pipeline = [&](auto&& fetch_fn, auto&& stash_fn) {
-        if (steps > 0) fetch_fn(t_begin);
-        for (int32_t it = 0; it < steps; ++it) {
-            stash_fn();
-            if (it + 1 < steps) fetch_fn(t_begin + it + 1);
-            workgroup_barrier();
-            compute(t_begin + it);
-            workgroup_barrier();   // the stage's fragments have been read: the next one may overwrite them
-        }
-    };
-    if constexpr (TN) {
-        // Every wavefront serves 8 x 4 blocks of one operand only (BM and BN are multiples of 64), so the role is
-        // a scalar and each role gets a loop of its own: one shared loop with per-thread role tests made the
-        // compiler copy the 32 staging registers between the paths every step.
-        const int role = __builtin_amdgcn_readfirstlane(tid < BM ? 0 : (tid < BM + BN ? 1 : 2));
-        auto run = [&](auto is_a) {
-            constexpr bool A = decltype(is_a)::value;
-            constexpr bool G = GATE && !A;
-            ColRegs<G> cr;
-            const int b = A ? tid : tid - BM;
-            const uint32_t col_off = A ? col_offset(b, m0, g.m) : col_offset(b, n0, g.n);
-            const SplitOperand& op = A ? g.a : g.b;
-            const uint32_t ld_bytes = uint32_t(op.ld) * 4u;
-            auto fetch_cols = [&](int32_t t) {
-                const int32_t k0 = t * BK, k_left = g.k - k0;
-                const float* base = static_cast<const float*>(A ? a_ptr : op.ptr) + int64_t(k0) * op.ld + (A ? m0 : n0) - 4;
-                const float* gbase = G ? op.gate + int64_t(k0) * op.ld + n0 - 4 : nullptr;
-                if (k_left >= BK)
-                    load_cols<G, false, A>(base, gbase, b, col_off, ld_bytes, k_left, cr);
-                else
-                    load_cols<G, true, A>(base, gbase, b, col_off, ld_bytes, k_left, cr);
-            };
-            pipeline(fetch_cols, [&]() { store_cols<TERMS, A ? BM : BN, G, !A>(cr, b, A ? m0 : n0, A ? g.m : g.n, sign, A ? sa : sb); });
-        };
-        if (role == 0)
-            run(std::true_type{});
-        else if (role == 1)
-            run(std::false_type{});
-        else
-            pipeline([](int32_t) {}, []() {});
-    } else {
-        pipeline(fetch, stash);
-    }
-    if (steps == 0) return;
-    if (sign) {
-#pragma unroll
-        for (int i = 0; i < TMB; ++i)
-#pragma unroll
-            for (int j = 0; j < TNB; ++j) acc[i][j] = -acc[i][j];
+    if (steps > 0) fetch(0);
+    for (int32_t t = 0; t < steps; ++t) {
+        stash();
+        if (t + 1 < steps) fetch(t + 1);
+        __syncthreads();
+        compute(t);
+        __syncthreads();       // the stage's fragments have been read: the next one may overwrite them
     }
 
     // epilogue: accumulator register v of a lane is element (8 * (v / 4) + 4 * (lane / 32) + v % 4, lane % 32).
@@ -483,10 +309,9 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_split_kernel(SplitGemm g) {
     // runs on the scalar unit and the vector unit only sees the loads, adds and stores; the edge tiles take the
     // path with per-element tests and clamped addresses. When C is added to, the old values of a block are fetched
     // by loads that are all issued before the first one is used, not one round trip per element.
-    const bool to_partial = g.split_k > 1;
-    const int64_t pitch = to_partial ? int64_t(g.n) : g.ldc;
-    float* const base = to_partial ? g.partial + (int64_t(second ? g.split_k : 0) + z) * g.m * g.n : second ? g.c_dual : g.c;
-    const bool add_old = !to_partial && g.accumulate, relu = !to_partial && g.relu;
+    const int64_t pitch = g.ldc;
+    float* const base = g.c;
+    const bool add_old = g.accumulate, relu = g.relu;
     if (m0 + BM <= g.m && n0 + BN <= g.n) {
         float* const tile = base + int64_t(m0 + wm) * pitch + (n0 + wn);               // scalar
         const uint32_t lane_off = uint32_t(4 * lk) * uint32_t(pitch) + uint32_t(lrow);  // a tile spans < 2^32 elements
@@ -753,21 +578,85 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_short_k_kernel(const T* __re
     }
 }
 
-// Weight copies (see PrepJob). Expanded copies: element (term p, row r, column c) sits at
+// Weight copies (see PrepJob). Copies in terms: element (term p, row r, column c) sits at
 //   (((r / bn) * (pitch / BK) + c / BK) * terms + p) * bn * BK + (r % bn) * BK + c % BK,
-// bn = rows of a B tile (64 for at most 64 rows, else 128). All copies of a step are made by one launch: a copy is a few
+// bn = rows of a B tile (64 for at most 64 rows, else 128). Behind two fp16 terms (rows_padded * pitch * 2 elements) follow the
+// scale exponents of the rows as 32-bit integers; there a workgroup takes 32 rows, looks for the largest value of each and splits them.
+// All copies of a step are made by one launch: a copy is a few
 // thousand elements, far less than a launch costs.
 template <int CAP>               // the table travels with the launch: a single copy should not carry 3 KB of it
 struct PrepJobs {
     PrepJob job[CAP];
     int32_t n;
 };
+// (not transposed) Eight lanes to a row, each with every eighth group of 8 columns: whole lines per load, and the largest value of
+// a row is found among the eight.
+__device__ __forceinline__ void prep_halves(const PrepJob& jb, int32_t block) {
+    constexpr int HELD = 4;                                          // groups kept in registers between the two passes (256 columns)
+    const int32_t r = block * 32 + (int32_t(threadIdx.x) >> 3), g0 = threadIdx.x & 7, groups = jb.pitch / 8, bn = jb.rows <= 64 ? 64 : 128;
+    const float* const row = jb.h + int64_t(min(r, jb.rows - 1)) * jb.ld;
+    auto read = [&](int32_t g, float (&x)[8]) {
+        const int32_t left = r < jb.rows ? jb.cols - g * 8 : 0;
+        if (left >= 8) {
+            const float4 u = load4_at(row, uint32_t(g) * 32u), v = load4_at(row, uint32_t(g) * 32u + 16u);
+            x[0] = u.x, x[1] = u.y, x[2] = u.z, x[3] = u.w, x[4] = v.x, x[5] = v.y, x[6] = v.z, x[7] = v.w;
+        } else {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) x[i] = i < left ? row[g * 8 + i] : 0.f;
+        }
+    };
+    float held[HELD][8], m = 0.f;
+#pragma unroll
+    for (int q = 0; q < HELD; ++q) {
+        if (g0 + 8 * q < groups) read(g0 + 8 * q, held[q]);
+    }
+#pragma unroll
+    for (int q = 0; q < HELD; ++q)
+        if (g0 + 8 * q < groups) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) m = fmaxf(m, fabsf(held[q][i]));
+        }
+    for (int32_t g = g0 + 8 * HELD; g < groups; g += 8) {
+        float x[8];
+        read(g, x);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) m = fmaxf(m, fabsf(x[i]));
+    }
+#pragma unroll
+    for (int d = 4; d; d >>= 1) m = fmaxf(m, __shfl_xor(m, d));
+    const int e = scale_exponent(m, kHalfTop);
+    const float s = power_of_two(e);
+    uint16_t* const out = static_cast<uint16_t*>(jb.out);
+    auto write = [&](int32_t g, const float (&x)[8]) {
+        uint32_t hi[4], lo[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) split_pair(x[2 * i] * s, x[2 * i + 1] * s, hi[i], lo[i]);
+        const int64_t at = (int64_t(r / bn) * (jb.pitch / BK) + g * 8 / BK) * 2;
+        uint16_t* const dst = out + at * bn * BK + (r % bn) * BK + g * 8 % BK;
+        *reinterpret_cast<uint4*>(dst) = make_uint4(hi[0], hi[1], hi[2], hi[3]);
+        *reinterpret_cast<uint4*>(dst + bn * BK) = make_uint4(lo[0], lo[1], lo[2], lo[3]);
+    };
+#pragma unroll
+    for (int q = 0; q < HELD; ++q)
+        if (g0 + 8 * q < groups) write(g0 + 8 * q, held[q]);
+    for (int32_t g = g0 + 8 * HELD; g < groups; g += 8) {
+        float x[8];
+        read(g, x);
+        write(g, x);
+    }
+    if (g0 == 0) reinterpret_cast<int32_t*>(out + int64_t(jb.rows_padded) * jb.pitch * 2)[r] = e;
+}
 template <int CAP>
 __global__ __launch_bounds__(kThreads) void prep_weights_kernel(PrepJobs<CAP> jobs) {
     int32_t at = 0;
     while (at + 1 < jobs.n && int32_t(blockIdx.x) >= jobs.job[at + 1].first_block) ++at;
     const PrepJob& jb = jobs.job[at];
-    const int64_t idx = int64_t(int32_t(blockIdx.x) - jb.first_block) * kThreads + threadIdx.x;
+    const int32_t block = int32_t(blockIdx.x) - jb.first_block;
+    if (jb.terms == kHalfTerms) {
+        prep_halves(jb, block);
+        return;
+    }
+    const int64_t idx = int64_t(block) * kThreads + threadIdx.x;
     if (idx >= int64_t(jb.rows_padded) * jb.pitch) return;
     const int32_t r = int32_t(idx / jb.pitch), c = int32_t(idx % jb.pitch);
     float x = 0.f;
@@ -778,11 +667,11 @@ __global__ __launch_bounds__(kThreads) void prep_weights_kernel(PrepJobs<CAP> jo
         return;
     }
     const int32_t bn = jb.rows <= 64 ? 64 : 128;
-    const int64_t block = (int64_t(r / bn) * (jb.pitch / BK) + c / BK) * jb.terms;
+    const int64_t first = (int64_t(r / bn) * (jb.pitch / BK) + c / BK) * jb.terms;
     const int32_t inside = (r % bn) * BK + c % BK;
     for (int p = 0; p < jb.terms; ++p) {
         const uint16_t t = float_to_bf16(x);
-        out[(block + p) * bn * BK + inside] = t;
+        out[(first + p) * bn * BK + inside] = t;
         x -= __uint_as_float(uint32_t(t) << 16);
     }
 }
@@ -806,10 +695,10 @@ hipError_t varco_launch_prep_weights(PrepJob* jobs, int n, hipStream_t stream) {
     for (int i = 0; i < n; ++i) {
         PrepJob& j = jobs[i];
         const bool plain = j.terms == 1 && j.rows_padded == j.rows && j.pitch >= j.cols;
-        const bool tiled = (j.terms == 2 || j.terms == 3) && j.rows_padded >= j.rows && j.rows_padded % kPrepRows == 0 && j.pitch >= j.cols && j.pitch % BK == 0;
+        const bool tiled = (j.terms == 2 || j.terms == 3 || (j.terms == kHalfTerms && !j.transpose)) && j.rows_padded >= j.rows && j.rows_padded % kPrepRows == 0 && j.pitch >= j.cols && j.pitch % BK == 0;
         if (!plain && !tiled) return hipErrorInvalidValue;
         j.first_block = int32_t(blocks);
-        blocks += (int64_t(j.rows_padded) * j.pitch + kThreads - 1) / kThreads;
+        blocks += j.terms == kHalfTerms ? j.rows_padded / 32 : (int64_t(j.rows_padded) * j.pitch + kThreads - 1) / kThreads;
     }
     if (blocks == 0) return hipSuccess;
     auto go = [&](auto cap) {
@@ -873,93 +762,51 @@ hipError_t varco_launch_gemm_short_k(const GemmArgs& ga, int terms, hipStream_t 
 bool varco_gemm_split_usable(const GemmArgs& ga) {
     if (ga.f32_terms != 2 && ga.f32_terms != 3) return false;
     if (ga.m <= 0 || ga.n <= 0) return false;
-    if (ga.a.dtype != VARCO_F32 || ga.c_dtype != VARCO_F32) return false;
-    auto ok4 = [](const GemmOperand& o) { return aligned_to(o.ptr, 4) && aligned_to(o.gate, 4); };
-    if (!ga.a.transposed) {   // NT: needs the library's expanded weight copy [term][rows][pitch], padded to whole tiles
-        auto prep_ok = [&](const void* p, int64_t ld, int64_t plane, int32_t k) {
-            return p && aligned_to(p, 16) && ld % BK == 0 && ld >= k && plane == (int64_t(ga.n) + kPrepRows - 1) / kPrepRows * kPrepRows * ld;
-        };
-        if (!prep_ok(ga.b_prep, ga.b_prep_ld, ga.b_prep_plane, ga.k)) return false;
-        // (Other reductions keep fp32 matrix instructions: the same sums in the same order as ever, so that a ReLU whose
-        // argument is within rounding of zero opens as it did.)
-        if (ga.b.gate || ga.k % 4 != 0 || !ok4(ga.a)) return false;
-        if (ga.k2 > 0) {   // a chained product shares the first one's leading dimensions and is never masked
-            if (!prep_ok(ga.b2_prep, ga.b2_prep_ld, ga.b2_prep_plane, ga.k2) || ga.b2_prep_ld != ga.b_prep_ld) return false;
-            if (ga.k2 % 4 != 0 || !ok4(ga.a2) || ga.a2.ld != ga.a.ld || ga.a.gate || ga.a2.gate || ga.a2.dtype != VARCO_F32 ||
-                ga.a2.transposed)
-                return false;
-        }
-        return !ga.c_dual || (ga.k2 == 0 && ga.split_k <= 1 && ga.b_dual_prep && aligned_to(ga.b_dual_prep, 16));
+    if (ga.a.dtype != VARCO_F32 || ga.c_dtype != VARCO_F32 || ga.a.transposed || ga.a.gate || ga.b.gate || ga.c_dual || ga.split_k > 1 || ga.b_halves)
+        return false;
+    // needs the library's expanded weight copy [term][rows][pitch], padded to whole tiles
+    auto prep_ok = [&](const void* p, int64_t ld, int64_t plane, int32_t k) {
+        return p && aligned_to(p, 16) && ld % BK == 0 && ld >= k && plane == (int64_t(ga.n) + kPrepRows - 1) / kPrepRows * kPrepRows * ld;
+    };
+    if (!prep_ok(ga.b_prep, ga.b_prep_ld, ga.b_prep_plane, ga.k)) return false;
+    // (Other reductions keep fp32 matrix instructions: the same sums in the same order as ever, so that a ReLU whose
+    // argument is within rounding of zero opens as it did.)
+    if (ga.k % 4 != 0 || !aligned_to(ga.a.ptr, 4)) return false;
+    if (ga.k2 > 0) {   // a chained product shares the first one's leading dimensions
+        if (!prep_ok(ga.b2_prep, ga.b2_prep_ld, ga.b2_prep_plane, ga.k2) || ga.b2_prep_ld != ga.b_prep_ld) return false;
+        if (ga.k2 % 4 != 0 || !aligned_to(ga.a2.ptr, 4) || ga.a2.ld != ga.a.ld || ga.a2.gate || ga.a2.dtype != VARCO_F32 || ga.a2.transposed) return false;
     }
-    // TN: weight gradient
-    if (ga.c_dual && (!ga.a_dual || !aligned_to(ga.a_dual, 4))) return false;
-    if (ga.b.transposed || ga.b.dtype != VARCO_F32 || ga.k2 > 0 || ga.a.gate) return false;
-    return ok4(ga.a) && ok4(ga.b) && ga.m >= 4 && ga.n >= 4;
+    return true;
 }
 
-hipError_t varco_launch_gemm_split(const GemmArgs& ga, hipStream_t stream, const LaunchTag& tag, int32_t* split_used) {
-    const bool tn = ga.a.transposed;
+hipError_t varco_launch_gemm_split(const GemmArgs& ga, hipStream_t stream, const LaunchTag& tag) {
     const bool narrow = ga.n <= 64;
     const int bm = 128, bn = narrow ? 64 : 128;
-    const bool a8 = !tn && ga.k % 8 == 0 && (ga.k2 == 0 || ga.k2 % 8 == 0);
-    const bool gate = tn ? ga.b.gate != nullptr : ga.a.gate != nullptr;
+    const bool a8 = ga.k % 8 == 0 && (ga.k2 == 0 || ga.k2 % 8 == 0);
 
     SplitGemm g;
     g.m = ga.m, g.n = ga.n, g.k = ga.k, g.k2 = ga.k2;
-    auto f32 = [](const void* p) { return static_cast<const float*>(p); };
-    g.a = {ga.a.ptr, f32(ga.a.gate), ga.a.ld, 0};
-    g.a2 = {ga.a2.ptr, f32(ga.a2.gate), ga.a2.ld, 0};
-    if (tn) {
-        g.b = {ga.b.ptr, f32(ga.b.gate), ga.b.ld, 0};
-        g.b2 = {nullptr, nullptr, 0, 0};
-    } else {
-        g.b = {ga.b_prep, nullptr, ga.b_prep_ld, ga.b_prep_plane};
-        g.b2 = {ga.b2_prep, nullptr, ga.b2_prep_ld, ga.b2_prep_plane};
-    }
+    g.a = {ga.a.ptr, ga.a.ld};
+    g.a2 = {ga.a2.ptr, ga.a2.ld};
+    g.b = {ga.b_prep, ga.b_prep_ld};
+    g.b2 = {ga.b2_prep, ga.b2_prep_ld};
     g.c = static_cast<float*>(ga.c);
     g.ldc = ga.ldc;
     g.accumulate = ga.accumulate ? 1 : 0;
     g.relu = ga.relu ? 1 : 0;
     g.tiles_m = (ga.m + bm - 1) / bm;
     g.tiles_n = (ga.n + bn - 1) / bn;
-    const int32_t k_tiles = (ga.k + BK - 1) / BK + (ga.k2 + BK - 1) / BK;
-    int32_t split = ga.split_k < 1 ? 1 : ga.split_k;
-    if (split > k_tiles) split = k_tiles < 1 ? 1 : k_tiles;
-    g.tiles_per_split = (k_tiles + split - 1) / split;
-    split = g.tiles_per_split > 0 ? (k_tiles + g.tiles_per_split - 1) / g.tiles_per_split : 1;
-    if (split < 1) split = 1;
-    g.split_k = split;
-    g.partial = ga.partial;
-    if (split > 1 && !ga.partial) return hipErrorInvalidValue;
-    g.dual = ga.c_dual ? (tn ? ga.a_dual : ga.b_dual_prep) : nullptr;
-    g.c_dual = static_cast<float*>(ga.c_dual);
-    const int32_t products = ga.c_dual ? 2 : 1;     // the dual product's tiles come right behind the first one's, on the same XCD
-    if (split > 1 || tn) {
-        g.inner = g.tiles_m * g.tiles_n * products;
-        g.outer = split;
-    } else {
-        g.inner = g.tiles_n * products;
-        g.outer = g.tiles_m;
-    }
-    const int64_t blocks = int64_t((g.outer + 7) / 8 * 8) * g.inner;
+    const int64_t blocks = int64_t((g.tiles_m + 7) / 8 * 8) * g.tiles_n;
     if (blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
     const dim3 grid{unsigned(blocks)};
-    *split_used = split;
 
     tag.begin(stream);
     with_flag(ga.f32_terms == 3, [&](auto t3) {
         with_flag(narrow, [&](auto nr) {
-            with_flag(gate, [&](auto gt) {
-                constexpr int T = decltype(t3)::value ? 3 : 2;
-                constexpr bool NR = decltype(nr)::value, GT = decltype(gt)::value;
-                constexpr int WM = NR ? 4 : 2, WN = NR ? 1 : 2, TMB = NR ? 1 : 2, TNB = 2;
-                if (tn) {
-                    hipLaunchKernelGGL((gemm_split_kernel<T, true, WM, WN, TMB, TNB, 4, GT>), grid, dim3(kThreads), 0, stream, g);
-                } else if (a8) {
-                    hipLaunchKernelGGL((gemm_split_kernel<T, false, WM, WN, TMB, TNB, 8, GT>), grid, dim3(kThreads), 0, stream, g);
-                } else {
-                    hipLaunchKernelGGL((gemm_split_kernel<T, false, WM, WN, TMB, TNB, 4, GT>), grid, dim3(kThreads), 0, stream, g);
-                }
+            with_flag(a8, [&](auto c8) {
+                constexpr bool NR = decltype(nr)::value;
+                hipLaunchKernelGGL((gemm_split_kernel<decltype(t3)::value ? 3 : 2, NR ? 4 : 2, NR ? 1 : 2, NR ? 1 : 2, 2, decltype(c8)::value ? 8 : 4>), grid,
+                                   dim3(kThreads), 0, stream, g);
             });
         });
     });

@@ -235,7 +235,7 @@ int32_t plain_bf16_split(int32_t m, int32_t n, int64_t k) {
     return int32_t(std::min<int64_t>(std::max<int64_t>(1, 512 / tiles), std::max<int64_t>(1, (k + 31) / 32 / 8)));
 }
 int gemm_kind(const GemmArgs& g) {
-    return varco_gemm_bf16_usable(g) ? kGemmBf16 : varco_gemm_split_usable(g) ? kGemmExpanded : kGemmF32;
+    return varco_gemm_bf16_usable(g) ? kGemmBf16 : varco_gemm_half_usable(g) ? kGemmExpanded : kGemmF32;
 }
 
 int32_t pad8(int32_t x) { return (x + 7) / 8 * 8; }
@@ -256,7 +256,7 @@ int32_t ensure_tables(varco_ctx* ctx) {
 
 // Copy of a weight matrix in the form the bf16 matrix-core kernels take (B or B2 of `g`): rows = the product's
 // output index, pitch padded; bf16 storage: one rounded copy; fp32 storage: the terms of the exact bf16
-// expansion, one plane each. Nothing to do when fp32 instructions are used. Every (layer, weight, orientation)
+// expansion for the transform, two scaled fp16 terms for the input gradient. Nothing to do when fp32 instructions are used. Every (layer, weight, orientation)
 // has a slot of its own in the stream's workspace, and a copy made earlier in the same step from the same
 // pointer is reused: the weights of a step do not change (they are updated between steps). Returns whether `job`, which
 // makes the copy, has to run before the product.
@@ -264,7 +264,7 @@ bool prep_slot(varco_ctx* ctx, Workspace& ws, int32_t layer, const void* h, int3
                GemmArgs& g, PrepJob* job) {
     const bool bf16 = ctx->dtype == VARCO_BF16;
     if (!bf16 && ctx->f32_terms == 0) return false;
-    const int32_t terms = bf16 ? 1 : ctx->f32_terms;
+    const int32_t terms = bf16 ? 1 : transpose ? ctx->f32_terms : kHalfTerms;      // the transform reads H^T, the input gradient H
     const int32_t rows = transpose ? fo : fi, cols = transpose ? fi : fo;
     const int32_t p = bf16 ? pad8(cols) : pad_to(cols, 32);
     const int32_t rows_padded = bf16 ? rows : pad_to(rows, 128);   // whole tiles: the kernel reads the copy without bounds checks
@@ -274,7 +274,8 @@ bool prep_slot(varco_ctx* ctx, Workspace& ws, int32_t layer, const void* h, int3
     (as_b2 ? g.b2_prep_ld : g.b_prep_ld) = p;
     if (!bf16) {
         (as_b2 ? g.b2_prep_plane : g.b_prep_plane) = int64_t(rows_padded) * p;
-        g.f32_terms = terms;
+        g.f32_terms = ctx->f32_terms;
+        g.b_halves = terms == kHalfTerms;
     }
     Workspace::WeightTag& tag = ws.w_tags[slot];
     if (tag.h == h && tag.epoch == ctx->weight_epoch && tag.terms == terms) return false;

@@ -240,11 +240,12 @@ struct GemmArgs {
     const void* b_prep = nullptr;
     const void* b2_prep = nullptr;
     int64_t b_prep_ld = 0, b2_prep_ld = 0;
-    // fp32 operands on the bf16 matrix cores: 0 = no (fp32 matrix instructions); 2 or 3 = each operand is
-    // expanded into that many bf16 terms, and b_prep / b2_prep are expanded copies made by
-    // varco_launch_prep_weights (by tile and stage, `plane` elements per term in all)
+    // fp32 operands on the 16-bit matrix cores: 0 = no (fp32 matrix instructions); 2 or 3 = in the transform each operand is
+    // expanded into that many bf16 terms, in the gradients into two scaled fp16 terms, and b_prep / b2_prep are expanded copies made
+    // by varco_launch_prep_weights (by tile and stage, `plane` elements per term in all)
     int32_t f32_terms = 0;
     int64_t b_prep_plane = 0, b2_prep_plane = 0;
+    bool b_halves = false;        // b_prep (and b_dual_prep) hold two scaled fp16 terms instead (kHalfTerms)
     void* c = nullptr;
     int c_dtype = VARCO_F32;
     int64_t ldc = 0;
@@ -327,15 +328,20 @@ hipError_t varco_launch_gemm_bf16(const GemmArgs& g, hipStream_t stream, const L
 bool varco_gemm_tn_bf16_usable(const GemmArgs& g);
 void varco_gemm_tn_bf16_tile(int32_t m, int32_t n, int32_t* bm, int32_t* bn, int32_t* per_cu);
 hipError_t varco_launch_gemm_tn_bf16(const GemmArgs& g, hipStream_t stream, const LaunchTag& tag, int32_t* split_used);
-// fp32 operands as sums of bf16 terms on the bf16 matrix cores (kernels_gemm_split.hip); same contract as
-// the bf16 path above.
+// fp32 operands as sums of bf16 terms on the bf16 matrix cores (kernels_gemm_split.hip): the transform.
 bool varco_gemm_split_usable(const GemmArgs& g);
-hipError_t varco_launch_gemm_split(const GemmArgs& g, hipStream_t stream, const LaunchTag& tag, int32_t* split_used);
+hipError_t varco_launch_gemm_split(const GemmArgs& g, hipStream_t stream, const LaunchTag& tag);
+// fp32 operands as two scaled fp16 terms on the fp16 matrix cores (kernels_gemm_half.hip): input and weight gradients; same
+// contract as the bf16 path above.
+bool varco_gemm_half_usable(const GemmArgs& g);
+hipError_t varco_launch_gemm_half(const GemmArgs& g, hipStream_t stream, const LaunchTag& tag, int32_t* split_used);
 // Copies of weight matrices in the form the bf16 matrix-core kernels take, several per launch: (transpose ? h[c][r] : h[r][c])
 // for r < rows, c < cols, zero beyond.
 //   terms = 1: one rounded bf16 copy [row][pitch], rows_padded = rows;
 //   terms = 2, 3: the terms of the exact expansion, rows padded to rows_padded (a multiple of 128) and columns to pitch (a
-//   multiple of 32), stored by row tile and stage of 32 columns as the product kernel fetches it (kernels_gemm_split.hip).
+//   multiple of 32), stored by row tile and stage of 32 columns as the product kernel fetches it (kernels_gemm_split.hip);
+//   kHalfTerms: two scaled fp16 terms in the same order, then the rows' scale exponents (kernels_gemm_half.hip).
+constexpr int kHalfTerms = 4;
 struct PrepJob {
     const float* h;
     void* out;

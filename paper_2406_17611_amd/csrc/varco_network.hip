@@ -40,20 +40,20 @@ size_t prod_floats(const varco_ctx* ctx, int32_t layer, int64_t k) {
 // matrix - a handful of workgroups then walks a chain of round trips while the device idles, 16 us against 6.)
 // The fp32 sum of a slab loses accuracy with the square root of its length, so there are as many rounds as keep the result
 // no less accurate than the partitions' gradients formed one after the other (by fp32 sums over the slabs of each). Those have
-// slabs of `alone` rows; the longest ones here are as long with fp32 instructions; longer with expanded operands, by a factor
-// that grows with the rows as the drift grew that slabs of alternating sign are free of (kernels_gemm_split.hip); longer with
+// slabs of `alone` rows; the longest ones here are as long with fp32 instructions; longer with two fp16 terms (kernels_gemm_half.hip),
+// whose sums take one rounding per 16 rows and change sign from slab to slab, by a factor that grows with the rows; longer with
 // bf16 by 4 rows per slab and 16 per partition, which is what adding one cost (these sums are exact now). Fitted to 110 shapes
 // of 12,000 to 2,449,029 rows, 2 to 32 partitions and 64 x 64 to 512 x 512 weights; relative error against fp64 of independent
 // products, partition after partition / one round / now (and the time of the last two):
-//   fp32  256 x 256   2,449,029 rows, 8 parts   3.4e-6 / 8.8e-6 / 2.0e-6  (one round)
-//                     169,343 rows, 4 parts     4.7e-7 / 8.6e-7 / 3.8e-7  (170, 180 us)
+//   fp32  256 x 256   2,449,029 rows, 8 parts   3.3e-7 / 8.8e-7 / 8.8e-7  (one round; three bf16 terms: 7.2e-7, 2.0e-6)
+//                     169,343 rows, 4 parts     1.5e-7 / 2.5e-7 / 2.5e-7  (one round, 165 us; three bf16 terms: 2.9e-7, 3.8e-7 in two, 178 us)
 //   bf16  512 x 512   2,449,029 rows, 32 parts  2.1e-7 / 1.2e-6 / 2.0e-7  (1.81, 2.26 ms)
 //                     169,343 rows, 4 parts     1.5e-7 / 2.6e-7 / 1.3e-7  (158, 210 us: writing and reading the partial products)
 int32_t wgrad_splits(const varco_ctx* ctx, int32_t m, int32_t n, int64_t rows, int kind, int products) {
     const int64_t step = kind == kGemmF32 ? 16 : 32;
     const int64_t slots = wgrad_slots(m, n, kind, products), most = ctx->net.largest;
     const int64_t split = kind == kGemmBf16 ? plain_bf16_split(m, n, most) : gemm_split_for(m, n, most, kind), alone = most / split;
-    const int64_t longest = kind == kGemmExpanded ? alone * (137'500 + rows) / 110'000 : kind == kGemmBf16 ? alone + 4 * split + 16 * ctx->n_parts : alone;
+    const int64_t longest = kind == kGemmExpanded ? alone * (137'500 + rows) / 73'300 : kind == kGemmBf16 ? alone + 4 * split + 16 * ctx->n_parts : alone;
     const int64_t round = slots * std::max<int64_t>(1, longest);
     const int64_t rounds = std::max<int64_t>(1, std::min((rows + round - 1) / round, kPartialElems / (slots * products * m * n)));
     return int32_t(std::min<int64_t>(rounds * slots, std::max<int64_t>(1, (rows + step - 1) / step / 2)));

@@ -1,0 +1,89 @@
+"""Gradients of the dense transform as products of two scaled fp16 terms (fp32 storage), where their scales have work to do: rows and
+columns of very different magnitude, values that grow along the reduction, leading zeros, reductions of any length, values that are
+not finite. Against fp64 products of the same inputs."""
+import numpy as np
+import pytest
+import torch
+
+from gpu_common import KEY, dev
+from paper_2406_17611_amd import binding as vb
+from paper_2406_17611_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+def _context(fi, fo, rows=0):
+    ctx = vb.Context([fi, fo], [vb.ACT_RELU], vb.CONV_GCN, 1, KEY)
+    if rows:                    # the partial products of a weight gradient are sized by a registered partition
+        g = synth.small_random_graph(max(rows, 8), 3.0, "gcn", seed=5)
+        host = vb.partition_build(g.n, g.rowptr, g.colidx, g.vals, np.zeros(g.n, dtype=np.int32), 1)
+        ctx.register_partition(0, host[0])
+    ctx.prepare()
+    return ctx
+
+
+def _bound(length, a, b):
+    """Per element: both terms of either operand within 2^-23 of the value, one rounding of 2^-24 per 16 products on a partial sum,
+    which is at most sum |a||b|: sqrt of their number for the error of independent roundings, four times that for the tail."""
+    return (2.0 ** -21 + 4 * 2.0 ** -23 * np.sqrt(np.ceil(length / 16) + 1)) * (np.abs(a) @ np.abs(b))
+
+
+@pytest.mark.parametrize("fo", [65, 66, 75, 96, 97, 128, 260, 512])
+@pytest.mark.parametrize("growth", [0, 5, 7, 12])
+def test_input_gradient_rows_of_any_magnitude(fo, growth):
+    n, fi = 300, 136
+    rng = np.random.default_rng(fo + growth)
+    d = rng.standard_normal((n, fo)) * np.exp2(rng.integers(-90, 20, size=(n, 1)))
+    d *= np.exp2(growth * (np.arange(fo) // 32))[None, :] if growth * (fo // 32) < 60 else np.exp2(growth * (np.arange(fo) >= 64))[None, :]
+    d[::7, :32] = 0.0                                     # nothing in the first stage
+    d[5] = 0.0
+    d = d.astype(np.float32)
+    xo = rng.standard_normal((n, fo)).astype(np.float32)
+    h = (synth.glorot(fi, fo, 3, 1) * np.exp2(rng.integers(-30, 30, size=(fi, 1)))).astype(np.float32)
+    out = torch.empty(n, fi, device="cuda")
+    _context(fi, fo).transform_bwd_input(0, dev(d), dev(xo), dev(h), out, False)
+    torch.cuda.synchronize()
+    dz = d.astype(np.float64) * (xo > 0)
+    err = np.abs(out.cpu().numpy() - dz @ h.astype(np.float64).T)
+    assert (err <= _bound(fo, dz, h.astype(np.float64).T)).all()
+
+
+@pytest.mark.parametrize("fi,fo", [(4, 4), (75, 47), (64, 65), (130, 136)])
+@pytest.mark.parametrize("growth", [0, 7])
+@pytest.mark.parametrize("n", [1, 31, 33, 2333])
+def test_weight_gradient_of_growing_values(n, growth, fi, fo):
+    rng = np.random.default_rng(n + fi + growth)
+    steps = np.exp2(growth * np.minimum(np.arange(n) // 32 % 8, 6))[:, None]      # up to 2^42 larger than the first stage, and back
+    y = (rng.standard_normal((n, fi)) * steps * 2.0 ** -40).astype(np.float32)
+    y[: min(n - 1, 40)] = 0.0
+    d = (rng.standard_normal((n, fo)) * 2.0 ** 30 / steps[::-1]).astype(np.float32)
+    xo = rng.standard_normal((n, fo)).astype(np.float32)
+    dh = torch.zeros(fi, fo, device="cuda")
+    _context(fi, fo, n).transform_bwd_weight(0, dev(y), dev(d), dev(xo), dh)
+    torch.cuda.synchronize()
+    dz = d.astype(np.float64) * (xo > 0)
+    err = np.abs(dh.cpu().numpy() - y.astype(np.float64).T @ dz)
+    # a value far below the largest of its 64 columns and slab is within 2^-42 of that one
+    floor = 2.0 ** -42 * (np.abs(y).max() * np.abs(dz).sum(0)[None, :] + np.abs(y).sum(0)[:, None] * np.abs(dz).max())
+    assert (err <= _bound(n, y.astype(np.float64).T, dz) + floor).all()
+
+
+def test_infinite_values_stay_in_their_rows_and_columns():
+    n, fi, fo = 700, 128, 96
+    rng = np.random.default_rng(9)
+    y, d = rng.standard_normal((n, fi)).astype(np.float32), rng.standard_normal((n, fo)).astype(np.float32)
+    h = synth.glorot(fi, fo, 3, 1).astype(np.float32)
+    ones = torch.ones(n, fo, device="cuda")
+    y[321, 17], d[650, 40] = np.inf, -np.inf
+    ctx = _context(fi, fo, n)
+    dh, dx = torch.zeros(fi, fo, device="cuda"), torch.empty(n, fi, device="cuda")
+    ctx.transform_bwd_weight(0, dev(y), dev(d), ones, dh)
+    ctx.transform_bwd_input(0, dev(d), ones, dev(h), dx, False)
+    torch.cuda.synchronize()
+    got_h, got_x = dh.cpu().numpy(), dx.cpu().numpy()
+    assert not np.isfinite(got_h[17]).any() and not np.isfinite(got_h[:, 40]).any() and not np.isfinite(got_x[650]).any()
+    rows, cols, nodes = np.arange(fi) != 17, np.arange(fo) != 40, np.arange(n) != 650
+    ref_h = y[:, rows].astype(np.float64).T @ d[:, cols].astype(np.float64)
+    assert (np.abs(got_h[rows][:, cols] - ref_h) <= _bound(n, y[:, rows].astype(np.float64).T, d[:, cols].astype(np.float64))).all()
+    ref_x = d[nodes].astype(np.float64) @ h.astype(np.float64).T
+    assert (np.abs(got_x[nodes] - ref_x) <= _bound(fo, d[nodes].astype(np.float64), h.astype(np.float64).T)).all()
