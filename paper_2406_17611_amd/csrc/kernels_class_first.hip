@@ -1,4 +1,5 @@
-// A layer that applies its weights before the aggregation (varco_set_layer_order; bf16 storage, at most 64 outputs), for
+// A layer that applies its weights before the aggregation (varco_set_layer_order; bf16 storage, at most 64 outputs), and the input
+// gradient of any class layer (at most 64 outputs, either storage type), for
 // all partitions of a device at once. Every consumer of a node receives the same compressed row, so on one device that row
 // is transformed once (b_total rows instead of one per consumer), and the errors of all its consumers are summed before they
 // are taken back through the weights:
@@ -6,14 +7,16 @@
 //   X_out[i] = sum of S[i, v] Y[v]        narrow gather below
 //   G_loc[v], G_z[v] = sums of S[i, v] dZ[i] over v's local and cross entries (narrow gather)
 //   dH += X^T G_loc + X~_z^T G_z          GEMM and halo_transform_wgrad_kernel
-//   dX[v] = G_loc[v] H^T + kept positions of (G_z[v] H^T)                                             class_dgrad_kernel
-// Rows of Y, G and of the copy of dZ take kClassPitch = 64 elements, 128 bytes: one cache line per gathered row, read by
-// eight lanes with 16-byte loads, eight rows per instruction (rows of 47 elements, unaligned, took a 2-byte load per lane and
-// one row per instruction).
+//   dX[v] = G_loc[v] H^T + kept positions of (G_z[v] H^T)                                             class_dgrad_kernel,
+//                                                                                                     class_dgrad_f32_kernel
+// Rows of Y, G and of the copy of dZ take kClassPitch = 64 elements (32 with fp32 storage and at most 32 outputs): whole cache lines
+// per gathered row, read by 8 or 16 lanes with 16-byte loads, eight or four rows per instruction (rows of 47 elements, unaligned, took
+// an element load per lane and one row per instruction).
 #include <algorithm>
 #include <type_traits>
 
 #include "gather_device.h"
+#include "half_terms.h"
 #include "mask_device.h"
 
 namespace {
@@ -25,15 +28,30 @@ constexpr int P = kClassPitch;
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
-__device__ __forceinline__ void add_row(float (&acc)[8], float w, const uint4& v) {
-    const uint32_t u[4] = {v.x, v.y, v.z, v.w};
+// The columns of a row that a lane holds, and the row's weighted sum.
+template <typename T>
+struct Columns;
+template <>
+struct Columns<bf16_t> {
+    static constexpr int N = 8;
+    static __device__ __forceinline__ void add(float (&acc)[8], float w, const uint4& v) {
+        const uint32_t u[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
-    for (int i = 0; i < 4; ++i) acc[2 * i] += w * __uint_as_float(u[i] << 16), acc[2 * i + 1] += w * __uint_as_float(u[i] & 0xFFFF0000u);
-}
+        for (int i = 0; i < 4; ++i) acc[2 * i] += w * __uint_as_float(u[i] << 16), acc[2 * i + 1] += w * __uint_as_float(u[i] & 0xFFFF0000u);
+    }
+};
+template <>
+struct Columns<float> {
+    static constexpr int N = 4;
+    static __device__ __forceinline__ void add(float (&acc)[4], float w, const uint4& v) {
+        acc[0] += w * __uint_as_float(v.x), acc[1] += w * __uint_as_float(v.y);
+        acc[2] += w * __uint_as_float(v.z), acc[3] += w * __uint_as_float(v.w);
+    }
+};
 
-// Sum of the rows of a range of entries, column `lane` of it in every lane. Lane t of a group of eight takes columns 8 t ..
-// 8 t + 7, the groups take different entries; at the end the groups exchange halves of what they hold until one column is left
-// per lane (7 exchanges and additions instead of 24 in a butterfly of whole rows). record(e): {row of src, weight bits}.
+// Sum of the rows (ROW elements each) of a range of entries, column my_column() of it in every lane. A group of lanes covers a row
+// with 16-byte loads, the groups take different entries; at the end the groups exchange halves of what they hold until one column is
+// left per lane (bf16: 7 exchanges and additions instead of 24 in a butterfly of whole rows). record(e): {row of src, weight bits}.
 __device__ __forceinline__ float add_halves32(float a, float b) {      // lanes below 32: a of both halves; above: b of both
     const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
@@ -42,12 +60,14 @@ __device__ __forceinline__ float add_halves16(float a, float b) {      // the sa
     const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
-template <class F>
-__device__ __forceinline__ float narrow_sum(const uint16_t* src, int32_t e0, int32_t e1, int lane, F&& record) {
-    const int t = lane & 7, g = lane >> 3;
-    float acc[8];
+template <typename T, int ROW, class F>
+__device__ __forceinline__ float narrow_sum(const T* src, int32_t e0, int32_t e1, int lane, F&& record) {
+    constexpr int C = Columns<T>::N, LANES = ROW / C, ROWS = 64 / LANES, MOST = 32 / ROWS;      // 32 rows in flight
+    static_assert(LANES == 8 || LANES == 16, "a row is covered by 8 or 16 lanes");
+    const int t = lane % LANES, g = lane / LANES;
+    float acc[C];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) acc[i] = 0.f;
+    for (int i = 0; i < C; ++i) acc[i] = 0.f;
     for (int32_t base = e0; base < e1; base += 64) {
         uint2 mine = make_uint2(0u, 0u);
         if (base + lane < e1) mine = record(base + lane);
@@ -58,46 +78,52 @@ __device__ __forceinline__ float narrow_sum(const uint16_t* src, int32_t e0, int
             uint32_t w[N];
 #pragma unroll
             for (int u = 0; u < N; ++u) {
-                const int i = i0 + 8 * u + g;
+                const int i = i0 + ROWS * u + g;
                 const uint32_t r = lane_value(mine.x, 4 * i);
                 w[u] = lane_value(mine.y, 4 * i);
-                v[u] = *reinterpret_cast<const uint4*>(src + int64_t(i < cnt ? r : 0u) * P + 8 * t);
+                v[u] = *reinterpret_cast<const uint4*>(src + int64_t(i < cnt ? r : 0u) * ROW + C * t);
             }
 #pragma unroll
             for (int u = 0; u < N; ++u)
-                if (i0 + 8 * u + g < cnt) add_row(acc, __uint_as_float(w[u]), v[u]);
+                if (i0 + ROWS * u + g < cnt) Columns<T>::add(acc, __uint_as_float(w[u]), v[u]);
         };
         int i0 = 0;
-        for (; i0 + 16 < cnt; i0 += 32) batch(i0, std::integral_constant<int, 4>{});
+        for (; i0 + 16 < cnt; i0 += 32) batch(i0, std::integral_constant<int, MOST>{});
         if (i0 + 8 < cnt)
-            batch(i0, std::integral_constant<int, 2>{});
+            batch(i0, std::integral_constant<int, MOST / 2>{});
         else if (i0 < cnt)
-            batch(i0, std::integral_constant<int, 1>{});
+            batch(i0, std::integral_constant<int, MOST / 4>{});
     }
-    // columns 8 t + 4 (lane / 32) + 2 (lane / 16 % 2) + (lane / 8 % 2) of the sums
-    float h[4], q[2];
+    float h[C / 2], q[C / 4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) h[i] = add_halves32(acc[i], acc[i + 4]);
+    for (int i = 0; i < C / 2; ++i) h[i] = add_halves32(acc[i], acc[i + C / 2]);
 #pragma unroll
-    for (int i = 0; i < 2; ++i) q[i] = add_halves16(h[i], h[i + 2]);
-    const bool odd = lane & 8;
-    const float keep = odd ? q[1] : q[0], give = odd ? q[0] : q[1];
-    return keep + __shfl_xor(give, 8);
+    for (int i = 0; i < C / 4; ++i) q[i] = add_halves16(h[i], h[i + C / 4]);
+    if constexpr (C == 8) {
+        const bool odd = lane & 8;
+        const float keep = odd ? q[1] : q[0], give = odd ? q[0] : q[1];
+        return keep + __shfl_xor(give, 8);
+    }
+    return LANES == 8 ? q[0] + __shfl_xor(q[0], 8) : q[0];      // (eight lanes to an fp32 row: every column twice)
 }
-__device__ __forceinline__ int my_column(int lane) { return 8 * (lane & 7) + 4 * (lane >> 5) + 2 * ((lane >> 4) & 1) + ((lane >> 3) & 1); }
+template <typename T, int ROW>
+__device__ __forceinline__ int my_column(int lane) {
+    if constexpr (sizeof(T) == 2) return 8 * (lane & 7) + 4 * (lane >> 5) + 2 * ((lane >> 4) & 1) + ((lane >> 3) & 1);
+    return 4 * (lane % (ROW / 4)) + 2 * (lane >> 5) + ((lane >> 4) & 1);
+}
 
 // X_out rows from the forward work list; pieces of split rows go to `partial` (P floats each).
 __global__ __launch_bounds__(kBlock) void narrow_forward_kernel(const SpmmItem* items, int32_t n_items, const VarcoEdge* edge, const float* vals,
-                                                                const uint16_t* y, int32_t rows, bf16_t* out, int32_t fo, float* partial) {
+                                                                const bf16_t* y, int32_t rows, bf16_t* out, int32_t fo, float* partial) {
     const int lane = threadIdx.x & 63;
     const int32_t idx = blockIdx.x * kWaves + __builtin_amdgcn_readfirstlane(int32_t(threadIdx.x >> 6));
     if (idx >= n_items) return;
     const SpmmItem it = items[idx];
-    const float x = narrow_sum(y, it.e0, it.e1, lane, [&](int32_t e) {
+    const float x = narrow_sum<bf16_t, P>(y, it.e0, it.e1, lane, [&](int32_t e) {
         const VarcoEdge ed = edge[e];
         return make_uint2(uint32_t(ed.gid < 0 ? ed.src : rows + ed.src), __float_as_uint(vals[e]));
     });
-    const int c = my_column(lane);
+    const int c = my_column<bf16_t, P>(lane);
     if (it.dst >= 0)
         partial[int64_t(it.dst) * P + c] = x;
     else if (c < fo)
@@ -116,17 +142,17 @@ __global__ __launch_bounds__(kBlock) void narrow_fixup_kernel(const SpmmSplit* s
 
 // G_loc[row] and G_z[zrow of row] (zeros beyond fo). SPLIT = false: partial sums of the pieces of long ranges (the launch's
 // first wavefronts) and the nodes without pieces; SPLIT = true: the others, from the partial sums.
-template <bool SPLIT>
+template <typename T, int ROW, bool SPLIT>
 __global__ __launch_bounds__(kBlock) void narrow_backward_kernel(const NodeItem* nodes, int32_t n, const SpmmItem* pieces, int32_t n_pieces,
-                                                                 const uint2* t_local, const uint2* t_cross, const uint16_t* dz,
-                                                                 const int32_t* zrow_of, bf16_t* g_loc, bf16_t* g_z, int32_t fo, float* partial) {
-    const int lane = threadIdx.x & 63, c = my_column(lane);
+                                                                 const uint2* t_local, const uint2* t_cross, const T* dz,
+                                                                 const int32_t* zrow_of, T* g_loc, T* g_z, int32_t fo, float* partial) {
+    const int lane = threadIdx.x & 63, c = my_column<T, ROW>(lane);
     int32_t idx = blockIdx.x * kWaves + __builtin_amdgcn_readfirstlane(int32_t(threadIdx.x >> 6));
     if constexpr (!SPLIT) {
         if (idx < n_pieces) {
             const SpmmItem it = pieces[idx];
             const uint2* pairs = it.row == 0 ? t_local : t_cross;
-            partial[int64_t(it.dst) * P + c] = narrow_sum(dz, it.e0, it.e1, lane, [&](int32_t e) { return pairs[e]; });
+            partial[int64_t(it.dst) * ROW + c] = narrow_sum<T, ROW>(dz, it.e0, it.e1, lane, [&](int32_t e) { return pairs[e]; });
             return;
         }
         idx -= n_pieces;
@@ -136,21 +162,24 @@ __global__ __launch_bounds__(kBlock) void narrow_backward_kernel(const NodeItem*
     auto range = [&](const uint2* pairs, int32_t e0, int32_t e1, bool split) {
         float x = 0.f;
         if (SPLIT && split)
-            for (int32_t s = e0; s < e1; ++s) x += partial[int64_t(s) * P + c];
+            for (int32_t s = e0; s < e1; ++s) x += partial[int64_t(s) * ROW + c];
         else
-            x = narrow_sum(dz, e0, e1, lane, [&](int32_t e) { return pairs[e]; });
+            x = narrow_sum<T, ROW>(dz, e0, e1, lane, [&](int32_t e) { return pairs[e]; });
         return c < fo ? x : 0.f;
     };
     const int32_t zr = zrow_of[it.row];
-    Elem<bf16_t>::store(g_loc + int64_t(it.row) * P + c, range(t_local, it.l0, it.l1, it.flags & VARCO_NODE_LOCAL_SPLIT));
-    if (g_z && zr >= 0) Elem<bf16_t>::store(g_z + int64_t(zr) * P + c, range(t_cross, it.c0, it.c1, it.flags & VARCO_NODE_CROSS_SPLIT));
+    Elem<T>::store(g_loc + int64_t(it.row) * ROW + c, range(t_local, it.l0, it.l1, it.flags & VARCO_NODE_LOCAL_SPLIT));
+    if (g_z && zr >= 0) Elem<T>::store(g_z + int64_t(zr) * ROW + c, range(t_cross, it.c0, it.c1, it.flags & VARCO_NODE_CROSS_SPLIT));
 }
 
-// Rows of fo elements -> rows of P elements, zeros beyond fo.
-__global__ __launch_bounds__(kBlock) void pad_rows_kernel(const uint16_t* __restrict__ in, int64_t n, int32_t fo, uint16_t* __restrict__ out) {
-    const int64_t stride = int64_t(gridDim.x) * kWaves;
-    const int c = threadIdx.x & 63;
-    for (int64_t r = int64_t(blockIdx.x) * kWaves + (threadIdx.x >> 6); r < n; r += stride) out[r * P + c] = c < fo ? in[r * fo + c] : uint16_t(0);
+// Rows of fo elements -> rows of ROW elements, zeros beyond fo.
+template <typename T, int ROW>
+__global__ __launch_bounds__(kBlock) void pad_rows_kernel(const T* __restrict__ in, int64_t n, int32_t fo, T* __restrict__ out) {
+    const int64_t total = n * ROW, stride = int64_t(gridDim.x) * kBlock;
+    for (int64_t i = int64_t(blockIdx.x) * kBlock + threadIdx.x; i < total; i += stride) {
+        const int c = int(i % ROW);
+        out[i] = c < fo ? in[i / ROW * fo + c] : T{};
+    }
 }
 
 // dX[v] = G_loc[v] H^T + kept positions of (G_z[v] H^T). A workgroup walks tiles of 32 rows; wavefront w holds the weights of
@@ -247,6 +276,188 @@ __global__ __launch_bounds__(kBlock, 2) void class_dgrad_kernel(const uint16_t* 
     }
 }
 
+// The same for fp32 storage, with the self tap of a SAGE layer: dX[v] = G_loc[v] H1^T + kept positions of (G_z[v] H1^T) (+ dZ[v] H0^T)
+// from two scaled fp16 terms per operand (kernels_gemm_half.hip). A workgroup of eight wavefronts walks tiles of ROWS rows; a wavefront
+// holds the weights of 32 positions as matrix operands in registers, both taps at the same scale per position. The rows of the next
+// tile are on their way while one is multiplied: 16 or 8 lanes take a row of each source, agree on one scale for the three, and write
+// the terms to LDS once for all wavefronts. A half wavefront stores 32 positions of a row, one line. Bound by writing dX and reading the
+// three sources: 2,449,029 x 256 from 47 outputs with both taps 1.45 ms, 169,343 x 256 from 40 outputs 74 us (one workgroup per compute unit:
+// 97 us).
+constexpr int kWide = 512;
+// Wavefronts per SIMD: two workgroups are resident where 128 registers hold the weights, the sums and the next tile.
+constexpr int class_waves(int ks, int rows, bool self) { return ks * (self ? 2 : 1) <= 4 && (rows == 32 || ks < 3) ? 4 : 2; }
+template <int KS, int ROWS, int ROW, bool SELF>
+__global__ __launch_bounds__(kWide, class_waves(KS, ROWS, SELF)) void class_dgrad_f32_kernel(const float* __restrict__ g_loc, const float* __restrict__ g_z,
+                                                                    const float* __restrict__ dz, const int32_t* __restrict__ zrow_of,
+                                                                    const int32_t* __restrict__ bgid, int32_t n, MaskRule rule, int32_t fo,
+                                                                    const float* __restrict__ h1, const float* __restrict__ h0, float* __restrict__ dx) {
+    constexpr int S = SELF ? 3 : 2, kRow = 16 * KS + 8, kPlane = ROWS * kRow;         // sources: G_loc, G_z, dZ
+    constexpr int LANES = ROW / 4, kPass = kWide / LANES, N = (ROWS + kPass - 1) / kPass;      // rows per pass, passes
+    static_assert(LANES == 8 || LANES == 16, "rows of 32 or 64 values");
+    __shared__ __attribute__((aligned(16))) uint16_t tile[S * 2 * kPlane];            // [source][term][row][column]
+    __shared__ __attribute__((aligned(16))) int32_t exps[ROWS];
+    __shared__ __attribute__((aligned(16))) uint2 rows_ab[ROWS];               // {a_inv, b}; a_inv = 0, b = width: nothing came back
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lcol = lane & 31, lk = lane >> 5;
+    const int32_t width = int32_t(rule.width), first = int32_t(blockIdx.y) * 256;
+    // groups of 32 positions; with fewer than eight the blocks of rows are dealt as well
+    const int groups = width - first > 128 ? 8 : width - first > 64 ? 4 : width - first > 32 ? 2 : 1;
+    const int32_t pos = first + wave % groups * 32 + lcol, wave_rb = __builtin_amdgcn_readfirstlane(wave / groups);
+
+    // operands: lane holds H[position][16 s + 8 lk .. + 7], both terms
+    uint4 w[SELF ? 2 : 1][KS][2];
+    int32_t eb;
+    {
+        float x[SELF ? 2 : 1][KS][8], m = 0.f;
+#pragma unroll
+        for (int tap = 0; tap < (SELF ? 2 : 1); ++tap)
+#pragma unroll
+            for (int s = 0; s < KS; ++s)
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    const int k = 16 * s + 8 * lk + i;
+                    x[tap][s][i] = pos < width && k < fo ? (tap ? h0 : h1)[int64_t(pos) * fo + k] : 0.f;
+                    m = fmaxf(m, fabsf(x[tap][s][i]));
+                }
+        m = fmaxf(m, __shfl_xor(m, 32));
+        eb = scale_exponent(m, kHalfTop);
+        const float sc = power_of_two(eb);
+#pragma unroll
+        for (int tap = 0; tap < (SELF ? 2 : 1); ++tap)
+#pragma unroll
+            for (int s = 0; s < KS; ++s) {
+                uint32_t hi[4], lo[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) split_pair(x[tap][s][2 * i] * sc, x[tap][s][2 * i + 1] * sc, hi[i], lo[i]);
+                w[tap][s][0] = make_uint4(hi[0], hi[1], hi[2], hi[3]), w[tap][s][1] = make_uint4(lo[0], lo[1], lo[2], lo[3]);
+            }
+    }
+
+    const int32_t n_tiles = (n + ROWS - 1) / ROWS;
+    const int fr = threadIdx.x / LANES, fc = (threadIdx.x % LANES) * 4;               // rows fr + kPass h, columns fc .. fc + 3
+    float4 next[N][S];
+    int32_t next_z[N];
+    auto fetch = [&](int32_t t) {
+#pragma unroll
+        for (int h = 0; h < N; ++h) {
+            const int32_t row = min(t * ROWS + min(fr + kPass * h, ROWS - 1), n - 1);
+            next[h][0] = *reinterpret_cast<const float4*>(g_loc + int64_t(row) * ROW + fc);
+            if constexpr (SELF) next[h][2] = *reinterpret_cast<const float4*>(dz + int64_t(row) * ROW + fc);
+            next_z[h] = g_z ? zrow_of[row] : -1;
+        }
+#pragma unroll
+        for (int h = 0; h < N; ++h) {
+            next[h][1] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (next_z[h] >= 0) next[h][1] = *reinterpret_cast<const float4*>(g_z + int64_t(next_z[h]) * ROW + fc);
+        }
+    };
+    if (int32_t(blockIdx.x) < n_tiles) fetch(blockIdx.x);
+    for (int32_t t = blockIdx.x; t < n_tiles; t += gridDim.x) {
+        const int32_t row0 = t * ROWS, rows = min(ROWS, n - row0);
+#pragma unroll
+        for (int h = 0; h < N; ++h) {
+            float m = 0.f;
+#pragma unroll
+            for (int s = 0; s < S; ++s)
+                m = fmaxf(fmaxf(fmaxf(m, fabsf(next[h][s].x)), fmaxf(fabsf(next[h][s].y), fabsf(next[h][s].z))), fabsf(next[h][s].w));
+            auto largest_of_row = [&]() {
+#pragma unroll
+                for (int d = LANES / 2; d; d >>= 1) m = fmaxf(m, __shfl_xor(m, d));
+            };
+            largest_of_row();
+            if (__float_as_uint(m) >= 0x7F800000u) {         // an infinite error of one source says nothing about the others' scale
+                m = 0.f;
+                auto finite = [](float x) { return fabsf(x) < __builtin_inff() ? fabsf(x) : 0.f; };
+#pragma unroll
+                for (int s = 0; s < S; ++s)
+                    m = fmaxf(fmaxf(fmaxf(m, finite(next[h][s].x)), fmaxf(finite(next[h][s].y), finite(next[h][s].z))), finite(next[h][s].w));
+                largest_of_row();                             // (all lanes of a row are here)
+            }
+            const int e = scale_exponent(m, kHalfTop);
+            const float sc = power_of_two(e);
+            const int r = fr + kPass * h;
+            if (r < ROWS && fc < 16 * KS) {
+#pragma unroll
+                for (int s = 0; s < S; ++s) {
+                    uint32_t hi[2], lo[2];
+                    split_pair(next[h][s].x * sc, next[h][s].y * sc, hi[0], lo[0]);
+                    split_pair(next[h][s].z * sc, next[h][s].w * sc, hi[1], lo[1]);
+                    *reinterpret_cast<uint2*>(&tile[(2 * s) * kPlane + r * kRow + fc]) = make_uint2(hi[0], hi[1]);
+                    *reinterpret_cast<uint2*>(&tile[(2 * s + 1) * kPlane + r * kRow + fc]) = make_uint2(lo[0], lo[1]);
+                }
+            }
+            if (r < ROWS && fc == 0) {
+                exps[r] = e;
+                uint2 ab = make_uint2(0u, rule.width);
+                if (next_z[h] >= 0 && rule.k < rule.width) {
+                    const MaskAffine a = varco_affine(rule, uint32_t(bgid[next_z[h]]));
+                    ab = make_uint2(a.a_inv, a.b);
+                }
+                rows_ab[r] = ab;
+            }
+        }
+        __syncthreads();
+        if (t + int32_t(gridDim.x) < n_tiles) fetch(t + gridDim.x);
+        for (int rb = wave_rb; rb * 32 < rows && pos - lcol < width; rb += 8 / groups) {
+            floatx16 sum, low, far;
+            int frag_at = (rb * 32 + lcol) * kRow + 8 * lk;
+            asm volatile("" : "+v"(frag_at));
+            auto frag = [&](int source, int term, int s) {
+                return __builtin_bit_cast(halfx8, *reinterpret_cast<const uint4*>(&tile[(2 * source + term) * kPlane + frag_at + 16 * s]));
+            };
+            auto product = [&](int source, int tap) {
+#pragma unroll
+                for (int s = 0; s < KS; ++s) {
+                    const halfx8 a0 = frag(source, 0, s), a1 = frag(source, 1, s);
+                    const halfx8 b0 = __builtin_bit_cast(halfx8, w[tap][s][0]), b1 = __builtin_bit_cast(halfx8, w[tap][s][1]);
+                    sum = __builtin_amdgcn_mfma_f32_32x32x16_f16(a0, b0, sum, 0, 0, 0);
+                    low = __builtin_amdgcn_mfma_f32_32x32x16_f16(a0, b1, low, 0, 0, 0);
+                    low = __builtin_amdgcn_mfma_f32_32x32x16_f16(a1, b0, low, 0, 0, 0);
+                    if constexpr (KS == 1) low = __builtin_amdgcn_mfma_f32_32x32x16_f16(a1, b1 * _Float16(1.f / kHalfLow), low, 0, 0, 0);
+                }
+            };
+            // accumulator register v of a lane is element (8 * (v / 4) + 4 * (lane / 32) + v % 4, lane % 32)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) sum[v] = low[v] = far[v] = 0.f;
+            if (g_z) {                                // first, and down to one register per value before the others start
+                product(1, 0);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int r0 = rb * 32 + 8 * q + 4 * lk;
+                    const uint4 ab01 = *reinterpret_cast<const uint4*>(&rows_ab[r0]), ab23 = *reinterpret_cast<const uint4*>(&rows_ab[r0 + 2]);
+                    const uint32_t a_inv[4] = {ab01.x, ab01.z, ab23.x, ab23.z}, at[4] = {ab01.y, ab01.w, ab23.y, ab23.w};
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const int v = 4 * q + i;
+                        const uint32_t d = uint32_t(pos) >= at[i] ? uint32_t(pos) - at[i] : uint32_t(pos) + rule.width - at[i];
+                        const bool kept = rule.k == rule.width || varco_mod_width(a_inv[i] * d, rule.width, rule.width_magic) < rule.k;
+                        far[v] = kept ? sum[v] + low[v] * (1.f / kHalfLow) : 0.f;
+                        sum[v] = low[v] = 0.f;
+                    }
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            product(0, 0);
+            if constexpr (SELF) product(2, 1);
+            float* const out = dx + int64_t(row0 + rb * 32) * width;      // a scalar per row and one offset per lane
+            uint32_t lane_off = uint32_t(4 * lk) * uint32_t(width) + uint32_t(pos);
+            asm volatile("" : "+v"(lane_off));
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int r0 = 8 * q + 4 * lk;
+                const int4 ev = *reinterpret_cast<const int4*>(&exps[rb * 32 + r0]);
+                const int32_t e[4] = {ev.x, ev.y, ev.z, ev.w};
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const float y = __builtin_ldexpf(sum[4 * q + i] + low[4 * q + i] * (1.f / kHalfLow) + far[4 * q + i], -(e[i] + eb));
+                    if (rb * 32 + r0 + i < rows && pos < width) (out + int64_t(8 * q + i) * width)[lane_off] = y;
+                }
+                __builtin_amdgcn_sched_barrier(0);            // (a group's scales are read when it is its turn)
+            }
+        }
+        __syncthreads();
+    }
+}
+
 dim3 waves_for(int64_t n) { return dim3(unsigned((n + kWaves - 1) / kWaves)); }
 
 }  // namespace
@@ -256,7 +467,7 @@ hipError_t varco_launch_narrow_forward(const SpmmPlan& plan, const VarcoEdge* ed
     if (plan.n_items == 0) return hipSuccess;
     tag.begin(stream);
     hipLaunchKernelGGL(narrow_forward_kernel, waves_for(plan.n_items), dim3(kBlock), 0, stream, plan.items, plan.n_items, edge, vals,
-                       static_cast<const uint16_t*>(y), rows, static_cast<bf16_t*>(out), fo, partial);
+                       static_cast<const bf16_t*>(y), rows, static_cast<bf16_t*>(out), fo, partial);
     tag.end(stream);
     if (plan.n_splits > 0) {
         tag.begin_as(VARCO_K_REDUCE, stream, 4.0 * plan.n_partials * P);
@@ -267,22 +478,33 @@ hipError_t varco_launch_narrow_forward(const SpmmPlan& plan, const VarcoEdge* ed
     return hipGetLastError();
 }
 
-hipError_t varco_launch_narrow_backward(const NodePlan& plan, const uint2* t_local, const uint2* t_cross, const void* dz, int64_t rows,
+namespace {
+template <typename T, int ROW>
+hipError_t narrow_backward(const NodePlan& plan, const uint2* t_local, const uint2* t_cross, const void* dz, int64_t rows, const int32_t* zrow_of,
+                           void* dz_padded, void* g_loc, void* g_z, int32_t fo, float* partial, hipStream_t stream) {
+    const T* const src = static_cast<const T*>(dz_padded);
+    if (dz_padded != dz)
+        hipLaunchKernelGGL((pad_rows_kernel<T, ROW>), dim3(unsigned(std::min<int64_t>((rows * ROW + kBlock - 1) / kBlock, 256 * 32))), dim3(kBlock), 0, stream,
+                           static_cast<const T*>(dz), rows, fo, static_cast<T*>(dz_padded));
+    hipLaunchKernelGGL((narrow_backward_kernel<T, ROW, false>), waves_for(int64_t(plan.n_pieces) + plan.n_whole), dim3(kBlock), 0, stream, plan.nodes,
+                       plan.n_whole, plan.pieces, plan.n_pieces, t_local, t_cross, src, zrow_of, static_cast<T*>(g_loc), static_cast<T*>(g_z), fo, partial);
+    if (plan.n_nodes > plan.n_whole)
+        hipLaunchKernelGGL((narrow_backward_kernel<T, ROW, true>), waves_for(plan.n_nodes - plan.n_whole), dim3(kBlock), 0, stream,
+                           plan.nodes + plan.n_whole, plan.n_nodes - plan.n_whole, plan.pieces, 0, t_local, t_cross, src, zrow_of,
+                           static_cast<T*>(g_loc), static_cast<T*>(g_z), fo, partial);
+    return hipGetLastError();
+}
+}  // namespace
+
+hipError_t varco_launch_narrow_backward(int dtype, const NodePlan& plan, const uint2* t_local, const uint2* t_cross, const void* dz, int64_t rows,
                                         const int32_t* zrow_of, void* dz_padded, void* g_loc, void* g_z, int32_t fo, float* partial,
                                         hipStream_t stream, const LaunchTag& tag) {
     if (plan.n_nodes == 0) return hipSuccess;
     tag.begin(stream);
-    hipLaunchKernelGGL(pad_rows_kernel, dim3(unsigned(std::min<int64_t>((rows + kWaves - 1) / kWaves, 256 * 32))), dim3(kBlock), 0, stream,
-                       static_cast<const uint16_t*>(dz), rows, fo, static_cast<uint16_t*>(dz_padded));
-    const uint16_t* src = static_cast<const uint16_t*>(dz_padded);
-    hipLaunchKernelGGL(narrow_backward_kernel<false>, waves_for(int64_t(plan.n_pieces) + plan.n_whole), dim3(kBlock), 0, stream, plan.nodes, plan.n_whole,
-                       plan.pieces, plan.n_pieces, t_local, t_cross, src, zrow_of, static_cast<bf16_t*>(g_loc), static_cast<bf16_t*>(g_z), fo, partial);
-    if (plan.n_nodes > plan.n_whole)
-        hipLaunchKernelGGL(narrow_backward_kernel<true>, waves_for(plan.n_nodes - plan.n_whole), dim3(kBlock), 0, stream, plan.nodes + plan.n_whole,
-                           plan.n_nodes - plan.n_whole, plan.pieces, 0, t_local, t_cross, src, zrow_of, static_cast<bf16_t*>(g_loc),
-                           static_cast<bf16_t*>(g_z), fo, partial);
+    auto go = [&](auto fn) { return fn(plan, t_local, t_cross, dz, rows, zrow_of, dz_padded, g_loc, g_z, fo, partial, stream); };
+    const hipError_t e = dtype == VARCO_BF16 ? go(narrow_backward<bf16_t, 64>) : varco_class_pitch(dtype, fo) == 32 ? go(narrow_backward<float, 32>) : go(narrow_backward<float, 64>);
     tag.end(stream);
-    return hipGetLastError();
+    return e;
 }
 
 hipError_t varco_launch_class_dgrad(const void* g_loc, const void* g_z, const int32_t* zrow_of, const int32_t* bgid, int64_t rows,
@@ -296,6 +518,43 @@ hipError_t varco_launch_class_dgrad(const void* g_loc, const void* g_z, const in
     hipLaunchKernelGGL(class_dgrad_kernel, dim3(unsigned(std::min<int64_t>(tiles, 512))), dim3(kBlock), 0, stream, static_cast<const uint16_t*>(g_loc),
                        static_cast<const uint16_t*>(g_z), zrow_of, bgid, int32_t(rows), rule, fo, static_cast<const uint16_t*>(wr), cpitch,
                        static_cast<uint16_t*>(dx));
+    tag.end(stream);
+    return hipGetLastError();
+}
+
+hipError_t varco_launch_class_dgrad_f32(const void* g_loc, const void* g_z, const void* dz, const int32_t* zrow_of, const int32_t* bgid, int64_t rows,
+                                        const MaskRule& rule, int32_t fo, const void* h1, const void* h0, void* dx, hipStream_t stream,
+                                        const LaunchTag& tag) {
+    if (rows == 0) return hipSuccess;
+    if (fo < 1 || fo > 64) return hipErrorInvalidValue;
+    tag.begin(stream);
+    auto go = [&](auto ks, auto tile, auto row, auto self) {
+        constexpr int ROWS = decltype(tile)::value;
+        const int64_t tiles = (rows + ROWS - 1) / ROWS, slices = (rule.width + 255) / 256;
+        const dim3 grid{unsigned(std::min<int64_t>(tiles, std::max<int64_t>(1, 128 * class_waves(decltype(ks)::value, ROWS, decltype(self)::value) / slices))), unsigned(slices)};
+        hipLaunchKernelGGL((class_dgrad_f32_kernel<decltype(ks)::value, ROWS, decltype(row)::value, decltype(self)::value>), grid, dim3(kWide), 0, stream,
+                           static_cast<const float*>(g_loc), static_cast<const float*>(g_z), static_cast<const float*>(dz), zrow_of, bgid, int32_t(rows),
+                           rule, fo, static_cast<const float*>(h1), static_cast<const float*>(h0), static_cast<float*>(dx));
+    };
+    using std::integral_constant;
+    auto with_self = [&](auto ks, auto tile, auto row) {
+        if (h0)
+            go(ks, tile, row, std::true_type{});
+        else
+            go(ks, tile, row, std::false_type{});
+    };
+    auto with_tile = [&](auto ks, auto row) {        // at most 128 positions occupy half of the wavefronts: tiles of two blocks of rows then
+        if (rule.width > 128)
+            with_self(ks, integral_constant<int, 32>{}, row);
+        else
+            with_self(ks, integral_constant<int, 64>{}, row);
+    };
+    switch ((fo + 15) / 16) {
+        case 1: with_tile(integral_constant<int, 1>{}, integral_constant<int, 32>{}); break;
+        case 2: with_tile(integral_constant<int, 2>{}, integral_constant<int, 32>{}); break;
+        case 3: with_tile(integral_constant<int, 3>{}, integral_constant<int, 64>{}); break;
+        default: with_tile(integral_constant<int, 4>{}, integral_constant<int, 64>{}); break;
+    }
     tag.end(stream);
     return hipGetLastError();
 }

@@ -360,8 +360,8 @@ int32_t size_workspace(varco_ctx* ctx, Workspace& ws) {
 }
 bool narrow_sums_possible(const varco_ctx* ctx, int32_t l) {
     const int32_t fi = ctx->widths[l], fo = ctx->widths[l + 1];
-    return l > 0 && ctx->dtype == VARCO_BF16 && ctx->layers[l].order == VARCO_ORDER_AGGREGATE_FIRST && ctx->act[l] == VARCO_ACT_IDENTITY &&
-           fo <= kClassPitch && fo < fi && fi % 16 == 0 && fi <= 512;
+    const bool kernels = ctx->dtype == VARCO_BF16 ? fi % 16 == 0 && fi <= 512 : ctx->f32_terms == 3;
+    return l > 0 && kernels && ctx->layers[l].order == VARCO_ORDER_AGGREGATE_FIRST && ctx->act[l] == VARCO_ACT_IDENTITY && fo <= kClassPitch && fo < fi;
 }
 size_t class_block_floats(const varco_ctx* ctx) {
     return size_t(2 * ctx->net.rows + ctx->net.boundary) * kClassPitch * size_t(ctx->elem_bytes()) / 4;

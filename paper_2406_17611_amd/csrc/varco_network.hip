@@ -60,19 +60,22 @@ int32_t wgrad_splits(const varco_ctx* ctx, int32_t m, int32_t n, int64_t rows, i
 }
 
 // Whether the input gradient of a class layer that aggregated first is formed from errors summed at the width of the outputs
-// (class_sums, class_input). Bytes per entry: a row of kClassPitch elements, against a whole row of dM for a local entry and,
+// (class_sums, class_input). Bytes per entry: a row of varco_class_pitch elements, against a whole row of dM for a local entry and,
 // for a cross one, a row of products written and read back (which costs no less than 128 bytes do, however short) or a whole row
 // of dM; dM itself is then neither written nor read. A whole step, widths at the layer's inputs and products, us:
 //   bf16, 2,449,029 nodes, 97 % of 126,167,309 entries cross, 512 inputs: ratio 4 54,160 -> 44,070, 32 38,620 -> 33,160,
 //     64 38,000 -> 32,540
 //   bf16, 169,343 nodes, 75 % of 2,501,829 entries cross: 512 inputs, ratio 1 2,577 -> 2,343, 4 2,190 -> 1,931, 64 1,871 -> 1,737;
 //     64 inputs, ratio 32 1,029 -> 939; 128 inputs, ratio 8, SAGE 1,314 -> 1,255, ratio 16, GCN 1,098 -> 1,039
+//   fp32, 2,449,029 nodes, 88 % of 123,718,280 entries cross, 256 inputs, SAGE: ratio 8 47,900 -> 44,200
+//   fp32, 169,343 nodes, as above: 256 inputs, ratio 8 1,763 -> 1,650, 1 2,587 -> 2,335; 32 inputs, 24 outputs 1,274 -> 1,197; 64 inputs
+//     and 40 outputs, where the rule says no, 1,329 and 1,326 with all other steps
 bool narrow_sums_pay(const varco_ctx* ctx, int32_t l) {
     if (!narrow_sums_possible(ctx, l)) return false;
     const NetState& net = ctx->net;
     const double row = ctx->widths[l] * ctx->elem_bytes(), k = ctx->layers[l].k, cross = k > 0 ? double(net.nnz_cross) : 0.0;
     const double wide = double(net.nnz_local) * row + cross * std::min(std::max(2.0 * k * ctx->elem_bytes(), 128.0), row) + 2.0 * double(net.rows) * row;
-    return (double(net.nnz_local) + cross) * kClassPitch * ctx->elem_bytes() <= wide;
+    return (double(net.nnz_local) + cross) * varco_class_pitch(ctx->dtype, ctx->widths[l + 1]) * ctx->elem_bytes() <= wide;
 }
 
 template <typename P>
@@ -395,14 +398,19 @@ int32_t add_weight_product(varco_ctx* ctx, Workspace& ws, GemmArgs& g, WeightSum
 //   dX[v] = G_loc[v] H1^T + kept positions of (G_z[v] H1^T) (+ dZ[v] H0^T),
 // instead of through the weights first and summed at the width of the inputs (dM = dZ H1^T; dX = S^T dM).
 struct ClassRows {
-    uint16_t *dz, *g_loc, *g_z;      // rows of kClassPitch elements in the workspace; g_z null: no errors come back
+    void *dz, *g_loc, *g_z;          // rows of varco_class_pitch elements; g_z null: no errors come back
 };
-ClassRows class_rows(const varco_ctx* ctx, const Workspace& ws, const MaskRule& rule) {
+ClassRows class_rows(const varco_ctx* ctx, const Workspace& ws, const varco_network_buffers& b, int32_t l, const MaskRule& rule) {
     const NetState& net = ctx->net;
+    const int32_t pitch = varco_class_pitch(ctx->dtype, ctx->widths[l + 1]);
+    const size_t bytes = size_t(net.rows) * size_t(pitch) * size_t(ctx->elem_bytes());
+    char* const at = reinterpret_cast<char*>(ws.tf);
     ClassRows r;
-    r.dz = reinterpret_cast<uint16_t*>(ws.tf);
-    r.g_loc = r.dz + net.rows * kClassPitch;
-    r.g_z = net.nnz_cross > 0 && rule.k > 0 ? r.g_loc + net.rows * kClassPitch : nullptr;
+    // dZ as it is where its rows are whole aligned lines already, else a padded copy
+    const bool whole = ctx->widths[l + 1] == pitch && (reinterpret_cast<uintptr_t>(b.dx[l + 1]) & 15u) == 0;
+    r.dz = whole ? b.dx[l + 1] : at;
+    r.g_loc = at + bytes;
+    r.g_z = net.nnz_cross > 0 && rule.k > 0 ? at + 2 * bytes : nullptr;
     return r;
 }
 int32_t class_sums(varco_ctx* ctx, Workspace& ws, const varco_network_buffers& b, int32_t l, const ClassRows& r, hipStream_t st) {
@@ -410,7 +418,7 @@ int32_t class_sums(varco_ctx* ctx, Workspace& ws, const varco_network_buffers& b
     const int32_t fo = ctx->widths[l + 1];
     const double es = ctx->elem_bytes();
     const double entries = double(net.nnz) * 8.0 + (double(net.rows) + 1.0) * 4.0;
-    VARCO_HIP(ctx, varco_launch_narrow_backward(net.nodes, net.t_local, net.t_cross, b.dx[l + 1], net.rows, net.zrow_of, r.dz, r.g_loc, r.g_z,
+    VARCO_HIP(ctx, varco_launch_narrow_backward(ctx->dtype, net.nodes, net.t_local, net.t_cross, b.dx[l + 1], net.rows, net.zrow_of, r.dz, r.g_loc, r.g_z,
                                                 fo, ws.spmm, st,
                                                 ctx->tag(VARCO_K_AGG_BWD_LOCAL, entries + (2.0 * double(net.rows) + double(net.boundary)) * fo * es, 0,
                                                          entries + (double(net.rows) + double(net.nnz)) * fo * es)));
@@ -420,11 +428,21 @@ int32_t class_input(varco_ctx* ctx, Workspace& ws, const varco_network_buffers& 
     const NetState& net = ctx->net;
     const int32_t fi = ctx->widths[l], fo = ctx->widths[l + 1];
     const int dt = ctx->dtype;
+    const bool sage = ctx->conv == VARCO_CONV_SAGE;
+    if (rule.k > 0) {
+        ctx->stats.bwd_elems[l] += net.halo_rows * rule.k;
+        ctx->stats.full_bwd_elems[l] += net.halo_rows * fi;
+    }
+    if (dt == VARCO_F32) {
+        VARCO_HIP(ctx, varco_launch_class_dgrad_f32(r.g_loc, r.g_z, r.dz, net.zrow_of, net.bgid, net.rows, rule, fo, b.h1[l], sage ? b.h0[l] : nullptr,
+                                                    b.dx[l], st, ctx->tag(VARCO_K_GEMM_DGRAD, 0, (sage ? 4.0 : 2.0) * fi * fo * double(net.rows))));
+        return VARCO_OK;
+    }
     GemmArgs gw;                       // carries the slot of the weights' bf16 copy [position][column]
     VARCO_HIP(ctx, prep_weight(ctx, ws, l, b.h1[l], fi, fo, false, 0, false, st, gw));
     VARCO_HIP(ctx, varco_launch_class_dgrad(r.g_loc, r.g_z, net.zrow_of, net.bgid, net.rows, rule, fo, gw.b_prep, int32_t(gw.b_prep_ld),
                                             b.dx[l], st, ctx->tag(VARCO_K_GEMM_DGRAD, 0, 2.0 * fi * fo * double(net.rows))));
-    if (ctx->conv == VARCO_CONV_SAGE) {                        // + dZ H0^T
+    if (sage) {                        // + dZ H0^T
         GemmArgs g0;
         g0.m = int32_t(net.rows), g0.n = fi, g0.k = fo;
         g0.a.ptr = b.dx[l + 1], g0.a.ld = fo, g0.a.dtype = dt;
@@ -432,10 +450,6 @@ int32_t class_input(varco_ctx* ctx, Workspace& ws, const varco_network_buffers& 
         g0.c = b.dx[l], g0.ldc = fi, g0.c_dtype = dt;
         g0.accumulate = true;
         VARCO_HIP(ctx, varco_launch_gemm(g0, st, ctx->tag(VARCO_K_GEMM_DGRAD, 0, 2.0 * fi * fo * double(net.rows))));
-    }
-    if (rule.k > 0) {
-        ctx->stats.bwd_elems[l] += net.halo_rows * rule.k;
-        ctx->stats.full_bwd_elems[l] += net.halo_rows * fi;
     }
     return VARCO_OK;
 }
@@ -447,7 +461,7 @@ int32_t class_bwd(varco_ctx* ctx, Workspace& ws, const varco_network_buffers& b,
     const double es = ctx->elem_bytes();
     const MaskRule rule = make_rule(ctx, l);
     if (int32_t rc = class_fits(ctx, ws, "varco_network_backward")) return rc;
-    const ClassRows r = class_rows(ctx, ws, rule);
+    const ClassRows r = class_rows(ctx, ws, b, l, rule);
     if (int32_t rc = class_sums(ctx, ws, b, l, r, st)) return rc;
     GemmArgs g;
     g.m = fi, g.n = fo, g.k = int32_t(net.rows);
@@ -540,9 +554,9 @@ int32_t layer_bwd(varco_ctx* ctx, Workspace& ws, const varco_network_buffers& b,
         }
     }
     if (!need) return VARCO_OK;
-    if (narrow_sums_pay(ctx, l) && class_block_floats(ctx) <= ws.tf_elems && (reinterpret_cast<uintptr_t>(b.dx[l]) & 15u) == 0) {
+    if (narrow_sums_pay(ctx, l) && class_block_floats(ctx) <= ws.tf_elems && (dt == VARCO_F32 || (reinterpret_cast<uintptr_t>(b.dx[l]) & 15u) == 0)) {
         const MaskRule rule = make_rule(ctx, l);
-        const ClassRows r = class_rows(ctx, ws, rule);
+        const ClassRows r = class_rows(ctx, ws, b, l, rule);
         if (int32_t rc = class_sums(ctx, ws, b, l, r, st)) return rc;
         return class_input(ctx, ws, b, l, rule, r, st);
     }
@@ -599,7 +613,7 @@ int32_t prep_all(varco_ctx* ctx, Workspace& ws, const varco_network_buffers& b, 
             const void* h = which ? b.h0[l] : b.h1[l];
             n += prep_slot(ctx, ws, l, h, fi, fo, true, which, false, unused, jobs + n) ? 1 : 0;
             // at most 64 outputs: the short-reduction kernels take the weights as they are
-            if (b.dh1[l] && l > 0 && (fo > 64 || (which == 0 && (first || narrow_sums_pay(ctx, l)))))
+            if (b.dh1[l] && l > 0 && (fo > 64 || (which == 0 && ctx->dtype == VARCO_BF16 && (first || narrow_sums_pay(ctx, l)))))
                 n += prep_slot(ctx, ws, l, h, fi, fo, false, which, false, unused, jobs + n) ? 1 : 0;
         }
     }
@@ -638,7 +652,7 @@ size_t varco::network_prod_need(const varco_ctx* ctx, size_t* most) {
     size_t need = 0;
     *most = 0;
     for (int32_t l = 1; l < ctx->n_layers; ++l) {     // the first layer's input needs no gradient
-        if (products_pay(ctx, l, ctx->layers[l].k) && !narrow_sums_pay(ctx, l)) need = std::max(need, prod_floats(ctx, l, ctx->layers[l].k));
+        if (products_pay(ctx, l, ctx->layers[l].k)) need = std::max(need, prod_floats(ctx, l, ctx->layers[l].k));
         int64_t k = (ctx->widths[l] - 1) / 3;
         while (k > 0 && !products_pay(ctx, l, k)) --k;
         if (k > 0) *most = std::max(*most, prod_floats(ctx, l, k));

@@ -34,7 +34,11 @@ def test_class_layer_transforms_first_with_hubs(conv, widths):
 
 
 @pytest.mark.parametrize("conv,widths,dtype", [("gcn", (20, 112, 1), "bf16"), ("sage", (16, 64, 33), "bf16"), ("sage", (24, 512, 64), "bf16"),
-                                               ("gcn", (40, 208, 47), "bf16"), ("gcn", (20, 24, 96, 80), "bf16"), ("sage", (17, 512, 72), "bf16")])
+                                               ("gcn", (40, 208, 47), "bf16"), ("gcn", (20, 24, 96, 80), "bf16"), ("sage", (17, 512, 72), "bf16"),
+                                               ("gcn", (20, 112, 1), "f32"), ("sage", (16, 65, 33), "f32"), ("sage", (24, 512, 64), "f32"),
+                                               ("gcn", (40, 208, 47), "f32"), ("sage", (17, 72, 16), "f32"), ("sage", (16, 61, 32), "f32"),
+                                               ("gcn", (24, 516, 48), "f32"), ("gcn", (20, 64, 80), "f32"), ("sage", (33, 30, 70), "f32"),
+                                               ("gcn", (16, 256, 72), "f32"), ("sage", (24, 516, 70), "f32")])
 def test_class_layer_errors_with_hubs(conv, widths, dtype):
     # an aggregated-first class layer sums its errors at the width of its outputs (1 to 64 of them), wider outputs at the width of
     # the inputs; k short, ragged, complete and 0
