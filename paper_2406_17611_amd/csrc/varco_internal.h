@@ -304,16 +304,16 @@ constexpr int kClassPitch = 64;
 inline int32_t varco_class_pitch(int dtype, int32_t fo) { return dtype == VARCO_F32 && fo <= 32 ? 32 : kClassPitch; }
 hipError_t varco_launch_narrow_forward(const SpmmPlan& plan, const VarcoEdge* edge, const float* vals, const void* y, int32_t rows, void* out,
                                        int32_t fo, float* partial, hipStream_t stream, const LaunchTag& tag);
-// g_z may be null (nothing exchanged). dz: rows x fo; dz_padded (made here unless it is dz itself), g_loc: rows x varco_class_pitch,
-// 16-byte aligned; partial: kClassPitch floats per piece.
+// g_z may be null (nothing exchanged). dz: rows x fo; dz_padded: the same with rows of varco_class_pitch, made here, or dz itself where
+// its rows are whole aligned 16-byte pieces; g_loc: rows x varco_class_pitch; partial: kClassPitch floats per piece.
 hipError_t varco_launch_narrow_backward(int dtype, const NodePlan& plan, const uint2* t_local, const uint2* t_cross, const void* dz, int64_t rows,
                                         const int32_t* zrow_of, void* dz_padded, void* g_loc, void* g_z, int32_t fo, float* partial,
                                         hipStream_t stream, const LaunchTag& tag);
 hipError_t varco_launch_class_dgrad(const void* g_loc, const void* g_z, const int32_t* zrow_of, const int32_t* bgid, int64_t rows,
                                     const MaskRule& rule, int32_t fo, const void* wr, int32_t cpitch, void* dx, hipStream_t stream,
                                     const LaunchTag& tag);
-// The same for fp32 storage from the weights as they are; with h0 and dz (padded rows) dX takes the self tap dZ H0^T as well.
-hipError_t varco_launch_class_dgrad_f32(const void* g_loc, const void* g_z, const void* dz, const int32_t* zrow_of, const int32_t* bgid, int64_t rows,
+// The same for fp32 storage from the weights as they are; with h0 and dz (rows dz_ld apart, whole 16-byte pieces) dX takes the self tap dZ H0^T as well.
+hipError_t varco_launch_class_dgrad_f32(const void* g_loc, const void* g_z, const void* dz, int32_t dz_ld, const int32_t* zrow_of, const int32_t* bgid, int64_t rows,
                                         const MaskRule& rule, int32_t fo, const void* h1, const void* h0, void* dx, hipStream_t stream,
                                         const LaunchTag& tag);
 // y[s, :] = X~[s, :] H (n x fo, bf16), H as its bf16 copy wt[column][position] (pitch wpitch).

@@ -17,6 +17,7 @@ namespace {
 constexpr int32_t kNodeLocal = 64, kNodeCross = 128;
 // Largest product buffer (bytes); beyond it the masked form is used, which needs none.
 constexpr double kProdBytes = 48.0 * (1ull << 30);
+constexpr int64_t kFewStages = 128;
 // Most floats of partial products that one launch writes out for the sake of shorter sums (4 GiB).
 constexpr int64_t kPartialElems = int64_t(1) << 30;
 
@@ -56,7 +57,10 @@ int32_t wgrad_splits(const varco_ctx* ctx, int32_t m, int32_t n, int64_t rows, i
     const int64_t longest = kind == kGemmExpanded ? alone * (137'500 + rows) / 73'300 : kind == kGemmBf16 ? alone + 4 * split + 16 * ctx->n_parts : alone;
     const int64_t round = slots * std::max<int64_t>(1, longest);
     const int64_t rounds = std::max<int64_t>(1, std::min((rows + round - 1) / round, kPartialElems / (slots * products * m * n)));
-    return int32_t(std::min<int64_t>(rounds * slots, std::max<int64_t>(1, (rows + step - 1) / step / 2)));
+    // (the stages of a slab follow one another, 1.4 us each: few rows take slabs of a single one, 2,000 x 16 x 32 9.4 -> 6.6 us; beyond, adding the
+    // partial products costs more: 16,000 x 32 x 64 in slabs of two stages 8.4 and 5.6 us, of one 9.1 and 8.5)
+    const int64_t stages = (rows + step - 1) / step;
+    return int32_t(std::min<int64_t>(rounds * slots, stages <= kFewStages ? stages : stages / 2));
 }
 
 // Whether the input gradient of a class layer that aggregated first is formed from errors summed at the width of the outputs
@@ -398,7 +402,8 @@ int32_t add_weight_product(varco_ctx* ctx, Workspace& ws, GemmArgs& g, WeightSum
 //   dX[v] = G_loc[v] H1^T + kept positions of (G_z[v] H1^T) (+ dZ[v] H0^T),
 // instead of through the weights first and summed at the width of the inputs (dM = dZ H1^T; dX = S^T dM).
 struct ClassRows {
-    void *dz, *g_loc, *g_z;          // rows of varco_class_pitch elements; g_z null: no errors come back
+    void *dz, *g_loc, *g_z;          // rows of varco_class_pitch elements, of dz dz_ld; g_z null: no errors come back
+    int32_t dz_ld;
 };
 ClassRows class_rows(const varco_ctx* ctx, const Workspace& ws, const varco_network_buffers& b, int32_t l, const MaskRule& rule) {
     const NetState& net = ctx->net;
@@ -406,9 +411,9 @@ ClassRows class_rows(const varco_ctx* ctx, const Workspace& ws, const varco_netw
     const size_t bytes = size_t(net.rows) * size_t(pitch) * size_t(ctx->elem_bytes());
     char* const at = reinterpret_cast<char*>(ws.tf);
     ClassRows r;
-    // dZ as it is where its rows are whole aligned lines already, else a padded copy
-    const bool whole = ctx->widths[l + 1] == pitch && (reinterpret_cast<uintptr_t>(b.dx[l + 1]) & 15u) == 0;
-    r.dz = whole ? b.dx[l + 1] : at;
+    // dZ as it is where its rows are whole aligned 16-byte pieces, else a padded copy
+    const bool whole = ctx->widths[l + 1] * int(ctx->elem_bytes()) % 16 == 0 && (reinterpret_cast<uintptr_t>(b.dx[l + 1]) & 15u) == 0;
+    r.dz = whole ? b.dx[l + 1] : at, r.dz_ld = whole ? ctx->widths[l + 1] : pitch;
     r.g_loc = at + bytes;
     r.g_z = net.nnz_cross > 0 && rule.k > 0 ? at + 2 * bytes : nullptr;
     return r;
@@ -434,7 +439,7 @@ int32_t class_input(varco_ctx* ctx, Workspace& ws, const varco_network_buffers& 
         ctx->stats.full_bwd_elems[l] += net.halo_rows * fi;
     }
     if (dt == VARCO_F32) {
-        VARCO_HIP(ctx, varco_launch_class_dgrad_f32(r.g_loc, r.g_z, r.dz, net.zrow_of, net.bgid, net.rows, rule, fo, b.h1[l], sage ? b.h0[l] : nullptr,
+        VARCO_HIP(ctx, varco_launch_class_dgrad_f32(r.g_loc, r.g_z, r.dz, r.dz_ld, net.zrow_of, net.bgid, net.rows, rule, fo, b.h1[l], sage ? b.h0[l] : nullptr,
                                                     b.dx[l], st, ctx->tag(VARCO_K_GEMM_DGRAD, 0, (sage ? 4.0 : 2.0) * fi * fo * double(net.rows))));
         return VARCO_OK;
     }
@@ -471,7 +476,7 @@ int32_t class_bwd(varco_ctx* ctx, Workspace& ws, const varco_network_buffers& b,
     g.accumulate = true;
     if (int32_t rc = add_weight_product(ctx, ws, g, sums, st)) return rc;
     if (ctx->conv == VARCO_CONV_SAGE) {
-        g.b.ptr = r.dz, g.c = b.dh0[l];
+        g.b.ptr = r.dz, g.b.ld = r.dz_ld, g.c = b.dh0[l];
         if (int32_t rc = add_weight_product(ctx, ws, g, sums, st)) return rc;
     }
     if (r.g_z) {   // + X~_z^T G_z: per-workgroup shares
