@@ -3,20 +3,20 @@
 // caller; the library hands this kernel a bf16 copy laid out [output index][reduction index] (see
 // varco_launch_prep_weights). Weight gradients are in kernels_gemm_tn_bf16.hip.
 //
-// A workgroup of 8 wavefronts computes a 256 x 256 tile of C in stages of 64 reduction steps (rows of whole 128-byte lines
-// from memory), or one of 4 wavefronts a 256 x 128 or 256 x 64 tile in stages of 32. A wavefront owns 128 x 64 (or 64 x 64) of
-// it as 32 x 32 blocks: at bf16 rates a wavefront tile smaller than that is limited by LDS reads of its fragments, not by
+// A workgroup of 4 wavefronts computes a 128 x 256 tile of C in stages of 64 reduction steps (rows of whole 128-byte lines
+// from memory), or a 256 x 128 or 256 x 64 tile in stages of 32. A wavefront owns 64 x 128 (128 x 64, 64 x 64) of it as
+// 32 x 32 blocks: at bf16 rates a wavefront tile smaller than that is limited by LDS reads of its fragments, not by
 // the matrix cores. Operands are staged through LDS as rows of one output index with the reduction index contiguous (16
-// bytes of padding per row: fragment reads without bank conflicts), double-buffered against the global loads of the next
-// stage, copied 8 elements at a time unchanged. The ReLU mask of the backward pass is applied when a stage is written
-// to LDS, the activation in the epilogue.
+// bytes of padding per row: fragment reads without bank conflicts), copied 8 elements at a time unchanged. The narrower tiles
+// keep two stages in LDS, one written while the other is read; the 128 x 256 tile keeps one (55 KB), so that two workgroups
+// share a compute unit and one computes while the other waits or stores. The next stage's loads are in flight in both. The
+// ReLU mask of the backward pass is applied when a stage is written to LDS, the activation in the epilogue.
 #include <type_traits>
 
 #include "elem.h"
 #include "varco_internal.h"
 
 namespace {
-
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -50,7 +50,8 @@ __device__ __forceinline__ uint32_t gate_pair(uint32_t v, uint32_t g) {
 // One operand's share of a stage: ROWS rows x BK reduction steps in chunks of 8 elements. A thread keeps its place in the
 // stage, so its byte offsets into the operand are formed once and the stage's base stays in scalar registers. Rows past the
 // matrix repeat its last one (their results are never stored); reduction steps past the end are zero. ANY: rows of any
-// alignment and any length from 8 on (a chunk that crosses the end is loaded from before it and moved up), else padded ones.
+// alignment and any length from 8 on (a chunk that crosses the end is loaded from before it and moved up, one past it repeats
+// the row's last 8 elements: the last row may end the allocation), else padded ones.
 template <int ROWS, bool GATE, bool ANY, int BK, int kThreads>
 struct RowSlab {
     static constexpr int PER_ROW = BK / 8, kPitch = BK + 8;
@@ -71,7 +72,7 @@ struct RowSlab {
         const char* const mask = reinterpret_cast<const char*>(gate - 8);
 #pragma unroll
         for (int h = 0; h < N; ++h) {
-            const uint32_t off = k < left ? at[h] - 2u * uint32_t(over) : 16u;
+            const uint32_t off = ANY ? at[h] - 2u * uint32_t(over) : k < left ? at[h] : 16u;
             v[h] = ANY ? load8_any(from + off) : *reinterpret_cast<const uint4*>(from + off);
             if constexpr (GATE) g[h] = load8_any(mask + off);
         }
@@ -103,13 +104,19 @@ __device__ __forceinline__ bf16x8 fragment(const uint16_t* s) { return __builtin
 // at a time. Stored from the registers, 2 bytes per lane, the 128 store instructions of a thread kept the vector memory unit
 // busy for as long as all matrix instructions of a K = 512 tile take.
 // 169,343 rows, 512 x 512, masked: 208 us with the 256 x 128 tile, whose four column tiles read A and the mask four times
-// through L2 in half lines (18 TB/s), 184 with 256 x 256.
-template <int WM, int WN, int TMB, int TNB, int BK, bool GATE>
+// through L2 in half lines (18 TB/s), 184 with 256 x 256, 164 with 128 x 256. One workgroup of 256 x 256 to a compute unit
+// leaves its matrix cores idle while the tile's first stage arrives, at each barrier and while it stores; the smaller
+// tile reads the weights, which L2 holds, twice as often instead. The plain product takes 94 us (108 with 256 x 256);
+// 2,449,029 rows, 256 wide: 1.28 and, masked, 2.18 ms (1.44 and 2.31). Also tried, us at 512 wide plain / masked and ms at 256:
+// 256 x 128 with one stage 95 / 197, 1.40 / 2.50; 128 x 128, three to a unit, 91 / 166, 1.31 / 2.34; 64 x 256 98 / 161,
+// 1.47 / 2.25; workgroups that stay and fetch the next 256 x 256 tile behind the stores 108 / 197, 1.46 / 2.39.
+// STAGES: stages of A and B kept in LDS, 2 or 1 (then a further barrier parts the reads of a stage from the next one's writes).
+template <int WM, int WN, int TMB, int TNB, int BK, int STAGES, bool GATE>
 __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_bf16_kernel(GemmDev g) {
     constexpr int BM = 32 * TMB * WM, BN = 32 * TNB * WN, kThreads = WM * WN * 64, kPitch = BK + 8;
-    extern __shared__ __attribute__((aligned(16))) uint16_t lds[];       // two stages of A, then of B
+    extern __shared__ __attribute__((aligned(16))) uint16_t lds[];       // STAGES stages of A, then of B
     auto sa = [&](int buf) { return lds + buf * (BM * kPitch); };
-    auto sb = [&](int buf) { return lds + 2 * BM * kPitch + buf * (BN * kPitch); };
+    auto sb = [&](int buf) { return lds + STAGES * BM * kPitch + buf * (BN * kPitch); };
 
     // workgroup -> tile: tiles that share streamed data go to one XCD (workgroups are dealt to the 8 XCDs
     // round-robin), so that the streamed operand is fetched into a single L2
@@ -160,12 +167,14 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_bf16_kernel(GemmDev g) {
     if (t_end > 0) {
         enter(g.a, b_ptr, g.b.ld, g.k);
         fetch(0);
-        stash(0);
+        if constexpr (STAGES == 2) stash(0);
     }
-    __syncthreads();
+    if constexpr (STAGES == 2) __syncthreads();
     for (int32_t t = 0; t < t_end; ++t) {
-        const int buf = t & 1;
+        const int buf = STAGES == 2 ? t & 1 : 0;
+        if constexpr (STAGES == 1) stash(0);
         if (t + 1 < t_end) fetch(t + 1);
+        if constexpr (STAGES == 1) __syncthreads();
 #pragma unroll
         for (int s = 0; s < BK / 16; ++s) {
             const int koff = s * 16 + lk * 8;
@@ -180,13 +189,14 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_bf16_kernel(GemmDev g) {
                 for (int j = 0; j < TNB; ++j)
                     acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[j], fa[i], acc[i][j], 0, 0, 0);
         }
-        if (t + 1 < t_end) stash(buf ^ 1);
+        if constexpr (STAGES == 2)
+            if (t + 1 < t_end) stash(buf ^ 1);
         __syncthreads();
     }
 
     // accumulator register v of a lane is element (row lane % 32, column 8 * (v / 4) + 4 * (lane / 32) + v % 4)
     constexpr int kOut = 32 * TNB + 8;                     // elements per row of the wavefront's 32-row strip in LDS
-    static_assert(kThreads / 64 * 32 * kOut <= 2 * (BM + BN) * kPitch, "a strip per wavefront");
+    static_assert(kThreads / 64 * 32 * kOut <= STAGES * (BM + BN) * kPitch, "a strip per wavefront");
     uint16_t* const strip = lds + wave * 32 * kOut;
     bf16_t* const base = static_cast<bf16_t*>(second ? g.c_dual : g.c);
     const bool vec = g.vec_c;
@@ -261,9 +271,10 @@ bool varco_gemm_bf16_usable(const GemmArgs& ga) {
 
 hipError_t varco_launch_gemm_bf16(const GemmArgs& ga, hipStream_t stream, const LaunchTag& tag, int32_t* split_used) {
     if (ga.a.transposed) return varco_launch_gemm_tn_bf16(ga, stream, tag, split_used);
-    // 256 x 256 where its tiles fill the device and pad no more columns than 256 x 128
-    const int64_t wide = int64_t((ga.m + 255) / 256) * ((ga.n + 255) / 256);
-    const int bm = 256, bn = ga.n <= 64 ? 64 : wide >= 256 && (ga.n + 255) / 256 * 2 == (ga.n + 127) / 128 ? 256 : 128;
+    // 128 x 256 where its tiles fill the device, two to a compute unit, and pad no more columns than 256 x 128
+    const int64_t wide = int64_t((ga.m + 127) / 128) * ((ga.n + 255) / 256);
+    const int bn = ga.n <= 64 ? 64 : wide >= 512 && (ga.n + 255) / 256 * 2 == (ga.n + 127) / 128 ? 256 : 128;
+    const int bm = bn == 256 ? 128 : 256;
     const bool gate = ga.a.gate != nullptr;
 
     GemmDev g;
@@ -289,12 +300,12 @@ hipError_t varco_launch_gemm_bf16(const GemmArgs& ga, hipStream_t stream, const 
     *split_used = 1;
 
     hipError_t err = hipSuccess;
-    auto launch = [&](auto wm, auto wn, auto tmb, auto tnb, auto bk) {
+    auto launch = [&](auto wm, auto wn, auto tmb, auto tnb, auto bk, auto stages) {
         constexpr int WM = decltype(wm)::value, WN = decltype(wn)::value, TMB = decltype(tmb)::value, TNB = decltype(tnb)::value;
-        constexpr int BK = decltype(bk)::value;
-        constexpr size_t bytes = size_t(2) * 32 * (TMB * WM + TNB * WN) * (BK + 8) * 2;
+        constexpr int BK = decltype(bk)::value, STAGES = decltype(stages)::value;
+        constexpr size_t bytes = size_t(STAGES) * 32 * (TMB * WM + TNB * WN) * (BK + 8) * 2;
         with_flag(gate, [&](auto gt) {
-            const auto kernel = gemm_bf16_kernel<WM, WN, TMB, TNB, BK, decltype(gt)::value>;
+            const auto kernel = gemm_bf16_kernel<WM, WN, TMB, TNB, BK, STAGES, decltype(gt)::value>;
             if (bytes > 64 * 1024)
                 err = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, int(bytes));
             if (err != hipSuccess) return;
@@ -309,10 +320,10 @@ hipError_t varco_launch_gemm_bf16(const GemmArgs& ga, hipStream_t stream, const 
     using I32 = std::integral_constant<int, 32>;
     using I64 = std::integral_constant<int, 64>;
     if (bn == 256)
-        launch(I2{}, I4{}, I4{}, I2{}, I64{});
+        launch(I2{}, I2{}, I2{}, I4{}, I64{}, I1{});
     else if (bn == 128)
-        launch(I2{}, I2{}, I4{}, I2{}, I32{});
+        launch(I2{}, I2{}, I4{}, I2{}, I32{}, I2{});
     else
-        launch(I4{}, I1{}, I2{}, I2{}, I32{});
+        launch(I4{}, I1{}, I2{}, I2{}, I32{}, I2{});
     return err != hipSuccess ? err : hipGetLastError();
 }

@@ -106,6 +106,34 @@ def test_input_gradient_short_reduction(first_row, dtype):
         assert_close(gout.float().cpu().numpy(), ref, f"G0 + dZ H^T from row {first_row}", tol)
 
 
+@pytest.mark.parametrize("n,wide,short", [(8100, 2040, 48), (8065, 2048, 70), (16350, 1012, 200)])
+def test_bf16_products_of_whole_device_tiles(n, wide, short):
+    """bf16 products wide and tall enough for 128 x 256 tiles (512 of them or more): ragged last tiles in both directions,
+    reductions shorter than a stage of 64 steps, past one and over several, rows of any alignment; plain and masked."""
+    from oracle.rounding import round_bf16
+    rng = np.random.default_rng(n + wide + short)
+    rnd = lambda a: round_bf16(a).astype(np.float32)
+    bf = torch.bfloat16
+    y = rnd(rng.standard_normal((n, short)))
+    h = synth.glorot(short, wide, 5, 2).astype(np.float32)
+    c = torch.empty(n, wide, dtype=bf, device="cuda")
+    ctx = vb.Context([short, wide], [vb.ACT_IDENTITY], vb.CONV_GCN, 1, KEY, vb.BF16)
+    ctx.prepare()
+    ctx.transform_fwd(0, dev(y, bf), dev(h), c, False, False)
+    torch.cuda.synchronize()
+    # weights and results are rounded to bf16 (2^-9 relative each)
+    assert_close(c.float().cpu().numpy(), y.astype(np.float64) @ h.astype(np.float64), "Y H", 2.0 ** -7)
+
+    ctx = vb.Context([wide, short], [vb.ACT_RELU], vb.CONV_GCN, 1, KEY, vb.BF16)
+    ctx.prepare()
+    xo = rnd(np.maximum(rng.standard_normal((n, short)), 0.0))
+    gin = torch.empty(n, wide, dtype=bf, device="cuda")
+    ctx.transform_bwd_input(0, dev(y, bf), dev(xo, bf), dev(np.ascontiguousarray(h.T)), gin, False)
+    torch.cuda.synchronize()
+    ref = (y.astype(np.float64) * (xo > 0)) @ h.astype(np.float64)
+    assert_close(gin.float().cpu().numpy(), ref, "masked dZ H^T", 2.0 ** -7)
+
+
 @pytest.mark.parametrize("mode", ["f32x3", "f32x2", "bf16"])
 @pytest.mark.parametrize("fo", [47, 3, 1, 62])
 @pytest.mark.parametrize("first_row", [0, 1])
