@@ -19,6 +19,14 @@ __device__ __forceinline__ void split_pair(float x0, float x1, uint32_t& hi, uin
     hi = __builtin_bit_cast(uint32_t, h), lo = __builtin_bit_cast(uint32_t, l);
 }
 
+// And what the second terms leave, at their scale: x s = h0 + (h1 + h2) / kHalfLow.
+__device__ __forceinline__ uint32_t third_pair(float x0, float x1, uint32_t hi, uint32_t lo) {
+    typedef float floatx2 __attribute__((ext_vector_type(2)));
+    const halfx2 h = __builtin_bit_cast(halfx2, hi), l = __builtin_bit_cast(halfx2, lo);
+    const floatx2 r = {__builtin_fmaf(float(h[0]), -kHalfLow, x0 * kHalfLow) - float(l[0]), __builtin_fmaf(float(h[1]), -kHalfLow, x1 * kHalfLow) - float(l[1])};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(r, halfx2));
+}
+
 // Exponent of the scale that brings `largest` (>= 0; zero and denormals count as the smallest normal number) to [2^target,
 // 2^(target + 1)), as far as the scale is a normal number.
 __device__ __forceinline__ int scale_exponent(float largest, int target) { return min(target + 127 - int(__float_as_uint(largest) >> 23), 126); }

@@ -50,6 +50,18 @@ struct Columns<float> {
     }
 };
 
+__device__ __forceinline__ uint32_t bits_of(float x) { return __float_as_uint(x); }
+__device__ __forceinline__ uint32_t bits_of(bf16_t x) { return x.bits; }
+
+// A piece that was loaded `by` elements early, moved up; zeros follow.
+template <typename T>
+__device__ __forceinline__ uint4 moved_up(uint4 x, int by) {
+    if constexpr (sizeof(T) == 2) return moved_up8(x, by);
+    if (by & 2) x = make_uint4(x.z, x.w, 0u, 0u);
+    if (by & 1) x = make_uint4(x.y, x.z, x.w, 0u);
+    return x;
+}
+
 // Sum of the rows (ROW elements each) of a range of entries, column my_column() of it in every lane. A group of lanes covers a row
 // with 16-byte loads, the groups take different entries; at the end the groups exchange halves of what they hold until one column is
 // left per lane (bf16: 7 exchanges and additions instead of 24 in a butterfly of whole rows). record(e): {row of src, weight bits}.
@@ -177,36 +189,63 @@ __global__ __launch_bounds__(kBlock) void narrow_backward_kernel(const NodeItem*
     if (g_z && zr >= 0) Elem<T>::store(g_z + int64_t(zr) * ROW + c, range(t_cross, it.c0, it.c1, it.flags & VARCO_NODE_CROSS_SPLIT));
 }
 
-// Rows of fo elements -> rows of ROW elements, zeros beyond fo.
+// Rows of fo elements -> rows of ROW elements, zeros beyond fo. A thread writes 16 bytes; a piece that crosses a row's end is loaded
+// from before it and moved up. (2,449,029 rows of 47 bf16 elements: 85 us, 212 element by element.)
 template <typename T, int ROW>
 __global__ __launch_bounds__(kBlock) void pad_rows_kernel(const T* __restrict__ in, int64_t n, int32_t fo, T* __restrict__ out) {
-    const int64_t total = n * ROW, stride = int64_t(gridDim.x) * kBlock;
+    constexpr int C = Columns<T>::N, PIECES = ROW / C;
+    const int64_t total = n * PIECES, stride = int64_t(gridDim.x) * kBlock;
     for (int64_t i = int64_t(blockIdx.x) * kBlock + threadIdx.x; i < total; i += stride) {
-        const int c = int(i % ROW);
-        out[i] = c < fo ? in[i / ROW * fo + c] : T{};
+        const int64_t row = i / PIECES;
+        const int c = int(i % PIECES) * C, over = c + C - fo;
+        const T* const from = in + row * fo;
+        uint4 v = make_uint4(0u, 0u, 0u, 0u);
+        if (over < C) {
+            if (fo >= C) {
+                v = load8_any(reinterpret_cast<const char*>(from + (over > 0 ? fo - C : c)));
+                if (over > 0) v = moved_up<T>(v, over);
+            } else {
+                uint32_t u[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+                for (int j = 0; j < C; ++j)
+                    if (j < fo) u[j * 4 / C] |= bits_of(from[j]) << (32 * 4 / C * (j % (C / 4)) & 31);
+                v = make_uint4(u[0], u[1], u[2], u[3]);
+            }
+        }
+        reinterpret_cast<uint4*>(out)[i] = v;
     }
 }
 
-// dX[v] = G_loc[v] H^T + kept positions of (G_z[v] H^T). A workgroup walks tiles of 32 rows; wavefront w holds the weights of
-// positions 128 w .. 128 w + 127 ([position][column], at most 64 columns) as matrix operands in registers, forms both
-// products, drops the second at positions that the row's message did not carry, and the tile leaves through LDS in 16-byte
-// pieces. Bound by writing dX.
-constexpr int kTile = 32, kMaxWidth = 512, kPitch = kMaxWidth + 8, kPitchG = P + 8;
-__global__ __launch_bounds__(kBlock, 2) void class_dgrad_kernel(const uint16_t* __restrict__ g_loc, const uint16_t* __restrict__ g_z,
-                                                                const int32_t* __restrict__ zrow_of, const int32_t* __restrict__ bgid, int32_t n,
-                                                                MaskRule rule, int32_t fo, const uint16_t* __restrict__ wr, int32_t cpitch,
-                                                                uint16_t* __restrict__ dx) {
-    __shared__ __attribute__((aligned(16))) uint16_t tile[kTile * kPitch];
-    __shared__ __attribute__((aligned(16))) uint16_t ga[2][kTile * kPitchG];
-    __shared__ uint2 rows_ab[kTile];              // {a_inv, b}; a_inv = 0 and b = width: nothing kept
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lrow = lane & 31, lk = lane >> 5;
+// dX[v] = G_loc[v] H^T + kept positions of (G_z[v] H^T). A workgroup of eight wavefronts walks tiles of 64 rows; a wavefront holds the
+// weights of 64 positions ([position][column], at most 64 columns) as matrix operands in registers, the groups of positions are
+// dealt to the wavefronts and, with fewer than eight groups, the two blocks of 32 rows as well. The weights are the first matrix
+// operand, which leaves positions of one row in a lane: its rule is read once, the places of positions next to each other differ by a_inv
+// (an addition and a wrap instead of a multiplication and a division by the width for each), and four results are packed at a time.
+// They leave through the wavefront's own strip of LDS as whole lines. One barrier per tile; the rows of the next tile, and the
+// places of the one after it, are on their way meanwhile. Bound by writing dX: 2,449,029 x 512 from 47 outputs 606 us (rows of the
+// result first, four wavefronts of 128 positions, the rule worked out for each element: 1,530), 169,343 x 512 from 40 47 us (104).
+constexpr int kWide = 512, kMaxWidth = 512, kTile = 64, kPitchG = P + 8, kStrip = 64 + 8;
+struct alignas(16) ClassLds {
+    uint16_t strips[kWide / 64][32 * kStrip];
+    uint16_t g[2][2][kTile * kPitchG];            // [buffer][G_loc, G_z]
+    uint2 rows_ab[2][kTile];                      // {a_inv, b}; a_inv = 0: every position kept (nothing came back, or everything)
+};
+__global__ __launch_bounds__(kWide, 4) void class_dgrad_kernel(const uint16_t* __restrict__ g_loc, const uint16_t* __restrict__ g_z,
+                                                               const int32_t* __restrict__ zrow_of, const int32_t* __restrict__ bgid, int32_t n,
+                                                               MaskRule rule, int32_t fo, const uint16_t* __restrict__ wr, int32_t cpitch,
+                                                               uint16_t* __restrict__ dx) {
+    extern __shared__ __attribute__((aligned(16))) char class_lds[];
+    ClassLds& lds = *reinterpret_cast<ClassLds*>(class_lds);
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(int32_t(threadIdx.x >> 6)), lrow = lane & 31, lk = lane >> 5;
     const int32_t width = int32_t(rule.width);
     const int ksteps = (fo + 15) / 16;
+    const int groups = width > 256 ? 8 : width > 128 ? 4 : width > 64 ? 2 : 1;
+    const int32_t first = wave % groups * 64;
     auto frag = [](const uint16_t* p) { return __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(p)); };
-    bf16x8 wf[4][4];
+    bf16x8 wf[2][4];
 #pragma unroll
-    for (int b = 0; b < 4; ++b) {
-        const int32_t pos = wave * 128 + b * 32 + lrow;
+    for (int b = 0; b < 2; ++b) {
+        const int32_t pos = first + b * 32 + lrow;
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
             wf[b][s] = __builtin_bit_cast(bf16x8, make_uint4(0u, 0u, 0u, 0u));
@@ -214,103 +253,122 @@ __global__ __launch_bounds__(kBlock, 2) void class_dgrad_kernel(const uint16_t* 
             if (s < ksteps && pos < width && c0 + 8 <= cpitch) wf[b][s] = frag(wr + int64_t(pos) * cpitch + c0);
         }
     }
-    const int32_t n_tiles = (n + kTile - 1) / kTile;
+    const int32_t n_tiles = (n + kTile - 1) / kTile, step = int32_t(gridDim.x);
     const int fr = threadIdx.x >> 3, fc = (threadIdx.x & 7) * 8;      // this thread's 16-byte piece of a tile of G: row, first column
+    auto row_of = [&](int32_t t) { return min(t * kTile + fr, n - 1); };
     uint4 nl, nz;
-    int32_t nzr = -1;
+    int32_t nzr = -1, ngid = 0;
+    int32_t after = g_z && int32_t(blockIdx.x) < n_tiles ? zrow_of[row_of(blockIdx.x)] : -1;
     auto fetch = [&](int32_t t) {
-        const int32_t row = min(t * kTile + fr, n - 1);
-        nl = *reinterpret_cast<const uint4*>(g_loc + int64_t(row) * P + fc);
-        nzr = g_z ? zrow_of[row] : -1;
+        nzr = after;
+        nl = *reinterpret_cast<const uint4*>(g_loc + int64_t(row_of(t)) * P + fc);
         nz = make_uint4(0u, 0u, 0u, 0u);
-        if (nzr >= 0) nz = *reinterpret_cast<const uint4*>(g_z + int64_t(nzr) * P + fc);
+        if (nzr >= 0) nz = *reinterpret_cast<const uint4*>(g_z + int64_t(nzr) * P + fc), ngid = bgid[nzr];
+        if (g_z && t + step < n_tiles) after = zrow_of[row_of(t + step)];
     };
     if (int32_t(blockIdx.x) < n_tiles) fetch(blockIdx.x);
-    for (int32_t t = blockIdx.x; t < n_tiles; t += gridDim.x) {
-        const int32_t row0 = t * kTile, rows = min(kTile, n - row0);
-        *reinterpret_cast<uint4*>(&ga[0][fr * kPitchG + fc]) = nl;
-        *reinterpret_cast<uint4*>(&ga[1][fr * kPitchG + fc]) = nz;
-        if ((threadIdx.x & 7) == 0) {
+    int buf = 0;
+    for (int32_t t = blockIdx.x; t < n_tiles; t += step, buf ^= 1) {      // (a buffer is written again behind the next tile's barrier)
+        *reinterpret_cast<uint4*>(&lds.g[buf][0][fr * kPitchG + fc]) = nl;
+        *reinterpret_cast<uint4*>(&lds.g[buf][1][fr * kPitchG + fc]) = nz;
+        if (fc == 0) {
             uint2 ab = make_uint2(0u, 0u);
             if (nzr >= 0 && rule.k < rule.width) {
-                const MaskAffine m = varco_affine(rule, uint32_t(bgid[nzr]));
+                const MaskAffine m = varco_affine(rule, uint32_t(ngid));
                 ab = make_uint2(m.a_inv, m.b);
             }
-            rows_ab[fr] = ab;
+            lds.rows_ab[buf][fr] = ab;
         }
         __syncthreads();
-        if (t + int32_t(gridDim.x) < n_tiles) fetch(t + gridDim.x);
-        bf16x8 fl[4], fz[4];
+        if (t + step < n_tiles) fetch(t + step);
+        if (first >= width) continue;
+        for (int rb = wave / groups; rb < kTile / 32; rb += 8 / groups) {
+            const int32_t row0 = t * kTile + rb * 32, rows = min(32, n - row0);
+            if (rows <= 0) break;
+            const uint2 ab = lds.rows_ab[buf][rb * 32 + lrow];
+            const uint32_t p0 = uint32_t(first + 4 * lk), a8 = varco_mod_width(8u * ab.x, rule.width, rule.width_magic);
+            uint32_t q8 = varco_mod_width(ab.x * (p0 + rule.width - ab.y), rule.width, rule.width_magic);
+            uint16_t* const strip = lds.strips[wave];
 #pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            fl[s] = frag(&ga[0][lrow * kPitchG + 16 * s + 8 * lk]);
-            fz[s] = frag(&ga[1][lrow * kPitchG + 16 * s + 8 * lk]);
-        }
+            for (int b = 0; b < 2; ++b) {
+                floatx16 al, az;
 #pragma unroll
-        for (int b = 0; b < 4; ++b) {
-            const int32_t pos = wave * 128 + b * 32 + lrow;
-            if (wave * 128 + b * 32 >= width) break;
-            floatx16 al, az;
+                for (int v = 0; v < 16; ++v) al[v] = az[v] = 0.f;
 #pragma unroll
-            for (int v = 0; v < 16; ++v) al[v] = az[v] = 0.f;
+                for (int s = 0; s < 4; ++s)
+                    if (s < ksteps) {
+                        const int at = (rb * 32 + lrow) * kPitchG + 16 * s + 8 * lk;
+                        al = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[b][s], frag(&lds.g[buf][0][at]), al, 0, 0, 0);
+                        az = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[b][s], frag(&lds.g[buf][1][at]), az, 0, 0, 0);
+                    }
+                // accumulator register v of a lane is position 8 * (v / 4) + 4 * (lane / 32) + v % 4 of row lane % 32
 #pragma unroll
-            for (int s = 0; s < 4; ++s)
-                if (s < ksteps) {
-                    al = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fl[s], wf[b][s], al, 0, 0, 0);
-                    az = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fz[s], wf[b][s], az, 0, 0, 0);
+                for (int g = 0; g < 4; ++g) {
+                    float x[4];
+                    uint32_t q = q8;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        x[i] = al[4 * g + i] + (q < rule.k ? az[4 * g + i] : 0.f);
+                        q += ab.x, q = min(q, q - rule.width);
+                    }
+                    q8 += a8, q8 = min(q8, q8 - rule.width);
+                    *reinterpret_cast<uint2*>(strip + lrow * kStrip + 32 * b + 8 * g + 4 * lk) = make_uint2(bf16_pair(x[0], x[1]), bf16_pair(x[2], x[3]));
                 }
-            // accumulator register v of a lane is element (8 * (v / 4) + 4 * (lane / 32) + v % 4, lane % 32)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int r = 8 * (v >> 2) + 4 * lk + (v & 3);
-                const uint2 ab = rows_ab[r];
-                bool kept = rule.k == rule.width;
-                if (!kept) {
-                    const uint32_t d = uint32_t(pos) >= ab.y ? uint32_t(pos) - ab.y : uint32_t(pos) + rule.width - ab.y;
-                    kept = varco_mod_width(ab.x * d, rule.width, rule.width_magic) < rule.k;
-                }
-                if (pos < width) tile[r * kPitch + pos] = float_to_bf16(al[v] + (kept ? az[v] : 0.f));
             }
-        }
-        __syncthreads();
-        const int per_row = width / 8;                 // width is a multiple of 16
-        for (int e = threadIdx.x; e < rows * per_row; e += kBlock) {
-            const int r = e / per_row, c = (e - r * per_row) * 8;
-            *reinterpret_cast<uint4*>(dx + int64_t(row0 + r) * width + c) = *reinterpret_cast<const uint4*>(&tile[r * kPitch + c]);
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            const int sr = lane >> 3, sc = (lane & 7) * 8;                // width is a multiple of 16
+            if (first + sc < width)
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (sr + 8 * i < rows)
+                        *reinterpret_cast<uint4*>(dx + int64_t(row0 + sr + 8 * i) * width + first + sc) =
+                            *reinterpret_cast<const uint4*>(strip + (sr + 8 * i) * kStrip + sc);
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         }
     }
 }
 
 // The same for fp32 storage, with the self tap of a SAGE layer: dX[v] = G_loc[v] H1^T + kept positions of (G_z[v] H1^T) (+ dZ[v] H0^T)
-// from two scaled fp16 terms per operand (kernels_gemm_half.hip). A workgroup of eight wavefronts walks tiles of ROWS rows; a wavefront
-// holds the weights of 32 positions as matrix operands in registers, both taps at the same scale per position. The rows of the next
-// tile are on their way while one is multiplied: 16 or 8 lanes take a row of each source, agree on one scale for the three, and write
-// the terms to LDS once for all wavefronts. A half wavefront stores 32 positions of a row, one line. Bound by writing dX and reading the
-// three sources: 2,449,029 x 256 from 47 outputs with both taps 1.45 ms, 169,343 x 256 from 40 outputs 74 us (one workgroup per compute unit:
-// 97 us).
-constexpr int kWide = 512;
-// Wavefronts per SIMD: two workgroups are resident where 128 registers hold the weights, the sums and the next tile.
-constexpr int class_waves(int ks, int rows, bool self) { return ks * (self ? 2 : 1) <= 4 && (rows == 32 || ks < 3) ? 4 : 2; }
+// from two scaled fp16 terms per operand (kernels_gemm_half.hip), three where at most 16 columns are summed: there the rounding of the
+// terms does not average out (128 positions from 3 columns: Frobenius error 9.2e-8 with two, 7.0e-8 with three, 8.4e-8 for sums over
+// products formed in fp32). A workgroup of eight wavefronts walks tiles of ROWS rows; a wavefront holds the weights of 32 positions as
+// matrix operands in registers, both taps at the same scale per position. 16 or 8 lanes take a row of each source, agree on one scale
+// for the three, and write the terms to LDS once for all wavefronts. The cross product comes first and is cleared where nothing came
+// back, so that all three are summed in the same registers; 128 of them hold everything of two workgroups per compute unit. Bound by
+// writing dX and reading the three sources: 2,449,029 x 256 from 47 outputs with both taps 0.96 ms (1.45 with rows of the result first,
+// one workgroup per compute unit and dependent loads at each tile), 169,343 x 256 from 40 outputs 61 us (74).
+// Wavefronts per SIMD: two workgroups are resident where 128 registers hold the weights, the sums and the next tile (and the LDS allows).
+constexpr int class_waves(int ks, int rows, bool self) { return !self || ks < (rows == 32 ? 4 : 3) ? 4 : 2; }
+constexpr int kStripF = 32 + 4;
+template <int KS, int ROWS, bool SELF>
+struct alignas(16) ClassLdsF32 {
+    static constexpr int TERMS = KS == 1 ? 3 : 2, kTile = (SELF ? 3 : 2) * TERMS * ROWS * (16 * KS + 8), kStrips = kWide / 64 * 32 * kStripF;
+    static constexpr int BUFS = 2 * 2 * kTile + 4 * kStrips + 32 * ROWS + 4 * 256 <= 80 * 1024 ? 2 : 1;      // two where two workgroups still fit
+    float strips[kWide / 64][32 * kStripF];
+    uint16_t tile[BUFS][kTile];                   // [source][term][row][column]
+    uint4 rows[BUFS][ROWS];                       // {a_inv, b, scale}; a_inv = 0: every position kept (nothing came back, or everything)
+    int32_t eb[kWide / 64][32];                   // scale of each position's weights
+};
 template <int KS, int ROWS, int ROW, bool SELF>
 __global__ __launch_bounds__(kWide, class_waves(KS, ROWS, SELF)) void class_dgrad_f32_kernel(const float* __restrict__ g_loc, const float* __restrict__ g_z,
                                                                     const float* __restrict__ dz, int32_t dz_ld, const int32_t* __restrict__ zrow_of,
                                                                     const int32_t* __restrict__ bgid, int32_t n, MaskRule rule, int32_t fo,
-                                                                    const float* __restrict__ h1, const float* __restrict__ h0, float* __restrict__ dx) {
+                                                                    const float* __restrict__ h1, const float* __restrict__ h0, float* __restrict__ dx, bool vec) {
     constexpr int S = SELF ? 3 : 2, kRow = 16 * KS + 8, kPlane = ROWS * kRow;         // sources: G_loc, G_z, dZ
     constexpr int LANES = ROW / 4, kPass = kWide / LANES, N = (ROWS + kPass - 1) / kPass;      // rows per pass, passes
     static_assert(LANES == 8 || LANES == 16, "rows of 32 or 64 values");
-    __shared__ __attribute__((aligned(16))) uint16_t tile[S * 2 * kPlane];            // [source][term][row][column]
-    __shared__ __attribute__((aligned(16))) int32_t exps[ROWS];
-    __shared__ __attribute__((aligned(16))) uint2 rows_ab[ROWS];               // {a_inv, b}; a_inv = 0, b = width: nothing came back
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lcol = lane & 31, lk = lane >> 5;
+    using Lds = ClassLdsF32<KS, ROWS, SELF>;
+    constexpr int BUFS = Lds::BUFS, TERMS = Lds::TERMS;
+    extern __shared__ __attribute__((aligned(16))) char class_lds[];
+    Lds& lds = *reinterpret_cast<Lds*>(class_lds);
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(int32_t(threadIdx.x >> 6)), lcol = lane & 31, lk = lane >> 5;
     const int32_t width = int32_t(rule.width), first = int32_t(blockIdx.y) * 256;
     // groups of 32 positions; with fewer than eight the blocks of rows are dealt as well
     const int groups = width - first > 128 ? 8 : width - first > 64 ? 4 : width - first > 32 ? 2 : 1;
-    const int32_t pos = first + wave % groups * 32 + lcol, wave_rb = __builtin_amdgcn_readfirstlane(wave / groups);
+    const int32_t pos0 = first + wave % groups * 32, pos = pos0 + lcol;
 
     // operands: lane holds H[position][16 s + 8 lk .. + 7], both terms
-    uint4 w[SELF ? 2 : 1][KS][2];
-    int32_t eb;
+    uint4 w[SELF ? 2 : 1][KS][TERMS];
     {
         float x[SELF ? 2 : 1][KS][8], m = 0.f;
 #pragma unroll
@@ -324,7 +382,8 @@ __global__ __launch_bounds__(kWide, class_waves(KS, ROWS, SELF)) void class_dgra
                     m = fmaxf(m, fabsf(x[tap][s][i]));
                 }
         m = fmaxf(m, __shfl_xor(m, 32));
-        eb = scale_exponent(m, kHalfTop);
+        const int32_t eb = scale_exponent(m, kHalfTop);
+        if (lk == 0) lds.eb[wave][lcol] = eb;                 // (read by this wavefront only, behind the first tile's barrier)
         const float sc = power_of_two(eb);
 #pragma unroll
         for (int tap = 0; tap < (SELF ? 2 : 1); ++tap)
@@ -334,33 +393,46 @@ __global__ __launch_bounds__(kWide, class_waves(KS, ROWS, SELF)) void class_dgra
 #pragma unroll
                 for (int i = 0; i < 4; ++i) split_pair(x[tap][s][2 * i] * sc, x[tap][s][2 * i + 1] * sc, hi[i], lo[i]);
                 w[tap][s][0] = make_uint4(hi[0], hi[1], hi[2], hi[3]), w[tap][s][1] = make_uint4(lo[0], lo[1], lo[2], lo[3]);
+                if constexpr (TERMS == 3) {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) lo[i] = third_pair(x[tap][s][2 * i] * sc, x[tap][s][2 * i + 1] * sc, hi[i], lo[i]);
+                    w[tap][s][2] = make_uint4(lo[0], lo[1], lo[2], lo[3]);
+                }
             }
     }
 
-    const int32_t n_tiles = (n + ROWS - 1) / ROWS;
+    const int32_t n_tiles = (n + ROWS - 1) / ROWS, step = int32_t(gridDim.x);
     const int fr = threadIdx.x / LANES, fc = (threadIdx.x % LANES) * 4;               // rows fr + kPass h, columns fc .. fc + 3
+    auto row_of = [&](int32_t t, int h) { return uint32_t(min(min(fr + kPass * h, ROWS - 1), n - 1 - t * ROWS)); };     // within the tile
     float4 next[N][S];
-    int32_t next_z[N];
+    int32_t next_gid[N], after[N];
+    auto places = [&](int32_t t) {
+#pragma unroll
+        for (int h = 0; h < N; ++h) after[h] = g_z ? (zrow_of + t * ROWS)[row_of(t, h)] : -1;
+    };
     auto fetch = [&](int32_t t) {
 #pragma unroll
         for (int h = 0; h < N; ++h) {
-            const int32_t row = min(t * ROWS + min(fr + kPass * h, ROWS - 1), n - 1);
-            next[h][0] = *reinterpret_cast<const float4*>(g_loc + int64_t(row) * ROW + fc);
+            uint32_t row = row_of(t, h);
+            asm volatile("" : "+v"(row));
+            next_gid[h] = -1;
+            next[h][0] = *reinterpret_cast<const float4*>(g_loc + int64_t(t) * (ROWS * ROW) + (row * ROW + uint32_t(fc)));
+            next[h][1] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (after[h] >= 0) next[h][1] = *reinterpret_cast<const float4*>(g_z + int64_t(after[h]) * ROW + fc), next_gid[h] = bgid[after[h]];
             if constexpr (SELF) {
                 next[h][2] = make_float4(0.f, 0.f, 0.f, 0.f);
-                if (fc < dz_ld) next[h][2] = *reinterpret_cast<const float4*>(dz + int64_t(row) * dz_ld + fc);
+                if (fc < dz_ld) next[h][2] = *reinterpret_cast<const float4*>(dz + int64_t(t) * ROWS * dz_ld + (row * uint32_t(dz_ld) + uint32_t(fc)));
             }
-            next_z[h] = g_z ? zrow_of[row] : -1;
         }
-#pragma unroll
-        for (int h = 0; h < N; ++h) {
-            next[h][1] = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (next_z[h] >= 0) next[h][1] = *reinterpret_cast<const float4*>(g_z + int64_t(next_z[h]) * ROW + fc);
-        }
+        if (t + step < n_tiles) places(t + step);
     };
-    if (int32_t(blockIdx.x) < n_tiles) fetch(blockIdx.x);
-    for (int32_t t = blockIdx.x; t < n_tiles; t += gridDim.x) {
-        const int32_t row0 = t * ROWS, rows = min(ROWS, n - row0);
+    if (int32_t(blockIdx.x) < n_tiles) {
+        places(blockIdx.x);
+        fetch(blockIdx.x);
+    }
+    int buf = 0;
+    for (int32_t t = blockIdx.x; t < n_tiles; t += step, buf ^= BUFS - 1) {    // (a second buffer is written again behind the next tile's barrier)
+        uint16_t* const tile = lds.tile[buf];
 #pragma unroll
         for (int h = 0; h < N; ++h) {
             float m = 0.f;
@@ -389,80 +461,104 @@ __global__ __launch_bounds__(kWide, class_waves(KS, ROWS, SELF)) void class_dgra
                     uint32_t hi[2], lo[2];
                     split_pair(next[h][s].x * sc, next[h][s].y * sc, hi[0], lo[0]);
                     split_pair(next[h][s].z * sc, next[h][s].w * sc, hi[1], lo[1]);
-                    *reinterpret_cast<uint2*>(&tile[(2 * s) * kPlane + r * kRow + fc]) = make_uint2(hi[0], hi[1]);
-                    *reinterpret_cast<uint2*>(&tile[(2 * s + 1) * kPlane + r * kRow + fc]) = make_uint2(lo[0], lo[1]);
+                    *reinterpret_cast<uint2*>(&tile[(TERMS * s) * kPlane + r * kRow + fc]) = make_uint2(hi[0], hi[1]);
+                    *reinterpret_cast<uint2*>(&tile[(TERMS * s + 1) * kPlane + r * kRow + fc]) = make_uint2(lo[0], lo[1]);
+                    if constexpr (TERMS == 3)
+                        *reinterpret_cast<uint2*>(&tile[(TERMS * s + 2) * kPlane + r * kRow + fc]) =
+                            make_uint2(third_pair(next[h][s].x * sc, next[h][s].y * sc, hi[0], lo[0]), third_pair(next[h][s].z * sc, next[h][s].w * sc, hi[1], lo[1]));
                 }
             }
             if (r < ROWS && fc == 0) {
-                exps[r] = e;
-                uint2 ab = make_uint2(0u, rule.width);
-                if (next_z[h] >= 0 && rule.k < rule.width) {
-                    const MaskAffine a = varco_affine(rule, uint32_t(bgid[next_z[h]]));
+                uint2 ab = make_uint2(0u, 0u);
+                if (next_gid[h] >= 0 && rule.k < rule.width) {
+                    const MaskAffine a = varco_affine(rule, uint32_t(next_gid[h]));
                     ab = make_uint2(a.a_inv, a.b);
                 }
-                rows_ab[r] = ab;
+                lds.rows[buf][r] = make_uint4(ab.x, ab.y, uint32_t(e), 0u);
             }
         }
         __syncthreads();
-        if (t + int32_t(gridDim.x) < n_tiles) fetch(t + gridDim.x);
-        for (int rb = wave_rb; rb * 32 < rows && pos - lcol < width; rb += 8 / groups) {
-            floatx16 sum, low, far;
-            int frag_at = (rb * 32 + lcol) * kRow + 8 * lk;
-            asm volatile("" : "+v"(frag_at));
+        if (t + step < n_tiles) fetch(t + step);
+        for (int rb = wave / groups; rb < ROWS / 32 && pos0 < width; rb += 8 / groups) {
+            const int32_t row0 = t * ROWS + rb * 32, rows = min(32, n - row0);
+            if (rows <= 0) break;
+            floatx16 sum, low;
+            int me = lane;
+            asm volatile("" : "+v"(me));              // addresses are formed where they are used
+            const int lcol = me & 31, lk = me >> 5;
+            const int frag_at = (rb * 32 + lcol) * kRow + 8 * lk;
             auto frag = [&](int source, int term, int s) {
-                return __builtin_bit_cast(halfx8, *reinterpret_cast<const uint4*>(&tile[(2 * source + term) * kPlane + frag_at + 16 * s]));
+                return __builtin_bit_cast(halfx8, *reinterpret_cast<const uint4*>(&tile[(TERMS * source + term) * kPlane + frag_at + 16 * s]));
             };
             auto product = [&](int source, int tap) {
 #pragma unroll
                 for (int s = 0; s < KS; ++s) {
                     const halfx8 a0 = frag(source, 0, s), a1 = frag(source, 1, s);
                     const halfx8 b0 = __builtin_bit_cast(halfx8, w[tap][s][0]), b1 = __builtin_bit_cast(halfx8, w[tap][s][1]);
-                    sum = __builtin_amdgcn_mfma_f32_32x32x16_f16(a0, b0, sum, 0, 0, 0);
-                    low = __builtin_amdgcn_mfma_f32_32x32x16_f16(a0, b1, low, 0, 0, 0);
-                    low = __builtin_amdgcn_mfma_f32_32x32x16_f16(a1, b0, low, 0, 0, 0);
-                    if constexpr (KS == 1) low = __builtin_amdgcn_mfma_f32_32x32x16_f16(a1, b1 * _Float16(1.f / kHalfLow), low, 0, 0, 0);
+                    sum = __builtin_amdgcn_mfma_f32_32x32x16_f16(b0, a0, sum, 0, 0, 0);
+                    low = __builtin_amdgcn_mfma_f32_32x32x16_f16(b1, a0, low, 0, 0, 0);
+                    low = __builtin_amdgcn_mfma_f32_32x32x16_f16(b0, a1, low, 0, 0, 0);
+                    if constexpr (TERMS == 3) {
+                        const halfx8 a2 = frag(source, 2, s), b2 = __builtin_bit_cast(halfx8, w[tap][s][2]);
+                        low = __builtin_amdgcn_mfma_f32_32x32x16_f16(b1 * _Float16(1.f / kHalfLow), a1, low, 0, 0, 0);
+                        low = __builtin_amdgcn_mfma_f32_32x32x16_f16(b2, a0, low, 0, 0, 0);
+                        low = __builtin_amdgcn_mfma_f32_32x32x16_f16(b0, a2, low, 0, 0, 0);
+                    }
                 }
             };
-            // accumulator register v of a lane is element (8 * (v / 4) + 4 * (lane / 32) + v % 4, lane % 32)
+            // accumulator register v of a lane is position 8 * (v / 4) + 4 * (lane / 32) + v % 4 of row lane % 32
 #pragma unroll
-            for (int v = 0; v < 16; ++v) sum[v] = low[v] = far[v] = 0.f;
-            if (g_z) {                                // first, and down to one register per value before the others start
+            for (int v = 0; v < 16; ++v) sum[v] = low[v] = 0.f;
+            if (g_z) {                                // first, and dropped where the row's message did not carry it
                 product(1, 0);
+                const uint2 ab = *reinterpret_cast<const uint2*>(&lds.rows[buf][rb * 32 + lcol]);
+                const uint32_t a_inv = ab.x, at = ab.y, p0 = uint32_t(pos0 + 4 * lk);
+                const uint32_t a8 = varco_mod_width(8u * a_inv, rule.width, rule.width_magic);
+                uint32_t q8 = varco_mod_width(a_inv * (p0 >= at ? p0 - at : p0 + rule.width - at), rule.width, rule.width_magic);
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int r0 = rb * 32 + 8 * q + 4 * lk;
-                    const uint4 ab01 = *reinterpret_cast<const uint4*>(&rows_ab[r0]), ab23 = *reinterpret_cast<const uint4*>(&rows_ab[r0 + 2]);
-                    const uint32_t a_inv[4] = {ab01.x, ab01.z, ab23.x, ab23.z}, at[4] = {ab01.y, ab01.w, ab23.y, ab23.w};
+                for (int g = 0; g < 4; ++g) {
+                    uint32_t q = q8;
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
-                        const int v = 4 * q + i;
-                        const uint32_t d = uint32_t(pos) >= at[i] ? uint32_t(pos) - at[i] : uint32_t(pos) + rule.width - at[i];
-                        const bool kept = rule.k == rule.width || varco_mod_width(a_inv[i] * d, rule.width, rule.width_magic) < rule.k;
-                        far[v] = kept ? sum[v] + low[v] * (1.f / kHalfLow) : 0.f;
-                        sum[v] = low[v] = 0.f;
+                        if (q >= rule.k) sum[4 * g + i] = low[4 * g + i] = 0.f;
+                        q += a_inv, q = min(q, q - rule.width);
                     }
+                    q8 += a8, q8 = min(q8, q8 - rule.width);
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
             product(0, 0);
+            __builtin_amdgcn_sched_barrier(0);
             if constexpr (SELF) product(2, 1);
-            float* const out = dx + int64_t(row0 + rb * 32) * width;      // a scalar per row and one offset per lane
-            uint32_t lane_off = uint32_t(4 * lk) * uint32_t(width) + uint32_t(pos);
-            asm volatile("" : "+v"(lane_off));
+            float* const strip = lds.strips[wave];
+            const int32_t row_scale = int32_t(lds.rows[buf][rb * 32 + lcol].z);
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int r0 = 8 * q + 4 * lk;
-                const int4 ev = *reinterpret_cast<const int4*>(&exps[rb * 32 + r0]);
-                const int32_t e[4] = {ev.x, ev.y, ev.z, ev.w};
+            for (int g = 0; g < 4; ++g) {
+                const int4 eb = *reinterpret_cast<const int4*>(&lds.eb[wave][8 * g + 4 * lk]);
+                const int32_t e[4] = {eb.x, eb.y, eb.z, eb.w};
+                float y[4];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const float y = __builtin_ldexpf(sum[4 * q + i] + low[4 * q + i] * (1.f / kHalfLow) + far[4 * q + i], -(e[i] + eb));
-                    if (rb * 32 + r0 + i < rows && pos < width) (out + int64_t(8 * q + i) * width)[lane_off] = y;
-                }
+                for (int i = 0; i < 4; ++i)
+                    y[i] = __builtin_ldexpf(sum[4 * g + i] + low[4 * g + i] * (1.f / kHalfLow), -(row_scale + e[i]));
+                *reinterpret_cast<float4*>(strip + lcol * kStripF + 8 * g + 4 * lk) = make_float4(y[0], y[1], y[2], y[3]);
                 __builtin_amdgcn_sched_barrier(0);            // (a group's scales are read when it is its turn)
             }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            float* const out = dx + int64_t(row0) * width + pos0;
+            if (vec) {                                // a scalar per row and one offset per lane
+                const int sr = me >> 3, sc = (me & 7) * 4;
+                const uint32_t lane_off = uint32_t(sr) * uint32_t(width) + uint32_t(sc);
+                if (pos0 + sc < width)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        if (sr + 8 * i < rows)
+                            *reinterpret_cast<float4*>(out + int64_t(8 * i) * width + lane_off) = *reinterpret_cast<const float4*>(strip + (sr + 8 * i) * kStripF + sc);
+            } else if (pos < width) {
+                for (int r = lk; r < rows; r += 2) out[int64_t(r) * width + lcol] = strip[r * kStripF + lcol];
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         }
-        __syncthreads();
+        if constexpr (BUFS == 1) __syncthreads();
     }
 }
 
@@ -493,7 +589,7 @@ hipError_t narrow_backward(const NodePlan& plan, const uint2* t_local, const uin
     const T* const src = static_cast<const T*>(dz_padded);
     const int32_t ld = dz_padded == dz ? fo : ROW;
     if (dz_padded != dz)
-        hipLaunchKernelGGL((pad_rows_kernel<T, ROW>), dim3(unsigned(std::min<int64_t>((rows * ROW + kBlock - 1) / kBlock, 256 * 32))), dim3(kBlock), 0, stream,
+        hipLaunchKernelGGL((pad_rows_kernel<T, ROW>), dim3(unsigned(std::min<int64_t>((rows * ROW / Columns<T>::N + kBlock - 1) / kBlock, 256 * 32))), dim3(kBlock), 0, stream,
                            static_cast<const T*>(dz), rows, fo, static_cast<T*>(dz_padded));
     hipLaunchKernelGGL((narrow_backward_kernel<T, ROW, false>), waves_for(int64_t(plan.n_pieces) + plan.n_whole), dim3(kBlock), 0, stream, plan.nodes,
                        plan.n_whole, plan.pieces, plan.n_pieces, t_local, t_cross, src, ld, zrow_of, static_cast<T*>(g_loc), static_cast<T*>(g_z), fo, partial);
@@ -522,9 +618,11 @@ hipError_t varco_launch_class_dgrad(const void* g_loc, const void* g_z, const in
     if (rows == 0) return hipSuccess;
     if (rule.width % 16 != 0 || rule.width > uint32_t(kMaxWidth) || fo > P || cpitch < fo || cpitch % 8 != 0 || (reinterpret_cast<uintptr_t>(dx) & 15u))
         return hipErrorInvalidValue;
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(class_dgrad_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, int(sizeof(ClassLds)));
+    if (e != hipSuccess) return e;
     tag.begin(stream);
     const int64_t tiles = (rows + kTile - 1) / kTile;
-    hipLaunchKernelGGL(class_dgrad_kernel, dim3(unsigned(std::min<int64_t>(tiles, 512))), dim3(kBlock), 0, stream, static_cast<const uint16_t*>(g_loc),
+    hipLaunchKernelGGL(class_dgrad_kernel, dim3(unsigned(std::min<int64_t>(tiles, 512))), dim3(kWide), sizeof(ClassLds), stream, static_cast<const uint16_t*>(g_loc),
                        static_cast<const uint16_t*>(g_z), zrow_of, bgid, int32_t(rows), rule, fo, static_cast<const uint16_t*>(wr), cpitch,
                        static_cast<uint16_t*>(dx));
     tag.end(stream);
@@ -537,13 +635,19 @@ hipError_t varco_launch_class_dgrad_f32(const void* g_loc, const void* g_z, cons
     if (rows == 0) return hipSuccess;
     if (fo < 1 || fo > 64) return hipErrorInvalidValue;
     tag.begin(stream);
+    hipError_t err = hipSuccess;
+    const bool vec = rule.width % 4 == 0 && (reinterpret_cast<uintptr_t>(dx) & 15u) == 0;
     auto go = [&](auto ks, auto tile, auto row, auto self) {
         constexpr int ROWS = decltype(tile)::value;
         const int64_t tiles = (rows + ROWS - 1) / ROWS, slices = (rule.width + 255) / 256;
         const dim3 grid{unsigned(std::min<int64_t>(tiles, std::max<int64_t>(1, 128 * class_waves(decltype(ks)::value, ROWS, decltype(self)::value) / slices))), unsigned(slices)};
-        hipLaunchKernelGGL((class_dgrad_f32_kernel<decltype(ks)::value, ROWS, decltype(row)::value, decltype(self)::value>), grid, dim3(kWide), 0, stream,
+        using Lds = ClassLdsF32<decltype(ks)::value, ROWS, decltype(self)::value>;
+        const auto kernel = class_dgrad_f32_kernel<decltype(ks)::value, ROWS, decltype(row)::value, decltype(self)::value>;
+        if (sizeof(Lds) > 64 * 1024) err = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, int(sizeof(Lds)));
+        if (err != hipSuccess) return;
+        hipLaunchKernelGGL(kernel, grid, dim3(kWide), sizeof(Lds), stream,
                            static_cast<const float*>(g_loc), static_cast<const float*>(g_z), static_cast<const float*>(dz), dz_ld, zrow_of, bgid, int32_t(rows),
-                           rule, fo, static_cast<const float*>(h1), static_cast<const float*>(h0), static_cast<float*>(dx));
+                           rule, fo, static_cast<const float*>(h1), static_cast<const float*>(h0), static_cast<float*>(dx), vec);
     };
     using std::integral_constant;
     auto with_self = [&](auto ks, auto tile, auto row) {
@@ -565,5 +669,5 @@ hipError_t varco_launch_class_dgrad_f32(const void* g_loc, const void* g_z, cons
         default: with_tile(integral_constant<int, 4>{}, integral_constant<int, 64>{}); break;
     }
     tag.end(stream);
-    return hipGetLastError();
+    return err != hipSuccess ? err : hipGetLastError();
 }

@@ -48,6 +48,16 @@ def test_class_layer_errors_with_hubs(conv, widths, dtype):
     _compare_network(g, part, 3, conv, widths, ratios, steps=list(range(5)), tol=BF16_TOL if dtype == "bf16" else 1e-4, dtype=dtype)
 
 
+@pytest.mark.parametrize("conv,widths,dtype", [("gcn", (16, 48, 3), "bf16"), ("sage", (16, 144, 33), "bf16"), ("sage", (16, 144, 33), "f32"),
+                                               ("gcn", (16, 40, 47), "f32"), ("sage", (16, 65, 50), "f32")])
+def test_class_layer_errors_over_many_tiles(conv, widths, dtype):
+    # more tiles of rows than workgroups, several times over: both LDS buffers are written again, the last tile has a remainder; rows
+    # of dZ of any length padded (shorter than 16 bytes, and longer)
+    g = hub_graph(131_100, 3, 900, 2.0, conv, seed=93)
+    part = synth.random_partition(g.n, 3, seed=94)
+    _compare_network(g, part, 3, conv, widths, [(5, 1), (1, 1)], steps=[0, 1], tol=BF16_TOL if dtype == "bf16" else 1e-4, dtype=dtype)
+
+
 def test_uneven_and_empty_partitions():
     g = synth.small_random_graph(300, 5.0, "gcn", seed=83)
     part = np.zeros(g.n, dtype=np.int32)
