@@ -12,9 +12,9 @@
 // of each other decide as they always did; that forgoes 0.9 of 3.47 ms for K = 2 x 256, N = 256 over 2,449,029 rows.)
 //
 // A workgroup of four wavefronts computes a 128 x 128 tile of C (128 x 64 for outputs at most 64 columns wide), a
-// wavefront 64 x 64 (32 x 64); two workgroups are resident per compute unit (see the kernel). A stage of 32
+// wavefront 64 x 64 (32 x 64); three workgroups are resident per compute unit (see the kernel). A stage of 32
 // reduction steps is fetched into registers one step ahead, then expanded and written to LDS as TERMS planes of
-// bf16 rows (one output index per row, reduction index contiguous, 80-byte pitch). A has the reduction index contiguous and is
+// bf16 rows (one output index per row, reduction index contiguous, 64-byte pitch, pieces rotated). A has the reduction index contiguous and is
 // expanded here; B is the library's own expanded copy of the weights (varco_launch_prep_weights), zero-padded
 // to whole tiles and copied as is. The activation is applied in the epilogue.
 #include <algorithm>
@@ -28,7 +28,7 @@ namespace {
 
 constexpr int BK = 32;
 constexpr int kThreads = 256;
-constexpr int kPitch = BK + 8;   // bf16 elements per LDS row (80 bytes)
+constexpr int kPitch = BK;       // bf16 elements per LDS row (64 bytes)
 constexpr int kPrepRows = 128;   // expanded weight copies are padded to this many rows (the widest B tile) and to BK columns
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
@@ -70,10 +70,9 @@ __device__ __forceinline__ void expand_pair(float x0, float x1, uint32_t (&w)[TE
     }
 }
 
-// Consecutive groups of lanes write consecutive tile rows; with an 80-byte pitch rows r and r + 1 overlap in
-// four LDS banks while rows r and r + 4 tile all of them, so the q-th row group of a wavefront goes to row
-// (q with its low three bits rotated): 0 4 1 5 2 6 3 7.
-__device__ __forceinline__ int tile_row(int q) { return (q & ~7) | ((q & 1) << 2) | ((q >> 1) & 3); }
+// LDS rows are 64 bytes, four of them cover the banks once; the 16-byte pieces of every fourth row are rotated differently, so that
+// the 16 rows whose fragments are read together lie in 16 different places.
+__device__ __forceinline__ int lds_at(int row, int k) { return row * kPitch + (k ^ ((row << 1) & 24)); }      // (bits 2, 3 of the row)
 
 template <typename T>
 __device__ __forceinline__ T load_at(const void* base, uint32_t byte_offset) {
@@ -105,7 +104,7 @@ struct RowPlan {
 #pragma unroll
         for (int h = 0; h < N; ++h) {
             const int c = tid + h * kThreads;
-            const int32_t r = min(tile_row(c / PER_ROW), extent - 1 - i0);
+            const int32_t r = min(c / PER_ROW, extent - 1 - i0);
             off[h] = uint32_t(r * ld + (c % PER_ROW) * CH) * 4u;
         }
     }
@@ -136,7 +135,7 @@ __device__ __forceinline__ void store_rows(int tid, const RowRegs<ROWS, CH>& r, 
             expand_pair<TERMS>(x.x, x.y, w[2 * u]);
             expand_pair<TERMS>(x.z, x.w, w[2 * u + 1]);
         }
-        uint16_t* dst = s + tile_row(c / R::PER_ROW) * kPitch + (c % R::PER_ROW) * CH;
+        uint16_t* dst = s + lds_at(c / R::PER_ROW, (c % R::PER_ROW) * CH);
 #pragma unroll
         for (int p = 0; p < TERMS; ++p) {
             if constexpr (CH == 8)
@@ -159,24 +158,9 @@ struct PrepRegs {
 };
 
 template <int TERMS, int ROWS>
-struct PrepPlan {
-    static constexpr int PER_ROW = BK / 8;
-    static constexpr int N = TERMS * ROWS * PER_ROW / kThreads;
-    uint32_t off[N];     // bytes from the block's base
-    __device__ __forceinline__ void init(int tid) {
+__device__ __forceinline__ void load_prep(int tid, const uint16_t* base, PrepRegs<TERMS, ROWS>& r) {
 #pragma unroll
-        for (int h = 0; h < N; ++h) {
-            const int c = tid + h * kThreads;
-            const int p = c / (ROWS * PER_ROW), rc = c % (ROWS * PER_ROW);
-            off[h] = uint32_t((p * ROWS + tile_row(rc / PER_ROW)) * BK + (rc % PER_ROW) * 8) * 2u;
-        }
-    }
-};
-
-template <int TERMS, int ROWS>
-__device__ __forceinline__ void load_prep(const uint16_t* base, const PrepPlan<TERMS, ROWS>& plan, PrepRegs<TERMS, ROWS>& r) {
-#pragma unroll
-    for (int h = 0; h < PrepRegs<TERMS, ROWS>::N; ++h) r.v[h] = load_at<uint4>(base, plan.off[h]);
+    for (int h = 0; h < PrepRegs<TERMS, ROWS>::N; ++h) r.v[h] = load_at<uint4>(base + h * kThreads * 8, uint32_t(tid) * 16u);
 }
 
 template <int TERMS, int ROWS>
@@ -186,12 +170,12 @@ __device__ __forceinline__ void store_prep(int tid, const PrepRegs<TERMS, ROWS>&
     for (int h = 0; h < R::N; ++h) {
         const int c = tid + h * kThreads;
         const int p = c / (ROWS * R::PER_ROW), rc = c % (ROWS * R::PER_ROW);
-        *reinterpret_cast<uint4*>(s + p * ROWS * kPitch + tile_row(rc / R::PER_ROW) * kPitch + (rc % R::PER_ROW) * 8) = r.v[h];
+        *reinterpret_cast<uint4*>(s + p * ROWS * kPitch + lds_at(rc / R::PER_ROW, (rc % R::PER_ROW) * 8)) = r.v[h];
     }
 }
 
 __device__ __forceinline__ bf16x8 fragment(const uint16_t* s, int row, int koff) {
-    return __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(s + row * kPitch + koff));
+    return __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(s + lds_at(row, koff)));
 }
 
 template <int TMB, int TNB, int PA, int PB>
@@ -205,16 +189,17 @@ __device__ __forceinline__ void multiply(const bf16x8 (&fa)[3][TMB], const bf16x
 
 // WM x WN wavefronts per tile, each TMB x TNB blocks of 32 x 32. A_CH: floats per chunk of A.
 //
-// A workgroup is four wavefronts with one tile and one LDS stage (60 KB), so that two workgroups are resident
-// on a compute unit and each SIMD holds one wavefront of either. On this device the vector ALU and the matrix
+// A workgroup is four wavefronts with one tile and one LDS stage (48 KB, rows without padding), so that three workgroups are
+// resident on a compute unit and each SIMD holds one wavefront of each. On this device the vector ALU and the matrix
 // unit of a SIMD do not run side by side (hardware counters: their busy times add up), so nothing is gained by
 // steering one wavefront's conversions under the other's products; what matters is that the SIMD always has a
 // wavefront that can issue, and that as few vector instructions as possible accompany the matrix instructions.
-// Two independent workgroups give the first: while one waits at a barrier, for its global loads, or stores its
-// tile, the other multiplies. (Two groups in lock step inside one 512-thread workgroup, the previous form, left
-// a tile's first fetch and epilogue uncovered and tied both groups to the slower one.)
+// Independent workgroups give the first: while one waits at a barrier, for its global loads, or stores its
+// tile, the others multiply. (With rows padded to 80 bytes, two resident: the units idle 38 % of the time. 2,449,029 rows, 256 x 256
+// 1,996 -> 1,895 us, 100 x 256 1,171 -> 1,086; 169,343 rows 146 -> 137, 77 -> 70; 50,021 rows, whose tiles end just past a round of three
+// per unit, 47.6 -> 49.5.)
 template <int TERMS, int WM, int WN, int TMB, int TNB, int A_CH>
-__global__ __launch_bounds__(kThreads, 2) void gemm_split_kernel(SplitGemm g) {
+__global__ __launch_bounds__(kThreads, 3) void gemm_split_kernel(SplitGemm g) {
     static_assert(TERMS == 2 || TERMS == 3, "two or three bf16 terms per operand");
     constexpr int BM = 32 * TMB * WM, BN = 32 * TNB * WN;
     __shared__ __attribute__((aligned(16))) uint16_t smem[TERMS * (BM + BN) * kPitch];
@@ -247,9 +232,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_split_kernel(SplitGemm g) {
     RowRegs<BM, A_CH> ra;
     PrepRegs<TERMS, BN> rb;
     RowPlan<BM, A_CH> plan_a;
-    PrepPlan<TERMS, BN> plan_b;
     plan_a.init(tid, m0, g.m, g.a.ld);            // a chained second product has the same leading dimensions
-    plan_b.init(tid);
 
     auto fetch = [&](int32_t t) {
         const bool first = t < tiles1;
@@ -258,14 +241,14 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_split_kernel(SplitGemm g) {
         const uint16_t* bbase = static_cast<const uint16_t*>(first ? g.b.ptr : g.b2.ptr) +
                                 (int64_t(tn) * (g.b.ld / BK) + k0 / BK) * (TERMS * BN * BK);      // g.b.ld: padded reduction length
         load_rows<BM, A_CH>(tid, abase, plan_a, k_left, ra);
-        load_prep<TERMS, BN>(bbase, plan_b, rb);
+        load_prep<TERMS, BN>(tid, bbase, rb);
     };
     auto stash = [&]() {
         store_rows<TERMS, BM, A_CH>(tid, ra, sa);
         store_prep<TERMS, BN>(tid, rb, sb);
     };
     // Half steps that hold padding only are left out: at most 16 values left means that only the first half multiplies.
-    // (K = 2 x 100, N = 256 over 2,449,029 rows: 2.04 ms for all of 2 x 128, 1.92 now.)
+    // (K = 2 x 100, N = 256 over 2,449,029 rows: 2.04 ms for all of 2 x 128, 1.92 without, both with two workgroups resident.)
     auto compute = [&](int32_t t) {
         const int32_t left = t < tiles1 ? g.k - t * BK : g.k2 - (t - tiles1) * BK;
 #pragma unroll
