@@ -242,9 +242,11 @@ def main():
             if w.dtype == "bf16":
                 peak = MFMA_BF16_PEAK_TFLOPS
             else:
-                # fp32 products from bf16 terms: 6 (3) bf16 matrix instructions per algorithmic product-sum
+                # fp32 products from 16-bit terms, matrix instructions per algorithmic product-sum: the transform 6 (3) from
+                # three (two) bf16 terms, the gradients 3 from two fp16 terms (the same rate)
                 terms = 3 if args.matmul_terms is None else args.matmul_terms
-                peak = {0: MFMA_FP32_PEAK_TFLOPS, 3: MFMA_BF16_PEAK_TFLOPS / 6, 2: MFMA_BF16_PEAK_TFLOPS / 3}[terms]
+                instructions = 6 if terms == 3 and name == "gemm_fwd" else 3
+                peak = MFMA_BF16_PEAK_TFLOPS / instructions if terms else MFMA_FP32_PEAK_TFLOPS
             entry.update(bound="mfma", achieved=ach, peak=peak, unit="TFLOP/s", frac=ach / peak)
         else:
             ach = p["bytes"] / p["ms"] / 1e6

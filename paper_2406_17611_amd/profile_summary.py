@@ -46,7 +46,8 @@ def _short(name: str) -> str:
 
 def _kernel_class(n: str):
     """bench.py's kernel class of a kernel name (None for kernels outside the memory-bound classes)."""
-    for prefix, c in (("spmm_kernel", "agg_fwd"), ("node_sum_kernel", "agg_bwd_local"), ("halo_products_kernel", "agg_bwd_halo"),
+    for prefix, c in (("spmm_kernel", "agg_fwd"), ("node_sum_kernel", "agg_bwd_local"),
+                      ("narrow_backward_kernel", "agg_bwd_local"), ("halo_products_kernel", "agg_bwd_halo"),
                       ("codec_rows_kernel", "compress"), ("whole_rows_kernel", "compress"), ("compress_kernel", "compress")):
         if n.startswith(prefix):
             return c
@@ -133,10 +134,11 @@ def summarise(workload: str, out_dir: str) -> dict:
             if c:
                 per_class[c][0] += sum(fetch[n]) * 1024 / sf
                 per_class[c][1] += sum(write[n]) * 1024 / sw if n in write else 0.0
-                if not (n.startswith("node_sum_kernel") and n.endswith("true>")):      # second kernel of the same call
+                if not (n.startswith(("node_sum_kernel", "narrow_backward_kernel")) and n.endswith("true>")):      # second kernel of the same call
                     per_class[c][2] += len(fetch[n])
         f.write("\n(spmm_kernel: forward aggregation, all layers; node_sum_kernel: backward aggregation by node, in a second "
-                "launch (<..., true>) the hub nodes whose pieces the first one summed. Launches of one class are averaged together.)\n")
+                "launch (<..., true>) the hub nodes whose pieces the first one summed; narrow_backward_kernel: the same for the class layer, at the "
+                "width of its outputs. Launches of one class are averaged together.)\n")
 
     path = os.path.join(prof_dir, "hbm_traffic.json")
     try:
