@@ -509,9 +509,19 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_small_k_kernel(const T* __re
     }
 }
 
+// Short reductions of fp32 storage that go to kernels_gemm_half.hip, like long ones. It spends half the matrix instructions and splits
+// a value once per 128 columns; the persistent kernel for short reductions is ahead where its tiles of rows are many and a third stage would be
+// half empty, and below 17 steps, where the rounding of two fp16 terms does not average out. us, short / half, masked: 2,000 x 40 x 256
+// 12.1 / 8.0, 16,000 x 64 x 256 17.1 / 8.8, 60,013 x 24 x 128 16.4 / 10.1, 169,343 x 47 x 256 48.4 / 47.9, x 64 x 128 46.6 / 31.1,
+// 1,200,000 x 24 x 128 168 / 159, x 64 x 256 396 / 384, but x 40 x 256 334 / 362.
+bool half_takes_short(const GemmArgs& ga) {
+    return ga.a.dtype == VARCO_F32 && ga.f32_terms != 0 && ga.k > 16 && (ga.k <= 32 || ga.k > 48 || ga.m <= 300'000);
+}
+
 // A [m x k] with k contiguous and rows densely stored, B = fp32 weights stored [n x k], no chained product,
 // no split, no activation.
 bool small_k_usable(const GemmArgs& ga) {
+    if (half_takes_short(ga)) return false;
     const uintptr_t pa = reinterpret_cast<uintptr_t>(ga.a.ptr), pg = reinterpret_cast<uintptr_t>(ga.a.gate);
     const uintptr_t es = ga.a.dtype == VARCO_BF16 ? 2 : 4;
     const bool same_skew = !ga.a.gate || (pa & 15u) == (pg & 15u);     // A and its mask are read with the same chunking

@@ -711,7 +711,7 @@ hipError_t varco_launch_gemm_short_k(const GemmArgs& ga, int terms, hipStream_t 
     const int64_t tiles = (ga.m + kShortRows - 1) / kShortRows, others = int64_t((ga.n + 255) / 256) * (ga.c_dual ? 2 : 1);
     const dim3 grid(unsigned(std::min<int64_t>(tiles, std::max<int64_t>(1, 512 / others))), unsigned((ga.n + 255) / 256), ga.c_dual ? 2 : 1);
     const int ks = (ga.k + 15) / 16;
-    if (ks < 1 || ks > 4) return hipErrorInvalidValue;
+    if (ks < 1 || ks > 4 || (ga.a.dtype == VARCO_F32 && ks % 2 == 0)) return hipErrorInvalidValue;
     auto go = [&](auto type, auto ksc, auto gt, auto tc) {
         using T = typename decltype(type)::type;
         hipLaunchKernelGGL((gemm_short_k_kernel<T, decltype(ksc)::value, decltype(gt)::value, decltype(tc)::value>), grid,
@@ -720,11 +720,11 @@ hipError_t varco_launch_gemm_short_k(const GemmArgs& ga, int terms, hipStream_t 
                            ga.accumulate ? 1 : 0, static_cast<const float*>(ga.b_dual), static_cast<T*>(ga.c_dual));
     };
     auto with_ks = [&](auto type, auto gt, auto tc) {
-        switch (ks) {
-            case 1: go(type, std::integral_constant<int, 1>{}, gt, tc); break;
-            case 2: go(type, std::integral_constant<int, 2>{}, gt, tc); break;
-            case 3: go(type, std::integral_constant<int, 3>{}, gt, tc); break;
-            default: go(type, std::integral_constant<int, 4>{}, gt, tc); break;
+        if (ks == 1) return go(type, std::integral_constant<int, 1>{}, gt, tc);
+        if (ks == 3) return go(type, std::integral_constant<int, 3>{}, gt, tc);
+        if constexpr (sizeof(typename decltype(type)::type) == 2) {      // (the others of fp32 storage go to kernels_gemm_half.hip)
+            if (ks == 2) return go(type, std::integral_constant<int, 2>{}, gt, tc);
+            return go(type, std::integral_constant<int, 4>{}, gt, tc);
         }
     };
     auto with_gate = [&](auto type, auto tc) {

@@ -48,6 +48,12 @@ def test_input_gradient_rows_of_any_magnitude(fo, growth):
     assert (err <= _bound(fo, dz, h.astype(np.float64).T)).all()
 
 
+@pytest.mark.parametrize("fo", [17, 24, 32, 33, 47, 48, 49, 64])
+@pytest.mark.parametrize("growth", [0, 7, 12])
+def test_short_input_gradient_rows_of_any_magnitude(fo, growth):
+    test_input_gradient_rows_of_any_magnitude(fo, growth)      # one stage or two, with a remainder or none
+
+
 @pytest.mark.parametrize("fi,fo", [(4, 4), (75, 47), (64, 65), (130, 136)])
 @pytest.mark.parametrize("growth", [0, 7])
 @pytest.mark.parametrize("n", [1, 31, 33, 2333])
