@@ -350,10 +350,10 @@ __global__ __launch_bounds__(kThreads, 3) void gemm_split_kernel(SplitGemm g) {
     }
 }
 
-
 // ---------------------------------------------------------------------------------------------------------
 // Short reductions on the bf16 matrix units: C (+)= A B^T with at most 64 reduction steps and densely stored
-// rows of A (the input gradient of the last layer: the reduction runs over the classes). Rows of, say, 47
+// rows of A (an input gradient that reduces over few outputs; fp32 storage with 17 steps and more mostly goes to kernels_gemm_half.hip,
+// half_takes_short). Rows of, say, 47
 // elements are not 16-byte aligned, so a workgroup takes tiles of 64 rows of A, each one contiguous range of memory,
 // with 16-byte loads, masks the values, expands them into TERMS bf16 terms once and writes them to LDS as rows of matrix
 // operands (16 bytes of padding per row). Each wavefront owns 64 columns of C: their weights, expanded alike, sit in registers
@@ -361,7 +361,7 @@ __global__ __launch_bounds__(kThreads, 3) void gemm_split_kernel(SplitGemm g) {
 // current one is multiplied. The blocks are formed transposed (weights as the first matrix operand): a lane then holds four
 // consecutive columns of a row, and a block of 32 rows leaves through LDS in whole lines.
 // Bound by writing C. (One tile of 128 rows per workgroup, its values expanded by each wavefront from fp32 rows in LDS, which
-// lay in few banks when the number of classes was a multiple of 8: 169,343 x 256 from 40 classes 77 us, 57 now; 2,449,029
+// lay in few banks when the number of classes was a multiple of 8: 169,343 x 256 from 40 outputs 77 us, 57 now; 2,449,029
 // x 2 x 256 from 47: 1.96 ms, 1.40 now.)
 // With fp32 matrix instructions (still used when the context asks for them) the product is bound by those. TERMS = 1: bf16
 // storage (the values are bf16 already; the weights are rounded to bf16 as for the other products of that storage type).
