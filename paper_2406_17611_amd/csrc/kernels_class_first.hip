@@ -156,12 +156,13 @@ __global__ __launch_bounds__(kBlock) void narrow_fixup_kernel(const SpmmSplit* s
     if (c < fo) Elem<bf16_t>::store(out + int64_t(sp.row) * fo + c, x);
 }
 
-// G_loc[row] and G_z[zrow of row] (zeros beyond fo). SPLIT = false: partial sums of the pieces of long ranges (the launch's
-// first wavefronts) and the nodes without pieces; SPLIT = true: the others, from the partial sums.
+// G_loc[row] and G_z[zrow of row] (zeros beyond fo), rows g_ld apart. SPLIT = false: partial sums of the pieces of long ranges (the
+// launch's first wavefronts) and the nodes without pieces; SPLIT = true: the others, from the partial sums. bf16 rows of 2 ROW elements
+// hold a sum as two terms, x = g[c] + g[ROW + c]: 16 of its bits.
 template <typename T, int ROW, bool SPLIT>
 __global__ __launch_bounds__(kBlock) void narrow_backward_kernel(const NodeItem* nodes, int32_t n, const SpmmItem* pieces, int32_t n_pieces,
                                                                  const uint2* t_local, const uint2* t_cross, const T* dz, int32_t ld,
-                                                                 const int32_t* zrow_of, T* g_loc, T* g_z, int32_t fo, float* partial) {
+                                                                 const int32_t* zrow_of, T* g_loc, T* g_z, int32_t g_ld, int32_t fo, float* partial) {
     const int lane = threadIdx.x & 63, c = my_column<T, ROW>(lane);
     const int32_t cols = min(ld, ROW);                 // rows that are not padded have no more
     int32_t idx = blockIdx.x * kWaves + __builtin_amdgcn_readfirstlane(int32_t(threadIdx.x >> 6));
@@ -184,9 +185,16 @@ __global__ __launch_bounds__(kBlock) void narrow_backward_kernel(const NodeItem*
             x = narrow_sum<T, ROW>(dz, ld, cols, e0, e1, lane, [&](int32_t e) { return pairs[e]; });
         return c < fo ? x : 0.f;
     };
+    auto put = [&](T* at, float x) {
+        Elem<T>::store(at, x);
+        if constexpr (sizeof(T) == 2) {
+            const float high = bf16_to_float(float_to_bf16(x));
+            if (g_ld > ROW) Elem<T>::store(at + ROW, fabsf(high) < __builtin_inff() ? x - high : 0.f);      // (infinities and NaN are the first term's)
+        }
+    };
     const int32_t zr = zrow_of[it.row];
-    Elem<T>::store(g_loc + int64_t(it.row) * ROW + c, range(t_local, it.l0, it.l1, it.flags & VARCO_NODE_LOCAL_SPLIT));
-    if (g_z && zr >= 0) Elem<T>::store(g_z + int64_t(zr) * ROW + c, range(t_cross, it.c0, it.c1, it.flags & VARCO_NODE_CROSS_SPLIT));
+    put(g_loc + int64_t(it.row) * g_ld + c, range(t_local, it.l0, it.l1, it.flags & VARCO_NODE_LOCAL_SPLIT));
+    if (g_z && zr >= 0) put(g_z + int64_t(zr) * g_ld + c, range(t_cross, it.c0, it.c1, it.flags & VARCO_NODE_CROSS_SPLIT));
 }
 
 // Rows of fo elements -> rows of ROW elements, zeros beyond fo. A thread writes 16 bytes; a piece that crosses a row's end is loaded
@@ -225,17 +233,21 @@ __global__ __launch_bounds__(kBlock) void pad_rows_kernel(const T* __restrict__ 
 // places of the one after it, are on their way meanwhile. Bound by writing dX: 2,449,029 x 512 from 47 outputs 606 us (rows of the
 // result first, four wavefronts of 128 positions, the rule worked out for each element: 1,530), 169,343 x 512 from 40 47 us (104).
 constexpr int kWide = 512, kMaxWidth = 512, kTile = 64, kPitchG = P + 8, kStrip = 64 + 8;
+template <int TERMS>
 struct alignas(16) ClassLds {
+    static constexpr int BUFS = 3 - TERMS;        // as many as leave room for two workgroups
     uint16_t strips[kWide / 64][32 * kStrip];
-    uint16_t g[2][2][kTile * kPitchG];            // [buffer][G_loc, G_z]
-    uint2 rows_ab[2][kTile];                      // {a_inv, b}; a_inv = 0: every position kept (nothing came back, or everything)
+    uint16_t g[BUFS][2 * TERMS][kTile * kPitchG];      // [buffer][terms of G_loc, of G_z]
+    uint2 rows_ab[BUFS][kTile];                   // {a_inv, b}; a_inv = 0: every position kept (nothing came back, or everything)
 };
+template <int TERMS>
 __global__ __launch_bounds__(kWide, 4) void class_dgrad_kernel(const uint16_t* __restrict__ g_loc, const uint16_t* __restrict__ g_z,
                                                                const int32_t* __restrict__ zrow_of, const int32_t* __restrict__ bgid, int32_t n,
                                                                MaskRule rule, int32_t fo, const uint16_t* __restrict__ wr, int32_t cpitch,
                                                                uint16_t* __restrict__ dx) {
     extern __shared__ __attribute__((aligned(16))) char class_lds[];
-    ClassLds& lds = *reinterpret_cast<ClassLds*>(class_lds);
+    using Lds = ClassLds<TERMS>;
+    Lds& lds = *reinterpret_cast<Lds*>(class_lds);
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(int32_t(threadIdx.x >> 6)), lrow = lane & 31, lk = lane >> 5;
     const int32_t width = int32_t(rule.width);
     const int ksteps = (fo + 15) / 16;
@@ -256,21 +268,30 @@ __global__ __launch_bounds__(kWide, 4) void class_dgrad_kernel(const uint16_t* _
     const int32_t n_tiles = (n + kTile - 1) / kTile, step = int32_t(gridDim.x);
     const int fr = threadIdx.x >> 3, fc = (threadIdx.x & 7) * 8;      // this thread's 16-byte piece of a tile of G: row, first column
     auto row_of = [&](int32_t t) { return min(t * kTile + fr, n - 1); };
-    uint4 nl, nz;
+    uint4 nl, nz, nl2, nz2;                       // (the last two: second terms)
     int32_t nzr = -1, ngid = 0;
     int32_t after = g_z && int32_t(blockIdx.x) < n_tiles ? zrow_of[row_of(blockIdx.x)] : -1;
     auto fetch = [&](int32_t t) {
         nzr = after;
-        nl = *reinterpret_cast<const uint4*>(g_loc + int64_t(row_of(t)) * P + fc);
-        nz = make_uint4(0u, 0u, 0u, 0u);
-        if (nzr >= 0) nz = *reinterpret_cast<const uint4*>(g_z + int64_t(nzr) * P + fc), ngid = bgid[nzr];
+        const uint16_t* const gl = g_loc + int64_t(row_of(t)) * (TERMS * P) + fc;
+        nl = *reinterpret_cast<const uint4*>(gl), nz = make_uint4(0u, 0u, 0u, 0u);
+        if constexpr (TERMS == 2) nl2 = *reinterpret_cast<const uint4*>(gl + P), nz2 = nz;
+        if (nzr >= 0) {
+            const uint16_t* const gz = g_z + int64_t(nzr) * (TERMS * P) + fc;
+            nz = *reinterpret_cast<const uint4*>(gz), ngid = bgid[nzr];
+            if constexpr (TERMS == 2) nz2 = *reinterpret_cast<const uint4*>(gz + P);
+        }
         if (g_z && t + step < n_tiles) after = zrow_of[row_of(t + step)];
     };
     if (int32_t(blockIdx.x) < n_tiles) fetch(blockIdx.x);
     int buf = 0;
-    for (int32_t t = blockIdx.x; t < n_tiles; t += step, buf ^= 1) {      // (a buffer is written again behind the next tile's barrier)
+    for (int32_t t = blockIdx.x; t < n_tiles; t += step, buf ^= Lds::BUFS - 1) {      // (of two buffers, one is written again behind the next tile's barrier)
         *reinterpret_cast<uint4*>(&lds.g[buf][0][fr * kPitchG + fc]) = nl;
-        *reinterpret_cast<uint4*>(&lds.g[buf][1][fr * kPitchG + fc]) = nz;
+        *reinterpret_cast<uint4*>(&lds.g[buf][TERMS][fr * kPitchG + fc]) = nz;
+        if constexpr (TERMS == 2) {
+            *reinterpret_cast<uint4*>(&lds.g[buf][1][fr * kPitchG + fc]) = nl2;
+            *reinterpret_cast<uint4*>(&lds.g[buf][3][fr * kPitchG + fc]) = nz2;
+        }
         if (fc == 0) {
             uint2 ab = make_uint2(0u, 0u);
             if (nzr >= 0 && rule.k < rule.width) {
@@ -281,8 +302,7 @@ __global__ __launch_bounds__(kWide, 4) void class_dgrad_kernel(const uint16_t* _
         }
         __syncthreads();
         if (t + step < n_tiles) fetch(t + step);
-        if (first >= width) continue;
-        for (int rb = wave / groups; rb < kTile / 32; rb += 8 / groups) {
+        for (int rb = wave / groups; rb < kTile / 32 && first < width; rb += 8 / groups) {
             const int32_t row0 = t * kTile + rb * 32, rows = min(32, n - row0);
             if (rows <= 0) break;
             const uint2 ab = lds.rows_ab[buf][rb * 32 + lrow];
@@ -298,8 +318,11 @@ __global__ __launch_bounds__(kWide, 4) void class_dgrad_kernel(const uint16_t* _
                 for (int s = 0; s < 4; ++s)
                     if (s < ksteps) {
                         const int at = (rb * 32 + lrow) * kPitchG + 16 * s + 8 * lk;
-                        al = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[b][s], frag(&lds.g[buf][0][at]), al, 0, 0, 0);
-                        az = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[b][s], frag(&lds.g[buf][1][at]), az, 0, 0, 0);
+#pragma unroll
+                        for (int m = 0; m < TERMS; ++m) {
+                            al = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[b][s], frag(&lds.g[buf][m][at]), al, 0, 0, 0);
+                            az = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[b][s], frag(&lds.g[buf][TERMS + m][at]), az, 0, 0, 0);
+                        }
                     }
                 // accumulator register v of a lane is position 8 * (v / 4) + 4 * (lane / 32) + v % 4 of row lane % 32
 #pragma unroll
@@ -325,6 +348,7 @@ __global__ __launch_bounds__(kWide, 4) void class_dgrad_kernel(const uint16_t* _
                             *reinterpret_cast<const uint4*>(strip + (sr + 8 * i) * kStrip + sc);
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         }
+        if constexpr (Lds::BUFS == 1) __syncthreads();
     }
 }
 
@@ -585,48 +609,55 @@ hipError_t varco_launch_narrow_forward(const SpmmPlan& plan, const VarcoEdge* ed
 namespace {
 template <typename T, int ROW>
 hipError_t narrow_backward(const NodePlan& plan, const uint2* t_local, const uint2* t_cross, const void* dz, int64_t rows, const int32_t* zrow_of,
-                           void* dz_padded, void* g_loc, void* g_z, int32_t fo, float* partial, hipStream_t stream) {
+                           void* dz_padded, void* g_loc, void* g_z, int32_t g_ld, int32_t fo, float* partial, hipStream_t stream) {
     const T* const src = static_cast<const T*>(dz_padded);
     const int32_t ld = dz_padded == dz ? fo : ROW;
     if (dz_padded != dz)
         hipLaunchKernelGGL((pad_rows_kernel<T, ROW>), dim3(unsigned(std::min<int64_t>((rows * ROW / Columns<T>::N + kBlock - 1) / kBlock, 256 * 32))), dim3(kBlock), 0, stream,
                            static_cast<const T*>(dz), rows, fo, static_cast<T*>(dz_padded));
     hipLaunchKernelGGL((narrow_backward_kernel<T, ROW, false>), waves_for(int64_t(plan.n_pieces) + plan.n_whole), dim3(kBlock), 0, stream, plan.nodes,
-                       plan.n_whole, plan.pieces, plan.n_pieces, t_local, t_cross, src, ld, zrow_of, static_cast<T*>(g_loc), static_cast<T*>(g_z), fo, partial);
+                       plan.n_whole, plan.pieces, plan.n_pieces, t_local, t_cross, src, ld, zrow_of, static_cast<T*>(g_loc), static_cast<T*>(g_z), g_ld, fo, partial);
     if (plan.n_nodes > plan.n_whole)
         hipLaunchKernelGGL((narrow_backward_kernel<T, ROW, true>), waves_for(plan.n_nodes - plan.n_whole), dim3(kBlock), 0, stream,
                            plan.nodes + plan.n_whole, plan.n_nodes - plan.n_whole, plan.pieces, 0, t_local, t_cross, src, ld, zrow_of,
-                           static_cast<T*>(g_loc), static_cast<T*>(g_z), fo, partial);
+                           static_cast<T*>(g_loc), static_cast<T*>(g_z), g_ld, fo, partial);
     return hipGetLastError();
 }
 }  // namespace
 
 hipError_t varco_launch_narrow_backward(int dtype, const NodePlan& plan, const uint2* t_local, const uint2* t_cross, const void* dz, int64_t rows,
-                                        const int32_t* zrow_of, void* dz_padded, void* g_loc, void* g_z, int32_t fo, float* partial,
+                                        const int32_t* zrow_of, void* dz_padded, void* g_loc, void* g_z, bool two_terms, int32_t fo, float* partial,
                                         hipStream_t stream, const LaunchTag& tag) {
     if (plan.n_nodes == 0) return hipSuccess;
+    if (two_terms && dtype != VARCO_BF16) return hipErrorInvalidValue;
     tag.begin(stream);
-    auto go = [&](auto fn) { return fn(plan, t_local, t_cross, dz, rows, zrow_of, dz_padded, g_loc, g_z, fo, partial, stream); };
+    const int32_t g_ld = varco_class_pitch(dtype, fo) * (two_terms ? 2 : 1);
+    auto go = [&](auto fn) { return fn(plan, t_local, t_cross, dz, rows, zrow_of, dz_padded, g_loc, g_z, g_ld, fo, partial, stream); };
     const hipError_t e = dtype == VARCO_BF16 ? go(narrow_backward<bf16_t, 64>) : varco_class_pitch(dtype, fo) == 32 ? go(narrow_backward<float, 32>) : go(narrow_backward<float, 64>);
     tag.end(stream);
     return e;
 }
 
-hipError_t varco_launch_class_dgrad(const void* g_loc, const void* g_z, const int32_t* zrow_of, const int32_t* bgid, int64_t rows,
+hipError_t varco_launch_class_dgrad(const void* g_loc, const void* g_z, bool two_terms, const int32_t* zrow_of, const int32_t* bgid, int64_t rows,
                                     const MaskRule& rule, int32_t fo, const void* wr, int32_t cpitch, void* dx, hipStream_t stream,
                                     const LaunchTag& tag) {
     if (rows == 0) return hipSuccess;
     if (rule.width % 16 != 0 || rule.width > uint32_t(kMaxWidth) || fo > P || cpitch < fo || cpitch % 8 != 0 || (reinterpret_cast<uintptr_t>(dx) & 15u))
         return hipErrorInvalidValue;
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(class_dgrad_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, int(sizeof(ClassLds)));
-    if (e != hipSuccess) return e;
-    tag.begin(stream);
-    const int64_t tiles = (rows + kTile - 1) / kTile;
-    hipLaunchKernelGGL(class_dgrad_kernel, dim3(unsigned(std::min<int64_t>(tiles, 512))), dim3(kWide), sizeof(ClassLds), stream, static_cast<const uint16_t*>(g_loc),
-                       static_cast<const uint16_t*>(g_z), zrow_of, bgid, int32_t(rows), rule, fo, static_cast<const uint16_t*>(wr), cpitch,
-                       static_cast<uint16_t*>(dx));
-    tag.end(stream);
-    return hipGetLastError();
+    auto go = [&](auto terms) {
+        using Lds = ClassLds<decltype(terms)::value>;
+        const auto kernel = class_dgrad_kernel<decltype(terms)::value>;
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, int(sizeof(Lds)));
+        if (e != hipSuccess) return e;
+        tag.begin(stream);
+        const int64_t tiles = (rows + kTile - 1) / kTile;
+        hipLaunchKernelGGL(kernel, dim3(unsigned(std::min<int64_t>(tiles, 512))), dim3(kWide), sizeof(Lds), stream, static_cast<const uint16_t*>(g_loc),
+                           static_cast<const uint16_t*>(g_z), zrow_of, bgid, int32_t(rows), rule, fo, static_cast<const uint16_t*>(wr), cpitch,
+                           static_cast<uint16_t*>(dx));
+        tag.end(stream);
+        return hipGetLastError();
+    };
+    return two_terms ? go(std::integral_constant<int, 2>{}) : go(std::integral_constant<int, 1>{});
 }
 
 hipError_t varco_launch_class_dgrad_f32(const void* g_loc, const void* g_z, const void* dz, int32_t dz_ld, const int32_t* zrow_of, const int32_t* bgid, int64_t rows,

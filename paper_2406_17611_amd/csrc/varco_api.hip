@@ -324,7 +324,7 @@ void transform_first_need(const varco_ctx* ctx, size_t* rows_out, size_t* record
     *rows_out = fo ? (size_t(rows) * size_t(fo) * size_t(ctx->elem_bytes()) + 3) / 4 : 0;
     *records_out = fo ? size_t(halo) * 2 : 0;
     if (fo && ctx->net.linked) {     // all partitions at once
-        *rows_out = std::max(*rows_out, class_block_floats(ctx));
+        *rows_out = std::max(*rows_out, class_block_floats(ctx, false));
         *records_out = std::max(*records_out, size_t(ctx->net.boundary) * 2);
     }
 }
@@ -350,7 +350,8 @@ int32_t size_workspace(varco_ctx* ctx, Workspace& ws) {
     bool narrow = false;
     for (int32_t l = 0; l < ctx->n_layers; ++l) narrow = narrow || (ctx->net.linked && narrow_sums_possible(ctx, l));
     // (an option like the products: without these rows errors are summed at the width of the inputs)
-    if (!narrow || class_block_floats(ctx) <= tf_rows || grow(ws, ws.tf, ws.tf_elems, class_block_floats(ctx)) != hipSuccess) {
+    const size_t sums = class_block_floats(ctx, ctx->dtype == VARCO_BF16);
+    if (!narrow || sums <= tf_rows || grow(ws, ws.tf, ws.tf_elems, sums) != hipSuccess) {
         (void)hipGetLastError();
         VARCO_HIP(ctx, grow(ws, ws.tf, ws.tf_elems, tf_rows));
     }
@@ -363,8 +364,9 @@ bool narrow_sums_possible(const varco_ctx* ctx, int32_t l) {
     const bool kernels = ctx->dtype == VARCO_BF16 ? fi % 16 == 0 && fi <= 512 : ctx->f32_terms == 3;
     return l > 0 && kernels && ctx->layers[l].order == VARCO_ORDER_AGGREGATE_FIRST && ctx->act[l] == VARCO_ACT_IDENTITY && fo <= kClassPitch && fo < fi;
 }
-size_t class_block_floats(const varco_ctx* ctx) {
-    return size_t(2 * ctx->net.rows + ctx->net.boundary) * kClassPitch * size_t(ctx->elem_bytes()) / 4;
+size_t class_block_floats(const varco_ctx* ctx, bool two_terms) {
+    const size_t rows = size_t(ctx->net.rows), sums = rows + size_t(ctx->net.boundary);
+    return (rows + (two_terms ? 2 * sums : sums)) * kClassPitch * size_t(ctx->elem_bytes()) / 4;
 }
 
 int32_t size_all_workspaces(varco_ctx* ctx) {

@@ -131,9 +131,9 @@ void free_network(NetState& net);
 // Floats of a workspace's product buffer that the calls on all partitions ask for at the current ratios, and at most at any.
 size_t network_prod_need(const varco_ctx* ctx, size_t* most);
 // Whether the input gradient of layer l can be formed from errors summed at the width of its outputs, and the workspace's
-// floats for the rows of a class layer over all partitions: [Y ; Y_z], or dZ, G_loc and G_z.
+// floats for the rows of a class layer over all partitions: [Y ; Y_z], or dZ, G_loc and G_z (two_terms: each sum as two bf16 numbers).
 bool narrow_sums_possible(const varco_ctx* ctx, int32_t l);
-size_t class_block_floats(const varco_ctx* ctx);
+size_t class_block_floats(const varco_ctx* ctx, bool two_terms);
 enum GemmKind { kGemmF32 = 0, kGemmBf16 = 1, kGemmExpanded = 2 };     // kGemmBf16: as weight gradients
 int32_t gemm_split_for(int32_t m, int32_t n, int64_t k, int kind);
 int32_t plain_bf16_split(int32_t m, int32_t n, int64_t k);      // the same for bf16 in tiles of 256 x 128, two workgroups per compute unit

@@ -305,11 +305,12 @@ inline int32_t varco_class_pitch(int dtype, int32_t fo) { return dtype == VARCO_
 hipError_t varco_launch_narrow_forward(const SpmmPlan& plan, const VarcoEdge* edge, const float* vals, const void* y, int32_t rows, void* out,
                                        int32_t fo, float* partial, hipStream_t stream, const LaunchTag& tag);
 // g_z may be null (nothing exchanged). dz: rows x fo; dz_padded: the same with rows of varco_class_pitch, made here, or dz itself where
-// its rows are whole aligned 16-byte pieces; g_loc: rows x varco_class_pitch; partial: kClassPitch floats per piece.
+// its rows are whole aligned 16-byte pieces; g_loc, g_z: rows of varco_class_pitch, or (bf16) of twice that with every sum in two terms;
+// partial: kClassPitch floats per piece.
 hipError_t varco_launch_narrow_backward(int dtype, const NodePlan& plan, const uint2* t_local, const uint2* t_cross, const void* dz, int64_t rows,
-                                        const int32_t* zrow_of, void* dz_padded, void* g_loc, void* g_z, int32_t fo, float* partial,
+                                        const int32_t* zrow_of, void* dz_padded, void* g_loc, void* g_z, bool two_terms, int32_t fo, float* partial,
                                         hipStream_t stream, const LaunchTag& tag);
-hipError_t varco_launch_class_dgrad(const void* g_loc, const void* g_z, const int32_t* zrow_of, const int32_t* bgid, int64_t rows,
+hipError_t varco_launch_class_dgrad(const void* g_loc, const void* g_z, bool two_terms, const int32_t* zrow_of, const int32_t* bgid, int64_t rows,
                                     const MaskRule& rule, int32_t fo, const void* wr, int32_t cpitch, void* dx, hipStream_t stream,
                                     const LaunchTag& tag);
 // The same for fp32 storage from the weights as they are; with h0 and dz (rows dz_ld apart, whole 16-byte pieces) dX takes the self tap dZ H0^T as well.
