@@ -192,7 +192,7 @@ int32_t varco_advance_step(varco_ctx* ctx, varco_stream stream);
  * has the accuracy of fp32 arithmetic at well under half the cost. In the gradients (the input gradient of more than 64
  * outputs) each operand is scaled by a power of two and written as two fp16 numbers, 22 to 23 of its bits, three products, with sums
  * that are rounded less often: less error than the former at under two thirds of its cost. Values more than 2^22 below the largest of their row (weight gradients: of
- * 64 columns of a slab of rows) are within 2^-44 of that one. terms = 0: fp32 matrix instructions
+ * their own column of y or dz) are within 2^-44 of that one. terms = 0: fp32 matrix instructions
  * throughout (also used, whatever the setting, for shapes the expanded forms do not take: transforms whose reduction length is
  * no multiple of 4, gradients with fewer than 4 rows or columns). terms = 2: transforms and input gradients of at most 64 outputs
  * from two bf16 terms, three products, relative error about 2^-16 per product (a

@@ -13,10 +13,12 @@
 // 2.1e-6 / 8.3e-7; alike with rectified values and with values over 12 or 20 binades. What the rounding of the accumulators leaves is
 // below zero on average, so every second slab of a weight gradient multiplies -B (its scale is negative) and changes sign in the epilogue.
 // Scales: the largest value of a row of the weights' copy is brought to [2^14, 2^15) when it is made. Rows of A
-// (and 64 columns at a time in weight gradients) are scaled as they arrive, by what brings the largest value of the first stage to
+// (in weight gradients the columns of both operands) are scaled as they arrive, by what brings the largest value of the first stage to
 // [2^8, 2^9); a later stage that exceeds that more than 64-fold takes a smaller scale, and the sums so far follow it (a power of two:
-// exact). Values down to 2^-22 of the largest keep all bits of both terms, below that the error is 2^-44 of the largest. An infinity or
-// NaN makes NaN of every output it meets.
+// exact). Values down to 2^-22 of the largest that they are summed with keep all bits of both terms, below that the error is 2^-44 of that
+// one. An infinity or NaN makes NaN of every output it meets. (One scale for 64 columns of a weight gradient, a single maximum per
+// wavefront, lost the gradients of columns far smaller than their neighbours - features of different units: 2^-31 of the largest, relative
+// error 1.7e-4.)
 //
 // A workgroup of four wavefronts computes a 128 x 128 tile of C (128 x 64 for outputs at most 64 columns wide), a
 // wavefront 64 x 64 (32 x 64); two workgroups are resident per compute unit. A stage of 32
@@ -90,15 +92,6 @@ __device__ __forceinline__ float largest_of_lanes(float x) {
     x = max_moved<0x4E>(max_moved<0xB1>(x));           // quad_perm: lane xor 1, lane xor 2
     return LANES == 8 ? max_moved<0x141>(x) : x;       // row_half_mirror
 }
-// Largest value of a wavefront, uniform.
-__device__ __forceinline__ float largest_of_wave(float x) {
-    x = max_moved<0x121>(max_moved<0x122>(max_moved<0x124>(max_moved<0x128>(x))));       // of 16 lanes: row_ror 8, 4, 2, 1
-    // (not negative: the order of the values is that of their bits, and the scalar unit finishes; a NaN, which is above all, has been
-    // dropped before)
-    auto lane = [&](int l) { return uint32_t(__builtin_amdgcn_readlane(int(__float_as_uint(x)), l)); };
-    return __uint_as_float(max(max(lane(0), lane(16)), max(lane(32), lane(48))));
-}
-
 __device__ __forceinline__ float4 gate4(float4 x, float4 y) {
     x.x = y.x > 0.f ? x.x : 0.f, x.y = y.y > 0.f ? x.y : 0.f;
     x.z = y.z > 0.f ? x.z : 0.f, x.w = y.w > 0.f ? x.w : 0.f;
@@ -302,34 +295,38 @@ __device__ __forceinline__ void load_cols(const float* base, const float* gate, 
     }
 }
 
-// Masks, scales, splits and writes a stage's block of 64 columns of one wavefront; e: its scale exponent, kept from stage to stage (126 before
-// the first value that is not zero). scale = {exponent, bits of the factor that the sums so far take}. Whether the scale got smaller.
+// Masks, scales, splits and writes a stage's block of four columns; e: their scale exponents, kept from stage to stage (126 before the
+// first value that is not zero). scales[column] = {exponent, bits of the factor that the sums so far take}; the four lanes that share
+// the columns agree. Whether a scale got smaller.
 template <int ROWS, bool GATE>
-__device__ __forceinline__ bool store_cols(const ColRegs<GATE>& r, int b, int32_t i0, int32_t extent, float sign, int& e, uint16_t* s, int2* scale) {
+__device__ __forceinline__ bool store_cols(const ColRegs<GATE>& r, int b, int32_t i0, int32_t extent, float sign, int (&e)[4], uint16_t* s, int2* scales) {
     const bool crosses = (extent & 3) && i0 + (b >> 2) * 4 == (extent & ~3);
-    float x[8][4], m = 0.f;
+    float x[8][4], m[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int kk = 0; kk < 8; ++kk) {
         float4 v = r.v[kk];
         if constexpr (GATE) v = gate4(v, r.g[kk]);
         if (extent & 3) v = crosses ? moved_up(v, 4 - (extent & 3)) : v;
         x[kk][0] = v.x, x[kk][1] = v.y, x[kk][2] = v.z, x[kk][3] = v.w;
-        m = largest4(m, v);
-    }
-    m = largest_of_wave(m);
-    if (__float_as_uint(m) >= 0x7F800000u) {                  // an infinity says nothing about the scale of the other columns
-        m = 0.f;
 #pragma unroll
-        for (int kk = 0; kk < 8; ++kk)
-#pragma unroll
-            for (int ii = 0; ii < 4; ++ii) m = fabsf(x[kk][ii]) < __builtin_inff() ? fmaxf(m, fabsf(x[kk][ii])) : m;
-        m = largest_of_wave(m);
+        for (int ii = 0; ii < 4; ++ii) m[ii] = fmaxf(m[ii], fabsf(x[kk][ii]));
     }
-    const int now = scale_exponent(m, kFirst), old = e;
-    const bool smaller = now < old - kRoom;
-    if (smaller) e = now;
-    if ((b & 63) == 0) *scale = make_int2(e, int(__float_as_uint(power_of_two(max(e - old, -126)))));
-    const float sc = sign * power_of_two(e);
+    bool grew = false;
+    int f[4];
+    float sc[4];
+#pragma unroll
+    for (int ii = 0; ii < 4; ++ii) {
+        const int now = scale_exponent(largest_of_lanes<4>(m[ii]), kFirst), old = e[ii];
+        const bool smaller = now < old - kRoom;
+        if (smaller) e[ii] = now;
+        grew = grew || smaller;
+        f[ii] = int(__float_as_uint(power_of_two(max(e[ii] - old, -126))));
+        sc[ii] = sign * power_of_two(e[ii]);
+    }
+    if ((b & 3) == 0) {
+        int4* const at = reinterpret_cast<int4*>(scales + (b >> 2) * 4);
+        at[0] = make_int4(e[0], f[0], e[1], f[1]), at[1] = make_int4(e[2], f[2], e[3], f[3]);
+    }
     uint16_t* base = s + (b >> 2) * 4 * kPitch + (b & 3) * 8;
     // An LDS row holds one output index with its 8 reduction steps contiguous, two steps per 32-bit word: the two
     // values split together are steps 2 q and 2 q + 1 of one output index, which is the transposition itself.
@@ -337,11 +334,11 @@ __device__ __forceinline__ bool store_cols(const ColRegs<GATE>& r, int b, int32_
     for (int ii = 0; ii < 4; ++ii) {                          // output index i + ii: its 8 reduction steps
         uint32_t hi[4], lo[4];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) split_pair(x[2 * q][ii] * sc, x[2 * q + 1][ii] * sc, hi[q], lo[q]);
+        for (int q = 0; q < 4; ++q) split_pair(x[2 * q][ii] * sc[ii], x[2 * q + 1][ii] * sc[ii], hi[q], lo[q]);
         *reinterpret_cast<uint4*>(base + ii * kPitch) = make_uint4(hi[0], hi[1], hi[2], hi[3]);
         *reinterpret_cast<uint4*>(base + ROWS * kPitch + ii * kPitch) = make_uint4(lo[0], lo[1], lo[2], lo[3]);
     }
-    return smaller;
+    return grew;
 }
 
 __device__ __forceinline__ halfx8 fragment(const uint16_t* s, int row, int koff) {
@@ -381,7 +378,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_half_kernel(HalfGemm g) {
     constexpr int BM = 32 * TMB * WM, BN = 32 * TNB * WN;
     static_assert(BM + BN <= kThreads, "one 8 x 4 block per thread in the TN layout");
     __shared__ __attribute__((aligned(16))) uint16_t smem[TERMS * (BM + BN) * kPitch];
-    __shared__ __attribute__((aligned(16))) int2 scales[BM];      // NT: of every row; TN: of 64 columns of A at a time, then of B
+    __shared__ __attribute__((aligned(16))) int2 scales[TN ? BM + BN : BM];      // NT: of every row; TN: of the columns of A, then of B
     __shared__ int32_t smaller_at;                                // last stage in which a scale got smaller
     const int tid = threadIdx.x;
     uint16_t* const sa = smem;
@@ -488,14 +485,20 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_half_kernel(HalfGemm g) {
         for (int i = 0; i < TMB; ++i)
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
-                float f;
-                if constexpr (TN)
-                    f = __uint_as_float(uint32_t(scales[(wm + i * 32) / 64].y)) * __uint_as_float(uint32_t(scales[BM / 64 + wn / 64].y));
-                else
-                    f = __uint_as_float(uint32_t(scales[wm + i * 32 + 8 * (v >> 2) + 4 * lk + (v & 3)].y));
+                const float f = __uint_as_float(uint32_t(scales[wm + i * 32 + 8 * (v >> 2) + 4 * lk + (v & 3)].y));
 #pragma unroll
                 for (int j = 0; j < TNB; ++j) acc[i][j][v] *= f, low[i][j][v] *= f;
             }
+        if constexpr (TN) {
+#pragma unroll
+            for (int j = 0; j < TNB; ++j) {
+                const float f = __uint_as_float(uint32_t(scales[BM + wn + j * 32 + lrow].y));
+#pragma unroll
+                for (int i = 0; i < TMB; ++i)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) acc[i][j][v] *= f, low[i][j][v] *= f;
+            }
+        }
     };
 
     // One LDS stage: a step's operands are fetched into registers while the previous step is multiplied, then
@@ -534,10 +537,9 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_half_kernel(HalfGemm g) {
                 else
                     load_cols<G, true, A>(base, gbase, b, col_off, ld_bytes, k_left, cr);
             };
-            int e = 126;
-            int2* const scale = scales + (A ? 0 : BM / 64) + (b >> 6);
+            int e[4] = {126, 126, 126, 126};
             pipeline(fetch_cols, [&](int32_t t) {
-                if (store_cols<A ? BM : BN, G>(cr, b, A ? m0 : n0, A ? g.m : g.n, A ? 1.f : sign, e, A ? sa : sb, scale)) smaller_at = t;
+                if (store_cols<A ? BM : BN, G>(cr, b, A ? m0 : n0, A ? g.m : g.n, A ? 1.f : sign, e, A ? sa : sb, A ? scales : scales + BM)) smaller_at = t;
             });
         };
         if (role == 0)
@@ -555,20 +557,12 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_half_kernel(HalfGemm g) {
     for (int i = 0; i < TMB; ++i) {
         int e[16];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            if constexpr (TN) {
-#pragma unroll
-                for (int v = 4 * q; v < 4 * q + 4; ++v) e[v] = scales[(wm + i * 32) / 64].x;
-            } else {
-#pragma unroll
-                for (int v = 0; v < 4; ++v) e[4 * q + v] = scales[wm + i * 32 + 8 * q + 4 * lk + v].x;
-            }
-        }
+        for (int v = 0; v < 16; ++v) e[v] = scales[wm + i * 32 + 8 * (v >> 2) + 4 * lk + (v & 3)].x;
 #pragma unroll
         for (int j = 0; j < TNB; ++j) {
             int eb;
             if constexpr (TN)
-                eb = scales[BM / 64 + wn / 64].x;
+                eb = scales[BM + wn + j * 32 + lrow].x;
             else
                 eb = reinterpret_cast<const int32_t*>(static_cast<const uint16_t*>(b_ptr) + g.exps)[n0 + wn + j * 32 + lrow];
 #pragma unroll

@@ -12,8 +12,8 @@ from paper_2406_17611_amd import synth
 pytestmark = pytest.mark.gpu
 
 
-def _context(fi, fo, rows=0):
-    ctx = vb.Context([fi, fo], [vb.ACT_RELU], vb.CONV_GCN, 1, KEY)
+def _context(fi, fo, rows=0, conv=vb.CONV_GCN):
+    ctx = vb.Context([fi, fo], [vb.ACT_RELU], conv, 1, KEY)
     if rows:                    # the partial products of a weight gradient are sized by a registered partition
         g = synth.small_random_graph(max(rows, 8), 3.0, "gcn", seed=5)
         host = vb.partition_build(g.n, g.rowptr, g.colidx, g.vals, np.zeros(g.n, dtype=np.int32), 1)
@@ -72,6 +72,36 @@ def test_weight_gradient_of_growing_values(n, growth, fi, fo):
     # a value far below the largest of its 64 columns and slab is within 2^-42 of that one
     floor = 2.0 ** -42 * (np.abs(y).max() * np.abs(dz).sum(0)[None, :] + np.abs(y).sum(0)[:, None] * np.abs(dz).max())
     assert (err <= _bound(n, y.astype(np.float64).T, dz) + floor).all()
+
+
+@pytest.mark.parametrize("fi,fo", [(4, 4), (75, 47), (64, 65), (130, 136)])
+@pytest.mark.parametrize("growth", [0, 7])
+@pytest.mark.parametrize("n", [1, 33, 2333])
+def test_weight_gradient_of_columns_of_any_magnitude(n, growth, fi, fo):
+    """Features of different units, outputs of different weight: every column keeps its own bits, alone and where two taps share
+    the errors."""
+    rng = np.random.default_rng(n + fi + growth)
+    steps = np.exp2(growth * np.minimum(np.arange(n) // 32 % 8, 6))[:, None]
+    y = [(rng.standard_normal((n, fi)) * np.exp2(rng.integers(-60, 30, size=(1, fi))) * steps).astype(np.float32) for _ in range(2)]
+    d = (rng.standard_normal((n, fo)) * np.exp2(rng.integers(-50, 30, size=(1, fo))) / steps[::-1]).astype(np.float32)
+    xo = rng.standard_normal((n, fo)).astype(np.float32)
+    xo[0] = 1.0                                           # (no column without a value)
+    ctx = _context(fi, fo, n, vb.CONV_SAGE)
+    single, pair = torch.zeros(fi, fo, device="cuda"), [torch.zeros(fi, fo, device="cuda") for _ in range(2)]
+    ctx.transform_bwd_weight(0, dev(y[0]), dev(d), dev(xo), single)
+    rows = max(n, 8)                                      # (the partition's: zeros follow)
+    padded = lambda a: dev(np.concatenate([a, np.zeros((rows - n, a.shape[1]), dtype=np.float32)]))
+    assert ctx.link_partitions()
+    ctx.prepare()
+    ctx.network_taps_bwd_weight(0, [padded(a) for a in y], padded(d), padded(xo), pair)
+    torch.cuda.synchronize()
+    dz = d.astype(np.float64) * (xo > 0)
+    for a, got in zip((y[0], *y), (single, *pair)):
+        a = a.astype(np.float64)
+        err = np.abs(got.cpu().numpy() - a.T @ dz)
+        # a value far below the largest of its own column is within 2^-42 of that one
+        floor = 2.0 ** -42 * (np.abs(a).max(0)[:, None] * np.abs(dz).sum(0)[None, :] + np.abs(a).sum(0)[:, None] * np.abs(dz).max(0)[None, :])
+        assert (err <= _bound(n, a.T, dz) + floor).all()
 
 
 def test_infinite_values_stay_in_their_rows_and_columns():
