@@ -27,6 +27,19 @@ __device__ __forceinline__ uint32_t third_pair(float x0, float x1, uint32_t hi, 
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(r, halfx2));
 }
 
+// Largest value of a group of 4, 8 or 16 consecutive lanes, in all of them.
+template <int CTRL>
+__device__ __forceinline__ float max_moved(float x) {
+    return fmaxf(x, __uint_as_float(__builtin_amdgcn_update_dpp(0, int(__float_as_uint(x)), CTRL, 0xF, 0xF, false)));
+}
+template <int LANES>
+__device__ __forceinline__ float largest_of_lanes(float x) {
+    static_assert(LANES == 4 || LANES == 8 || LANES == 16, "a row of lanes or a part of it");
+    x = max_moved<0x4E>(max_moved<0xB1>(x));           // quad_perm: lane xor 1, lane xor 2
+    if (LANES >= 8) x = max_moved<0x141>(x);           // row_half_mirror
+    return LANES == 16 ? max_moved<0x128>(x) : x;      // row_ror 8
+}
+
 // Exponent of the scale that brings `largest` (>= 0; zero and denormals count as the smallest normal number) to [2^target,
 // 2^(target + 1)), as far as the scale is a normal number.
 __device__ __forceinline__ int scale_exponent(float largest, int target) { return min(target + 127 - int(__float_as_uint(largest) >> 23), 126); }

@@ -356,9 +356,12 @@ __global__ __launch_bounds__(kWide, 4) void class_dgrad_kernel(const uint16_t* _
 // from two scaled fp16 terms per operand (kernels_gemm_half.hip), three where at most 16 columns are summed: there the rounding of the
 // terms does not average out (128 positions from 3 columns: Frobenius error 9.2e-8 with two, 7.0e-8 with three, 8.4e-8 for sums over
 // products formed in fp32). A workgroup of eight wavefronts walks tiles of ROWS rows; a wavefront holds the weights of 32 positions as
-// matrix operands in registers, both taps at the same scale per position. 16 or 8 lanes take a row of each source, agree on one scale
-// for the three, and write the terms to LDS once for all wavefronts. The cross product comes first and is cleared where nothing came
-// back, so that all three are summed in the same registers; 128 of them hold everything of two workgroups per compute unit. Bound by
+// matrix operands in registers. 16 or 8 lanes take a row of each source, agree on its scale and write the terms to LDS once for all
+// wavefronts. The cross product comes first and is cleared where nothing came back, so that all three are summed in the same registers;
+// 128 of them hold everything of two workgroups per compute unit. Sources of a row, and taps of a position, share a scale unless one is
+// more than 2^8 smaller than the largest; that one is scaled by itself, sources up to 2^64 and taps up to 2^24 further (then its error is
+// 2^-108, 2^-68 of the largest), and the sums follow from scale to scale. (One scale for all lost the errors of a node's own partition
+// at positions that larger remote ones do not reach: 2^35 between them, relative error 4e-4.) Bound by
 // writing dX and reading the three sources: 2,449,029 x 256 from 47 outputs with both taps 0.96 ms (1.45 with rows of the result first,
 // one workgroup per compute unit and dependent loads at each tile), 169,343 x 256 from 40 outputs 61 us (74).
 // Wavefronts per SIMD: two workgroups are resident where 128 registers hold the weights, the sums and the next tile (and the LDS allows).
@@ -370,9 +373,18 @@ struct alignas(16) ClassLdsF32 {
     static constexpr int BUFS = 2 * 2 * kTile + 4 * kStrips + 32 * ROWS + 4 * 256 <= 80 * 1024 ? 2 : 1;      // two where two workgroups still fit
     float strips[kWide / 64][32 * kStripF];
     uint16_t tile[BUFS][kTile];                   // [source][term][row][column]
-    uint4 rows[BUFS][ROWS];                       // {a_inv, b, scale}; a_inv = 0: every position kept (nothing came back, or everything)
-    int32_t eb[kWide / 64][32];                   // scale of each position's weights
+    // {a_inv, b, scale of the last source, steps of the scale to the second and the third source (16 bits each)};
+    // a_inv = 0: every position kept (nothing came back, or everything)
+    uint4 rows[BUFS][ROWS];
+    int32_t eb[kWide / 64][32];                   // of each position's weights: scale of the last tap (16 bits), step of the scale to it
 };
+// Scale of a source or tap beside the largest one's. Sums are below 2^38 at the scale of the largest (three sources of 64 products of
+// 2^30), so that the furthest steps of both together keep them finite.
+constexpr int kApart = 8, kSourceSteps = 64, kTapSteps = 24;
+__device__ __forceinline__ int own_scale(float largest, int shared, int most) {
+    const int e = scale_exponent(largest, kHalfTop);
+    return largest > 0.f && e > shared + kApart ? min(e, shared + most) : shared;
+}
 template <int KS, int ROWS, int ROW, bool SELF>
 __global__ __launch_bounds__(kWide, class_waves(KS, ROWS, SELF)) void class_dgrad_f32_kernel(const float* __restrict__ g_loc, const float* __restrict__ g_z,
                                                                     const float* __restrict__ dz, int32_t dz_ld, const int32_t* __restrict__ zrow_of,
@@ -393,8 +405,9 @@ __global__ __launch_bounds__(kWide, class_waves(KS, ROWS, SELF)) void class_dgra
 
     // operands: lane holds H[position][16 s + 8 lk .. + 7], both terms
     uint4 w[SELF ? 2 : 1][KS][TERMS];
+    bool taps_apart;
     {
-        float x[SELF ? 2 : 1][KS][8], m = 0.f;
+        float x[SELF ? 2 : 1][KS][8], m[2] = {0.f, 0.f};
 #pragma unroll
         for (int tap = 0; tap < (SELF ? 2 : 1); ++tap)
 #pragma unroll
@@ -403,16 +416,22 @@ __global__ __launch_bounds__(kWide, class_waves(KS, ROWS, SELF)) void class_dgra
                 for (int i = 0; i < 8; ++i) {
                     const int k = 16 * s + 8 * lk + i;
                     x[tap][s][i] = pos < width && k < fo ? (tap ? h0 : h1)[int64_t(pos) * fo + k] : 0.f;
-                    m = fmaxf(m, fabsf(x[tap][s][i]));
+                    m[tap] = fmaxf(m[tap], fabsf(x[tap][s][i]));
                 }
-        m = fmaxf(m, __shfl_xor(m, 32));
-        const int32_t eb = scale_exponent(m, kHalfTop);
-        if (lk == 0) lds.eb[wave][lcol] = eb;                 // (read by this wavefront only, behind the first tile's barrier)
-        const float sc = power_of_two(eb);
+        int32_t eb[2];
+        {
+            m[0] = fmaxf(m[0], __shfl_xor(m[0], 32)), m[1] = fmaxf(m[1], __shfl_xor(m[1], 32));
+            const int32_t shared = scale_exponent(fmaxf(m[0], m[1]), kHalfTop);
+            eb[0] = own_scale(m[0], shared, kTapSteps), eb[1] = own_scale(m[1], shared, kTapSteps);
+        }
+        const int32_t last = SELF ? eb[1] : eb[0], by = last - eb[0];
+        if (lk == 0) lds.eb[wave][lcol] = (last & 0xFFFF) | by << 16;      // (read by this wavefront only, behind the first tile's barrier)
+        taps_apart = __any(by != 0);
 #pragma unroll
         for (int tap = 0; tap < (SELF ? 2 : 1); ++tap)
 #pragma unroll
             for (int s = 0; s < KS; ++s) {
+                const float sc = power_of_two(eb[tap]);
                 uint32_t hi[4], lo[4];
 #pragma unroll
                 for (int i = 0; i < 4; ++i) split_pair(x[tap][s][2 * i] * sc, x[tap][s][2 * i + 1] * sc, hi[i], lo[i]);
@@ -459,29 +478,21 @@ __global__ __launch_bounds__(kWide, class_waves(KS, ROWS, SELF)) void class_dgra
         uint16_t* const tile = lds.tile[buf];
 #pragma unroll
         for (int h = 0; h < N; ++h) {
-            float m = 0.f;
+            float m[S], most = 0.f;
 #pragma unroll
-            for (int s = 0; s < S; ++s)
-                m = fmaxf(fmaxf(fmaxf(m, fabsf(next[h][s].x)), fmaxf(fabsf(next[h][s].y), fabsf(next[h][s].z))), fabsf(next[h][s].w));
-            auto largest_of_row = [&]() {
-#pragma unroll
-                for (int d = LANES / 2; d; d >>= 1) m = fmaxf(m, __shfl_xor(m, d));
-            };
-            largest_of_row();
-            if (__float_as_uint(m) >= 0x7F800000u) {         // an infinite error of one source says nothing about the others' scale
-                m = 0.f;
-                auto finite = [](float x) { return fabsf(x) < __builtin_inff() ? fabsf(x) : 0.f; };
-#pragma unroll
-                for (int s = 0; s < S; ++s)
-                    m = fmaxf(fmaxf(fmaxf(m, finite(next[h][s].x)), fmaxf(finite(next[h][s].y), finite(next[h][s].z))), finite(next[h][s].w));
-                largest_of_row();                             // (all lanes of a row are here)
+            for (int s = 0; s < S; ++s) {                    // (all lanes of a row are here)
+                m[s] = largest_of_lanes<LANES>(fmaxf(fmaxf(fabsf(next[h][s].x), fabsf(next[h][s].y)), fmaxf(fabsf(next[h][s].z), fabsf(next[h][s].w))));
+                m[s] = m[s] < __builtin_inff() ? m[s] : 0.f;         // an infinite source says nothing about the others' scale, and is NaN at any
+                most = fmaxf(most, m[s]);
             }
-            const int e = scale_exponent(m, kHalfTop);
-            const float sc = power_of_two(e);
+            int e[S];
+#pragma unroll
+            for (int s = 0; s < S; ++s) e[s] = own_scale(m[s], scale_exponent(most, kHalfTop), kSourceSteps);
             const int r = fr + kPass * h;
             if (r < ROWS && fc < 16 * KS) {
 #pragma unroll
                 for (int s = 0; s < S; ++s) {
+                    const float sc = power_of_two(e[s]);
                     uint32_t hi[2], lo[2];
                     split_pair(next[h][s].x * sc, next[h][s].y * sc, hi[0], lo[0]);
                     split_pair(next[h][s].z * sc, next[h][s].w * sc, hi[1], lo[1]);
@@ -498,7 +509,7 @@ __global__ __launch_bounds__(kWide, class_waves(KS, ROWS, SELF)) void class_dgra
                     const MaskAffine a = varco_affine(rule, uint32_t(next_gid[h]));
                     ab = make_uint2(a.a_inv, a.b);
                 }
-                lds.rows[buf][r] = make_uint4(ab.x, ab.y, uint32_t(e), 0u);
+                lds.rows[buf][r] = make_uint4(ab.x, ab.y, uint32_t(e[SELF ? 2 : 0]), (uint32_t(e[0] - e[1]) & 0xFFFFu) | uint32_t(e[SELF ? 2 : 0] - e[0]) << 16);
             }
         }
         __syncthreads();
@@ -533,6 +544,7 @@ __global__ __launch_bounds__(kWide, class_waves(KS, ROWS, SELF)) void class_dgra
             // accumulator register v of a lane is position 8 * (v / 4) + 4 * (lane / 32) + v % 4 of row lane % 32
 #pragma unroll
             for (int v = 0; v < 16; ++v) sum[v] = low[v] = 0.f;
+            const int32_t steps = int32_t(lds.rows[buf][rb * 32 + lcol].w);      // of the scale of the row's sums
             if (g_z) {                                // first, and dropped where the row's message did not carry it
                 product(1, 0);
                 const uint2 ab = *reinterpret_cast<const uint2*>(&lds.rows[buf][rb * 32 + lcol]);
@@ -549,17 +561,32 @@ __global__ __launch_bounds__(kWide, class_waves(KS, ROWS, SELF)) void class_dgra
                     }
                     q8 += a8, q8 = min(q8, q8 - rule.width);
                 }
+                if (__any(int16_t(steps))) {
+                    const float f = power_of_two(int16_t(steps));
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) sum[v] *= f, low[v] *= f;
+                }
                 __builtin_amdgcn_sched_barrier(0);
             }
             product(0, 0);
             __builtin_amdgcn_sched_barrier(0);
-            if constexpr (SELF) product(2, 1);
+            if constexpr (SELF) {
+                if (taps_apart || __any(steps >> 16)) {
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) {
+                        const float f = power_of_two((steps >> 16) + (lds.eb[wave][8 * (v >> 2) + 4 * lk + (v & 3)] >> 16));
+                        sum[v] *= f, low[v] *= f;
+                    }
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                product(2, 1);
+            }
             float* const strip = lds.strips[wave];
             const int32_t row_scale = int32_t(lds.rows[buf][rb * 32 + lcol].z);
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
                 const int4 eb = *reinterpret_cast<const int4*>(&lds.eb[wave][8 * g + 4 * lk]);
-                const int32_t e[4] = {eb.x, eb.y, eb.z, eb.w};
+                const int32_t e[4] = {int16_t(eb.x), int16_t(eb.y), int16_t(eb.z), int16_t(eb.w)};
                 float y[4];
 #pragma unroll
                 for (int i = 0; i < 4; ++i)

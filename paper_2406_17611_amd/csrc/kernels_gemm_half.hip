@@ -82,16 +82,6 @@ typedef float floatx2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ float largest4(float m, const float4& x) {
     return fmaxf(fmaxf(fmaxf(m, fabsf(x.x)), fmaxf(fabsf(x.y), fabsf(x.z))), fabsf(x.w));
 }
-template <int CTRL>
-__device__ __forceinline__ float max_moved(float x) {
-    return fmaxf(x, __uint_as_float(__builtin_amdgcn_update_dpp(0, int(__float_as_uint(x)), CTRL, 0xF, 0xF, false)));
-}
-// Largest value of a group of 4 or 8 consecutive lanes, in all of them.
-template <int LANES>
-__device__ __forceinline__ float largest_of_lanes(float x) {
-    x = max_moved<0x4E>(max_moved<0xB1>(x));           // quad_perm: lane xor 1, lane xor 2
-    return LANES == 8 ? max_moved<0x141>(x) : x;       // row_half_mirror
-}
 __device__ __forceinline__ float4 gate4(float4 x, float4 y) {
     x.x = y.x > 0.f ? x.x : 0.f, x.y = y.y > 0.f ? x.y : 0.f;
     x.z = y.z > 0.f ? x.z : 0.f, x.w = y.w > 0.f ? x.w : 0.f;
