@@ -37,17 +37,21 @@ size_t prod_floats(const varco_ctx* ctx, int32_t layer, int64_t k) {
 }
 
 // Split of a weight gradient's reduction over the arena's rows: whole rounds of resident workgroups, at least two
-// stages of 32 rows each. (The per-partition calls stop at eight stages: with few rows - 2,000 rows and a 32 x 8 weight
-// matrix - a handful of workgroups then walks a chain of round trips while the device idles, 16 us against 6.)
-// The fp32 sum of a slab loses accuracy with the square root of its length, so there are as many rounds as keep the result
-// no less accurate than the partitions' gradients formed one after the other (by fp32 sums over the slabs of each). Those have
-// slabs of `alone` rows; the longest ones here are as long with fp32 instructions; longer with two fp16 terms (kernels_gemm_half.hip),
-// whose sums take one rounding per 16 rows and change sign from slab to slab, by a factor that grows with the rows; longer with
-// bf16 by 4 rows per slab and 16 per partition, which is what adding one cost (these sums are exact now). Fitted to 110 shapes
-// of 12,000 to 2,449,029 rows, 2 to 32 partitions and 64 x 64 to 512 x 512 weights; relative error against fp64 of independent
-// products, partition after partition / one round / now (and the time of the last two):
-//   fp32  256 x 256   2,449,029 rows, 8 parts   3.3e-7 / 8.8e-7 / 8.8e-7  (one round; three bf16 terms: 7.2e-7, 2.0e-6)
-//                     169,343 rows, 4 parts     1.5e-7 / 2.5e-7 / 2.5e-7  (one round, 165 us; three bf16 terms: 2.9e-7, 3.8e-7 in two, 178 us)
+// stages of 32 rows each (one, where there are few). (The per-partition calls stop at eight stages: with few rows - 2,000 rows and a
+// 32 x 8 weight matrix - a handful of workgroups then walks a chain of round trips while the device idles, 16 us against 6.)
+// The fp32 sum of a slab loses accuracy with the square root of its length, so that there is a longest slab. With fp32 instructions it is
+// that of the partitions' gradients formed one after the other (`alone` rows); with bf16 4 rows per slab and 16 per partition more, which is
+// what adding a partition's gradient to the last one's cost (these sums are exact now): no less accurate than those. With two
+// fp16 terms (kernels_gemm_half.hip) it is longer by a factor that grows with the rows, and the result up to 4 times as far from exact as the
+// partitions' own: slabs as short as theirs took 7 (2,449,029 rows) to 32 % longer. What the factor keeps is an error below that of three
+// bf16 terms in their slabs: 0.45 to 0.85 of it at 13 shapes of 2,000 to 2,449,029 rows. Relative error against fp64 of independent products,
+// partition after partition / slabs as short as theirs / now, and the time of the last two:
+//   fp32  256 x 256   2,449,029 rows, 8 parts   3.3e-7 / 3.1e-7 / 8.8e-7  (1,993, 1,864 us; three bf16 terms 2.0e-6)
+//            two taps in a launch               3.3e-7 / 3.1e-7 / 1.2e-6  (3,748, 3,500 us; 2.7e-6)
+//                     600,000 rows, 8 parts     1.9e-7 / 1.7e-7 / 4.5e-7  (582, 471 us; 7.1e-7)
+//                     169,343 rows, 4 parts     1.5e-7 / 1.4e-7 / 2.5e-7  (198, 150 us; 3.9e-7)
+//         200 x 136   50,021 rows, 5 parts      1.5e-7 / 1.3e-7 / 1.6e-7  (61, 50 us; 3.0e-7)
+// and partition after partition / one round / now:
 //   bf16  512 x 512   2,449,029 rows, 32 parts  2.1e-7 / 1.2e-6 / 2.0e-7  (1.81, 2.26 ms)
 //                     169,343 rows, 4 parts     1.5e-7 / 2.6e-7 / 1.3e-7  (158, 210 us: writing and reading the partial products)
 int32_t wgrad_splits(const varco_ctx* ctx, int32_t m, int32_t n, int64_t rows, int kind, int products) {
