@@ -510,12 +510,20 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_small_k_kernel(const T* __re
 }
 
 // Short reductions of fp32 storage that go to kernels_gemm_half.hip, like long ones. It spends half the matrix instructions and splits
-// a value once per 128 columns; the persistent kernel for short reductions is ahead where its tiles of rows are many and a third stage would be
-// half empty, and below 17 steps, where the rounding of two fp16 terms does not average out. us, short / half, masked: 2,000 x 40 x 256
-// 12.1 / 8.0, 16,000 x 64 x 256 17.1 / 8.8, 60,013 x 24 x 128 16.4 / 10.1, 169,343 x 47 x 256 48.4 / 47.9, x 64 x 128 46.6 / 31.1,
-// 1,200,000 x 24 x 128 168 / 159, x 64 x 256 396 / 384, but x 40 x 256 334 / 362.
+// a value once per 128 columns; the persistent kernel for short reductions is ahead where a third stage would be half empty, more than one
+// tile of columns splits the values again and its tiles of rows are many, and it keeps what has fewer than 17 steps, where the rounding of
+// two fp16 terms does not average out. us, short / half, masked:
+//   steps x columns     2,000 rows  16,000     60,013     170,000    300,000   420,000    600,000    1,200,000
+//   24 x 128                                   16 / 10                                                168 / 159
+//   33 x 64                                               30 / 23    44 / 34   57 / 43    91 / 71    167 / 134
+//   47 x 128                                              36 / 32    57 / 51   83 / 78    110 / 107  209 / 204
+//   33 x 256                                              46 / 45    91 / 98   127 / 141  171 / 188  330 / 373
+//   40 x 256            12 / 8                            51 / 44    100 / 104 127 / 131  175 / 185  338 / 360
+//   47 x 256                                              49 / 48    97 / 107  133 / 140  179 / 195  342 / 380
+//   48 x 256                                              55 / 46    102 / 100 135 / 137  187 / 207  352 / 375
+//   64 x 256                        17 / 9                                                            396 / 384
 bool half_takes_short(const GemmArgs& ga) {
-    return ga.a.dtype == VARCO_F32 && ga.f32_terms != 0 && ga.k > 16 && (ga.k <= 32 || ga.k > 48 || ga.m <= 300'000);
+    return ga.a.dtype == VARCO_F32 && ga.f32_terms != 0 && ga.k > 16 && (ga.k <= 32 || ga.k > 48 || ga.n <= 128 || ga.m <= 250'000);
 }
 
 // A [m x k] with k contiguous and rows densely stored, B = fp32 weights stored [n x k], no chained product,

@@ -80,7 +80,8 @@ def test_transform_products(n, fi, fo, terms):
 @pytest.mark.parametrize("first_row", [0, 1, 3])
 def test_input_gradient_short_reduction(first_row, dtype):
     """dZ H^T with 47 reduction steps (the class logits' gradient) on row ranges that start at any row of a
-    larger tensor, so that the rows are neither 16-byte aligned nor is the range's start; masked and not."""
+    larger tensor, so that the rows are neither 16-byte aligned nor is the range's start; masked and not. (fp32 storage:
+    products from two fp16 terms; bf16 storage: the kernel for short reductions.)"""
     from oracle.rounding import round_bf16
     n, fi, fo = 700, 256, 47
     rng = np.random.default_rng(40 + first_row)
@@ -104,6 +105,42 @@ def test_input_gradient_short_reduction(first_row, dtype):
             dz = dz * (xo_all[first_row:] > 0)
         ref = g0.astype(np.float64) + dz @ h.astype(np.float64).T
         assert_close(gout.float().cpu().numpy(), ref, f"G0 + dZ H^T from row {first_row}", tol)
+
+
+@pytest.mark.parametrize("terms", [3, 2])
+@pytest.mark.parametrize("fo", [33, 47, 48])
+def test_input_gradient_short_reduction_over_many_rows(fo, terms):
+    """fp32 input gradients of 33 to 48 steps, more than 128 columns and 250,000 rows: the kernel for short reductions, from any row,
+    masked, alone (adding to the result) and for two taps in one launch."""
+    from test_gpu_weight_gradients import _linked_context
+    n, fi = 250_013, 132
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(fo)
+    randn = lambda *s: torch.randn(*s, generator=gen, device="cuda")     # noqa: E731
+    h = [randn(fi, fo) for _ in range(2)]
+    d, x = randn(n + 1, fo), randn(n + 1, fo)
+    dz = torch.where(x > 0, d, torch.zeros_like(d)).double()
+    # a product-sum in fp32 (terms 3), 2^-16 per product and operand (terms 2); adding to g0 rounds once more
+    tol = 8 * 2.0 ** -24 * np.sqrt(fo) if terms == 3 else 2.0 ** -14
+
+    def check(got, ref):
+        assert float((got.double() - ref).norm()) <= tol * float(ref.norm())
+        assert float((got.double() - ref).abs().max()) <= tol * float(ref.abs().max())
+
+    ctx = _ctx(fi, fo, vb.ACT_RELU, terms)
+    g0 = randn(n, fi)
+    out = g0.clone()
+    ctx.transform_bwd_input(0, d[1:], x[1:], h[0], out, True)
+    torch.cuda.synchronize()
+    check(out, g0.double() + dz[1:] @ h[0].double().t())
+    ctx, held = _linked_context(n, 2, fi, fo, vb.F32, terms)
+    pair = [torch.empty(n, fi, device="cuda") for _ in range(2)]
+    ctx.network_taps_bwd_input(0, d[:n], x[:n], h, pair)
+    torch.cuda.synchronize()
+    for got, ht in zip(pair, h):
+        check(got, dz[:n] @ ht.double().t())
+    ctx.close()
+    del held
 
 
 @pytest.mark.parametrize("n,wide,short", [(8100, 2040, 48), (8065, 2048, 70), (16350, 1012, 200)])
