@@ -41,6 +41,7 @@
 #include <type_traits>
 
 #include "elem.h"
+#include "gemm_tile.h"
 #include "half_terms.h"
 #include "varco_internal.h"
 
@@ -93,16 +94,6 @@ __device__ __forceinline__ float4 gate4(float4 x, float4 y) {
 // (q with its low three bits rotated): 0 4 1 5 2 6 3 7.
 __device__ __forceinline__ int tile_row(int q) { return (q & ~7) | ((q & 1) << 2) | ((q >> 1) & 3); }
 
-template <typename T>
-__device__ __forceinline__ T load_at(const void* base, uint32_t byte_offset) {
-    return *reinterpret_cast<const T*>(static_cast<const char*>(base) + byte_offset);
-}
-// Four floats from any address of a float (the device loads 16 bytes from there just as well).
-__device__ __forceinline__ float4 load4_at(const void* base, uint32_t byte_offset) {
-    typedef float any4 __attribute__((ext_vector_type(4), aligned(4)));
-    const any4 v = *reinterpret_cast<const any4*>(static_cast<const char*>(base) + byte_offset);
-    return make_float4(v[0], v[1], v[2], v[3]);
-}
 // A group of four that crosses the end of its row is loaded from four elements before the end and moved up by `by` (1 to 3)
 // elements; what follows the end is zero.
 __device__ __forceinline__ float4 moved_up(float4 x, int by) {
@@ -560,69 +551,11 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_half_kernel(HalfGemm g) {
         }
     }
 
-    // epilogue: accumulator register v of a lane is element (8 * (v / 4) + 4 * (lane / 32) + v % 4, lane % 32).
-    // A tile that lies wholly inside C (all but the last row and column of tiles) is stored through one scalar
-    // base per output row plus one 32-bit lane offset (4 lk rows + lrow columns), so that the address arithmetic
-    // runs on the scalar unit and the vector unit only sees the loads, adds and stores; the edge tiles take the
-    // path with per-element tests and clamped addresses. When C is added to, the old values of a block are fetched
-    // by loads that are all issued before the first one is used, not one round trip per element.
     const bool to_partial = g.split_k > 1;
-    const int64_t pitch = to_partial ? int64_t(g.n) : g.ldc;
     float* const base = to_partial ? g.partial + (int64_t(second ? g.split_k : 0) + z) * g.m * g.n : second ? g.c_dual : g.c;
-    const bool add_old = !to_partial && g.accumulate;
-    if (m0 + BM <= g.m && n0 + BN <= g.n) {
-        float* const tile = base + int64_t(m0 + wm) * pitch + (n0 + wn);               // scalar
-        const uint32_t lane_off = uint32_t(4 * lk) * uint32_t(pitch) + uint32_t(lrow);  // a tile spans < 2^32 elements
-#pragma unroll
-        for (int i = 0; i < TMB; ++i) {
-#pragma unroll
-            for (int j = 0; j < TNB; ++j) {
-                float old[16];
-#pragma unroll
-                for (int v = 0; v < 16; ++v) old[v] = 0.f;
-                if (add_old) {
-#pragma unroll
-                    for (int v = 0; v < 16; ++v)
-                        old[v] = (tile + int64_t(i * 32 + 8 * (v >> 2) + (v & 3)) * pitch + j * 32)[lane_off];
-                }
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const float x = acc[i][j][v] + old[v];
-                    (tile + int64_t(i * 32 + 8 * (v >> 2) + (v & 3)) * pitch + j * 32)[lane_off] = x;
-                }
-            }
-        }
-        return;
-    }
-    const int32_t col_base = n0 + wn + lrow;
-#pragma unroll
-    for (int i = 0; i < TMB; ++i) {
-#pragma unroll
-        for (int j = 0; j < TNB; ++j) {
-            float* ptr[16];
-            bool ok[16];
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int32_t row = m0 + wm + i * 32 + 4 * lk + 8 * (v >> 2) + (v & 3), col = col_base + j * 32;
-                ok[v] = row < g.m && col < g.n;
-                ptr[v] = base + int64_t(min(row, g.m - 1)) * pitch + min(col, g.n - 1);
-            }
-            float old[16];
-#pragma unroll
-            for (int v = 0; v < 16; ++v) old[v] = 0.f;
-            if (add_old) {
-#pragma unroll
-                for (int v = 0; v < 16; ++v) old[v] = *ptr[v];
-            }
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const float x = acc[i][j][v] + old[v];
-                if (ok[v]) *ptr[v] = x;
-            }
-        }
-    }
+    store_tile(acc, base, to_partial ? int64_t(g.n) : g.ldc, g.m, g.n, m0 + wm, n0 + wn, m0 + BM <= g.m && n0 + BN <= g.n, lane,
+               !to_partial && g.accumulate, false);
 }
-
 
 bool aligned_to(const void* p, uintptr_t bytes) { return (reinterpret_cast<uintptr_t>(p) & (bytes - 1)) == 0; }
 

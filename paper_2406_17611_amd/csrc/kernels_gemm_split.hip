@@ -21,6 +21,7 @@
 #include <type_traits>
 
 #include "elem.h"
+#include "gemm_tile.h"
 #include "half_terms.h"
 #include "varco_internal.h"
 
@@ -74,16 +75,6 @@ __device__ __forceinline__ void expand_pair(float x0, float x1, uint32_t (&w)[TE
 // the 16 rows whose fragments are read together lie in 16 different places.
 __device__ __forceinline__ int lds_at(int row, int k) { return row * kPitch + (k ^ ((row << 1) & 24)); }      // (bits 2, 3 of the row)
 
-template <typename T>
-__device__ __forceinline__ T load_at(const void* base, uint32_t byte_offset) {
-    return *reinterpret_cast<const T*>(static_cast<const char*>(base) + byte_offset);
-}
-// Four floats from any address of a float (the device loads 16 bytes from there just as well).
-__device__ __forceinline__ float4 load4_at(const void* base, uint32_t byte_offset) {
-    typedef float any4 __attribute__((ext_vector_type(4), aligned(4)));
-    const any4 v = *reinterpret_cast<const any4*>(static_cast<const char*>(base) + byte_offset);
-    return make_float4(v[0], v[1], v[2], v[3]);
-}
 // ---- fp32 operand with the reduction index contiguous: chunks of CH floats ----
 // Addresses are a per-tile base (uniform) plus a 32-bit offset per chunk that does not change along the
 // reduction. Rows beyond the matrix are clamped to its last row (their results are never stored); chunks
@@ -286,68 +277,7 @@ __global__ __launch_bounds__(kThreads, 3) void gemm_split_kernel(SplitGemm g) {
         __syncthreads();       // the stage's fragments have been read: the next one may overwrite them
     }
 
-    // epilogue: accumulator register v of a lane is element (8 * (v / 4) + 4 * (lane / 32) + v % 4, lane % 32).
-    // A tile that lies wholly inside C (all but the last row and column of tiles) is stored through one scalar
-    // base per output row plus one 32-bit lane offset (4 lk rows + lrow columns), so that the address arithmetic
-    // runs on the scalar unit and the vector unit only sees the loads, adds and stores; the edge tiles take the
-    // path with per-element tests and clamped addresses. When C is added to, the old values of a block are fetched
-    // by loads that are all issued before the first one is used, not one round trip per element.
-    const int64_t pitch = g.ldc;
-    float* const base = g.c;
-    const bool add_old = g.accumulate, relu = g.relu;
-    if (m0 + BM <= g.m && n0 + BN <= g.n) {
-        float* const tile = base + int64_t(m0 + wm) * pitch + (n0 + wn);               // scalar
-        const uint32_t lane_off = uint32_t(4 * lk) * uint32_t(pitch) + uint32_t(lrow);  // a tile spans < 2^32 elements
-#pragma unroll
-        for (int i = 0; i < TMB; ++i) {
-#pragma unroll
-            for (int j = 0; j < TNB; ++j) {
-                float old[16];
-#pragma unroll
-                for (int v = 0; v < 16; ++v) old[v] = 0.f;
-                if (add_old) {
-#pragma unroll
-                    for (int v = 0; v < 16; ++v)
-                        old[v] = (tile + int64_t(i * 32 + 8 * (v >> 2) + (v & 3)) * pitch + j * 32)[lane_off];
-                }
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    float x = acc[i][j][v] + old[v];
-                    if (relu) x = fmaxf(x, 0.f);
-                    (tile + int64_t(i * 32 + 8 * (v >> 2) + (v & 3)) * pitch + j * 32)[lane_off] = x;
-                }
-            }
-        }
-        return;
-    }
-    const int32_t col_base = n0 + wn + lrow;
-#pragma unroll
-    for (int i = 0; i < TMB; ++i) {
-#pragma unroll
-        for (int j = 0; j < TNB; ++j) {
-            float* ptr[16];
-            bool ok[16];
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int32_t row = m0 + wm + i * 32 + 4 * lk + 8 * (v >> 2) + (v & 3), col = col_base + j * 32;
-                ok[v] = row < g.m && col < g.n;
-                ptr[v] = base + int64_t(min(row, g.m - 1)) * pitch + min(col, g.n - 1);
-            }
-            float old[16];
-#pragma unroll
-            for (int v = 0; v < 16; ++v) old[v] = 0.f;
-            if (add_old) {
-#pragma unroll
-                for (int v = 0; v < 16; ++v) old[v] = *ptr[v];
-            }
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                float x = acc[i][j][v] + old[v];
-                if (relu) x = fmaxf(x, 0.f);
-                if (ok[v]) *ptr[v] = x;
-            }
-        }
-    }
+    store_tile(acc, g.c, g.ldc, g.m, g.n, m0 + wm, n0 + wn, m0 + BM <= g.m && n0 + BN <= g.n, lane, g.accumulate != 0, g.relu != 0);
 }
 
 // ---------------------------------------------------------------------------------------------------------
