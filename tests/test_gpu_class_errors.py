@@ -56,6 +56,12 @@ def _class_layer(conv, fi, fo, ratio, dtype, dz, h1, h0, seed=7, n=500):
     return got, dx(np.float64), dx(np.float64, True), reached, ((s_intra + s_cross) != 0).sum(0)[:, None], dx(np.float32)[1]
 
 
+def _bf16_bound(conv, agg, ref, absolute):
+    """Every store of dX rounds to 8 bits, to within 2^-8 (SAGE stores the aggregated part first); sums of errors keep 16 bits (2^-16) and
+    are added in fp32: up to 300 entries a sum over 64 lanes, at most 64 products."""
+    return 2.0 ** -8 * (np.abs(ref) + (np.abs(agg) if conv == "sage" else 0.0)) * (1 + 2.0 ** -7) + (2.0 ** -16 + 80 * 2.0 ** -24) * absolute
+
+
 @pytest.mark.parametrize("conv,fi,fo,ratio", [("gcn", 64, 1, (8, 1)), ("gcn", 256, 3, (8, 1)), ("sage", 128, 16, (8, 1)), ("gcn", 512, 47, (5, 1)),
                                               ("sage", 272, 33, (1, 1)), ("gcn", 208, 64, (8, 1))])
 def test_bf16_errors_of_one_sign(conv, fi, fo, ratio):
@@ -65,9 +71,7 @@ def test_bf16_errors_of_one_sign(conv, fi, fo, ratio):
     dz = bf(np.abs(rng.standard_normal((500, fo))) * np.where(rng.random(fo) < 0.5, -1.0, 1.0))
     h1, h0 = bf(rng.standard_normal((fi, fo))), bf(rng.standard_normal((fi, fo)))
     got, (agg, ref), (_, absolute), *_ = _class_layer(conv, fi, fo, ratio, "bf16", dz, h1, h0)
-    # every store of dX rounds to 8 bits, to within 2^-8 (SAGE stores the aggregated part first); sums of errors keep 16 bits
-    # (2^-16) and are added in fp32: up to 300 entries a sum over 64 lanes, at most 64 products
-    bound = 2.0 ** -8 * (np.abs(ref) + (np.abs(agg) if conv == "sage" else 0.0)) * (1 + 2.0 ** -7) + (2.0 ** -16 + 80 * 2.0 ** -24) * absolute
+    bound = _bf16_bound(conv, agg, ref, absolute)
     assert (np.abs(got - ref) <= bound).all(), float((np.abs(got - ref) / bound.clip(1e-300)).max())
 
 
@@ -112,13 +116,17 @@ def test_fp32_sources_and_weights_of_any_magnitude(conv, fi, fo, ratio, spread):
         assert np.linalg.norm(got - ref) <= 1.25 * np.linalg.norm(plain - ref)
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("conv,fi,fo,ratio", _SHAPES)
-def test_fp32_infinite_errors_stay_where_they_are_received(conv, fi, fo, ratio):
+def test_infinite_errors_stay_where_they_are_received(conv, fi, fo, ratio, dtype):
     """An infinite error of one node: its consumers' elements are lost, all others keep their accuracy, the positions of the same row that
     a message did not carry among them."""
     rng = np.random.default_rng(fi + fo)
-    dz, h1, h0 = [rng.standard_normal(shape).astype(np.float32) for shape in ((500, fo), (fi, fo), (fi, fo))]
+    fi = min(fi // 16 * 16, 512) if dtype == "bf16" else fi      # (what bf16 storage sums at the width of the outputs)
+    stored = (lambda a: round_bf16(a).astype(np.float32)) if dtype == "bf16" else (lambda a: a.astype(np.float32))
+    dz, h1, h0 = [stored(rng.standard_normal(shape)) for shape in ((500, fo), (fi, fo), (fi, fo))]
     dz[123, fo // 2] = np.inf
-    got, (_, ref), (_, absolute), reached, entries, _ = _class_layer(conv, fi, fo, ratio, "f32", dz, h1, h0)
+    got, (agg, ref), (_, absolute), reached, entries, _ = _class_layer(conv, fi, fo, ratio, dtype, dz, h1, h0)
     assert reached.any() and not reached.all() and not np.isfinite(got[reached]).any()
-    assert (np.abs(got - ref) <= _fp32_bound(fo, entries, absolute))[~reached].all()
+    bound = _fp32_bound(fo, entries, absolute) if dtype == "f32" else _bf16_bound(conv, agg, ref, absolute)
+    assert (np.abs(got - ref) <= bound)[~reached].all()
