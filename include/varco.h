@@ -189,13 +189,14 @@ int32_t varco_advance_step(varco_ctx* ctx, varco_stream stream);
  * (the paper fixes no arithmetic; VARCO_BF16 contexts ignore this). terms = 3 (the default): in the transform each fp32 operand
  * is written exactly as a sum of three bf16 numbers and the six largest cross products are formed on the bf16
  * matrix units with fp32 accumulation; the dropped products are below 2^-24 of each full product, so the result
- * has the accuracy of fp32 arithmetic at well under half the cost. In the gradients (the input gradient of more than 64
- * outputs) each operand is scaled by a power of two and written as two fp16 numbers, 22 to 23 of its bits, three products, with sums
+ * has the accuracy of fp32 arithmetic at well under half the cost. In the gradients
+ * (input gradients of 17 outputs and more, in fewer three bf16 terms; of 33 to 48 outputs the faster of the two, by size) each operand is
+ * scaled by a power of two and written as two fp16 numbers, 22 to 23 of its bits, three products, with sums
  * that are rounded less often: less error than the former at under two thirds of its cost. Values more than 2^22 below the largest of their row (weight gradients: of
  * their own column of y or dz) are within 2^-44 of that one. terms = 0: fp32 matrix instructions
  * throughout (also used, whatever the setting, for shapes the expanded forms do not take: transforms whose reduction length is
- * no multiple of 4, gradients with fewer than 4 rows or columns). terms = 2: transforms and input gradients of at most 64 outputs
- * from two bf16 terms, three products, relative error about 2^-16 per product (a
+ * no multiple of 4, gradients with fewer than 4 rows or columns). terms = 2: what three bf16 terms form above (transforms, short input
+ * gradients) from two, three products, relative error about 2^-16 per product (a
  * lower-precision setting nothing in this library selects by itself). With terms 2 or 3 an operand that is
  * infinite, NaN or (bf16 terms) within 2^-9 of the fp32 overflow threshold turns the outputs it meets into NaN (fp32
  * instructions would keep an infinity times a finite number infinite); use terms = 0 where such values must
@@ -356,8 +357,10 @@ int32_t varco_accumulate_returned(varco_ctx* ctx, int32_t layer, int32_t p, cons
  * ratio first): 28 bytes per entry and up to 60 per node, in this call; per prepared stream, in varco_prepare, n_total
  * rows of the widest layer and the partial products of the weight gradients (1.3 GB for 512 x 512 bf16 weights over
  * 2.4 million nodes; 4 GiB per weight matrix or pair at most); and while 3 k < width[l] for an l > 0, in
- * varco_set_ratio, up to 1.25 k elements per entry of a halo column, 48 GiB at most. The last is optional: beyond that size,
- * or where it cannot be had, whole rows are gathered instead. With fp32 storage that changes the order of sums only; with
+ * varco_set_ratio, up to 1.25 k elements per entry of a halo column, 48 GiB at most; and for a class layer
+ * of at most 64 outputs (l > 0, identity activation, fewer outputs than inputs) 512 bytes per node and 256 per boundary row (bf16: 384
+ * and 256) for its errors summed at the width of the outputs. The last two are optional: beyond that size,
+ * or where they cannot be had, whole rows are gathered instead. With fp32 storage that changes the order of sums only; with
  * bf16 storage the products are rounded to bf16 and gathered rows are not, so the input gradients then differ by such
  * roundings (2^-9 each). A step captured into a graph prepares its own stream, hence takes a second set.
  *

@@ -628,7 +628,8 @@ int32_t prep_all(varco_ctx* ctx, Workspace& ws, const varco_network_buffers& b, 
         for (int which = 0; which < (ctx->conv == VARCO_CONV_SAGE ? 2 : 1); ++which) {
             const void* h = which ? b.h0[l] : b.h1[l];
             n += prep_slot(ctx, ws, l, h, fi, fo, true, which, false, unused, jobs + n) ? 1 : 0;
-            // at most 64 outputs: the short-reduction kernels take the weights as they are
+            // (fp32 layers of at most 64 outputs take their weights as they are, or, from 17 outputs on where no narrow sums are formed, have them
+            // copied by layer_bwd)
             if (b.dh1[l] && l > 0 && (fo > 64 || (which == 0 && ctx->dtype == VARCO_BF16 && (first || narrow_sums_pay(ctx, l)))))
                 n += prep_slot(ctx, ws, l, h, fi, fo, false, which, false, unused, jobs + n) ? 1 : 0;
         }
