@@ -40,12 +40,19 @@ def test_input_gradient_rows_of_any_magnitude(fo, growth):
     d = d.astype(np.float32)
     xo = rng.standard_normal((n, fo)).astype(np.float32)
     h = (synth.glorot(fi, fo, 3, 1) * np.exp2(rng.integers(-30, 30, size=(fi, 1)))).astype(np.float32)
-    out = torch.empty(n, fi, device="cuda")
-    _context(fi, fo).transform_bwd_input(0, dev(d), dev(xo), dev(h), out, False)
+    taps = [h, h[::-1].copy()]
+    out = [torch.empty(n, fi, device="cuda") for _ in range(3)]
+    ctx = _context(fi, fo, n, vb.CONV_SAGE)
+    ctx.transform_bwd_input(0, dev(d), dev(xo), dev(h), out[0], False)
+    assert ctx.link_partitions()
+    ctx.prepare()
+    ctx.set_step(1)
+    ctx.network_taps_bwd_input(0, dev(d), dev(xo), [dev(a) for a in taps], out[1:])      # two taps share the rows of dZ and their scales
     torch.cuda.synchronize()
     dz = d.astype(np.float64) * (xo > 0)
-    err = np.abs(out.cpu().numpy() - dz @ h.astype(np.float64).T)
-    assert (err <= _bound(fo, dz, h.astype(np.float64).T)).all()
+    for a, got in zip((h, *taps), out):
+        err = np.abs(got.cpu().numpy() - dz @ a.astype(np.float64).T)
+        assert (err <= _bound(fo, dz, a.astype(np.float64).T)).all()
 
 
 @pytest.mark.parametrize("fo", [17, 24, 32, 33, 47, 48, 49, 64])
