@@ -512,7 +512,8 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_small_k_kernel(const T* __re
 // Short reductions of fp32 storage that go to kernels_gemm_half.hip, like long ones. It spends half the matrix instructions and splits
 // a value once per 128 columns; the persistent kernel for short reductions is ahead where a third stage would be half empty, more than one
 // tile of columns splits the values again and its tiles of rows are many, and it keeps what has fewer than 17 steps, where the rounding of
-// two fp16 terms does not average out. us, short / half, masked:
+// two fp16 terms does not average out. (Around the line at 300,000 rows, where they are about level, two fp16 terms are the more accurate.)
+// us, short / half, masked:
 //   steps x columns     2,000 rows  16,000     60,013     170,000    300,000   420,000    600,000    1,200,000
 //   24 x 128                                   16 / 10                                                168 / 159
 //   33 x 64                                               30 / 23    44 / 34   57 / 43    91 / 71    167 / 134
@@ -523,7 +524,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_small_k_kernel(const T* __re
 //   48 x 256                                              55 / 46    102 / 100 135 / 137  187 / 207  352 / 375
 //   64 x 256                        17 / 9                                                            396 / 384
 bool half_takes_short(const GemmArgs& ga) {
-    return ga.a.dtype == VARCO_F32 && ga.f32_terms != 0 && ga.k > 16 && (ga.k <= 32 || ga.k > 48 || ga.n <= 128 || ga.m <= 250'000);
+    return ga.a.dtype == VARCO_F32 && ga.f32_terms != 0 && ga.k > 16 && (ga.k <= 32 || ga.k > 48 || ga.n <= 128 || ga.m <= 300'000);
 }
 
 // A [m x k] with k contiguous and rows densely stored, B = fp32 weights stored [n x k], no chained product,

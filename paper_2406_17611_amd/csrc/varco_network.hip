@@ -61,8 +61,12 @@ int32_t wgrad_splits(const varco_ctx* ctx, int32_t m, int32_t n, int64_t rows, i
     const int64_t longest = kind == kGemmExpanded ? alone * (137'500 + rows) / 73'300 : kind == kGemmBf16 ? alone + 4 * split + 16 * ctx->n_parts : alone;
     const int64_t round = slots * std::max<int64_t>(1, longest);
     const int64_t rounds = std::max<int64_t>(1, std::min((rows + round - 1) / round, kPartialElems / (slots * products * m * n)));
-    // (the stages of a slab follow one another, 1.4 us each: few rows take slabs of a single one, 2,000 x 16 x 32 9.4 -> 6.6 us; beyond, adding the
-    // partial products costs more: 16,000 x 32 x 64 in slabs of two stages 8.4 and 5.6 us, of one 9.1 and 8.5)
+    // (The stages of a slab follow one another, 1.4 us each: few rows take slabs of a single one. Beyond, and with large weights, adding the
+    // partial products costs more; their sums are the more accurate all the same. Slabs of two stages / of one, one tap with its sums, us:
+    //   fp32 16 x 32     2,000 rows 11.5 / 9.4    4,000 11.4 / 9.7    6,000 11.0 / 10.6   16,000 12.5 / 15.6
+    //        64 x 128               16.1 / 13.2         16.0 / 14.4         15.4 / 16.0          19.1 / 24.2
+    //        128 x 256              15.2 / 14.9         16.8 / 18.3         17.1 / 20.7
+    //   bf16 64 x 128                9.9 / 9.8          10.4 / 11.2         11.0 / 12.3          14.0 / 19.2)
     const int64_t stages = (rows + step - 1) / step;
     return int32_t(std::min<int64_t>(rounds * slots, stages <= kFewStages ? stages : stages / 2));
 }

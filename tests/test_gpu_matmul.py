@@ -110,10 +110,10 @@ def test_input_gradient_short_reduction(first_row, dtype):
 @pytest.mark.parametrize("terms", [3, 2])
 @pytest.mark.parametrize("fo", [33, 47, 48])
 def test_input_gradient_short_reduction_over_many_rows(fo, terms):
-    """fp32 input gradients of 33 to 48 steps, more than 128 columns and 250,000 rows: the kernel for short reductions, from any row,
+    """fp32 input gradients of 33 to 48 steps, more than 128 columns and 300,000 rows: the kernel for short reductions, from any row,
     masked, alone (adding to the result) and for two taps in one launch."""
     from test_gpu_weight_gradients import _linked_context
-    n, fi = 250_013, 132
+    n, fi = 300_013, 132
     gen = torch.Generator(device="cuda")
     gen.manual_seed(fo)
     randn = lambda *s: torch.randn(*s, generator=gen, device="cuda")     # noqa: E731
