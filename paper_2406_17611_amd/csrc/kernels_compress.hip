@@ -39,16 +39,22 @@ __global__ __launch_bounds__(kBlock) void compress_kernel(MaskRule rule, const i
 
 // Encoder and decoder through LDS. Kept positions are spread over the whole row, so a row's cache lines all travel whether
 // 4 bytes of a line are wanted or 128, and element-wise accesses (64 scattered addresses per instruction) cost the vector
-// memory unit about a cycle each: instead a wavefront moves whole rows with 16-byte accesses, kRowsInFlight of them at a
-// time with the next ones already requested, and picks (encoder) or places (decoder) the kept elements in LDS. 450,000 rows
+// memory unit about a cycle each: instead a wavefront moves whole rows with 16-byte accesses, rows_in_flight of them at a
+// time, and picks (encoder) or places (decoder) the kept elements in LDS. 450,000 rows
 // of 256, element-wise -> through LDS: decoder 265 -> 116 us (fp32, k = 32), 197 -> 64 (bf16, k = 64); encoder 197 -> 133
-// (fp32, k = 128), 136 -> 46 (bf16, k = 64); decoder with sum 224 -> 196 (fp32, k = 32: the rate of a copy), 194 -> 135
+// (fp32, k = 128), 136 -> 46 (bf16, k = 64); decoder with sum 224 -> 196 (fp32, k = 32), 194 -> 135
 // (bf16, k = 128). Where the element-wise kernels win (few kept elements, narrow or unaligned rows): codec_rows_pay.
+// A wavefront is a workgroup and takes one group of rows: workgroups start in the order of the rows, so that what is in flight lies
+// close together in memory, which drifting wavefronts that each walk the whole range lose (a plain copy: 6.2 against 4.8 TB/s; this
+// encoder / decoder / decoder with sum of 450,007 of 600,011 fp32 rows of 256, k = 32: persistent workgroups of four wavefronts
+// 103 / 114 / 197 us, one group of rows each 97 / 108 / 183; the three calls in turn 432 -> 404 us).
 //   MODE 0: z[i, j] = x[row_i, pi(j)];  1: x[row_i, :] = 0 except x[row_i, pi(j)] = z[i, j];  2: x[row_i, pi(j)] += z[i, j],
 //   in LDS on the old row, which is written back whole: what is not added to keeps its bits
 // S: the storage word (fp32 or bf16 bits); V: elements per access to x (16 bytes, or 1 for unaligned rows); PE: elements of z
 // per lane (2 for bf16 pairs); ONE: a row is at most one access per lane.
-constexpr int kRowsInFlight = 4;
+constexpr int kCodecBlock = 64;
+constexpr int64_t kCodecGrid = int64_t(1) << 24;      // a launch holds fewer than 2^32 threads
+constexpr int rows_in_flight(int mode) { return mode == 2 ? 2 : 4; }      // (two, with rows read and written: 183 us against 192)
 template <typename S>
 __device__ __forceinline__ S add_words(S x, S z) {
     if constexpr (sizeof(S) == 4)
@@ -58,79 +64,47 @@ __device__ __forceinline__ S add_words(S x, S z) {
 }
 
 template <typename S, int MODE, int V, int PE, bool ONE>
-__global__ __launch_bounds__(kBlock) void codec_rows_kernel(MaskRule rule, const int32_t* __restrict__ gids, const int32_t* __restrict__ rows,
-                                                            int64_t n_rows, S* x, int64_t ldx, S* z, int lpe_log2) {
-    constexpr int U = kRowsInFlight;
+__global__ __launch_bounds__(kCodecBlock) void codec_rows_kernel(MaskRule rule, const int32_t* __restrict__ gids, const int32_t* __restrict__ rows,
+                                                                 int64_t n_rows, S* x, int64_t ldx, S* z, int lpe_log2) {
+    constexpr int U = rows_in_flight(MODE);
     typedef S Vec __attribute__((ext_vector_type(V)));
     typedef S Pair __attribute__((ext_vector_type(PE)));
     extern __shared__ __attribute__((aligned(16))) unsigned char codec_lds[];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x;
     const int32_t width = int32_t(rule.width), k = int32_t(rule.k);
     const int32_t pitch = (width + 7) & ~7;
-    S* const buf = reinterpret_cast<S*>(codec_lds) + wave * U * pitch;
+    S* const buf = reinterpret_cast<S*>(codec_lds);
     const int lpe = 1 << lpe_log2, sub = lane >> lpe_log2, jl = lane & (lpe - 1), n_sub = 64 >> lpe_log2;
-    auto clear = [&]() {
-        for (int u = 0; u < U; ++u)
-            for (int c = lane * V; c < width; c += 64 * V) *reinterpret_cast<Vec*>(buf + u * pitch + c) = Vec(S(0));
-    };
-    if (MODE == 1) clear();
-    const int64_t stride = int64_t(gridDim.x) * (kBlock / 64) * U;
-    int64_t r0 = (int64_t(blockIdx.x) * (kBlock / 64) + wave) * U;
-    if (r0 >= n_rows) return;                        // wavefronts are independent: no barrier
-    // Software pipeline over groups of U rows: the rows' ids are fetched two groups ahead, their data one group ahead.
-    int32_t gid = 0, src = 0;                        // lane u: of row u of a group (past the end: the last row)
-    auto load_ids = [&](int64_t r) {
-        const int64_t i = min(r + (lane & (U - 1)), n_rows - 1);
-        gid = gids[i];
-        if (rows) src = rows[i];
-    };
-    int64_t at[U];                                   // element offset of the group's rows in x
-    uint32_t ab = 0;
-    auto resolve = [&](int64_t r) {
-        const MaskAffine m = varco_affine(rule, uint32_t(gid));
-        ab = m.a | (m.b << 16);
+    for (int64_t r0 = int64_t(blockIdx.x) * U; r0 < n_rows; r0 += int64_t(gridDim.x) * U) {      // (once, up to kCodecGrid workgroups)
+        const int n_here = int(min(int64_t(U), n_rows - r0));
+        const int64_t i = min(r0 + (lane & (U - 1)), n_rows - 1);      // lane u: row u of the group (past the end: the last row)
+        const int32_t gid = gids[i], src = rows ? rows[i] : 0;
+        int64_t at[U];                                   // element offset of the group's rows in x
 #pragma unroll
-        for (int u = 0; u < U; ++u) at[u] = (rows ? int64_t(__shfl(src, u)) : min(r + u, n_rows - 1)) * ldx;
-    };
-    Vec v[U];
-    const int own = min(lane * V, width - V);        // lanes past the row repeat its last access (never stored)
-    auto load_rows = [&]() {
-        if constexpr (ONE && MODE != 1) {
+        for (int u = 0; u < U; ++u) at[u] = (rows ? int64_t(__shfl(src, u)) : min(r0 + u, n_rows - 1)) * ldx;
+        if constexpr (MODE == 1) {
+            for (int u = 0; u < U; ++u)
+                for (int c = lane * V; c < width; c += 64 * V) *reinterpret_cast<Vec*>(buf + u * pitch + c) = Vec(S(0));
+        } else if constexpr (ONE) {
+            Vec v[U];
+            const int own = min(lane * V, width - V);    // lanes past the row repeat its last access (never stored)
 #pragma unroll
             for (int u = 0; u < U; ++u) v[u] = *reinterpret_cast<const Vec*>(x + at[u] + own);
-        }
-    };
-    load_ids(r0);
-    resolve(r0);
-    load_rows();
-    if (r0 + stride < n_rows) load_ids(r0 + stride);
-    for (; r0 < n_rows; r0 += stride) {
-        const int n_here = int(min(int64_t(U), n_rows - r0));
-        const uint32_t ab_now = ab;
-        int64_t at_now[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) at_now[u] = at[u];
-        if constexpr (MODE != 1) {
-            if constexpr (ONE) {
+            for (int u = 0; u < U; ++u)
+                if (lane * V < width) *reinterpret_cast<Vec*>(buf + u * pitch + lane * V) = v[u];
+        } else {
+            for (int c = lane * V; c < width; c += 64 * V)
 #pragma unroll
-                for (int u = 0; u < U; ++u)
-                    if (lane * V < width) *reinterpret_cast<Vec*>(buf + u * pitch + lane * V) = v[u];
-            } else {
-                for (int c = lane * V; c < width; c += 64 * V)
-#pragma unroll
-                    for (int u = 0; u < U; ++u) *reinterpret_cast<Vec*>(buf + u * pitch + c) = *reinterpret_cast<const Vec*>(x + at_now[u] + c);
-            }
+                for (int u = 0; u < U; ++u) *reinterpret_cast<Vec*>(buf + u * pitch + c) = *reinterpret_cast<const Vec*>(x + at[u] + c);
         }
-        if (r0 + stride < n_rows) {
-            resolve(r0 + stride);
-            load_rows();
-            if (r0 + 2 * stride < n_rows) load_ids(r0 + 2 * stride);
-        }
+        const MaskAffine rm = varco_affine(rule, uint32_t(gid));
+        const uint32_t ab = rm.a | (rm.b << 16);
         __builtin_amdgcn_wave_barrier();
         // the kept elements: a group of lanes serves one row, the groups different rows
         for (int u0 = 0; u0 < n_here; u0 += n_sub) {
             const int u = u0 + sub;
-            const uint32_t m = __shfl(ab_now, u & (U - 1)), a = m & 0xFFFFu;
+            const uint32_t m = __shfl(ab, u & (U - 1)), a = m & 0xFFFFu;
             if (u < n_here) {
                 S* const row = buf + u * pitch;
                 for (int j = jl * PE; j < k; j += lpe * PE) {
@@ -156,9 +130,8 @@ __global__ __launch_bounds__(kBlock) void codec_rows_kernel(MaskRule rule, const
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             if (u >= n_here) break;
-            for (int c = lane * V; c < width; c += 64 * V) *reinterpret_cast<Vec*>(x + at_now[u] + c) = *reinterpret_cast<const Vec*>(buf + u * pitch + c);
+            for (int c = lane * V; c < width; c += 64 * V) *reinterpret_cast<Vec*>(x + at[u] + c) = *reinterpret_cast<const Vec*>(buf + u * pitch + c);
         }
-        if (MODE == 1) clear();
         __builtin_amdgcn_wave_barrier();
     }
 }
@@ -276,7 +249,7 @@ int group_log2(uint32_t elems) {
 unsigned grid_for(int64_t n_rows, int g_log2) {
     const int64_t threads = n_rows << g_log2;
     int64_t blocks = (threads + kBlock - 1) / kBlock;
-    const int64_t cap = 256 * 16;  // 16 resident blocks on each of the 256 compute units, grid-stride beyond
+    const int64_t cap = int64_t(1) << 22;  // a launch holds fewer than 2^32 threads; workgroups that each take one place start in memory order
     if (blocks > cap) blocks = cap;
     if (blocks < 1) blocks = 1;
     return unsigned(blocks);
@@ -363,16 +336,16 @@ hipError_t launch_codec_rows(const MaskRule& rule, const int32_t* gids, const in
                              hipStream_t stream) {
     using S = std::conditional_t<sizeof(T) == 2, uint16_t, uint32_t>;
     constexpr int V16 = 16 / int(sizeof(S));
-    constexpr int W = kBlock / 64;
+    constexpr int U = rows_in_flight(MODE);
     const bool vec = rule.width % V16 == 0 && ldx % V16 == 0 && (reinterpret_cast<uintptr_t>(x) & 15u) == 0;
     const bool pair = sizeof(S) == 2 && rule.k % 2 == 0 && (reinterpret_cast<uintptr_t>(z) & 3u) == 0;
     const bool one = int(rule.width) <= 64 * (vec ? V16 : 1);
     const int lpe = group_log2(pair ? rule.k / 2 : rule.k);
-    const size_t lds = size_t(W) * kRowsInFlight * ((rule.width + 7) & ~7u) * sizeof(S);
-    const int64_t blocks = std::min<int64_t>((n_rows + W * kRowsInFlight - 1) / (W * kRowsInFlight), 256 * 32);
+    const size_t lds = size_t(U) * ((rule.width + 7) & ~7u) * sizeof(S);
+    const int64_t blocks = std::min((n_rows + U - 1) / U, kCodecGrid);
     auto go = [&](auto vc, auto pc, auto oc) {
         hipLaunchKernelGGL((codec_rows_kernel<S, MODE, decltype(vc)::value, decltype(pc)::value, decltype(oc)::value>), dim3(unsigned(blocks)),
-                           dim3(kBlock), lds, stream, rule, gids, rows, n_rows, static_cast<S*>(x), ldx, static_cast<S*>(z), lpe);
+                           dim3(kCodecBlock), lds, stream, rule, gids, rows, n_rows, static_cast<S*>(x), ldx, static_cast<S*>(z), lpe);
     };
     auto with_one = [&](auto vc, auto pc) {
         if (one)
