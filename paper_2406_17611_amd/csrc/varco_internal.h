@@ -339,10 +339,11 @@ hipError_t varco_launch_gemm_tn_bf16(const GemmArgs& g, hipStream_t stream, cons
 // fp32 operands as sums of bf16 terms on the bf16 matrix cores (kernels_gemm_split.hip): the transform.
 bool varco_gemm_split_usable(const GemmArgs& g);
 hipError_t varco_launch_gemm_split(const GemmArgs& g, hipStream_t stream, const LaunchTag& tag);
-// fp32 operands as two scaled fp16 terms on the fp16 matrix cores (kernels_gemm_half.hip): input and weight gradients; same
-// contract as the bf16 path above.
+// fp32 operands as two scaled fp16 terms on the fp16 matrix cores: input gradients (kernels_gemm_half.hip) and weight gradients (A transposed,
+// kernels_gemm_half_tn.hip); same contract as the bf16 path above.
 bool varco_gemm_half_usable(const GemmArgs& g);
-hipError_t varco_launch_gemm_half(const GemmArgs& g, hipStream_t stream, const LaunchTag& tag, int32_t* split_used);
+hipError_t varco_launch_gemm_half(const GemmArgs& g, hipStream_t stream, const LaunchTag& tag);
+hipError_t varco_launch_gemm_half_tn(const GemmArgs& g, hipStream_t stream, const LaunchTag& tag, int32_t* split_used);
 // Copies of weight matrices in the form the bf16 matrix-core kernels take, several per launch: (transpose ? h[c][r] : h[r][c])
 // for r < rows, c < cols, zero beyond.
 //   terms = 1: one rounded bf16 copy [row][pitch], rows_padded = rows;

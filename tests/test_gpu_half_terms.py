@@ -111,6 +111,12 @@ def test_weight_gradient_of_columns_of_any_magnitude(n, growth, fi, fo):
         assert (err <= _bound(n, a.T, dz) + floor).all()
 
 
+@pytest.mark.parametrize("fi,fo", [(5, 63), (63, 129), (65, 64), (127, 4), (128, 128), (129, 66), (192, 127), (193, 5), (256, 130), (257, 64), (321, 47)])
+@pytest.mark.parametrize("n", [31, 97])
+def test_weight_gradient_at_the_edges_of_tiles(n, fi, fo):
+    test_weight_gradient_of_columns_of_any_magnitude(n, 7, fi, fo)      # 64 columns a unit, 128 or 256 a tile, one tap and two
+
+
 def test_infinite_values_stay_in_their_rows_and_columns():
     n, fi, fo = 700, 128, 96
     rng = np.random.default_rng(9)
