@@ -683,7 +683,7 @@ hipError_t varco_launch_gemm(const GemmArgs& ga, hipStream_t stream, const Launc
         return e != hipSuccess ? e : finish(split);
     }
     if (varco_gemm_half_usable(ga)) {
-        if (!ga.a.transposed) return varco_launch_gemm_half(ga, stream, tag);
+        if (!ga.a.transposed) return varco_gemm_half_nt_usable(ga) ? varco_launch_gemm_half_nt(ga, stream, tag) : varco_launch_gemm_half(ga, stream, tag);
         int32_t split = 1;
         const hipError_t e = varco_launch_gemm_half_tn(ga, stream, tag, &split);
         return e != hipSuccess ? e : finish(split);

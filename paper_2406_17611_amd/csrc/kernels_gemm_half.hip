@@ -1,4 +1,5 @@
-// Input gradients of the dense feature transform of eq. (2) for fp32-stored activations, dM = dZ H^T, on the fp16 matrix units. Operands are scaled by
+// Input gradients of the dense feature transform of eq. (2) for fp32-stored activations, dM = dZ H^T, on the fp16 matrix units: what all gradients of that
+// storage type have in common, and the kernel for reductions of 17 to 64 and of more than 512 steps (65 to 512: kernels_gemm_half_nt.hip). Operands are scaled by
 // powers of two and every value is written as two fp16 terms,
 //     x s = h0 + h1 / 2048,   h0 = fp16(x s), h1 = fp16(2048 (x s - h0))
 // (the difference is exact in fp32; two 11-bit significands cover 23 of the 24 bits of x, the last one is lost for a quarter of
@@ -26,10 +27,7 @@
 // reduction steps is fetched into registers one step ahead, then split and written to LDS as two planes of
 // fp16 rows (one output index per row, reduction index contiguous, 80-byte pitch). A is split here; B is the library's own split copy of the
 // weights (varco_launch_prep_weights), zero-padded to whole tiles and copied as is. The ReLU mask of the backward pass is applied before
-// the split. Three bf16 terms / this, 2,449,029 rows: masked dZ (256 wide) times two 256 x 256 weights 4.47 / 3.50 ms; 169,343 rows: one
-// masked input gradient 161 / 133 us.
-// (Measured and not kept: 64 rows per workgroup, expanded once for all columns, weights straight from the L2 as operands: 3.0 to 3.9 ms
-// for the first, bound by the vector memory path.)
+// the split.
 #include <algorithm>
 #include <type_traits>
 

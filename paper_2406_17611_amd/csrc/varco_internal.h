@@ -339,10 +339,12 @@ hipError_t varco_launch_gemm_tn_bf16(const GemmArgs& g, hipStream_t stream, cons
 // fp32 operands as sums of bf16 terms on the bf16 matrix cores (kernels_gemm_split.hip): the transform.
 bool varco_gemm_split_usable(const GemmArgs& g);
 hipError_t varco_launch_gemm_split(const GemmArgs& g, hipStream_t stream, const LaunchTag& tag);
-// fp32 operands as two scaled fp16 terms on the fp16 matrix cores: input gradients (kernels_gemm_half.hip) and weight gradients (A transposed,
-// kernels_gemm_half_tn.hip); same contract as the bf16 path above.
+// fp32 operands as two scaled fp16 terms on the fp16 matrix cores: input gradients (kernels_gemm_half.hip, kernels_gemm_half_nt.hip) and weight
+// gradients (A transposed, kernels_gemm_half_tn.hip); same contract as the bf16 path above.
 bool varco_gemm_half_usable(const GemmArgs& g);
 hipError_t varco_launch_gemm_half(const GemmArgs& g, hipStream_t stream, const LaunchTag& tag);
+bool varco_gemm_half_nt_usable(const GemmArgs& g);      // input gradients with 65 to 512 reduction steps (kernels_gemm_half_nt.hip)
+hipError_t varco_launch_gemm_half_nt(const GemmArgs& g, hipStream_t stream, const LaunchTag& tag);
 hipError_t varco_launch_gemm_half_tn(const GemmArgs& g, hipStream_t stream, const LaunchTag& tag, int32_t* split_used);
 // Copies of weight matrices in the form the bf16 matrix-core kernels take, several per launch: (transpose ? h[c][r] : h[r][c])
 // for r < rows, c < cols, zero beyond.

@@ -61,6 +61,24 @@ def test_short_input_gradient_rows_of_any_magnitude(fo, growth):
     test_input_gradient_rows_of_any_magnitude(fo, growth)      # one stage or two, with a remainder or none
 
 
+@pytest.mark.parametrize("fi,fo", [(1, 65), (31, 127), (33, 128), (64, 129), (129, 159), (255, 192), (257, 225), (300, 256), (15, 257), (65, 289), (128, 320), (250, 511), (48, 512), (40, 516)])
+@pytest.mark.parametrize("n,accumulate", [(1, False), (33, True), (63, False), (64, True), (8225, False)])
+def test_input_gradient_at_the_edges_of_blocks(n, accumulate, fi, fo):
+    """Rows in blocks of 32 or 64 of workgroups that walk over them, columns in units of 16 or 32 of wavefronts, every number of stages."""
+    rng = np.random.default_rng(n + fi + fo)
+    d, xo = (rng.standard_normal((n, fo)).astype(np.float32) for _ in range(2))
+    h = synth.glorot(fi, fo, 3, 1).astype(np.float32)
+    old = rng.standard_normal((n + 1, fi)).astype(np.float32)
+    out = dev(old)
+    _context(fi, fo).transform_bwd_input(0, dev(d), dev(xo), dev(h), out[:n], accumulate)
+    torch.cuda.synchronize()
+    dz, got = d.astype(np.float64) * (xo > 0), out.cpu().numpy()
+    want = dz @ h.astype(np.float64).T + (old[:n] if accumulate else 0.0)
+    slack = 2.0 ** -24 * np.abs(want) if accumulate else 0.0          # the addition's own rounding
+    assert (np.abs(got[:n] - want) <= _bound(fo, dz, h.astype(np.float64).T) + slack).all()
+    assert np.array_equal(got[n], old[n])                             # the row behind the last one
+
+
 @pytest.mark.parametrize("fi,fo", [(4, 4), (75, 47), (64, 65), (130, 136)])
 @pytest.mark.parametrize("growth", [0, 7])
 @pytest.mark.parametrize("n", [1, 31, 33, 2333])
