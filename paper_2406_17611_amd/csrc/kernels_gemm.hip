@@ -688,6 +688,7 @@ hipError_t varco_launch_gemm(const GemmArgs& ga, hipStream_t stream, const Launc
         const hipError_t e = varco_launch_gemm_half_tn(ga, stream, tag, &split);
         return e != hipSuccess ? e : finish(split);
     }
+    if (varco_gemm_split_rows_usable(ga)) return varco_launch_gemm_split_rows(ga, stream, tag);
     if (varco_gemm_split_usable(ga)) return varco_launch_gemm_split(ga, stream, tag);
     // A is M x K: k-contiguous as stored unless transposed. B is K x N: k-contiguous only when transposed.
     const bool a_kc = !ga.a.transposed, b_kc = ga.b.transposed;

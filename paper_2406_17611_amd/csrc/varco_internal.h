@@ -336,9 +336,11 @@ hipError_t varco_launch_gemm_bf16(const GemmArgs& g, hipStream_t stream, const L
 bool varco_gemm_tn_bf16_usable(const GemmArgs& g);
 void varco_gemm_tn_bf16_tile(int32_t m, int32_t n, int32_t* bm, int32_t* bn, int32_t* per_cu);
 hipError_t varco_launch_gemm_tn_bf16(const GemmArgs& g, hipStream_t stream, const LaunchTag& tag, int32_t* split_used);
-// fp32 operands as sums of bf16 terms on the bf16 matrix cores (kernels_gemm_split.hip): the transform.
+// fp32 operands as sums of bf16 terms on the bf16 matrix cores (kernels_gemm_split.hip, kernels_gemm_split_rows.hip): the transform.
 bool varco_gemm_split_usable(const GemmArgs& g);
 hipError_t varco_launch_gemm_split(const GemmArgs& g, hipStream_t stream, const LaunchTag& tag);
+bool varco_gemm_split_rows_usable(const GemmArgs& g);   // of 65 to 256 reduction steps, where weights in registers are faster
+hipError_t varco_launch_gemm_split_rows(const GemmArgs& g, hipStream_t stream, const LaunchTag& tag);
 // fp32 operands as two scaled fp16 terms on the fp16 matrix cores: input gradients (kernels_gemm_half.hip, kernels_gemm_half_nt.hip) and weight
 // gradients (A transposed, kernels_gemm_half_tn.hip); same contract as the bf16 path above.
 bool varco_gemm_half_usable(const GemmArgs& g);

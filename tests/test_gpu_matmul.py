@@ -251,3 +251,38 @@ def test_non_finite_operand_stays_in_its_row(terms):
         assert np.isnan(got[137]).all()
     keep = np.arange(n) != 137
     assert_close(got[keep], ref[keep], "rows without the infinite element", _bound(terms, fi))
+
+
+@pytest.mark.parametrize("fi,fo", [(65, 8), (75, 200), (96, 72), (100, 256), (127, 130), (131, 40), (160, 129), (192, 136), (200, 257), (224, 65), (255, 512), (256, 256)])
+@pytest.mark.parametrize("taps", [1, 2])
+@pytest.mark.parametrize("n", [2, 31, 33, 3001, 32801])
+def test_transform_at_the_edges_of_blocks(n, taps, fi, fo):
+    """Rows in blocks of 32 of workgroups that walk over them, columns in units of 16 or 32 of wavefronts, every number of stages, rows
+    that start at any word of a larger tensor; one tap added to what is there, two written."""
+    from test_gpu_weight_gradients import _linked_context
+    rng = np.random.default_rng(n + fi + fo)
+    y = [rng.standard_normal((n, fi)).astype(np.float32) for _ in range(taps)]
+    h = [synth.glorot(fi, fo, 3, 1 + t).astype(np.float32) for t in range(taps)]
+    old = rng.standard_normal((n + 1, fo)).astype(np.float32)
+    out = dev(old)
+    held = [torch.zeros(n * fi + 1, device="cuda") for _ in y]
+    for t, one in zip(held, y):
+        t[1:] = dev(one).flatten()
+    rows = [t[1:].view(n, fi) for t in held]
+    if taps == 1:
+        ctx, parts = _ctx(fi, fo, vb.ACT_RELU, 3), None
+        ctx.transform_fwd(0, rows[0], dev(h[0]), out[:n], True, True)
+    else:
+        ctx, parts = _linked_context(n, 2, fi, fo, vb.F32, 3)
+        ctx.network_taps_fwd(0, rows, [dev(w) for w in h], out[:n])
+    torch.cuda.synchronize()
+    want = sum(a.astype(np.float64) @ b.astype(np.float64) for a, b in zip(y, h)) + (old[:n] if taps == 1 else 0.0)
+    size = sum(np.abs(a) @ np.abs(b) for a, b in zip(y, h))
+    # terms left out are below 2^-24 of a product; one rounding of 2^-24 per instruction (six per 32 steps) on a partial sum that is at most `size`:
+    # sqrt of their number for independent ones, four times that for the tail; the addition rounds once more
+    bound = (2.0 ** -24 + 4 * 2.0 ** -24 * np.sqrt(6 * taps * np.ceil(fi / 32))) * size + (2.0 ** -24 * np.abs(want) if taps == 1 else 0.0)
+    got = out.cpu().numpy()
+    assert (np.abs(got[:n] - np.maximum(want, 0.0)) <= bound).all()
+    assert np.array_equal(got[n], old[n])                             # the row behind the last one
+    ctx.close()
+    del parts
