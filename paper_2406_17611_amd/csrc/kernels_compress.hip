@@ -39,7 +39,7 @@ __global__ __launch_bounds__(kBlock) void compress_kernel(MaskRule rule, const i
 
 // Encoder and decoder through LDS. Kept positions are spread over the whole row, so a row's cache lines all travel whether
 // 4 bytes of a line are wanted or 128, and element-wise accesses (64 scattered addresses per instruction) cost the vector
-// memory unit about a cycle each: instead a wavefront moves whole rows with 16-byte accesses, rows_in_flight of them at a
+// memory unit about a cycle each: instead a wavefront moves whole rows with 16-byte accesses, a group of them at a
 // time, and picks (encoder) or places (decoder) the kept elements in LDS. 450,000 rows
 // of 256, element-wise -> through LDS: decoder 265 -> 116 us (fp32, k = 32), 197 -> 64 (bf16, k = 64); encoder 197 -> 133
 // (fp32, k = 128), 136 -> 46 (bf16, k = 64); decoder with sum 224 -> 196 (fp32, k = 32), 194 -> 135
@@ -51,10 +51,10 @@ __global__ __launch_bounds__(kBlock) void compress_kernel(MaskRule rule, const i
 //   MODE 0: z[i, j] = x[row_i, pi(j)];  1: x[row_i, :] = 0 except x[row_i, pi(j)] = z[i, j];  2: x[row_i, pi(j)] += z[i, j],
 //   in LDS on the old row, which is written back whole: what is not added to keeps its bits
 // S: the storage word (fp32 or bf16 bits); V: elements per access to x (16 bytes, or 1 for unaligned rows); PE: elements of z
-// per lane (2 for bf16 pairs); ONE: a row is at most one access per lane.
+// per lane (2 for bf16 pairs); U: rows of a group; ONE: a row is at most one access per lane.
 constexpr int kCodecBlock = 64;
+constexpr int64_t kL2Bytes = int64_t(8) * 4 << 20;      // eight L2 caches of 4 MB
 constexpr int64_t kCodecGrid = int64_t(1) << 24;      // a launch holds fewer than 2^32 threads
-constexpr int rows_in_flight(int mode) { return mode == 2 ? 2 : 4; }      // (two, with rows read and written: 183 us against 192)
 template <typename S>
 __device__ __forceinline__ S add_words(S x, S z) {
     if constexpr (sizeof(S) == 4)
@@ -63,10 +63,9 @@ __device__ __forceinline__ S add_words(S x, S z) {
         return float_to_bf16(bf16_to_float(x) + bf16_to_float(z));
 }
 
-template <typename S, int MODE, int V, int PE, bool ONE>
+template <typename S, int MODE, int U, int V, int PE, bool ONE>
 __global__ __launch_bounds__(kCodecBlock) void codec_rows_kernel(MaskRule rule, const int32_t* __restrict__ gids, const int32_t* __restrict__ rows,
                                                                  int64_t n_rows, S* x, int64_t ldx, S* z, int lpe_log2) {
-    constexpr int U = rows_in_flight(MODE);
     typedef S Vec __attribute__((ext_vector_type(V)));
     typedef S Pair __attribute__((ext_vector_type(PE)));
     extern __shared__ __attribute__((aligned(16))) unsigned char codec_lds[];
@@ -77,15 +76,18 @@ __global__ __launch_bounds__(kCodecBlock) void codec_rows_kernel(MaskRule rule, 
     const int lpe = 1 << lpe_log2, sub = lane >> lpe_log2, jl = lane & (lpe - 1), n_sub = 64 >> lpe_log2;
     for (int64_t r0 = int64_t(blockIdx.x) * U; r0 < n_rows; r0 += int64_t(gridDim.x) * U) {      // (once, up to kCodecGrid workgroups)
         const int n_here = int(min(int64_t(U), n_rows - r0));
-        const int64_t i = min(r0 + (lane & (U - 1)), n_rows - 1);      // lane u: row u of the group (past the end: the last row)
-        const int32_t gid = gids[i], src = rows ? rows[i] : 0;
-        int64_t at[U];                                   // element offset of the group's rows in x
-#pragma unroll
-        for (int u = 0; u < U; ++u) at[u] = (rows ? int64_t(__shfl(src, u)) : min(r0 + u, n_rows - 1)) * ldx;
         if constexpr (MODE == 1) {
             for (int u = 0; u < U; ++u)
                 for (int c = lane * V; c < width; c += 64 * V) *reinterpret_cast<Vec*>(buf + u * pitch + c) = Vec(S(0));
-        } else if constexpr (ONE) {
+        }
+        const int64_t i = min(r0 + (lane & (U - 1)), n_rows - 1);      // lane u: row u of the group (past the end: the last row)
+        const int32_t gid = gids[i], src = rows ? rows[i] : 0;
+        const MaskAffine rm = varco_affine(rule, uint32_t(gid));
+        const uint32_t ab = rm.a | (rm.b << 16);
+        int64_t at[U];                                   // element offset of the group's rows in x
+#pragma unroll
+        for (int u = 0; u < U; ++u) at[u] = (rows ? int64_t(__shfl(src, u)) : min(r0 + u, n_rows - 1)) * ldx;
+        if constexpr (MODE != 1 && ONE) {
             Vec v[U];
             const int own = min(lane * V, width - V);    // lanes past the row repeat its last access (never stored)
 #pragma unroll
@@ -93,13 +95,11 @@ __global__ __launch_bounds__(kCodecBlock) void codec_rows_kernel(MaskRule rule, 
 #pragma unroll
             for (int u = 0; u < U; ++u)
                 if (lane * V < width) *reinterpret_cast<Vec*>(buf + u * pitch + lane * V) = v[u];
-        } else {
+        } else if constexpr (MODE != 1) {
             for (int c = lane * V; c < width; c += 64 * V)
 #pragma unroll
                 for (int u = 0; u < U; ++u) *reinterpret_cast<Vec*>(buf + u * pitch + c) = *reinterpret_cast<const Vec*>(x + at[u] + c);
         }
-        const MaskAffine rm = varco_affine(rule, uint32_t(gid));
-        const uint32_t ab = rm.a | (rm.b << 16);
         __builtin_amdgcn_wave_barrier();
         // the kept elements: a group of lanes serves one row, the groups different rows
         for (int u0 = 0; u0 < n_here; u0 += n_sub) {
@@ -254,6 +254,10 @@ unsigned grid_for(int64_t n_rows, int g_log2) {
     if (blocks < 1) blocks = 1;
     return unsigned(blocks);
 }
+// For kernels that move an element per lane: 16 resident workgroups on each of the 256 compute units, which walk on. One place each, as
+// for 16-byte accesses, costs them 5 to 10 % (216,537 rows of 188 bf16 values, 23 of them kept, encoder 33.5 -> 35.7 us; 129,597 rows of 118 fp32
+// values, 39 kept, decoder with sum 32.2 -> 33.7).
+unsigned walking_grid(int64_t n_rows, int g_log2) { return std::min(grid_for(n_rows, g_log2), 256u * 16u); }
 
 // Per halo row: its position rule (element j sits at position (a j + b) mod width) and its row in the compressed
 // buffer, for the kernels that transform halo rows from their received elements.
@@ -321,8 +325,8 @@ hipError_t launch_whole_rows(const MaskRule& rule, const int32_t* rows, int64_t 
                      ((reinterpret_cast<uintptr_t>(x) | reinterpret_cast<uintptr_t>(z)) & 15u) == 0;
     const int gl = group_log2(vec ? rule.width / V16 : rule.width);
     auto go = [&](auto vc) {
-        hipLaunchKernelGGL((whole_rows_kernel<S, decltype(vc)::value, TO_Z, ADD>), dim3(grid_for(n_rows, gl)), dim3(kBlock), 0, stream, rows, n_rows,
-                           static_cast<S*>(x), ldx, static_cast<S*>(z), int32_t(rule.width), gl);
+        hipLaunchKernelGGL((whole_rows_kernel<S, decltype(vc)::value, TO_Z, ADD>), dim3(vec ? grid_for(n_rows, gl) : walking_grid(n_rows, gl)), dim3(kBlock), 0,
+                           stream, rows, n_rows, static_cast<S*>(x), ldx, static_cast<S*>(z), int32_t(rule.width), gl);
     };
     if (vec)
         go(std::integral_constant<int, V16>{});
@@ -331,12 +335,11 @@ hipError_t launch_whole_rows(const MaskRule& rule, const int32_t* rows, int64_t 
     return hipGetLastError();
 }
 
-template <typename T, int MODE>
+template <typename T, int MODE, int U = 4>
 hipError_t launch_codec_rows(const MaskRule& rule, const int32_t* gids, const int32_t* rows, int64_t n_rows, void* x, int64_t ldx, void* z,
                              hipStream_t stream) {
     using S = std::conditional_t<sizeof(T) == 2, uint16_t, uint32_t>;
     constexpr int V16 = 16 / int(sizeof(S));
-    constexpr int U = rows_in_flight(MODE);
     const bool vec = rule.width % V16 == 0 && ldx % V16 == 0 && (reinterpret_cast<uintptr_t>(x) & 15u) == 0;
     const bool pair = sizeof(S) == 2 && rule.k % 2 == 0 && (reinterpret_cast<uintptr_t>(z) & 3u) == 0;
     const bool one = int(rule.width) <= 64 * (vec ? V16 : 1);
@@ -344,7 +347,7 @@ hipError_t launch_codec_rows(const MaskRule& rule, const int32_t* gids, const in
     const size_t lds = size_t(U) * ((rule.width + 7) & ~7u) * sizeof(S);
     const int64_t blocks = std::min((n_rows + U - 1) / U, kCodecGrid);
     auto go = [&](auto vc, auto pc, auto oc) {
-        hipLaunchKernelGGL((codec_rows_kernel<S, MODE, decltype(vc)::value, decltype(pc)::value, decltype(oc)::value>), dim3(unsigned(blocks)),
+        hipLaunchKernelGGL((codec_rows_kernel<S, MODE, U, decltype(vc)::value, decltype(pc)::value, decltype(oc)::value>), dim3(unsigned(blocks)),
                            dim3(kCodecBlock), lds, stream, rule, gids, rows, n_rows, static_cast<S*>(x), ldx, static_cast<S*>(z), lpe);
     };
     auto with_one = [&](auto vc, auto pc) {
@@ -371,7 +374,7 @@ hipError_t launch_compress_t(const MaskRule& rule, const int32_t* gids, const in
     if (rule.k == rule.width) return launch_whole_rows<T, true, false>(rule, rows, n_rows, const_cast<void*>(x), ldx, z, stream);
     if (codec_rows_pay<T, 0>(rule, x, ldx)) return launch_codec_rows<T, 0>(rule, gids, rows, n_rows, const_cast<void*>(x), ldx, z, stream);
     const int gl = group_log2(rule.k);
-    hipLaunchKernelGGL(compress_kernel<T>, dim3(grid_for(n_rows, gl)), dim3(kBlock), 0, stream, rule, gids, rows, n_rows,
+    hipLaunchKernelGGL(compress_kernel<T>, dim3(walking_grid(n_rows, gl)), dim3(kBlock), 0, stream, rule, gids, rows, n_rows,
                        static_cast<const T*>(x), ldx, static_cast<T*>(z), gl);
     return hipGetLastError();
 }
@@ -384,9 +387,14 @@ hipError_t launch_decompress_t(const MaskRule& rule, const int32_t* gids, const 
         return accumulate ? launch_whole_rows<T, false, true>(rule, rows, n_rows, x, ldx, zw, stream)
                           : launch_whole_rows<T, false, false>(rule, rows, n_rows, x, ldx, zw, stream);
     if (!accumulate) return launch_codec_rows<T, 1>(rule, gids, rows, n_rows, x, ldx, zw, stream);
-    if (codec_rows_pay<T, 2>(rule, x, ldx)) return launch_codec_rows<T, 2>(rule, gids, rows, n_rows, x, ldx, zw, stream);
+    if (codec_rows_pay<T, 2>(rule, x, ldx)) {
+        // rows read and written, from memory: two at a time (256 fp32 values, 450,007 rows 183 us against 192); in the L2 caches: four (9,064 rows
+        // of 224 5.9 against 6.3)
+        if (n_rows * int64_t(rule.width) * int64_t(sizeof(T)) <= kL2Bytes) return launch_codec_rows<T, 2, 4>(rule, gids, rows, n_rows, x, ldx, zw, stream);
+        return launch_codec_rows<T, 2, 2>(rule, gids, rows, n_rows, x, ldx, zw, stream);
+    }
     const int gl = group_log2(rule.k);
-    hipLaunchKernelGGL(decompress_add_kernel<T>, dim3(grid_for(n_rows, gl)), dim3(kBlock), 0, stream, rule, gids, rows, n_rows,
+    hipLaunchKernelGGL(decompress_add_kernel<T>, dim3(walking_grid(n_rows, gl)), dim3(kBlock), 0, stream, rule, gids, rows, n_rows,
                        static_cast<const T*>(z), static_cast<T*>(x), ldx, gl);
     return hipGetLastError();
 }
@@ -404,7 +412,7 @@ hipError_t launch_accumulate_t(const MaskRule& rule, const int32_t* gids, const 
             break;
         }
     const int gl = group_log2(rule.k / ev);
-    const dim3 grid(grid_for(n_rows, gl)), block(kBlock);
+    const dim3 grid(walking_grid(n_rows, gl)), block(kBlock);
     const T* ret = static_cast<const T*>(returned);
     T* xt = static_cast<T*>(x);
     if (ev == 4)
