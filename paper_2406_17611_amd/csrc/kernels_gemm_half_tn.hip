@@ -49,7 +49,13 @@ struct WeightGrad {
     int32_t split, stages_per_split;
     int32_t units_per_tap, units;      // units of 64 columns of A
     int32_t tiles_n, inner;            // tiles along B, and in all
+    int32_t first;                     // workgroup of a launch of several (a multiple of eight)
 };
+struct WeightGrads {
+    WeightGrad job[kMaxWeightJobs];
+    int32_t n;
+};
+enum Gate { kOpen, kMasked, kEither };      // B as it is, masked, or as the job says
 
 // Descriptor of `bytes` bytes from p on; what lies behind reads as zero.
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t rows_at(const float* p, int32_t bytes) {
@@ -75,8 +81,8 @@ __device__ __forceinline__ float& part(float4& v, int i) { return i == 0 ? v.x :
 __device__ __forceinline__ int slot(int col, int p) { return col ^ p; }
 
 // UM, UN: units of 64 columns of the two operands in a tile.
-template <int UM, int UN, bool GATE>
-__global__ __launch_bounds__(kThreads, 2) void weight_grad_kernel(WeightGrad g) {
+template <int UM, int UN, Gate GATE>
+__device__ __forceinline__ void weight_grad(const WeightGrad& g, uint32_t block) {
     constexpr int BM = 64 * UM, BN = 64 * UN, COLS = BM + BN;
     constexpr int WM = 4, WN = 2, TMB = BM / 32 / WM, TNB = BN / 32 / WN;
     constexpr int kStage = COLS / 32 * 4 * kFragment;                  // fp16 elements: [32 columns][16 nodes][term]
@@ -86,7 +92,7 @@ __global__ __launch_bounds__(kThreads, 2) void weight_grad_kernel(WeightGrad g) 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
-    const int32_t xcd = blockIdx.x & 7, within = blockIdx.x >> 3;
+    const int32_t xcd = block & 7, within = block >> 3;
     const int32_t in = within % g.inner, z = (within / g.inner) * 8 + xcd;
     if (z >= g.split) return;                  // whole workgroup leaves together: no barrier is skipped
     const int32_t all = (g.nodes + BK - 1) / BK;
@@ -146,7 +152,7 @@ __global__ __launch_bounds__(kThreads, 2) void weight_grad_kernel(WeightGrad g) 
 
     // NK: nodes per lane (8: a wavefront serves 64 columns, 4: 32).
     auto run = [&](auto is_a, auto nk, auto idle) __attribute__((always_inline)) {
-        constexpr bool A = decltype(is_a)::value, IDLE = decltype(idle)::value, G = GATE && !A;
+        constexpr bool A = decltype(is_a)::value, IDLE = decltype(idle)::value, G = GATE != kOpen && !A;
         constexpr int NK = decltype(nk)::value, NG = BK / NK;          // node groups
         constexpr int WC = 4 * 64 / NG;                                // columns of this wavefront
         const int w = A ? wave : wave - 4;
@@ -158,6 +164,7 @@ __global__ __launch_bounds__(kThreads, 2) void weight_grad_kernel(WeightGrad g) 
         const float* const src = A ? g.a[tap] : g.b;
         const int64_t ld = A ? g.lda : g.ldb;
         const bool live = !IDLE && first < extent && (!A || unit < g.units);
+        const bool masked = GATE == kMasked || g.gate;
         const int32_t row_bytes = int32_t(ld) * 4;
         const uint32_t off = uint32_t(q * NK) * uint32_t(row_bytes) + (first + 4 * cg < extent ? 16u * cg : 0u);
         float4 rx[NK], ry[G ? NK : 1];
@@ -165,7 +172,7 @@ __global__ __launch_bounds__(kThreads, 2) void weight_grad_kernel(WeightGrad g) 
             if (IDLE) return;
             const int32_t k0 = t * BK, rows = min(BK, g.nodes - k0), bytes = live && t < t_end ? (rows - 1) * row_bytes + (extent - first) * 4 : 0;
             const auto from = rows_at(src + int64_t(k0) * ld + first, bytes);
-            const auto mask = rows_at(G ? g.gate + int64_t(k0) * ld + first : src, bytes);
+            const auto mask = rows_at(G && masked ? g.gate + int64_t(k0) * ld + first : src, bytes);
 #pragma unroll
             for (int kk = 0; kk < NK; ++kk) {
                 rx[kk] = load_row4(from, off, kk * row_bytes);
@@ -182,7 +189,7 @@ __global__ __launch_bounds__(kThreads, 2) void weight_grad_kernel(WeightGrad g) 
 #pragma unroll
                 for (int ii = 0; ii < 4; ++ii) {
                     float& x = part(rx[kk], ii);
-                    if constexpr (G) x = part(ry[kk], ii) > 0.f ? x : 0.f;
+                    if constexpr (G) x = part(ry[kk], ii) > 0.f || !masked ? x : 0.f;
                     m[ii] = fmaxf(m[ii], fabsf(x));
                 }
             float sc[4], f[4] = {1.f, 1.f, 1.f, 1.f};
@@ -265,12 +272,22 @@ __global__ __launch_bounds__(kThreads, 2) void weight_grad_kernel(WeightGrad g) 
     }
 }
 
-}  // namespace
+template <int UM, int UN, Gate GATE>
+__global__ __launch_bounds__(kThreads, 2) void weight_grad_kernel(WeightGrad g) {
+    weight_grad<UM, UN, GATE>(g, blockIdx.x);
+}
 
-// Tiles of 256 columns of A unless tiles of 128 cover them with fewer; 64 columns of B where that is all there are.
-hipError_t varco_launch_gemm_half_tn(const GemmArgs& ga, hipStream_t stream, const LaunchTag& tag, int32_t* split_used) {
+// Products of several layers: each workgroup belongs to one of them.
+template <int UN>
+__global__ __launch_bounds__(kThreads, 2) void weight_grads_kernel(WeightGrads all) {
+    int i = 0;
+    while (i + 1 < all.n && int32_t(blockIdx.x) >= all.job[i + 1].first) ++i;
+    weight_grad<2, UN, kEither>(all.job[i], blockIdx.x - all.job[i].first);
+}
+
+// The product `ga` in tiles of 64 UM x 64 UN, its reduction in about `split` slabs; workgroups in all.
+int64_t make_job(const GemmArgs& ga, int um, int un, int64_t split_wanted, WeightGrad& g) {
     const int32_t products = ga.c_dual ? 2 : 1;
-    WeightGrad g{};
     auto f32 = [](const void* p) { return static_cast<const float*>(p); };
     g.a[0] = f32(ga.a.ptr), g.a[1] = ga.c_dual ? f32(ga.a_dual) : g.a[0];
     g.b = f32(ga.b.ptr), g.gate = f32(ga.b.gate);
@@ -279,31 +296,67 @@ hipError_t varco_launch_gemm_half_tn(const GemmArgs& ga, hipStream_t stream, con
     g.c[0] = static_cast<float*>(ga.c), g.c[1] = static_cast<float*>(ga.c_dual), g.partial = ga.partial;
     g.ldc = ga.ldc, g.accumulate = ga.accumulate ? 1 : 0;
     g.units_per_tap = (ga.m + 63) / 64, g.units = products * g.units_per_tap;
-    const bool wide = (g.units + 3) / 4 * 4 <= (g.units + 1) / 2 * 2;
-    const int um = wide ? 4 : 2, un = ga.n <= 64 ? 1 : 2;
     g.tiles_n = (ga.n + 64 * un - 1) / (64 * un);
     g.inner = (g.units + um - 1) / um * g.tiles_n;
     const int32_t stages = (ga.k + BK - 1) / BK;
-    int32_t split = std::max(1, std::min(ga.split_k, stages));
+    const int32_t split = int32_t(std::max<int64_t>(1, std::min<int64_t>(split_wanted, stages)));
     g.stages_per_split = std::max(1, (stages + split - 1) / split);
-    split = std::max(1, (stages + g.stages_per_split - 1) / g.stages_per_split);
-    g.split = split;
-    if (split > 1 && !ga.partial) return hipErrorInvalidValue;
-    const int64_t blocks = int64_t((split + 7) / 8 * 8) * g.inner;
-    if (blocks > 0x7FFFFFFF / kThreads) return hipErrorInvalidValue;
-    *split_used = split;
+    g.split = std::max(1, (stages + g.stages_per_split - 1) / g.stages_per_split);
+    return int64_t((g.split + 7) / 8 * 8) * g.inner;
+}
+
+}  // namespace
+
+int64_t varco_gemm_half_tn_tiles(const GemmArgs& ga) {
+    const int32_t units = (ga.c_dual ? 2 : 1) * ((ga.m + 63) / 64);
+    return int64_t((units + 1) / 2) * ((ga.n + 127) / 128);
+}
+
+hipError_t varco_launch_gemm_half_tn_jobs(const GemmArgs* ga, int32_t n, hipStream_t stream, const LaunchTag& tag, int32_t* split_used) {
+    if (n < 1 || n > kMaxWeightJobs) return hipErrorInvalidValue;
+    bool narrow = true;
+    for (int32_t i = 0; i < n; ++i) narrow = narrow && ga[i].n <= 64;
+    WeightGrads all{};
+    all.n = n;
+    int64_t blocks = 0;
+    for (int32_t i = 0; i < n; ++i) {
+        all.job[i].first = int32_t(blocks);
+        blocks += make_job(ga[i], 2, narrow ? 1 : 2, ga[i].split_k, all.job[i]);
+        if (blocks > 0x7FFFFFFF / kThreads || (all.job[i].split > 1 && !ga[i].partial)) return hipErrorInvalidValue;
+        split_used[i] = all.job[i].split;
+    }
     const dim3 grid{unsigned(blocks)};
     tag.begin(stream);
+    if (narrow)
+        hipLaunchKernelGGL(weight_grads_kernel<1>, grid, dim3(kThreads), 0, stream, all);
+    else
+        hipLaunchKernelGGL(weight_grads_kernel<2>, grid, dim3(kThreads), 0, stream, all);
+    tag.end(stream);
+    return hipGetLastError();
+}
+
+// Tiles of 256 columns of A unless tiles of 128 cover them with fewer; 64 columns of B where that is all there are.
+hipError_t varco_launch_gemm_half_tn(const GemmArgs& ga, hipStream_t stream, const LaunchTag& tag, int32_t* split_used) {
+    const int32_t units = (ga.c_dual ? 2 : 1) * ((ga.m + 63) / 64);
+    const bool wide = (units + 3) / 4 * 4 <= (units + 1) / 2 * 2;
+    const int un = ga.n <= 64 ? 1 : 2;
+    WeightGrad g{};
+    const int64_t blocks = make_job(ga, wide ? 4 : 2, un, ga.split_k, g);
+    if (g.split > 1 && !ga.partial) return hipErrorInvalidValue;
+    if (blocks > 0x7FFFFFFF / kThreads) return hipErrorInvalidValue;
+    *split_used = g.split;
+    const dim3 grid{unsigned(blocks)};
+    tag.begin(stream);
+    using std::integral_constant;
     auto go = [&](auto m, auto n, auto gt) {
         hipLaunchKernelGGL((weight_grad_kernel<decltype(m)::value, decltype(n)::value, decltype(gt)::value>), grid, dim3(kThreads), 0, stream, g);
     };
     auto with_gate = [&](auto m, auto n) {
         if (ga.b.gate)
-            go(m, n, std::true_type{});
+            go(m, n, integral_constant<Gate, kMasked>{});
         else
-            go(m, n, std::false_type{});
+            go(m, n, integral_constant<Gate, kOpen>{});
     };
-    using std::integral_constant;
     auto with_n = [&](auto m) {
         if (un == 1)
             with_gate(m, integral_constant<int, 1>{});

@@ -348,6 +348,10 @@ hipError_t varco_launch_gemm_half(const GemmArgs& g, hipStream_t stream, const L
 bool varco_gemm_half_nt_usable(const GemmArgs& g);      // input gradients with 65 to 512 reduction steps (kernels_gemm_half_nt.hip)
 hipError_t varco_launch_gemm_half_nt(const GemmArgs& g, hipStream_t stream, const LaunchTag& tag);
 hipError_t varco_launch_gemm_half_tn(const GemmArgs& g, hipStream_t stream, const LaunchTag& tag, int32_t* split_used);
+// Several of them by one launch, of 128 x 128 tiles (128 x 64 where none has more than 64 columns) and g[i].split_k slabs; their tiles.
+constexpr int kMaxWeightJobs = 8;
+hipError_t varco_launch_gemm_half_tn_jobs(const GemmArgs* g, int32_t n, hipStream_t stream, const LaunchTag& tag, int32_t* split_used);
+int64_t varco_gemm_half_tn_tiles(const GemmArgs& g);
 // Copies of weight matrices in the form the bf16 matrix-core kernels take, several per launch: (transpose ? h[c][r] : h[r][c])
 // for r < rows, c < cols, zero beyond.
 //   terms = 1: one rounded bf16 copy [row][pitch], rows_padded = rows;

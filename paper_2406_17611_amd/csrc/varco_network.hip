@@ -54,12 +54,14 @@ size_t prod_floats(const varco_ctx* ctx, int32_t layer, int64_t k) {
 // and partition after partition / one round / now:
 //   bf16  512 x 512   2,449,029 rows, 32 parts  2.1e-7 / 1.2e-6 / 2.0e-7  (1.81, 2.26 ms)
 //                     169,343 rows, 4 parts     1.5e-7 / 2.6e-7 / 1.3e-7  (158, 210 us: writing and reading the partial products)
+int64_t longest_slab(const varco_ctx* ctx, int32_t m, int32_t n, int64_t rows, int kind) {
+    const int64_t most = ctx->net.largest;
+    const int64_t split = kind == kGemmBf16 ? plain_bf16_split(m, n, most) : gemm_split_for(m, n, most, kind), alone = most / split;
+    return std::max<int64_t>(1, kind == kGemmExpanded ? alone * (137'500 + rows) / 73'300 : kind == kGemmBf16 ? alone + 4 * split + 16 * ctx->n_parts : alone);
+}
 int32_t wgrad_splits(const varco_ctx* ctx, int32_t m, int32_t n, int64_t rows, int kind, int products) {
     const int64_t step = kind == kGemmF32 ? 16 : 32;
-    const int64_t slots = wgrad_slots(m, n, kind, products), most = ctx->net.largest;
-    const int64_t split = kind == kGemmBf16 ? plain_bf16_split(m, n, most) : gemm_split_for(m, n, most, kind), alone = most / split;
-    const int64_t longest = kind == kGemmExpanded ? alone * (137'500 + rows) / 73'300 : kind == kGemmBf16 ? alone + 4 * split + 16 * ctx->n_parts : alone;
-    const int64_t round = slots * std::max<int64_t>(1, longest);
+    const int64_t slots = wgrad_slots(m, n, kind, products), round = slots * longest_slab(ctx, m, n, rows, kind);
     const int64_t rounds = std::max<int64_t>(1, std::min((rows + round - 1) / round, kPartialElems / (slots * products * m * n)));
     // (The stages of a slab follow one another, 1.4 us each: few rows take slabs of a single one. Beyond, and with large weights, adding the
     // partial products costs more; their sums are the more accurate all the same. Slabs of two stages / of one, one tap with its sums, us:
@@ -321,6 +323,8 @@ struct WeightSums {
     ReduceJob job[kMaxReduceJobs];
     int n = 0;
     size_t used = 0;              // floats of the workspace's partial buffer
+    GemmArgs waiting[kMaxWeightJobs];      // small products, for one launch at the end
+    int n_waiting = 0;
 };
 
 // A layer that transforms before it aggregates (kernels_class_first.hip).
@@ -387,6 +391,14 @@ int32_t class_fwd(varco_ctx* ctx, Workspace& ws, const varco_network_buffers& b,
     return VARCO_OK;
 }
 
+int32_t sum_later(varco_ctx* ctx, const GemmArgs& g, int32_t split, WeightSums& sums) {
+    const int products = g.c_dual ? 2 : 1;
+    if (sums.n + products > kMaxReduceJobs) return varco_fail(ctx, VARCO_ERR_STATE, "varco_network_backward: workspace too small");
+    for (int i = 0; split > 1 && i < products; ++i)
+        sums.job[sums.n++] = ReduceJob{g.partial + size_t(i) * split * g.m * g.n, static_cast<float*>(i ? g.c_dual : g.c), g.ldc, split, g.m, g.n, 0};
+    return VARCO_OK;
+}
+
 // One split product into the weight sums; `g` with everything but the split set.
 int32_t add_weight_product(varco_ctx* ctx, Workspace& ws, GemmArgs& g, WeightSums& sums, hipStream_t st) {
     const int products = g.c_dual ? 2 : 1;
@@ -398,11 +410,63 @@ int32_t add_weight_product(varco_ctx* ctx, Workspace& ws, GemmArgs& g, WeightSum
         return varco_fail(ctx, VARCO_ERR_STATE, "varco_network_backward: workspace too small");
     g.partial = ws.gemm + sums.used;
     VARCO_HIP(ctx, varco_launch_gemm(g, st, ctx->tag(VARCO_K_GEMM_WGRAD, 0, 2.0 * products * double(one) * double(g.k))));
-    for (int i = 0; split > 1 && i < products; ++i) {
-        sums.job[sums.n++] = ReduceJob{g.partial + size_t(i) * split * one, static_cast<float*>(i ? g.c_dual : g.c), g.ldc, split, g.m, g.n, 0};
-        sums.used += size_t(split) * one;
+    if (split > 1) sums.used += size_t(split) * one * products;
+    return sum_later(ctx, g, split, sums);
+}
+
+// Whether a layer's weight products may wait for the end of the pass, where one launch takes them all: stages of 32 rows times 128 x 128 tiles
+// are few, and nothing that the layers below write lies in what they read. A launch of few stages is a chain of round trips on a device that the
+// next one could use: a step of 2,000 nodes 16-32-8 55.4 -> 51.7 us, 16,000 nodes 32-64-8 92.9 -> 88.0, 3,997 nodes 93-208-120-14 200 -> 184;
+// 46 networks of 2,000 to 300,000 nodes 0.99 to 1.09 of the speed. Limits of 256 and 2,048 lose most of it (the last: 199); with 4,096 or 16,384 for
+// all, tiles of 256 columns that some shapes would take alone are missed (10,455 nodes 125-168-18 178 -> 185, 50,021 nodes 75-200-136-47 750 -> 788).
+constexpr int64_t kFewTiles = 1024, kFewNarrowTiles = 4096;
+bool may_wait(const varco_ctx* ctx, const varco_network_buffers& b, int32_t l, const GemmArgs& g, const WeightSums& sums) {
+    if (sums.n_waiting == kMaxWeightJobs || gemm_kind(g) != kGemmExpanded || int64_t((g.k + 31) / 32) * varco_gemm_half_tn_tiles(g) > (g.n <= 64 ? kFewNarrowTiles : kFewTiles)) return false;
+    const size_t rows = size_t(g.k) * sizeof(float);
+    auto apart = [](const void* p, size_t np, const void* q, size_t nq) {
+        const uintptr_t a = reinterpret_cast<uintptr_t>(p), c = reinterpret_cast<uintptr_t>(q);
+        return a + np <= c || c + nq <= a;
+    };
+    for (int32_t j = 1; j <= l; ++j) {
+        const size_t written = rows * size_t(ctx->widths[j]);
+        for (const void* p : {g.a.ptr, g.a_dual})
+            if (p && !apart(p, rows * size_t(g.m), b.dx[j], written)) return false;
+        for (const void* p : {g.b.ptr, g.b.gate})
+            if (p && !apart(p, rows * size_t(g.n), b.dx[j], written)) return false;
     }
+    return true;
+}
+
+// The products that waited, one launch for those of up to 64 columns and one for the others.
+int32_t launch_together(varco_ctx* ctx, Workspace& ws, GemmArgs* g, int n, WeightSums& sums, hipStream_t st) {
+    if (n == 0) return VARCO_OK;
+    if (n == 1) return add_weight_product(ctx, ws, *g, sums, st);
+    int64_t tiles = 0;
+    for (int i = 0; i < n; ++i) tiles += varco_gemm_half_tn_tiles(g[i]);
+    const int64_t stages = (g->k + 31) / 32, slots = g->n <= 64 ? 512 : 256;       // (two workgroups of 128 x 64 tiles on a unit)
+    const int64_t per_slab = (stages * tiles + slots - 1) / slots;
+    double flops = 0;
+    int32_t split[kMaxWeightJobs] = {};
+    for (int i = 0; i < n; ++i) {
+        const int products = g[i].c_dual ? 2 : 1;
+        const int64_t here = std::min(per_slab, std::max<int64_t>(1, longest_slab(ctx, g[i].m, g[i].n, g[i].k, kGemmExpanded) / 32));
+        g[i].split_k = int32_t(std::min<int64_t>((stages + here - 1) / here, wgrad_splits(ctx, g[i].m, g[i].n, g[i].k, kGemmExpanded, products)));
+        g[i].partial = ws.gemm + sums.used;
+        sums.used += size_t(g[i].split_k) * size_t(g[i].m) * size_t(g[i].n) * size_t(products);
+        flops += 2.0 * products * double(g[i].m) * double(g[i].n) * double(g[i].k);
+    }
+    if (sums.used > ws.gemm_elems) return varco_fail(ctx, VARCO_ERR_STATE, "varco_network_backward: workspace too small");
+    VARCO_HIP(ctx, varco_launch_gemm_half_tn_jobs(g, n, st, ctx->tag(VARCO_K_GEMM_WGRAD, 0, flops), split));
+    for (int i = 0; i < n; ++i)
+        if (int32_t rc = sum_later(ctx, g[i], split[i], sums)) return rc;
     return VARCO_OK;
+}
+int32_t launch_waiting(varco_ctx* ctx, Workspace& ws, WeightSums& sums, hipStream_t st) {
+    GemmArgs* const end = sums.waiting + sums.n_waiting;
+    GemmArgs* const wide = std::stable_partition(sums.waiting, end, [](const GemmArgs& g) { return g.n <= 64; });
+    sums.n_waiting = 0;
+    if (int32_t rc = launch_together(ctx, ws, sums.waiting, int(wide - sums.waiting), sums, st)) return rc;
+    return launch_together(ctx, ws, wide, int(end - wide), sums, st);
 }
 
 // Backward pass of a narrowing class layer in two steps that do not depend on the order of its forward pass: the errors of all
@@ -570,7 +634,10 @@ int32_t layer_bwd(varco_ctx* ctx, Workspace& ws, const varco_network_buffers& b,
         const int products = g.c_dual ? 2 : 1;
         for (int tap = 0; tap < (sage ? 2 : 1); tap += products) {
             if (tap == 1) g.a.ptr = b.x[l], g.c = b.dh0[l];
-            if (int32_t rc = add_weight_product(ctx, ws, g, sums, st)) return rc;
+            if (may_wait(ctx, b, l, g, sums))
+                g.deferred = nullptr, sums.waiting[sums.n_waiting++] = g;
+            else if (int32_t rc = add_weight_product(ctx, ws, g, sums, st))
+                return rc;
         }
     }
     if (!need) return VARCO_OK;
@@ -723,6 +790,7 @@ extern "C" int32_t varco_network_backward(varco_ctx* ctx, const varco_network_bu
     WeightSums sums;
     for (int32_t l = ctx->n_layers - 1; l >= 0; --l)
         if (int32_t rc = layer_bwd(ctx, *ws, *b, l, sums, st)) return rc;
+    if (int32_t rc = launch_waiting(ctx, *ws, sums, st)) return rc;
     return finish_sums(ctx, sums, st);
 }
 

@@ -80,3 +80,38 @@ def test_received_rows_of_many_shares():
         net.ctx.close()
     # three bf16 roundings of 2^-9 at most lie between the stored activations and a gradient in either order
     assert np.abs(got[0] - got[1]).max() <= 6 * 2.0 ** -9 * np.abs(got[1]).max()
+
+
+@pytest.mark.parametrize("conv,widths", [("sage", (33, 64, 65, 40, 7)), ("gcn", (130, 128, 200, 64, 3)), ("sage", (16, 32, 8)), ("gcn", (7, 129, 130, 131))])
+@pytest.mark.parametrize("n", [31, 700])
+@pytest.mark.parametrize("shared", [False, True])
+def test_products_of_all_layers_in_one_launch(n, conv, widths, shared):
+    """Products of layers of few rows wait for the end of the pass: narrow and wide outputs, masked and not, one tap and two, one layer of a kind.
+    shared: the rows that a product reads are where a lower layer's gradient goes."""
+    g = synth.small_random_graph(n, 5.0, conv, seed=7)
+    host = vb.partition_build(g.n, g.rowptr, g.colidx, g.vals, synth.random_partition(g.n, 3, seed=8), 3)
+    net = PartitionedNetwork(host, widths, conv, KEY)
+    layers = range(len(widths) - 1)
+    rng = np.random.default_rng(n)
+    net.set_inputs(rng.standard_normal((n, widths[0])).astype(np.float32))
+    weights = [[rng.standard_normal((widths[l], widths[l + 1])).astype(np.float32) for l in layers] for _ in range(2)]
+    net.set_weights(weights[0], weights[1] if conv == "sage" else None)
+    net.set_upstream(rng.standard_normal((n, widths[-1])).astype(np.float32))
+    net.zero_grads()
+    net.forward(0, (2, 1))
+    m = [net.m[l].double() for l in layers]
+    if shared:
+        for l in layers[1:]:
+            net.dx[l] = net.m[l]
+    net.backward()
+    torch.cuda.synchronize()
+    for l in layers:
+        dz = net.dx[l + 1].double()
+        if l < layers[-1]:
+            dz = torch.where(net.x[l + 1] > 0, dz, torch.zeros_like(dz))
+        for got, a in [(net.dh1[l], m[l])] + ([(net.dh0[l], net.x[l].double())] if conv == "sage" else []):
+            # two scaled terms within 2^-23 of either operand, a rounding of 2^-24 per 16 rows of a slab and per slab, and four times their root for the tail
+            bound = (2.0 ** -21 + 4 * 2.0 ** -23 * (n / 16 + 1) ** 0.5) * (a.abs().t() @ dz.abs())
+            # values far below the largest of their column keep 2^-42 of that one
+            floor = 2.0 ** -42 * (a.abs().max() * dz.abs().sum(0)[None, :] + a.abs().sum(0)[:, None] * dz.abs().max())
+            assert ((got.double() - a.t() @ dz).abs() <= bound + floor).all(), l
