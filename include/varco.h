@@ -398,6 +398,12 @@ int32_t varco_network_taps_bwd_weight(varco_ctx* ctx, int32_t layer, int32_t n_t
                                       const void* x_out, void* const* dh, varco_stream stream);
 int32_t varco_network_taps_bwd_input(varco_ctx* ctx, int32_t layer, int32_t n_taps, const void* dx_out, const void* x_out,
                                      const void* const* h, void* const* g_out, varco_stream stream);
+/* The input gradient's walk over the hops of a layer without activation, its first stretch in one call: with *formed = 1,
+ * g_in = varco_network_aggregate_bwd(tap, dx_out h_last^T) + dx_out h_next^T, tap = VARCO_TAP(layer, K - 1), h_last and h_next
+ * the weights of taps K - 1 and K - 2. *formed = 0: nothing was done, since the separate calls are the faster form or the only one
+ * (a layer with an activation, more than 64 outputs or no fewer than inputs, ratios that send little). g_in and dx_out do not overlap. */
+int32_t varco_network_taps_bwd_last_hop(varco_ctx* ctx, int32_t tap, const void* dx_out, const void* h_last, const void* h_next, void* g_in,
+                                        int32_t* formed, varco_stream stream);
 
 int32_t varco_get_stats(const varco_ctx* ctx, varco_stats* out);
 int32_t varco_reset_stats(varco_ctx* ctx);

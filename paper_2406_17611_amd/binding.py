@@ -35,6 +35,7 @@ EXPORTS = [
     "varco_link_partitions", "varco_network_forward", "varco_network_backward", "varco_network_compress",
     "varco_network_aggregate_fwd", "varco_network_aggregate_bwd",
     "varco_network_taps_fwd", "varco_network_taps_bwd_weight", "varco_network_taps_bwd_input",
+    "varco_network_taps_bwd_last_hop",
 ]
 KERNEL_CLASSES = ["compress", "decompress", "agg_fwd", "gemm_fwd", "gemm_wgrad", "gemm_dgrad", "agg_bwd_local",
                   "agg_bwd_halo", "reduce", "agg_bwd_halo_sum"]
@@ -137,6 +138,7 @@ def lib() -> C.CDLL:
         L.varco_network_taps_fwd.argtypes = [vp, i32, i32, vp, vp, vp, vp]
         L.varco_network_taps_bwd_weight.argtypes = [vp, i32, i32, vp, vp, vp, vp, vp]
         L.varco_network_taps_bwd_input.argtypes = [vp, i32, i32, vp, vp, vp, vp, vp]
+        L.varco_network_taps_bwd_last_hop.argtypes = [vp, i32, vp, vp, vp, vp, C.POINTER(i32), vp]
         L.varco_profile_enable.argtypes = [vp, i32]
         L.varco_profile_read.argtypes = [vp, C.POINTER(Profile), i32]
         for name in EXPORTS:
@@ -422,6 +424,12 @@ class Context:
     def network_taps_bwd_input(self, layer, dx_out, x_out, h, g, stream=None):
         _check(lib().varco_network_taps_bwd_input(self._h, layer, len(h), _ptr(dx_out), _ptr(x_out), self._ptrs(h), self._ptrs(g),
                                                   _stream(stream)), self._h)
+
+    def network_taps_bwd_last_hop(self, tap, dx_out, h_last, h_next, g_in, stream=None) -> bool:
+        formed = C.c_int32(0)
+        _check(lib().varco_network_taps_bwd_last_hop(self._h, tap, _ptr(dx_out), _ptr(h_last), _ptr(h_next), _ptr(g_in), C.byref(formed),
+                                                     _stream(stream)), self._h)
+        return bool(formed.value)
 
     def softmax_xent(self, logits, labels, n_classes, scale, dlogits, row_loss, row_correct, totals, stream=None):
         n_rows = logits.shape[0]

@@ -483,59 +483,77 @@ struct ClassRows {
     int32_t dz_ld;
     bool two_terms;
 };
-ClassRows class_rows(const varco_ctx* ctx, const Workspace& ws, const varco_network_buffers& b, int32_t l, const MaskRule& rule) {
+// What such a pass is given: dZ, the weights of the aggregated tap and of the one that is not (or null), and where dX goes.
+struct ClassCall {
+    void* dz;
+    const void *h1, *h0;
+    void* dx;
+};
+ClassCall class_call(const varco_ctx* ctx, const varco_network_buffers& b, int32_t l) {
+    return {b.dx[l + 1], b.h1[l], ctx->conv == VARCO_CONV_SAGE ? b.h0[l] : nullptr, b.dx[l]};
+}
+ClassRows class_rows(const varco_ctx* ctx, const Workspace& ws, const ClassCall& c, int32_t l, const MaskRule& rule) {
     const NetState& net = ctx->net;
     const int32_t pitch = varco_class_pitch(ctx->dtype, ctx->widths[l + 1]);
     const size_t bytes = size_t(net.rows) * size_t(pitch) * size_t(ctx->elem_bytes());
     char* const at = reinterpret_cast<char*>(ws.tf);
     ClassRows r;
     // dZ as it is where its rows are whole aligned 16-byte pieces, else a padded copy
-    const bool whole = ctx->widths[l + 1] * int(ctx->elem_bytes()) % 16 == 0 && (reinterpret_cast<uintptr_t>(b.dx[l + 1]) & 15u) == 0;
-    r.dz = whole ? b.dx[l + 1] : at, r.dz_ld = whole ? ctx->widths[l + 1] : pitch;
+    const bool whole = ctx->widths[l + 1] * int(ctx->elem_bytes()) % 16 == 0 && (reinterpret_cast<uintptr_t>(c.dz) & 15u) == 0;
+    r.dz = whole ? c.dz : at, r.dz_ld = whole ? ctx->widths[l + 1] : pitch;
     r.two_terms = ctx->dtype == VARCO_BF16 && ctx->layers[l].order == VARCO_ORDER_AGGREGATE_FIRST;
     r.g_loc = at + bytes;
     r.g_z = net.nnz_cross > 0 && rule.k > 0 ? at + (r.two_terms ? 3 : 2) * bytes : nullptr;
     return r;
 }
-int32_t class_sums(varco_ctx* ctx, Workspace& ws, const varco_network_buffers& b, int32_t l, const ClassRows& r, hipStream_t st) {
+int32_t class_sums(varco_ctx* ctx, Workspace& ws, const ClassCall& c, int32_t l, const ClassRows& r, hipStream_t st) {
     const NetState& net = ctx->net;
     const int32_t fo = ctx->widths[l + 1];
     const double es = ctx->elem_bytes();
     const double entries = double(net.nnz) * 8.0 + (double(net.rows) + 1.0) * 4.0;
-    VARCO_HIP(ctx, varco_launch_narrow_backward(ctx->dtype, net.nodes, net.t_local, net.t_cross, b.dx[l + 1], net.rows, net.zrow_of, r.dz, r.g_loc, r.g_z,
+    VARCO_HIP(ctx, varco_launch_narrow_backward(ctx->dtype, net.nodes, net.t_local, net.t_cross, c.dz, net.rows, net.zrow_of, r.dz, r.g_loc, r.g_z,
                                                 r.two_terms, fo, ws.spmm, st,
                                                 ctx->tag(VARCO_K_AGG_BWD_LOCAL, entries + (2.0 * double(net.rows) + double(net.boundary)) * fo * es, 0,
                                                          entries + (double(net.rows) + double(net.nnz)) * fo * es)));
     return VARCO_OK;
 }
-int32_t class_input(varco_ctx* ctx, Workspace& ws, const varco_network_buffers& b, int32_t l, const MaskRule& rule, const ClassRows& r, hipStream_t st) {
+int32_t class_input(varco_ctx* ctx, Workspace& ws, const ClassCall& c, int32_t l, const MaskRule& rule, const ClassRows& r, hipStream_t st) {
     const NetState& net = ctx->net;
     const int32_t fi = ctx->widths[l], fo = ctx->widths[l + 1];
     const int dt = ctx->dtype;
-    const bool sage = ctx->conv == VARCO_CONV_SAGE;
     if (rule.k > 0) {
         ctx->stats.bwd_elems[l] += net.halo_rows * rule.k;
         ctx->stats.full_bwd_elems[l] += net.halo_rows * fi;
     }
     if (dt == VARCO_F32) {
-        VARCO_HIP(ctx, varco_launch_class_dgrad_f32(r.g_loc, r.g_z, r.dz, r.dz_ld, net.zrow_of, net.bgid, net.rows, rule, fo, b.h1[l], sage ? b.h0[l] : nullptr,
-                                                    b.dx[l], st, ctx->tag(VARCO_K_GEMM_DGRAD, 0, (sage ? 4.0 : 2.0) * fi * fo * double(net.rows))));
+        VARCO_HIP(ctx, varco_launch_class_dgrad_f32(r.g_loc, r.g_z, r.dz, r.dz_ld, net.zrow_of, net.bgid, net.rows, rule, fo, c.h1, c.h0,
+                                                    c.dx, st, ctx->tag(VARCO_K_GEMM_DGRAD, 0, (c.h0 ? 4.0 : 2.0) * fi * fo * double(net.rows))));
         return VARCO_OK;
     }
     GemmArgs gw;                       // carries the slot of the weights' bf16 copy [position][column]
-    VARCO_HIP(ctx, prep_weight(ctx, ws, l, b.h1[l], fi, fo, false, 0, false, st, gw));
+    VARCO_HIP(ctx, prep_weight(ctx, ws, l, c.h1, fi, fo, false, 0, false, st, gw));
     VARCO_HIP(ctx, varco_launch_class_dgrad(r.g_loc, r.g_z, r.two_terms, net.zrow_of, net.bgid, net.rows, rule, fo, gw.b_prep, int32_t(gw.b_prep_ld),
-                                            b.dx[l], st, ctx->tag(VARCO_K_GEMM_DGRAD, 0, 2.0 * fi * fo * double(net.rows))));
-    if (sage) {                        // + dZ H0^T
+                                            c.dx, st, ctx->tag(VARCO_K_GEMM_DGRAD, 0, 2.0 * fi * fo * double(net.rows))));
+    if (c.h0) {                        // + dZ H0^T
         GemmArgs g0;
         g0.m = int32_t(net.rows), g0.n = fi, g0.k = fo;
-        g0.a.ptr = b.dx[l + 1], g0.a.ld = fo, g0.a.dtype = dt;
-        g0.b.ptr = b.h0[l], g0.b.ld = fo, g0.b.transposed = true;
-        g0.c = b.dx[l], g0.ldc = fi, g0.c_dtype = dt;
+        g0.a.ptr = c.dz, g0.a.ld = fo, g0.a.dtype = dt;
+        g0.b.ptr = c.h0, g0.b.ld = fo, g0.b.transposed = true;
+        g0.c = c.dx, g0.ldc = fi, g0.c_dtype = dt;
         g0.accumulate = true;
         VARCO_HIP(ctx, varco_launch_gemm(g0, st, ctx->tag(VARCO_K_GEMM_DGRAD, 0, 2.0 * fi * fo * double(net.rows))));
     }
     return VARCO_OK;
+}
+
+bool narrow_sums_taken(const varco_ctx* ctx, const Workspace& ws, int32_t l, const ClassCall& c) {
+    const bool bf16 = ctx->dtype == VARCO_BF16;
+    return narrow_sums_pay(ctx, l) && class_block_floats(ctx, bf16) <= ws.tf_elems && (!bf16 || (reinterpret_cast<uintptr_t>(c.dx) & 15u) == 0);
+}
+int32_t narrow_bwd(varco_ctx* ctx, Workspace& ws, const ClassCall& c, int32_t l, const MaskRule& rule, hipStream_t st) {
+    const ClassRows r = class_rows(ctx, ws, c, l, rule);
+    if (int32_t rc = class_sums(ctx, ws, c, l, r, st)) return rc;
+    return class_input(ctx, ws, c, l, rule, r, st);
 }
 
 int32_t class_bwd(varco_ctx* ctx, Workspace& ws, const varco_network_buffers& b, int32_t l, WeightSums& sums, hipStream_t st) {
@@ -545,8 +563,9 @@ int32_t class_bwd(varco_ctx* ctx, Workspace& ws, const varco_network_buffers& b,
     const double es = ctx->elem_bytes();
     const MaskRule rule = make_rule(ctx, l);
     if (int32_t rc = class_fits(ctx, ws, "varco_network_backward")) return rc;
-    const ClassRows r = class_rows(ctx, ws, b, l, rule);
-    if (int32_t rc = class_sums(ctx, ws, b, l, r, st)) return rc;
+    const ClassCall c = class_call(ctx, b, l);
+    const ClassRows r = class_rows(ctx, ws, c, l, rule);
+    if (int32_t rc = class_sums(ctx, ws, c, l, r, st)) return rc;
     GemmArgs g;
     g.m = fi, g.n = fo, g.k = int32_t(net.rows);
     g.a.ptr = b.x[l], g.a.ld = fi, g.a.transposed = true, g.a.dtype = dt;
@@ -571,7 +590,7 @@ int32_t class_bwd(varco_ctx* ctx, Workspace& ws, const varco_network_buffers& b,
         // (added by a launch of its own: the sums of a pass go to distinct results)
         VARCO_HIP(ctx, varco_launch_gemm_reduce(partial, slabs, fi, fo, static_cast<float*>(b.dh1[l]), fo, true, st, tag));
     }
-    return l > 0 ? class_input(ctx, ws, b, l, rule, r, st) : VARCO_OK;
+    return l > 0 ? class_input(ctx, ws, c, l, rule, r, st) : VARCO_OK;
 }
 
 int32_t layer_fwd(varco_ctx* ctx, Workspace& ws, const varco_network_buffers& b, int32_t l, hipStream_t st) {
@@ -641,12 +660,7 @@ int32_t layer_bwd(varco_ctx* ctx, Workspace& ws, const varco_network_buffers& b,
         }
     }
     if (!need) return VARCO_OK;
-    if (narrow_sums_pay(ctx, l) && class_block_floats(ctx, dt == VARCO_BF16) <= ws.tf_elems && (dt == VARCO_F32 || (reinterpret_cast<uintptr_t>(b.dx[l]) & 15u) == 0)) {
-        const MaskRule rule = make_rule(ctx, l);
-        const ClassRows r = class_rows(ctx, ws, b, l, rule);
-        if (int32_t rc = class_sums(ctx, ws, b, l, r, st)) return rc;
-        return class_input(ctx, ws, b, l, rule, r, st);
-    }
+    if (const ClassCall c = class_call(ctx, b, l); narrow_sums_taken(ctx, ws, l, c)) return narrow_bwd(ctx, ws, c, l, make_rule(ctx, l), st);
     GemmArgs g;                    // dM = dZ H1^T
     g.m = nl, g.n = fi, g.k = fo;
     g.a.ptr = b.dx[l + 1], g.a.gate = gate, g.a.ld = fo, g.a.dtype = dt;
@@ -953,4 +967,19 @@ extern "C" int32_t varco_network_taps_bwd_input(varco_ctx* ctx, int32_t layer, i
     for (int32_t i = 0; i < launches; ++i)
         VARCO_HIP(ctx, varco_launch_gemm(g[i], st, ctx->tag(VARCO_K_GEMM_DGRAD, 0, (g[i].c_dual ? 4.0 : 2.0) * fi * fo * double(g[i].m))));
     return VARCO_OK;
+}
+
+// The hop of the last tap is the same product either way round: S^T (dZ H^T), or (S^T dZ) H^T as a class layer forms it (class_sums, class_input),
+// with the next tap's dZ H'^T in the same launch. A step of 60,013 nodes 64-128-24, three taps, ratio 4: 633 -> 576 us.
+extern "C" int32_t varco_network_taps_bwd_last_hop(varco_ctx* ctx, int32_t tap, const void* dx_out, const void* h_last, const void* h_next, void* g_in,
+                                                   int32_t* formed, varco_stream stream) {
+    const char* fn = "varco_network_taps_bwd_last_hop";
+    int32_t layer = 0, hop = 0;
+    Workspace* ws = nullptr;
+    if (int32_t rc = tap_prologue(ctx, tap, stream, fn, &layer, &hop, &ws)) return rc;
+    if (!formed || !h_last || !h_next || (ctx->net.rows > 0 && (!dx_out || !g_in))) return null_pointer(ctx, fn);
+    if (int32_t rc = check_wide_rows(ctx, ctx->widths[layer], {g_in}, fn)) return rc;
+    const ClassCall c{const_cast<void*>(dx_out), h_last, h_next, g_in};
+    *formed = ctx->net.rows > 0 && narrow_sums_taken(ctx, *ws, layer, c) ? 1 : 0;
+    return *formed ? narrow_bwd(ctx, *ws, c, layer, make_rule(ctx, layer, hop), static_cast<hipStream_t>(stream)) : VARCO_OK;
 }

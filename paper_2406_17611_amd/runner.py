@@ -477,16 +477,20 @@ class KTapNetwork(PartitionedNetwork):
     def _input_gradient(self, l, bufs, stream):
         """dx[l]: every tap's dZ H^T, the hops walked in reverse on top of them. Two taps' products share a call where the
         second one's place is free (the last hop's sum, still being handed on, takes one of the two buffers). With bf16
-        storage the products are added to the hops instead, which rounds a sum's smaller part, not its larger one."""
+        storage the products are added to the hops instead, which rounds a sum's smaller part, not its larger one. The hop of
+        the last tap, with both taps that it joins, is one call where the library sums the errors of narrow outputs."""
         ctx, into = self.ctx, lambda t: self.dx[l] if t == 0 else bufs[(self.K - 1 - t) % 2]   # noqa: E731
+        top = self.K - 1                                     # taps from here on are left
+        if top > 0 and ctx.network_taps_bwd_last_hop(vb.tap(l, top), self.dx[l + 1], self.h[l][top], self.h[l][top - 1], into(top - 1), stream):
+            top -= 2
         if self.dtype == "bf16":
-            for t in range(self.K - 1, -1, -1):
+            for t in range(top, -1, -1):
                 if t < self.K - 1:
                     ctx.network_aggregate_bwd(vb.tap(l, t + 1), into(t + 1), into(t), False, stream)
                 ctx.transform_bwd_input(l, self.dx[l + 1], self.x[l + 1], self.h[l][t], into(t), t < self.K - 1, stream)
             return
-        ready = self.K                                       # taps >= ready have their product in place
-        for t in range(self.K - 1, -1, -1):
+        ready = top + 1                                      # taps >= ready have their product in place
+        for t in range(top, -1, -1):
             if t < ready:
                 taps = [t, t - 1] if t > 0 and (t == self.K - 1 or t == 1) else [t]
                 ctx.network_taps_bwd_input(l, self.dx[l + 1], self.x[l + 1], [self.h[l][i] for i in taps], [into(i) for i in taps], stream)

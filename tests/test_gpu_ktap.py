@@ -9,6 +9,7 @@ from oracle import ktap as oktap
 from oracle import layer as olayer
 from oracle import mask as omask
 from oracle.rounding import round_bf16
+from paper_2406_17611_amd import binding as vb
 from paper_2406_17611_amd import synth
 from paper_2406_17611_amd.runner import KTapNetwork
 
@@ -80,3 +81,33 @@ def test_zero_grads_clears_a_replaced_gradient():
     net.dh[0][0].fill_(1.0)
     net.zero_grads()
     assert not any(bool(m.any()) for taps in net.dh for m in taps)
+
+
+@pytest.mark.parametrize("widths,n_taps,ratio,dtype", [((8, 75, 47), 2, (3, 1), "f32"), ((8, 130, 5), 4, (8, 1), "f32"), ((8, 516, 64), 3, (1, 1), "f32"),
+                                                       ((8, 40, 33), 3, (1, 0), "f32"), ((16, 144, 17), 3, (7, 2), "bf16"), ((16, 512, 64), 2, (16, 1), "bf16")])
+def test_hop_of_the_last_tap_in_one_call(widths, n_taps, ratio, dtype):
+    """The errors of a narrow layer summed before they pass the weights: the same dX as through the separate calls (either form is
+    within the tolerance of the exact one), from whichever hop, and left alone where the library says that it does not form it."""
+    g = synth.small_random_graph(1500, 11.0, "sage", seed=80)
+    host, _ = both_partitions(g, synth.random_partition(g.n, 3, seed=81), 3)
+    net = KTapNetwork(host, widths, n_taps, KEY, dtype=dtype)
+    net.set_tap_weights([[synth.glorot(widths[l], widths[l + 1], synth.SEED_WEIGHT, 8 * l + hop) for hop in range(n_taps)] for l in range(2)])
+    net.set_inputs(synth.features(g.n, widths[0], synth.SEED_FEAT))
+    net.set_upstream(synth.upstream_grad(g.n, widths[-1], synth.SEED_GRAD))
+    net.forward(3, ratio)
+    tap, far, near = vb.tap(1, n_taps - 1), net.h[1][n_taps - 1], net.h[1][n_taps - 2]
+    got, through, want = (torch.full_like(net.x[1], 7.0) for _ in range(3))
+    net.ctx.reset_stats()
+    formed = net.ctx.network_taps_bwd_last_hop(tap, net.dx[2], far, near, got)
+    handed = net.ctx.stats()["bwd_elems"]
+    net.ctx.reset_stats()
+    net.ctx.network_taps_bwd_input(1, net.dx[2], net.x[2], [far], [through])
+    net.ctx.network_aggregate_bwd(tap, through, want, False)
+    assert not formed or handed == net.ctx.stats()["bwd_elems"]
+    net.ctx.transform_bwd_input(1, net.dx[2], net.x[2], near, want, True)
+    torch.cuda.synchronize()
+    if not formed:                   # few errors are sent: the sums at the width of the inputs move less
+        assert bool((got == 7.0).all()) and ratio == (1, 0)
+    else:
+        assert_close(net.to_global(got), net.to_global(want), "dX", 2.0 ** -6 if dtype == "bf16" else 2 * TOL)
+    assert not net.ctx.network_taps_bwd_last_hop(vb.tap(0, 1), net.dx[1], net.h[0][1], net.h[0][0], net.x[0].clone())      # a layer with an activation
