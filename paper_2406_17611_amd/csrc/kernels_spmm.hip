@@ -91,6 +91,11 @@ struct SpmmArgs {
     int32_t ku;               // loads per compressed row = k / ev
     int32_t lpe_log2;         // lanes that share one compressed row = 1 << lpe_log2 (>= min(ku, 64))
     int32_t epi;              // compressed rows handled per instruction = private LDS rows per wavefront
+    // kOwner: the messages themselves, written by the workgroups from `copy_block` on (see owner_messages)
+    const int32_t *brow, *bgid;
+    T* messages;
+    uint32_t n_messages;      // elements: boundary rows x k
+    int32_t copy_block;
 };
 
 // N consecutive stored elements as they come from memory (bf16 stays packed until it is used).
@@ -242,14 +247,73 @@ __device__ __forceinline__ void sparse_phase(const SpmmArgs<T>& p, int lane, int
     }
 }
 
+// The same sums, in the same order, from the owners' rows of x instead of the compressed ones: `xoff` is a row's byte offset, mab its (a, b).
+// An element is a load of its own, behind its position: for launches whose chain of round trips costs less than the launch that writes the
+// compressed rows first (varco_spmm_owners_pay).
+template <typename T, int EV>
+__device__ __forceinline__ void owner_phase(const SpmmArgs<T>& p, int lane, int nd, int ns, uint32_t xoff, float w, uint32_t mab, float* lrows) {
+    constexpr int G = EV == 4 ? 2 : EV == 2 ? 4 : 6;       // loads in flight: 8, 8, 6 per lane
+    using S = typename Stored<T, 1>::type;
+    const uint32_t width = p.rule.width;
+    const int sub = lane >> p.lpe_log2, jl = lane & ((1 << p.lpe_log2) - 1);
+    float* const mine = lrows + sub * width;
+    for (int j0 = 0; j0 < p.ku; j0 += 64) {
+        const bool j_ok = sub < p.epi && jl < p.ku && j0 + jl < p.ku;
+        const uint32_t j = uint32_t(j0 + jl) * EV;
+        for (int r0 = 0; r0 < ns; r0 += p.epi * G) {
+            S v[G][EV];
+            uint32_t q[G][EV];
+            float wi[G];
+            bool ok[G];
+#pragma unroll
+            for (int u = 0; u < G; ++u) {
+                const int es = r0 + u * p.epi + sub, at = 4 * (nd + es);
+                ok[u] = j_ok && es < ns;
+                const uint32_t row = lane_value(xoff, at), ab = lane_value(mab, at);
+                wi[u] = __uint_as_float(lane_value(__float_as_uint(w), at));
+                const uint32_t a = ab & 0xFFFFu;
+                q[u][0] = varco_mod_width(__umul24(a, j) + (ab >> 16), width, p.rule.width_magic);
+#pragma unroll
+                for (int i = 1; i < EV; ++i) q[u][i] = q[u][i - 1] + a, q[u][i] = min(q[u][i], q[u][i] - width);
+#pragma unroll
+                for (int i = 0; i < EV; ++i)       // lanes without an entry read the first element, unused
+                    v[u][i] = *reinterpret_cast<const S*>(reinterpret_cast<const char*>(p.dense) + (ok[u] ? row + q[u][i] * uint32_t(sizeof(T)) : 0u));
+            }
+#pragma unroll
+            for (int u = 0; u < G; ++u)
+                if (ok[u]) {
+                    float cur[EV];
+#pragma unroll
+                    for (int i = 0; i < EV; ++i) cur[i] = mine[q[u][i]];          // distinct positions of one entry
+#pragma unroll
+                    for (int i = 0; i < EV; ++i) mine[q[u][i]] = cur[i] + wi[u] * Stored<T, 1>::get(v[u][i], 0);
+                }
+        }
+    }
+}
+
+// Elements [256 block, 256 block + 256) of the messages, by one wavefront.
+template <typename T>
+__device__ __forceinline__ void owner_messages(const SpmmArgs<T>& p, uint32_t block, int lane) {
+#pragma unroll
+    for (uint32_t i = 0; i < 4; ++i) {
+        const uint32_t t = (4 * block + i) * 64 + uint32_t(lane);
+        if (t >= p.n_messages) continue;
+        const uint32_t b = t / p.rule.k, j = t - b * p.rule.k;
+        const MaskAffine m = varco_affine(p.rule, uint32_t(p.bgid[b]));
+        p.messages[t] = p.dense[uint32_t(p.brow[b]) * p.rule.width + varco_position(p.rule, m, j)];
+    }
+}
+
 // T: storage type of the dense rows, the compressed rows and the output (sums are kept in fp32);
 // VEC: elements per lane per load of a dense row (16 bytes, or fewer when the width or the bases do not allow it);
 // NV: such loads per lane per row (0: fewer than 64 lanes cover a row, see gather_rows);
 // MODE: kDenseOnly: all rows are dense; forward aggregation: kFull: halo rows are complete; kSparse / kSparseZ32: compressed,
-// EV elements per lane and load, power-of-two width or not, the latter mode with 32-bit offsets (see sparse_phase). One
+// EV elements per lane and load, power-of-two width or not, the latter mode with 32-bit offsets (see sparse_phase); kOwner: kept elements come from
+// the owners' rows and the launch writes the messages as well (owner_phase, owner_messages). One
 // kernel per form: the constants of forms that do not run would take registers, i.e. resident wavefronts, from the one
 // that does.
-constexpr int kDenseOnly = 0, kFull = 1, kSparse = 2, kSparseZ32 = 3;
+constexpr int kDenseOnly = 0, kFull = 1, kSparse = 2, kSparseZ32 = 3, kOwner = 4;
 template <typename T, int VEC, int NV, int MODE, int EV = 1, bool POW2 = false>
 __global__ __launch_bounds__(agg_block(MODE), MODE >= kSparse && VEC * NV <= 8 ? kHaloWaves : 1) void spmm_kernel(SpmmArgs<T> p) {
     constexpr bool HALO = MODE != kDenseOnly, SPARSE = MODE >= kSparse, Z32 = MODE == kSparseZ32;
@@ -261,6 +325,11 @@ __global__ __launch_bounds__(agg_block(MODE), MODE >= kSparse && VEC * NV <= 8 ?
     const int wave = threadIdx.x >> 6;
     const int32_t width = int32_t(p.rule.width);
 
+    if constexpr (MODE == kOwner)
+        if (int32_t(blockIdx.x) >= p.copy_block) {
+            owner_messages(p, blockIdx.x - uint32_t(p.copy_block), lane);
+            return;
+        }
     // Workgroups are dealt to the 8 XCDs round-robin; an XCD takes the work list in runs of kXcdRun consecutive
     // workgroups (the grid is a multiple of 8 runs), so that rows next to each other - which on a graph with any
     // locality share source rows - are aggregated through the same L2 at about the same time, while every XCD still
@@ -278,7 +347,7 @@ __global__ __launch_bounds__(agg_block(MODE), MODE >= kSparse && VEC * NV <= 8 ?
         if (base + lane < it.e1) {
             if (HALO)
                 ed = p.edge[base + lane];
-            else
+            if (!HALO || MODE == kOwner)
                 col = p.colidx[base + lane];
             w = p.vals[base + lane];
         }
@@ -300,7 +369,7 @@ __global__ __launch_bounds__(agg_block(MODE), MODE >= kSparse && VEC * NV <= 8 ?
         const bool is_halo = HALO && ed.gid >= 0;
         uint32_t zoff = 0, shift = 0, unit = 0;
         if (SPARSE && is_halo) {         // the multiplier table (at most 2 KB) comes from the cache, used behind the first rows
-            zoff = Z32 ? uint32_t(ed.src) * (p.rule.k * uint32_t(sizeof(T))) : uint32_t(ed.src);
+            zoff = MODE == kOwner ? uint32_t(col) * (uint32_t(width) * uint32_t(sizeof(T))) : Z32 ? uint32_t(ed.src) * (p.rule.k * uint32_t(sizeof(T))) : uint32_t(ed.src);
             const uint32_t h1 = varco_mix32(uint32_t(ed.gid) ^ key0);
             unit = p.rule.units[__umulhi(varco_mix32(h1 ^ key1), p.rule.n_units)];
             shift = __umulhi(h1, p.rule.width) << 16;
@@ -316,7 +385,10 @@ __global__ __launch_bounds__(agg_block(MODE), MODE >= kSparse && VEC * NV <= 8 ?
             if (ns > 0) {
                 if (!any_sparse) __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");     // the rows are cleared
                 any_sparse = true;
-                sparse_phase<T, EV, Z32, POW2>(p, lane, nd, ns, zoff, w, (unit | shift) << (POW2 ? 2 : 0), reinterpret_cast<char*>(lds));
+                if constexpr (MODE == kOwner)
+                    owner_phase<T, EV>(p, lane, nd, ns, zoff, w, unit | shift, lds);
+                else
+                    sparse_phase<T, EV, Z32, POW2>(p, lane, nd, ns, zoff, w, (unit | shift) << (POW2 ? 2 : 0), reinterpret_cast<char*>(lds));
             }
         }
     }
@@ -935,7 +1007,7 @@ bool aligned_to(const void* p, size_t bytes) { return (reinterpret_cast<uintptr_
 template <typename T>
 hipError_t spmm_t(const SpmmPlan& plan, const VarcoEdge* edge, const int32_t* colidx, const float* vals, const void* dense_v,
                   const void* z_v, int64_t z_rows, const MaskRule& rule, void* out_v, int32_t row_base, float* partial,
-                  hipStream_t stream, const LaunchTag& tag) {
+                  const SpmmOwners* owners, hipStream_t stream, const LaunchTag& tag) {
     const T* dense = static_cast<const T*>(dense_v);
     const T* z = static_cast<const T*>(z_v);
     T* out = static_cast<T*>(out_v);
@@ -957,11 +1029,11 @@ hipError_t spmm_t(const SpmmPlan& plan, const VarcoEdge* edge, const int32_t* co
     while (nv && nv * 64 < per_row) nv <<= 1;
     if (nv > 8) return hipErrorInvalidValue;
 
-    SpmmArgs<T> a;
+    SpmmArgs<T> a{};
     a.items = plan.items;
     a.n_items = plan.n_items;
     a.edge = edge;
-    a.colidx = colidx;
+    a.colidx = owners ? owners->arow : colidx;
     a.vals = vals;
     a.dense = dense;
     a.z = z;
@@ -990,7 +1062,14 @@ hipError_t spmm_t(const SpmmPlan& plan, const VarcoEdge* edge, const int32_t* co
     a.epi = std::max(1, std::min(64 >> a.lpe_log2, epi_cap));
     const int agg_waves = agg_block(halo ? kFull : kDenseOnly) / 64;
     const int32_t per_round = 8 * kXcdRun;                                         // see the kernel's XCD mapping
-    const dim3 grid(((plan.n_items + agg_waves - 1) / agg_waves + per_round - 1) / per_round * per_round);
+    dim3 grid(((plan.n_items + agg_waves - 1) / agg_waves + per_round - 1) / per_round * per_round);
+    if (owners) {
+        a.brow = owners->brow, a.bgid = owners->bgid;
+        a.messages = static_cast<T*>(const_cast<void*>(z_v));
+        a.n_messages = uint32_t(z_rows) * rule.k;
+        a.copy_block = int32_t(grid.x);
+        grid.x += (a.n_messages + 255) / 256;
+    }
     size_t lds_bytes = 0;
     if (halo && !full)
         lds_bytes = (size_t(a.epi) * width * sizeof(float) + 15) / 16 * 16;
@@ -1004,7 +1083,16 @@ hipError_t spmm_t(const SpmmPlan& plan, const VarcoEdge* edge, const int32_t* co
             if (vec == 8) return launch_spmm_vec<T, 8, MODE>(nv, ev, a, grid, lds_bytes, stream);
         return vec4 ? launch_spmm_vec<T, 4, MODE>(nv, ev, a, grid, lds_bytes, stream) : launch_spmm_vec<T, 1, MODE>(nv, ev, a, grid, lds_bytes, stream);
     };
-    if (halo && full)
+    if (owners) {
+        auto with_ev = [&](auto e) {
+            constexpr int EV = decltype(e)::value;
+            const auto kernel = nv == 0 ? spmm_kernel<T, 4, 0, kOwner, EV> : spmm_kernel<T, 4, 1, kOwner, EV>;
+            hipLaunchKernelGGL(kernel, grid, dim3(agg_block(kOwner)), lds_bytes, stream, a);
+            return hipGetLastError();
+        };
+        if (vec == 4 && nv <= 1 && halo && !full)
+            err = ev == 4 ? with_ev(std::integral_constant<int, 4>{}) : ev == 2 ? with_ev(std::integral_constant<int, 2>{}) : with_ev(std::integral_constant<int, 1>{});
+    } else if (halo && full)
         err = with_vec(std::integral_constant<int, kFull>{});
     else if (halo && z32)
         err = with_vec(std::integral_constant<int, kSparseZ32>{});
@@ -1214,14 +1302,30 @@ hipError_t varco_launch_validate_partition(const varco_partition_desc& d, int32_
     return hipGetLastError();
 }
 
+// The launch saved is worth 2 to 4 us and the reading of x by it. Against it: an entry touches a cache line per kept element, up to the whole row of
+// its owner, where the compressed row is a line or two (all cross entries: at most 64 MB here), and where an entry takes all lanes the runs of long rows
+// become chains of round trips. Forward pass, messages first / together, us (62 networks of 2,000 to 100,000 nodes: 0.99 to 1.29 of the speed):
+//   2,000 nodes 16-32-8, ratio 4 28.1 / 21.8     16,000 nodes 32-64-8, 8 partitions 48.5 / 42.4     100,000 nodes of 6 neighbours 16-32-8 165 / 156
+//   2,000 nodes of 30 neighbours 128-256-256-40, ratio 8 96 / 90.5     16,000 of 8, bf16 125 / 115
+// beyond the lines: 40,000 nodes of 20 neighbours 128-256-256-40 262 / 363, 64-128-24 103 / 110; 43 and 86 kept elements, 6,000 nodes 86 / 91
+bool varco_spmm_owners_pay(int dtype, const SpmmPlan& plan, const MaskRule& rule, int64_t rows, int64_t cross, int64_t boundary, const void* dense,
+                           const void* out, const void* partial) {
+    const int64_t es = dtype == VARCO_BF16 ? 2 : 4, row = (int64_t(rule.width) * es + 127) / 128;
+    if (rule.k == 0 || rule.k >= rule.width || rule.width % 4 != 0 || rule.width > 256 || boundary <= 0 || plan.n_items <= 0) return false;
+    if (!aligned_to(dense, 4 * es) || !aligned_to(out, 4 * es) || !aligned_to(partial, 16)) return false;
+    if (rows * rule.width * es >= int64_t(1) << 32) return false;          // 32-bit offsets
+    const uint32_t loads = rule.k % 4 == 0 ? rule.k / 4 : rule.k % 2 == 0 ? rule.k / 2 : rule.k;       // lanes of an entry
+    return rule.k <= 64 && loads <= 32 && cross * std::min<int64_t>(rule.k, row) * 128 <= int64_t(1) << 26;
+}
+
 hipError_t varco_launch_spmm(int dtype, const SpmmPlan& plan, const VarcoEdge* edge, const int32_t* colidx,
                              const float* vals, const void* dense, const void* z, int64_t z_rows, const MaskRule& rule,
-                             void* out, int32_t row_base, float* partial, hipStream_t stream, const LaunchTag& tag) {
+                             void* out, int32_t row_base, float* partial, hipStream_t stream, const LaunchTag& tag, const SpmmOwners* owners) {
     hipError_t err = hipSuccess;
     if (plan.n_items > 0)
         err = dtype == VARCO_BF16
-                  ? spmm_t<bf16_t>(plan, edge, colidx, vals, dense, z, z_rows, rule, out, row_base, partial, stream, tag)
-                  : spmm_t<float>(plan, edge, colidx, vals, dense, z, z_rows, rule, out, row_base, partial, stream, tag);
+                  ? spmm_t<bf16_t>(plan, edge, colidx, vals, dense, z, z_rows, rule, out, row_base, partial, owners, stream, tag)
+                  : spmm_t<float>(plan, edge, colidx, vals, dense, z, z_rows, rule, out, row_base, partial, owners, stream, tag);
     if (err != hipSuccess || plan.short_rows == 0) return err;
     if (edge) return hipErrorInvalidValue;     // short-row plans are built for dense-only blocks
     LaunchTag rest = tag;                      // the block's bytes are booked once

@@ -162,6 +162,11 @@ hipError_t varco_launch_validate_partition(const varco_partition_desc& d, int32_
 hipError_t varco_launch_build_edges(const int32_t* colidx, int64_t nnz, int32_t n_local, const int32_t* halo_zrow,
                                     const int32_t* halo_gid, VarcoEdge* edge, hipStream_t stream);
 
+// Where a launch finds the owners' rows: the row of `dense` of every entry's column, and row and node of every row of z.
+struct SpmmOwners {
+    const int32_t *arow, *brow, *bgid;
+};
+
 // out[row - row_base, :] = sum_e vals[e] * source_row(e) for the rows of `plan`, width = rule.width.
 //   edge != null (forward): entry e reads dense + edge[e].src * width when edge[e].gid < 0, else the k kept
 //       elements z[edge[e].src * k + j], which land at pi_gid(j) (a full row of z when k == width);
@@ -170,7 +175,11 @@ hipError_t varco_launch_build_edges(const int32_t* colidx, int64_t nnz, int32_t 
 // unknown); a compressed buffer below 4 GiB is addressed with 32-bit offsets.
 hipError_t varco_launch_spmm(int dtype, const SpmmPlan& plan, const VarcoEdge* edge, const int32_t* colidx,
                              const float* vals, const void* dense, const void* z, int64_t z_rows, const MaskRule& rule,
-                             void* out, int32_t row_base, float* partial, hipStream_t stream, const LaunchTag& tag);
+                             void* out, int32_t row_base, float* partial, hipStream_t stream, const LaunchTag& tag,
+                             const SpmmOwners* owners = nullptr);
+// Whether one launch may aggregate and write the messages (`owners`: z is written, not read) instead of varco_launch_compress before it.
+bool varco_spmm_owners_pay(int dtype, const SpmmPlan& plan, const MaskRule& rule, int64_t rows, int64_t cross, int64_t boundary, const void* dense,
+                           const void* out, const void* partial);
 
 // prow[e] = position of forward entry e among the halo entries of the transposed order (-1 for local entries).
 hipError_t varco_launch_build_prow(const int32_t* rowptr, const int32_t* colidx, int32_t n_local,

@@ -268,7 +268,9 @@ int32_t null_pointer(const varco_ctx* ctx, const char* fn) {
 }
 
 // M = S [local rows of x; compressed rows of z] for all partitions.
-int32_t aggregate_fwd(varco_ctx* ctx, Workspace& ws, int32_t layer, const MaskRule& rule, const void* x, const void* z, void* m, hipStream_t st) {
+// write_z: z is written by the same launch and not read (varco_spmm_owners_pay).
+int32_t aggregate_fwd(varco_ctx* ctx, Workspace& ws, int32_t layer, const MaskRule& rule, const void* x, const void* z, void* m, hipStream_t st,
+                      bool write_z = false) {
     const NetState& net = ctx->net;
     const double es = ctx->elem_bytes();
     const int32_t fi = ctx->widths[layer];
@@ -278,8 +280,11 @@ int32_t aggregate_fwd(varco_ctx* ctx, Workspace& ws, int32_t layer, const MaskRu
     const LaunchTag tag = ctx->tag(VARCO_K_AGG_FWD, bytes, 0, stream);
     if (rule.k == rule.width)   // lossless: a message equals the owner's row, which is nearer (the same rows serve the local entries)
         VARCO_HIP(ctx, varco_launch_spmm(ctx->dtype, net.fwd, nullptr, net.arow, net.vals, x, nullptr, 0, full_rule(fi), m, 0, ws.spmm, st, tag));
-    else
-        VARCO_HIP(ctx, varco_launch_spmm(ctx->dtype, net.fwd, net.edges, nullptr, net.vals, x, z, net.boundary, rule, m, 0, ws.spmm, st, tag));
+    else {
+        const SpmmOwners owners{net.arow, net.brow, net.bgid};
+        VARCO_HIP(ctx, varco_launch_spmm(ctx->dtype, net.fwd, net.edges, nullptr, net.vals, x, z, net.boundary, rule, m, 0, ws.spmm, st, tag,
+                                         write_z ? &owners : nullptr));
+    }
     ctx->stats.fwd_elems[layer] += net.halo_rows * rule.k;
     ctx->stats.full_fwd_elems[layer] += net.halo_rows * fi;
     return VARCO_OK;
@@ -596,16 +601,17 @@ int32_t class_bwd(varco_ctx* ctx, Workspace& ws, const varco_network_buffers& b,
 int32_t layer_fwd(varco_ctx* ctx, Workspace& ws, const varco_network_buffers& b, int32_t l, hipStream_t st) {
     const NetState& net = ctx->net;
     const int32_t fi = ctx->widths[l], fo = ctx->widths[l + 1];
-    const bool sage = ctx->conv == VARCO_CONV_SAGE, last = l == ctx->n_layers - 1;
+    const bool sage = ctx->conv == VARCO_CONV_SAGE;
     const int dt = ctx->dtype;
     const double es = ctx->elem_bytes();
-    if (ctx->layers[l].order == VARCO_ORDER_TRANSFORM_FIRST) {
-        if (int32_t rc = class_fwd(ctx, ws, b, l, st)) return rc;
-        return last ? VARCO_OK : compress_all(ctx, l + 1, make_rule(ctx, l + 1), b.x[l + 1], b.z[l + 1], st);
-    }
+    const bool first = ctx->layers[l].order == VARCO_ORDER_TRANSFORM_FIRST;
     const MaskRule rule = make_rule(ctx, l);
+    const bool together = !first && varco_spmm_owners_pay(dt, net.fwd, rule, net.rows, net.nnz_cross, net.boundary, b.x[l], b.m[l], ws.spmm);
+    if (!together)
+        if (int32_t rc = compress_all(ctx, l, rule, b.x[l], b.z[l], st)) return rc;
+    if (first) return class_fwd(ctx, ws, b, l, st);
     ctx->layers[l].ran_forward = true;
-    if (int32_t rc = aggregate_fwd(ctx, ws, l, rule, b.x[l], b.z[l], b.m[l], st)) return rc;
+    if (int32_t rc = aggregate_fwd(ctx, ws, l, rule, b.x[l], b.z[l], b.m[l], st, together)) return rc;
     if (net.rows > 0) {
         GemmArgs g;
         g.m = int32_t(net.rows), g.n = fo, g.k = fi;
@@ -622,7 +628,7 @@ int32_t layer_fwd(varco_ctx* ctx, Workspace& ws, const varco_network_buffers& b,
         if (sage) VARCO_HIP(ctx, prep_weight(ctx, ws, l, b.h0[l], fi, fo, true, 1, true, st, g));
         VARCO_HIP(ctx, varco_launch_gemm(g, st, ctx->tag(VARCO_K_GEMM_FWD, 0, 2.0 * g.m * double(g.n) * (double(g.k) + g.k2))));
     }
-    return last ? VARCO_OK : compress_all(ctx, l + 1, make_rule(ctx, l + 1), b.x[l + 1], b.z[l + 1], st);
+    return VARCO_OK;
 }
 
 int32_t layer_bwd(varco_ctx* ctx, Workspace& ws, const varco_network_buffers& b, int32_t l, WeightSums& sums, hipStream_t st) {
@@ -787,7 +793,6 @@ extern "C" int32_t varco_network_forward(varco_ctx* ctx, const varco_network_buf
     Workspace* ws = nullptr;
     if (int32_t rc = workspace_for(ctx, st, &ws, fn)) return rc;
     if (int32_t rc = prep_all(ctx, *ws, *b, st)) return rc;
-    if (int32_t rc = compress_all(ctx, 0, make_rule(ctx, 0), b->x[0], b->z[0], st)) return rc;
     for (int32_t l = 0; l < ctx->n_layers; ++l)
         if (int32_t rc = layer_fwd(ctx, *ws, *b, l, st)) return rc;
     return VARCO_OK;

@@ -90,3 +90,28 @@ def test_linked_calls_need_a_link_and_a_changed_partition_drops_it():
     with pytest.raises(vb.VarcoError) as e:
         net.ctx.link_partitions()
     assert e.value.code == vb.ERR_SHAPE
+
+
+@pytest.mark.parametrize("widths,ratio,dtype,n", [((4, 8, 4), (2, 1), "f32", 900), ((20, 36, 7), (3, 1), "f32", 900), ((128, 256, 5), (8, 1), "bf16", 900),
+                                                  ((252, 60, 9), (4, 1), "f32", 700), ((256, 128, 9), (4, 1), "f32", 1), ((64, 256, 9), (2, 1), "bf16", 700),
+                                                  ((100, 256, 9), (4, 1), "f32", 600), ((75, 130, 9), (3, 1), "f32", 500)])
+def test_messages_written_with_the_sums(widths, ratio, dtype, n):
+    """A forward pass of few entries writes the messages and sums their kept elements from the owners' rows in one launch: the same bits
+    as messages first and their sums after, for every lane layout, rows long enough to be split, and widths that keep to two launches."""
+    if n == 1:
+        g = synth.small_random_graph(6, 2.0, "gcn", seed=90)
+    else:
+        g = synth.gcn_operator(n, *synth.chung_lu_edges(n, 12 * n, 2.1, 91))
+    host, _ = both_partitions(g, synth.random_partition(g.n, 3, seed=92), 3)
+    net = PartitionedNetwork(host, widths, "gcn", KEY, dtype=dtype)
+    net.set_inputs(synth.features(g.n, widths[0], synth.SEED_FEAT))
+    net.set_weights([synth.glorot(widths[l], widths[l + 1], synth.SEED_WEIGHT, 2 * l) for l in range(2)])
+    for step in (3, 4):
+        net.forward(step, ratio)
+        for l in range(2):
+            z, m = torch.full_like(net.z[l], 7.0), torch.full_like(net.m[l], 7.0)
+            net.ctx.network_compress(l, net.x[l], z)
+            net.ctx.network_aggregate_fwd(l, net.x[l], z, m)
+            torch.cuda.synchronize()
+            sent = net.b_total * net.ctx.keep(l)
+            assert torch.equal(net.z[l][:sent], z[:sent]) and torch.equal(net.m[l], m), (l, step)
