@@ -1,22 +1,20 @@
-// The dense transform of eq. (2) for fp32-stored activations whose reduction takes 65 to 256 steps (both taps: twice that), act(M H + X H0), from three
-// bf16 terms of either operand and six products (kernels_gemm_split.hip: the expansion and what it keeps). The products of a stage of 32 steps
-// are summed from the smallest to the largest, on v_mfma_f32_16x16x32_bf16, which rounds half as often as two of 16 steps: the errors against
-// fp64 are 0.73 to 0.96 of those of the tiles there.
+// The dense transform of eq. (2) for fp32-stored activations whose reduction takes 65 to 256 steps (both taps together), act(M H + X H0), from three
+// bf16 terms of either operand and six products (kernels_gemm_split.hip: the expansion and what it keeps). The same instructions on the same
+// values in the same order as the tiles there, so the same bits: a ReLU whose argument is within rounding of zero decides alike in either. (Summed
+// from the smallest product on 16 x 16 x 32 instructions, which round half as often, errors against fp64 are 0.73 to 0.96 of these and 169,343
+// rows 256 -> 256 take 117 us; but one gate of a hub that decides otherwise moves the gradients of 50,021 nodes by 1.6e-3 as a whole.)
 //
-// The weights stay in registers: a wavefront holds 16 or 32 columns of them, all terms, of both taps, up to 192 registers, for all the rows that
-// its workgroup walks over. Blocks of 32 rows come in whole rows, 16 lanes to one, from any 4-byte address, one block (of one tap) ahead in
+// The weights stay in registers: a wavefront holds 32 columns of them, all terms, of both taps, 24 registers per stage of 32 steps, for all the
+// rows that its workgroup walks over. Blocks of 32 rows come in whole rows, 16 lanes to one, from any 4-byte address, one block (of one tap) ahead in
 // registers; they are split once for the eight wavefronts and lie in LDS as the matrix unit reads them, [stage][term][16 rows][eight steps][row],
 // rows swapped by their place so that neither writes nor reads meet in a bank; two buffers, one barrier per block and tap. One half of the
-// wavefronts splits the next block while the other multiplies, and the other way round: every SIMD holds one of either half. The weights are
-// the first operand: a lane then holds four consecutive columns of a row and stores them together.
-// Bound by the matrix units (1.1 to 1.3 of the 1.6 PFLOP/s that random operands reach from LDS) and, two taps of 129 steps and more, by the reads
-// from LDS for 16 columns alone. 128 x 128 tiles that each split their rows again and fetch weights by stage / this, us:
-//   169,343 rows 256 -> 256 134 / 117, 128 -> 256 76 / 64     1,638,400 rows 256 -> 256 1,500 / 1,140     300,007 rows 200 -> 200 208 / 152
-//   50,021 rows 200 -> 136 two taps 77 / 64     300,007 rows 100 -> 256 two taps 210 / 167     2,449,029 rows 256 -> 256 two taps 3,540 / 3,290
-//   3,001 rows 256 -> 256 20 / 11, two taps 32 / 16
-// Rows that are no whole number of 16-byte pieces stay with fp32 instructions although this would be as accurate and faster (50,021 rows 75 -> 200 two
-// taps 67 / 37): with every layer's roundings changed, twice as many ReLU gates within rounding of zero decide otherwise, and gradients
-// of a small graph then move by 1e-3 as a whole.
+// wavefronts splits the next block while the other multiplies, and the other way round: every SIMD holds one of either half (all splitting and
+// multiplying at once: 900,000 rows 256 -> 256 657 us). The weights are the first operand: a lane then holds four consecutive columns of a row and
+// stores them together. Bound by the matrix units' chain of dependent products and, 225 steps and more, by fragments read just before their use,
+// for which no registers are left to have more in flight.
+// 128 x 128 tiles that each split their rows again and fetch weights by stage / this, us:
+//   169,343 rows 256 -> 256 146 / 135     900,000 rows 256 -> 256 653 / 592, 800,000 rows 160 -> 512 787 / 750     300,007 rows 200 -> 200 218 / 170
+//   50,021 rows 128 -> 136 two taps 50 / 43     300,007 rows 100 -> 256 two taps 218 / 186     3,001 rows 256 -> 256 20 / 17, 128 -> 256 two taps 20 / 16
 #include <algorithm>
 #include <type_traits>
 
@@ -32,8 +30,12 @@ constexpr int kUnits = 256;          // compute units: one workgroup is resident
 constexpr int kRows = 32;            // rows of a block
 constexpr int kStage = 32;           // reduction steps of a stage
 constexpr int kTerms = 3;
+constexpr int kColumns = 32;         // columns of a wavefront
+constexpr int kMostStages = 8;       // of all taps: 192 registers of weights
+constexpr int kTileRows = 128;       // rows of a tile of the expanded weights
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef float any4 __attribute__((ext_vector_type(4), aligned(4)));
 typedef uint32_t words4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -43,7 +45,6 @@ struct Transform {
     int64_t lda;
     int32_t m, n, k;
     const uint16_t* b[2];            // expanded copies of the weights
-    int32_t tile_rows;               // rows of a tile of theirs
     int64_t pitch;                   // their padded reduction length
     float* c;
     int64_t ldc;
@@ -67,24 +68,25 @@ __device__ __forceinline__ void expand2(float x0, float x1, uint32_t (&w)[kTerms
     }
 }
 
-// KT: stages of a tap; CT: tiles of 16 columns of a wavefront.
-template <int KT, int TAPS, int CT>
+// KT: stages of a tap.
+template <int KT, int TAPS>
 __global__ __launch_bounds__(kThreads, 2) void transform_kernel(Transform g) {
-    constexpr int J = (KT + 1) / 2, RT = kRows / 16, CW = 16 * CT;
+    static_assert(KT * TAPS <= kMostStages, "the weights are 24 registers per stage");
+    constexpr int J = (KT + 1) / 2, RT = kRows / 16;
     constexpr int kBlock = KT * kTerms * RT * 512;
     __shared__ __attribute__((aligned(16))) uint16_t smem[2][kBlock];
-    const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, lg = lane >> 4;
+    const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, lg = lane >> 4, l32 = lane & 31, lk = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int32_t xcd = blockIdx.x & 7, within = blockIdx.x >> 3, group = within % g.groups;
     const int32_t first = (within / g.groups) * 8 + xcd, n_blocks = (g.m + kRows - 1) / kRows;
     if (first >= n_blocks || first >= g.stride) return;         // whole workgroup
 
-    const int32_t unit = group * kWaves + wave, n0 = min(unit, g.units - 1) * CW;
+    const int32_t unit = group * kWaves + wave, n0 = min(unit, g.units - 1) * kColumns;
     const bool mine = unit < g.units;
-    bf16x8 w[TAPS][KT][kTerms][CT];
+    bf16x8 w[TAPS][KT][kTerms][2];       // [..][half of a stage]
     {
-        const int32_t plane = g.tile_rows * kStage;
-        const int64_t at = int64_t(n0 / g.tile_rows) * (g.pitch / kStage) * kTerms * plane + (n0 % g.tile_rows + l16) * kStage + lg * 8;
+        const int32_t plane = kTileRows * kStage;
+        const int64_t at = int64_t(n0 / kTileRows) * (g.pitch / kStage) * kTerms * plane + (n0 % kTileRows + l32) * kStage + lk * 8;
 #pragma unroll
         for (int tap = 0; tap < TAPS; ++tap)
 #pragma unroll
@@ -92,8 +94,8 @@ __global__ __launch_bounds__(kThreads, 2) void transform_kernel(Transform g) {
 #pragma unroll
                 for (int p = 0; p < kTerms; ++p)
 #pragma unroll
-                    for (int ct = 0; ct < CT; ++ct)
-                        w[tap][t][p][ct] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(g.b[tap] + at + (kTerms * t + p) * plane + ct * 16 * kStage));
+                    for (int s = 0; s < 2; ++s)
+                        w[tap][t][p][s] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(g.b[tap] + at + (kTerms * t + p) * plane + s * 16));
     }
 
     float4 x[J];
@@ -125,14 +127,13 @@ __global__ __launch_bounds__(kThreads, 2) void transform_kernel(Transform g) {
     fetch(g.a[TAPS - 1], TAPS == 2 ? first : first + g.stride);
     __syncthreads();
 
-    const bool early = wave >= kWaves / 2;
+    const bool early = wave >= kWaves / 2, half_last = g.k <= (KT - 1) * kStage + 16;        // half a stage of padding is left out
+    const int32_t place = (lg & 1) * 512;
     int buf = 0;
     for (int32_t block = first; block < n_blocks; block += g.stride) {
-        floatx4 acc[RT][CT];
+        floatx16 acc;
 #pragma unroll
-        for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-            for (int ct = 0; ct < CT; ++ct) acc[rt][ct] = floatx4{0.f, 0.f, 0.f, 0.f};
+        for (int v = 0; v < 16; ++v) acc[v] = 0.f;
 #pragma unroll
         for (int tap = 0; tap < TAPS; ++tap) {
             auto next = [&]() __attribute__((always_inline)) {
@@ -142,48 +143,43 @@ __global__ __launch_bounds__(kThreads, 2) void transform_kernel(Transform g) {
             if (early) next();
             if (mine) {
 #pragma unroll
-                for (int t = 0; t < KT; ++t) {
-                    const uint16_t* const at = &smem[buf][t * kTerms * RT * 512 + (lg * 16 + (l16 ^ (2 * lg + 8 * (t & 1)))) * 8];
+                for (int t = 0; t < KT; ++t)
 #pragma unroll
-                    for (int rt = 0; rt < RT; ++rt) {
+                    for (int s = 0; s < 2; ++s) {
+                        if (t + 1 == KT && s == 1 && half_last) break;
+                        const int eight = 2 * s + lk;
+                        const uint16_t* const at = &smem[buf][t * kTerms * RT * 512 + place + (eight * 16 + (l16 ^ (2 * eight + 8 * (t & 1)))) * 8];
                         bf16x8 f[kTerms];
 #pragma unroll
-                        for (int p = 0; p < kTerms; ++p) f[p] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(at + (p * RT + rt) * 512));
+                        for (int p = 0; p < kTerms; ++p) f[p] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(at + p * RT * 512));
                         auto multiply = [&](int pa, int pw) __attribute__((always_inline)) {
-#pragma unroll
-                            for (int ct = 0; ct < CT; ++ct) acc[rt][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[tap][t][pw][ct], f[pa], acc[rt][ct], 0, 0, 0);
+                            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[tap][t][pw][s], f[pa], acc, 0, 0, 0);
                         };
-                        multiply(2, 0), multiply(0, 2), multiply(1, 1), multiply(1, 0), multiply(0, 1), multiply(0, 0);
+                        multiply(0, 0), multiply(0, 1), multiply(1, 0), multiply(1, 1), multiply(0, 2), multiply(2, 0);
                     }
-                }
             }
             if (!early) next();
             buf ^= 1;
             if (tap + 1 < TAPS) __syncthreads();
         }
-        if (mine) {
-            float* const c = g.c + int64_t(block) * kRows * g.ldc + n0;
-            const bool inside = (block + 1) * kRows <= g.m && n0 + CW <= g.n;
+        if (mine) {                  // a lane holds a row's columns 8 c + 4 lk .. + 3
+            float* const c = g.c + (int64_t(block) * kRows + l32) * g.ldc + n0 + 4 * lk;
+            const bool inside = (block + 1) * kRows <= g.m && n0 + kColumns <= g.n;
 #pragma unroll
-            for (int rt = 0; rt < RT; ++rt) {
-                const int row = rt * 16 + l16;
+            for (int q = 0; q < 4; ++q) {
+                floatx4 o = {acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]};
+                float* const dst = c + 8 * q;
+                if (inside) {
+                    o += g.accumulate ? floatx4(*reinterpret_cast<const any4*>(dst)) : floatx4{0.f, 0.f, 0.f, 0.f};       // (-0 becomes 0)
+                    if (g.relu) o = floatx4{fmaxf(o[0], 0.f), fmaxf(o[1], 0.f), fmaxf(o[2], 0.f), fmaxf(o[3], 0.f)};
+                    *reinterpret_cast<any4*>(dst) = o;
+                } else if (block * kRows + l32 < g.m) {
 #pragma unroll
-                for (int ct = 0; ct < CT; ++ct) {
-                    floatx4 o = acc[rt][ct];
-                    const int col = ct * 16 + 4 * lg;
-                    float* const dst = c + int64_t(row) * g.ldc + col;
-                    if (inside) {
-                        if (g.accumulate) o += *reinterpret_cast<const any4*>(dst);
-                        if (g.relu) o = floatx4{fmaxf(o[0], 0.f), fmaxf(o[1], 0.f), fmaxf(o[2], 0.f), fmaxf(o[3], 0.f)};
-                        *reinterpret_cast<any4*>(dst) = o;
-                    } else if (block * kRows + row < g.m) {
-#pragma unroll
-                        for (int v = 0; v < 4; ++v)
-                            if (n0 + col + v < g.n) {
-                                const float s = g.accumulate ? o[v] + dst[v] : o[v];
-                                dst[v] = g.relu ? fmaxf(s, 0.f) : s;
-                            }
-                    }
+                    for (int v = 0; v < 4; ++v)
+                        if (n0 + 8 * q + 4 * lk + v < g.n) {
+                            const float s = o[v] + (g.accumulate ? dst[v] : 0.f);
+                            dst[v] = g.relu ? fmaxf(s, 0.f) : s;
+                        }
                 }
             }
         }
@@ -193,15 +189,10 @@ __global__ __launch_bounds__(kThreads, 2) void transform_kernel(Transform g) {
 
 bool aligned_to(const void* p, uintptr_t bytes) { return (reinterpret_cast<uintptr_t>(p) & (bytes - 1)) == 0; }
 
-template <class F>
-void with_flag(bool b, F&& f) {
-    b ? f(std::true_type{}) : f(std::false_type{});
-}
-
 // Columns that each row is charged for when the device is full: the idle wavefronts of a group, and the compute units that no group has.
-int32_t charged_columns(int32_t n, int32_t cw) {
-    const int32_t groups = ((n + cw - 1) / cw + kWaves - 1) / kWaves;
-    return kUnits * kWaves * cw / std::max(8, kUnits / groups / 8 * 8);
+int32_t charged_columns(int32_t n) {
+    const int32_t groups = ((n + kColumns - 1) / kColumns + kWaves - 1) / kWaves;
+    return kUnits * kWaves * kColumns / std::max(8, kUnits / groups / 8 * 8);
 }
 
 }  // namespace
@@ -210,21 +201,24 @@ bool varco_gemm_split_rows_usable(const GemmArgs& ga) {
     auto copy_ok = [&](const void* p, int64_t ld, int64_t plane) {
         return p && aligned_to(p, 16) && ld == (int64_t(ga.k) + kStage - 1) / kStage * kStage && plane == (int64_t(ga.n) + 127) / 128 * 128 * ld;
     };
-    if (ga.f32_terms != kTerms || ga.m <= 0 || ga.n <= 0 || ga.k <= 64 || ga.k > 8 * kStage) return false;
+    if (ga.f32_terms != kTerms || ga.m <= 0 || ga.n <= 0 || ga.k <= 64) return false;
     if (ga.a.dtype != VARCO_F32 || ga.c_dtype != VARCO_F32 || ga.a.transposed || ga.a.gate || ga.b.gate || ga.c_dual || ga.split_k > 1 || ga.b_halves)
         return false;
     if (!copy_ok(ga.b_prep, ga.b_prep_ld, ga.b_prep_plane) || !aligned_to(ga.a.ptr, 4) || ga.a.ld > (int64_t(1) << 26)) return false;
     if (ga.k2 > 0 && (ga.k2 != ga.k || !copy_ok(ga.b2_prep, ga.b2_prep_ld, ga.b2_prep_plane) || !aligned_to(ga.a2.ptr, 4) || ga.a2.ld != ga.a.ld ||
                       ga.a2.gate || ga.a2.dtype != VARCO_F32 || ga.a2.transposed))
         return false;
+    // Whole 16-byte pieces as the tiles take them; weights that fit.
+    const int32_t stages = (ga.k + kStage - 1) / kStage * (ga.k2 > 0 ? 2 : 1);
+    if (ga.k % 4 != 0 || stages > kMostStages) return false;
     // The tiles of kernels_gemm_split.hip are level or ahead (us, there / here):
-    if (ga.k % 4 != 0) return false;
     if (ga.n <= 64) return false;                       // idle wavefronts here: 2,449,029 rows 256 -> 47 two taps 1,094 / 1,290
+    const int32_t n_blocks = (ga.m + kRows - 1) / kRows, groups = (ga.n + kColumns * kWaves - 1) / (kColumns * kWaves);
+    if (int64_t(n_blocks) * groups <= kUnits) return true;           // a block for every workgroup: 3,001 rows 256 -> 256 20 / 17
     const int64_t tiles = (int64_t(ga.m) + 127) / 128 * ((int64_t(ga.n) + 127) / 128);
-    if (tiles <= 3 * kUnits / 2) return true;           // units without a tile there: 10,007 rows 128 -> 200 two taps 23 / 17
-    if (tiles <= 2 * kUnits) return false;              // just two for every unit: 31,000 rows 100 -> 256 two taps 30 / 33
-    if (ga.k2 == 0 && ga.k <= 96) return false;         // few products a block: 300,007 rows 72 -> 136 88 / 92
-    return charged_columns(ga.n, 16) <= (ga.n + 127) / 128 * 128;      // 169,343 rows 100 -> 320 two taps 174 / 185
+    if (tiles <= 2 * kUnits) return false;              // few blocks in turn: 10,007 rows 256 -> 256 21 / 23, 31,000 rows 256 -> 128 23 / 28
+    if (stages <= 4) return false;                      // few products a block: 169,343 rows 128 -> 256 77 / 81
+    return charged_columns(ga.n) <= (ga.n + 127) / 128 * 128;      // 169,343 rows 100 -> 320 two taps 174 / 185
 }
 
 hipError_t varco_launch_gemm_split_rows(const GemmArgs& ga, hipStream_t stream, const LaunchTag& tag) {
@@ -233,32 +227,24 @@ hipError_t varco_launch_gemm_split_rows(const GemmArgs& ga, hipStream_t stream, 
     g.lda = ga.a.ld;
     g.m = ga.m, g.n = ga.n, g.k = ga.k;
     g.b[0] = static_cast<const uint16_t*>(ga.b_prep), g.b[1] = static_cast<const uint16_t*>(ga.b2_prep);
-    g.tile_rows = ga.n <= 64 ? 64 : 128;
     g.pitch = ga.b_prep_ld;
     g.c = static_cast<float*>(ga.c), g.ldc = ga.ldc;
     g.accumulate = ga.accumulate ? 1 : 0, g.relu = ga.relu ? 1 : 0;
     const int32_t n_blocks = (ga.m + kRows - 1) / kRows;
-    // Twice the columns halve the reads of the rows' fragments, half the columns spread few rows over more units (10,007 rows 256 -> 256 22 us
-    // against 18; 300,007 rows 160 against 183).
-    const bool wide = n_blocks >= 4 * kUnits && charged_columns(ga.n, 32) <= charged_columns(ga.n, 16);
+    g.units = (ga.n + kColumns - 1) / kColumns;
+    g.groups = (g.units + kWaves - 1) / kWaves;
+    g.stride = std::max(8, kUnits / g.groups / 8 * 8);
+    const dim3 grid{unsigned((std::min(g.stride, n_blocks) + 7) / 8 * 8 * g.groups)};
     tag.begin(stream);
-    auto launch = [&](auto kt, auto taps, auto ct) {
-        constexpr int CW = 16 * decltype(ct)::value;
-        g.units = (ga.n + CW - 1) / CW;
-        g.groups = (g.units + kWaves - 1) / kWaves;
-        g.stride = std::max(8, kUnits / g.groups / 8 * 8);
-        const dim3 grid{unsigned((std::min(g.stride, n_blocks) + 7) / 8 * 8 * g.groups)};
-        hipLaunchKernelGGL((transform_kernel<decltype(kt)::value, decltype(taps)::value, decltype(ct)::value>), grid, dim3(kThreads), 0, stream, g);
-    };
     using std::integral_constant;
     auto go = [&](auto kt) {
-        with_flag(ga.k2 > 0, [&](auto two) {
-            constexpr int TAPS = decltype(two)::value ? 2 : 1;
-            with_flag(wide, [&](auto w) {
-                constexpr int CT = decltype(w)::value && decltype(kt)::value * TAPS <= 8 ? 2 : 1;
-                launch(kt, integral_constant<int, TAPS>{}, integral_constant<int, CT>{});
-            });
-        });
+        constexpr int KT = decltype(kt)::value;
+        if constexpr (2 * KT <= kMostStages)
+            if (ga.k2 > 0) {
+                hipLaunchKernelGGL((transform_kernel<KT, 2>), grid, dim3(kThreads), 0, stream, g);
+                return;
+            }
+        hipLaunchKernelGGL((transform_kernel<KT, 1>), grid, dim3(kThreads), 0, stream, g);
     };
     switch ((ga.k + kStage - 1) / kStage) {
         case 3: go(integral_constant<int, 3>{}); break;

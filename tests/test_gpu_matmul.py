@@ -11,6 +11,7 @@ import torch
 from gpu_common import KEY, assert_close, dev
 from paper_2406_17611_amd import binding as vb
 from paper_2406_17611_amd import synth
+from paper_2406_17611_amd.runner import PartitionedNetwork
 
 pytestmark = pytest.mark.gpu
 
@@ -257,7 +258,7 @@ def test_non_finite_operand_stays_in_its_row(terms):
 @pytest.mark.parametrize("taps", [1, 2])
 @pytest.mark.parametrize("n", [2, 31, 33, 3001, 32801])
 def test_transform_at_the_edges_of_blocks(n, taps, fi, fo):
-    """Rows in blocks of 32 of workgroups that walk over them, columns in units of 16 or 32 of wavefronts, every number of stages, rows
+    """Rows in blocks of 32 of workgroups that walk over them, columns in units of 32 of wavefronts, every number of stages, rows
     that start at any word of a larger tensor; one tap added to what is there, two written."""
     from test_gpu_weight_gradients import _linked_context
     rng = np.random.default_rng(n + fi + fo)
@@ -278,11 +279,35 @@ def test_transform_at_the_edges_of_blocks(n, taps, fi, fo):
     torch.cuda.synchronize()
     want = sum(a.astype(np.float64) @ b.astype(np.float64) for a, b in zip(y, h)) + (old[:n] if taps == 1 else 0.0)
     size = sum(np.abs(a) @ np.abs(b) for a, b in zip(y, h))
-    # terms left out are below 2^-24 of a product; one rounding of 2^-24 per instruction (six per 32 steps) on a partial sum that is at most `size`:
+    # terms left out are below 2^-24 of a product; one rounding of 2^-24 per instruction (six per 16 steps) on a partial sum that is at most `size`:
     # sqrt of their number for independent ones, four times that for the tail; the addition rounds once more
-    bound = (2.0 ** -24 + 4 * 2.0 ** -24 * np.sqrt(6 * taps * np.ceil(fi / 32))) * size + (2.0 ** -24 * np.abs(want) if taps == 1 else 0.0)
+    bound = (2.0 ** -24 + 4 * 2.0 ** -24 * np.sqrt(6 * taps * np.ceil(fi / 16))) * size + (2.0 ** -24 * np.abs(want) if taps == 1 else 0.0)
     got = out.cpu().numpy()
     assert (np.abs(got[:n] - np.maximum(want, 0.0)) <= bound).all()
     assert np.array_equal(got[n], old[n])                             # the row behind the last one
     ctx.close()
     del parts
+
+
+@pytest.mark.parametrize("fi,fo", [(68, 72), (80, 132), (96, 130), (100, 256), (128, 136), (144, 96), (180, 257), (224, 65), (256, 512)])
+@pytest.mark.parametrize("conv", ["gcn", "sage"])
+@pytest.mark.parametrize("n", [2, 33, 3001, 32801])
+def test_transform_sums_do_not_depend_on_the_kernel(n, conv, fi, fo):
+    """Outputs of up to 64 columns are formed by tiles, wider ones mostly by wavefronts that keep the weights: the same bits, since a ReLU whose
+    argument is within rounding of zero must not open by the width of its layer or the number of rows."""
+    graph = synth.small_random_graph(n, 2.0, conv, seed=n)
+    host = vb.partition_build(graph.n, graph.rowptr, graph.colidx, graph.vals, synth.random_partition(graph.n, 2, seed=5), 2)
+    h1, h0 = (synth.glorot(fi, fo, 7, 1 + t).astype(np.float32) for t in range(2))
+    x0 = np.random.default_rng(n + fi).standard_normal((n, fi)).astype(np.float32)
+
+    def outputs(c0, c1):
+        net = PartitionedNetwork(host, (fi, c1 - c0), conv, 17, need_backward=False)
+        net.set_inputs(x0)
+        net.set_weights([np.ascontiguousarray(h1[:, c0:c1])], [np.ascontiguousarray(h0[:, c0:c1])])
+        net.forward(1, (4, 1))
+        torch.cuda.synchronize()
+        return net.x[1].clone()
+
+    whole = outputs(0, fo)
+    for c0 in range(0, fo, 64):
+        assert torch.equal(whole[:, c0:c0 + 64].view(torch.int32), outputs(c0, min(c0 + 64, fo)).view(torch.int32)), c0
