@@ -30,6 +30,7 @@ namespace {
 
 constexpr int BK = 32;
 constexpr int kThreads = 256;
+constexpr int kMaxChain = 4;     // products of a chain (gemm_split_kernel)
 constexpr int kPitch = BK;       // bf16 elements per LDS row (64 bytes)
 constexpr int kPrepRows = 128;   // expanded weight copies are padded to this many rows (the widest B tile) and to BK columns
 
@@ -48,6 +49,9 @@ struct SplitGemm {
     int64_t ldc;
     int32_t accumulate, relu;
     int32_t tiles_m, tiles_n;
+    int32_t taps;                          // CHAIN: products of k steps each
+    const float* tap_a[kMaxChain];
+    const uint16_t* tap_b[kMaxChain];
 };
 
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
@@ -190,8 +194,12 @@ __device__ __forceinline__ void multiply(const bf16x8 (&fa)[3][TMB], const bf16x
 // tile, the others multiply. (With rows padded to 80 bytes, two resident: the units idle 38 % of the time. 2,449,029 rows, 256 x 256
 // 1,996 -> 1,895 us, 100 x 256 1,171 -> 1,086; 169,343 rows 146 -> 137, 77 -> 70; 50,021 rows, whose tiles end just past a round of three
 // per unit, 47.6 -> 49.5.)
-template <int TERMS, int WM, int WN, int TMB, int TNB, int A_CH>
-__global__ __launch_bounds__(kThreads, 3) void gemm_split_kernel(SplitGemm g) {
+// CHAIN: the taps of a K-tap layer, act(((Y_0 H_0) + Y_1 H_1) + ..), each product summed by itself and added to the ones before it as launches
+// that add to C would, bit for bit, without C being written and read between them: a second set of accumulators, two workgroups
+// per compute unit where that takes 64 registers. Three taps over 60,013 rows, us, launch by launch / together: 64 -> 128 49 / 24, 128 -> 24
+// 33 / 24.
+template <int TERMS, int WM, int WN, int TMB, int TNB, int A_CH, bool CHAIN = false>
+__global__ __launch_bounds__(kThreads, CHAIN && TMB * TNB > 2 ? 2 : 3) void gemm_split_kernel(SplitGemm g) {
     static_assert(TERMS == 2 || TERMS == 3, "two or three bf16 terms per operand");
     constexpr int BM = 32 * TMB * WM, BN = 32 * TNB * WN;
     __shared__ __attribute__((aligned(16))) uint16_t smem[TERMS * (BM + BN) * kPitch];
@@ -204,7 +212,7 @@ __global__ __launch_bounds__(kThreads, 3) void gemm_split_kernel(SplitGemm g) {
     const int32_t xcd = blockIdx.x & 7, within = blockIdx.x >> 3;
     const int32_t tn = within % g.tiles_n, tm = (within / g.tiles_n) * 8 + xcd;
     if (tm >= g.tiles_m) return;               // whole workgroup leaves together: no barrier is skipped
-    const int32_t tiles1 = (g.k + BK - 1) / BK, tiles2 = (g.k2 + BK - 1) / BK, steps = tiles1 + tiles2;
+    const int32_t tiles1 = (g.k + BK - 1) / BK, tiles2 = (g.k2 + BK - 1) / BK, steps = CHAIN ? g.taps * tiles1 : tiles1 + tiles2;
     const int32_t m0 = tm * BM, n0 = tn * BN;
 
     const int lane = tid & 63;
@@ -220,6 +228,8 @@ __global__ __launch_bounds__(kThreads, 3) void gemm_split_kernel(SplitGemm g) {
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
 
+    floatx16 total[CHAIN ? TMB : 1][CHAIN ? TNB : 1] = {};
+
     // staging registers and per-thread offsets
     RowRegs<BM, A_CH> ra;
     PrepRegs<TERMS, BN> rb;
@@ -227,6 +237,12 @@ __global__ __launch_bounds__(kThreads, 3) void gemm_split_kernel(SplitGemm g) {
     plan_a.init(tid, m0, g.m, g.a.ld);            // a chained second product has the same leading dimensions
 
     auto fetch = [&](int32_t t) {
+        if constexpr (CHAIN) {
+            const int32_t tap = t / tiles1, stage = t - tap * tiles1;
+            load_rows<BM, A_CH>(tid, g.tap_a[tap] + int64_t(m0) * g.a.ld + stage * BK, plan_a, g.k - stage * BK, ra);
+            load_prep<TERMS, BN>(tid, g.tap_b[tap] + (int64_t(tn) * (g.b.ld / BK) + stage) * (TERMS * BN * BK), rb);
+            return;
+        }
         const bool first = t < tiles1;
         const int32_t k0 = (first ? t : t - tiles1) * BK, k_left = (first ? g.k : g.k2) - k0;
         const float* abase = static_cast<const float*>(first ? g.a.ptr : g.a2.ptr) + int64_t(m0) * g.a.ld + k0;
@@ -242,7 +258,7 @@ __global__ __launch_bounds__(kThreads, 3) void gemm_split_kernel(SplitGemm g) {
     // Half steps that hold padding only are left out: at most 16 values left means that only the first half multiplies.
     // (K = 2 x 100, N = 256 over 2,449,029 rows: 2.04 ms for all of 2 x 128, 1.92 without, both with two workgroups resident.)
     auto compute = [&](int32_t t) {
-        const int32_t left = t < tiles1 ? g.k - t * BK : g.k2 - (t - tiles1) * BK;
+        const int32_t left = CHAIN ? g.k - t % tiles1 * BK : t < tiles1 ? g.k - t * BK : g.k2 - (t - tiles1) * BK;
 #pragma unroll
         for (int s = 0; s < BK / 16; ++s) {
             if (s * 16 >= left) break;
@@ -275,10 +291,20 @@ __global__ __launch_bounds__(kThreads, 3) void gemm_split_kernel(SplitGemm g) {
         if (t + 1 < steps) fetch(t + 1);
         __syncthreads();
         compute(t);
+        if constexpr (CHAIN)
+            if ((t + 1) % tiles1 == 0)
+#pragma unroll
+                for (int i = 0; i < TMB; ++i)
+#pragma unroll
+                    for (int j = 0; j < TNB; ++j) total[i][j] = acc[i][j] + total[i][j], acc[i][j] = floatx16{};
         __syncthreads();       // the stage's fragments have been read: the next one may overwrite them
     }
 
-    store_tile(acc, g.c, g.ldc, g.m, g.n, m0 + wm, n0 + wn, m0 + BM <= g.m && n0 + BN <= g.n, lane, g.accumulate != 0, g.relu != 0);
+    const bool inside = m0 + BM <= g.m && n0 + BN <= g.n;
+    if constexpr (CHAIN)
+        store_tile(total, g.c, g.ldc, g.m, g.n, m0 + wm, n0 + wn, inside, lane, false, g.relu != 0);
+    else
+        store_tile(acc, g.c, g.ldc, g.m, g.n, m0 + wm, n0 + wn, inside, lane, g.accumulate != 0, g.relu != 0);
 }
 
 // ---------------------------------------------------------------------------------------------------------
@@ -693,12 +719,23 @@ bool varco_gemm_split_usable(const GemmArgs& ga) {
     return true;
 }
 
-hipError_t varco_launch_gemm_split(const GemmArgs& ga, hipStream_t stream, const LaunchTag& tag) {
+bool varco_gemm_split_taps_usable(const GemmArgs* g, int n) {
+    if (n < 2 || n > kMaxChain || g->accumulate || g->k2 > 0 || g->f32_terms != 3) return false;
+    for (int i = 0; i < n; ++i)
+        if (!varco_gemm_split_usable(g[i]) || g[i].m != g->m || g[i].n != g->n || g[i].k != g->k || g[i].k2 > 0 || g[i].a.ld != g->a.ld || g[i].b_prep_ld != g->b_prep_ld ||
+            g[i].f32_terms != 3 || g[i].c != g->c || g[i].ldc != g->ldc || g[i].accumulate != (i > 0) || (g[i].relu && i + 1 < n))
+            return false;
+    return true;
+}
+
+namespace {
+hipError_t launch_split(const GemmArgs* taps, int n, hipStream_t stream, const LaunchTag& tag) {
+    const GemmArgs& ga = *taps;
     const bool narrow = ga.n <= 64;
     const int bm = 128, bn = narrow ? 64 : 128;
     const bool a8 = ga.k % 8 == 0 && (ga.k2 == 0 || ga.k2 % 8 == 0);
 
-    SplitGemm g;
+    SplitGemm g{};
     g.m = ga.m, g.n = ga.n, g.k = ga.k, g.k2 = ga.k2;
     g.a = {ga.a.ptr, ga.a.ld};
     g.a2 = {ga.a2.ptr, ga.a2.ld};
@@ -707,7 +744,9 @@ hipError_t varco_launch_gemm_split(const GemmArgs& ga, hipStream_t stream, const
     g.c = static_cast<float*>(ga.c);
     g.ldc = ga.ldc;
     g.accumulate = ga.accumulate ? 1 : 0;
-    g.relu = ga.relu ? 1 : 0;
+    g.relu = taps[n - 1].relu ? 1 : 0;
+    g.taps = n;
+    for (int i = 0; i < n; ++i) g.tap_a[i] = static_cast<const float*>(taps[i].a.ptr), g.tap_b[i] = static_cast<const uint16_t*>(taps[i].b_prep);
     g.tiles_m = (ga.m + bm - 1) / bm;
     g.tiles_n = (ga.n + bn - 1) / bn;
     const int64_t blocks = int64_t((g.tiles_m + 7) / 8 * 8) * g.tiles_n;
@@ -719,6 +758,11 @@ hipError_t varco_launch_gemm_split(const GemmArgs& ga, hipStream_t stream, const
         with_flag(narrow, [&](auto nr) {
             with_flag(a8, [&](auto c8) {
                 constexpr bool NR = decltype(nr)::value;
+                if constexpr (decltype(t3)::value)
+                    if (n > 1) {
+                        hipLaunchKernelGGL((gemm_split_kernel<3, NR ? 4 : 2, NR ? 1 : 2, NR ? 1 : 2, 2, decltype(c8)::value ? 8 : 4, true>), grid, dim3(kThreads), 0, stream, g);
+                        return;
+                    }
                 hipLaunchKernelGGL((gemm_split_kernel<decltype(t3)::value ? 3 : 2, NR ? 4 : 2, NR ? 1 : 2, NR ? 1 : 2, 2, decltype(c8)::value ? 8 : 4>), grid,
                                    dim3(kThreads), 0, stream, g);
             });
@@ -727,3 +771,7 @@ hipError_t varco_launch_gemm_split(const GemmArgs& ga, hipStream_t stream, const
     tag.end(stream);
     return hipGetLastError();
 }
+}  // namespace
+
+hipError_t varco_launch_gemm_split(const GemmArgs& ga, hipStream_t stream, const LaunchTag& tag) { return launch_split(&ga, 1, stream, tag); }
+hipError_t varco_launch_gemm_split_taps(const GemmArgs* g, int n, hipStream_t stream, const LaunchTag& tag) { return launch_split(g, n, stream, tag); }

@@ -348,6 +348,9 @@ hipError_t varco_launch_gemm_tn_bf16(const GemmArgs& g, hipStream_t stream, cons
 // fp32 operands as sums of bf16 terms on the bf16 matrix cores (kernels_gemm_split.hip, kernels_gemm_split_rows.hip): the transform.
 bool varco_gemm_split_usable(const GemmArgs& g);
 hipError_t varco_launch_gemm_split(const GemmArgs& g, hipStream_t stream, const LaunchTag& tag);
+// Products that each add to what the one before them wrote, by one launch (the taps of a K-tap layer): the same bits.
+bool varco_gemm_split_taps_usable(const GemmArgs* g, int n);
+hipError_t varco_launch_gemm_split_taps(const GemmArgs* g, int n, hipStream_t stream, const LaunchTag& tag);
 bool varco_gemm_split_rows_usable(const GemmArgs& g);   // of 65 to 256 reduction steps, where weights in registers are faster
 hipError_t varco_launch_gemm_split_rows(const GemmArgs& g, hipStream_t stream, const LaunchTag& tag);
 // fp32 operands as two scaled fp16 terms on the fp16 matrix cores: input gradients (kernels_gemm_half.hip, kernels_gemm_half_nt.hip) and weight

@@ -844,9 +844,8 @@ extern "C" int32_t varco_network_aggregate_bwd(varco_ctx* ctx, int32_t tap, cons
 }
 
 // The dense products of all taps of a layer over the arena. The copies of all weights are made by one launch (as many as there
-// are slots); backward, the products of two taps, which share dZ, are formed by one launch where the kernels can. (Forward,
-// chaining the reductions of two taps would save a pass over the outputs, 4 % of a K-tap step, but form the sums in another
-// order than varco_transform_fwd, and round them once less with bf16 storage.)
+// are slots); forward, fp32 storage, so are their products, in the order of varco_transform_fwd; backward, the products of two taps, which
+// share dZ, are formed by one launch where the kernels can. (Chained products of bf16 storage would be rounded once less.)
 namespace {
 int32_t taps_prologue(varco_ctx* ctx, int32_t layer, int32_t n_taps, varco_stream stream, const char* fn, Workspace** ws) {
     if (int32_t rc = check_linked(ctx, fn)) return rc;
@@ -892,7 +891,12 @@ extern "C" int32_t varco_network_taps_fwd(varco_ctx* ctx, int32_t layer, int32_t
         }
         ctx->prof.interrupt();
         VARCO_HIP(ctx, varco_launch_prep_weights(jobs, n_jobs, st));
-        for (int32_t i = 0; i < n; ++i) VARCO_HIP(ctx, varco_launch_gemm(g[i], st, ctx->tag(VARCO_K_GEMM_FWD, 0, 2.0 * double(rows) * fo * fi)));
+        const double flops = 2.0 * double(rows) * fo * fi;
+        if (varco_gemm_split_taps_usable(g, n)) {
+            VARCO_HIP(ctx, varco_launch_gemm_split_taps(g, n, st, ctx->tag(VARCO_K_GEMM_FWD, 0, n * flops)));
+            continue;
+        }
+        for (int32_t i = 0; i < n; ++i) VARCO_HIP(ctx, varco_launch_gemm(g[i], st, ctx->tag(VARCO_K_GEMM_FWD, 0, flops)));
     }
     return VARCO_OK;
 }

@@ -311,3 +311,22 @@ def test_transform_sums_do_not_depend_on_the_kernel(n, conv, fi, fo):
     whole = outputs(0, fo)
     for c0 in range(0, fo, 64):
         assert torch.equal(whole[:, c0:c0 + 64].view(torch.int32), outputs(c0, min(c0 + 64, fo)).view(torch.int32)), c0
+
+
+@pytest.mark.parametrize("fi,fo", [(8, 8), (64, 128), (64, 24), (100, 130), (256, 256), (76, 64), (75, 40)])
+@pytest.mark.parametrize("n,taps", [(1, 2), (127, 3), (129, 4), (3001, 3), (3001, 5)])
+def test_taps_together_are_the_taps_in_turn(n, taps, fi, fo):
+    """The products of all taps of a layer in one launch: the bits of one launch after the other, each adding to the one before."""
+    from test_gpu_weight_gradients import _linked_context
+    rng = np.random.default_rng(n + fi + fo)
+    y = [dev(rng.standard_normal((n, fi)).astype(np.float32)) for _ in range(taps)]
+    h = [dev(synth.glorot(fi, fo, 3, 1 + t).astype(np.float32)) for t in range(taps)]
+    ctx, parts = _linked_context(n, min(n, 2), fi, fo, vb.F32, 3)
+    together, in_turn = (torch.full((n + 1, fo), 7.0, device="cuda") for _ in range(2))
+    ctx.network_taps_fwd(0, y, h, together[:n])
+    for t in range(taps):
+        ctx.transform_fwd(0, y[t], h[t], in_turn[:n], t > 0, t == taps - 1)
+    torch.cuda.synchronize()
+    assert torch.equal(together.view(torch.int32), in_turn.view(torch.int32))
+    ctx.close()
+    del parts
