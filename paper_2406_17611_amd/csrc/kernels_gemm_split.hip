@@ -24,6 +24,7 @@
 #include "elem.h"
 #include "gemm_tile.h"
 #include "half_terms.h"
+#include "prep_device.h"
 #include "varco_internal.h"
 
 namespace {
@@ -518,102 +519,9 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_short_k_kernel(const T* __re
     }
 }
 
-// Weight copies (see PrepJob). Copies in terms: element (term p, row r, column c) sits at
-//   (((r / bn) * (pitch / BK) + c / BK) * terms + p) * bn * BK + (r % bn) * BK + c % BK,
-// bn = rows of a B tile (64 for at most 64 rows, else 128). Behind two fp16 terms (rows_padded * pitch * 2 elements) follow the
-// scale exponents of the rows as 32-bit integers; there a workgroup takes 32 rows, looks for the largest value of each and splits them.
-// All copies of a step are made by one launch: a copy is a few
-// thousand elements, far less than a launch costs.
 template <int CAP>               // the table travels with the launch: a single copy should not carry 3 KB of it
-struct PrepJobs {
-    PrepJob job[CAP];
-    int32_t n;
-};
-// (not transposed) Eight lanes to a row, each with every eighth group of 8 columns: whole lines per load, and the largest value of
-// a row is found among the eight.
-__device__ __forceinline__ void prep_halves(const PrepJob& jb, int32_t block) {
-    constexpr int HELD = 4;                                          // groups kept in registers between the two passes (256 columns)
-    const int32_t r = block * 32 + (int32_t(threadIdx.x) >> 3), g0 = threadIdx.x & 7, groups = jb.pitch / 8, bn = jb.rows <= 64 ? 64 : 128;
-    const float* const row = jb.h + int64_t(min(r, jb.rows - 1)) * jb.ld;
-    auto read = [&](int32_t g, float (&x)[8]) {
-        const int32_t left = r < jb.rows ? jb.cols - g * 8 : 0;
-        if (left >= 8) {
-            const float4 u = load4_at(row, uint32_t(g) * 32u), v = load4_at(row, uint32_t(g) * 32u + 16u);
-            x[0] = u.x, x[1] = u.y, x[2] = u.z, x[3] = u.w, x[4] = v.x, x[5] = v.y, x[6] = v.z, x[7] = v.w;
-        } else {
-#pragma unroll
-            for (int i = 0; i < 8; ++i) x[i] = i < left ? row[g * 8 + i] : 0.f;
-        }
-    };
-    float held[HELD][8], m = 0.f;
-#pragma unroll
-    for (int q = 0; q < HELD; ++q) {
-        if (g0 + 8 * q < groups) read(g0 + 8 * q, held[q]);
-    }
-#pragma unroll
-    for (int q = 0; q < HELD; ++q)
-        if (g0 + 8 * q < groups) {
-#pragma unroll
-            for (int i = 0; i < 8; ++i) m = fmaxf(m, fabsf(held[q][i]));
-        }
-    for (int32_t g = g0 + 8 * HELD; g < groups; g += 8) {
-        float x[8];
-        read(g, x);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) m = fmaxf(m, fabsf(x[i]));
-    }
-#pragma unroll
-    for (int d = 4; d; d >>= 1) m = fmaxf(m, __shfl_xor(m, d));
-    const int e = scale_exponent(m, kHalfTop);
-    const float s = power_of_two(e);
-    uint16_t* const out = static_cast<uint16_t*>(jb.out);
-    auto write = [&](int32_t g, const float (&x)[8]) {
-        uint32_t hi[4], lo[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) split_pair(x[2 * i] * s, x[2 * i + 1] * s, hi[i], lo[i]);
-        const int64_t at = (int64_t(r / bn) * (jb.pitch / BK) + g * 8 / BK) * 2;
-        uint16_t* const dst = out + at * bn * BK + (r % bn) * BK + g * 8 % BK;
-        *reinterpret_cast<uint4*>(dst) = make_uint4(hi[0], hi[1], hi[2], hi[3]);
-        *reinterpret_cast<uint4*>(dst + bn * BK) = make_uint4(lo[0], lo[1], lo[2], lo[3]);
-    };
-#pragma unroll
-    for (int q = 0; q < HELD; ++q)
-        if (g0 + 8 * q < groups) write(g0 + 8 * q, held[q]);
-    for (int32_t g = g0 + 8 * HELD; g < groups; g += 8) {
-        float x[8];
-        read(g, x);
-        write(g, x);
-    }
-    if (g0 == 0) reinterpret_cast<int32_t*>(out + int64_t(jb.rows_padded) * jb.pitch * 2)[r] = e;
-}
-template <int CAP>
-__global__ __launch_bounds__(kThreads) void prep_weights_kernel(PrepJobs<CAP> jobs) {
-    int32_t at = 0;
-    while (at + 1 < jobs.n && int32_t(blockIdx.x) >= jobs.job[at + 1].first_block) ++at;
-    const PrepJob& jb = jobs.job[at];
-    const int32_t block = int32_t(blockIdx.x) - jb.first_block;
-    if (jb.terms == kHalfTerms) {
-        prep_halves(jb, block);
-        return;
-    }
-    const int64_t idx = int64_t(block) * kThreads + threadIdx.x;
-    if (idx >= int64_t(jb.rows_padded) * jb.pitch) return;
-    const int32_t r = int32_t(idx / jb.pitch), c = int32_t(idx % jb.pitch);
-    float x = 0.f;
-    if (r < jb.rows && c < jb.cols) x = jb.transpose ? jb.h[int64_t(c) * jb.ld + r] : jb.h[int64_t(r) * jb.ld + c];
-    uint16_t* const out = static_cast<uint16_t*>(jb.out);
-    if (jb.terms == 1) {
-        out[idx] = float_to_bf16(x);
-        return;
-    }
-    const int32_t bn = jb.rows <= 64 ? 64 : 128;
-    const int64_t first = (int64_t(r / bn) * (jb.pitch / BK) + c / BK) * jb.terms;
-    const int32_t inside = (r % bn) * BK + c % BK;
-    for (int p = 0; p < jb.terms; ++p) {
-        const uint16_t t = float_to_bf16(x);
-        out[(first + p) * bn * BK + inside] = t;
-        x -= __uint_as_float(uint32_t(t) << 16);
-    }
+__global__ __launch_bounds__(kPrepThreads) void prep_weights_kernel(PrepJobs<CAP> jobs) {
+    prep_weights(jobs, int32_t(blockIdx.x), int32_t(threadIdx.x));
 }
 
 bool aligned_to(const void* p, uintptr_t bytes) { return (reinterpret_cast<uintptr_t>(p) & (bytes - 1)) == 0; }
@@ -631,29 +539,35 @@ void with_flag(bool b, F&& f) {
 hipError_t varco_launch_prep_weights(PrepJob* jobs, int n, hipStream_t stream) {
     if (n <= 0) return hipSuccess;
     if (n > kMaxPrepJobs) return hipErrorInvalidValue;
-    int64_t blocks = 0;
-    for (int i = 0; i < n; ++i) {
-        PrepJob& j = jobs[i];
-        const bool plain = j.terms == 1 && j.rows_padded == j.rows && j.pitch >= j.cols;
-        const bool tiled = (j.terms == 2 || j.terms == 3 || (j.terms == kHalfTerms && !j.transpose)) && j.rows_padded >= j.rows && j.rows_padded % kPrepRows == 0 && j.pitch >= j.cols && j.pitch % BK == 0;
-        if (!plain && !tiled) return hipErrorInvalidValue;
-        j.first_block = int32_t(blocks);
-        blocks += j.terms == kHalfTerms ? j.rows_padded / 32 : (int64_t(j.rows_padded) * j.pitch + kThreads - 1) / kThreads;
-    }
+    const int64_t blocks = varco_prep_blocks(jobs, n);
+    if (blocks < 0) return hipErrorInvalidValue;
     if (blocks == 0) return hipSuccess;
     auto go = [&](auto cap) {
         PrepJobs<decltype(cap)::value> args{};
         for (int i = 0; i < n; ++i) args.job[i] = jobs[i];
         args.n = n;
-        hipLaunchKernelGGL((prep_weights_kernel<decltype(cap)::value>), dim3(unsigned(blocks)), dim3(kThreads), 0, stream, args);
+        hipLaunchKernelGGL((prep_weights_kernel<decltype(cap)::value>), dim3(unsigned(blocks)), dim3(kPrepThreads), 0, stream, args);
     };
     if (n == 1)
         go(std::integral_constant<int, 1>{});
-    else if (n <= 8)
-        go(std::integral_constant<int, 8>{});
+    else if (n <= kFewPrepJobs)
+        go(std::integral_constant<int, kFewPrepJobs>{});
     else
         go(std::integral_constant<int, kMaxPrepJobs>{});
     return hipGetLastError();
+}
+
+int64_t varco_prep_blocks(PrepJob* jobs, int n) {
+    int64_t blocks = 0;
+    for (int i = 0; i < n; ++i) {
+        PrepJob& j = jobs[i];
+        const bool plain = j.terms == 1 && j.rows_padded == j.rows && j.pitch >= j.cols;
+        const bool tiled = (j.terms == 2 || j.terms == 3 || (j.terms == kHalfTerms && !j.transpose)) && j.rows_padded >= j.rows && j.rows_padded % kPrepRows == 0 && j.pitch >= j.cols && j.pitch % BK == 0;
+        if (!plain && !tiled) return -1;
+        j.first_block = int32_t(blocks);
+        blocks += j.terms == kHalfTerms ? j.rows_padded / 32 : (int64_t(j.rows_padded) * j.pitch + kThreads - 1) / kThreads;
+    }
+    return blocks;
 }
 
 namespace {

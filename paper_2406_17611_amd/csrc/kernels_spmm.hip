@@ -24,6 +24,7 @@
 #include "elem.h"
 #include "gather_device.h"
 #include "mask_device.h"
+#include "prep_device.h"
 
 namespace {
 
@@ -91,11 +92,11 @@ struct SpmmArgs {
     int32_t ku;               // loads per compressed row = k / ev
     int32_t lpe_log2;         // lanes that share one compressed row = 1 << lpe_log2 (>= min(ku, 64))
     int32_t epi;              // compressed rows handled per instruction = private LDS rows per wavefront
-    // kOwner: the messages themselves, written by the workgroups from `copy_block` on (see owner_messages)
+    // kOwner: the messages themselves, written by the workgroups from `copy_block` to `prep_block` (see owner_messages)
     const int32_t *brow, *bgid;
     T* messages;
     uint32_t n_messages;      // elements: boundary rows x k
-    int32_t copy_block;
+    int32_t copy_block, prep_block;
 };
 
 // N consecutive stored elements as they come from memory (bf16 stays packed until it is used).
@@ -314,8 +315,8 @@ __device__ __forceinline__ void owner_messages(const SpmmArgs<T>& p, uint32_t bl
 // kernel per form: the constants of forms that do not run would take registers, i.e. resident wavefronts, from the one
 // that does.
 constexpr int kDenseOnly = 0, kFull = 1, kSparse = 2, kSparseZ32 = 3, kOwner = 4;
-template <typename T, int VEC, int NV, int MODE, int EV = 1, bool POW2 = false>
-__global__ __launch_bounds__(agg_block(MODE), MODE >= kSparse && VEC * NV <= 8 ? kHaloWaves : 1) void spmm_kernel(SpmmArgs<T> p) {
+template <typename T, int VEC, int NV, int MODE, int EV, bool POW2>
+__device__ __forceinline__ void spmm_rows(const SpmmArgs<T>& p) {
     constexpr bool HALO = MODE != kDenseOnly, SPARSE = MODE >= kSparse, Z32 = MODE == kSparseZ32;
     constexpr int kAggBlock = agg_block(MODE), kAggWaves = kAggBlock / 64;
     constexpr int U = NV >= 4 ? 1 : (NV == 2 ? 2 : (HALO ? kUnroll : kUnrollDense)), NR = loads_per_row(NV);
@@ -325,11 +326,6 @@ __global__ __launch_bounds__(agg_block(MODE), MODE >= kSparse && VEC * NV <= 8 ?
     const int wave = threadIdx.x >> 6;
     const int32_t width = int32_t(p.rule.width);
 
-    if constexpr (MODE == kOwner)
-        if (int32_t(blockIdx.x) >= p.copy_block) {
-            owner_messages(p, blockIdx.x - uint32_t(p.copy_block), lane);
-            return;
-        }
     // Workgroups are dealt to the 8 XCDs round-robin; an XCD takes the work list in runs of kXcdRun consecutive
     // workgroups (the grid is a multiple of 8 runs), so that rows next to each other - which on a graph with any
     // locality share source rows - are aggregated through the same L2 at about the same time, while every XCD still
@@ -408,6 +404,22 @@ __global__ __launch_bounds__(agg_block(MODE), MODE >= kSparse && VEC * NV <= 8 ?
                 put_floats<VEC>(p.partial + int64_t(it.dst) * width + c, acc[m]);
         }
     }
+}
+
+template <typename T, int VEC, int NV, int MODE, int EV = 1, bool POW2 = false>
+__global__ __launch_bounds__(agg_block(MODE), MODE >= kSparse && VEC * NV <= 8 ? kHaloWaves : 1) void spmm_kernel(SpmmArgs<T> p) {
+    spmm_rows<T, VEC, NV, MODE, EV, POW2>(p);
+}
+// kOwner, then the messages, then weight copies, a workgroup of which is four here.
+template <typename T, int NV, int EV>
+__global__ __launch_bounds__(64, kHaloWaves) void spmm_owner_kernel(SpmmArgs<T> p, PrepJobs<kFewPrepJobs> copies) {
+    const int32_t block = int32_t(blockIdx.x), lane = int32_t(threadIdx.x);
+    if (block < p.copy_block)
+        spmm_rows<T, 4, NV, kOwner, EV, false>(p);
+    else if (block < p.prep_block)
+        owner_messages(p, uint32_t(block - p.copy_block), lane);
+    else
+        prep_weights(copies, (block - p.prep_block) >> 2, ((block - p.prep_block) & 3) * 64 + lane);
 }
 
 // Dense-only blocks whose rows are very short (the transposed local block of a finely partitioned graph has
@@ -1063,12 +1075,18 @@ hipError_t spmm_t(const SpmmPlan& plan, const VarcoEdge* edge, const int32_t* co
     const int agg_waves = agg_block(halo ? kFull : kDenseOnly) / 64;
     const int32_t per_round = 8 * kXcdRun;                                         // see the kernel's XCD mapping
     dim3 grid(((plan.n_items + agg_waves - 1) / agg_waves + per_round - 1) / per_round * per_round);
+    PrepJobs<kFewPrepJobs> copies{};
     if (owners) {
         a.brow = owners->brow, a.bgid = owners->bgid;
         a.messages = static_cast<T*>(const_cast<void*>(z_v));
         a.n_messages = uint32_t(z_rows) * rule.k;
         a.copy_block = int32_t(grid.x);
-        grid.x += (a.n_messages + 255) / 256;
+        a.prep_block = a.copy_block + int32_t((a.n_messages + 255) / 256);
+        const int64_t blocks = varco_prep_blocks(owners->jobs, owners->n_jobs);
+        if (blocks < 0 || owners->n_jobs > kFewPrepJobs) return hipErrorInvalidValue;
+        for (int i = 0; i < owners->n_jobs; ++i) copies.job[i] = owners->jobs[i];
+        copies.n = owners->n_jobs;
+        grid.x = unsigned(a.prep_block + 4 * blocks);
     }
     size_t lds_bytes = 0;
     if (halo && !full)
@@ -1086,8 +1104,8 @@ hipError_t spmm_t(const SpmmPlan& plan, const VarcoEdge* edge, const int32_t* co
     if (owners) {
         auto with_ev = [&](auto e) {
             constexpr int EV = decltype(e)::value;
-            const auto kernel = nv == 0 ? spmm_kernel<T, 4, 0, kOwner, EV> : spmm_kernel<T, 4, 1, kOwner, EV>;
-            hipLaunchKernelGGL(kernel, grid, dim3(agg_block(kOwner)), lds_bytes, stream, a);
+            const auto kernel = nv == 0 ? spmm_owner_kernel<T, 0, EV> : spmm_owner_kernel<T, 1, EV>;
+            hipLaunchKernelGGL(kernel, grid, dim3(64), lds_bytes, stream, a, copies);
             return hipGetLastError();
         };
         if (vec == 4 && nv <= 1 && halo && !full)

@@ -163,8 +163,12 @@ hipError_t varco_launch_build_edges(const int32_t* colidx, int64_t nnz, int32_t 
                                     const int32_t* halo_gid, VarcoEdge* edge, hipStream_t stream);
 
 // Where a launch finds the owners' rows: the row of `dense` of every entry's column, and row and node of every row of z.
+// jobs: weight copies to be made by the launch as well (at most kFewPrepJobs).
+struct PrepJob;
 struct SpmmOwners {
     const int32_t *arow, *brow, *bgid;
+    PrepJob* jobs;
+    int n_jobs;
 };
 
 // out[row - row_base, :] = sum_e vals[e] * source_row(e) for the rows of `plan`, width = rule.width.
@@ -377,7 +381,9 @@ struct PrepJob {
     int32_t ld, rows, cols, rows_padded, pitch, transpose, terms, first_block;
 };
 constexpr int kMaxPrepJobs = 4 * VARCO_MAX_LAYERS;
+constexpr int kFewPrepJobs = 8;         // copies that a launch which does something else as well may carry
 hipError_t varco_launch_prep_weights(PrepJob* jobs, int n, hipStream_t stream);
+int64_t varco_prep_blocks(PrepJob* jobs, int n);       // sets their first_block; workgroups of all copies, -1: a job that is none
 
 // Whether varco_launch_gemm forms g and its dual product in one launch.
 bool varco_gemm_dual_usable(const GemmArgs& g);

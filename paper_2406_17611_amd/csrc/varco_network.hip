@@ -268,9 +268,13 @@ int32_t null_pointer(const varco_ctx* ctx, const char* fn) {
 }
 
 // M = S [local rows of x; compressed rows of z] for all partitions.
-// write_z: z is written by the same launch and not read (varco_spmm_owners_pay).
+// with_z: z is written by the same launch and not read (varco_spmm_owners_pay), and the given weight copies are made by it.
+struct PrepList {
+    PrepJob job[kMaxPrepJobs];
+    int n = 0;
+};
 int32_t aggregate_fwd(varco_ctx* ctx, Workspace& ws, int32_t layer, const MaskRule& rule, const void* x, const void* z, void* m, hipStream_t st,
-                      bool write_z = false) {
+                      PrepList* with_z = nullptr) {
     const NetState& net = ctx->net;
     const double es = ctx->elem_bytes();
     const int32_t fi = ctx->widths[layer];
@@ -281,9 +285,10 @@ int32_t aggregate_fwd(varco_ctx* ctx, Workspace& ws, int32_t layer, const MaskRu
     if (rule.k == rule.width)   // lossless: a message equals the owner's row, which is nearer (the same rows serve the local entries)
         VARCO_HIP(ctx, varco_launch_spmm(ctx->dtype, net.fwd, nullptr, net.arow, net.vals, x, nullptr, 0, full_rule(fi), m, 0, ws.spmm, st, tag));
     else {
-        const SpmmOwners owners{net.arow, net.brow, net.bgid};
+        SpmmOwners owners{net.arow, net.brow, net.bgid, nullptr, 0};
+        if (with_z) owners.jobs = with_z->job, owners.n_jobs = with_z->n;
         VARCO_HIP(ctx, varco_launch_spmm(ctx->dtype, net.fwd, net.edges, nullptr, net.vals, x, z, net.boundary, rule, m, 0, ws.spmm, st, tag,
-                                         write_z ? &owners : nullptr));
+                                         with_z ? &owners : nullptr));
     }
     ctx->stats.fwd_elems[layer] += net.halo_rows * rule.k;
     ctx->stats.full_fwd_elems[layer] += net.halo_rows * fi;
@@ -598,7 +603,8 @@ int32_t class_bwd(varco_ctx* ctx, Workspace& ws, const varco_network_buffers& b,
     return l > 0 ? class_input(ctx, ws, c, l, rule, r, st) : VARCO_OK;
 }
 
-int32_t layer_fwd(varco_ctx* ctx, Workspace& ws, const varco_network_buffers& b, int32_t l, hipStream_t st) {
+// copies: weight copies that have not been made yet (the pass's first layer); made here.
+int32_t layer_fwd(varco_ctx* ctx, Workspace& ws, const varco_network_buffers& b, int32_t l, PrepList& copies, hipStream_t st) {
     const NetState& net = ctx->net;
     const int32_t fi = ctx->widths[l], fo = ctx->widths[l + 1];
     const bool sage = ctx->conv == VARCO_CONV_SAGE;
@@ -607,11 +613,17 @@ int32_t layer_fwd(varco_ctx* ctx, Workspace& ws, const varco_network_buffers& b,
     const bool first = ctx->layers[l].order == VARCO_ORDER_TRANSFORM_FIRST;
     const MaskRule rule = make_rule(ctx, l);
     const bool together = !first && varco_spmm_owners_pay(dt, net.fwd, rule, net.rows, net.nnz_cross, net.boundary, b.x[l], b.m[l], ws.spmm);
+    if (copies.n > 0 && !(together && copies.n <= kFewPrepJobs)) {
+        ctx->prof.interrupt();
+        VARCO_HIP(ctx, varco_launch_prep_weights(copies.job, copies.n, st));
+        copies.n = 0;
+    }
     if (!together)
         if (int32_t rc = compress_all(ctx, l, rule, b.x[l], b.z[l], st)) return rc;
     if (first) return class_fwd(ctx, ws, b, l, st);
     ctx->layers[l].ran_forward = true;
-    if (int32_t rc = aggregate_fwd(ctx, ws, l, rule, b.x[l], b.z[l], b.m[l], st, together)) return rc;
+    if (int32_t rc = aggregate_fwd(ctx, ws, l, rule, b.x[l], b.z[l], b.m[l], st, together ? &copies : nullptr)) return rc;
+    copies.n = 0;
     if (net.rows > 0) {
         GemmArgs g;
         g.m = int32_t(net.rows), g.n = fo, g.k = fi;
@@ -707,11 +719,11 @@ int32_t finish_sums(varco_ctx* ctx, WeightSums& sums, hipStream_t st) {
     return VARCO_OK;
 }
 
-// All weight copies a pass needs, in one launch: those of the forward products, and when the buffers hold weight gradients
+// All weight copies a pass needs, for one launch: those of the forward products, and when the buffers hold weight gradients
 // (a backward pass follows) those of the input gradients as well.
-int32_t prep_all(varco_ctx* ctx, Workspace& ws, const varco_network_buffers& b, hipStream_t st) {
-    PrepJob jobs[kMaxPrepJobs];
-    int n = 0;
+void prep_all(varco_ctx* ctx, Workspace& ws, const varco_network_buffers& b, PrepList& list) {
+    PrepJob* const jobs = list.job;
+    int& n = list.n;
     GemmArgs unused;
     for (int32_t l = 0; l < ctx->n_layers; ++l) {
         const int32_t fi = ctx->widths[l], fo = ctx->widths[l + 1];
@@ -725,9 +737,6 @@ int32_t prep_all(varco_ctx* ctx, Workspace& ws, const varco_network_buffers& b, 
                 n += prep_slot(ctx, ws, l, h, fi, fo, false, which, false, unused, jobs + n) ? 1 : 0;
         }
     }
-    ctx->prof.interrupt();
-    VARCO_HIP(ctx, varco_launch_prep_weights(jobs, n, st));
-    return VARCO_OK;
 }
 
 int32_t check_buffers(const varco_ctx* ctx, const varco_network_buffers* b, bool backward, const char* fn) {
@@ -792,9 +801,10 @@ extern "C" int32_t varco_network_forward(varco_ctx* ctx, const varco_network_buf
     hipStream_t st = static_cast<hipStream_t>(stream);
     Workspace* ws = nullptr;
     if (int32_t rc = workspace_for(ctx, st, &ws, fn)) return rc;
-    if (int32_t rc = prep_all(ctx, *ws, *b, st)) return rc;
+    PrepList copies;
+    prep_all(ctx, *ws, *b, copies);
     for (int32_t l = 0; l < ctx->n_layers; ++l)
-        if (int32_t rc = layer_fwd(ctx, *ws, *b, l, st)) return rc;
+        if (int32_t rc = layer_fwd(ctx, *ws, *b, l, copies, st)) return rc;
     return VARCO_OK;
 }
 
