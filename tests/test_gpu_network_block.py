@@ -115,3 +115,13 @@ def test_messages_written_with_the_sums(widths, ratio, dtype, n):
             torch.cuda.synchronize()
             sent = net.b_total * net.ctx.keep(l)
             assert torch.equal(net.z[l][:sent], z[:sent]) and torch.equal(net.m[l], m), (l, step)
+
+
+@pytest.mark.parametrize("conv,widths", [("gcn", (20, 96, 130, 72, 9)), ("sage", (24, 96, 8)), ("sage", (20, 96, 130, 72, 9)), ("gcn", (21, 256, 66, 5))])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_weight_copies_made_with_the_first_sums(conv, widths, dtype):
+    """At most eight copies, for products and input gradients, made by the first aggregation's launch; more than eight, an input width that
+    is no multiple of 4 and a lossless first layer, where they have a launch of their own."""
+    g = synth.small_random_graph(700, 7.0, conv, seed=95)
+    _compare_network(g, synth.random_partition(g.n, 3, seed=96), 3, conv, widths, [(4, 1), (3, 1), (1, 1)], steps=[0, 1, 2],
+                     tol=BF16_TOL if dtype == "bf16" else 1e-4, dtype=dtype)
