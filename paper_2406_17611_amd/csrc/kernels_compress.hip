@@ -44,15 +44,15 @@ __global__ __launch_bounds__(kBlock) void compress_kernel(MaskRule rule, const i
 // of 256, element-wise -> through LDS: decoder 265 -> 116 us (fp32, k = 32), 197 -> 64 (bf16, k = 64); encoder 197 -> 133
 // (fp32, k = 128), 136 -> 46 (bf16, k = 64); decoder with sum 224 -> 196 (fp32, k = 32), 194 -> 135
 // (bf16, k = 128). Where the element-wise kernels win (few kept elements, narrow or unaligned rows): codec_rows_pay.
-// A wavefront is a workgroup and takes one group of rows: workgroups start in the order of the rows, so that what is in flight lies
-// close together in memory, which drifting wavefronts that each walk the whole range lose (a plain copy: 6.2 against 4.8 TB/s; this
-// encoder / decoder / decoder with sum of 450,007 of 600,011 fp32 rows of 256, k = 32: persistent workgroups of four wavefronts
-// 103 / 114 / 197 us, one group of rows each 97 / 108 / 183; the three calls in turn 432 -> 404 us).
+// Two forms. codec_rows_kernel: persistent workgroups of four wavefronts that walk the range, the next group's rows already requested.
+// codec_wide_rows_kernel: a wavefront is a workgroup and takes one group of rows; workgroups start in the order of the rows, so that
+// what is in flight lies close together in memory, which drifting wavefronts lose (a plain copy: 6.2 against 4.8 TB/s). Which one: codec_rows_wide.
 //   MODE 0: z[i, j] = x[row_i, pi(j)];  1: x[row_i, :] = 0 except x[row_i, pi(j)] = z[i, j];  2: x[row_i, pi(j)] += z[i, j],
 //   in LDS on the old row, which is written back whole: what is not added to keeps its bits
 // S: the storage word (fp32 or bf16 bits); V: elements per access to x (16 bytes, or 1 for unaligned rows); PE: elements of z
-// per lane (2 for bf16 pairs); U: rows of a group; ONE: a row is at most one access per lane.
-constexpr int kCodecBlock = 64;
+// per lane (2 for bf16 pairs); U: rows of a group (codec_rows_kernel: kRowsInFlight); ONE: a row is at most one access per lane.
+constexpr int kRowsInFlight = 4;         // of codec_rows_kernel
+constexpr int kCodecBlock = 64;          // of codec_wide_rows_kernel
 constexpr int64_t kL2Bytes = int64_t(8) * 4 << 20;      // eight L2 caches of 4 MB
 constexpr int64_t kCodecGrid = int64_t(1) << 24;      // a launch holds fewer than 2^32 threads
 template <typename S>
@@ -63,8 +63,114 @@ __device__ __forceinline__ S add_words(S x, S z) {
         return float_to_bf16(bf16_to_float(x) + bf16_to_float(z));
 }
 
+template <typename S, int MODE, int V, int PE, bool ONE>
+__global__ __launch_bounds__(kBlock) void codec_rows_kernel(MaskRule rule, const int32_t* __restrict__ gids, const int32_t* __restrict__ rows,
+                                                            int64_t n_rows, S* x, int64_t ldx, S* z, int lpe_log2) {
+    constexpr int U = kRowsInFlight;
+    typedef S Vec __attribute__((ext_vector_type(V)));
+    typedef S Pair __attribute__((ext_vector_type(PE)));
+    extern __shared__ __attribute__((aligned(16))) unsigned char codec_lds[];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int32_t width = int32_t(rule.width), k = int32_t(rule.k);
+    const int32_t pitch = (width + 7) & ~7;
+    S* const buf = reinterpret_cast<S*>(codec_lds) + wave * U * pitch;
+    const int lpe = 1 << lpe_log2, sub = lane >> lpe_log2, jl = lane & (lpe - 1), n_sub = 64 >> lpe_log2;
+    auto clear = [&]() {
+        for (int u = 0; u < U; ++u)
+            for (int c = lane * V; c < width; c += 64 * V) *reinterpret_cast<Vec*>(buf + u * pitch + c) = Vec(S(0));
+    };
+    if (MODE == 1) clear();
+    const int64_t stride = int64_t(gridDim.x) * (kBlock / 64) * U;
+    int64_t r0 = (int64_t(blockIdx.x) * (kBlock / 64) + wave) * U;
+    if (r0 >= n_rows) return;                        // wavefronts are independent: no barrier
+    // Software pipeline over groups of U rows: the rows' ids are fetched two groups ahead, their data one group ahead.
+    int32_t gid = 0, src = 0;                        // lane u: of row u of a group (past the end: the last row)
+    auto load_ids = [&](int64_t r) {
+        const int64_t i = min(r + (lane & (U - 1)), n_rows - 1);
+        gid = gids[i];
+        if (rows) src = rows[i];
+    };
+    int64_t at[U];                                   // element offset of the group's rows in x
+    uint32_t ab = 0;
+    auto resolve = [&](int64_t r) {
+        const MaskAffine m = varco_affine(rule, uint32_t(gid));
+        ab = m.a | (m.b << 16);
+#pragma unroll
+        for (int u = 0; u < U; ++u) at[u] = (rows ? int64_t(__shfl(src, u)) : min(r + u, n_rows - 1)) * ldx;
+    };
+    Vec v[U];
+    const int own = min(lane * V, width - V);        // lanes past the row repeat its last access (never stored)
+    auto load_rows = [&]() {
+        if constexpr (ONE && MODE != 1) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) v[u] = *reinterpret_cast<const Vec*>(x + at[u] + own);
+        }
+    };
+    load_ids(r0);
+    resolve(r0);
+    load_rows();
+    if (r0 + stride < n_rows) load_ids(r0 + stride);
+    for (; r0 < n_rows; r0 += stride) {
+        const int n_here = int(min(int64_t(U), n_rows - r0));
+        const uint32_t ab_now = ab;
+        int64_t at_now[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) at_now[u] = at[u];
+        if constexpr (MODE != 1) {
+            if constexpr (ONE) {
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    if (lane * V < width) *reinterpret_cast<Vec*>(buf + u * pitch + lane * V) = v[u];
+            } else {
+                for (int c = lane * V; c < width; c += 64 * V)
+#pragma unroll
+                    for (int u = 0; u < U; ++u) *reinterpret_cast<Vec*>(buf + u * pitch + c) = *reinterpret_cast<const Vec*>(x + at_now[u] + c);
+            }
+        }
+        if (r0 + stride < n_rows) {
+            resolve(r0 + stride);
+            load_rows();
+            if (r0 + 2 * stride < n_rows) load_ids(r0 + 2 * stride);
+        }
+        __builtin_amdgcn_wave_barrier();
+        // the kept elements: a group of lanes serves one row, the groups different rows
+        for (int u0 = 0; u0 < n_here; u0 += n_sub) {
+            const int u = u0 + sub;
+            const uint32_t m = __shfl(ab_now, u & (U - 1)), a = m & 0xFFFFu;
+            if (u < n_here) {
+                S* const row = buf + u * pitch;
+                for (int j = jl * PE; j < k; j += lpe * PE) {
+                    uint32_t q = varco_mod_width(__umul24(a, uint32_t(j)) + (m >> 16), rule.width, rule.width_magic);
+                    Pair* const zp = reinterpret_cast<Pair*>(z + (r0 + u) * k + j);
+                    Pair e;
+                    if constexpr (MODE != 0) e = *zp;
+#pragma unroll
+                    for (int i = 0; i < PE; ++i) {
+                        if constexpr (MODE == 0)
+                            e[i] = row[q];
+                        else
+                            row[q] = MODE == 1 ? e[i] : add_words<S>(row[q], e[i]);
+                        q += a;
+                        q = min(q, q - rule.width);
+                    }
+                    if (MODE == 0) *zp = e;
+                }
+            }
+        }
+        __builtin_amdgcn_wave_barrier();
+        if (MODE == 0) continue;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (u >= n_here) break;
+            for (int c = lane * V; c < width; c += 64 * V) *reinterpret_cast<Vec*>(x + at_now[u] + c) = *reinterpret_cast<const Vec*>(buf + u * pitch + c);
+        }
+        if (MODE == 1) clear();
+        __builtin_amdgcn_wave_barrier();
+    }
+}
+// The other form: one group of rows per wavefront.
 template <typename S, int MODE, int U, int V, int PE, bool ONE>
-__global__ __launch_bounds__(kCodecBlock) void codec_rows_kernel(MaskRule rule, const int32_t* __restrict__ gids, const int32_t* __restrict__ rows,
+__global__ __launch_bounds__(kCodecBlock) void codec_wide_rows_kernel(MaskRule rule, const int32_t* __restrict__ gids, const int32_t* __restrict__ rows,
                                                                  int64_t n_rows, S* x, int64_t ldx, S* z, int lpe_log2) {
     typedef S Vec __attribute__((ext_vector_type(V)));
     typedef S Pair __attribute__((ext_vector_type(PE)));
@@ -335,6 +441,18 @@ hipError_t launch_whole_rows(const MaskRule& rule, const int32_t* rows, int64_t 
     return hipGetLastError();
 }
 
+// One group of rows per wavefront pays where a row is long enough to hide the wavefront's start and its chain of ids, rows, picks: from 1.5 KB on,
+// from 1 KB on with 16-bit elements or where at most an eighth is kept. Encoder, decoder and decoder with sum in turn, walking / one group each, us:
+//   490,000 fp32 rows of 400, ratio 2, 4, 16 990 / 967, 835 / 830, 738 / 720    505 1,387 / 1,295, 1,194 / 1,172, 930 / 924    512 1,204 / 1,180, 1,004 / 993,
+//   803 / 822    bf16 rows of 512 552 / 539, 484 / 468, 476 / 472    450,007 fp32 rows of 256, ratio 8 435 / 417
+// below: 630,000 fp32 rows of 256, ratio 2 and 4 668 / 689, 585 / 589    770,000 of 64 283 / 349, 229 / 307    118 466 / 498, 423 / 426
+//   bf16 rows of 64 211 / 271, 182 / 199    256 390 / 410, 334 / 359    490,000 of 505 723 / 792, 610 / 609
+template <typename T>
+bool codec_rows_wide(const MaskRule& rule) {
+    const uint32_t bytes = rule.width * uint32_t(sizeof(T));
+    return bytes >= 1536 || (bytes >= 1024 && (sizeof(T) == 2 || rule.k * 8 <= rule.width));
+}
+
 template <typename T, int MODE, int U = 4>
 hipError_t launch_codec_rows(const MaskRule& rule, const int32_t* gids, const int32_t* rows, int64_t n_rows, void* x, int64_t ldx, void* z,
                              hipStream_t stream) {
@@ -344,11 +462,19 @@ hipError_t launch_codec_rows(const MaskRule& rule, const int32_t* gids, const in
     const bool pair = sizeof(S) == 2 && rule.k % 2 == 0 && (reinterpret_cast<uintptr_t>(z) & 3u) == 0;
     const bool one = int(rule.width) <= 64 * (vec ? V16 : 1);
     const int lpe = group_log2(pair ? rule.k / 2 : rule.k);
-    const size_t lds = size_t(U) * ((rule.width + 7) & ~7u) * sizeof(S);
-    const int64_t blocks = std::min((n_rows + U - 1) / U, kCodecGrid);
+    constexpr int W = kBlock / 64;
+    const bool wide = codec_rows_wide<T>(rule);
+    const size_t row = size_t((rule.width + 7) & ~7u) * sizeof(S);
+    const int64_t blocks = wide ? std::min((n_rows + U - 1) / U, kCodecGrid) : std::min<int64_t>((n_rows + W * kRowsInFlight - 1) / (W * kRowsInFlight), 256 * 32);
     auto go = [&](auto vc, auto pc, auto oc) {
-        hipLaunchKernelGGL((codec_rows_kernel<S, MODE, U, decltype(vc)::value, decltype(pc)::value, decltype(oc)::value>), dim3(unsigned(blocks)),
-                           dim3(kCodecBlock), lds, stream, rule, gids, rows, n_rows, static_cast<S*>(x), ldx, static_cast<S*>(z), lpe);
+        constexpr int V = decltype(vc)::value, PE = decltype(pc)::value;
+        constexpr bool ONE = decltype(oc)::value;
+        if (wide)
+            hipLaunchKernelGGL((codec_wide_rows_kernel<S, MODE, U, V, PE, ONE>), dim3(unsigned(blocks)), dim3(kCodecBlock), U * row, stream, rule, gids, rows,
+                               n_rows, static_cast<S*>(x), ldx, static_cast<S*>(z), lpe);
+        else
+            hipLaunchKernelGGL((codec_rows_kernel<S, MODE, V, PE, ONE>), dim3(unsigned(blocks)), dim3(kBlock), W * kRowsInFlight * row, stream, rule, gids,
+                               rows, n_rows, static_cast<S*>(x), ldx, static_cast<S*>(z), lpe);
     };
     auto with_one = [&](auto vc, auto pc) {
         if (one)

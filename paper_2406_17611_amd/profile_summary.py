@@ -48,7 +48,7 @@ def _kernel_class(n: str):
     """bench.py's kernel class of a kernel name (None for kernels outside the memory-bound classes)."""
     for prefix, c in (("spmm_kernel", "agg_fwd"), ("node_sum_kernel", "agg_bwd_local"),
                       ("narrow_backward_kernel", "agg_bwd_local"), ("halo_products_kernel", "agg_bwd_halo"),
-                      ("codec_rows_kernel", "compress"), ("whole_rows_kernel", "compress"), ("compress_kernel", "compress")):
+                      ("codec_rows_kernel", "compress"), ("codec_wide_rows_kernel", "compress"), ("whole_rows_kernel", "compress"), ("compress_kernel", "compress")):
         if n.startswith(prefix):
             return c
     return None

@@ -51,6 +51,13 @@ def test_aligned_rows(dtype, width, ratio, n_rows):
     ctx.close()
 
 
+@pytest.mark.parametrize("dtype,width,ratio,n_rows", [("f32", 256, (7, 1), 1025), ("f32", 255, (2, 1), 1025), ("f32", 380, (2, 1), 3), ("f32", 384, (2, 1), 1025),
+                                                      ("f32", 385, (2, 1), 5), ("bf16", 511, (2, 1), 1025), ("bf16", 516, (2, 1), 3),
+                                                      ("f32", 12, (3, 1), 131_107), ("bf16", 16, (2, 1), 262_147)])
+def test_both_sides_of_the_line_by_row_length(dtype, width, ratio, n_rows):
+    test_aligned_rows(dtype, width, ratio, n_rows)      # the last two: wavefronts that walk take more than one group
+
+
 @pytest.mark.parametrize("dtype,width,ratio", [("f32", 256, (8, 1)), ("f32", 2048, (4, 1)), ("f32", 75, (2, 1)), ("bf16", 512, (4, 1)),
                                                ("bf16", 2048, (3, 1)), ("bf16", 256, (1, 1))])
 def test_adding_decoder_leaves_other_elements_alone(dtype, width, ratio):
