@@ -443,13 +443,14 @@ hipError_t launch_whole_rows(const MaskRule& rule, const int32_t* rows, int64_t 
 
 // One group of rows per wavefront pays where a row is long enough to hide the wavefront's start and its chain of ids, rows, picks: from 1.5 KB on,
 // from 1 KB on with 16-bit elements or where at most an eighth is kept. Encoder, decoder and decoder with sum in turn, walking / one group each, us:
-//   490,000 fp32 rows of 400, ratio 2, 4, 16 990 / 967, 835 / 830, 738 / 720    505 1,387 / 1,295, 1,194 / 1,172, 930 / 924    512 1,204 / 1,180, 1,004 / 993,
-//   803 / 822    bf16 rows of 512 552 / 539, 484 / 468, 476 / 472    450,007 fp32 rows of 256, ratio 8 435 / 417
+//   490,000 fp32 rows of 400, ratio 2 and 4 990 / 967, 835 / 830    505 1,387 / 1,295, 1,194 / 1,172    512 1,204 / 1,180, 1,004 / 993
+//   bf16 rows of 512, ratio 2, 4, 16 552 / 539, 484 / 468, 476 / 472    450,007 fp32 rows of 256, ratio 8 435 / 417
 // below: 630,000 fp32 rows of 256, ratio 2 and 4 668 / 689, 585 / 589    770,000 of 64 283 / 349, 229 / 307    118 466 / 498, 423 / 426
 //   bf16 rows of 64 211 / 271, 182 / 199    256 390 / 410, 334 / 359    490,000 of 505 723 / 792, 610 / 609
 template <typename T>
 bool codec_rows_wide(const MaskRule& rule) {
     const uint32_t bytes = rule.width * uint32_t(sizeof(T));
+    if (sizeof(T) == 4 && rule.k * 16 <= rule.width) return false;      // fp32 rows of 512, ratio 16 794 / 834, 256 508 / 523
     return bytes >= 1536 || (bytes >= 1024 && (sizeof(T) == 2 || rule.k * 8 <= rule.width));
 }
 
