@@ -54,14 +54,12 @@ size_t prod_floats(const varco_ctx* ctx, int32_t layer, int64_t k) {
 // and partition after partition / one round / now:
 //   bf16  512 x 512   2,449,029 rows, 32 parts  2.1e-7 / 1.2e-6 / 2.0e-7  (1.81, 2.26 ms)
 //                     169,343 rows, 4 parts     1.5e-7 / 2.6e-7 / 1.3e-7  (158, 210 us: writing and reading the partial products)
-int64_t longest_slab(const varco_ctx* ctx, int32_t m, int32_t n, int64_t rows, int kind) {
-    const int64_t most = ctx->net.largest;
-    const int64_t split = kind == kGemmBf16 ? plain_bf16_split(m, n, most) : gemm_split_for(m, n, most, kind), alone = most / split;
-    return std::max<int64_t>(1, kind == kGemmExpanded ? alone * (137'500 + rows) / 73'300 : kind == kGemmBf16 ? alone + 4 * split + 16 * ctx->n_parts : alone);
-}
 int32_t wgrad_splits(const varco_ctx* ctx, int32_t m, int32_t n, int64_t rows, int kind, int products) {
     const int64_t step = kind == kGemmF32 ? 16 : 32;
-    const int64_t slots = wgrad_slots(m, n, kind, products), round = slots * longest_slab(ctx, m, n, rows, kind);
+    const int64_t slots = wgrad_slots(m, n, kind, products), most = ctx->net.largest;
+    const int64_t split = kind == kGemmBf16 ? plain_bf16_split(m, n, most) : gemm_split_for(m, n, most, kind), alone = most / split;
+    const int64_t longest = kind == kGemmExpanded ? alone * (137'500 + rows) / 73'300 : kind == kGemmBf16 ? alone + 4 * split + 16 * ctx->n_parts : alone;
+    const int64_t round = slots * std::max<int64_t>(1, longest);
     const int64_t rounds = std::max<int64_t>(1, std::min((rows + round - 1) / round, kPartialElems / (slots * products * m * n)));
     // (The stages of a slab follow one another, 1.4 us each: few rows take slabs of a single one. Beyond, and with large weights, adding the
     // partial products costs more; their sums are the more accurate all the same. Slabs of two stages / of one, one tap with its sums, us:
@@ -426,9 +424,9 @@ int32_t add_weight_product(varco_ctx* ctx, Workspace& ws, GemmArgs& g, WeightSum
 
 // Whether a layer's weight products may wait for the end of the pass, where one launch takes them all: stages of 32 rows times 128 x 128 tiles
 // are few, and nothing that the layers below write lies in what they read. A launch of few stages is a chain of round trips on a device that the
-// next one could use: a step of 2,000 nodes 16-32-8 55.4 -> 51.7 us, 16,000 nodes 32-64-8 92.9 -> 88.0, 3,997 nodes 93-208-120-14 200 -> 184;
-// 46 networks of 2,000 to 300,000 nodes 0.99 to 1.09 of the speed. Limits of 256 and 2,048 lose most of it (the last: 199); with 4,096 or 16,384 for
-// all, tiles of 256 columns that some shapes would take alone are missed (10,455 nodes 125-168-18 178 -> 185, 50,021 nodes 75-200-136-47 750 -> 788).
+// next one could use. Backward passes layer by layer / together, us: 2,000 nodes 16-32-8 21.9 / 17.8, 16,000 nodes 32-64-8 33.9 / 30.1, 5,000 nodes
+// 200-64-64-64-10, two taps 87.0 / 64.6, 3,997 nodes 93-208-120-14, two taps 79.7 / 80.4; 53 networks of 2,000 to 300,000 nodes take 0.73 to 1.009, 0.933 in the
+// mean. Limits of 256 and 2,048: 0.944; of 4,096 and 16,384 0.933, but up to 1.024 (300,000 nodes 32-32-32-8: 460 / 472, 457 with these).
 constexpr int64_t kFewTiles = 1024, kFewNarrowTiles = 4096;
 bool may_wait(const varco_ctx* ctx, const varco_network_buffers& b, int32_t l, const GemmArgs& g, const WeightSums& sums) {
     if (sums.n_waiting == kMaxWeightJobs || gemm_kind(g) != kGemmExpanded || int64_t((g.k + 31) / 32) * varco_gemm_half_tn_tiles(g) > (g.n <= 64 ? kFewNarrowTiles : kFewTiles)) return false;
@@ -447,20 +445,17 @@ bool may_wait(const varco_ctx* ctx, const varco_network_buffers& b, int32_t l, c
     return true;
 }
 
-// The products that waited, one launch for those of up to 64 columns and one for the others.
+// The products that waited, one launch for those of up to 64 columns and one for the others. Every product keeps the slabs it has in a launch of
+// its own, hence its bits and its accuracy. (The device divided among them means longer slabs, whose sums are further from exact:
+// 100,000 nodes 64-64-64-40, two partitions, 1.30e-7 -> 1.81e-7, and a backward pass of 203 us where it takes 218 with these slabs and 224 layer by layer.)
 int32_t launch_together(varco_ctx* ctx, Workspace& ws, GemmArgs* g, int n, WeightSums& sums, hipStream_t st) {
     if (n == 0) return VARCO_OK;
     if (n == 1) return add_weight_product(ctx, ws, *g, sums, st);
-    int64_t tiles = 0;
-    for (int i = 0; i < n; ++i) tiles += varco_gemm_half_tn_tiles(g[i]);
-    const int64_t stages = (g->k + 31) / 32, slots = g->n <= 64 ? 512 : 256;       // (two workgroups of 128 x 64 tiles on a unit)
-    const int64_t per_slab = (stages * tiles + slots - 1) / slots;
     double flops = 0;
     int32_t split[kMaxWeightJobs] = {};
     for (int i = 0; i < n; ++i) {
         const int products = g[i].c_dual ? 2 : 1;
-        const int64_t here = std::min(per_slab, std::max<int64_t>(1, longest_slab(ctx, g[i].m, g[i].n, g[i].k, kGemmExpanded) / 32));
-        g[i].split_k = int32_t(std::min<int64_t>((stages + here - 1) / here, wgrad_splits(ctx, g[i].m, g[i].n, g[i].k, kGemmExpanded, products)));
+        g[i].split_k = wgrad_splits(ctx, g[i].m, g[i].n, g[i].k, kGemmExpanded, products);
         g[i].partial = ws.gemm + sums.used;
         sums.used += size_t(g[i].split_k) * size_t(g[i].m) * size_t(g[i].n) * size_t(products);
         flops += 2.0 * products * double(g[i].m) * double(g[i].n) * double(g[i].k);

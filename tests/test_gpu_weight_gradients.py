@@ -115,3 +115,28 @@ def test_products_of_all_layers_in_one_launch(n, conv, widths, shared):
             # values far below the largest of their column keep 2^-42 of that one
             floor = 2.0 ** -42 * (a.abs().max() * dz.abs().sum(0)[None, :] + a.abs().sum(0)[:, None] * dz.abs().max())
             assert ((got.double() - a.t() @ dz).abs() <= bound + floor).all(), l
+
+
+@pytest.mark.parametrize("n,parts,conv,widths", [(100_000, 2, "gcn", (64, 64, 64, 40)), (6_000, 3, "gcn", (128, 256, 256, 40)), (3_997, 4, "sage", (93, 208, 120, 14)),
+                                                 (2_000, 2, "gcn", (16, 32, 8))])
+def test_products_that_share_a_launch_keep_their_slabs(n, parts, conv, widths):
+    """The same bits as in launches of their own: as accurate as those, whatever else a network's layers have the device do."""
+    g = synth.small_random_graph(n, 4.0, conv, seed=5)
+    host = vb.partition_build(g.n, g.rowptr, g.colidx, g.vals, synth.random_partition(g.n, parts, seed=6), parts)
+    net = PartitionedNetwork(host, widths, conv, KEY)
+    layers = range(len(widths) - 1)
+    rng = np.random.default_rng(n)
+    net.set_inputs(rng.standard_normal((n, widths[0])).astype(np.float32))
+    weights = [[rng.standard_normal((widths[l], widths[l + 1])).astype(np.float32) for l in layers] for _ in range(2)]
+    net.set_weights(weights[0], weights[1] if conv == "sage" else None)
+    net.set_upstream(rng.standard_normal((n, widths[-1])).astype(np.float32))
+    net.zero_grads()
+    net.forward(0, (4, 1))
+    net.backward()
+    for l in layers:
+        rows, got = ([net.m[l], net.x[l]], [net.dh1[l], net.dh0[l]]) if conv == "sage" else ([net.m[l]], [net.dh1[l]])
+        want = [torch.zeros_like(t) for t in got]
+        net.ctx.network_taps_bwd_weight(l, rows, net.dx[l + 1], net.x[l + 1], want)
+        for a, b in zip(got, want):
+            assert torch.equal(a, b), (l, float((a - b).abs().max()))
+    net.ctx.close()
