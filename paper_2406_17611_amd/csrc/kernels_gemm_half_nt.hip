@@ -15,6 +15,8 @@
 //   410,003 rows 256 -> 256 two taps 607 / 468, 512 -> 256 two taps 1,161 / 912     50,021 rows 136 -> 200 two taps 64 / 41
 //   1,000,000 rows 96 -> 64 two taps 274 / 236; at 64 steps and below the tiles are level or ahead (30,000 rows 17 -> 64 8.5 / 9.6, 2,449,029 rows
 //   47 -> 256 two taps 1,490 / 1,560)
+// The last rows and columns are stored four columns at a time like the others: element by element, the remainder alone took a launch of few blocks 2 to 4 us
+// (3,000 rows 72 -> 256 12.2 / 8.2, two taps 13.6 / 8.7, 6,000 rows 96 -> 256 11.6 / 8.6, 45,000 rows 256 -> 200 29.3 / 27.4).
 // (Measured and not kept: rows in registers and weights through LDS, 6,100 us for the first; 32x32x16 instructions, whose two sums wait for each other, 3,190;
 // both halves in step, 2,590.)
 #include <algorithm>
@@ -198,12 +200,13 @@ __global__ __launch_bounds__(kThreads, 2) void input_grad_kernel(InputGrad g) {
                     for (int v = 0; v < 4; ++v) o[v] = __builtin_ldexpf(acc[rt][ct][v] + low[rt][ct][v] * (1.f / kHalfLow), -(ea + e[v]));
                     const int col = ct * 16 + 4 * lg;
                     float* const dst = c + int64_t(row) * g.ldc + col;
-                    if (inside) {
+                    if (!inside && block * ROWS + row >= g.m) continue;
+                    if (inside || n0 + col + 4 <= g.n) {
                         if (g.accumulate) o += *reinterpret_cast<const any4*>(dst);
                         *reinterpret_cast<any4*>(dst) = o;
-                    } else if (block * ROWS + row < g.m) {
+                    } else {
 #pragma unroll
-                        for (int v = 0; v < 4; ++v)
+                        for (int v = 0; v < 3; ++v)
                             if (n0 + col + v < g.n) dst[v] = g.accumulate ? dst[v] + o[v] : o[v];
                     }
                 }
