@@ -216,6 +216,15 @@ __global__ __launch_bounds__(kThreads, 2) void input_grad_kernel(InputGrad g) {
     }
 }
 
+// How the columns of both products are dealt: wavefronts' shares, groups of eight of them, and workgroups of a group.
+struct Groups {
+    int32_t units, all_units, groups, stride;
+};
+Groups groups_of(const GemmArgs& ga, int stages) {
+    const int32_t cw = 16 * column_tiles(stages), units = (ga.n + cw - 1) / cw, all = units * (ga.c_dual ? 2 : 1), groups = (all + kWaves - 1) / kWaves;
+    return {units, all, groups, std::max(8, kUnits / groups / 8 * 8)};
+}
+
 template <class F>
 void with_flag(bool b, F&& f) {
     if (b)
@@ -226,7 +235,29 @@ void with_flag(bool b, F&& f) {
 
 }  // namespace
 
-bool varco_gemm_half_nt_usable(const GemmArgs& ga) { return !ga.a.transposed && ga.k > kShortest && ga.k <= 16 * kStage && varco_gemm_half_usable(ga); }
+bool varco_gemm_half_nt_usable(const GemmArgs& ga) {
+    if (ga.a.transposed || ga.k <= kShortest || ga.k > 16 * kStage || !varco_gemm_half_usable(ga)) return false;
+    // The tiles of kernels_gemm_half.hip are ahead where wavefronts here have no columns to multiply and the launch is a chain of blocks: `rounds` of them,
+    // while `tiles` workgroups, 512 of which are resident, do their share at once. Same accuracy. Time of the tiles / of the rows, us:
+    const int stages = (ga.k + kStage - 1) / kStage, taps = ga.c_dual ? 2 : 1, n_tile = ga.n <= 64 ? 64 : 128;
+    const Groups at = groups_of(ga, stages);
+    const int32_t rows = kRows * row_blocks(stages), rounds = ((ga.m + rows - 1) / rows + at.stride - 1) / at.stride;
+    const int64_t tiles = (int64_t(ga.m) + 127) / 128 * ((ga.n + n_tile - 1) / n_tile) * taps;
+    if (ga.n <= 64) {
+        // up to 128 steps: 24,000 rows 80 -> 16 6.6 / 9.5, 80 -> 64 7.0 / 9.6, two taps 80 -> 16 8.3 / 10.0, 56,000 rows 96 -> 16 11.0 / 14.9. More tiles than are
+        // resident: one tap 220,000 rows 96 -> 16 30.6 / 40.9, 65,536 rows 128 -> 48 16.3 / 19.0, but 110,000 rows 120 -> 32, whose rows begin inside
+        // lines, 29.3 / 24.4, two taps 96 -> 32 24.6 / 23.0, and beyond four rounds of tiles 600,000 rows 80 -> 32 101 / 88. Rows that are not whole
+        // 32 bytes cost the tiles more: 24,000 rows 100 -> 32 8.8 / 9.8, but 2,000 rows 8.4 / 7.2.
+        const bool wave_after_wave = taps == 1 && (ga.k % kStage == 0 || ga.k <= 80);
+        if (stages <= 4 && tiles <= (wave_after_wave ? 2048 : 512) && (ga.k % 8 == 0 || rounds > 1)) return false;
+        // more steps: 30,000 rows 224 -> 32 12.9 / 14.8, 192 -> 16 11.6 / 12.8; 20,000 rows (three rounds) 240 -> 32 14.0 / 12.9; 40,000 rows, more
+        // tiles than compute units, 22.0 / 18.1
+        if (taps == 1 && rounds > 3 && tiles <= 256) return false;
+    } else if (stages <= 4 && tiles <= 512 && rounds > 1 && ga.n % 128 == 0 && at.all_units > kWaves && at.all_units % kWaves) {
+        return false;                  // a last group with idle wavefronts, whole tiles: 10,000 rows 96 -> 384 9.8 / 13.0, 20,000 rows 13.3 / 17.0; one round: 8,000 rows 128 -> 384 12.0 / 10.2
+    }
+    return true;
+}
 
 hipError_t varco_launch_gemm_half_nt(const GemmArgs& ga, hipStream_t stream, const LaunchTag& tag) {
     auto f32 = [](const void* p) { return static_cast<const float*>(p); };
@@ -240,10 +271,9 @@ hipError_t varco_launch_gemm_half_nt(const GemmArgs& ga, hipStream_t stream, con
     g.accumulate = ga.accumulate ? 1 : 0;
     tag.begin(stream);
     auto go = [&](auto kt) {
-        constexpr int KT = decltype(kt)::value, ROWS = kRows * row_blocks(KT), CW = 16 * column_tiles(KT);
-        g.units = (ga.n + CW - 1) / CW, g.all_units = g.units * (ga.c_dual ? 2 : 1);
-        g.groups = (g.all_units + kWaves - 1) / kWaves;
-        g.stride = std::max(8, kUnits / g.groups / 8 * 8);
+        constexpr int KT = decltype(kt)::value, ROWS = kRows * row_blocks(KT);
+        const Groups at = groups_of(ga, KT);
+        g.units = at.units, g.all_units = at.all_units, g.groups = at.groups, g.stride = at.stride;
         const dim3 grid{unsigned((std::min(g.stride, (ga.m + ROWS - 1) / ROWS) + 7) / 8 * 8 * g.groups)};
         with_flag(ga.a.gate != nullptr, [&](auto gt) {
             hipLaunchKernelGGL((input_grad_kernel<KT, decltype(gt)::value>), grid, dim3(kThreads), 0, stream, g);

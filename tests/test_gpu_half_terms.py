@@ -79,6 +79,30 @@ def test_input_gradient_at_the_edges_of_blocks(n, accumulate, fi, fo):
     assert np.array_equal(got[n], old[n])                             # the row behind the last one
 
 
+@pytest.mark.parametrize("n,fi,fo", [(65_537, 16, 120), (65_500, 16, 120), (262_145, 33, 96), (261_990, 33, 80), (2_001, 32, 102), (24_001, 32, 102), (24_575, 48, 225),
+                                     (32_767, 48, 225), (32_769, 64, 225), (8_192, 384, 96), (8_193, 384, 96), (21_889, 384, 66), (21_762, 384, 128)])
+def test_input_gradient_on_both_sides_of_the_lines(n, fi, fo):
+    test_input_gradient_at_the_edges_of_blocks(n, False, fi, fo)      # few outputs, and a last group with idle wavefronts: tiles or blocks of rows
+
+
+@pytest.mark.parametrize("n,fi,fo", [(32_768, 16, 96), (32_769, 16, 96), (16_129, 33, 100), (33_025, 33, 100)])
+def test_two_input_gradients_on_both_sides_of_the_line(n, fi, fo):
+    rng = np.random.default_rng(n + fi + fo)
+    d, xo = (rng.standard_normal((n, fo)).astype(np.float32) for _ in range(2))
+    h = [synth.glorot(fi, fo, 3, t).astype(np.float32) for t in range(2)]
+    out = [torch.full((n + 1, fi), 7.0, device="cuda") for _ in range(2)]
+    ctx = _context(fi, fo, n, vb.CONV_SAGE)
+    assert ctx.link_partitions()
+    ctx.prepare()
+    ctx.network_taps_bwd_input(0, dev(d), dev(xo), [dev(a) for a in h], out)
+    torch.cuda.synchronize()
+    dz = d.astype(np.float64) * (xo > 0)
+    for a, got in zip(h, out):
+        got = got.cpu().numpy()
+        assert (np.abs(got[:n] - dz @ a.astype(np.float64).T) <= _bound(fo, dz, a.astype(np.float64).T)).all()
+        assert (got[n] == 7.0).all()
+
+
 @pytest.mark.parametrize("fi,fo", [(4, 4), (75, 47), (64, 65), (130, 136)])
 @pytest.mark.parametrize("growth", [0, 7])
 @pytest.mark.parametrize("n", [1, 31, 33, 2333])
