@@ -53,7 +53,6 @@ __global__ __launch_bounds__(kBlock) void compress_kernel(MaskRule rule, const i
 // per lane (2 for bf16 pairs); U: rows of a group (codec_rows_kernel: kRowsInFlight); ONE: a row is at most one access per lane.
 constexpr int kRowsInFlight = 4;         // of codec_rows_kernel
 constexpr int kCodecBlock = 64;          // of codec_wide_rows_kernel
-constexpr int64_t kL2Bytes = int64_t(8) * 4 << 20;      // eight L2 caches of 4 MB
 constexpr int64_t kCodecGrid = int64_t(1) << 24;      // a launch holds fewer than 2^32 threads
 template <typename S>
 __device__ __forceinline__ S add_words(S x, S z) {
@@ -454,7 +453,9 @@ bool codec_rows_wide(const MaskRule& rule) {
     return bytes >= 1536 || (bytes >= 1024 && (sizeof(T) == 2 || rule.k * 8 <= rule.width));
 }
 
-template <typename T, int MODE, int U = 4>
+// Rows of a group of codec_wide_rows_kernel: two where rows are read and written, else four. The adding decoder with two / four, us: 460 MB of rows, 512 fp32
+// values, ratio 2 224 / 251, 256 values, ratio 8 185 / 193, 768 bf16 values, ratio 4 202 / 210; 14 MB, 512 fp32 values, ratio 4 6.0 / 7.3, 256 values 6.1 / 6.5.
+template <typename T, int MODE, int U = MODE == 2 ? 2 : 4>
 hipError_t launch_codec_rows(const MaskRule& rule, const int32_t* gids, const int32_t* rows, int64_t n_rows, void* x, int64_t ldx, void* z,
                              hipStream_t stream) {
     using S = std::conditional_t<sizeof(T) == 2, uint16_t, uint32_t>;
@@ -514,12 +515,7 @@ hipError_t launch_decompress_t(const MaskRule& rule, const int32_t* gids, const 
         return accumulate ? launch_whole_rows<T, false, true>(rule, rows, n_rows, x, ldx, zw, stream)
                           : launch_whole_rows<T, false, false>(rule, rows, n_rows, x, ldx, zw, stream);
     if (!accumulate) return launch_codec_rows<T, 1>(rule, gids, rows, n_rows, x, ldx, zw, stream);
-    if (codec_rows_pay<T, 2>(rule, x, ldx)) {
-        // rows read and written, from memory: two at a time (256 fp32 values, 450,007 rows 183 us against 192); in the L2 caches: four (9,064 rows
-        // of 224 5.9 against 6.3)
-        if (n_rows * int64_t(rule.width) * int64_t(sizeof(T)) <= kL2Bytes) return launch_codec_rows<T, 2, 4>(rule, gids, rows, n_rows, x, ldx, zw, stream);
-        return launch_codec_rows<T, 2, 2>(rule, gids, rows, n_rows, x, ldx, zw, stream);
-    }
+    if (codec_rows_pay<T, 2>(rule, x, ldx)) return launch_codec_rows<T, 2>(rule, gids, rows, n_rows, x, ldx, zw, stream);
     const int gl = group_log2(rule.k);
     hipLaunchKernelGGL(decompress_add_kernel<T>, dim3(walking_grid(n_rows, gl)), dim3(kBlock), 0, stream, rule, gids, rows, n_rows,
                        static_cast<const T*>(z), static_cast<T*>(x), ldx, gl);

@@ -58,6 +58,34 @@ def test_both_sides_of_the_line_by_row_length(dtype, width, ratio, n_rows):
     test_aligned_rows(dtype, width, ratio, n_rows)      # the last two: wavefronts that walk take more than one group
 
 
+@pytest.mark.parametrize("dtype,width,ratio,n_rows", [("f32", 256, (8, 1), 33_001), ("f32", 384, (4, 1), 22_003), ("f32", 385, (2, 1), 22_001), ("f32", 505, (2, 1), 3),
+                                                      ("bf16", 512, (4, 1), 33_001), ("bf16", 772, (2, 1), 22_003), ("bf16", 768, (8, 1), 1025)])
+@pytest.mark.parametrize("listed", [True, False])
+def test_adding_decoder_of_many_rows(dtype, width, ratio, n_rows, listed):
+    """Groups of two rows, an odd number of them, on either side of what the caches hold; rows of a list or in order."""
+    bf16 = dtype == "bf16"
+    rng = np.random.default_rng(width)
+    stored = (lambda a: round_bf16(a).astype(np.float32)) if bf16 else (lambda a: np.asarray(a, dtype=np.float32))
+    tdt = torch.bfloat16 if bf16 else torch.float32
+    n_src = n_rows + 9
+    x = stored(rng.standard_normal((n_src, width), dtype=np.float32))
+    rows = np.sort(rng.permutation(n_src)[:n_rows]).astype(np.int32) if listed else np.arange(n_rows, dtype=np.int32)
+    gids = rng.integers(0, 2_449_029, size=n_rows).astype(np.int32)
+    ctx = vb.Context([8, width, 8], [1, 0], vb.CONV_GCN, 1, KEY, vb.BF16 if bf16 else vb.F32)
+    ctx.prepare()
+    ctx.begin_step(6)
+    ctx.set_ratio(1, *ratio)
+    k = ctx.keep(1)
+    z = stored(rng.standard_normal((n_rows, k), dtype=np.float32))
+    cols = np.asarray(omask.kept_columns(gids, width, k, KEY, 6, 1), dtype=np.int64).reshape(n_rows, k)
+    acc = dev(x, tdt)
+    ctx.decompress(1, dev(gids), dev(rows) if listed else None, n_rows, dev(z, tdt), acc, width, 1)
+    at = rows.astype(np.int64)[:, None]
+    x[at, cols] = stored(x[at, cols] + z)
+    assert np.array_equal(acc.float().cpu().numpy(), x)
+    ctx.close()
+
+
 @pytest.mark.parametrize("dtype,width,ratio", [("f32", 256, (8, 1)), ("f32", 2048, (4, 1)), ("f32", 75, (2, 1)), ("bf16", 512, (4, 1)),
                                                ("bf16", 2048, (3, 1)), ("bf16", 256, (1, 1))])
 def test_adding_decoder_leaves_other_elements_alone(dtype, width, ratio):
