@@ -440,17 +440,30 @@ hipError_t launch_whole_rows(const MaskRule& rule, const int32_t* rows, int64_t 
     return hipGetLastError();
 }
 
-// One group of rows per wavefront pays where a row is long enough to hide the wavefront's start and its chain of ids, rows, picks: from 1.5 KB on,
-// from 1 KB on with 16-bit elements or where at most an eighth is kept. Encoder, decoder and decoder with sum in turn, walking / one group each, us:
-//   490,000 fp32 rows of 400, ratio 2 and 4 990 / 967, 835 / 830    505 1,387 / 1,295, 1,194 / 1,172    512 1,204 / 1,180, 1,004 / 993
-//   bf16 rows of 512, ratio 2, 4, 16 552 / 539, 484 / 468, 476 / 472    450,007 fp32 rows of 256, ratio 8 435 / 417
-// below: 630,000 fp32 rows of 256, ratio 2 and 4 668 / 689, 585 / 589    770,000 of 64 283 / 349, 229 / 307    118 466 / 498, 423 / 426
-//   bf16 rows of 64 211 / 271, 182 / 199    256 390 / 410, 334 / 359    490,000 of 505 723 / 792, 610 / 609
-template <typename T>
-bool codec_rows_wide(const MaskRule& rule) {
-    const uint32_t bytes = rule.width * uint32_t(sizeof(T));
-    if (sizeof(T) == 4 && rule.k * 16 <= rule.width) return false;      // fp32 rows of 512, ratio 16 794 / 834, 256 508 / 523
-    return bytes >= 1536 || (bytes >= 1024 && (sizeof(T) == 2 || rule.k * 8 <= rule.width));
+// Which of the two forms, by what a call does and by the bytes of a row and of all rows. Measured at 34 widths of fp32 and 21 of bf16, ratios 2 to 32, 3 to 460 MB of
+// rows; walking / one group per wavefront, us (or the latter's gain or loss).
+// Adding decoder: one group for 1,024 bytes, an access of every lane, and from 1,536 on. 460 MB: 256 fp32 values, ratio 2 234 / 218, 8 197 / 185, 16 190 / 178, 1,024 values, ratio 4
+//   263 / 213, bf16 rows of 512, ratio 8 -7 %; 14 MB, 512 fp32 values, ratio 2 9.6 / 6.6; the worst, 180 MB, 256 values, ratio 12 55.6 / 59.0. Between, where a second access has few lanes, from
+//   memory or from the L2 caches (320 values, ratio 4 460 MB 207 / 203, 14 MB -13 %, but 230 MB 90.5 / 95.5, 90 MB, ratio 16 29.4 / 30.4). Below: 128 values, ratio 4 206 / 225,
+//   192 values, 90 MB 33.6 / 34.9, bf16 rows of 256, ratio 8 +17 %.
+// Encoder: from 1,536 bytes on (460 MB, 384 fp32 values, ratio 4 110 / 107, 1,536 values 183 / 140; 230 MB, 384 values, ratio 8 +4 %, the worst), from 1,024 bytes on where the rows
+//   come from memory: 256 values, ratio 8 460 MB 103 / 97, 340 MB 72 / 69, 280 MB 48.8 / 49.2, 180 MB 30.3 / 31.3, 90 MB 16.5 / 17.0; bf16 rows of 640 102 / 98, 180 MB +4 %.
+// Decoder, rows written and not read: into the cache, one group (14 MB, 256 values, ratio 4 6.4 / 6.1, 1,024 values, ratio 2 -25 %; 90 MB, 512 values, ratio 8 -5 %, 256 values
+//   17.5 / 17.3, 230 MB 256 values, ratio 2 +9 %). To memory, walking where little is kept, a fill (460 MB, 384 values, ratio 32 93 / 103, 16 110 / 108, 512 values 91 / 100, 104 / 109), unless
+//   rows are long (896 values, ratio 16 149 / 131, 32 level; 800 values +3, +7 %), and where a short row takes many picks (256 values, ratio 2 147 / 162, 4 121 / 126, 320 values 161 / 177,
+//   146 / 147); between, one group (256 values, ratio 6 134 / 135, 8 112 / 109, 12 114 / 115, 320 values 126 / 122, 128 / 118, 115 / 107, bf16 rows of 640, ratio 8 129 / 119; 352 values, ratio 8 129 / 133).
+// Rows that are no whole 16-byte pieces, 64 values to an access: 301 fp32 values, ratio 2, 460 MB +5, +5, +3 %, 385 values +3, -4, -6 %, 505 values 147 / 146, 242 / 228, 309 / 255; bf16 rows of
+//   516, 180 MB, ratio 2 62 / 65, 83 / 80, 115 / 131, ratio 8 43 / 43, 51 / 46; of 772 level, -4 %, level.
+constexpr int64_t kCachedBytes = int64_t(320) << 20;      // rows in all of which the last-level cache (256 MB) serves a part
+template <typename T, int MODE>
+bool codec_rows_wide(const MaskRule& rule, int64_t n_rows, bool vec) {
+    const int64_t bytes = int64_t(rule.width) * int64_t(sizeof(T)), all = n_rows * bytes;
+    if (bytes < 1024) return false;
+    const bool longer = bytes >= 1536, few = rule.k * 12 < rule.width, many = rule.k * 5 > rule.width;
+    if (MODE == 0) return longer || (vec && all > kCachedBytes);
+    if (MODE == 2) return longer || (vec && (bytes == 1024 || all > kCachedBytes || 8 * all <= kCachedBytes));
+    if (!vec) return rule.width >= 384;
+    return longer ? !few || all <= kCachedBytes || bytes >= 3584 : (!few && !many) || 2 * all <= kCachedBytes;
 }
 
 // Rows of a group of codec_wide_rows_kernel: two where rows are read and written, else four. The adding decoder with two / four, us: 460 MB of rows, 512 fp32
@@ -465,7 +478,7 @@ hipError_t launch_codec_rows(const MaskRule& rule, const int32_t* gids, const in
     const bool one = int(rule.width) <= 64 * (vec ? V16 : 1);
     const int lpe = group_log2(pair ? rule.k / 2 : rule.k);
     constexpr int W = kBlock / 64;
-    const bool wide = codec_rows_wide<T>(rule);
+    const bool wide = codec_rows_wide<T, MODE>(rule, n_rows, vec);
     const size_t row = size_t((rule.width + 7) & ~7u) * sizeof(S);
     const int64_t blocks = wide ? std::min((n_rows + U - 1) / U, kCodecGrid) : std::min<int64_t>((n_rows + W * kRowsInFlight - 1) / (W * kRowsInFlight), 256 * 32);
     auto go = [&](auto vc, auto pc, auto oc) {

@@ -86,6 +86,39 @@ def test_adding_decoder_of_many_rows(dtype, width, ratio, n_rows, listed):
     ctx.close()
 
 
+@pytest.mark.parametrize("dtype,width,ratio,n_rows", [("f32", 256, (8, 1), 327_679), ("f32", 256, (8, 1), 327_683), ("f32", 320, (2, 1), 262_145), ("f32", 512, (16, 1), 163_841),
+                                                      ("f32", 896, (32, 1), 93_623), ("bf16", 512, (4, 1), 163_839), ("bf16", 512, (4, 1), 163_843), ("bf16", 516, (2, 1), 325_145)])
+def test_on_both_sides_of_the_line_by_all_rows(dtype, width, ratio, n_rows):
+    """Rows that the last-level cache holds, or half of it, and more: all three calls, against index operations on the same device."""
+    bf16 = dtype == "bf16"
+    tdt, idt = (torch.bfloat16, torch.int16) if bf16 else (torch.float32, torch.int32)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(width)
+    n_src = n_rows + 5
+    x = torch.randn(n_src, width, generator=gen, device="cuda").to(tdt)
+    rows = torch.randperm(n_src, generator=gen, device="cuda")[:n_rows].sort().values
+    gids = (rows * 3 + 1).to(torch.int32)
+    ctx = vb.Context([8, width, 8], [1, 0], vb.CONV_GCN, 1, KEY, vb.BF16 if bf16 else vb.F32)
+    ctx.prepare()
+    ctx.begin_step(6)
+    ctx.set_ratio(1, *ratio)
+    k = ctx.keep(1)
+    cols = dev(np.asarray(omask.kept_columns(gids.cpu().numpy(), width, k, KEY, 6, 1), dtype=np.int64).reshape(n_rows, k))
+    z = torch.zeros((n_rows + 1, k), dtype=tdt, device="cuda")
+    ctx.compress(1, gids, rows.to(torch.int32), n_rows, x, width, z)
+    want = x[rows].gather(1, cols)
+    assert torch.equal(z[:n_rows].view(idt), want.view(idt)) and not z[n_rows].any()
+    out = torch.full((n_src, width), 7.0, dtype=tdt, device="cuda")
+    ctx.decompress(1, gids, None, n_rows, z, out, width, 0)
+    assert torch.equal(out[:n_rows].view(idt), torch.zeros_like(out[:n_rows]).scatter_(1, cols, want).view(idt)) and bool((out[n_rows:] == 7.0).all())
+    add = torch.randn(n_rows, k, generator=gen, device="cuda").to(tdt)
+    old = x.clone()
+    ctx.decompress(1, gids, rows.to(torch.int32), n_rows, add, x, width, 1)
+    old[rows] = old[rows].scatter(1, cols, (want.float() + add.float()).to(tdt))
+    assert torch.equal(x.view(idt), old.view(idt))
+    ctx.close()
+
+
 @pytest.mark.parametrize("dtype,width,ratio", [("f32", 256, (8, 1)), ("f32", 2048, (4, 1)), ("f32", 75, (2, 1)), ("bf16", 512, (4, 1)),
                                                ("bf16", 2048, (3, 1)), ("bf16", 256, (1, 1))])
 def test_adding_decoder_leaves_other_elements_alone(dtype, width, ratio):
