@@ -417,9 +417,11 @@ int32_t varco_reset_stats(varco_ctx* ctx);
  * memory-bound classes, floating-point operations (2 m n k) for the matrix-core classes.
  */
 enum {
-    VARCO_K_COMPRESS = 0,       /* encoder: boundary rows -> k kept elements */
+    VARCO_K_COMPRESS = 0,       /* encoder: boundary rows -> k kept elements; linked partitions of few entries: see AGG_FWD */
     VARCO_K_DECOMPRESS = 1,     /* decoder / owner-side accumulation of returned errors */
-    VARCO_K_AGG_FWD = 2,        /* M = S_q [X_loc ; compressed halo] */
+    VARCO_K_AGG_FWD = 2,        /* M = S_q [X_loc ; compressed halo]. varco_network_forward over few entries: one launch that also writes the
+                                 * compressed rows and, in the first layer, the copies of the weights. It counts here, bytes of all three
+                                 * included (kept elements come from the owners' rows), and the layer has no COMPRESS launch */
     VARCO_K_GEMM_FWD = 3,       /* act(M H1 + X H0) */
     VARCO_K_GEMM_WGRAD = 4,     /* dH += M^T dZ, X^T dZ (split reduction, partial products) */
     VARCO_K_GEMM_DGRAD = 5,     /* dM = dZ H1^T, dX += dZ H0^T */

@@ -276,9 +276,18 @@ int32_t aggregate_fwd(varco_ctx* ctx, Workspace& ws, int32_t layer, const MaskRu
     const NetState& net = ctx->net;
     const double es = ctx->elem_bytes();
     const int32_t fi = ctx->widths[layer];
-    const double bytes = double(net.nnz) * 8.0 + (double(net.rows) + 1.0) * 4.0 + (2.0 * double(net.rows) * fi + double(net.halo_rows) * rule.k) * es;
-    const double stream = double(net.nnz) * 8.0 + (double(net.rows) + 1.0) * 4.0 +
-                          (double(net.rows) * fi + double(net.nnz_local) * fi + double(net.nnz_cross) * rule.k) * es;
+    // one launch: kept elements come from the owners' rows, the messages and the copies are written (and the copies' weights read)
+    double extra = 0;
+    if (with_z) {
+        extra = double(net.boundary) * rule.k * es;
+        for (int i = 0; i < with_z->n; ++i) {
+            const PrepJob& j = with_z->job[i];
+            extra += 4.0 * j.rows * j.cols + double(j.rows_padded) * (2.0 * j.pitch * (j.terms == kHalfTerms ? 2 : j.terms) + (j.terms == kHalfTerms ? 4.0 : 0.0));
+        }
+    }
+    const double entries = double(net.nnz) * 8.0 + (double(net.rows) + 1.0) * 4.0;
+    const double bytes = entries + (2.0 * double(net.rows) * fi + (with_z ? 0.0 : double(net.halo_rows) * rule.k)) * es + extra;
+    const double stream = entries + (double(net.rows) * fi + double(net.nnz_local) * fi + (double(net.nnz_cross) + (with_z ? double(net.boundary) : 0.0)) * rule.k) * es + extra;
     const LaunchTag tag = ctx->tag(VARCO_K_AGG_FWD, bytes, 0, stream);
     if (rule.k == rule.width)   // lossless: a message equals the owner's row, which is nearer (the same rows serve the local entries)
         VARCO_HIP(ctx, varco_launch_spmm(ctx->dtype, net.fwd, nullptr, net.arow, net.vals, x, nullptr, 0, full_rule(fi), m, 0, ws.spmm, st, tag));

@@ -44,11 +44,15 @@ def _short(name: str) -> str:
     return name.replace("(anonymous namespace)::", "").replace("void ", "").split("(")[0]
 
 
+# Kernel name prefixes of bench.py's memory-bound kernel classes.
+KERNEL_CLASSES = (("spmm_kernel", "agg_fwd"), ("spmm_owner_kernel", "agg_fwd"), ("node_sum_kernel", "agg_bwd_local"),
+                  ("narrow_backward_kernel", "agg_bwd_local"), ("halo_products_kernel", "agg_bwd_halo"), ("codec_rows_kernel", "compress"),
+                  ("codec_wide_rows_kernel", "compress"), ("whole_rows_kernel", "compress"), ("compress_kernel", "compress"))
+
+
 def _kernel_class(n: str):
     """bench.py's kernel class of a kernel name (None for kernels outside the memory-bound classes)."""
-    for prefix, c in (("spmm_kernel", "agg_fwd"), ("node_sum_kernel", "agg_bwd_local"),
-                      ("narrow_backward_kernel", "agg_bwd_local"), ("halo_products_kernel", "agg_bwd_halo"),
-                      ("codec_rows_kernel", "compress"), ("codec_wide_rows_kernel", "compress"), ("whole_rows_kernel", "compress"), ("compress_kernel", "compress")):
+    for prefix, c in KERNEL_CLASSES:
         if n.startswith(prefix):
             return c
     return None
@@ -136,7 +140,7 @@ def summarise(workload: str, out_dir: str) -> dict:
                 per_class[c][1] += sum(write[n]) * 1024 / sw if n in write else 0.0
                 if not (n.startswith(("node_sum_kernel", "narrow_backward_kernel")) and n.endswith("true>")):      # second kernel of the same call
                     per_class[c][2] += len(fetch[n])
-        f.write("\n(spmm_kernel: forward aggregation, all layers; node_sum_kernel: backward aggregation by node, in a second "
+        f.write("\n(spmm_kernel: forward aggregation, all layers (spmm_owner_kernel: with the messages and weight copies); node_sum_kernel: backward aggregation by node, in a second "
                 "launch (<..., true>) the hub nodes whose pieces the first one summed; narrow_backward_kernel: the same for the class layer, at the "
                 "width of its outputs. Launches of one class are averaged together.)\n")
 

@@ -47,6 +47,17 @@ def test_kernel_sources_hash_follows_the_sources(tmp_path, monkeypatch):
     assert ps.kernel_sources_hash() != h
 
 
+def test_kernel_classes_of_the_traffic_summary_name_the_kernels_there_are():
+    import re
+    from paper_2406_17611_amd import profile_summary as ps
+    csrc = os.path.join(ROOT, "paper_2406_17611_amd", "csrc")
+    text = "".join(open(os.path.join(csrc, f)).read() for f in os.listdir(csrc) if f.endswith(".hip"))
+    kernels = set(re.findall(r"__global__ [^;{]*?void (\w+)\(", text))
+    for prefix, _ in ps.KERNEL_CLASSES:
+        assert prefix in kernels, prefix
+    assert ps._kernel_class("spmm_owner_kernel<float, 0, 4>") == "agg_fwd" and ps._kernel_class("spmm_fixup4_kernel<float>") is None
+
+
 def test_source_row_reuse_counts_match_a_direct_count():
     """The reuse count's totals against a plain loop over one partition's rows of the smallest workload."""
     import numpy as np

@@ -125,3 +125,26 @@ def test_weight_copies_made_with_the_first_sums(conv, widths, dtype):
     g = synth.small_random_graph(700, 7.0, conv, seed=95)
     _compare_network(g, synth.random_partition(g.n, 3, seed=96), 3, conv, widths, [(4, 1), (3, 1), (1, 1)], steps=[0, 1, 2],
                      tol=BF16_TOL if dtype == "bf16" else 1e-4, dtype=dtype)
+
+
+@pytest.mark.parametrize("widths,together", [((16, 32, 8), True), ((75, 130, 9), False)])
+def test_bytes_of_a_launch_that_writes_the_messages_too(widths, together):
+    """What the per-kernel profile counts: one launch per layer with the bytes of the sums and of the messages, or two launches."""
+    g = synth.small_random_graph(700, 7.0, "gcn", seed=97)
+    host, _ = both_partitions(g, synth.random_partition(g.n, 3, seed=98), 3)
+    net = PartitionedNetwork(host, widths, "gcn", KEY)
+    net.set_inputs(synth.features(g.n, widths[0], synth.SEED_FEAT))
+    net.set_weights([synth.glorot(widths[l], widths[l + 1], synth.SEED_WEIGHT, 2 * l) for l in range(2)])
+    net.forward(0, (4, 1))
+    net.ctx.profile_enable(True)
+    net.ctx.profile_read()
+    net.ctx.network_forward(net._network_buffers())            # in the same step: the copies of the weights are there
+    p = net.ctx.profile_read()
+    net.forward(1)                                             # the first layer's launch makes them
+    first = net.ctx.profile_read()
+    nnz, n_halo = sum(h.nnz for h in host), sum(h.n_halo for h in host)
+    moved = sum(8 * nnz + 4 * (g.n + 1) + 4 * (2 * g.n * widths[l] + (net.b_total if together else n_halo) * net.ctx.keep(l)) for l in range(2))
+    assert p["agg_fwd"]["launches"] == 2 and p["compress"]["launches"] == (0 if together else 2)
+    assert abs(p["agg_fwd"]["bytes"] - moved) <= 1e-9 * moved
+    weights = 4 * sum(widths[l] * widths[l + 1] for l in range(2))
+    assert first["agg_fwd"]["bytes"] >= moved + weights if together else first["agg_fwd"]["bytes"] == p["agg_fwd"]["bytes"]
