@@ -335,13 +335,19 @@ hipError_t varco_launch_gemm_half_tn_jobs(const GemmArgs* ga, int32_t n, hipStre
     return hipGetLastError();
 }
 
-// Tiles of 256 columns of A unless tiles of 128 cover them with fewer; 64 columns of B where that is all there are.
+// Tiles of 256 columns of A unless tiles of 128 cover them with fewer; 64 columns of B where that is all there are. (The tile changes no sum.)
+// Tiles of 128 x 64 where slabs are up to three stages long and all of them start at once, two to a compute unit (in place of tiles of 128 columns: one): such a launch waits
+// for its first loads, and a smaller tile has fewer of them and less to write. Other tiles / these, with the sums of the slabs, us: 2,000 rows 200 x 100 15.6 / 11.3,
+// 256 x 16 11.5 / 9.4, 128 x 100 11.8 / 10.3, 256 x 256 (504 of them) 19.9 / 18.5, both taps 100 x 100 16.3 / 11.8, 10,007 rows 200 x 100 21.6 / 17.9, 100 x 100 15.2 / 13.3.
+// More, or longer: 2,000 rows 512 x 200 +3 %, 16 x 512 +4 %, 10,007 rows 200 x 200 +9 %, 100 x 256 +3 %, 500,000 rows 200 x 64 134 / 151.
 hipError_t varco_launch_gemm_half_tn(const GemmArgs& ga, hipStream_t stream, const LaunchTag& tag, int32_t* split_used) {
     const int32_t units = (ga.c_dual ? 2 : 1) * ((ga.m + 63) / 64);
-    const bool wide = (units + 3) / 4 * 4 <= (units + 1) / 2 * 2;
-    const int un = ga.n <= 64 ? 1 : 2;
+    const bool fewer_wide = (units + 3) / 4 * 4 <= (units + 1) / 2 * 2;
     WeightGrad g{};
-    const int64_t blocks = make_job(ga, wide ? 4 : 2, un, ga.split_k, g);
+    int64_t blocks = make_job(ga, 2, 1, ga.split_k, g);
+    const bool few = g.stages_per_split <= 3 && int64_t(g.split) * g.inner <= (fewer_wide ? 512 : 256), wide = fewer_wide && !few;
+    const int un = few || ga.n <= 64 ? 1 : 2;
+    if (wide || un == 2) blocks = make_job(ga, wide ? 4 : 2, un, ga.split_k, g);
     if (g.split > 1 && !ga.partial) return hipErrorInvalidValue;
     if (blocks > 0x7FFFFFFF / kThreads) return hipErrorInvalidValue;
     *split_used = g.split;

@@ -140,3 +140,24 @@ def test_products_that_share_a_launch_keep_their_slabs(n, parts, conv, widths):
         for a, b in zip(got, want):
             assert torch.equal(a, b), (l, float((a - b).abs().max()))
     net.ctx.close()
+
+
+@pytest.mark.parametrize("fi,fo", [(16, 200), (100, 130), (129, 65), (200, 136), (300, 60), (257, 257)])
+@pytest.mark.parametrize("n", [31, 1_999, 5_003, 20_011])
+def test_tiles_of_any_size(n, fi, fo):
+    """Few slabs, which take small tiles, to many: one tap and two, masked, columns and rows that no tile divides."""
+    ctx, held = _linked_context(n, 3, fi, fo, vb.F32, 3)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(n + fi)
+    randn = lambda *s: torch.randn(*s, generator=gen, device="cuda")     # noqa: E731
+    y, d, x = [randn(n, fi) for _ in range(2)], randn(n, fo), randn(n, fo)
+    dz = torch.where(x > 0, d, torch.zeros_like(d)).double()
+    for taps in (1, 2):
+        dh = [torch.full((fi, fo), 3.0, device="cuda") for _ in range(taps)]
+        ctx.network_taps_bwd_weight(0, y[:taps], d, x, dh)
+        for yt, got in zip(y, dh):
+            # two scaled terms within 2^-23 of either operand, a rounding of 2^-24 per 16 rows of a slab and per slab, four times their root for the tail
+            bound = (2.0 ** -21 + 4 * 2.0 ** -23 * (n / 16 + 1) ** 0.5) * (yt.double().abs().t() @ dz.abs()) + 2.0 ** -23 * 3.0
+            assert ((got.double() - 3.0 - yt.double().t() @ dz).abs() <= bound + 2.0 ** -42 * n * float(yt.abs().max() * d.abs().max())).all()
+    ctx.close()
+    del held
