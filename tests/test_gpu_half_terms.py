@@ -28,7 +28,7 @@ def _bound(length, a, b):
     return (2.0 ** -21 + 4 * 2.0 ** -23 * np.sqrt(np.ceil(length / 16) + 1)) * (np.abs(a) @ np.abs(b))
 
 
-@pytest.mark.parametrize("fo", [65, 66, 75, 96, 97, 128, 260, 512])
+@pytest.mark.parametrize("fo", [65, 66, 75, 96, 97, 128, 200, 260, 321, 352, 384, 385, 417, 448, 449, 512])
 @pytest.mark.parametrize("growth", [0, 5, 7, 12])
 def test_input_gradient_rows_of_any_magnitude(fo, growth):
     n, fi = 300, 136
@@ -61,10 +61,12 @@ def test_short_input_gradient_rows_of_any_magnitude(fo, growth):
     test_input_gradient_rows_of_any_magnitude(fo, growth)      # one stage or two, with a remainder or none
 
 
-@pytest.mark.parametrize("fi,fo", [(1, 65), (31, 127), (33, 128), (64, 129), (129, 159), (255, 192), (257, 225), (300, 256), (15, 257), (65, 289), (128, 320), (250, 511), (48, 512), (40, 516)])
+@pytest.mark.parametrize("fi,fo", [(1, 65), (31, 127), (33, 128), (64, 129), (129, 159), (255, 192), (257, 225), (300, 256), (15, 257), (65, 289), (128, 320), (250, 511), (48, 512), (40, 516),
+                                   (100, 193), (130, 200), (70, 321), (96, 352), (65, 353), (129, 384), (77, 385), (128, 416), (100, 417), (250, 448), (66, 449)])
 @pytest.mark.parametrize("n,accumulate", [(1, False), (33, True), (63, False), (64, True), (8225, False)])
 def test_input_gradient_at_the_edges_of_blocks(n, accumulate, fi, fo):
-    """Rows in blocks of 32 or 64 of workgroups that walk over them, columns in units of 16 or 32 of wavefronts, every number of stages."""
+    """Rows in blocks of 32 or 64 of workgroups that walk over them, columns in units of 16 or 32 of wavefronts, every number of stages from three to
+    sixteen (those that an odd number leaves empty among them), and what is left to the tiles."""
     rng = np.random.default_rng(n + fi + fo)
     d, xo = (rng.standard_normal((n, fo)).astype(np.float32) for _ in range(2))
     h = synth.glorot(fi, fo, 3, 1).astype(np.float32)

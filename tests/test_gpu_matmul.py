@@ -258,8 +258,8 @@ def test_non_finite_operand_stays_in_its_row(terms):
 @pytest.mark.parametrize("taps", [1, 2])
 @pytest.mark.parametrize("n", [2, 31, 33, 3001, 32801])
 def test_transform_at_the_edges_of_blocks(n, taps, fi, fo):
-    """Rows in blocks of 32 of workgroups that walk over them, columns in units of 32 of wavefronts, every number of stages, rows
-    that start at any word of a larger tensor; one tap added to what is there, two written."""
+    """One tap: rows in blocks of 32 of workgroups that walk over them, columns in units of 32 of wavefronts, every number of stages, added to
+    what is there. Two: the chained tiles of a K-tap layer. Rows that start at any word of a larger tensor."""
     from test_gpu_weight_gradients import _linked_context
     rng = np.random.default_rng(n + fi + fo)
     y = [rng.standard_normal((n, fi)).astype(np.float32) for _ in range(taps)]
@@ -287,6 +287,34 @@ def test_transform_at_the_edges_of_blocks(n, taps, fi, fo):
     assert np.array_equal(got[n], old[n])                             # the row behind the last one
     ctx.close()
     del parts
+
+
+@pytest.mark.parametrize("fi,fo", [(68, 65), (80, 132), (96, 72), (100, 256), (104, 257), (124, 136), (128, 130)])
+@pytest.mark.parametrize("n", [2, 33, 3001, 32801])
+def test_layer_of_two_taps_at_the_edges_of_blocks(n, fi, fo):
+    """A SAGE layer's transform, both taps' weights in the wavefronts: blocks of 32 rows, a tap at a time, units of 32 columns, three and four
+    stages to a tap, the rows of either tap from any word of a larger tensor on."""
+    graph = synth.small_random_graph(n, 2.0, "sage", seed=n)
+    host = vb.partition_build(graph.n, graph.rowptr, graph.colidx, graph.vals, synth.random_partition(graph.n, 2, seed=5), 2)
+    rng = np.random.default_rng(n + fi + fo)
+    net = PartitionedNetwork(host, (fi, fo, 4), "sage", 17, need_backward=False)
+    moved = [torch.zeros(n * fi + 1, device="cuda") for _ in range(2)]
+    net.x[0], net.m[0] = (t[1:].view(n, fi) for t in moved)
+    whole = torch.full((n + 1, fo), 7.0, device="cuda")
+    net.x[1] = whole[:n]
+    h = [[synth.glorot(a, b, 3, 1 + t).astype(np.float32) for a, b in ((fi, fo), (fo, 4))] for t in range(2)]
+    net.set_weights(*h)
+    net.set_inputs(rng.standard_normal((n, fi)).astype(np.float32))
+    net.forward(1, (4, 1))
+    torch.cuda.synchronize()
+    taps = [(net.m[0].cpu().numpy().astype(np.float64), h[0][0]), (net.x[0].cpu().numpy().astype(np.float64), h[1][0])]
+    want = sum(a @ b.astype(np.float64) for a, b in taps)
+    size = sum(np.abs(a) @ np.abs(b) for a, b in taps)
+    bound = (2.0 ** -24 + 4 * 2.0 ** -24 * np.sqrt(6 * 2 * np.ceil(fi / 16))) * size       # as above
+    got = whole.cpu().numpy()
+    assert (np.abs(got[:n] - np.maximum(want, 0.0)) <= bound).all()
+    assert (got[n] == 7.0).all()                                      # the row behind the last one
+    net.ctx.close()
 
 
 @pytest.mark.parametrize("fi,fo", [(68, 72), (80, 132), (96, 130), (100, 256), (128, 136), (144, 96), (180, 257), (224, 65), (256, 512)])
