@@ -217,8 +217,9 @@ hipError_t grow_products(Workspace& ws, size_t want, size_t most) {
 // Number of slabs the node dimension of a weight-gradient product is cut into: the workgroups of one launch
 // should fill the chip exactly once (three 256-thread workgroups of the GEMM kernel are resident per
 // compute unit, 256 compute units), so that no partly filled second round is left over.
-// (The bf16 kernel chooses its tile by the shape, the kernel on expanded fp32 operands has 128-row tiles and two resident
-// workgroups per unit; both take 32 reduction steps per tile.)
+// (The bf16 kernel chooses its tile by the shape. Expanded fp32 operands: the slabs that tiles of 128 x 128 with two workgroups per unit
+// would fill it with, which tiles of 256 x 128 with one fill it with as well; the kernel's other tiles keep that number, since the error of a
+// sum follows from its slab. Both take 32 reduction steps per tile.)
 int64_t wgrad_slots(int32_t m, int32_t n, int kind, int products) {
     int32_t bm = kind == kGemmF32 && n <= 64 ? 256 : 128, bn = n <= 64 ? 64 : 128, per_cu = kind == kGemmF32 ? 3 : 2;
     if (kind == kGemmBf16) varco_gemm_tn_bf16_tile(m, n, &bm, &bn, &per_cu);
