@@ -8,7 +8,7 @@
 // taps of a layer of up to 64 inputs fill a tile of 128.
 //
 // Bound by what the L2s deliver to the compute units: the same pattern of loads with nothing else in the kernel takes 2.1 of 3.0 ms (256 x 256,
-// both taps, 2,449,029 nodes; 20 GB out of the L2s, 10 GB into them). Hence the tile: 256 x 128 by 512 threads, one workgroup per compute unit,
+// both taps, 2,449,029 nodes; 20 GB out of the L2s, 12 GB into them; matrix units 31 % busy, vector ALUs 31 %). Hence the tile: 256 x 128 by 512 threads, one workgroup per compute unit,
 // loads 8 KB per node where four 128 x 128 tiles of two workgroups per unit load 12, and splits a value once per 128 or 256 columns of the
 // other operand. 128 columns of A where 256 would be padding. One barrier per stage of 32 nodes: the next stage is split into a second LDS buffer
 // while other wavefronts still multiply. The maximum of a column is only looked at when a value leaves the range that its scale leaves (one

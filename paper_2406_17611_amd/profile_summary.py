@@ -21,6 +21,7 @@ import csv
 import hashlib
 import json
 import os
+import re
 import sys
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -41,7 +42,8 @@ def kernel_sources_hash() -> str:
 
 
 def _short(name: str) -> str:
-    return name.replace("(anonymous namespace)::", "").replace("void ", "").split("(")[0]
+    name = name.replace("(anonymous namespace)::", "").replace("void ", "")
+    return re.sub(r"\((\w+)\)(?=\d)", r"\1 ", name).split("(")[0]       # (an enumerator among the template's arguments is "(Type)value")
 
 
 # Kernel name prefixes of bench.py's memory-bound kernel classes.

@@ -55,6 +55,8 @@ def test_kernel_classes_of_the_traffic_summary_name_the_kernels_there_are():
     kernels = set(re.findall(r"__global__ [^;{]*?void (\w+)\(", text))
     for prefix, _ in ps.KERNEL_CLASSES:
         assert prefix in kernels, prefix
+    name = "void (anonymous namespace)::weight_grad_kernel<4, 2, ((anonymous namespace)::Gate)1>((anonymous namespace)::WeightGrad)"
+    assert ps._short(name) == "weight_grad_kernel<4, 2, Gate 1>" and ps._short("void (anonymous namespace)::spmm_kernel<float, 4>(int)") == "spmm_kernel<float, 4>"
     assert ps._kernel_class("spmm_owner_kernel<float, 0, 4>") == "agg_fwd" and ps._kernel_class("spmm_fixup4_kernel<float>") is None
 
 
