@@ -690,6 +690,7 @@ hipError_t varco_launch_gemm(const GemmArgs& ga, hipStream_t stream, const Launc
     }
     if (varco_gemm_split_rows_usable(ga)) return varco_launch_gemm_split_rows(ga, stream, tag);
     if (varco_gemm_split_usable(ga)) return varco_launch_gemm_split(ga, stream, tag);
+    if (varco_gemm_rows_usable(ga)) return varco_launch_gemm_rows(ga, stream, tag);
     // A is M x K: k-contiguous as stored unless transposed. B is K x N: k-contiguous only when transposed.
     const bool a_kc = !ga.a.transposed, b_kc = ga.b.transposed;
     const bool a_gate = ga.a.gate != nullptr, b_gate = ga.b.gate != nullptr;

@@ -357,6 +357,9 @@ bool varco_gemm_split_taps_usable(const GemmArgs* g, int n);
 hipError_t varco_launch_gemm_split_taps(const GemmArgs* g, int n, hipStream_t stream, const LaunchTag& tag);
 bool varco_gemm_split_rows_usable(const GemmArgs& g);   // of 65 to 256 reduction steps, where weights in registers are faster
 hipError_t varco_launch_gemm_split_rows(const GemmArgs& g, hipStream_t stream, const LaunchTag& tag);
+// The transform in fp32 instructions, up to 256 steps a tap, where the forms above do not take it (kernels_gemm_rows.hip): the sums of the general tiles.
+bool varco_gemm_rows_usable(const GemmArgs& g);
+hipError_t varco_launch_gemm_rows(const GemmArgs& g, hipStream_t stream, const LaunchTag& tag);
 // fp32 operands as two scaled fp16 terms on the fp16 matrix cores: input gradients (kernels_gemm_half.hip, kernels_gemm_half_nt.hip) and weight
 // gradients (A transposed, kernels_gemm_half_tn.hip); same contract as the bf16 path above.
 bool varco_gemm_half_usable(const GemmArgs& g);
