@@ -96,6 +96,29 @@ struct RowSlab {
     }
 };
 
+// A stage of the weights in TERMS terms: the copy holds every 32 of its steps in one piece, [term][row][32], padded to whole tiles and to 32 steps.
+template <int ROWS, int TERMS, int BK, int kThreads>
+struct TermSlab {
+    static constexpr int kPitch = BK + 8, PART = TERMS * ROWS * 4, N = PART * (BK / 32) / kThreads;      // pieces of eight: of 32 steps, of a thread
+    static_assert(PART % kThreads == 0, "a thread's pieces lie in the same 32 steps for the whole workgroup");
+    uint4 v[N];
+    __device__ __forceinline__ void place(int32_t, int64_t) {}
+    __device__ __forceinline__ void load(const uint16_t* base, const uint16_t*, int32_t left) {
+#pragma unroll
+        for (int h = 0; h < N; ++h) {
+            v[h] = make_uint4(0u, 0u, 0u, 0u);
+            if (h * kThreads / PART * 32 < left) v[h] = *reinterpret_cast<const uint4*>(base + (uint32_t(threadIdx.x) + h * kThreads) * 8u);
+        }
+    }
+    __device__ __forceinline__ void store(uint16_t* s, int32_t) const {
+#pragma unroll
+        for (int h = 0; h < N; ++h) {
+            const int c = int(threadIdx.x) + h * kThreads % PART;
+            *reinterpret_cast<uint4*>(s + (c / 4) * kPitch + h * kThreads / PART * 32 + (c % 4) * 8) = v[h];
+        }
+    }
+};
+
 __device__ __forceinline__ bf16x8 fragment(const uint16_t* s) { return __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(s)); }
 
 // WM x WN wavefronts, each TMB x TNB blocks of 32 x 32. B is the library's own padded weight copy. GATE masks A.
@@ -111,12 +134,16 @@ __device__ __forceinline__ bf16x8 fragment(const uint16_t* s) { return __builtin
 // 256 x 128 with one stage 95 / 197, 1.40 / 2.50; 128 x 128, three to a unit, 91 / 166, 1.31 / 2.34; 64 x 256 98 / 161,
 // 1.47 / 2.25; workgroups that stay and fetch the next 256 x 256 tile behind the stores 108 / 197, 1.46 / 2.39.
 // STAGES: stages of A and B kept in LDS, 2 or 1 (then a further barrier parts the reads of a stage from the next one's writes).
-template <int WM, int WN, int TMB, int TNB, int BK, int STAGES, bool GATE>
+// TERMS = 3: the weights in three bf16 terms that add up to them exactly (kExactTerms), one product of each block of A with every term. Bound by the
+// path of A into LDS: rows at odd addresses come in pieces of half a line in stages of 32 steps, most lines twice (the first three shapes of
+// varco_gemm_bf16_usable 260, 283 and 229 us), in whole lines in stages of 64 (175, 178, 138). One stage in LDS, two workgroups to a compute unit.
+template <int WM, int WN, int TMB, int TNB, int BK, int STAGES, bool GATE, int TERMS = 1>
 __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_bf16_kernel(GemmDev g) {
     constexpr int BM = 32 * TMB * WM, BN = 32 * TNB * WN, kThreads = WM * WN * 64, kPitch = BK + 8;
+    static_assert(TERMS == 1 || !GATE, "the transform's weights only");
     extern __shared__ __attribute__((aligned(16))) uint16_t lds[];       // STAGES stages of A, then of B
     auto sa = [&](int buf) { return lds + buf * (BM * kPitch); };
-    auto sb = [&](int buf) { return lds + STAGES * BM * kPitch + buf * (BN * kPitch); };
+    auto sb = [&](int buf) { return lds + STAGES * BM * kPitch + buf * (TERMS * BN * kPitch); };
 
     // workgroup -> tile: tiles that share streamed data go to one XCD (workgroups are dealt to the 8 XCDs
     // round-robin), so that the streamed operand is fetched into a single L2
@@ -142,11 +169,11 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_bf16_kernel(GemmDev g) {
             for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
 
     RowSlab<BM, GATE, true, BK, kThreads> ra;
-    RowSlab<BN, false, false, BK, kThreads> rb;
+    std::conditional_t<TERMS == 1, RowSlab<BN, false, false, BK, kThreads>, TermSlab<BN, TERMS, BK, kThreads>> rb;
     const uint16_t *pa = nullptr, *pg = nullptr, *pb = nullptr;     // the next stage's bases, and what is left of its product's steps
     int32_t left = 0;
     auto enter = [&](const OperandDev& a, const uint16_t* b, int64_t ldb, int32_t steps) {
-        pa = a.ptr + int64_t(m0) * a.ld, pg = a.gate + int64_t(m0) * a.ld, pb = b + int64_t(n0) * ldb;
+        pa = a.ptr + int64_t(m0) * a.ld, pg = a.gate + int64_t(m0) * a.ld, pb = b + int64_t(n0) * ldb * TERMS;
         ra.place(g.m - m0, a.ld);
         rb.place(g.n - n0, ldb);
         left = steps;
@@ -157,7 +184,7 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_bf16_kernel(GemmDev g) {
         ra.load(pa, pg, left);
         rb.load(pb, nullptr, left);
         held = left;
-        pa += BK, pg += BK, pb += BK, left -= BK;
+        pa += BK, pg += BK, pb += TERMS == 1 ? BK : TERMS * BN * BK, left -= BK;
     };
     auto stash = [&](int buf) {
         ra.store(sa(buf), held);
@@ -178,16 +205,20 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_bf16_kernel(GemmDev g) {
 #pragma unroll
         for (int s = 0; s < BK / 16; ++s) {
             const int koff = s * 16 + lk * 8;
-            bf16x8 fa[TMB], fb[TNB];
+            bf16x8 fa[TMB], fb[TERMS][TNB];
 #pragma unroll
             for (int i = 0; i < TMB; ++i) fa[i] = fragment(sa(buf) + (wm + i * 32 + lrow) * kPitch + koff);
 #pragma unroll
-            for (int j = 0; j < TNB; ++j) fb[j] = fragment(sb(buf) + (wn + j * 32 + lrow) * kPitch + koff);
+            for (int p = 0; p < TERMS; ++p)
 #pragma unroll
-            for (int i = 0; i < TMB; ++i)
+                for (int j = 0; j < TNB; ++j) fb[p][j] = fragment(sb(buf) + (p * BN + wn + j * 32 + lrow) * kPitch + koff);
 #pragma unroll
-                for (int j = 0; j < TNB; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[j], fa[i], acc[i][j], 0, 0, 0);
+            for (int p = 0; p < TERMS; ++p)
+#pragma unroll
+                for (int i = 0; i < TMB; ++i)
+#pragma unroll
+                    for (int j = 0; j < TNB; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[p][j], fa[i], acc[i][j], 0, 0, 0);
         }
         if constexpr (STAGES == 2)
             if (t + 1 < t_end) stash(buf ^ 1);
@@ -196,7 +227,7 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_bf16_kernel(GemmDev g) {
 
     // accumulator register v of a lane is element (row lane % 32, column 8 * (v / 4) + 4 * (lane / 32) + v % 4)
     constexpr int kOut = 32 * TNB + 8;                     // elements per row of the wavefront's 32-row strip in LDS
-    static_assert(kThreads / 64 * 32 * kOut <= STAGES * (BM + BN) * kPitch, "a strip per wavefront");
+    static_assert(kThreads / 64 * 32 * kOut <= STAGES * (BM + TERMS * BN) * kPitch, "a strip per wavefront");
     uint16_t* const strip = lds + wave * 32 * kOut;
     bf16_t* const base = static_cast<bf16_t*>(second ? g.c_dual : g.c);
     const bool vec = g.vec_c;
@@ -258,7 +289,18 @@ bool varco_gemm_bf16_usable(const GemmArgs& ga) {
     if (ga.m <= 0 || ga.n <= 0) return false;
     if (ga.a.transposed) return varco_gemm_tn_bf16_usable(ga);
     if (ga.a.dtype != VARCO_BF16) return false;
-    // (Other reductions take fp32 matrix instructions and the weights as they are: here the weights are rounded to bf16.)
+    if (ga.bf16_terms == kExactTerms) {
+        // Rows of any length from 8 on, at any address of an element; weights that are not rounded, three products of each. fp32 instructions on
+        // tiles of 128 x 128 (256 x 64) in stages of 16 steps / this, us: 819,353 rows two taps 135 -> 40 363 / 175, 911,699 rows 227 -> 40 added to C
+        // 345 / 178, 323,741 rows 79 -> 272 239 / 138, 52,727 rows two taps 121 -> 168 93 / 36, 35,999 rows 221 -> 56 40 / 16. (Shorter rows, and
+        // rows of 4 elements, keep the fp32 instructions.)
+        auto ok3 = [&](const GemmOperand& o, const void* prep, int64_t pitch, int32_t k) {
+            return o.dtype == VARCO_BF16 && !o.transposed && !o.gate && prep && aligned_to(prep, 16) && k >= 8 && pitch == (int64_t(k) + 31) / 32 * 32;
+        };
+        return ga.c_dtype == VARCO_BF16 && !ga.b.gate && !ga.c_dual && ga.split_k <= 1 && ok3(ga.a, ga.b_prep, ga.b_prep_ld, ga.k) &&
+               (ga.k2 == 0 || ok3(ga.a2, ga.b2_prep, ga.b2_prep_ld, ga.k2));
+    }
+    // (Here the weights are rounded to bf16.)
     auto ok8 = [](const GemmOperand& o) { return aligned_to(o.ptr, 8) && aligned_to(o.gate, 8) && o.ld % 4 == 0; };
     // needs the library's bf16 weight copy [n][pitch], pitch a multiple of 8
     if (ga.c_dtype != VARCO_BF16 || !ga.b_prep || ga.b_prep_ld % 8 != 0 || !aligned_to(ga.b_prep, 16)) return false;
@@ -273,8 +315,9 @@ hipError_t varco_launch_gemm_bf16(const GemmArgs& ga, hipStream_t stream, const 
     if (ga.a.transposed) return varco_launch_gemm_tn_bf16(ga, stream, tag, split_used);
     // 128 x 256 where its tiles fill the device, two to a compute unit, and pad no more columns than 256 x 128
     const int64_t wide = int64_t((ga.m + 127) / 128) * ((ga.n + 255) / 256);
-    const int bn = ga.n <= 64 ? 64 : wide >= 512 && (ga.n + 255) / 256 * 2 == (ga.n + 127) / 128 ? 256 : 128;
-    const int bm = bn == 256 ? 128 : 256;
+    const bool exact = ga.bf16_terms == kExactTerms;
+    const int bn = ga.n <= 64 ? 64 : !exact && wide >= 512 && (ga.n + 255) / 256 * 2 == (ga.n + 127) / 128 ? 256 : 128;
+    const int bm = bn == 256 || (exact && bn == 128) ? 128 : 256;
     const bool gate = ga.a.gate != nullptr;
 
     GemmDev g;
@@ -319,7 +362,23 @@ hipError_t varco_launch_gemm_bf16(const GemmArgs& ga, hipStream_t stream, const 
     using I4 = std::integral_constant<int, 4>;
     using I32 = std::integral_constant<int, 32>;
     using I64 = std::integral_constant<int, 64>;
-    if (bn == 256)
+    if (exact) {
+        auto go = [&](auto wm, auto wn, auto stages) {
+            constexpr int WM = decltype(wm)::value, WN = decltype(wn)::value, STAGES = decltype(stages)::value;
+            constexpr size_t bytes = size_t(STAGES) * 32 * (2 * WM + 3 * 2 * WN) * (64 + 8) * 2;
+            const auto kernel = gemm_bf16_kernel<WM, WN, 2, 2, 64, STAGES, false, 3>;
+            if (bytes > 64 * 1024)
+                err = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, int(bytes));
+            if (err != hipSuccess) return;
+            tag.begin(stream);
+            hipLaunchKernelGGL(kernel, grid, dim3(WM * WN * 64), bytes, stream, g);
+            tag.end(stream);
+        };
+        if (bn == 128)
+            go(I2{}, I2{}, I1{});
+        else
+            go(I4{}, I1{}, I1{});
+    } else if (bn == 256)
         launch(I2{}, I2{}, I2{}, I4{}, I64{}, I1{});
     else if (bn == 128)
         launch(I2{}, I2{}, I4{}, I2{}, I32{}, I2{});

@@ -562,7 +562,7 @@ int64_t varco_prep_blocks(PrepJob* jobs, int n) {
     for (int i = 0; i < n; ++i) {
         PrepJob& j = jobs[i];
         const bool plain = j.terms == 1 && j.rows_padded == j.rows && j.pitch >= j.cols;
-        const bool tiled = (j.terms == 2 || j.terms == 3 || (j.terms == kHalfTerms && !j.transpose)) && j.rows_padded >= j.rows && j.rows_padded % kPrepRows == 0 && j.pitch >= j.cols && j.pitch % BK == 0;
+        const bool tiled = (j.terms == 2 || j.terms == 3 || j.terms == kExactTerms || (j.terms == kHalfTerms && !j.transpose)) && j.rows_padded >= j.rows && j.rows_padded % kPrepRows == 0 && j.pitch >= j.cols && j.pitch % BK == 0;
         if (!plain && !tiled) return -1;
         j.first_block = int32_t(blocks);
         blocks += j.terms == kHalfTerms ? j.rows_padded / 32 : (int64_t(j.rows_padded) * j.pitch + kThreads - 1) / kThreads;

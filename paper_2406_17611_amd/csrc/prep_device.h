@@ -97,10 +97,25 @@ __device__ __forceinline__ void prep_weights(const PrepJobs<CAP>& jobs, int32_t 
         out[idx] = float_to_bf16(x);
         return;
     }
-    const int32_t bn = jb.rows <= 64 ? 64 : 128;
-    const int64_t first = (int64_t(r / bn) * (jb.pitch / kPrepStage) + c / kPrepStage) * jb.terms;
+    const bool exact = jb.terms == kExactTerms;
+    const int32_t bn = jb.rows <= 64 ? 64 : 128, terms = exact ? 3 : jb.terms;
+    const int64_t first = (int64_t(r / bn) * (jb.pitch / kPrepStage) + c / kPrepStage) * terms;
     const int32_t inside = (r % bn) * kPrepStage + c % kPrepStage;
-    for (int p = 0; p < jb.terms; ++p) {
+    if (exact) {
+        // Cut, not rounded: every term has the sign of the value, and none but that of a zero is zero (2^-126 instead, beyond every sum's last
+        // bit), so that an infinite element of a row, or of the weights, gives the infinity or NaN that it gives in one product.
+        const uint32_t sign = __float_as_uint(x) & 0x80000000u;
+        const bool some = x != 0.f;
+        for (int p = 0; p < 3; ++p) {
+            uint32_t t = __float_as_uint(x) & 0xFFFF0000u;
+            if (x != x) t = 0x7FC00000u;                                                   // (a NaN whose upper bits say infinity)
+            x = isinf(x) ? 0.f : x - __uint_as_float(t);
+            if (some && (t & 0x7FFFFFFFu) < 0x00800000u) t = sign | 0x00800000u;
+            out[(first + p) * bn * kPrepStage + inside] = uint16_t(t >> 16);
+        }
+        return;
+    }
+    for (int p = 0; p < terms; ++p) {
         const uint16_t t = float_to_bf16(x);
         out[(first + p) * bn * kPrepStage + inside] = t;
         x -= __uint_as_float(uint32_t(t) << 16);

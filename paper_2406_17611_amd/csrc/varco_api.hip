@@ -255,8 +255,10 @@ int32_t ensure_tables(varco_ctx* ctx) {
     return VARCO_OK;
 }
 
+static bool exact_terms(int32_t fi, bool transpose) { return transpose && fi % 4 != 0 && fi >= 8; }
+
 // Copy of a weight matrix in the form the bf16 matrix-core kernels take (B or B2 of `g`): rows = the product's
-// output index, pitch padded; bf16 storage: one rounded copy; fp32 storage: the terms of the exact bf16
+// output index, pitch padded; bf16 storage: one rounded copy, or three terms (exact_terms); fp32 storage: the terms of the exact bf16
 // expansion for the transform, two scaled fp16 terms for the input gradient. Nothing to do when fp32 instructions are used. Every (layer, weight, orientation)
 // has a slot of its own in the stream's workspace, and a copy made earlier in the same step from the same
 // pointer is reused: the weights of a step do not change (they are updated between steps). Returns whether `job`, which
@@ -265,15 +267,19 @@ bool prep_slot(varco_ctx* ctx, Workspace& ws, int32_t layer, const void* h, int3
                GemmArgs& g, PrepJob* job) {
     const bool bf16 = ctx->dtype == VARCO_BF16;
     if (!bf16 && ctx->f32_terms == 0) return false;
-    const int32_t terms = bf16 ? 1 : transpose ? ctx->f32_terms : kHalfTerms;      // the transform reads H^T, the input gradient H
+    // Rows of a length that is no multiple of 4 meet weights that are not rounded (varco_gemm_bf16_usable).
+    const bool exact = bf16 && exact_terms(fi, transpose), plain = bf16 && !exact;
+    const int32_t terms = exact ? kExactTerms : bf16 ? 1 : transpose ? ctx->f32_terms : kHalfTerms;      // the transform reads H^T, the input gradient H
     const int32_t rows = transpose ? fo : fi, cols = transpose ? fi : fo;
-    const int32_t p = bf16 ? pad8(cols) : pad_to(cols, 32);
-    const int32_t rows_padded = bf16 ? rows : pad_to(rows, 128);   // whole tiles: the kernel reads the copy without bounds checks
+    const int32_t p = plain ? pad8(cols) : pad_to(cols, 32);
+    const int32_t rows_padded = plain ? rows : pad_to(rows, 128);   // whole tiles: the kernel reads the copy without bounds checks
     const size_t slot = (size_t(layer) * kWeightSlots + which) * 2 + (transpose ? 0 : 1);
     uint16_t* dst = reinterpret_cast<uint16_t*>(ws.w) + ctx->w_slot[slot];
     (as_b2 ? g.b2_prep : g.b_prep) = dst;
     (as_b2 ? g.b2_prep_ld : g.b_prep_ld) = p;
-    if (!bf16) {
+    if (bf16) {
+        g.bf16_terms = terms;
+    } else {
         (as_b2 ? g.b2_prep_plane : g.b_prep_plane) = int64_t(rows_padded) * p;
         g.f32_terms = ctx->f32_terms;
         g.b_halves = terms == kHalfTerms;
@@ -488,12 +494,12 @@ extern "C" int32_t varco_create(const varco_config* cfg, varco_ctx** out) {
     ctx->parts.resize(cfg->n_partitions);
     ctx->stats.bytes_per_elem = cfg->dtype == VARCO_BF16 ? 2 : 4;
     {   // converted weight copies: a slot per (layer, weight, orientation); bf16 storage: rows padded to 8 elements;
-        // fp32 storage: three terms each, padded to 128 rows of a multiple of 32 elements
+        // fp32 storage, and forward copies that are not rounded: three terms each, padded to 128 rows of a multiple of 32 elements
         const bool bf16 = ctx->dtype == VARCO_BF16;
         size_t total = 0;
         for (int32_t l = 0; l < ctx->n_layers; ++l) {
             const int32_t fi = ctx->widths[l], fo = ctx->widths[l + 1];
-            const size_t fwd = bf16 ? size_t(fo) * pad8(fi) : size_t(3) * pad_to(fo, 128) * pad_to(fi, 32);
+            const size_t fwd = bf16 && !exact_terms(fi, true) ? size_t(fo) * pad8(fi) : size_t(3) * pad_to(fo, 128) * pad_to(fi, 32);
             const size_t bwd = bf16 ? size_t(fi) * pad8(fo) : size_t(3) * pad_to(fi, 128) * pad_to(fo, 32);
             for (int which = 0; which < kWeightSlots; ++which)
                 for (size_t sz : {fwd, bwd}) {

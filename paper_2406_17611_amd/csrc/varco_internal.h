@@ -235,6 +235,9 @@ hipError_t varco_launch_link_transposed(const LinkPartition& p, const int32_t* p
 hipError_t varco_launch_link_items(const SpmmPlan& part, int32_t row_off, int32_t ent_off, int32_t slot_off, int32_t item_off,
                                    int32_t split_off, const SpmmPlan& out, hipStream_t stream);
 
+// Forms of weight copies beside a number of bf16 terms (varco_launch_prep_weights).
+constexpr int kHalfTerms = 4, kExactTerms = 5;
+
 // C (+)= op(A) op(B) in fp32 on the matrix cores, row-major everywhere.
 struct GemmOperand {
     const void* ptr = nullptr;    // matrix as stored
@@ -258,6 +261,7 @@ struct GemmArgs {
     // by varco_launch_prep_weights (by tile and stage, `plane` elements per term in all)
     int32_t f32_terms = 0;
     int64_t b_prep_plane = 0, b2_prep_plane = 0;
+    int32_t bf16_terms = 1;       // bf16 operands: form of b_prep and b2_prep, one rounded copy (1) or kExactTerms
     bool b_halves = false;        // b_prep (and b_dual_prep) hold two scaled fp16 terms instead (kHalfTerms)
     void* c = nullptr;
     int c_dtype = VARCO_F32;
@@ -377,7 +381,7 @@ int64_t varco_gemm_half_tn_tiles(const GemmArgs& g);
 //   terms = 2, 3: the terms of the exact expansion, rows padded to rows_padded (a multiple of 128) and columns to pitch (a
 //   multiple of 32), stored by row tile and stage of 32 columns as the product kernel fetches it (kernels_gemm_split.hip);
 //   kHalfTerms: two scaled fp16 terms in the same order, then the rows' scale exponents (kernels_gemm_half.hip).
-constexpr int kHalfTerms = 4;
+//   kExactTerms: three bf16 terms of the value's sign that add up to it, stored as terms = 3.
 struct PrepJob {
     const float* h;
     void* out;

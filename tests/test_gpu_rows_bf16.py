@@ -1,0 +1,75 @@
+"""The transform of bf16 rows whose length is no multiple of 4, by weights in three exact bf16 terms: stages of 32 steps, pieces of eight that cross the end of
+a row, tiles of 256 x 64 and 128 x 128, columns padded to whole tiles."""
+import numpy as np
+import pytest
+import torch
+
+from gpu_common import KEY, dev
+from paper_2406_17611_amd import binding as vb
+from paper_2406_17611_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+def _weights(rng, fi, fo):
+    # values of every size, some with bits in all three terms, some in the first alone, zeros
+    h = synth.glorot(fi, fo, 3, 1).astype(np.float32) * np.exp2(rng.integers(-9, 3, (fi, fo))).astype(np.float32)
+    h[rng.random((fi, fo)) < 0.1] = 0.25
+    h[rng.random((fi, fo)) < 0.1] = 0.0
+    return h
+
+
+@pytest.mark.parametrize("fi,fo", [(9, 1), (17, 33), (31, 64), (33, 65), (63, 8), (65, 128), (70, 129), (127, 256), (129, 40), (135, 200), (226, 72), (257, 47), (511, 130)])
+@pytest.mark.parametrize("n", [1, 127, 129, 257, 3001])
+def test_transform(n, fi, fo):
+    """Weights are not rounded: a result is the fp64 one to half a unit of bf16 and the rounding of fp32 sums. Added to what is there, from any
+    element of a larger tensor on; nothing behind the last row is read into it or written."""
+    rng = np.random.default_rng(n + fi + fo)
+    y = torch.from_numpy(rng.standard_normal((n, fi)).astype(np.float32)).to(torch.bfloat16)
+    h = _weights(rng, fi, fo)
+    old = torch.from_numpy(rng.standard_normal((n + 1, fo)).astype(np.float32)).to(torch.bfloat16)
+    held = torch.full((n * fi + 2,), float("nan"), device="cuda", dtype=torch.bfloat16)
+    held[1:-1] = y.cuda().flatten()
+    out = old.cuda()
+    ctx = vb.Context([fi, fo], [vb.ACT_RELU], vb.CONV_GCN, 1, KEY, vb.BF16)
+    ctx.prepare()
+    ctx.transform_fwd(0, held[1:-1].view(n, fi), dev(h), out[:n], True, True)
+    torch.cuda.synchronize()
+    a, b, o = y.double().numpy(), h.astype(np.float64), old.double().numpy()
+    want = np.maximum(a @ b + o[:n], 0.0)
+    size = np.abs(a) @ np.abs(b) + np.abs(o[:n])
+    got = out.double().cpu().numpy()
+    # three products a step, each added with a rounding of 2^-24: the square root of their number, four times for the tail
+    # and half a unit in the eighth digit of the result
+    half = np.exp2(np.floor(np.log2(np.maximum(np.maximum(want, got[:n]), 2.0 ** -120))) - 8)
+    bound = half + 4 * 2.0 ** -24 * np.sqrt(3 * fi + 1) * size
+    assert (np.abs(got[:n] - want) <= bound).all()
+    assert np.array_equal(got[n], o[n])
+    ctx.close()
+
+
+def test_values_that_are_not_finite():
+    """Infinite elements and weights give what one product of fp32 numbers gives, and stay in their row and column."""
+    n, fi, fo = 300, 75, 70
+    rng = np.random.default_rng(4)
+    y = torch.from_numpy(rng.standard_normal((n, fi)).astype(np.float32)).to(torch.bfloat16)
+    h = _weights(rng, fi, fo)
+    h[3], h[5, :20], h[5, 20:] = 0.5, 1.25, 0.0           # (one term; beside it 0 times infinity)
+    y[:, 5] = 1.0
+    y[2, 3], y[3, 3], y[4, 5], y[5, 7] = float("inf"), -float("inf"), float("inf"), float("nan")
+    h[11, 60], h[11, 61], h[12, 62] = np.inf, -np.inf, np.nan
+    y[:, 11] = 2.0
+    ctx = vb.Context([fi, fo], [vb.ACT_IDENTITY], vb.CONV_GCN, 1, KEY, vb.BF16)
+    ctx.prepare()
+    out = torch.zeros(n, fo, device="cuda", dtype=torch.bfloat16)
+    ctx.transform_fwd(0, y.cuda(), dev(h), out, False, False)
+    torch.cuda.synchronize()
+    want = (y.float()[:, :, None] * torch.from_numpy(h)[None]).double().sum(1)
+    got = out.double().cpu()
+    assert torch.equal(torch.isnan(got), torch.isnan(want))
+    for sign in (1, -1):
+        assert torch.equal(got == sign * np.inf, want == sign * np.inf)
+    finite = torch.isfinite(want)
+    assert finite.sum() > 0.9 * n * 60
+    assert ((got - want).abs()[finite] <= 2.0 ** -8 * want.abs()[finite] + 1e-3).all()
+    ctx.close()
