@@ -17,11 +17,13 @@ struct Packed<float, N> {
 #pragma unroll
         for (int i = 0; i < N; ++i) x[i] = v[i];
     }
+    template <bool ANY = false>
     static __device__ __forceinline__ void put(float* p, const float (&x)[N]) {
+        typedef type stored __attribute__((aligned(ANY ? sizeof(float) : sizeof(type))));
         type v;
 #pragma unroll
         for (int i = 0; i < N; ++i) v[i] = x[i];
-        *reinterpret_cast<type*>(p) = v;
+        *reinterpret_cast<stored*>(p) = v;
     }
 };
 template <>
@@ -29,6 +31,7 @@ struct Packed<float, 1> {
     using type = float;
     static __device__ __forceinline__ type load(const float* p) { return *p; }
     static __device__ __forceinline__ void get(const type& v, float (&x)[1]) { x[0] = v; }
+    template <bool ANY = false>
     static __device__ __forceinline__ void put(float* p, const float (&x)[1]) { *p = x[0]; }
 };
 template <int N>
@@ -39,11 +42,13 @@ struct Packed<bf16_t, N> {
 #pragma unroll
         for (int i = 0; i < N / 2; ++i) x[2 * i] = __uint_as_float(v[i] << 16), x[2 * i + 1] = __uint_as_float(v[i] & 0xFFFF0000u);
     }
+    template <bool ANY = false>
     static __device__ __forceinline__ void put(bf16_t* p, const float (&x)[N]) {
+        typedef type stored __attribute__((aligned(ANY ? sizeof(bf16_t) : sizeof(type))));
         type v;
 #pragma unroll
         for (int i = 0; i < N / 2; ++i) v[i] = bf16_pair(x[2 * i], x[2 * i + 1]);
-        *reinterpret_cast<type*>(p) = v;
+        *reinterpret_cast<stored*>(p) = v;
     }
 };
 template <>
@@ -51,8 +56,13 @@ struct Packed<bf16_t, 2> {
     using type = uint32_t;
     static __device__ __forceinline__ type load(const bf16_t* p) { return *reinterpret_cast<const uint32_t*>(p); }
     static __device__ __forceinline__ void get(const type& v, float (&x)[2]) { x[0] = __uint_as_float(v << 16), x[1] = __uint_as_float(v & 0xFFFF0000u); }
+    template <bool ANY = false>
     static __device__ __forceinline__ void put(bf16_t* p, const float (&x)[2]) {
-        *reinterpret_cast<uint32_t*>(p) = bf16_pair(x[0], x[1]);
+        typedef uint32_t any __attribute__((aligned(2)));
+        if constexpr (ANY)
+            *reinterpret_cast<any*>(p) = bf16_pair(x[0], x[1]);
+        else
+            *reinterpret_cast<uint32_t*>(p) = bf16_pair(x[0], x[1]);
     }
 };
 template <>
@@ -60,13 +70,19 @@ struct Packed<bf16_t, 1> {
     using type = uint16_t;
     static __device__ __forceinline__ type load(const bf16_t* p) { return p->bits; }
     static __device__ __forceinline__ void get(const type& v, float (&x)[1]) { x[0] = bf16_to_float(v); }
+    template <bool ANY = false>
     static __device__ __forceinline__ void put(bf16_t* p, const float (&x)[1]) { p->bits = float_to_bf16(x[0]); }
 };
 
-// Load from an address in global memory that was handled as a number (a generic address would go through the LDS check).
-template <typename T, int N>
+// Load from an address in global memory that was handled as a number (a generic address would go through the LDS check). ANY: from the
+// address of any element (the device loads up to 16 bytes from there just as well).
+template <typename T, int N, bool ANY = false>
 __device__ __forceinline__ typename Packed<T, N>::type load_packed(uint64_t address, uint32_t byte_offset) {
     using V = typename Packed<T, N>::type;
+    if constexpr (ANY) {
+        typedef V any __attribute__((aligned(sizeof(T))));
+        return *(const __attribute__((address_space(1))) any*)((const __attribute__((address_space(1))) char*)address + byte_offset);
+    }
     return *(const __attribute__((address_space(1))) V*)((const __attribute__((address_space(1))) char*)address + byte_offset);
 }
 
@@ -79,8 +95,12 @@ __device__ __forceinline__ uint32_t lane_value(uint32_t v, int byte_lane) { retu
 // what is the same for the whole wavefront stays in scalar registers: with all lanes on one row its address and weight come by
 // v_readlane and the load takes a scalar base; the last batch leaves out by scalar branches what
 // is not there.
+// ANY: rows of any length from VEC elements on; the lane that would reach past the end of its row takes the row's last VEC elements instead,
+// and adds to them what its neighbour adds.
 constexpr int loads_per_row(int nv) { return nv > 0 ? nv : 1; }
-template <typename T, int VEC, int NV, int U>
+template <int VEC, bool ANY>
+__device__ __forceinline__ int32_t row_column(int32_t c, int32_t width) { return ANY ? min(c, width - VEC) : c; }
+template <typename T, int VEC, int NV, int U, bool ANY = false>
 __device__ __forceinline__ void gather_rows(uint64_t addr, float w, int n, int32_t width, int lane, int lpr_log2, float (&acc)[loads_per_row(NV)][VEC]) {
     using P = Packed<T, VEC>;
     uint32_t lo = uint32_t(addr), hi = uint32_t(addr >> 32), wb = __float_as_uint(w);
@@ -90,7 +110,7 @@ __device__ __forceinline__ void gather_rows(uint64_t addr, float w, int n, int32
     if constexpr (NV > 0) {
         uint32_t off[NV];                        // lanes beyond the row re-read its start (their sums are never stored)
 #pragma unroll
-        for (int m = 0; m < NV; ++m) off[m] = VEC * (lane + 64 * m) < width ? uint32_t(VEC * sizeof(T)) * uint32_t(lane + 64 * m) : 0u;
+        for (int m = 0; m < NV; ++m) off[m] = VEC * (lane + 64 * m) < width ? uint32_t(sizeof(T)) * uint32_t(row_column<VEC, ANY>(VEC * (lane + 64 * m), width)) : 0u;
         auto batch = [&](int i0, auto partial) {
             constexpr bool PART = decltype(partial)::value;
             typename P::type v[U][NV];
@@ -102,7 +122,7 @@ __device__ __forceinline__ void gather_rows(uint64_t addr, float w, int n, int32
                                          uint32_t(__builtin_amdgcn_readlane(int(lo), i0 + u));
                     wi[u] = __uint_as_float(uint32_t(__builtin_amdgcn_readlane(int(wb), i0 + u)));
 #pragma unroll
-                    for (int m = 0; m < NV; ++m) v[u][m] = load_packed<T, VEC>(row, off[m]);
+                    for (int m = 0; m < NV; ++m) v[u][m] = load_packed<T, VEC, ANY>(row, off[m]);
                 }
 #pragma unroll
             for (int u = 0; u < U; ++u)
@@ -120,7 +140,7 @@ __device__ __forceinline__ void gather_rows(uint64_t addr, float w, int n, int32
         if (i0 < n) batch(i0, std::true_type{});
     } else {
         const int lpr = 1 << lpr_log2, ng = 64 >> lpr_log2, c = VEC * (lane & (lpr - 1)), g = lane >> lpr_log2;
-        const uint32_t off = c < width ? uint32_t(c) * uint32_t(sizeof(T)) : 0u;
+        const uint32_t off = c < width ? uint32_t(row_column<VEC, ANY>(c, width)) * uint32_t(sizeof(T)) : 0u;
         auto batch = [&](int i0, auto count, auto partial) {
             constexpr int N = decltype(count)::value;
             constexpr bool PART = decltype(partial)::value;
@@ -131,7 +151,7 @@ __device__ __forceinline__ void gather_rows(uint64_t addr, float w, int n, int32
                 const int i = i0 + u * ng + g;
                 const uint64_t row = (uint64_t(lane_value(hi, 4 * i)) << 32) | lane_value(lo, 4 * i);
                 wi[u] = lane_value(wb, 4 * i);
-                if (!PART || i < n) v[u] = load_packed<T, VEC>(row, off);
+                if (!PART || i < n) v[u] = load_packed<T, VEC, ANY>(row, off);
             }
 #pragma unroll
             for (int u = 0; u < N; ++u)
@@ -160,10 +180,10 @@ __device__ __forceinline__ void sum_groups(int lpr_log2, float (&acc)[loads_per_
             for (int i = 0; i < VEC; ++i) acc[0][i] += __shfl_xor(acc[0][i], off);
 }
 
-// Rows of fp32 in LDS or memory, VEC at a time.
-template <int VEC>
+// Rows of fp32 in LDS or memory, VEC at a time (ANY: from the address of any element).
+template <int VEC, bool ANY = false>
 __device__ __forceinline__ void add_floats(const float* p, float (&x)[VEC]) {
-    constexpr int W = VEC < 4 ? VEC : 4;
+    constexpr int W = ANY ? 1 : VEC < 4 ? VEC : 4;
 #pragma unroll
     for (int i = 0; i < VEC; i += W) {
         const typename FloatVec<W>::type v = *reinterpret_cast<const typename FloatVec<W>::type*>(p + i);
@@ -172,9 +192,9 @@ __device__ __forceinline__ void add_floats(const float* p, float (&x)[VEC]) {
         for (int q = 0; q < W; ++q) x[i + q] += e[q];
     }
 }
-template <int VEC>
+template <int VEC, bool ANY = false>
 __device__ __forceinline__ void put_floats(float* p, const float (&x)[VEC]) {
-    constexpr int W = VEC < 4 ? VEC : 4;
+    constexpr int W = ANY ? 1 : VEC < 4 ? VEC : 4;
 #pragma unroll
     for (int i = 0; i < VEC; i += W) {
         typename FloatVec<W>::type v;

@@ -154,11 +154,14 @@ __device__ __forceinline__ float4 rotated(const float4& v, uint32_t rot) {
 // element for folding position bits into the address, and the rows are read back as they are.
 // (bf16, 512 wide, k = 128, a dozen entries per row: the forward aggregation took 314 us with the folded addresses, the
 // multiplier table staged per wavefront and per-lane dense addresses; 176 us now.)
-template <typename T, int EV, bool Z32, bool POW2>
+// REM: rows of any number of elements from EV on, at any address of an element. The last lane of an entry takes the row's last EV elements; those
+// that its neighbour has as well it adds to a word behind the private rows that nobody reads (two lanes at one address would lose a sum).
+template <typename T, int EV, bool Z32, bool POW2, bool REM>
 __device__ __forceinline__ void sparse_phase(const SpmmArgs<T>& p, int lane, int nd, int ns, uint32_t zoff, float w, uint32_t mab,
                                              char* lrows) {
     constexpr bool ROT = EV == 4;
     using S = typename Stored<T, EV>::type;
+    typedef S Any __attribute__((aligned(REM ? sizeof(T) : alignof(S))));
     // Gathers in flight per lane: six of at most 8 bytes (four bf16 or two fp32 elements), three of 16 bytes:
     // about the same registers either way. A wavefront waits for the slowest of its gathers, so fewer, larger
     // batches win even at the price of one resident wavefront (bf16 rows of 512 elements: 7 per SIMD, forward
@@ -173,10 +176,12 @@ __device__ __forceinline__ void sparse_phase(const SpmmArgs<T>& p, int lane, int
     const uint32_t base = uint32_t(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) char*)lrows)) + uint32_t(sub) * width * 4u;
     const uint32_t mask = (width - 1u) * 4u;
     const uint32_t rot = ROT ? uint32_t(jl >> 3) & 3u : 0u;
+    const uint32_t nowhere = base + uint32_t(p.epi - sub) * width * 4u;
     for (int j0 = 0; j0 < p.ku; j0 += 64) {          // more than one pass only when an entry needs > 64 lanes
         const int ju = j0 + jl;
         const bool j_ok = lane_ok && ju < p.ku;
-        const uint32_t j = uint32_t(ju) * EV, j_bytes = j * uint32_t(sizeof(T));
+        const uint32_t j = REM ? min(uint32_t(ju) * EV, p.rule.k - EV) : uint32_t(ju) * EV, j_bytes = j * uint32_t(sizeof(T));
+        const uint32_t again = REM ? uint32_t(ju) * EV - j : 0u;         // of the lane's elements, so many are its neighbour's
         // `count` entries per lane group from entry r0 on. All gathers are issued first, with the entries' weights and rules
         // fetched from their lanes behind them; the positions are computed after the wait, so that more gathers fit the
         // registers of a wavefront. Straight-line code: a branch per entry would wait for every fetch by itself.
@@ -191,9 +196,9 @@ __device__ __forceinline__ void sparse_phase(const SpmmArgs<T>& p, int lane, int
                 const uint32_t r = lane_value(zoff, 4 * (nd + es));
                 // lanes without an entry re-read the start of the buffer (never used, but no branch around the load)
                 if constexpr (Z32)
-                    v[u] = *reinterpret_cast<const S*>(reinterpret_cast<const char*>(p.z) + (j_ok && es < ns ? r + j_bytes : 0u));
+                    v[u] = *reinterpret_cast<const Any*>(reinterpret_cast<const char*>(p.z) + (j_ok && es < ns ? r + j_bytes : 0u));
                 else
-                    v[u] = *reinterpret_cast<const S*>(p.z + (j_ok && es < ns ? int64_t(r) * p.rule.k + j : int64_t(0)));
+                    v[u] = *reinterpret_cast<const Any*>(p.z + (j_ok && es < ns ? int64_t(r) * p.rule.k + j : int64_t(0)));
             }
 #pragma unroll
             for (int u = 0; u < N; ++u) {
@@ -230,6 +235,9 @@ __device__ __forceinline__ void sparse_phase(const SpmmArgs<T>& p, int lane, int
                             at[i] = q * 4u + base;
                         }
                     }
+                    if constexpr (REM)
+#pragma unroll
+                        for (int i = 0; i < EV; ++i) at[i] = ((uint32_t(i) + rot) & uint32_t(EV - 1)) < again ? nowhere : at[i];
                     S x = v[u];
                     if constexpr (ROT) x = rotated(x, rot);
 #pragma unroll
@@ -314,8 +322,10 @@ __device__ __forceinline__ void owner_messages(const SpmmArgs<T>& p, uint32_t bl
 // the owners' rows and the launch writes the messages as well (owner_phase, owner_messages). One
 // kernel per form: the constants of forms that do not run would take registers, i.e. resident wavefronts, from the one
 // that does.
+// ANY: rows of any length from VEC elements on, at any address of an element (gather_rows); the lane at the end of a row stores what its
+// neighbour stores as well.
 constexpr int kDenseOnly = 0, kFull = 1, kSparse = 2, kSparseZ32 = 3, kOwner = 4;
-template <typename T, int VEC, int NV, int MODE, int EV, bool POW2>
+template <typename T, int VEC, int NV, int MODE, int EV, bool POW2, bool ANY, bool REM>
 __device__ __forceinline__ void spmm_rows(const SpmmArgs<T>& p) {
     constexpr bool HALO = MODE != kDenseOnly, SPARSE = MODE >= kSparse, Z32 = MODE == kSparseZ32;
     constexpr int kAggBlock = agg_block(MODE), kAggWaves = kAggBlock / 64;
@@ -376,7 +386,7 @@ __device__ __forceinline__ void spmm_rows(const SpmmArgs<T>& p) {
         const int cnt = min(64, it.e1 - base);
         const int ns = SPARSE ? __popcll(hmask) : 0;
         const int nd = cnt - ns;        // columns ascend within a row, so dense entries sit in lanes [0, nd)
-        gather_rows<T, VEC, NV, U>(addr, w, nd, width, lane, p.lpr_log2, acc);
+        gather_rows<T, VEC, NV, U, ANY>(addr, w, nd, width, lane, p.lpr_log2, acc);
         if constexpr (SPARSE) {
             if (ns > 0) {
                 if (!any_sparse) __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");     // the rows are cleared
@@ -384,7 +394,7 @@ __device__ __forceinline__ void spmm_rows(const SpmmArgs<T>& p) {
                 if constexpr (MODE == kOwner)
                     owner_phase<T, EV>(p, lane, nd, ns, zoff, w, unit | shift, lds);
                 else
-                    sparse_phase<T, EV, Z32, POW2>(p, lane, nd, ns, zoff, w, (unit | shift) << (POW2 ? 2 : 0), reinterpret_cast<char*>(lds));
+                    sparse_phase<T, EV, Z32, POW2, REM>(p, lane, nd, ns, zoff, w, (unit | shift) << (POW2 ? 2 : 0), reinterpret_cast<char*>(lds));
             }
         }
     }
@@ -394,21 +404,21 @@ __device__ __forceinline__ void spmm_rows(const SpmmArgs<T>& p) {
     if (NV == 0 && lane >= (1 << p.lpr_log2)) return;
 #pragma unroll
     for (int m = 0; m < NR; ++m) {
-        const int c = VEC * (lane + 64 * m);
-        if (c < width) {
+        if (VEC * (lane + 64 * m) < width) {
+            const int c = row_column<VEC, ANY>(VEC * (lane + 64 * m), width);
             if (SPARSE && any_sparse)
-                for (int sub = 0; sub < p.epi; ++sub) add_floats<VEC>(lds + sub * width + c, acc[m]);
+                for (int sub = 0; sub < p.epi; ++sub) add_floats<VEC, ANY>(lds + sub * width + c, acc[m]);
             if (it.dst < 0)
-                Packed<T, VEC>::put(p.out + int64_t(it.row - p.row_base) * width + c, acc[m]);
+                Packed<T, VEC>::template put<ANY>(p.out + int64_t(it.row - p.row_base) * width + c, acc[m]);
             else
-                put_floats<VEC>(p.partial + int64_t(it.dst) * width + c, acc[m]);
+                put_floats<VEC, ANY>(p.partial + int64_t(it.dst) * width + c, acc[m]);
         }
     }
 }
 
-template <typename T, int VEC, int NV, int MODE, int EV = 1, bool POW2 = false>
+template <typename T, int VEC, int NV, int MODE, int EV = 1, bool POW2 = false, bool ANY = false, bool REM = false>
 __global__ __launch_bounds__(agg_block(MODE), MODE >= kSparse && VEC * NV <= 8 ? kHaloWaves : 1) void spmm_kernel(SpmmArgs<T> p) {
-    spmm_rows<T, VEC, NV, MODE, EV, POW2>(p);
+    spmm_rows<T, VEC, NV, MODE, EV, POW2, ANY, REM>(p);
 }
 // kOwner, then the messages, then weight copies, a workgroup of which is four here. Bound by the launch, 3 us of a small step for the
 // copies alone: forward passes with / without a launch of theirs, us, 2,000 nodes 16-32-8 21.8 / 19.7, 16,000 nodes 32-64-8 42.4 / 39.9,
@@ -417,7 +427,7 @@ template <typename T, int NV, int EV>
 __global__ __launch_bounds__(64, kHaloWaves) void spmm_owner_kernel(SpmmArgs<T> p, PrepJobs<kFewPrepJobs> copies) {
     const int32_t block = int32_t(blockIdx.x), lane = int32_t(threadIdx.x);
     if (block < p.copy_block)
-        spmm_rows<T, 4, NV, kOwner, EV, false>(p);
+        spmm_rows<T, 4, NV, kOwner, EV, false, false, false>(p);
     else if (block < p.prep_block)
         owner_messages(p, uint32_t(block - p.copy_block), lane);
     else
@@ -980,36 +990,48 @@ __global__ __launch_bounds__(kBlock) void validate_ids_kernel(const int32_t* a, 
     if (bad) atomicOr(flags, bit);
 }
 
-template <typename T, int VEC, int MODE, int EV, bool POW2>
+template <typename T, int VEC, int MODE, int EV, bool POW2, bool ANY, bool REM>
 hipError_t launch_spmm_nv(int nv, const SpmmArgs<T>& a, dim3 grid, size_t lds_bytes, hipStream_t stream) {
     auto go = [&](auto n) {
         constexpr int NV = decltype(n)::value;
-        hipLaunchKernelGGL((spmm_kernel<T, VEC, NV, MODE, EV, POW2>), grid, dim3(agg_block(MODE)), lds_bytes, stream, a);
+        hipLaunchKernelGGL((spmm_kernel<T, VEC, NV, MODE, EV, POW2, ANY, REM>), grid, dim3(agg_block(MODE)), lds_bytes, stream, a);
         return hipGetLastError();
     };
     switch (nv) {
         case 0:
-            if constexpr (VEC < 8) return go(std::integral_constant<int, 0>{});
+            if constexpr (VEC < 8 && !(ANY && sizeof(T) == 4)) return go(std::integral_constant<int, 0>{});
             break;
-        case 1: return go(std::integral_constant<int, 1>{});
-        case 2: return go(std::integral_constant<int, 2>{});
-        case 4: return go(std::integral_constant<int, 4>{});
+        case 1:
+            if constexpr (VEC > 1 || sizeof(T) == 4) return go(std::integral_constant<int, 1>{});
+            break;
+        case 2:
+            if constexpr (VEC >= 4) return go(std::integral_constant<int, 2>{});
+            break;
+        case 4:
+            if constexpr (VEC >= 4 && !ANY) return go(std::integral_constant<int, 4>{});
+            break;
         case 8:
-            if constexpr (VEC < 8) return go(std::integral_constant<int, 8>{});
+            if constexpr (VEC == 4 && !ANY) return go(std::integral_constant<int, 8>{});
     }
     return hipErrorInvalidValue;
 }
-template <typename T, int VEC, int MODE>
-hipError_t launch_spmm_vec(int nv, int ev, const SpmmArgs<T>& a, dim3 grid, size_t lds_bytes, hipStream_t stream) {
+template <typename T, int VEC, int MODE, bool ANY>
+hipError_t launch_spmm_vec(int nv, int ev, bool rem, const SpmmArgs<T>& a, dim3 grid, size_t lds_bytes, hipStream_t stream) {
     if constexpr (MODE < kSparse) {
-        return launch_spmm_nv<T, VEC, MODE, 1, false>(nv, a, grid, lds_bytes, stream);
+        return launch_spmm_nv<T, VEC, MODE, 1, false, ANY, false>(nv, a, grid, lds_bytes, stream);
     } else {
         const bool pow2 = (a.rule.width & (a.rule.width - 1)) == 0;
         auto with_ev = [&](auto e) {
             constexpr int EV = decltype(e)::value;
-            if constexpr (VEC > 1)
-                if (pow2) return launch_spmm_nv<T, VEC, MODE, EV, true>(nv, a, grid, lds_bytes, stream);
-            return launch_spmm_nv<T, VEC, MODE, EV, false>(nv, a, grid, lds_bytes, stream);
+            auto go = [&](auto rm) {
+                constexpr bool REM = decltype(rm)::value;
+                if constexpr (VEC > 1 && !ANY)
+                    if (pow2) return launch_spmm_nv<T, VEC, MODE, EV, true, false, REM>(nv, a, grid, lds_bytes, stream);
+                return launch_spmm_nv<T, VEC, MODE, EV, false, ANY, REM>(nv, a, grid, lds_bytes, stream);
+            };
+            if constexpr (EV > 1 && VEC > 1)
+                if (rem) return go(std::true_type{});
+            return go(std::false_type{});
         };
         return ev == 4 ? with_ev(std::integral_constant<int, 4>{}) : ev == 2 ? with_ev(std::integral_constant<int, 2>{})
                                                                              : with_ev(std::integral_constant<int, 1>{});
@@ -1035,13 +1057,20 @@ hipError_t spmm_t(const SpmmPlan& plan, const VarcoEdge* edge, const int32_t* co
     const bool vec4 = vec_ok(4);
     // bf16: 16-byte loads where a row then still takes all lanes. (Narrower rows would have twice as many lane groups, and the
     // forward sums another order.)
-    const int vec = sizeof(T) == 2 && width > 256 && vec_ok(8) ? 8 : vec4 ? 4 : 1;
+    const int vec = sizeof(T) == 2 && width > 256 && vec_ok(8) ? 8 : vec4 ? 4 : sizeof(T) == 2 ? (width < 4 ? 1 : 4) : width <= 64 ? 1 : width <= 128 ? 2 : 4;
+    // Rows whose length is no multiple of 4, or whose base is not aligned, are loaded from any address of an element as well. fp32: as many
+    // elements to a load as let a row take all lanes with one load (two above 256 elements). One row after the other is added up, so the bits
+    // are those of loads of one element, and a ReLU whose argument is within rounding of zero decides alike. bf16: four, and narrow rows in groups of
+    // lanes as aligned ones. One element to a load / this, us: fp32 116,187 nodes 147 wide 110 / 78, 265,139 nodes 209 wide, 105 kept, 276 / 218,
+    // 771,643 nodes 94 wide 444 / 398, 50,021 nodes 75 wide 49 / 45; bf16 (with the messages below) 35,999 nodes 221 wide 73 / 49, 819,353 nodes
+    // 135 wide 524 / 465, 52,727 nodes 121 wide 53 / 44.
+    const bool any = !vec4 && vec > 1;
     const int per_row = (width + vec - 1) / vec;   // loads of VEC elements that cover a row
     int lpr_log2 = 0;
     while ((1 << lpr_log2) < per_row && lpr_log2 < 6) ++lpr_log2;
     int nv = lpr_log2 < 6 ? 0 : 1;
     while (nv && nv * 64 < per_row) nv <<= 1;
-    if (nv > 8) return hipErrorInvalidValue;
+    if (nv > 8 || (any && nv > 2)) return hipErrorInvalidValue;
 
     SpmmArgs<T> a{};
     a.items = plan.items;
@@ -1070,7 +1099,28 @@ hipError_t spmm_t(const SpmmPlan& plan, const VarcoEdge* edge, const int32_t* co
             break;
         }
     }
-    a.ku = int32_t(rule.k) / ev;
+    // Numbers of kept elements that are no multiple of that (or rows at other addresses). fp32: two or four per lane only where an entry takes all
+    // lanes either way (65 elements and more): which entries share a private row, and with it the bits, stay. bf16: as above.
+    // One (two) per lane / this, us: fp32 50,021 nodes 200 wide, 67 kept, 107 / 76; bf16 2,449,029 nodes 100 wide, 25 kept, 3,544 / 3,076.
+    bool rem = false;
+    if (halo && !full && !owners && vec > 1) {
+        const int k = int(rule.k);
+        if (sizeof(T) == 4) {
+            const int wide = k <= 64 ? 1 : k <= 128 ? 2 : 4;
+            rem = wide > ev && (ev == 1 || k > 128);
+            if (rem) ev = wide;
+        } else {
+            for (int c : {4, 2}) {
+                int lg = 0;
+                while ((1 << lg) < (k + c - 1) / c && lg < 6) ++lg;
+                if (c <= ev || k < c) break;
+                if ((64 >> lg) > epi_cap) continue;
+                ev = c, rem = true;
+                break;
+            }
+        }
+    }
+    a.ku = (int32_t(rule.k) + ev - 1) / ev;
     a.lpe_log2 = 0;
     while ((1 << a.lpe_log2) < a.ku && a.lpe_log2 < 6) ++a.lpe_log2;
     a.epi = std::max(1, std::min(64 >> a.lpe_log2, epi_cap));
@@ -1092,7 +1142,7 @@ hipError_t spmm_t(const SpmmPlan& plan, const VarcoEdge* edge, const int32_t* co
     }
     size_t lds_bytes = 0;
     if (halo && !full)
-        lds_bytes = (size_t(a.epi) * width * sizeof(float) + 15) / 16 * 16;
+        lds_bytes = (size_t(a.epi) * width * sizeof(float) + 15) / 16 * 16 + (rem ? 16 : 0);
     tag.begin(stream);
     hipError_t err = hipErrorInvalidValue;
     // compressed buffer below 4 GiB: 32-bit row offsets (z_rows = 0: size unknown)
@@ -1100,8 +1150,11 @@ hipError_t spmm_t(const SpmmPlan& plan, const VarcoEdge* edge, const int32_t* co
     auto with_vec = [&](auto mode) {
         constexpr int MODE = decltype(mode)::value;
         if constexpr (sizeof(T) == 2)
-            if (vec == 8) return launch_spmm_vec<T, 8, MODE>(nv, ev, a, grid, lds_bytes, stream);
-        return vec4 ? launch_spmm_vec<T, 4, MODE>(nv, ev, a, grid, lds_bytes, stream) : launch_spmm_vec<T, 1, MODE>(nv, ev, a, grid, lds_bytes, stream);
+            if (vec == 8) return launch_spmm_vec<T, 8, MODE, false>(nv, ev, rem, a, grid, lds_bytes, stream);
+        if constexpr (sizeof(T) == 4)
+            if (vec == 2) return launch_spmm_vec<T, 2, MODE, true>(nv, ev, rem, a, grid, lds_bytes, stream);
+        if (any) return launch_spmm_vec<T, 4, MODE, true>(nv, ev, rem, a, grid, lds_bytes, stream);
+        return vec4 ? launch_spmm_vec<T, 4, MODE, false>(nv, ev, rem, a, grid, lds_bytes, stream) : launch_spmm_vec<T, 1, MODE, false>(nv, ev, rem, a, grid, lds_bytes, stream);
     };
     if (owners) {
         auto with_ev = [&](auto e) {
@@ -1110,7 +1163,7 @@ hipError_t spmm_t(const SpmmPlan& plan, const VarcoEdge* edge, const int32_t* co
             hipLaunchKernelGGL(kernel, grid, dim3(64), lds_bytes, stream, a, copies);
             return hipGetLastError();
         };
-        if (vec == 4 && nv <= 1 && halo && !full)
+        if (vec4 && vec == 4 && nv <= 1 && halo && !full)
             err = ev == 4 ? with_ev(std::integral_constant<int, 4>{}) : ev == 2 ? with_ev(std::integral_constant<int, 2>{}) : with_ev(std::integral_constant<int, 1>{});
     } else if (halo && full)
         err = with_vec(std::integral_constant<int, kFull>{});
