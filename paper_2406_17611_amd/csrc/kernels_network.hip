@@ -117,9 +117,7 @@ __device__ __forceinline__ void sum_rows(const S* src, int64_t pitch, int32_t c0
         batch(r, std::integral_constant<int, 2>{});
     else if (r < c1)
         batch(r, std::integral_constant<int, 1>{});
-    for (int off = 1 << lpe_log2; off < 64; off <<= 1)
-#pragma unroll
-        for (int i = 0; i < EV; ++i) acc[i] += __shfl_xor(acc[i], off);
+    add_lanes(acc, lpe_log2);
 }
 
 // Partial sum of a piece of a long range (hub nodes): a dense row of width floats, or k floats of summed products.
@@ -229,9 +227,7 @@ __global__ __launch_bounds__(kBlock) void node_sum_kernel(NodeArgs<T> p) {
                         if (on)
 #pragma unroll
                             for (int i = 0; i < EV; ++i) s[i] += p.partial[int64_t(r) * width + ju * EV + i];
-                    for (int off = 1 << p.lpe_log2; off < 64; off <<= 1)
-#pragma unroll
-                        for (int i = 0; i < EV; ++i) s[i] += __shfl_xor(s[i], off);
+                    add_lanes(s, p.lpe_log2);
                 } else {
                     sum_rows<T, EV>(p.prod, p.pitch, it.c0, it.c1, ju * EV, on, sub, n_sub, p.lpe_log2, s);
                 }
