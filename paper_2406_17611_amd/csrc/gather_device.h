@@ -175,37 +175,39 @@ __device__ __forceinline__ void gather_rows(uint64_t addr, float w, int n, int32
 // and l ^ off are added for off = 1 << log2, .., 32 in turn, by data paths of the vector ALU. (__shfl_xor goes through LDS: an instruction there and a
 // round trip for every value. Node sums with it / with this, us, bf16: 819,353 nodes 40 wide, 12 kept, 599 / 487, 911,699 nodes 40 wide, 5 kept, 722 /
 // 551, 35,999 nodes 56 wide 39 / 31; fp32 rows of 256 elements, three steps of four values a node, level at 153.)
+// lanes (the same in all of them): from that lane on there are zeros, and only the first 1 << log2 lanes are looked at afterwards: steps that add nothing
+// to those are left out.
 template <int N>
-__device__ __forceinline__ void add_lanes(float (&x)[N], int log2) {
+__device__ __forceinline__ void add_lanes(float (&x)[N], int log2, int lanes = 64) {
     auto moved = [](float v, auto ctrl, auto banks) __attribute__((always_inline)) {       // v where `banks` are not
         const int u = __builtin_bit_cast(int, v);
         return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(u, u, decltype(ctrl)::value, 0xF, decltype(banks)::value, false));
     };
     using std::integral_constant;
     using All = integral_constant<int, 0xF>;
-    if (log2 <= 0)
+    if (log2 <= 0 && lanes > 1)
 #pragma unroll
         for (int i = 0; i < N; ++i) x[i] += moved(x[i], integral_constant<int, 0xB1>{}, All{});        // quad_perm 1 0 3 2
-    if (log2 <= 1)
+    if (log2 <= 1 && lanes > 2)
 #pragma unroll
         for (int i = 0; i < N; ++i) x[i] += moved(x[i], integral_constant<int, 0x4E>{}, All{});        // quad_perm 2 3 0 1
-    if (log2 <= 2)
+    if (log2 <= 2 && lanes > 4)
 #pragma unroll
         for (int i = 0; i < N; ++i) {
             const float up = moved(x[i], integral_constant<int, 0x104>{}, integral_constant<int, 0x5>{});      // lanes 0-3 and 8-11 from four lanes above,
             const int u = __builtin_bit_cast(int, x[i]);                                                       // the others from four below
             x[i] += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, up), u, 0x114, 0xF, 0xA, false));
         }
-    if (log2 <= 3)
+    if (log2 <= 3 && lanes > 8)
 #pragma unroll
         for (int i = 0; i < N; ++i) x[i] += moved(x[i], integral_constant<int, 0x128>{}, All{});       // row_ror 8
-    if (log2 <= 4)
+    if (log2 <= 4 && lanes > 16)
 #pragma unroll
         for (int i = 0; i < N; ++i) {
             const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x[i]), __float_as_uint(x[i]), false, false);
             x[i] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
         }
-    if (log2 <= 5)
+    if (log2 <= 5 && lanes > 32)
 #pragma unroll
         for (int i = 0; i < N; ++i) {
             const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x[i]), __float_as_uint(x[i]), false, false);
@@ -213,10 +215,10 @@ __device__ __forceinline__ void add_lanes(float (&x)[N], int log2) {
         }
 }
 
-// Every lane of a position gets the sum over the groups.
+// The lanes of the first group get the sums over the groups, which took at most n entries.
 template <int VEC, int NV>
-__device__ __forceinline__ void sum_groups(int lpr_log2, float (&acc)[loads_per_row(NV)][VEC]) {
-    if constexpr (NV == 0) add_lanes(acc[0], lpr_log2);
+__device__ __forceinline__ void sum_groups(int lpr_log2, int n, float (&acc)[loads_per_row(NV)][VEC]) {
+    if constexpr (NV == 0) add_lanes(acc[0], lpr_log2, min(n, 64) << lpr_log2);
 }
 
 // Rows of fp32 in LDS or memory, VEC at a time (ANY: from the address of any element).

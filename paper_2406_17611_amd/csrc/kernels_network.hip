@@ -117,7 +117,7 @@ __device__ __forceinline__ void sum_rows(const S* src, int64_t pitch, int32_t c0
         batch(r, std::integral_constant<int, 2>{});
     else if (r < c1)
         batch(r, std::integral_constant<int, 1>{});
-    add_lanes(acc, lpe_log2);
+    add_lanes(acc, lpe_log2, min(c1 - c0, 64) << lpe_log2);
 }
 
 // Partial sum of a piece of a long range (hub nodes): a dense row of width floats, or k floats of summed products.
@@ -142,7 +142,7 @@ __device__ __forceinline__ void node_piece(const NodeArgs<T>& p, const SpmmItem&
     float acc[loads_per_row(NV)][VEC];
     clear(acc);
     gather_entries<T, VEC, NV>(p, it.row == 0 ? p.t_local : p.t_cross, it.e0, it.e1, lane, acc);
-    sum_groups<VEC, NV>(p.lpr_log2, acc);
+    sum_groups<VEC, NV>(p.lpr_log2, it.e1 - it.e0, acc);
     if (NV == 0 && lane >= (1 << p.lpr_log2)) return;
 #pragma unroll
     for (int m = 0; m < loads_per_row(NV); ++m) {
@@ -189,7 +189,7 @@ __global__ __launch_bounds__(kBlock) void node_sum_kernel(NodeArgs<T> p) {
         else
             gather_entries<T, VEC, NV>(p, p.t_cross, it.c0, it.c1, lane, acc);
     }
-    sum_groups<VEC, NV>(p.lpr_log2, acc);
+    sum_groups<VEC, NV>(p.lpr_log2, CROSS == kCrossFull ? it.l1 - it.l0 + (it.c1 - it.c0) : it.l1 - it.l0, acc);
     const int first = NV == 0 ? VEC * (lane & ((1 << p.lpr_log2) - 1)) : VEC * lane;     // first column of this lane
     if constexpr (CROSS == kCrossMasked) {
         if (cross) {
@@ -199,7 +199,7 @@ __global__ __launch_bounds__(kBlock) void node_sum_kernel(NodeArgs<T> p) {
                 add_partials<VEC, NV>(p.partial, width, it.c0, it.c1, lane, p.lpr_log2, far);
             else
                 gather_entries<T, VEC, NV>(p, p.t_cross, it.c0, it.c1, lane, far);
-            sum_groups<VEC, NV>(p.lpr_log2, far);
+            sum_groups<VEC, NV>(p.lpr_log2, it.c1 - it.c0, far);
             const MaskAffine ma = varco_affine(p.rule, it.gid);
 #pragma unroll
             for (int m = 0; m < NR; ++m) {

@@ -368,6 +368,7 @@ __device__ __forceinline__ void spmm_rows(const SpmmArgs<T>& p) {
 #pragma unroll
         for (int i = 0; i < VEC; ++i) acc[m][i] = 0.f;
     bool any_sparse = false;
+    int dense = 0;                      // entries of whole rows
     const uint32_t key0 = SPARSE ? varco_key0(p.rule) : 0u, key1 = SPARSE ? varco_key1(p.rule) : 0u;
 
     for (int32_t base = it.e0; base < it.e1; base += 64) {
@@ -386,6 +387,7 @@ __device__ __forceinline__ void spmm_rows(const SpmmArgs<T>& p) {
         const int cnt = min(64, it.e1 - base);
         const int ns = SPARSE ? __popcll(hmask) : 0;
         const int nd = cnt - ns;        // columns ascend within a row, so dense entries sit in lanes [0, nd)
+        dense += nd;
         gather_rows<T, VEC, NV, U, ANY>(addr, w, nd, width, lane, p.lpr_log2, acc);
         if constexpr (SPARSE) {
             if (ns > 0) {
@@ -399,7 +401,7 @@ __device__ __forceinline__ void spmm_rows(const SpmmArgs<T>& p) {
         }
     }
 
-    sum_groups<VEC, NV>(p.lpr_log2, acc);
+    sum_groups<VEC, NV>(p.lpr_log2, dense, acc);
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     if (NV == 0 && lane >= (1 << p.lpr_log2)) return;
 #pragma unroll
