@@ -197,11 +197,14 @@ hipError_t varco_launch_halo_grad(int dtype, const SpmmPlan& fwd_plan, const Spm
                                   const MaskRule& rule, void* prod, void* out, int32_t row_base, float* partial,
                                   hipStream_t stream, const LaunchTag& tag, const LaunchTag& sum_tag);
 
-// Elements between the rows of a product buffer of the library's own: k rounded up to whole 16-byte stores. (An odd k, as
-// compression schedules give, otherwise means element stores: 31 of 256 fp32 values per message, 1.75 million messages, 272 us
-// against 108.)
+// Elements between the rows of a product buffer of the library's own: k rounded up to whole 16-byte stores, and above 32 bytes to 64 bytes, so
+// that no row shares a 64-byte piece of memory with another: rows are written in row order and lie in node order, and a shared piece is written
+// twice, in parts. (An odd k, as compression schedules give, otherwise means element stores: 31 of 256 fp32 values per message, 1.75 million
+// messages, 272 us against 108. Whole steps with rows rounded to 16 bytes / to 64, us, 200,003 nodes, two hidden layers of 256 fp32: rows of 36 bytes
+// 1,798 / 1,719, 68 1,854 / 1,757, 132 2,032 / 1,919, 180 1,917 / 1,928, 260 2,274 / 2,157; of 512 bf16: 36 2,057 / 1,982, 68 2,104 / 2,000, 132
+// 2,285 / 2,163, 228 2,386 / 2,227. To 32 bytes: as 16 where that leaves half a piece. To 128 above 128: 1 % slower.)
 inline int32_t varco_product_pitch(const MaskRule& rule, int elem_bytes) {
-    const uint32_t unit = 16u / uint32_t(elem_bytes), up = (rule.k + unit - 1) / unit * unit;
+    const uint32_t unit = (rule.k * uint32_t(elem_bytes) > 32 ? 64u : 16u) / uint32_t(elem_bytes), up = (rule.k + unit - 1) / unit * unit;
     return int32_t(up <= rule.width ? up : rule.k);
 }
 // First pass of the product form: prod[prow[e] * pitch + j] = vals[e] * dm[row of e, pi_v(j)], j < k, for the halo entries of
