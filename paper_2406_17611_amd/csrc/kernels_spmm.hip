@@ -1101,13 +1101,14 @@ hipError_t spmm_t(const SpmmPlan& plan, const VarcoEdge* edge, const int32_t* co
             break;
         }
     }
-    // Numbers of kept elements that are no multiple of that (or rows at other addresses). fp32: two or four per lane only where an entry takes all
-    // lanes either way (65 elements and more): which entries share a private row, and with it the bits, stay. bf16: as above.
-    // One (two) per lane / this, us: fp32 50,021 nodes 200 wide, 67 kept, 107 / 76; bf16 2,449,029 nodes 100 wide, 25 kept, 3,544 / 3,076.
+    // Numbers of kept elements that are no multiple of that (or rows at other addresses): two or four per lane only where an entry takes all lanes either
+    // way (65 elements and more), so that the entries that share a private row, and with it the bits, stay. bf16 rows of odd lengths, whose dense sums
+    // have an order of their own here: as above. One per lane / this, us: 50,021 nodes 200 fp32 columns, 67 kept, 107 / 76. (For all bf16 rows: 2,449,029
+    // nodes of 100 columns, 25 kept, 3,544 / 3,076, but one rounding that falls otherwise decides gates of the layers behind it.)
     bool rem = false;
     if (halo && !full && !owners && vec > 1) {
         const int k = int(rule.k);
-        if (sizeof(T) == 4) {
+        if (sizeof(T) == 4 || !any) {
             const int wide = k <= 64 ? 1 : k <= 128 ? 2 : 4;
             rem = wide > ev && (ev == 1 || k > 128);
             if (rem) ev = wide;

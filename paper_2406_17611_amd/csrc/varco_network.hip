@@ -28,8 +28,18 @@ int32_t product_pitch(const varco_ctx* ctx, int32_t layer, int64_t k) {
     r.k = uint32_t(k), r.width = uint32_t(ctx->widths[layer]);
     return varco_product_pitch(r, ctx->elem_bytes());
 }
+// A message's products go to a place of their own, at least 35 to 48 ps each however few they are, and are read back: rows below some length are gathered whole.
+// Whole steps with products / with gathered rows, us, 8 partitions, widths 32-w-72-8, ratios 4 and 32:
+//   60,011 nodes of 60 neighbours   fp32 64 wide 557 / 474, 525 / 426, 96 664 / 568, 567 / 518, 128 674 / 637, 586 / 581, 160 wide, ratio 32, 641 / 694
+//                                   bf16 256 804 / 679, 720 / 618, 320 1,070 / 870, 806 / 737, 384 1,079 / 932, 840 / 816
+//   400,003 nodes of 50             fp32 64 2,913 / 2,695, 2,948 / 2,403, 96 3,450 / 3,314, 3,139 / 2,911, 128 3,466 / 3,701, 3,261 / 3,377
+//                                   bf16 256 3,949 / 3,832, 4,097 / 3,532, 320 5,311 / 4,751, 4,465 / 4,083, 384, ratio 8, 4,710 / 4,922
+// and with few entries to a row, where the pass of its own that forms the products costs more per entry:
+//   800,011 nodes of 12             fp32 128 3,945 / 3,810, 3,978 / 3,734, 192, ratio 8, 4,521 / 4,691    bf16 384 5,333 / 4,865, 4,950 / 4,517, 512 level
 bool products_pay(const varco_ctx* ctx, int32_t layer, int64_t k) {
-    return k > 0 && 3 * k < ctx->widths[layer] &&
+    const bool bf16 = ctx->dtype == VARCO_BF16, few = ctx->net.nnz_cross <= 16 * ctx->net.rows;
+    const int32_t gathered = bf16 ? (few ? 768 : 640) : (few ? 512 : 384);        // bytes of a row
+    return k > 0 && 3 * k < ctx->widths[layer] && ctx->widths[layer] * ctx->elem_bytes() > gathered &&
            double(ctx->net.nnz_cross) * product_pitch(ctx, layer, k) * ctx->elem_bytes() <= kProdBytes;
 }
 size_t prod_floats(const varco_ctx* ctx, int32_t layer, int64_t k) {
@@ -282,7 +292,7 @@ int32_t aggregate_fwd(varco_ctx* ctx, Workspace& ws, int32_t layer, const MaskRu
         extra = double(net.boundary) * rule.k * es;
         for (int i = 0; i < with_z->n; ++i) {
             const PrepJob& j = with_z->job[i];
-            extra += 4.0 * j.rows * j.cols + double(j.rows_padded) * (2.0 * j.pitch * (j.terms == kHalfTerms ? 2 : j.terms) + (j.terms == kHalfTerms ? 4.0 : 0.0));
+            extra += 4.0 * j.rows * j.cols + double(j.rows_padded) * (2.0 * j.pitch * (j.terms == kHalfTerms ? 2 : j.terms == kExactTerms ? 3 : j.terms) + (j.terms == kHalfTerms ? 4.0 : 0.0));
         }
     }
     const double entries = double(net.nnz) * 8.0 + (double(net.rows) + 1.0) * 4.0;
