@@ -1,7 +1,8 @@
-// The dense transform of eq. (2) in fp32 matrix instructions, act(M H + X H0), for rows of any length up to 256 (fp32 storage whose input width is
-// no multiple of 4). The instructions, their operands and their order are those of gemm_kernel in kernels_gemm.hip, so the bits are: a tile of 16
-// reduction steps is eight instructions, the t-th of which multiplies steps t and 8 + t, and the second tap follows in the same accumulators.
-// (A ReLU whose argument is within rounding of zero decides as it always did.)
+// The dense transform of eq. (2) in fp32 matrix instructions, act(M H + X H0), for rows of any length up to 256: fp32 storage whose input width is no
+// multiple of 4, and, where the caller asks for fp32 instructions (varco_set_matmul_terms), any. The instructions, their operands and their order are those
+// of gemm_kernel in kernels_gemm.hip, so the bits are: a tile of 16 reduction steps is eight instructions, the t-th of which multiplies steps t and 8 + t,
+// and the second tap follows in the same accumulators. Which of the two kernels takes a call depends on its number of rows (varco_gemm_rows_usable), and a
+// row's result must not.
 //
 // A wavefront keeps 32 columns of the weights in registers, both taps', for all the rows that its workgroup walks over. Blocks of 32 rows come 16 lanes
 // to a row, from any 4-byte address, one block ahead in registers, and lie in LDS as [tile][row][16 steps], the 16-byte pieces of every fourth row
@@ -11,6 +12,8 @@
 // launches by one block's chain. gemm_kernel's tiles of 128 rows x 128 columns in stages of 16 steps / this, us:
 //   3,000 rows 218 -> 48 34.2 / 9.6, 130 -> 256 22.3 / 8.5, two taps 233 -> 160 59.9 / 16.5     20,000 rows two taps 55 -> 160 29.4 / 17.6
 //   50,021 rows two taps 75 -> 200 64 / 50     200,000 rows 218 -> 160 264 / 186, 130 -> 256 192 / 154, two taps 233 -> 256 533 / 508, 55 -> 256 173 / 142
+// and rows of aligned length: 3,000 rows 64 -> 128 12.0 / 6.1, 256 -> 256 29 / 11     50,021 rows 100 -> 256 45 / 33, two taps 128 -> 256 91 / 72
+//   200,000 rows 128 -> 256 147 / 122, 256 -> 256 257 / 220     1,000,000 rows 100 -> 40 200 / 143, 256 -> 512 2,341 / 2,097
 // (Blocks of 64 rows, two accumulators: fewer wavefronts, 50,021 rows 75; the next block's loads and LDS writes among the products, two buffers:
 // two taps of 233 steps 490 instead of 508, two-wavefront workgroups lose by the LDS.)
 #include <algorithm>
@@ -58,7 +61,7 @@ __global__ __launch_bounds__(64 * WAVES, resident(J * TAPS)) void rows_kernel(Ro
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // the groups of one range of rows follow one another on one XCD: the rows come into a single L2
     const int32_t xcd = blockIdx.x & 7, within = blockIdx.x >> 3;
-    const int32_t first = (within / g.groups) * 8 + xcd, n_blocks = (g.m + kRows - 1) / kRows;
+    const int32_t first = (within / g.groups) * 8 + xcd, n_blocks = (g.m + kRows - 1) / kRows, whole = g.m / kRows;
     if (first >= n_blocks || first >= g.stride) return;         // whole workgroup
     const int32_t n0 = ((within % g.groups) * WAVES + (wave + first) % WAVES) * kColumns;       // (a wavefront without columns: on every SIMD in turn)
     const bool mine = n0 < g.n;
@@ -152,22 +155,31 @@ __global__ __launch_bounds__(64 * WAVES, resident(J * TAPS)) void rows_kernel(Ro
         if (mine) {
             // a lane holds a row's columns 8 q + 4 lk .. + 3
             float* const c = g.c + (int64_t(block) * kRows + l32) * g.ldc + n0 + 4 * lk;
-            const bool inside = (block + 1) * kRows <= g.m && n0 + kColumns <= g.n;
+            auto put4 = [&](float* dst, floatx4 o) __attribute__((always_inline)) {
+                o += g.accumulate ? floatx4(*reinterpret_cast<const any4*>(dst)) : floatx4{0.f, 0.f, 0.f, 0.f};
+                if (g.relu) o = floatx4{fmaxf(o[0], 0.f), fmaxf(o[1], 0.f), fmaxf(o[2], 0.f), fmaxf(o[3], 0.f)};
+                *reinterpret_cast<any4*>(dst) = o;
+            };
+            const bool inside = block < whole && n0 + kColumns <= g.n;
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                floatx4 o = {acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]};
+                const floatx4 o = {acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]};
                 float* const dst = c + 8 * q;
+                const int32_t left = g.n - (n0 + 8 * q + 4 * lk);       // columns from this lane's first one on
                 if (inside) {
-                    o += g.accumulate ? floatx4(*reinterpret_cast<const any4*>(dst)) : floatx4{0.f, 0.f, 0.f, 0.f};
-                    if (g.relu) o = floatx4{fmaxf(o[0], 0.f), fmaxf(o[1], 0.f), fmaxf(o[2], 0.f), fmaxf(o[3], 0.f)};
-                    *reinterpret_cast<any4*>(dst) = o;
-                } else if (block * kRows + l32 < g.m) {
+                    put4(dst, o);
+                } else if (block < whole || l32 < g.m - whole * kRows) {
+                    // (element by element only what is left of a row: 500,009 rows 31 -> 30 36 us instead of 46, 17 -> 63 43 / 66)
+                    if (left >= 4) {
+                        put4(dst, o);
+                    } else {
 #pragma unroll
-                    for (int v = 0; v < 4; ++v)
-                        if (n0 + 8 * q + 4 * lk + v < g.n) {
-                            const float s = o[v] + (g.accumulate ? dst[v] : 0.f);
-                            dst[v] = g.relu ? fmaxf(s, 0.f) : s;
-                        }
+                        for (int v = 0; v < 3; ++v)
+                            if (v < left) {
+                                const float s = o[v] + (g.accumulate ? dst[v] : 0.f);
+                                dst[v] = g.relu ? fmaxf(s, 0.f) : s;
+                            }
+                    }
                 }
             }
         }
@@ -193,14 +205,23 @@ bool varco_gemm_rows_usable(const GemmArgs& ga) {
     if (ga.k2 > 0 && (ga.k2 != ga.k || ga.a2.ld != ga.a.ld || ga.b2.ld != ga.b.ld || ga.a2.dtype != VARCO_F32 || ga.b2.dtype != VARCO_F32 || ga.a2.transposed ||
                       ga.b2.transposed || ga.a2.gate || ga.b2.gate))
         return false;
-    // The tiles of gemm_kernel are ahead (us, there / here):
-    // few products for a result that no cache holds: 1,000,000 rows 17 -> 64 97 / 121, 17 -> 256 305 / 387, 33 -> 256 389 / 399, but 63 -> 256 495 / 410
-    // and 200,000 rows 17 -> 256 64 / 48
-    if (ga.k2 == 0 && ga.k <= 48 && int64_t(ga.m) * ga.n * 4 > (int64_t(240) << 20)) return false;
-    // one wavefront to a SIMD and rows fetched three times or more: 200,000 rows two taps 233 -> 384 747 / 779, 512 950 / 959, but 320 735 / 647 and
-    // 20,000 rows 384 103 / 91
-    const int32_t pieces = (ga.k + kPiece - 1) / kPiece * (ga.k2 > 0 ? 2 : 1);
-    return pieces <= 4 || waves_of(ga.n) == 2 || ga.n <= 256 || ga.m < 100'000;
+    // Where the tiles of gemm_kernel are ahead (us, there / here; rows of aligned length come here with fp32 instructions on request only):
+    // few steps, once rows and results are more than the 256 MiB that the last cache holds: 1,000,000 rows 31 -> 47 98 / 119, 1,250,003 rows 15 -> 44
+    // 97 / 114, 17 -> 47 121 / 142, two taps 16 -> 64 92 / 126, but 1,000,000 rows 17 -> 44 84 / 56, 33 -> 47 126 / 115, and 700,001 rows 31 -> 47 67 / 57;
+    // results that no cache holds: 1,000,000 rows 17 -> 256 305 / 387, 33 -> 256 389 / 399, but 63 -> 256 495 / 410 and 200,000 rows 17 -> 256 64 / 48
+    const bool two = ga.k2 > 0, aligned = ga.k % 4 == 0 && ga.a.ld % 4 == 0 && (reinterpret_cast<uintptr_t>(ga.a.ptr) & 15u) == 0;
+    const int64_t out = int64_t(ga.m) * ga.n * 4, bytes = out + int64_t(ga.m) * ga.k * (two ? 8 : 4);
+    if (ga.k <= (two ? 16 : 32) && bytes > (int64_t(256) << 20)) return false;
+    if (!two && ga.k <= 48 && out > (int64_t(240) << 20)) return false;
+    // few steps and rows fetched by four groups: 100,003 rows 17 -> 512 61 / 66 (aligned 16 -> 512 46 / 67), but 384 50 / 35 and 50,021 rows 512 36 / 32
+    if (!two && ga.k <= 32 && ga.n > 384 && (aligned || ga.m > 64'000)) return false;
+    // one wavefront to a SIMD and four of them to a workgroup: two taps 200,000 rows 233 -> 384 747 / 779, 512 950 / 959, but 320 735 / 647 and 20,000
+    // rows 384 103 / 91; 1,000,003 rows 255 -> 200 2,354 / 2,450, 211 -> 256 2,073 / 2,140, but 193 -> 256 1,990 / 1,970 and 700,001 rows level; aligned
+    // ones earlier, 204 -> 200 1,846 / 2,045, 128 1,016 / 1,090, 200,003 rows 224 -> 256 477 / 495, but 192 -> 256 415 / 401
+    const int32_t pieces = (ga.k + kPiece - 1) / kPiece * (two ? 2 : 1);
+    if (pieces <= 4 || waves_of(ga.n) == 2) return true;
+    if (ga.n > 256 && ga.m >= 100'000) return false;
+    return !(ga.n > (aligned ? 64 : 128) && ga.k > (aligned ? 192 : 208) && ga.m > (aligned ? 150'000 : 800'000));
 }
 
 hipError_t varco_launch_gemm_rows(const GemmArgs& ga, hipStream_t stream, const LaunchTag& tag) {

@@ -70,3 +70,55 @@ def test_two_taps(n, fi, fo):
         assert (np.abs(got[:n][finite] - np.maximum(want, 0.0)) <= _bound(2, fi, size)).all()
         assert (got[n] == 7.0).all()
     net.ctx.close()
+
+
+def _bits(t):
+    return t.view(torch.int32)
+
+
+@pytest.mark.parametrize("fi,fo,n", [(17, 64, 991_003), (45, 47, 1_450_007), (16, 64, 991_003), (20, 30, 1_450_007)])
+@pytest.mark.parametrize("accumulate", [False, True])
+def test_bits_do_not_depend_on_the_number_of_rows(fi, fo, n, accumulate):
+    """So many rows that tiles of 256 x 64 take them (results or operands beyond the last cache), and ranges of them that wavefronts with the weights in
+    registers take, which start at any row: the same bits, added to what is there and through the ReLU as well."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(fi)
+    y, h = (torch.randn(*shape, generator=gen, device="cuda") for shape in ((n, fi), (fi, fo)))
+    old = torch.randn(n, fo, generator=gen, device="cuda")
+    ctx = vb.Context([fi, fo], [vb.ACT_RELU], vb.CONV_GCN, 1, KEY)
+    ctx.set_matmul_terms(3 if fi % 4 else 0)
+    ctx.prepare()
+    whole = old.clone()
+    ctx.transform_fwd(0, y, h, whole, accumulate, True)
+    for first, rows in ((0, 3001), (1, 33), (n - 40_007, 40_007)):
+        part = old[first:first + rows].clone()
+        ctx.transform_fwd(0, y[first:first + rows], h, part, accumulate, True)
+        assert torch.equal(_bits(part), _bits(whole[first:first + rows])), first
+    ctx.close()
+
+
+@pytest.mark.parametrize("fi,fo,terms", [(150, 384, 3), (161, 500, 3), (200, 384, 0)])
+def test_bits_of_two_taps_do_not_depend_on_the_columns(fi, fo, terms):
+    """A layer's two products of more than 256 columns and 100,000 rows, which tiles of 128 x 128 take, and the same columns by the wavefronts that keep
+    the weights, in units with and without a remainder."""
+    n = 100_013
+    graph = synth.small_random_graph(n, 2.0, "sage", seed=n)
+    host = vb.partition_build(graph.n, graph.rowptr, graph.colidx, graph.vals, synth.random_partition(graph.n, 2, seed=5), 2)
+    h1, h0 = (synth.glorot(fi, fo, 7, 1 + t).astype(np.float32) for t in range(2))
+    x0 = np.random.default_rng(fi).standard_normal((n, fi)).astype(np.float32)
+
+    def outputs(c0, c1):
+        net = PartitionedNetwork(host, (fi, c1 - c0, 4), "sage", 17, need_backward=False)      # (two layers: the first has a ReLU)
+        net.ctx.set_matmul_terms(terms)
+        net.set_inputs(x0)
+        narrow = np.zeros((c1 - c0, 4), dtype=np.float32)
+        net.set_weights([np.ascontiguousarray(h1[:, c0:c1]), narrow], [np.ascontiguousarray(h0[:, c0:c1]), narrow])
+        net.forward(1, (1, 0))
+        torch.cuda.synchronize()
+        out = net.x[1].clone()
+        net.ctx.close()
+        return out
+
+    whole = outputs(0, fo)
+    for c0, c1 in ((0, 256), (200, 247), (256, fo)):
+        assert torch.equal(_bits(whole[:, c0:c1]), _bits(outputs(c0, c1))), c0
