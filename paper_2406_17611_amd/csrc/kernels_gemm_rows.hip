@@ -169,7 +169,7 @@ __global__ __launch_bounds__(64 * WAVES, resident(J * TAPS)) void rows_kernel(Ro
                 if (inside) {
                     put4(dst, o);
                 } else if (block < whole || l32 < g.m - whole * kRows) {
-                    // (element by element only what is left of a row: 500,009 rows 31 -> 30 36 us instead of 46, 17 -> 63 43 / 66)
+                    // (element by element only what is left of a row: 500,009 rows 31 -> 30 36 us instead of 56, 17 -> 63 43 / 67)
                     if (left >= 4) {
                         put4(dst, o);
                     } else {
