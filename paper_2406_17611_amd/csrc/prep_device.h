@@ -102,16 +102,21 @@ __device__ __forceinline__ void prep_weights(const PrepJobs<CAP>& jobs, int32_t 
     const int64_t first = (int64_t(r / bn) * (jb.pitch / kPrepStage) + c / kPrepStage) * terms;
     const int32_t inside = (r % bn) * kPrepStage + c % kPrepStage;
     if (exact) {
-        // Cut, not rounded: every term has the sign of the value, and none but that of a zero is zero (2^-126 instead, beyond every sum's last
-        // bit), so that an infinite element of a row, or of the weights, gives the infinity or NaN that it gives in one product.
+        // Cut, not rounded: every term has the sign of the value, and none but that of a zero is zero (where one or two terms would do, the last of them is
+        // halved), so that an infinite element of a row, or of the weights, gives the infinity or NaN that it gives in one product. The terms add up to
+        // values of 2^-109 and more; below, bits under 2^-133 (the smallest bf16 number, which stands in for a zero term too) are lost: 2^-131 in all.
+        auto cut = [](float v) { return __uint_as_float(__float_as_uint(v) & 0xFFFF0000u); };
         const uint32_t sign = __float_as_uint(x) & 0x80000000u;
-        const bool some = x != 0.f;
+        const bool number = isfinite(x), some = x != 0.f;
+        float t[3] = {x != x ? __uint_as_float(0x7FC00000u) : cut(x)};                         // (a NaN whose upper bits say infinity)
+        const float rest = number ? x - t[0] : 0.f;
+        t[1] = cut(rest), t[2] = cut(rest - t[1]);
+        if (number && t[1] == 0.f) t[1] = t[0] = 0.5f * t[0];
+        if (number && t[2] == 0.f) t[2] = t[1] = 0.5f * t[1];
         for (int p = 0; p < 3; ++p) {
-            uint32_t t = __float_as_uint(x) & 0xFFFF0000u;
-            if (x != x) t = 0x7FC00000u;                                                   // (a NaN whose upper bits say infinity)
-            x = isinf(x) ? 0.f : x - __uint_as_float(t);
-            if (some && (t & 0x7FFFFFFFu) < 0x00800000u) t = sign | 0x00800000u;
-            out[(first + p) * bn * kPrepStage + inside] = uint16_t(t >> 16);
+            uint32_t u = __float_as_uint(t[p]) >> 16;
+            if (some && (u & 0x7FFFu) == 0u) u = sign >> 16 | 1u;
+            out[(first + p) * bn * kPrepStage + inside] = uint16_t(u);
         }
         return;
     }

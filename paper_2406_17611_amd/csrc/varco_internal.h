@@ -384,7 +384,7 @@ int64_t varco_gemm_half_tn_tiles(const GemmArgs& g);
 //   terms = 2, 3: the terms of the exact expansion, rows padded to rows_padded (a multiple of 128) and columns to pitch (a
 //   multiple of 32), stored by row tile and stage of 32 columns as the product kernel fetches it (kernels_gemm_split.hip);
 //   kHalfTerms: two scaled fp16 terms in the same order, then the rows' scale exponents (kernels_gemm_half.hip).
-//   kExactTerms: three bf16 terms of the value's sign that add up to it, stored as terms = 3.
+//   kExactTerms: three bf16 terms of the value's sign that add up to it (below 2^-109: to 2^-131), none of them zero, stored as terms = 3.
 struct PrepJob {
     const float* h;
     void* out;

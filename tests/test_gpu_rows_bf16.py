@@ -48,6 +48,37 @@ def test_transform(n, fi, fo):
     ctx.close()
 
 
+@pytest.mark.parametrize("fi,fo", [(9, 7), (75, 70), (130, 129)])
+def test_small_weights(fi, fo):
+    """Weights down to the smallest fp32 number, one scale to a column, against rows large enough that the products are not small. The terms add up to
+    what is 2^-109 or more; below, a weight is off by 2^-131 at most (bits under the smallest bf16 number, which stands in for zero terms too)."""
+    n = 257
+    rng = np.random.default_rng(fi)
+    y = torch.from_numpy((rng.standard_normal((n, fi)) * 2.0 ** 100).astype(np.float32)).to(torch.bfloat16)
+    exponent = -100.0 - 46.0 * np.arange(fo) / (fo - 1)
+    h = (synth.glorot(fi, fo, 3, 1).astype(np.float64) * np.exp2(np.round(exponent))).astype(np.float32)
+    few = rng.random((fi, fo))
+    h = np.where(few < 0.3, np.sign(h) * np.exp2(np.round(exponent)), h).astype(np.float32)              # (one bit)
+    h = np.where(few > 0.7, (h.view(np.uint32) & 0xFFFFF000).view(np.float32), h)                          # (two terms)
+    ctx = vb.Context([fi, fo], [vb.ACT_IDENTITY], vb.CONV_GCN, 1, KEY, vb.BF16)
+    ctx.prepare()
+    out = torch.zeros(n, fo, device="cuda", dtype=torch.bfloat16)
+    ctx.transform_fwd(0, y.cuda(), dev(h), out, False, False)
+    torch.cuda.synchronize()
+    a, b = y.double().numpy(), h.astype(np.float64)
+    want, size, got = a @ b, np.abs(a) @ np.abs(b), out.double().cpu().numpy()
+    half = np.exp2(np.floor(np.log2(np.maximum(np.abs(want), np.abs(got)) + 2.0 ** -120)) - 8)
+    lost = np.abs(a) @ np.where((np.abs(b) < 2.0 ** -109) & (b != 0.0), 2.0 ** -131, 0.0)
+    assert (np.abs(got - want) <= half + 4 * 2.0 ** -24 * np.sqrt(3 * fi + 1) * size + lost).all()
+    y[3, 2] = float("inf")
+    ctx.transform_fwd(0, y.cuda(), dev(h), out, False, False)
+    torch.cuda.synchronize()
+    got = out.double().cpu().numpy()
+    some = h[2] != 0.0
+    assert (got[3][some] == np.copysign(np.inf, h[2][some])).all() and np.isnan(got[3][~some]).all()
+    ctx.close()
+
+
 def test_values_that_are_not_finite():
     """Infinite elements and weights give what one product of fp32 numbers gives, and stay in their row and column."""
     n, fi, fo = 300, 75, 70
