@@ -36,9 +36,18 @@ int32_t product_pitch(const varco_ctx* ctx, int32_t layer, int64_t k) {
 //                                   bf16 256 3,949 / 3,832, 4,097 / 3,532, 320 5,311 / 4,751, 4,465 / 4,083, 384, ratio 8, 4,710 / 4,922
 // and with few entries to a row, where the pass of its own that forms the products costs more per entry:
 //   800,011 nodes of 12             fp32 128 3,945 / 3,810, 3,978 / 3,734, 192, ratio 8, 4,521 / 4,691    bf16 384 5,333 / 4,865, 4,950 / 4,517, 512 level
+// Between them the line of 16 entries is on the safe side (200,003 nodes, ratios 4 and 32): of 24 neighbours fp32 128 1,264 / 1,235, 1,205 / 1,186, bf16 384
+// 1,863 / 1,670, 1,591 / 1,527; of 36 fp32 96 1,429 / 1,346, 1,340 / 1,232, 128 1,463 / 1,492, 1,408 / 1,409, bf16 320 2,220 / 1,924, 1,853 / 1,685.
+// Rows whose length is no multiple of 4 are gathered one element to a lane (node_sum_kernel), a product's row is read by wide loads whatever the width:
+// the lines lie lower. Ratios 4, 8 and 32:
+//   400,003 nodes of 50             fp32 75 3,505 / 3,438, 3,116 / 3,229, 3,166 / 2,980, 95 3,587 / 3,702, 3,210 / 3,525, 3,246 / 3,244
+//                                   bf16 251 4,624 / 4,702, 4,436 / 4,379, 4,468 / 4,166, 319 5,753 / 5,575, 5,101 / 5,296, 4,887 / 5,002
+//   200,003 nodes of 36             fp32 95 1,512 / 1,487, 1,390 / 1,436, 1,377 / 1,365    bf16 251 2,005 / 1,939, 1,928 / 1,835, 1,866 / 1,754
+//   60,011 nodes of 12              fp32 127 445 / 426, 429 / 414, 397 / 406               bf16 319 619 / 557, 563 / 556, 506 / 537
 bool products_pay(const varco_ctx* ctx, int32_t layer, int64_t k) {
     const bool bf16 = ctx->dtype == VARCO_BF16, few = ctx->net.nnz_cross <= 16 * ctx->net.rows;
-    const int32_t gathered = bf16 ? (few ? 768 : 640) : (few ? 512 : 384);        // bytes of a row
+    const bool odd = ctx->widths[layer] % 4 != 0;
+    const int32_t gathered = bf16 ? (odd ? 512 : few ? 768 : 640) : (few ? 512 : odd ? 320 : 384);        // bytes of a row
     return k > 0 && 3 * k < ctx->widths[layer] && ctx->widths[layer] * ctx->elem_bytes() > gathered &&
            double(ctx->net.nnz_cross) * product_pitch(ctx, layer, k) * ctx->elem_bytes() <= kProdBytes;
 }

@@ -39,6 +39,17 @@ def dev(a, dtype=None):
     return t.cuda()
 
 
+def products_taken(ctx, run):
+    """Whether run(), backward passes of linked partitions, formed the products of cross entries (kernel class agg_bwd_halo)."""
+    ctx.profile_enable(True)
+    ctx.profile_read()
+    run()
+    torch.cuda.synchronize()
+    taken = ctx.profile_read()["agg_bwd_halo"]["launches"] > 0
+    ctx.profile_enable(False)
+    return taken
+
+
 def hub_graph(n, n_hubs, hub_deg, avg_deg, conv, seed):
     """Random graph with a few very high-degree nodes, so that rows longer than the kernels' chunk
     length (split rows) and many short rows occur together."""
