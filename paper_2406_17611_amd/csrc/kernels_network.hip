@@ -268,7 +268,7 @@ using Int = std::integral_constant<int, N>;
 
 template <typename T>
 hipError_t node_sum_t(const NodePlan& plan, const uint2* t_local, const uint2* t_cross, const void* dm, const void* prod,
-                      const MaskRule& rule, VarcoCross cross, void* out, bool add_old, float* partial, hipStream_t stream,
+                      int32_t pitch, const MaskRule& rule, VarcoCross cross, void* out, bool add_old, float* partial, hipStream_t stream,
                       const LaunchTag& tag) {
     NodeArgs<T> a;
     a.pieces = plan.pieces, a.n_pieces = plan.n_pieces;
@@ -289,7 +289,7 @@ hipError_t node_sum_t(const NodePlan& plan, const uint2* t_local, const uint2* t
     int nv = a.lpr_log2 < 6 ? 0 : 1;
     while (nv && nv * 64 < per_row) nv <<= 1;
     if (nv > 8) return hipErrorInvalidValue;
-    a.pitch = varco_product_pitch(rule, int(sizeof(T)));
+    a.pitch = pitch;
     int ev = 1;
     if (cross == kCrossProducts)
         for (int c : {int(16 / sizeof(T)), int(8 / sizeof(T)), 2})
@@ -466,11 +466,11 @@ dim3 blocks_for(int64_t n) { return dim3(unsigned((n + kBlock - 1) / kBlock)); }
 }  // namespace
 
 hipError_t varco_launch_node_sum(int dtype, const NodePlan& plan, const uint2* t_local, const uint2* t_cross, const void* dm,
-                                 const void* prod, const MaskRule& rule, VarcoCross cross, void* out, bool add_old, float* partial,
-                                 hipStream_t stream, const LaunchTag& tag) {
+                                 const void* prod, int32_t pitch, const MaskRule& rule, VarcoCross cross, void* out, bool add_old,
+                                 float* partial, hipStream_t stream, const LaunchTag& tag) {
     if (plan.n_nodes == 0) return hipSuccess;
-    return dtype == VARCO_BF16 ? node_sum_t<bf16_t>(plan, t_local, t_cross, dm, prod, rule, cross, out, add_old, partial, stream, tag)
-                               : node_sum_t<float>(plan, t_local, t_cross, dm, prod, rule, cross, out, add_old, partial, stream, tag);
+    return dtype == VARCO_BF16 ? node_sum_t<bf16_t>(plan, t_local, t_cross, dm, prod, pitch, rule, cross, out, add_old, partial, stream, tag)
+                               : node_sum_t<float>(plan, t_local, t_cross, dm, prod, pitch, rule, cross, out, add_old, partial, stream, tag);
 }
 
 hipError_t varco_launch_link_halo(const LinkPartition& p, int32_t* halo_len, int32_t* halo_gid, int32_t* halo_zrow, hipStream_t stream) {

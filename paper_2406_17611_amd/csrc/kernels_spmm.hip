@@ -609,7 +609,7 @@ struct ProductArgs {
     const T* dm;                // n_local x width
     MaskRule rule;
     T* prod;                    // (halo entries) x pitch, in the storage type
-    int32_t pitch;              // elements per row: k, or k rounded up to whole 16-byte stores (see varco_product_pitch)
+    int32_t pitch;              // elements per row: k, or k rounded up to whole 16-byte or 64-byte pieces (see varco_product_pitch)
     int32_t ku;                 // stores per entry = k / (elements per store)
     int32_t lpe_log2;           // lanes per entry
 };

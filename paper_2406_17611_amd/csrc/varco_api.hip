@@ -346,14 +346,22 @@ int32_t size_workspace(varco_ctx* ctx, Workspace& ws) {
     VARCO_HIP(ctx, grow(ws, ws.gemm, ws.gemm_elems, ctx->need_gemm + tf_shares));
     VARCO_HIP(ctx, grow(ws, ws.w, ws.w_elems, ctx->need_w));
     VARCO_HIP(ctx, grow(ws, ws.loss, ws.loss_elems, size_t(2) * kLossBlocks));
-    size_t most = 0, network_most = 0;
+    size_t most = 0;
     const size_t prod = prod_need(ctx, &most);
-    // the block's product buffer is an option (without it whole rows are gathered): a device that has no room for it goes on without
-    const size_t network = ctx->net.linked ? network_prod_need(ctx, &network_most) : 0;
-    if (network <= prod || grow_products(ws, network, std::max(most, network_most)) != hipSuccess) {
-        (void)hipGetLastError();
-        VARCO_HIP(ctx, grow_products(ws, prod, std::max(most, network_most)));
-    }
+    // the block's product buffer is an option: a device that has no room for rows of whole 64-byte pieces takes shorter ones, or goes on without
+    // (whole rows are gathered then)
+    bool room = false;
+    for (const bool whole : {true, false})
+        if (ctx->net.linked && !room) {
+            size_t network_most = 0;
+            const size_t network = network_prod_need(ctx, whole, &network_most);
+            if (whole && network >= ws.prod_refused) continue;          // (what was refused once is not tried, and the buffer given up for it, again)
+            most = std::max(most, network_most);
+            room = network <= prod || grow_products(ws, network, most) == hipSuccess;
+            if (!room) (void)hipGetLastError();
+            if (!room && whole) ws.prod_refused = network;
+        }
+    VARCO_HIP(ctx, grow_products(ws, prod, most));
     bool narrow = false;
     for (int32_t l = 0; l < ctx->n_layers; ++l) narrow = narrow || (ctx->net.linked && narrow_sums_possible(ctx, l));
     // (an option like the products: without these rows errors are summed at the width of the inputs)

@@ -66,6 +66,7 @@ struct Workspace {
     float* spmm = nullptr;      size_t spmm_elems = 0;      // partial rows of split CSR rows
     float* gemm = nullptr;      size_t gemm_elems = 0;      // split-K partial products
     float* prod = nullptr;      size_t prod_elems = 0;      // halo-gradient products: (halo entries) x k elements
+    size_t prod_refused = SIZE_MAX;     // floats of rows of whole 64-byte pieces that the device had no room for
     float* w = nullptr;         size_t w_elems = 0;         // converted copies of the weights, one slot per (layer, weight, orientation)
     float* tf = nullptr;        size_t tf_elems = 0;        // transform-first layers: [Y_loc ; Y_halo], (n_local + n_halo) x width[l+1]
     float* hrows = nullptr;     size_t hrows_elems = 0;     // and one record (two words) per halo row
@@ -129,7 +130,7 @@ MaskRule full_rule(int32_t width);
 void free_plan(SpmmPlan& p);
 void free_network(NetState& net);
 // Floats of a workspace's product buffer that the calls on all partitions ask for at the current ratios, and at most at any.
-size_t network_prod_need(const varco_ctx* ctx, size_t* most);
+size_t network_prod_need(const varco_ctx* ctx, bool whole, size_t* most);
 // Whether the input gradient of layer l can be formed from errors summed at the width of its outputs, and the workspace's
 // floats for the rows of a class layer over all partitions: [Y ; Y_z], or dZ, G_loc and G_z (two_terms: each sum as two bf16 numbers).
 bool narrow_sums_possible(const varco_ctx* ctx, int32_t l);

@@ -202,9 +202,10 @@ hipError_t varco_launch_halo_grad(int dtype, const SpmmPlan& fwd_plan, const Spm
 // twice, in parts. (An odd k, as compression schedules give, otherwise means element stores: 31 of 256 fp32 values per message, 1.75 million
 // messages, 272 us against 108. Whole steps with rows rounded to 16 bytes / to 64, us, 200,003 nodes, two hidden layers of 256 fp32: rows of 36 bytes
 // 1,798 / 1,719, 68 1,854 / 1,757, 132 2,032 / 1,919, 180 1,917 / 1,928, 260 2,274 / 2,157; of 512 bf16: 36 2,057 / 1,982, 68 2,104 / 2,000, 132
-// 2,285 / 2,163, 228 2,386 / 2,227. To 32 bytes: as 16 where that leaves half a piece. To 128 above 128: 1 % slower.)
-inline int32_t varco_product_pitch(const MaskRule& rule, int elem_bytes) {
-    const uint32_t unit = (rule.k * uint32_t(elem_bytes) > 32 ? 64u : 16u) / uint32_t(elem_bytes), up = (rule.k + unit - 1) / unit * unit;
+// 2,285 / 2,163, 228 2,386 / 2,227. To 32 bytes: as 16 where that leaves half a piece. To 128 above 128: 1 % slower.) The buffer grows by up to 1.8 times
+// (a third beyond the next 16 bytes); `whole` false, to 16 bytes, where that leaves no room for it. The sums are the same either way.
+inline int32_t varco_product_pitch(const MaskRule& rule, int elem_bytes, bool whole) {
+    const uint32_t unit = (whole && rule.k * uint32_t(elem_bytes) > 32 ? 64u : 16u) / uint32_t(elem_bytes), up = (rule.k + unit - 1) / unit * unit;
     return int32_t(up <= rule.width ? up : rule.k);
 }
 // First pass of the product form: prod[prow[e] * pitch + j] = vals[e] * dm[row of e, pi_v(j)], j < k, for the halo entries of
@@ -213,12 +214,12 @@ hipError_t varco_launch_halo_products(int dtype, const SpmmPlan& fwd_plan, const
                                       const void* dm, const MaskRule& rule, void* prod, int32_t pitch, hipStream_t stream, const LaunchTag& tag);
 
 // How the cross entries of varco_launch_node_sum are taken: not at all (k = 0); summed from the product buffer (rows of
-// varco_product_pitch elements, already weighted); gathered as whole rows of dm and kept only at the node's positions; gathered as whole rows (k = width).
+// `pitch` elements, already weighted); gathered as whole rows of dm and kept only at the node's positions; gathered as whole rows (k = width).
 enum VarcoCross { kCrossNone = 0, kCrossProducts = 1, kCrossMasked = 2, kCrossFull = 3 };
 // out[row, :] (+)= sum of local entries + cross entries for every node of the plan (see NodeItem). partial: one
 // width-float row per piece.
 hipError_t varco_launch_node_sum(int dtype, const NodePlan& plan, const uint2* t_local, const uint2* t_cross, const void* dm,
-                                 const void* prod, const MaskRule& rule, VarcoCross cross, void* out, bool add_old, float* partial,
+                                 const void* prod, int32_t pitch, const MaskRule& rule, VarcoCross cross, void* out, bool add_old, float* partial,
                                  hipStream_t stream, const LaunchTag& tag);
 
 // Set-up kernels of the network block (kernels_network.hip); *flags collects VARCO_BAD_* bits.

@@ -23,10 +23,12 @@ constexpr int64_t kPartialElems = int64_t(1) << 30;
 
 // Products of k values per cross entry are written and read back (2 k elements at about 4.8 TB/s), or whole rows are
 // gathered (width elements at about 7 TB/s).
-int32_t product_pitch(const varco_ctx* ctx, int32_t layer, int64_t k) {
+// (Rows of whole 64-byte pieces, `whole`, only where the buffer then stays within its limit.)
+int32_t product_pitch(const varco_ctx* ctx, int32_t layer, int64_t k, bool whole) {
     MaskRule r{};
     r.k = uint32_t(k), r.width = uint32_t(ctx->widths[layer]);
-    return varco_product_pitch(r, ctx->elem_bytes());
+    const int32_t pitch = varco_product_pitch(r, ctx->elem_bytes(), whole);
+    return whole && double(ctx->net.nnz_cross) * pitch * ctx->elem_bytes() > kProdBytes ? varco_product_pitch(r, ctx->elem_bytes(), false) : pitch;
 }
 // A message's products go to a place of their own, at least 35 to 48 ps each however few they are, and are read back: rows below some length are gathered whole.
 // Whole steps with products / with gathered rows, us, 8 partitions, widths 32-w-72-8, ratios 4 and 32:
@@ -49,10 +51,10 @@ bool products_pay(const varco_ctx* ctx, int32_t layer, int64_t k) {
     const bool odd = ctx->widths[layer] % 4 != 0;
     const int32_t gathered = bf16 ? (odd ? 512 : few ? 768 : 640) : (few ? 512 : odd ? 320 : 384);        // bytes of a row
     return k > 0 && 3 * k < ctx->widths[layer] && ctx->widths[layer] * ctx->elem_bytes() > gathered &&
-           double(ctx->net.nnz_cross) * product_pitch(ctx, layer, k) * ctx->elem_bytes() <= kProdBytes;
+           double(ctx->net.nnz_cross) * product_pitch(ctx, layer, k, false) * ctx->elem_bytes() <= kProdBytes;
 }
-size_t prod_floats(const varco_ctx* ctx, int32_t layer, int64_t k) {
-    return (size_t(ctx->net.nnz_cross) * size_t(product_pitch(ctx, layer, k)) * size_t(ctx->elem_bytes()) + 3) / 4;
+size_t prod_floats(const varco_ctx* ctx, int32_t layer, int64_t k, bool whole) {
+    return (size_t(ctx->net.nnz_cross) * size_t(product_pitch(ctx, layer, k, whole)) * size_t(ctx->elem_bytes()) + 3) / 4;
 }
 
 // Split of a weight gradient's reduction over the arena's rows: whole rounds of resident workgroups, at least two
@@ -327,16 +329,17 @@ int32_t aggregate_bwd(varco_ctx* ctx, Workspace& ws, int32_t layer, const MaskRu
     const double es = ctx->elem_bytes();
     const int32_t fi = ctx->widths[layer];
     VarcoCross cross = net.nnz_cross == 0 || rule.k == 0 ? kCrossNone : rule.k == rule.width ? kCrossFull : kCrossMasked;
-    if (cross == kCrossMasked && products_pay(ctx, layer, rule.k) && prod_floats(ctx, layer, rule.k) <= ws.prod_elems) {
+    const bool whole = prod_floats(ctx, layer, rule.k, true) <= ws.prod_elems;
+    const int32_t pitch = product_pitch(ctx, layer, rule.k, whole);
+    if (cross == kCrossMasked && products_pay(ctx, layer, rule.k) && (whole || prod_floats(ctx, layer, rule.k, false) <= ws.prod_elems)) {
         cross = kCrossProducts;
         const double bytes = double(net.nnz_cross) * 8.0 + double(net.rows) * fi * es;
-        VARCO_HIP(ctx, varco_launch_halo_products(ctx->dtype, net.fwd, net.edges, net.vals, net.prow, dm, rule, ws.prod,
-                                                  product_pitch(ctx, layer, rule.k), st,
+        VARCO_HIP(ctx, varco_launch_halo_products(ctx->dtype, net.fwd, net.edges, net.vals, net.prow, dm, rule, ws.prod, pitch, st,
                                                   ctx->tag(VARCO_K_AGG_BWD_HALO, bytes, 0)));
     }
     const double bytes = double(net.nnz_local) * 8.0 + (double(net.rows) + 1.0) * 4.0 + 2.0 * double(net.rows) * fi * es;
     const double stream = double(net.nnz_local) * (8.0 + fi * es) + (double(net.rows) + 1.0) * 4.0 + double(net.rows) * fi * es;
-    VARCO_HIP(ctx, varco_launch_node_sum(ctx->dtype, net.nodes, net.t_local, net.t_cross, dm, ws.prod, rule, cross, dx, add_old, ws.spmm, st,
+    VARCO_HIP(ctx, varco_launch_node_sum(ctx->dtype, net.nodes, net.t_local, net.t_cross, dm, ws.prod, pitch, rule, cross, dx, add_old, ws.spmm, st,
                                          ctx->tag(VARCO_K_AGG_BWD_LOCAL, bytes, 0, stream)));
     if (rule.k > 0) {
         ctx->stats.bwd_elems[layer] += net.halo_rows * rule.k;
@@ -788,14 +791,14 @@ int32_t tap_prologue(varco_ctx* ctx, int32_t tap, varco_stream stream, const cha
 
 }  // namespace
 
-size_t varco::network_prod_need(const varco_ctx* ctx, size_t* most) {
+size_t varco::network_prod_need(const varco_ctx* ctx, bool whole, size_t* most) {
     size_t need = 0;
     *most = 0;
     for (int32_t l = 1; l < ctx->n_layers; ++l) {     // the first layer's input needs no gradient
-        if (products_pay(ctx, l, ctx->layers[l].k)) need = std::max(need, prod_floats(ctx, l, ctx->layers[l].k));
+        if (products_pay(ctx, l, ctx->layers[l].k)) need = std::max(need, prod_floats(ctx, l, ctx->layers[l].k, whole));
         int64_t k = (ctx->widths[l] - 1) / 3;
         while (k > 0 && !products_pay(ctx, l, k)) --k;
-        if (k > 0) *most = std::max(*most, prod_floats(ctx, l, k));
+        if (k > 0) *most = std::max(*most, prod_floats(ctx, l, k, whole));
     }
     return need;
 }

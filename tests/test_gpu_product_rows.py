@@ -1,9 +1,11 @@
 """Rows of the product buffer on both sides of the sizes that they are rounded up to (16 bytes, 32, 64 and more), and rows on both sides of the length below
 which they are gathered whole instead, with few neighbours and with many."""
 import pytest
+import torch
 
 from gpu_common import hub_graph, products_taken
 from paper_2406_17611_amd import synth
+from test_gpu_graph import _network, _snapshot
 from test_gpu_network import BF16_TOL, _compare_network
 
 pytestmark = pytest.mark.gpu
@@ -38,3 +40,38 @@ def test_rows_gathered_or_not(dtype, width, degree):
 def test_lines_of_the_form(dtype, width, degree, products):
     """Rows of odd lengths are gathered an element to a lane, so products are formed from shorter ones on."""
     _check(dtype, width, 7, degree, products)
+
+
+def test_rows_of_less_than_64_bytes_where_the_device_is_full():
+    """Rows of 36 bytes take 64 bytes each, 4 million of them 244 MiB; on a device that has no room for that, 48 bytes and 183 MiB. The sums are the same."""
+    n, ratio = 60_000, (256, 9)
+    g = synth.gcn_operator(n, *synth.chung_lu_edges(n, 3_000_000, 2.5, 5))
+    part = synth.random_partition(n, 3, seed=6)
+    got = []
+    for room in (None, 212 << 20):
+        net = _network(g, part, 3, (8, 256, 72, 4), "gcn", 1)
+        entries = net.nnz_total - sum(int(hp.t_rowptr[hp.n_local]) for hp in net.host_parts)
+        assert 64 * entries > 240 << 20 and 48 * entries < 184 << 20
+        net.step(4, (1, 1))
+        torch.cuda.synchronize()
+        torch.cuda.empty_cache()
+        filler = []
+        try:
+            while room and (left := torch.cuda.mem_get_info()[0] - room) >= 8 << 20:
+                while left >= 8 << 20:                       # what cannot be had in one piece is taken in smaller ones
+                    try:
+                        filler.append(torch.empty(left, dtype=torch.uint8, device="cuda"))
+                        break
+                    except torch.OutOfMemoryError:
+                        left //= 2
+                else:
+                    break
+            assert products_taken(net.ctx, lambda: (net.zero_grads(), net.step(5, ratio)))
+            got.append(_snapshot(net))
+        finally:
+            filler.clear()
+            torch.cuda.empty_cache()
+        net.ctx.close()
+        del net
+    for a, b in zip(*got):
+        assert (a == b).all()
