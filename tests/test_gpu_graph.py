@@ -4,7 +4,7 @@ import numpy as np
 import pytest
 import torch
 
-from gpu_common import KEY, both_partitions, hub_graph
+from gpu_common import KEY, both_partitions, hub_graph, products_taken
 from paper_2406_17611_amd import synth
 from paper_2406_17611_amd.runner import PartitionedNetwork
 
@@ -31,8 +31,9 @@ def _snapshot(net):
 def test_graph_replays_equal_eager_steps(n_streams):
     g = hub_graph(5000, 3, 1200, 7.0, "sage", seed=15)       # includes rows split over wavefronts (fix-up launches)
     part = synth.random_partition(g.n, 4, seed=16)
-    widths, ratio, first = (64, 128, 128, 16), (4, 1), 100
+    widths, ratio, first = (64, 160, 128, 16), (4, 1), 100
     eager = _network(g, part, 4, widths, "sage", n_streams)
+    assert products_taken(eager.ctx, lambda: eager.step(first, ratio))
     want = []
     for t in range(first + 1, first + 4):
         eager.zero_grads()
@@ -64,9 +65,10 @@ def test_graph_replays_with_the_class_layer_transforming_first():
     # table like every other hashing kernel, so replays follow the steps
     g = hub_graph(5000, 3, 1200, 7.0, "gcn", seed=25)
     part = synth.random_partition(g.n, 4, seed=26)
-    widths, ratio, first = (64, 128, 128, 16), (4, 1), 40
+    widths, ratio, first = (64, 400, 128, 16), (4, 1), 40
     kw = dict(dtype="bf16", transform_first=(2,))
     eager = _network(g, part, 4, widths, "gcn", 1, **kw)
+    assert products_taken(eager.ctx, lambda: eager.step(first, ratio))
     want = []
     for t in range(first + 1, first + 4):
         eager.zero_grads()

@@ -4,7 +4,7 @@ import numpy as np
 import pytest
 import torch
 
-from gpu_common import KEY, TOL, assert_close, both_partitions
+from gpu_common import KEY, TOL, assert_close, both_partitions, products_taken
 from oracle import ktap as oktap
 from oracle import layer as olayer
 from oracle import mask as omask
@@ -29,9 +29,9 @@ def test_ktap_network(n_taps, ratio, dtype):
     g = synth.small_random_graph(2500, 9.0, "sage", seed=70 + n_taps)
     part = synth.random_partition(g.n, 3, seed=71)
     host, orc = both_partitions(g, part, 3)
-    widths = (64, 128, 24)
-    L = 2
     bf16 = dtype == "bf16"
+    widths = (64, 400 if bf16 else 160, 24)           # rows long enough for products
+    L = 2
     # bf16: the sum of K products is rounded after every product, each hop's aggregate once more
     tol = 2.0 ** -6 if bf16 else TOL
     x0 = synth.features(g.n, widths[0], synth.SEED_FEAT)
@@ -63,8 +63,8 @@ def test_ktap_network(n_taps, ratio, dtype):
         net.x[l + 1].copy_(torch.from_numpy(stored(np.vstack(ref["x"][l + 1]))))
         for hop in range(1, n_taps):
             net.y[l][hop].copy_(torch.from_numpy(stored(np.vstack(ref["y"][l][hop]))))
-    net.backward()
-    torch.cuda.synchronize()
+    # (the hop of the last tap may sum the errors of the narrow outputs instead, the others don't)
+    assert products_taken(net.ctx, net.backward) or not net.linked or n_taps < 3 or not ratio[0] > 3 * ratio[1] > 0
     for l in range(L):
         for hop in range(n_taps):
             assert_close(net.dh[l][hop].cpu().numpy(), ref["dh"][l][hop], f"dH_{l},{hop}", tol)

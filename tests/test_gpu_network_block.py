@@ -19,7 +19,7 @@ pytestmark = pytest.mark.gpu
 def test_node_sums_with_hubs(conv, widths, dtype):
     g = hub_graph(1500, 3, 1100, 6.0, conv, seed=81)
     part = synth.random_partition(g.n, 3, seed=82)
-    # 1/8 and 1/5 (ragged k) of a row: products; 2/3: whole rows masked; all; nothing
+    # 1/8 and 1/5 (ragged k) of a row: products, where a row is long enough (256 and 516 fp32 columns), or masked; 2/3: whole rows masked; all; nothing
     ratios = [(8, 1), (5, 1), (3, 2), (1, 1), (1, 0)]
     _compare_network(g, part, 3, conv, widths, ratios, steps=list(range(5)), tol=BF16_TOL if dtype == "bf16" else 1e-4, dtype=dtype)
 

@@ -4,7 +4,7 @@ import numpy as np
 import pytest
 import torch
 
-from gpu_common import hub_graph
+from gpu_common import hub_graph, products_taken
 from paper_2406_17611_amd import synth
 from test_gpu_graph import _network, _snapshot
 
@@ -20,9 +20,8 @@ def test_product_buffer_grows_in_few_steps():
         ctx.set_step(step)
         ctx.set_ratio(-1, 16 * steps - 15 * step, steps)           # 16 -> 1, as an exact rational
         sizes.append(torch.cuda.mem_get_info()[0])
-    # k from 16 to 85 takes the product form, in rows of 16, 20, ... 88 values (at least 18 MB apart); beyond, the calls per
-    # partition ask for (halo entries of the largest partition, fewer than half of all) x k, up to 255. Growing by a quarter, that is
-    # 1 + log(128 / 16) / log(1.25) = 10 allocations at most, against 18 for the product form alone
+    # k from 16 to 85 takes the product form, in rows of 16, 32, ... 96 values; beyond, the calls per partition ask for (halo entries of the largest
+    # partition, fewer than half of all) x k, up to 255. Growing by a quarter, that is 1 + log(128 / 16) / log(1.25) = 10 allocations at most
     changes = sum(a != b for a, b in zip(sizes, sizes[1:]))
     assert 1 <= changes <= 1 + int(np.log(128 / 16) / np.log(1.25)), changes
 
@@ -31,14 +30,14 @@ def test_product_buffer_grows_in_few_steps():
 def test_graphs_of_a_rising_schedule_keep_replaying(dtype):
     g = hub_graph(5000, 3, 1200, 7.0, "gcn", seed=35)
     part = synth.random_partition(g.n, 4, seed=36)
-    widths, first = (64, 128, 128, 16), 70
+    widths, first = (64, 400 if dtype == "bf16" else 160, 128, 16), 70           # rows long enough for products
     ratios = [(32, 1), (16, 1), (12, 1), (8, 1), (6, 1), (5, 1), (4, 1), (7, 2), (2, 1), (1, 1)]     # more than a context has streams
     kw = dict(dtype=dtype)
     eager = _network(g, part, 4, widths, "gcn", 1, **kw)
     want = []
     for ratio in ratios:
         eager.zero_grads()
-        eager.step(first + 1, ratio)
+        assert products_taken(eager.ctx, lambda: eager.step(first + 1, ratio)) is (ratio[0] > 3 * ratio[1])
         want.append(_snapshot(eager))
     eager.ctx.close()
     net = _network(g, part, 4, widths, "gcn", 1, **kw)
