@@ -11,7 +11,9 @@
 //             per entry at the rate of a copy;
 //   masked    the whole rows dM[i, :] are gathered and everything outside the kept positions is dropped once, from the
 //             sum: width elements of traffic per entry at the rate of a gather, no buffer. The better form when k is more
-//             than about a third of the width (a gather moves 7 TB/s on this device, write + read back 4.8 TB/s).
+//             than about a third of the width (a gather moves 7 TB/s on this device, write + read back 4.8 TB/s), and
+//             for rows of at most 320 to 768 bytes whatever k is: a product costs its place in memory however short it is
+//             (products_pay).
 // Against the per-partition calls this saves the per-consumer rows (written and read), one read-modify-write of every
 // gradient row and, for the sums over short consumer lists (a few entries per halo row on fine partitions), most of the
 // fixed cost per row; all partitions share one launch.
@@ -86,7 +88,7 @@ __device__ __forceinline__ void clear(float (&acc)[NR][VEC]) {
 
 // Sum of the rows [c0, c1) of `src` (pitch `pitch` elements of type S), elements j0 .. j0 + EV - 1 of every row; lane
 // groups take different rows, six rows of a group in flight (fewer at the end of the range); the groups' sums are added at the
-// end, so that every lane of position jl holds the total.
+// end, so that the lanes of the first group (sub = 0) hold the totals, and no others.
 template <typename S, int EV>
 __device__ __forceinline__ void sum_rows(const S* src, int64_t pitch, int32_t c0, int32_t c1, int j0, bool on, int sub, int n_sub,
                                          int lpe_log2, float (&acc)[EV]) {

@@ -89,7 +89,7 @@ struct SpmmArgs {
     int32_t row_base;
     float* partial;           // partial sums of split rows stay in fp32
     int32_t lpr_log2;         // lanes per dense row = 1 << lpr_log2
-    int32_t ku;               // loads per compressed row = k / ev
+    int32_t ku;               // loads per compressed row: k / ev, rounded up (the last one overlaps the one before)
     int32_t lpe_log2;         // lanes that share one compressed row = 1 << lpe_log2 (>= min(ku, 64))
     int32_t epi;              // compressed rows handled per instruction = private LDS rows per wavefront
     // kOwner: the messages themselves, written by the workgroups from `copy_block` to `prep_block` (see owner_messages)
@@ -1062,10 +1062,9 @@ hipError_t spmm_t(const SpmmPlan& plan, const VarcoEdge* edge, const int32_t* co
     const int vec = sizeof(T) == 2 && width > 256 && vec_ok(8) ? 8 : vec4 ? 4 : sizeof(T) == 2 ? (width < 4 ? 1 : 4) : width <= 64 ? 1 : width <= 128 ? 2 : 4;
     // Rows whose length is no multiple of 4, or whose base is not aligned, are loaded from any address of an element as well. fp32: as many
     // elements to a load as let a row take all lanes with one load (two above 256 elements). One row after the other is added up, so the bits
-    // are those of loads of one element, and a ReLU whose argument is within rounding of zero decides alike. bf16: four, and narrow rows in groups of
-    // lanes as aligned ones. One element to a load / this, us: fp32 116,187 nodes 147 wide 110 / 78, 265,139 nodes 209 wide, 105 kept, 276 / 218,
-    // 771,643 nodes 94 wide 444 / 398, 50,021 nodes 75 wide 49 / 45; bf16 (with the messages below) 35,999 nodes 221 wide 73 / 49, 819,353 nodes
-    // 135 wide 524 / 465, 52,727 nodes 121 wide 53 / 44.
+    // are those of loads of one element. bf16: four, and narrow rows in groups of lanes as aligned ones. One element to a load / this, us: fp32 116,187
+    // nodes 147 wide 110 / 78, 265,139 nodes 209 wide, 105 kept, 276 / 218, 771,643 nodes 94 wide 444 / 398, 50,021 nodes 75 wide 49 / 45; bf16 (with the
+    // messages below) 35,999 nodes 221 wide 73 / 49, 819,353 nodes 135 wide 524 / 465, 52,727 nodes 121 wide 53 / 44.
     const bool any = !vec4 && vec > 1;
     const int per_row = (width + vec - 1) / vec;   // loads of VEC elements that cover a row
     int lpr_log2 = 0;
@@ -1102,9 +1101,10 @@ hipError_t spmm_t(const SpmmPlan& plan, const VarcoEdge* edge, const int32_t* co
         }
     }
     // Numbers of kept elements that are no multiple of that (or rows at other addresses): two or four per lane only where an entry takes all lanes either
-    // way (65 elements and more), so that the entries that share a private row, and with it the bits, stay. bf16 rows of odd lengths, whose dense sums
-    // have an order of their own here: as above. One per lane / this, us: 50,021 nodes 200 fp32 columns, 67 kept, 107 / 76. (For all bf16 rows: 2,449,029
-    // nodes of 100 columns, 25 kept, 3,544 / 3,076, but one rounding that falls otherwise decides gates of the layers behind it.)
+    // way (65 elements and more), so that as many entries share a private row, and the sums are those of an aligned message of that many loads. (With one
+    // element per lane such an entry takes two passes, its last elements behind the first of the 64 entries around it: the same sums in another order.)
+    // bf16 rows of odd lengths: as above. One per lane / this, us: 50,021 nodes 200 fp32 columns, 67 kept, 107 / 76.
+    // (Not taken for aligned bf16 rows of at most 64 kept elements, which would share private rows otherwise.)
     bool rem = false;
     if (halo && !full && !owners && vec > 1) {
         const int k = int(rule.k);
