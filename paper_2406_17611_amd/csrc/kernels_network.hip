@@ -292,13 +292,8 @@ hipError_t node_sum_t(const NodePlan& plan, const uint2* t_local, const uint2* t
     while (nv && nv * 64 < per_row) nv <<= 1;
     if (nv > 8) return hipErrorInvalidValue;
     a.pitch = pitch;
-    int ev = 1;
-    if (cross == kCrossProducts)
-        for (int c : {int(16 / sizeof(T)), int(8 / sizeof(T)), 2})
-            if (a.pitch % c == 0 && aligned_to(prod, c * sizeof(T))) {
-                ev = c;
-                break;
-            }
+    constexpr int ev = 16 / sizeof(T);
+    if (cross == kCrossProducts && (a.pitch % ev != 0 || !aligned_to(prod, 16) || width * int(sizeof(T)) <= product_row_bytes(sizeof(T)))) return hipErrorInvalidValue;
     a.ku = (int32_t(rule.k) + ev - 1) / ev;
     a.lpe_log2 = 0;
     while ((1 << a.lpe_log2) < a.ku && a.lpe_log2 < 6) ++a.lpe_log2;
@@ -327,17 +322,9 @@ hipError_t node_sum_t(const NodePlan& plan, const uint2* t_local, const uint2* t
             case kCrossMasked: launch(vec, nvc, Int<kCrossMasked>{}, Int<1>{}); break;
             case kCrossFull: launch(vec, nvc, Int<kCrossFull>{}, Int<1>{}); break;
             default:
-                if constexpr (sizeof(T) == 2)
-                    if (ev == 8) {
-                        launch(vec, nvc, Int<kCrossProducts>{}, Int<8>{});
-                        break;
-                    }
-                if (ev == 4)
-                    launch(vec, nvc, Int<kCrossProducts>{}, Int<4>{});
-                else if (ev == 2)
-                    launch(vec, nvc, Int<kCrossProducts>{}, Int<2>{});
-                else
-                    launch(vec, nvc, Int<kCrossProducts>{}, Int<1>{});
+                // (loads of this kind that cover only rows too short for products: never asked for)
+                if constexpr ((decltype(nvc)::value > 0 ? 64 * decltype(nvc)::value : 32) * decltype(vec)::value * int(sizeof(T)) > product_row_bytes(sizeof(T)))
+                    launch(vec, nvc, Int<kCrossProducts>{}, Int<ev>{});
         }
     };
     auto with_nv = [&](auto vec) {

@@ -213,8 +213,11 @@ inline int32_t varco_product_pitch(const MaskRule& rule, int elem_bytes, bool wh
 hipError_t varco_launch_halo_products(int dtype, const SpmmPlan& fwd_plan, const VarcoEdge* edge, const float* vals, const int32_t* prow,
                                       const void* dm, const MaskRule& rule, void* prod, int32_t pitch, hipStream_t stream, const LaunchTag& tag);
 
+// Bytes of a row above which products may be formed (products_pay draws the lines, from here on); there are no kernels for the products of shorter ones.
+constexpr int product_row_bytes(int elem_bytes) { return elem_bytes == 2 ? 512 : 320; }
+
 // How the cross entries of varco_launch_node_sum are taken: not at all (k = 0); summed from the product buffer (rows of
-// `pitch` elements, already weighted); gathered as whole rows of dm and kept only at the node's positions; gathered as whole rows (k = width).
+// `pitch` elements, whole 16-byte pieces, already weighted; for rows of more than product_row_bytes); gathered as whole rows of dm and kept only at the node's positions; gathered as whole rows (k = width).
 enum VarcoCross { kCrossNone = 0, kCrossProducts = 1, kCrossMasked = 2, kCrossFull = 3 };
 // out[row, :] (+)= sum of local entries + cross entries for every node of the plan (see NodeItem). partial: one
 // width-float row per piece.

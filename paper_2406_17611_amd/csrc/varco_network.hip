@@ -49,7 +49,7 @@ int32_t product_pitch(const varco_ctx* ctx, int32_t layer, int64_t k, bool whole
 bool products_pay(const varco_ctx* ctx, int32_t layer, int64_t k) {
     const bool bf16 = ctx->dtype == VARCO_BF16, few = ctx->net.nnz_cross <= 16 * ctx->net.rows;
     const bool odd = ctx->widths[layer] % 4 != 0;
-    const int32_t gathered = bf16 ? (odd ? 512 : few ? 768 : 640) : (few ? 512 : odd ? 320 : 384);        // bytes of a row
+    const int32_t gathered = odd && (bf16 || !few) ? product_row_bytes(ctx->elem_bytes()) : bf16 ? (few ? 768 : 640) : (few ? 512 : 384);
     return k > 0 && 3 * k < ctx->widths[layer] && ctx->widths[layer] * ctx->elem_bytes() > gathered &&
            double(ctx->net.nnz_cross) * product_pitch(ctx, layer, k, false) * ctx->elem_bytes() <= kProdBytes;
 }

@@ -20,7 +20,8 @@ def _check(dtype, width, kept, degree, products=None):
 
 
 @pytest.mark.parametrize("dtype,width,kept", [("f32", 132, 4), ("f32", 136, 5), ("f32", 148, 8), ("f32", 150, 9), ("f32", 160, 16), ("f32", 200, 17), ("f32", 256, 33),
-                                              ("f32", 300, 67), ("bf16", 392, 8), ("bf16", 392, 9), ("bf16", 400, 16), ("bf16", 404, 17), ("bf16", 512, 32), ("bf16", 512, 33)])
+                                              ("f32", 299, 20), ("f32", 300, 67), ("f32", 516, 21), ("f32", 1028, 33), ("bf16", 392, 8), ("bf16", 392, 9), ("bf16", 400, 16), ("bf16", 404, 17), ("bf16", 512, 32), ("bf16", 512, 33), ("bf16", 516, 20), ("bf16", 520, 20),
+                                              ("bf16", 1028, 40), ("bf16", 1032, 40)])
 def test_products_of_any_length(dtype, width, kept):
     _check(dtype, width, kept, 6.0, True)
 
