@@ -185,28 +185,33 @@ __device__ __forceinline__ void add_lanes(float (&x)[N], int log2, int lanes = 6
     };
     using std::integral_constant;
     using All = integral_constant<int, 0xF>;
-    if (log2 <= 0 && lanes > 1)
+    // (nested: a wide row, whose few groups take the last steps only, passes one test)
+    if (log2 <= 4) {
+        if (log2 <= 2) {
+            if (log2 <= 0 && lanes > 1)
 #pragma unroll
-        for (int i = 0; i < N; ++i) x[i] += moved(x[i], integral_constant<int, 0xB1>{}, All{});        // quad_perm 1 0 3 2
-    if (log2 <= 1 && lanes > 2)
+                for (int i = 0; i < N; ++i) x[i] += moved(x[i], integral_constant<int, 0xB1>{}, All{});        // quad_perm 1 0 3 2
+            if (log2 <= 1 && lanes > 2)
 #pragma unroll
-        for (int i = 0; i < N; ++i) x[i] += moved(x[i], integral_constant<int, 0x4E>{}, All{});        // quad_perm 2 3 0 1
-    if (log2 <= 2 && lanes > 4)
+                for (int i = 0; i < N; ++i) x[i] += moved(x[i], integral_constant<int, 0x4E>{}, All{});        // quad_perm 2 3 0 1
+            if (lanes > 4)
 #pragma unroll
-        for (int i = 0; i < N; ++i) {
-            const float up = moved(x[i], integral_constant<int, 0x104>{}, integral_constant<int, 0x5>{});      // lanes 0-3 and 8-11 from four lanes above,
-            const int u = __builtin_bit_cast(int, x[i]);                                                       // the others from four below
-            x[i] += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, up), u, 0x114, 0xF, 0xA, false));
+                for (int i = 0; i < N; ++i) {
+                    const float up = moved(x[i], integral_constant<int, 0x104>{}, integral_constant<int, 0x5>{});      // lanes 0-3 and 8-11 from four lanes
+                    const int u = __builtin_bit_cast(int, x[i]);                                                       // above, the others from four below
+                    x[i] += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, up), u, 0x114, 0xF, 0xA, false));
+                }
         }
-    if (log2 <= 3 && lanes > 8)
+        if (log2 <= 3 && lanes > 8)
 #pragma unroll
-        for (int i = 0; i < N; ++i) x[i] += moved(x[i], integral_constant<int, 0x128>{}, All{});       // row_ror 8
-    if (log2 <= 4 && lanes > 16)
+            for (int i = 0; i < N; ++i) x[i] += moved(x[i], integral_constant<int, 0x128>{}, All{});       // row_ror 8
+        if (lanes > 16)
 #pragma unroll
-        for (int i = 0; i < N; ++i) {
-            const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x[i]), __float_as_uint(x[i]), false, false);
-            x[i] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
-        }
+            for (int i = 0; i < N; ++i) {
+                const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x[i]), __float_as_uint(x[i]), false, false);
+                x[i] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+            }
+    }
     if (log2 <= 5 && lanes > 32)
 #pragma unroll
         for (int i = 0; i < N; ++i) {
