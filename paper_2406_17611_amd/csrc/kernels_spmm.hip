@@ -1004,10 +1004,10 @@ hipError_t launch_spmm_nv(int nv, const SpmmArgs<T>& a, dim3 grid, size_t lds_by
             if constexpr (VEC < 8 && !(ANY && sizeof(T) == 4)) return go(std::integral_constant<int, 0>{});
             break;
         case 1:
-            if constexpr (VEC > 1 || sizeof(T) == 4) return go(std::integral_constant<int, 1>{});
+            if constexpr (VEC > 1 || sizeof(T) == 4 || MODE >= kSparse) return go(std::integral_constant<int, 1>{});
             break;
         case 2:
-            if constexpr (VEC >= 4) return go(std::integral_constant<int, 2>{});
+            if constexpr (VEC >= 4 || (VEC == 1 && sizeof(T) == 2 && MODE >= kSparse)) return go(std::integral_constant<int, 2>{});
             break;
         case 4:
             if constexpr (VEC >= 4 && !ANY) return go(std::integral_constant<int, 4>{});
@@ -1059,7 +1059,13 @@ hipError_t spmm_t(const SpmmPlan& plan, const VarcoEdge* edge, const int32_t* co
     const bool vec4 = vec_ok(4);
     // bf16: 16-byte loads where a row then still takes all lanes. (Narrower rows would have twice as many lane groups, and the
     // forward sums another order.)
-    const int vec = sizeof(T) == 2 && width > 256 && vec_ok(8) ? 8 : vec4 ? 4 : sizeof(T) == 2 ? (width < 4 ? 1 : 4) : width <= 64 ? 1 : width <= 128 ? 2 : 4;
+    // Compressed messages beside bf16 rows of at most 128 elements that are not aligned: one element to a load, in small launches up to 64. (With four, up
+    // to 64 private rows are added up four columns to a lane. One / four, us, 400,003 nodes of 10 neighbours: 5 wide, no messages, 167 / 368, 13 wide, 5 kept,
+    // 164 / 244, 63 wide, 8 kept, 164 / 212, 75 wide, 25 kept, 203 / 231, 127 wide, 16 kept, 208 / 231, but 135 wide, 17 kept, 278 / 231, and 20,011 nodes 13
+    // wide, 5 kept, 15.0 / 20.8, 63 wide, 8 kept, 18.1 / 19.4, 75 wide, 9 kept, 22.2 / 19.8, 127 wide, 43 kept, 34 / 27. Whole messages, 400,003 nodes: 13
+    // wide 130 / 111, 127 wide 252 / 217.)
+    const bool narrow = sizeof(T) == 2 && !vec4 && (width < 4 || (halo && !full && (width <= 64 || (width <= 128 && plan.n_items > 65'536))));
+    const int vec = sizeof(T) == 2 && width > 256 && vec_ok(8) ? 8 : vec4 ? 4 : narrow ? 1 : sizeof(T) == 2 ? 4 : width <= 64 ? 1 : width <= 128 ? 2 : 4;
     // Rows whose length is no multiple of 4, or whose base is not aligned, are loaded from any address of an element as well. fp32: as many
     // elements to a load as let a row take all lanes with one load (two above 256 elements). One row after the other is added up, so the bits
     // are those of loads of one element. bf16: four, and narrow rows in groups of lanes as aligned ones. One element to a load / this, us: fp32 116,187

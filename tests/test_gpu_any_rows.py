@@ -60,6 +60,14 @@ def _rows(width, dtype, seed):
     return host, torch.randn(g.n, width, generator=gen, device="cuda").to(torch.bfloat16 if dtype == "bf16" else torch.float32)
 
 
+@pytest.mark.parametrize("width", [1, 2, 3, 5, 7, 9, 13, 17, 25, 33, 47, 63, 126, 127, 129])
+def test_narrow_bf16_rows_of_any_length(width):
+    """One element to a load beside compressed messages, up to 64 private rows; four beside whole ones."""
+    g = hub_graph(420, 3, 300, 5.0, "gcn", seed=width)
+    part = synth.random_partition(g.n, 3, seed=92)
+    _compare_network(g, part, 3, "gcn", (width, 6), [(3, 1), (8, 1), (1, 0), (1, 1)], steps=[0, 1, 2, 3], tol=BF16_TOL, dtype="bf16")
+
+
 @pytest.mark.parametrize("width,shift", [(65, 0), (66, 0), (75, 0), (100, 1), (127, 0), (128, 3), (130, 0), (147, 0), (209, 0), (255, 0), (256, 1), (257, 0), (330, 0), (511, 0)])
 @pytest.mark.parametrize("whole", [True, False])
 def test_bits_do_not_depend_on_the_width(width, shift, whole):
@@ -73,9 +81,10 @@ def test_bits_do_not_depend_on_the_width(width, shift, whole):
             assert _same_bits(got[:, c0:c1], _aggregate(host, y[:, c0:c1].contiguous(), c1 - c0 if whole else 0, "f32")), c0
 
 
-@pytest.mark.parametrize("width,dtype", [(132, "f32"), (256, "f32"), (260, "f32"), (512, "f32"), (20, "bf16"), (100, "bf16"), (132, "bf16"), (260, "bf16")])
-@pytest.mark.parametrize("whole", [True, False])
+@pytest.mark.parametrize("width,dtype,whole", [(132, "f32", True), (132, "f32", False), (256, "f32", True), (260, "f32", False), (512, "f32", True), (512, "f32", False),
+                                               (20, "bf16", True), (100, "bf16", True), (132, "bf16", True), (132, "bf16", False), (260, "bf16", False)])
 def test_bits_do_not_depend_on_the_address(width, dtype, whole):
+    """(bf16 rows of at most 128 elements beside compressed messages take one element to a load there, in another order.)"""
     host, y = _rows(width, dtype, width)
     aligned, shifted = (_aggregate(host, y, width if whole else 0, dtype, shift, shift) for shift in (0, 1))
     assert _same_bits(aligned, shifted)
