@@ -292,8 +292,8 @@ bool varco_gemm_bf16_usable(const GemmArgs& ga) {
     if (ga.bf16_terms == kExactTerms) {
         // Rows of any length from 8 on, at any address of an element; weights that are not rounded, three products of each. fp32 instructions on
         // tiles of 128 x 128 (256 x 64) in stages of 16 steps / this, us: 819,353 rows two taps 135 -> 40 363 / 175, 911,699 rows 227 -> 40 added to C
-        // 345 / 178, 323,741 rows 79 -> 272 239 / 138, 52,727 rows two taps 121 -> 168 93 / 36, 35,999 rows 221 -> 56 40 / 16. (Shorter rows, and
-        // rows of 4 elements, keep the fp32 instructions.)
+        // 345 / 178, 323,741 rows 79 -> 272 239 / 138, 52,727 rows two taps 121 -> 168 93 / 36, 35,999 rows 221 -> 56 40 / 16. (Rows of at
+        // most 16 elements, and of at most 32 for some outputs, keep the fp32 instructions: exact_terms.)
         auto ok3 = [&](const GemmOperand& o, const void* prep, int64_t pitch, int32_t k) {
             return o.dtype == VARCO_BF16 && !o.transposed && !o.gate && prep && aligned_to(prep, 16) && k >= 8 && pitch == (int64_t(k) + 31) / 32 * 32;
         };

@@ -255,7 +255,11 @@ int32_t ensure_tables(varco_ctx* ctx) {
     return VARCO_OK;
 }
 
-static bool exact_terms(int32_t fi, bool transpose) { return transpose && fi % 4 != 0 && fi >= 8; }
+// bf16 storage, the transform of rows whose length is no multiple of 4: weights in three exact terms (varco_gemm_bf16_usable), where that is faster than fp32
+// instructions. Stages are of 64 steps, and rows of C that are not whole 16-byte pieces are stored element by element. fp32 instructions / this, us: 300,007
+// rows 9 -> 47 24 / 32, 130 60 / 88, 256 59 / 60, 17 -> 1 24 / 28, 31 -> 130 83 / 88, but 17 -> 40 30 / 23, 31 -> 256 84 / 60, 33 -> 1 32 / 28, 130 107 / 88,
+// 3,000 rows 9 -> 130 7.8 / 9.6, 33 -> 256 11.2 / 6.5.
+static bool exact_terms(int32_t fi, int32_t fo, bool transpose) { return transpose && fi % 4 != 0 && (fi > 32 || (fi > 16 && fo % 8 == 0)); }
 
 // Copy of a weight matrix in the form the bf16 matrix-core kernels take (B or B2 of `g`): rows = the product's
 // output index, pitch padded; bf16 storage: one rounded copy, or three terms (exact_terms); fp32 storage: the terms of the exact bf16
@@ -268,7 +272,7 @@ bool prep_slot(varco_ctx* ctx, Workspace& ws, int32_t layer, const void* h, int3
     const bool bf16 = ctx->dtype == VARCO_BF16;
     if (!bf16 && ctx->f32_terms == 0) return false;
     // Rows of a length that is no multiple of 4 meet weights that are not rounded (varco_gemm_bf16_usable).
-    const bool exact = bf16 && exact_terms(fi, transpose), plain = bf16 && !exact;
+    const bool exact = bf16 && exact_terms(fi, fo, transpose), plain = bf16 && !exact;
     const int32_t terms = exact ? kExactTerms : bf16 ? 1 : transpose ? ctx->f32_terms : kHalfTerms;      // the transform reads H^T, the input gradient H
     const int32_t rows = transpose ? fo : fi, cols = transpose ? fi : fo;
     const int32_t p = plain ? pad8(cols) : pad_to(cols, 32);
@@ -507,7 +511,7 @@ extern "C" int32_t varco_create(const varco_config* cfg, varco_ctx** out) {
         size_t total = 0;
         for (int32_t l = 0; l < ctx->n_layers; ++l) {
             const int32_t fi = ctx->widths[l], fo = ctx->widths[l + 1];
-            const size_t fwd = bf16 && !exact_terms(fi, true) ? size_t(fo) * pad8(fi) : size_t(3) * pad_to(fo, 128) * pad_to(fi, 32);
+            const size_t fwd = bf16 && !exact_terms(fi, fo, true) ? size_t(fo) * pad8(fi) : size_t(3) * pad_to(fo, 128) * pad_to(fi, 32);
             const size_t bwd = bf16 ? size_t(fi) * pad8(fo) : size_t(3) * pad_to(fi, 128) * pad_to(fo, 32);
             for (int which = 0; which < kWeightSlots; ++which)
                 for (size_t sz : {fwd, bwd}) {

@@ -1,4 +1,4 @@
-"""The transform of bf16 rows whose length is no multiple of 4, by weights in three exact bf16 terms: stages of 32 steps, pieces of eight that cross the end of
+"""The transform of bf16 rows whose length is no multiple of 4, by weights in three exact bf16 terms (the shortest rows by fp32 instructions): stages of 32 steps, pieces of eight that cross the end of
 a row, tiles of 256 x 64 and 128 x 128, columns padded to whole tiles."""
 import numpy as np
 import pytest
@@ -19,7 +19,7 @@ def _weights(rng, fi, fo):
     return h
 
 
-@pytest.mark.parametrize("fi,fo", [(9, 1), (17, 33), (31, 64), (33, 65), (63, 8), (65, 128), (70, 129), (127, 256), (129, 40), (135, 200), (226, 72), (257, 47), (511, 130)])
+@pytest.mark.parametrize("fi,fo", [(9, 1), (17, 8), (17, 33), (25, 40), (31, 64), (31, 136), (33, 1), (33, 65), (63, 8), (65, 128), (70, 129), (127, 256), (129, 40), (135, 200), (226, 72), (257, 47), (511, 130)])
 @pytest.mark.parametrize("n", [1, 127, 129, 257, 3001])
 def test_transform(n, fi, fo):
     """Weights are not rounded: a result is the fp64 one to half a unit of bf16 and the rounding of fp32 sums. Added to what is there, from any
@@ -48,7 +48,7 @@ def test_transform(n, fi, fo):
     ctx.close()
 
 
-@pytest.mark.parametrize("fi,fo", [(9, 7), (75, 70), (130, 129)])
+@pytest.mark.parametrize("fi,fo", [(9, 7), (17, 8), (33, 7), (75, 70), (130, 129)])
 def test_small_weights(fi, fo):
     """Weights down to the smallest fp32 number, one scale to a column, against rows large enough that the products are not small. The terms add up to
     what is 2^-109 or more; below, a weight is off by 2^-131 at most (bits under the smallest bf16 number, which stands in for zero terms too)."""
