@@ -293,7 +293,7 @@ hipError_t node_sum_t(const NodePlan& plan, const uint2* t_local, const uint2* t
     if (nv > 8) return hipErrorInvalidValue;
     a.pitch = pitch;
     constexpr int ev = 16 / sizeof(T);
-    if (cross == kCrossProducts && (a.pitch % ev != 0 || !aligned_to(prod, 16) || width * int(sizeof(T)) <= product_row_bytes(sizeof(T)))) return hipErrorInvalidValue;
+    if (cross == kCrossProducts && (a.pitch % ev != 0 || !aligned_to(prod, 16) || width * int(sizeof(T)) <= kProductRowBytes)) return hipErrorInvalidValue;
     a.ku = (int32_t(rule.k) + ev - 1) / ev;
     a.lpe_log2 = 0;
     while ((1 << a.lpe_log2) < a.ku && a.lpe_log2 < 6) ++a.lpe_log2;
@@ -323,7 +323,7 @@ hipError_t node_sum_t(const NodePlan& plan, const uint2* t_local, const uint2* t
             case kCrossFull: launch(vec, nvc, Int<kCrossFull>{}, Int<1>{}); break;
             default:
                 // (loads of this kind that cover only rows too short for products: never asked for)
-                if constexpr ((decltype(nvc)::value > 0 ? 64 * decltype(nvc)::value : 32) * decltype(vec)::value * int(sizeof(T)) > product_row_bytes(sizeof(T)))
+                if constexpr ((decltype(nvc)::value > 0 ? 64 * decltype(nvc)::value : 32) * decltype(vec)::value * int(sizeof(T)) > kProductRowBytes)
                     launch(vec, nvc, Int<kCrossProducts>{}, Int<ev>{});
         }
     };

@@ -214,10 +214,10 @@ hipError_t varco_launch_halo_products(int dtype, const SpmmPlan& fwd_plan, const
                                       const void* dm, const MaskRule& rule, void* prod, int32_t pitch, hipStream_t stream, const LaunchTag& tag);
 
 // Bytes of a row above which products may be formed (products_pay draws the lines, from here on); there are no kernels for the products of shorter ones.
-constexpr int product_row_bytes(int elem_bytes) { return elem_bytes == 2 ? 512 : 320; }
+constexpr int kProductRowBytes = 320;
 
 // How the cross entries of varco_launch_node_sum are taken: not at all (k = 0); summed from the product buffer (rows of
-// `pitch` elements, whole 16-byte pieces, already weighted; for rows of more than product_row_bytes); gathered as whole rows of dm and kept only at the node's positions; gathered as whole rows (k = width).
+// `pitch` elements, whole 16-byte pieces, already weighted; for rows of more than kProductRowBytes); gathered as whole rows of dm and kept only at the node's positions; gathered as whole rows (k = width).
 enum VarcoCross { kCrossNone = 0, kCrossProducts = 1, kCrossMasked = 2, kCrossFull = 3 };
 // out[row, :] (+)= sum of local entries + cross entries for every node of the plan (see NodeItem). partial: one
 // width-float row per piece.

@@ -31,27 +31,39 @@ int32_t product_pitch(const varco_ctx* ctx, int32_t layer, int64_t k, bool whole
     return whole && double(ctx->net.nnz_cross) * pitch * ctx->elem_bytes() > kProdBytes ? varco_product_pitch(r, ctx->elem_bytes(), false) : pitch;
 }
 // A message's products go to a place of their own, at least 35 to 48 ps each however few they are, and are read back: rows below some length are gathered whole.
-// Whole steps with products / with gathered rows, us, 8 partitions, widths 32-w-72-8, ratios 4 and 32:
-//   60,011 nodes of 60 neighbours   fp32 64 wide 557 / 474, 525 / 426, 96 664 / 568, 567 / 518, 128 674 / 637, 586 / 581, 160 wide, ratio 32, 641 / 694
-//                                   bf16 256 804 / 679, 720 / 618, 320 1,070 / 870, 806 / 737, 384 1,079 / 932, 840 / 816
-//   400,003 nodes of 50             fp32 64 2,913 / 2,695, 2,948 / 2,403, 96 3,450 / 3,314, 3,139 / 2,911, 128 3,466 / 3,701, 3,261 / 3,377
-//                                   bf16 256 3,949 / 3,832, 4,097 / 3,532, 320 5,311 / 4,751, 4,465 / 4,083, 384, ratio 8, 4,710 / 4,922
-// and with few entries to a row, where the pass of its own that forms the products costs more per entry:
-//   800,011 nodes of 12             fp32 128 3,945 / 3,810, 3,978 / 3,734, 192, ratio 8, 4,521 / 4,691    bf16 384 5,333 / 4,865, 4,950 / 4,517, 512 level
-// Between them the line of 16 entries is on the safe side (200,003 nodes, ratios 4 and 32): of 24 neighbours fp32 128 1,264 / 1,235, 1,205 / 1,186, bf16 384
-// 1,863 / 1,670, 1,591 / 1,527; of 36 fp32 96 1,429 / 1,346, 1,340 / 1,232, 128 1,463 / 1,492, 1,408 / 1,409, bf16 320 2,220 / 1,924, 1,853 / 1,685.
+// Steps with products / with gathered rows in the hidden layer of widths 32-w-72-8, us, 8 partitions, ratios 4, 8, 16 and 32:
+// few entries to a row (at most 16):
+//   800,011 nodes of 12            f32 128 3,943/3,760 3,895/3,783 3,953/3,693 3,935/3,677, 160 4,579/4,342 4,298/4,286 4,137/4,189 4,274/4,163
+//                                 bf16 320 4,813/4,502 4,398/4,314 4,258/4,246 4,332/4,166, 384 4,991/4,796 4,571/4,597 4,435/4,527 4,538/4,459, 448
+//                                 5,319/5,203 4,809/5,001 4,673/4,925 4,771/4,861
+//   60,011 nodes of 12 neighbours  f32 128 412/370 398/372 374/365 370/362    bf16 384 544/485 494/462 476/448 456/452
+// more:
+//   60,011 nodes of 60             f32 96 659/567 583/541 594/509 571/501, 160 859/747 699/714 616/686 650/674    bf16 256 721/672 644/642 656/624
+//                                 631/602, 288 967/842 784/766 698/729 710/704, 384 1,003/917 801/841 728/807 741/801
+//   200,003 nodes of 24            bf16 256 1,318/1,261 1,228/1,224 1,250/1,192 1,204/1,169, 320 1,689/1,518 1,436/1,423 1,361/1,395 1,368/1,358
+//   83,480 nodes of 41             f32 96 719/658 645/627 655/603 628/602, 128 736/736 666/706 671/679 650/674    bf16 256 777/751 708/732 724/705
+//                                 688/698, 288 1,016/920 835/852 763/819 767/798
+// and rows that the last cache does not hold, as far as others are in use:
+//   400,003 nodes of 50            f32 96 3,435/3,321 3,027/3,110 3,211/2,946 3,100/2,890, 128 3,448/3,715 3,111/3,573 3,337/3,440 3,222/3,351
+//                                 bf16 192 3,597/3,434 3,240/3,279 3,446/3,148 3,344/3,058, 256 3,624/3,874 3,317/3,772 3,568/3,655 3,458/3,571, 288
+//                                 4,934/4,677 3,906/4,323 3,569/4,180 3,798/4,050, 320 4,949/4,748 3,943/4,376 3,596/4,252 3,840/4,136
+// (bf16: products of more than 128 bytes, ratio 4 from 288 columns on here, pay from a longer row on.)
 // Rows whose length is no multiple of 4 are gathered one element to a lane (node_sum_kernel), a product's row is read by wide loads whatever the width:
-// the lines lie lower. Ratios 4, 8 and 32:
-//   400,003 nodes of 50             fp32 75 3,505 / 3,438, 3,116 / 3,229, 3,166 / 2,980, 95 3,587 / 3,702, 3,210 / 3,525, 3,246 / 3,244
-//                                   bf16 251 4,624 / 4,702, 4,436 / 4,379, 4,468 / 4,166, 319 5,753 / 5,575, 5,101 / 5,296, 4,887 / 5,002
-//   200,003 nodes of 36             fp32 95 1,512 / 1,487, 1,390 / 1,436, 1,377 / 1,365    bf16 251 2,005 / 1,939, 1,928 / 1,835, 1,866 / 1,754
-//   60,011 nodes of 12              fp32 127 445 / 426, 429 / 414, 397 / 406               bf16 319 619 / 557, 563 / 556, 506 / 537
+//   60,011 nodes of 12 neighbours  f32 127 442/420 421/414 404/405 398/405    bf16 127 398/394 386/385 378/383 377/370, 191 462/457 429/445 415/438
+//                                 407/435
+//   83,480 nodes of 41             f32 79 737/694 670/664 679/640 654/631, 127 781/814 709/789 717/763 687/749    bf16 127 720/679 697/641 670/626
+//                                 652/617, 191 881/884 789/847 787/819 758/818
+//   400,003 nodes of 50            f32 79 3,496/3,462 3,106/3,266 3,249/3,085 3,155/3,001, 95 3,571/3,686 3,181/3,482 3,339/3,309 3,207/3,202    bf16
+//                                 127 3,331/3,334 3,515/3,204 3,381/3,101 3,313/3,041, 191 4,045/4,284 3,689/4,102 3,828/3,950 3,716/3,872
 bool products_pay(const varco_ctx* ctx, int32_t layer, int64_t k) {
+    const int32_t width = ctx->widths[layer], row = width * int32_t(ctx->elem_bytes());
     const bool bf16 = ctx->dtype == VARCO_BF16, few = ctx->net.nnz_cross <= 16 * ctx->net.rows;
-    const bool odd = ctx->widths[layer] % 4 != 0;
-    const int32_t gathered = odd && (bf16 || !few) ? product_row_bytes(ctx->elem_bytes()) : bf16 ? (few ? 768 : 640) : (few ? 512 : 384);
-    return k > 0 && 3 * k < ctx->widths[layer] && ctx->widths[layer] * ctx->elem_bytes() > gathered &&
-           double(ctx->net.nnz_cross) * product_pitch(ctx, layer, k, false) * ctx->elem_bytes() <= kProdBytes;
+    int32_t gathered = few ? 512 : 384;                      // bytes of a row up to which it is gathered
+    if (width % 4 != 0)
+        gathered = !bf16 && few ? 512 : kProductRowBytes;
+    else if (bf16)
+        gathered = few ? 768 : product_pitch(ctx, layer, k, true) > 64 ? 640 : ctx->net.rows * row > (int64_t(128) << 20) ? 448 : 512;
+    return k > 0 && 3 * k < width && row > gathered && double(ctx->net.nnz_cross) * product_pitch(ctx, layer, k, false) * ctx->elem_bytes() <= kProdBytes;
 }
 size_t prod_floats(const varco_ctx* ctx, int32_t layer, int64_t k, bool whole) {
     return (size_t(ctx->net.nnz_cross) * size_t(product_pitch(ctx, layer, k, whole)) * size_t(ctx->elem_bytes()) + 3) / 4;
