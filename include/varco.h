@@ -356,8 +356,9 @@ int32_t varco_accumulate_returned(varco_ctx* ctx, int32_t layer, int32_t p, cons
  * Device memory of the joined form, allocated by the library itself (a caller whose allocator takes all memory sets the
  * ratio first): 28 bytes per entry and up to 60 per node, in this call; per prepared stream, in varco_prepare, n_total
  * rows of the widest layer and the partial products of the weight gradients (1.3 GB for 512 x 512 bf16 weights over
- * 2.4 million nodes; 4 GiB per weight matrix or pair at most); and while 3 k < width[l] for an l > 0, in
- * varco_set_ratio, up to 1.25 k elements per entry of a halo column, 48 GiB at most; and for a class layer
+ * 2.4 million nodes; 4 GiB per weight matrix or pair at most); and while 3 k < width[l] for an l > 0 with rows
+ * longer than 320 to 768 bytes, in varco_set_ratio, up to 1.25 k elements per entry of a halo column, k rounded up to
+ * whole 16 bytes, or above 32 bytes to 64 where there is room for that, 48 GiB at most; and for a class layer
  * of at most 64 outputs (l > 0, identity activation, fewer outputs than inputs) 512 bytes per node and 256 per boundary row (bf16: 384
  * and 256) for its errors summed at the width of the outputs. The last two are optional: beyond that size,
  * or where they cannot be had, whole rows are gathered instead. With fp32 storage that changes the order of sums only; with
