@@ -7,9 +7,8 @@
 // A wavefront keeps 32 columns of the weights in registers, both taps', for all the rows that its workgroup walks over. Blocks of 32 rows come 16 lanes
 // to a row, from any 4-byte address, one block ahead in registers, and lie in LDS as [tile][row][16 steps], the 16-byte pieces of every fourth row
 // swapped so that fragments are read without a bank conflict. One LDS buffer, two barriers per block: the other workgroups of the compute unit
-// multiply meanwhile. Bound by the matrix units (two taps of 233 steps, 211,211 rows: 66 % busy at 2.3 GHz, 8 % vector instructions beside them, the rest
-// waits, one wavefront to a SIMD; up to 256 steps two or three: 0.8 of the 142 TFLOP/s that a chain of these instructions reaches from registers), in small
-// launches by one block's chain. gemm_kernel's tiles of 128 rows x 128 columns in stages of 16 steps / this, us:
+// multiply meanwhile. Bound by the matrix units (two taps of 233 steps -> 160, 211,211 rows: 51 % busy at 2.3 GHz with five of six wavefronts at work, 8 % vector
+// instructions beside them, the rest waits, one wavefront to a SIMD; up to 256 steps two or three), in small launches by one block's chain. gemm_kernel's tiles of 128 rows x 128 columns in stages of 16 steps / this, us:
 //   3,000 rows 218 -> 48 34.2 / 9.6, 130 -> 256 22.3 / 8.5, two taps 233 -> 160 59.9 / 16.5     20,000 rows two taps 55 -> 160 29.4 / 17.6
 //   50,021 rows two taps 75 -> 200 64 / 50     200,000 rows 218 -> 160 264 / 186, 130 -> 256 192 / 154, two taps 233 -> 256 533 / 508, 55 -> 256 173 / 142
 // and rows of aligned length: 3,000 rows 64 -> 128 12.0 / 6.1, 256 -> 256 29 / 11     50,021 rows 100 -> 256 45 / 33, two taps 128 -> 256 91 / 72
